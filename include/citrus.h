@@ -131,9 +131,8 @@ typedef struct {
   int32_t q_heads;        /* Hq, a multiple of kv_heads, <= 65535; and B*L*Hq*ceil(max(chunk_len, instr_len)/32)
                              < 2^28 (the largest launch: 8 workgroups per 32 rows of a head); else CITRUS_ERR_SHAPE */
   int32_t kv_heads;       /* Hkv                                             >= 1 */
-  int32_t head_dim;       /* d: 64 or 128.  The matrix-core (MFMA) kernels exist for bf16 with d = 128 only;
-                             bf16 with d = 64 and every f32 configuration run on plain vector kernels (one
-                             wavefront per query row), which are meant for tests and small shapes        */
+  int32_t head_dim;       /* d: 64 or 128.  bf16 runs on matrix-core (MFMA) kernels, f32 on plain vector kernels,
+                             which are meant for tests and small shapes                                   */
   int32_t chunk_len;      /* l_s: maximum chunk length c                     >= 1 */
   int32_t budget;         /* k: states kept in the (instruction) cache       >= 1 */
   int32_t budget_lm;      /* DUAL: budget of the language-modelling cache; else ignored */
@@ -186,7 +185,7 @@ int32_t citrus_abi_version(void);
  * lse_cache   optional (cache_len >= 1), dense [B, L, Hq, chunk_len] f32: the same
  *             over the cache states alone, i.e. the normaliser of Eq. (1) as
  *             printed; citrus_cache_score takes it.  A by-product of the bf16
- *             d=128 kernel when cache_len is a multiple of 32, else one more pass.
+ *             kernel when cache_len is a multiple of 32, else one more pass.
  * lm_score    optional, dense [B, L, Hkv, n] f32: chunk-scored importance,
  *             lm_score[b,l,g,j] = sum over heads h of group g and chunk rows t
  *             of the attention probability p[h,t,j] (0 where masked); Eq. (1)

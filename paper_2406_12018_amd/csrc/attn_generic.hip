@@ -1,7 +1,5 @@
-// Generic (vector-ALU) attention kernels for f32 and bf16 element types.
-//
-// These are the kernels of the f32 mode (tiny parity configuration) and the
-// fallback for bf16 shapes the MFMA kernels do not cover.  They follow the same
+// Vector-ALU attention kernels of the f32 mode (bf16 runs on the matrix-core kernels for every head
+// dimension).  They follow the same
 // definitions as the fast path: softmax attention with the 1/sqrt(d_k) scaling
 // of Eq. (1) (Section 4.1 step 1), and the summed form of Eq. (1) for the
 // importance scores.
@@ -27,27 +25,6 @@ template <> struct Elem<float> {
   __device__ static float load1(const float* p) { return *p; }
   __device__ static void store1(float* p, float v) { *p = v; }
 };
-template <> struct Elem<uint16_t> {  // bf16 as raw bits
-  typedef float Logit;
-  static constexpr int kVec = 8;
-  __device__ static float cvt(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
-  __device__ static void load16(const uint16_t* p, float* dst) {
-    uint4 v = *reinterpret_cast<const uint4*>(p);
-    uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      dst[2 * i] = __uint_as_float(w[i] << 16);
-      dst[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-  __device__ static float load1(const uint16_t* p) { return cvt(*p); }
-  __device__ static void store1(uint16_t* p, float v) {  // round to nearest even
-    uint32_t u = __float_as_uint(v);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    *p = static_cast<uint16_t>(u >> 16);
-  }
-};
-
 template <typename T>
 __device__ inline const T* row_ptr(const View& v, int b, int l, int h, int s) {
   return static_cast<const T*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh + static_cast<int64_t>(s) * v.ss);
@@ -220,24 +197,16 @@ hipError_t colsum_launch_t(const Dims& dm, View q, int rows, Segments ks, int ca
 
 }  // namespace
 
-hipError_t launch_attn_generic(int dtype, const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal,
-                               View out, float* lse, hipStream_t st) {
-  if (dtype == CITRUS_F32) {
-    return dm.D == 64 ? attn_launch_t<float, 64>(dm, q, rows, ks, vs, causal, out, lse, st)
-                      : attn_launch_t<float, 128>(dm, q, rows, ks, vs, causal, out, lse, st);
-  }
-  return dm.D == 64 ? attn_launch_t<uint16_t, 64>(dm, q, rows, ks, vs, causal, out, lse, st)
-                    : attn_launch_t<uint16_t, 128>(dm, q, rows, ks, vs, causal, out, lse, st);
+hipError_t launch_attn_f32(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
+                           hipStream_t st) {
+  return dm.D == 64 ? attn_launch_t<float, 64>(dm, q, rows, ks, vs, causal, out, lse, st)
+                    : attn_launch_t<float, 128>(dm, q, rows, ks, vs, causal, out, lse, st);
 }
 
-hipError_t launch_colsum_generic(int dtype, const Dims& dm, View q, int rows, Segments ks, int causal,
-                                 const float* lse, float* score, hipStream_t st) {
-  if (dtype == CITRUS_F32) {
-    return dm.D == 64 ? colsum_launch_t<float, 64>(dm, q, rows, ks, causal, lse, score, st)
-                      : colsum_launch_t<float, 128>(dm, q, rows, ks, causal, lse, score, st);
-  }
-  return dm.D == 64 ? colsum_launch_t<uint16_t, 64>(dm, q, rows, ks, causal, lse, score, st)
-                    : colsum_launch_t<uint16_t, 128>(dm, q, rows, ks, causal, lse, score, st);
+hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse, float* score,
+                             hipStream_t st) {
+  return dm.D == 64 ? colsum_launch_t<float, 64>(dm, q, rows, ks, causal, lse, score, st)
+                    : colsum_launch_t<float, 128>(dm, q, rows, ks, causal, lse, score, st);
 }
 
 }  // namespace citrus

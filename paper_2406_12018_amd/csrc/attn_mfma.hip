@@ -1,4 +1,7 @@
-// bf16 MFMA kernels for head_dim 128 on gfx950 (CDNA4).
+// bf16 MFMA kernels for head_dim 64 and 128 on gfx950 (CDNA4): templates over the head dimension.
+// (head_dim 64 ran on one-wavefront-per-row vector kernels before, whose serial chain of key loads and f32
+// multiply-adds reached 7 TFLOP/s: 8 layers of 32/8 heads, a document of 4096 tokens in chunks of 512, budget 768,
+// took 37.8 ms; on these kernels 0.88 ms.)
 //
 //  attn_pipe_kernel_w8 flash-style chunk attention (Section 4.1 step 1; softmax
 //                      with the 1/sqrt(d_k) scaling of Eq. (1)): online softmax
@@ -32,16 +35,33 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short i16x4;
 
-constexpr int D = 128;
 constexpr int kWaves = 4;               // one wave per SIMD and block; two or more blocks share a CU
 constexpr int kThreads = kWaves * 64;
 constexpr int kRowsPerWave = 32;        // one 32-query column tile per wave
 constexpr int kTileN = 64;              // keys per LDS tile
 constexpr int kXcds = 8;
 constexpr int kBufferFlags = 0x00020000;  // raw buffer resource word 3 on CDNA: 32-bit data format, no swizzle
-constexpr int kPitchK = D + 8;          // padded LDS row pitch in bf16 (272 B) of the column-sum kernel's Q chunk
-constexpr int kRowBytes = 2 * D;        // K/V tile rows in LDS are unpadded (256 B) and XOR-swizzled
-constexpr int kTileBytes = kTileN * kRowBytes;
+
+// Geometry of K/V tiles in LDS for one head dimension (64 or 128).  Rows are unpadded; the 16-byte segment `seg` of
+// tile row `row` lives at segment position seg ^ swz(row), which keeps both read patterns (key rows as an operand,
+// transpose reads of value columns) free of bank conflicts.  swz is linear under XOR in the row's bits, so the
+// swizzle of a sum of disjoint bit ranges is the XOR of their swizzles, and 16 rows leave it unchanged.
+//   128: a row spans the 256 bytes of a 16-byte read cycle: sixteen consecutive rows take sixteen positions.
+//   64:  two rows span them: eight rows of one parity take the eight positions of a row, and the four rows of a
+//        transpose read (8-byte pieces of two neighbouring segments each) fall into four different 32-byte pairs.
+template <int D>
+struct Geo {
+  static constexpr int kSegs = D / 8;                    // 16-byte segments of a row
+  static constexpr int kRowBytes = 2 * D;
+  static constexpr int kTileBytes = kTileN * kRowBytes;
+  static constexpr int kRowsPerLoad = 1024 / kRowBytes;  // rows one wave-level LDS-direct load moves
+  static constexpr int kKk = D / 16;                     // contraction steps of K.Q^T
+  static constexpr int kOut = D / 32;                    // 32-row tiles of O^T
+  static constexpr int kPitchK = D + 8;                  // padded row pitch (bf16) of query rows staged by ordinary writes
+  __device__ static constexpr int swz(int row) {
+    return D == 128 ? (2 * (row % 8)) ^ ((row / 8) % 2) : (2 * ((row / 2) % 4)) ^ ((row / 8) % 2) ^ (4 * (row % 2));
+  }
+};
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kMaxSlack = 8.0f;  // probabilities stay below 2^8: exact in f32, same relative rounding in bf16
@@ -111,6 +131,13 @@ __device__ inline float exp2_then_mfma(float x, f32x16& acc, const bf16x8& a, co
   return y;
 }
 
+// two exponentials in front of one MFMA (head_dim 64: half the MFMAs per logit)
+__device__ inline void exp2x2_then_mfma(float x0, float x1, float& y0, float& y1, f32x16& acc, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_exp_f32 %0, %3\n\tv_exp_f32 %1, %4\n\tv_mfma_f32_32x32x16_bf16 %2, %5, %6, %2"
+               : "=&v"(y0), "=&v"(y1), "+v"(acc)
+               : "v"(x0), "v"(x1), "v"(__builtin_bit_cast(i32x4, a)), "v"(__builtin_bit_cast(i32x4, b)));
+}
+
 // Small fences for the optimiser, as functions so that kernel templates hold no asm of their own.
 __device__ inline void hide_loop_invariance(int& a, int& b) { asm volatile("" : "+v"(a), "+v"(b)); }
 __device__ inline void keep_values_here(uint32_t (&p)[8], float& l) {
@@ -141,8 +168,11 @@ __host__ __device__ inline TaskShape task_shape(int G, int waves = kWaves) {
 // Row normalisers only (no values, no output): the log-sum-exp of every query row over the keys it sees,
 // or, with key_splits > 1, one partial (running maximum, sum) pair per key range and row.  First pass of the
 // two-pass importance scores and of a cache-only normaliser that the attention launch could not emit.
+template <int D>
 __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, int rows, Segments ks, int causal,
                                                               float* lse, int key_splits, float2* part) {
+  typedef Geo<D> T;
+  constexpr int kRowBytes = T::kRowBytes, kTileBytes = T::kTileBytes;
   __shared__ __attribute__((aligned(1024))) char k_s[2 * kTileBytes];  // double-buffered tiles
 
   const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
@@ -178,12 +208,10 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
 
   // ---- global -> LDS staging of one 64-key tile, without a stop in registers ----
   // buffer_load ... lds: a wave-level instruction moves 64 x 16 B from per-lane global addresses
-  // to 1 KB of consecutive LDS, i.e. four unpadded 256-byte rows.  Bank conflicts of the column
-  // reads below are avoided by an XOR swizzle instead of padding: the 16-byte segment `seg` of
-  // tile row `row` lives at segment position seg ^ f(row), f(row) = 2 (row % 8) ^ ((row / 8) % 2),
-  // which the loading lane realises by fetching global segment (its LDS position) ^ f(row).
-  // Wave w fills rows 16 w + 4 i .. + 3 with instruction i = 0..3.  Rows that fall outside the
-  // candidates re-read the last row (finite values; their logits are masked).
+  // to 1 KB of consecutive LDS, i.e. four (head_dim 64: eight) unpadded rows.  The swizzle of a row's
+  // segments (Geo) is realised by the loading lane, which fetches global segment (its LDS position) ^ swz(row).
+  // Wave w fills rows 16 w .. + 15.  Rows that fall outside the candidates re-read the last row
+  // (finite values; their logits are masked).
   const int k_ss_cache = static_cast<int>(ks.cache.ss), k_ss_chunk = static_cast<int>(ks.chunk.ss);
   auto seg_bytes = [](int rows_, int ss_) { return rows_ > 0 ? ((rows_ - 1) * ss_ + D) * 2 : 0; };
   const __amdgpu_buffer_rsrc_t k_rs_cache = __builtin_amdgcn_make_buffer_rsrc(
@@ -191,24 +219,25 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
   const __amdgpu_buffer_rsrc_t k_rs_chunk = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(unit_ptr(ks.chunk, b, l, g)), 0, seg_bytes(ks.c, k_ss_chunk), kBufferFlags);
   const int wu = __builtin_amdgcn_readfirstlane(w);
-  const int fill_row = 16 * wu + lane / 16;                       // tile row this lane fills with instruction 0
-  const int fill_seg16 = ((lane % 16) ^ (2 * (lane / 16))) * 16;  // byte offset of its global segment, before ^ c_i
+  constexpr int kFillRows = kTileN / kWaves, kR = T::kRowsPerLoad;
+  const int fill_row = kFillRows * wu + lane / T::kSegs;                         // tile row this lane fills with load 0
+  const int fill_seg16 = ((lane % T::kSegs) ^ T::swz(lane / T::kSegs)) * 16;  // byte offset of its segment, before ^ c_i
   typedef __attribute__((address_space(3))) void* lds_void_ptr;
   auto fill4 = [&](char* lds_tile, __amdgpu_buffer_rsrc_t rs_cache, __amdgpu_buffer_rsrc_t rs_chunk, int ss_cache,
                    int ss_chunk, int j0) {
     const bool simple = (j0 + kTileN <= n_c) || (j0 >= n_c && j0 + kTileN <= n);  // block-uniform
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int ci16 = ((8 * (i & 1)) | (i >> 1)) * 16;
-      lds_void_ptr dst = (lds_void_ptr)(lds_tile + (16 * wu + 4 * i) * kRowBytes);
+    for (int i = 0; i < kFillRows / kR; ++i) {
+      const int ci16 = T::swz(kR * i) * 16;
+      lds_void_ptr dst = (lds_void_ptr)(lds_tile + (kFillRows * wu + kR * i) * kRowBytes);
       if (simple) {
         const bool in_cache = j0 < n_c;
         const int ss = in_cache ? ss_cache : ss_chunk;
         const int r0 = in_cache ? j0 : j0 - n_c;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(in_cache ? rs_cache : rs_chunk, dst, 16,
-                                                 fill_row * ss * 2 + (fill_seg16 ^ ci16), (r0 + 4 * i) * ss * 2, 0, 0);
+                                                 fill_row * ss * 2 + (fill_seg16 ^ ci16), (r0 + kR * i) * ss * 2, 0, 0);
       } else {  // the tile straddles the cache / chunk boundary or the end of the candidates
-        const int j = min(j0 + fill_row + 4 * i, n - 1);
+        const int j = min(j0 + fill_row + kR * i, n - 1);
         if (j < n_c)
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_cache, dst, 16, j * ss_cache * 2 + (fill_seg16 ^ ci16), 0, 0, 0);
         else
@@ -223,10 +252,10 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
 
   // per-lane LDS read offsets (bytes inside a tile buffer), swizzle included
   // A operand of S^T: key row `col`, head_dim segment 2 kk + grp
-  const int f_col = (2 * (col & 7)) ^ ((col >> 3) & 1);
-  int k_off[8];
+  const int f_col = T::swz(col);
+  int k_off[T::kKk];
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) k_off[kk] = col * kRowBytes + (((2 * kk + grp) ^ f_col) * 16);
+  for (int kk = 0; kk < T::kKk; ++kk) k_off[kk] = col * kRowBytes + (((2 * kk + grp) ^ f_col) * 16);
   for (int pass = 0; pass < passes; ++pass) {
   const int rb = pass == 0 ? rb_first : rb_second;
   const int row0 = (rb * ts.tiles_per_block + w / ts.heads_per_block) * kRowsPerWave;
@@ -244,12 +273,12 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
   const int wave_limit_min = causal ? n_c + row0 : n - 1;           // up to it every row sees everything
 
   // ---- Q^T operand, kept in registers: q_op[kk] = Q[row0 + col][16 kk + 8 grp ..+7] ----
-  bf16x8 q_op[8];
+  bf16x8 q_op[T::kKk];
   const int t_lane = max(min(row0 + col, rows - 1), 0);
   {
     const uint16_t* qp = unit_ptr(q, b, l, h) + static_cast<int64_t>(t_lane) * q.ss + 8 * grp;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < T::kKk; ++kk) {
       Pack8 p;
       p.u = *reinterpret_cast<const uint4*>(qp + 16 * kk);
       q_op[kk] = p.v;
@@ -281,7 +310,7 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
 #pragma unroll
         for (int i = 0; i < 16; ++i) s_acc[mt][i] = 0.f;
 #pragma unroll
-      for (int kh = 0; kh < 2; ++kh) {  // the two 32-key halves are independent MFMA chains: interleave them
+      for (int kh = 0; kh < T::kKk / 4; ++kh) {  // the two 32-key halves are independent MFMA chains: interleave them
         Pack8 a[2][4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
@@ -349,21 +378,25 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
 // half tile h, so that inside ONE wave the matrix pipe, the vector pipe and the LDS reads run at
 // the same time instead of taking turns (the order is fixed with volatile asm statements, see above).
 // K tiles are fetched one 64-key tile further ahead than V tiles; one barrier per 64 keys.
-template <int WAVES, bool ROTATE_Q>
+template <int D, int WAVES, bool ROTATE_Q>
 __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, int rows, const Segments& ks,
                                                const Segments& vs, int causal, const View& out, float* lse,
                                                float* lse_cache, int q_rope_pos0, float rope_log2_base) {
+  typedef Geo<D> T;
+  constexpr int kRowBytes = T::kRowBytes, kTileBytes = T::kTileBytes;
   constexpr bool HAS_PV = true;
   constexpr int key_splits = 1;
   float2* const part = nullptr;
   __shared__ __attribute__((aligned(1024))) char k_s[2 * kTileBytes];  // double-buffered tiles
   __shared__ __attribute__((aligned(1024))) char v_s[HAS_PV ? 2 * kTileBytes : 16];
-  extern __shared__ __attribute__((aligned(1024))) char q_stage[];  // [WAVES][32 rows][256 B], dynamic
+  extern __shared__ __attribute__((aligned(1024))) char q_stage[];  // [WAVES][32 rows][kRowBytes], dynamic
 
   const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
   const int col = lane % 32, grp = lane / 32;
-  constexpr int kFillRows = kTileN / WAVES;  // rows of a tile each wave fetches: 4 per instruction
-  constexpr int kFillInstr = kFillRows / 4;
+  constexpr int kR = T::kRowsPerLoad;
+  constexpr int kFillRows = kTileN / WAVES;  // rows of a tile each wave fetches: kR per instruction
+  constexpr int kFillInstr = kFillRows / kR;
+  static_assert(kFillInstr >= 1 && kFillInstr <= 2, "slots between the MFMAs of a step for a wave's fetches");
   const TaskShape ts = task_shape(dm.G, WAVES);
   const int head_groups = dm.G / ts.heads_per_block;
   const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
@@ -396,12 +429,9 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 
   // ---- global -> LDS staging of one 64-key tile, without a stop in registers ----
   // buffer_load ... lds: a wave-level instruction moves 64 x 16 B from per-lane global addresses
-  // to 1 KB of consecutive LDS, i.e. four unpadded 256-byte rows.  Bank conflicts of the column
-  // reads below are avoided by an XOR swizzle instead of padding: the 16-byte segment `seg` of
-  // tile row `row` lives at segment position seg ^ f(row), f(row) = 2 (row % 8) ^ ((row / 8) % 2),
-  // which the loading lane realises by fetching global segment (its LDS position) ^ f(row).
-  // Wave w fills rows 16 w + 4 i .. + 3 with instruction i = 0..3.  Rows that fall outside the
-  // candidates re-read the last row (finite values; their logits are masked).
+  // to 1 KB of consecutive LDS, i.e. four (head_dim 64: eight) unpadded rows.  The swizzle of a row's
+  // segments (Geo) is realised by the loading lane, which fetches global segment (its LDS position) ^ swz(row).
+  // Rows that fall outside the candidates re-read the last row (finite values; their logits are masked).
   const int k_ss_cache = static_cast<int>(ks.cache.ss), k_ss_chunk = static_cast<int>(ks.chunk.ss);
   const int v_ss_cache = static_cast<int>(vs.cache.ss), v_ss_chunk = static_cast<int>(vs.chunk.ss);
   auto seg_bytes = [](int rows_, int ss_) { return rows_ > 0 ? ((rows_ - 1) * ss_ + D) * 2 : 0; };
@@ -413,13 +443,10 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
       const_cast<uint16_t*>(unit_ptr(HAS_PV ? vs.cache : ks.cache, b, l, g)), 0, seg_bytes(n_c, v_ss_cache), kBufferFlags);
   const __amdgpu_buffer_rsrc_t v_rs_chunk = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(unit_ptr(HAS_PV ? vs.chunk : ks.chunk, b, l, g)), 0, seg_bytes(ks.c, v_ss_chunk), kBufferFlags);
-  const int fill_row_c = kFillRows * wu + lane / 16;                // tile row this lane fills with instruction 0
-  const int fill_seg16_c = ((lane % 16) ^ (2 * (lane / 16))) * 16;  // byte offset of its global segment, before ^ c_i
-  // instruction i covers rows r = kFillRows wu + 4 i .. + 3; the lane-independent part of f(row)
-  auto swz16 = [&](int i) {
-    const int r = kFillRows * wu + 4 * i;
-    return ((2 * (r % 8)) ^ ((r / 8) % 2)) * 16;
-  };
+  const int fill_row_c = kFillRows * wu + lane / T::kSegs;  // tile row this lane fills with instruction 0
+  const int fill_seg16_c = ((lane % T::kSegs) ^ T::swz(lane / T::kSegs)) * 16;  // byte offset of its global segment, before ^ c_i
+  // instruction i covers rows r = kFillRows wu + kR i .. + kR - 1; the lane-independent part of swz(row)
+  auto swz16 = [&](int i) { return T::swz(kFillRows * wu + kR * i) * 16; };
   typedef __attribute__((address_space(3))) void* lds_void_ptr;
   auto fill4 = [&](char* lds_tile, __amdgpu_buffer_rsrc_t rs_cache, __amdgpu_buffer_rsrc_t rs_chunk, int ss_cache,
                    int ss_chunk, int j0) {
@@ -436,14 +463,14 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
       const int row_off = fill_row * ss2;
 #pragma unroll
       for (int i = 0; i < kFillInstr; ++i)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_ptr)(lds_tile + (kFillRows * wu + 4 * i) * kRowBytes), 16,
-                                                 row_off + (fill_seg16 ^ swz16(i)), (r0 + 4 * i) * ss2, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_ptr)(lds_tile + (kFillRows * wu + kR * i) * kRowBytes), 16,
+                                                 row_off + (fill_seg16 ^ swz16(i)), (r0 + kR * i) * ss2, 0, 0);
     } else {  // the tile straddles the cache / chunk boundary or the end of the candidates
 #pragma unroll
       for (int i = 0; i < kFillInstr; ++i) {
-        lds_void_ptr dst = (lds_void_ptr)(lds_tile + (kFillRows * wu + 4 * i) * kRowBytes);
+        lds_void_ptr dst = (lds_void_ptr)(lds_tile + (kFillRows * wu + kR * i) * kRowBytes);
         const int seg = fill_seg16 ^ swz16(i);
-        const int j = min(j0 + fill_row + 4 * i, n - 1);
+        const int j = min(j0 + fill_row + kR * i, n - 1);
         if (j < n_c)
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_cache, dst, 16, j * ss_cache * 2 + seg, 0, 0, 0);
         else
@@ -454,25 +481,26 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 
   // per-lane LDS read offsets (bytes inside a tile buffer), swizzle included
   // A operand of S^T: key row `col`, head_dim segment 2 kk + grp
-  const int f_col = (2 * (col & 7)) ^ ((col >> 3) & 1);
+  const int f_col = T::swz(col);
   // k_off(kk) = col * kRowBytes + ((2 kk + grp) ^ f_col) * 16 = k_off0 ^ (32 kk): one register instead of eight
   const int k_off0 = col * kRowBytes + ((grp ^ f_col) * 16);
   auto k_off = [&](int kk) { return k_off0 ^ (32 * kk); };
   // V^T operand through transpose reads.  The 16-lane group q16 = lane / 16 serves MFMA rows
   // 16 (q16 % 2) .. +15 for contraction lane group q16 / 2; output row c' of tile r is head_dim
-  // 16 r + (c' % 16) + 64 (c' / 16).  Source lane s16 points at 4 consecutive head_dim values of key
-  // row 4 (q16 / 2) + s16 / 4 (+ 8 rd + 16 half + 32 mt): segment 2 r + 8 (q16 % 2) + (s16 % 4) / 2.
+  // 16 r + (c' % 16) + D / 2 (c' / 16).  Source lane s16 points at 4 consecutive head_dim values of key
+  // row 4 (q16 / 2) + s16 / 4 (+ 8 rd + 16 half + 32 mt): segment 2 r + D / 16 (q16 % 2) + (s16 % 4) / 2.
   const int s16 = lane % 16, q16 = lane / 16;
-  const int v_cl = (8 * (q16 % 2) + (s16 % 4) / 2) ^ (8 * (q16 / 2) + 2 * (s16 / 4));
-  // v_off(e), e = 2 r + rd (f(row) of read rd differs from read 0 by ^ rd), = v_off0 ^ (16 e)
+  const int v_cl = (T::kSegs / 2 * (q16 % 2) + (s16 % 4) / 2) ^ T::swz(4 * (q16 / 2) + s16 / 4);
+  // v_off(e), e = 2 r + rd (swz(row) of read rd differs from read 0 by ^ rd), = v_off0 ^ (16 e)
   const int v_off0 = (4 * (q16 / 2) + s16 / 4) * kRowBytes + (v_cl * 16) + 8 * (s16 % 2);
   auto v_off = [&](int e) { return v_off0 ^ (16 * e); };
 
   // The first step of a row block multiplies p_prev = 0 with the second half of V buffer 1, which nothing has
   // filled yet in the first row block: zero it once (0 x garbage could be NaN).  Published by the barrier
   // in front of the first operand reads.
-  *reinterpret_cast<uint4*>(v_s + kTileBytes + 32 * kRowBytes + 16 * tid) = make_uint4(0u, 0u, 0u, 0u);
-  static_assert(WAVES * 64 * 16 == 32 * kRowBytes, "one 16-byte store per thread covers the half tile");
+  static_assert(WAVES * 64 * 16 >= 32 * kRowBytes, "one 16-byte store per thread covers the half tile");
+  if (WAVES * 64 * 16 == 32 * kRowBytes || 16 * tid < 32 * kRowBytes)
+    *reinterpret_cast<uint4*>(v_s + kTileBytes + 32 * kRowBytes + 16 * tid) = make_uint4(0u, 0u, 0u, 0u);
 
   for (int pass = 0; pass < passes; ++pass) {
   const int rb = pass == 0 ? rb_first : rb_second;
@@ -491,7 +519,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   // ---- Q^T operand, kept in registers: q_op[kk] = Q[row0 + col][16 kk + 8 grp ..+7] ----
   // (loaded further down, behind the requests for the first tiles: a lane reads 16-byte pieces of its
   // own row, 64 scattered pieces per instruction, which keep the address path busy for a while)
-  bf16x8 q_op[8];
+  bf16x8 q_op[T::kKk];
   const int t_lane = max(min(row0 + col, rows - 1), 0);
   const int limit_lane = causal ? n_c + t_lane : n - 1;
 
@@ -503,9 +531,9 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   // on a half-tile boundary (the launcher checks); every row sees every cache state.
   const int snap_h = lse_cache != nullptr ? n_c / 32 - 1 : -1;
   float m_snap = -INFINITY, l_snap = 0.f;
-  f32x16 o_acc[4];
+  f32x16 o_acc[T::kOut];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o_acc[r][i] = 0.f;
 
@@ -522,8 +550,8 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
     __amdgpu_buffer_rsrc_t rs;
     char* lds;    // first row this wave fills
     int soff;     // byte offset of instruction 0's first row inside the segment
-    int ss8;      // bytes between the rows of consecutive instructions (4 rows)
-    int row_off;  // per lane: its row inside the instruction's four rows, in bytes
+    int ss8;      // bytes between the rows of consecutive instructions (kR rows)
+    int row_off;  // per lane: its row inside the instruction's rows, in bytes
     int seg16;    // per lane: byte offset of its 16-byte segment before the per-instruction swizzle term
   };
   // At most two tiles are not: the one that holds the cache / chunk boundary and the one that holds
@@ -536,19 +564,19 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
     const int j0 = tile * kTileN;
     const bool in_cache = j0 < n_c;
     const int ss2 = (in_cache ? ss_cache : ss_chunk) * 2;
-    int fill_row = lane / 16, fill_seg16 = fill_seg16_c;
+    int fill_row = lane / T::kSegs, fill_seg16 = fill_seg16_c;
     hide_loop_invariance(fill_row, fill_seg16);  // formed per fetch: see fill4
     FillPlan fp;
     fp.rs = in_cache ? rs_cache : rs_chunk;
     fp.lds = buffer + kFillRows * wu * kRowBytes;
     fp.soff = ((in_cache ? j0 : j0 - n_c) + kFillRows * wu) * ss2;
-    fp.ss8 = 4 * ss2;
+    fp.ss8 = kR * ss2;
     fp.row_off = fill_row * ss2;
     fp.seg16 = fill_seg16;
     return fp;
   };
   auto fill_one = [&](const FillPlan& fp, int i) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(fp.rs, (lds_void_ptr)(fp.lds + 4 * i * kRowBytes), 16,
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(fp.rs, (lds_void_ptr)(fp.lds + kR * i * kRowBytes), 16,
                                              fp.row_off + (fp.seg16 ^ swz16(i)),
                                              fp.soff + i * fp.ss8, 0, 0);
   };
@@ -556,7 +584,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   const int h_first = 2 * t_begin, h_last = 2 * t_end - 1;  // half tiles of 32 keys (block-uniform)
   f32x16 s_cur;            // logits of the half tile whose probabilities are computed next
   uint32_t p_prev[8];      // bf16 probabilities of the half tile before it, not yet multiplied with V
-  Pack8 ka[8];             // K operand of the next logit product, read one step ahead
+  Pack8 ka[T::kKk];        // K operand of the next logit product, read one step ahead
   float mx_cur = 0.f;      // this lane's maximum over s_cur (before masking)
 #pragma unroll
   for (int x = 0; x < 8; ++x) p_prev[x] = 0u;
@@ -564,7 +592,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
     const int hn = min(hn_raw, h_last);
     const char* k_t = k_s + (((hn >> 1) - t_begin) & 1) * kTileBytes + (hn & 1) * 32 * kRowBytes;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) ka[kk].u = *reinterpret_cast<const uint4*>(k_t + k_off(kk));
+    for (int kk = 0; kk < T::kKk; ++kk) ka[kk].u = *reinterpret_cast<const uint4*>(k_t + k_off(kk));
   };
 
   // The same with the buffer parity and the half tile as constants: inside the key loop (unrolled over the
@@ -573,7 +601,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   auto read_k_ops_at = [&](auto parity, auto half) {
     const char* k_t = k_s + decltype(parity)::value * kTileBytes + decltype(half)::value * 32 * kRowBytes;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) ka[kk].u = *reinterpret_cast<const uint4*>(k_t + k_off(kk));
+    for (int kk = 0; kk < T::kKk; ++kk) ka[kk].u = *reinterpret_cast<const uint4*>(k_t + k_off(kk));
   };
 
   // One step: finish the softmax of half tile h (logits in s_cur) while the logits of h + 1 and the
@@ -605,7 +633,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
       // the last P.V MFMAs of the previous step may still be in flight and the compiler cannot see them
       wait_for_pinned_mfmas();
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o_acc[r][i] *= alpha;
       // the probabilities still waiting for their product with V were taken against the old maximum
@@ -625,24 +653,33 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
     // The V^T operands of the second contraction step are read once half of the K operands are
     // spent (the empty asm with a memory clobber keeps the reads from being hoisted above it):
     // all sixteen up front would not fit the register budget.
-    Pack8 va[2][4];
+    Pack8 va[2][T::kOut];
     auto read_v_ops = [&](int half) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
         for (int rd = 0; rd < 2; ++rd)
           va[half][r].h[rd] = lds_read_tr16(v_t + (16 * half + 8 * rd) * kRowBytes + v_off(2 * r + rd));
     };
     read_v_ops(0);
-    // sixteen MFMAs; the exponential of logit x of half tile h is issued right before MFMA x + 1
+    // kKk MFMAs of S^T(h + 1), then 2 kOut of O^T: sixteen (head_dim 64: eight).  The exponential of logit x of half
+    // tile h is issued right before MFMA x + 1 (head_dim 64: those of logits 2 x and 2 x + 1).
     float p[16];
     float mx_nxt = 0.f;
     f32x16 s_nxt = mfma_pinned_first(ka[0].v, q_op[0]);
+    constexpr int kExp = 128 / D;  // exponentials per MFMA slot
+    auto exps_then_mfma = [&](int slot, f32x16& acc, const bf16x8& a, const bf16x8& b) {
+      const int x = kExp * slot;
+      if constexpr (kExp == 2)
+        exp2x2_then_mfma(fmaf(s_cur[x], c2, -m_sub), fmaf(s_cur[x + 1], c2, -m_sub), p[x], p[x + 1], acc, a, b);
+      else
+        p[x] = exp2_then_mfma(fmaf(s_cur[x], c2, -m_sub), acc, a, b);
+    };
 #pragma unroll
-    for (int kk = 1; kk < 8; ++kk) {
-      p[kk - 1] = exp2_then_mfma(fmaf(s_cur[kk - 1], c2, -m_sub), s_nxt, ka[kk].v, q_op[kk]);
+    for (int kk = 1; kk < T::kKk; ++kk) {
+      exps_then_mfma(kk - 1, s_nxt, ka[kk].v, q_op[kk]);
       if ((kk & 1) && kk / 2 < kFillInstr && fill_k) fill_one(fk, kk / 2);  // block-uniform
-      if (kk == 4) {
+      if (kk == T::kKk / 2) {
         no_memory_motion();
         read_v_ops(1);
       }
@@ -653,16 +690,24 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 #pragma unroll
       for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[4 * half + x];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int x = 7 + 4 * half + r;
-        p[x] = exp2_then_mfma(fmaf(s_cur[x], c2, -m_sub), o_acc[r], va[half][r].v, pb.v);
-        if ((r & 1) && 2 * half + r / 2 < kFillInstr && fill_v) fill_one(fv, 2 * half + r / 2);  // block-uniform
+      for (int r = 0; r < T::kOut; ++r) {
+        const int slot = T::kOut * half + r;  // of the second product
+        exps_then_mfma(T::kKk - 1 + slot, o_acc[r], va[half][r].v, pb.v);
+        if ((slot & 1) && slot / 2 < kFillInstr && fill_v) fill_one(fv, slot / 2);  // block-uniform
         // The lane's maximum of the next half tile's logits, one v_max3 per MFMA slot.  s_nxt was
-        // completed by the eighth MFMA of the step; three further MFMAs have been issued since.
-        const int y = 4 * half + r - 2;  // 0 .. 5
-        if (y == 0) mx_nxt = max3_pinned(s_nxt[0], s_nxt[1], s_nxt[2]);
-        if (y > 0) mx_nxt = max3_pinned(mx_nxt, s_nxt[2 * y + 1], s_nxt[2 * y + 2]);
+        // completed by the last MFMA of the first product; three further MFMAs have been issued since.
+        if (D == 128) {
+          const int y = slot - 2;  // 0 .. 5
+          if (y == 0) mx_nxt = max3_pinned(s_nxt[0], s_nxt[1], s_nxt[2]);
+          if (y > 0) mx_nxt = max3_pinned(mx_nxt, s_nxt[2 * y + 1], s_nxt[2 * y + 2]);
+        }
       }
+    }
+    if constexpr (kExp == 2) {
+      p[14] = exp2_pinned(fmaf(s_cur[14], c2, -m_sub));
+      mx_nxt = max3_pinned(s_nxt[0], s_nxt[1], s_nxt[2]);
+#pragma unroll
+      for (int y = 1; y < 6; ++y) mx_nxt = max3_pinned(mx_nxt, s_nxt[2 * y + 1], s_nxt[2 * y + 2]);
     }
     p[15] = exp2_pinned(fmaf(s_cur[15], c2, -m_sub));
     mx_nxt = max3_pinned(mx_nxt, s_nxt[13], s_nxt[14]);
@@ -697,22 +742,22 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   fetch_k(t_begin);
   fetch_v(t_begin);
   if (t_begin + 1 < t_end) fetch_k(t_begin + 1);
-  // The wave's 32 query rows come in through LDS as well: whole 256-byte rows, four per load
-  // instruction, into the wave's own 8 KB (same swizzle as a key tile), from where the B operand is
+  // The wave's 32 query rows come in through LDS as well: whole rows, kR per load
+  // instruction, into the wave's own region (same swizzle as a key tile), from where the B operand is
   // read like a key operand.  Loading them straight into the operand layout would put 64 scattered
   // 16-byte pieces into every load instruction.
   {
     const int q_ss2 = static_cast<int>(q.ss) * 2;
     const __amdgpu_buffer_rsrc_t q_rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t*>(unit_ptr(q, b, l, h)), 0, ((rows - 1) * static_cast<int>(q.ss) + D) * 2, kBufferFlags);
-    int r_in = lane / 16, pos = lane % 16;
+    int r_in = lane / T::kSegs, pos = lane % T::kSegs;
     hide_loop_invariance(r_in, pos);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = 4 * i + r_in;
-      const int f = (2 * (r % 8)) ^ ((r / 8) % 2);
+    for (int i = 0; i < 32 / kR; ++i) {
+      const int r = kR * i + r_in;
+      const int f = T::swz(r);
       const int row = min(row0 + r, rows - 1);  // rows past the end repeat the last one; never stored
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(q_rs, (lds_void_ptr)(q_stage + (32 * wu + 4 * i) * kRowBytes), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(q_rs, (lds_void_ptr)(q_stage + (32 * wu + kR * i) * kRowBytes), 16,
                                                max(row, 0) * q_ss2 + ((pos ^ f) * 16), 0, 0, 0);
     }
   }
@@ -720,16 +765,17 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   // Position shift: the query rows arrive without rotary embedding and are rotated here, in the staging
   // region, to position q_rope_pos0 + row, before the operands are read (only a few registers are live at
   // this point; rotating the operands in registers pushed the whole kernel over its register budget).
-  // Element i of a row pairs with element i + 64: 16-byte segment sg with segment sg + 8.  A lane takes
-  // one (row, sg) of the wave's 32 x 8 per round; the wave touches only its own rows, so no barrier.
+  // Element i of a row pairs with element i + D / 2: 16-byte segment sg with segment sg + D / 16.  A lane takes
+  // one (row, sg) of the wave's 32 x D / 16 per round; the wave touches only its own rows, so no barrier.
   if (ROTATE_Q) {
     char* q_t = q_stage + 32 * wu * kRowBytes;
+    constexpr int kPairs = T::kSegs / 2, kRoundRows = 64 / kPairs;
 #pragma unroll 1
-    for (int round = 0; round < 4; ++round) {
-      const int r = 8 * round + lane / 8, sg = lane % 8;
-      const int f = (2 * (r % 8)) ^ ((r / 8) % 2);
+    for (int round = 0; round < 32 / kRoundRows; ++round) {
+      const int r = kRoundRows * round + lane / kPairs, sg = lane % kPairs;
+      const int f = T::swz(r);
       uint4* lo_p = reinterpret_cast<uint4*>(q_t + r * kRowBytes + ((sg ^ f) * 16));
-      uint4* hi_p = reinterpret_cast<uint4*>(q_t + r * kRowBytes + (((sg + 8) ^ f) * 16));
+      uint4* hi_p = reinterpret_cast<uint4*>(q_t + r * kRowBytes + (((sg + kPairs) ^ f) * 16));
       Pack8 lo, hi;
       lo.u = *lo_p;
       hi.u = *hi_p;
@@ -749,7 +795,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   {
     const char* q_t = q_stage + 32 * wu * kRowBytes;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < T::kKk; ++kk) {
       Pack8 p;
       p.u = *reinterpret_cast<const uint4*>(q_t + k_off(kk));
       q_op[kk] = p.v;
@@ -759,7 +805,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 #pragma unroll
   for (int i = 0; i < 16; ++i) s_cur[i] = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk)  // logits of the first half tile
+  for (int kk = 0; kk < T::kKk; ++kk)  // logits of the first half tile
     s_cur = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk].v, q_op[kk], s_cur, 0, 0, 0);
   mx_cur = s_cur[0];
 #pragma unroll
@@ -796,9 +842,9 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
     const char* v_t = v_s + ((t_end - 1 - t_begin) & 1) * kTileBytes + 32 * kRowBytes;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      Pack8 va[4];
+      Pack8 va[T::kOut];
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
         for (int rd = 0; rd < 2; ++rd)
           va[r].h[rd] = lds_read_tr16(v_t + (16 * half + 8 * rd) * kRowBytes + v_off(2 * r + rd));
@@ -806,7 +852,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 #pragma unroll
       for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[4 * half + x];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) o_acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[r].v, pb.v, o_acc[r], 0, 0, 0);
+      for (int r = 0; r < T::kOut; ++r) o_acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[r].v, pb.v, o_acc[r], 0, 0, 0);
     }
   }
   __syncthreads();  // the buffers are free for the next row block
@@ -825,42 +871,45 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   // The output tile leaves through LDS: a lane holds 4-element pieces of ONE query row (256 bytes
   // between neighbouring lanes), so direct stores put 64 scattered 8-byte pieces into every store
   // instruction and keep the compute unit's address path busy for microseconds per row block.  Each
-  // wave parks its 32 x 128 tile in its own 8 KB of the tile buffers (free after the barrier above;
+  // wave parks its 32 x D tile in its own quarter of a K or V buffer pair (free after the barrier above;
   // 16-byte segments XOR-swizzled by the row so that the column-wise writes spread over the banks)
-  // and stores it back as whole 256-byte rows.
+  // and stores it back as whole rows.
   {
     int colx = col, lanex = lane;
     hide_loop_invariance(colx, lanex);  // offsets are formed here, per row block, not kept in registers
     char* o_s = (wu < 4 ? k_s : v_s) + (wu % 4) * (32 * kRowBytes) + colx * kRowBytes;
-    // A lane pair (col, col + 32) shares every 16-byte segment.  The LDS has 32 banks of 4 bytes, so segment
-    // positions p and p + 8 of a row meet in the same banks, and 16 lanes go through per cycle: the two 8-byte
-    // halves of a segment are kept swapped where (p / 8) ^ (row / 16) is odd, which gives the 16 lanes of a
-    // cycle 16 different 8-byte slots of the 128 bytes the banks span.
-    const int c16 = colx % 16, half0 = grp ^ (colx / 16);
+    // A lane pair (col, col + 32) shares every 16-byte segment.  The LDS has 32 banks of 4 bytes, and 16 lanes of an
+    // 8-byte write go through per cycle, so the sixteen rows of a cycle have to fall into sixteen 8-byte slots of 128
+    // bytes.  head_dim 128: segment positions p and p + 8 of a row meet in the same banks; the two halves of a segment
+    // are kept swapped where (p / 8) ^ (row / 16) is odd.  head_dim 64: a row has eight positions; the halves are
+    // swapped in every second group of eight rows.
+    constexpr int kSwzRows = T::kSegs;
+    const int c_swz = colx % kSwzRows, half0 = D == 128 ? grp ^ (colx / 16) : grp ^ ((colx / 8) & 1);
     const float inv = 1.f / l_tot;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
-        // registers 4 i4 .. +3 are rows c' = 8 i4 + 4 grp + 0..3 -> head_dim 16 r + (c' % 16) + 64 (c' / 16):
-        // 16-byte segment 2 r + (i4 % 2) + 8 (i4 / 2), its half `grp`
-        const int sg = 2 * r + (i4 % 2) + 8 * (i4 / 2);
+        // registers 4 i4 .. +3 are rows c' = 8 i4 + 4 grp + 0..3 -> head_dim 16 r + (c' % 16) + D / 2 (c' / 16):
+        // 16-byte segment 2 r + (i4 % 2) + D / 16 (i4 / 2), its half `grp`
+        const int sg = 2 * r + (i4 % 2) + T::kSegs / 2 * (i4 / 2);
         uint2 wds;
         wds.x = pack_bf16x2(o_acc[r][4 * i4] * inv, o_acc[r][4 * i4 + 1] * inv);
         wds.y = pack_bf16x2(o_acc[r][4 * i4 + 2] * inv, o_acc[r][4 * i4 + 3] * inv);
-        const int p = sg ^ c16;  // segment position
-        *reinterpret_cast<uint2*>(o_s + p * 16 + 8 * (half0 ^ (p >> 3))) = wds;
+        const int p = sg ^ c_swz;  // segment position
+        *reinterpret_cast<uint2*>(o_s + p * 16 + 8 * (D == 128 ? half0 ^ (p >> 3) : half0)) = wds;
       }
-    const char* o_r = (wu < 4 ? k_s : v_s) + (wu % 4) * (32 * kRowBytes) + lanex * 16;  // row lanex / 16 of a 4-row group
-    const int r_in = lanex / 16, pos = lanex % 16;
+    const char* o_r = (wu < 4 ? k_s : v_s) + (wu % 4) * (32 * kRowBytes) + lanex * 16;  // row lanex / kSegs of a kR-row group
+    const int r_in = lanex / T::kSegs, pos = lanex % T::kSegs;
     uint16_t* ob = const_cast<uint16_t*>(unit_ptr(out, b, l, h));
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = 4 * i + r_in;
-      uint4 piece = *reinterpret_cast<const uint4*>(o_r + 4 * i * kRowBytes);
-      if (((pos >> 3) ^ (i >> 2)) & 1) piece = make_uint4(piece.z, piece.w, piece.x, piece.y);  // halves back in order
+    for (int i = 0; i < 32 / kR; ++i) {
+      const int r = kR * i + r_in;
+      uint4 piece = *reinterpret_cast<const uint4*>(o_r + kR * i * kRowBytes);
+      const bool swapped = D == 128 ? ((pos >> 3) ^ (i >> 2)) & 1 : i & 1;
+      if (swapped) piece = make_uint4(piece.z, piece.w, piece.x, piece.y);  // halves back in order
       if (wave_active && row0 + r < rows)
-        *reinterpret_cast<uint4*>(ob + static_cast<int64_t>(row0 + r) * out.ss + 8 * (pos ^ (r % 16))) = piece;
+        *reinterpret_cast<uint4*>(ob + static_cast<int64_t>(row0 + r) * out.ss + 8 * (pos ^ (r % kSwzRows))) = piece;
     }
   }
   __syncthreads();  // the parked tiles have been read back: the next row block may fill the buffers
@@ -870,17 +919,21 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 // Eight waves per workgroup: two 32-row tiles of the four heads of a KV group (or the equivalent
 // split for smaller groups) share every K/V tile, which halves the fetch traffic per MFMA
 // against four waves; one workgroup per CU, two waves per SIMD.
-__global__ __launch_bounds__(512, 1) void attn_pipe_kernel_w8(Dims dm, View q, int rows, Segments ks, Segments vs,
-                                                             int causal, View out, float* lse, float* lse_cache) {
-  attn_pipe_body<8, false>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, -1, 0.f);
+template <int D>
+__global__ __launch_bounds__(512, D == 128 ? 1 : 2) void attn_pipe_kernel_w8(Dims dm, View q, int rows, Segments ks, Segments vs,
+                                                                            int causal, View out, float* lse,
+                                                                            float* lse_cache) {
+  attn_pipe_body<D, 8, false>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, -1, 0.f);
 }
 // The same kernel for query rows that arrive without rotary embedding (position shift): they are rotated
 // in the LDS staging region before the operands are read.  An instance of its own, so that the kernel
 // above does not carry the extra prologue.
-__global__ __launch_bounds__(512, 1) void attn_pipe_kernel_w8_rotq(Dims dm, View q, int rows, Segments ks, Segments vs,
-                                                                  int causal, View out, float* lse, float* lse_cache,
-                                                                  int q_rope_pos0, float rope_log2_base) {
-  attn_pipe_body<8, true>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, q_rope_pos0, rope_log2_base);
+template <int D>
+__global__ __launch_bounds__(512, D == 128 ? 1 : 2) void attn_pipe_kernel_w8_rotq(Dims dm, View q, int rows, Segments ks,
+                                                                                 Segments vs, int causal, View out, float* lse,
+                                                                                 float* lse_cache, int q_rope_pos0,
+                                                                                 float rope_log2_base) {
+  attn_pipe_body<D, 8, true>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, q_rope_pos0, rope_log2_base);
 }
 
 // Brings the per-range (maximum, sum) pairs of a row, part[s * rows_total + row], to one normaliser,
@@ -915,10 +968,12 @@ constexpr int kColsumQRows = 128;   // query rows per LDS chunk
 // STEPWISE: rows is a multiple of kColsumQRows, so every chunk of staged rows is full and lies inside one
 // head (an instance of its own: both address paths in one kernel cost the registers that two workgroups
 // per compute unit need).
-template <bool STEPWISE>
+template <int D, bool STEPWISE>
 __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims dm, View q, int rows, Segments ks,
                                                                         int causal, const float* lse, int key_splits,
                                                                         const float2* part, float* score) {
+  typedef Geo<D> T;
+  constexpr int kPitchK = T::kPitchK;
   // two staging buffers of query rows and their normalisers (log2 domain, +inf for padding rows)
   extern __shared__ __attribute__((aligned(16))) char colsum_smem[];
   uint16_t* const q_sb = reinterpret_cast<uint16_t*>(colsum_smem);                        // [2][kColsumQRows][kPitchK]
@@ -931,7 +986,7 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
   const bool wave_has_keys = j0 < n;
   const int j_last = j0 + 32 * kColsumKeyTiles - 1;
 
-  bf16x8 k_op[kColsumKeyTiles][8];
+  bf16x8 k_op[kColsumKeyTiles][T::kKk];
   // bases and strides are read once: a per-lane choice between the two structs' fields would compile to a
   // per-lane load of the chosen field from the argument block
   const uint16_t* const k_cache_u = unit_ptr(ks.cache, b, l, g) + 8 * grp;
@@ -944,7 +999,7 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
     const int64_t off = in_cache ? j * k_ss_cache : (j - n_c) * k_ss_chunk;
     const uint16_t* kp = (in_cache ? k_cache_u : k_chunk_u) + off;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < T::kKk; ++kk) {
       Pack8 p;
       p.u = *reinterpret_cast<const uint4*>(kp + 16 * kk);
       k_op[kt][kk] = p.v;
@@ -961,16 +1016,17 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
   const int64_t part_stride = static_cast<int64_t>(dm.B) * dm.L * dm.Hq * rows;
   // The rows of chunk c + 1 are requested (into registers) before the products of chunk c start and
   // written to the other buffer afterwards: one barrier per chunk, no exposed load latency.
-  // A thread stages 16 bytes of rows tid / 16 + 32 x of a chunk.  STEPWISE: every chunk lies inside one head
+  // A thread stages 16 bytes of rows st_row + kStageStep x of a chunk.  STEPWISE: every chunk lies inside one head
   // and is full, so its first row is a wave-uniform pointer that moves on by adds, and a thread's part of the
   // address never changes; dividing the flattened row index by `rows` for every load cost more vector
   // instructions per chunk than three of its four products.
-  constexpr int kStageLoads = kColsumQRows / (kColsumWaves * 4);  // 16 threads per row, 16 bytes each
-  constexpr int kStageStep = kColsumWaves * 4;                     // rows between a thread's loads
+  constexpr int kStageStep = kColsumWaves * 64 / T::kSegs;  // rows between a thread's loads: kSegs threads per row, 16 bytes each
+  constexpr int kStageLoads = kColsumQRows / kStageStep;
+  const int st_row = tid / T::kSegs, st_seg = tid % T::kSegs;
   i32x4 q_in[kStageLoads];
   float lse_in = INFINITY;
   const int64_t lse_row0 = (static_cast<int64_t>(bl) * dm.Hq + g * dm.G) * rows;  // the group's heads are consecutive
-  const uint32_t q_thread_off = ((tid / 16) * static_cast<uint32_t>(q.ss) + 8 * (tid % 16)) * 2;  // bytes; a head's rows span < 2 GiB
+  const uint32_t q_thread_off = (st_row * static_cast<uint32_t>(q.ss) + 8 * st_seg) * 2;  // bytes; a head's rows span < 2 GiB
   int stage_head = 0, stage_row = 0;  // where the next requested chunk starts (block-uniform)
   auto request_chunk = [&](int f0) {
     if constexpr (STEPWISE) {
@@ -988,10 +1044,10 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
     } else {
 #pragma unroll
       for (int x = 0; x < kStageLoads; ++x) {
-        const int f = min(f0 + tid / 16 + x * kStageStep, total_rows - 1);
+        const int f = min(f0 + st_row + x * kStageStep, total_rows - 1);
         const int hh = f / rows, t = f % rows;
         q_in[x] = *reinterpret_cast<const i32x4*>(unit_ptr(q, b, l, g * dm.G + hh) + static_cast<int64_t>(t) * q.ss +
-                                                  8 * (tid % 16));
+                                                  8 * st_seg);
       }
     }
     float v = INFINITY;  // padding rows contribute exp2(-inf) = 0
@@ -1022,7 +1078,7 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
     // this buffer was last read two chunks ago, and every wave has passed the previous chunk's barrier since
 #pragma unroll
     for (int x = 0; x < kStageLoads; ++x)
-      *reinterpret_cast<i32x4*>(&q_s[(tid / 16 + x * kStageStep) * kPitchK + 8 * (tid % 16)]) = q_in[x];
+      *reinterpret_cast<i32x4*>(&q_s[(st_row + x * kStageStep) * kPitchK + 8 * st_seg]) = q_in[x];
     if (tid < kColsumQRows) lse_s[tid] = lse_in;
     if (f0 + kColsumQRows < total_rows) request_chunk(f0 + kColsumQRows);  // block-uniform
     __syncthreads();
@@ -1034,10 +1090,10 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
           const int t_last = t_first + 31 >= rows ? rows - 1 : t_first + 31;  // a tile that wraps reaches a head's end
           if (n_c + t_last < j0) continue;
         }
-        Pack8 qb[8];
+        Pack8 qb[T::kKk];
         const uint16_t* qrow = &q_s[(32 * qt + col) * kPitchK + 8 * grp];
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qb[kk].u = *reinterpret_cast<const uint4*>(qrow + 16 * kk);
+        for (int kk = 0; kk < T::kKk; ++kk) qb[kk].u = *reinterpret_cast<const uint4*>(qrow + 16 * kk);
         const float lse2 = lse_s[32 * qt + col];
         // A mask is needed only where a key of this wave can be invisible to a row of this tile:
         // past the last candidate, or (causal) a chunk key later than the tile's first row.  The
@@ -1054,7 +1110,7 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
 #pragma unroll
           for (int i = 0; i < 16; ++i) s_t[i] = 0.f;
 #pragma unroll
-          for (int kk = 0; kk < 8; ++kk)
+          for (int kk = 0; kk < T::kKk; ++kk)
             s_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op[kt][kk], qb[kk].v, s_t, 0, 0, 0);
           if (need_mask) {
 #pragma unroll
@@ -1115,9 +1171,11 @@ __device__ inline float reduce16_over32(const float (&v)[16], int col) {
 // Partial column sums of the q shares meet in LDS and are added in a fixed order: no atomics.
 // With KREG > 0 a wave keeps its (at most KREG) key tiles in registers from the first pass to the
 // second: K is read from memory once, and all its loads are in flight together at the start.
-template <int QT_TOTAL, int Q_SPLIT, int WAVES, int KREG>
+template <int D, int QT_TOTAL, int Q_SPLIT, int WAVES, int KREG>
 __global__ __launch_bounds__(WAVES * 64) void instr_fused_kernel(Dims dm, View q, int rows, Segments ks,
                                                                  float* score) {
+  typedef Geo<D> T;
+  constexpr int kPitchK = T::kPitchK;
   constexpr int KW = WAVES / Q_SPLIT;         // waves that share the key tiles
   constexpr int QT_PER = QT_TOTAL / Q_SPLIT;  // q-tiles per wave
   constexpr int QROWS = QT_TOTAL * 32;
@@ -1141,28 +1199,28 @@ __global__ __launch_bounds__(WAVES * 64) void instr_fused_kernel(Dims dm, View q
   // the strides are read here, once: a per-lane choice between the two struct fields inside the loader
   // would compile to a per-lane LOAD of the chosen field from the argument block, in front of every tile
   const int64_t k_ss_cache = ks.cache.ss, k_ss_chunk = ks.chunk.ss;
-  auto load_keys = [&](int kt, bf16x8 (&k_op)[8]) {
+  auto load_keys = [&](int kt, bf16x8 (&k_op)[T::kKk]) {
     const int j = min(32 * kt + col, n - 1);
     const bool in_cache = j < n_c;
     const int64_t off = in_cache ? j * k_ss_cache : (j - n_c) * k_ss_chunk;
     const uint16_t* kp = (in_cache ? k_cache_u : k_chunk_u) + off;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < T::kKk; ++kk) {
       Pack8 p;
       p.u = *reinterpret_cast<const uint4*>(kp + 16 * kk);
       k_op[kk] = p.v;
     }
   };
-  auto logits = [&](const bf16x8 (&k_op)[8], int qt) {  // S^T tile: 32 keys x the 32 rows of q-tile qt
-    Pack8 qb[8];
+  auto logits = [&](const bf16x8 (&k_op)[T::kKk], int qt) {  // S^T tile: 32 keys x the 32 rows of q-tile qt
+    Pack8 qb[T::kKk];
     const uint16_t* qrow = &q_s[(32 * qt + col) * kPitchK + 8 * grp];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) qb[kk].u = *reinterpret_cast<const uint4*>(qrow + 16 * kk);
+    for (int kk = 0; kk < T::kKk; ++kk) qb[kk].u = *reinterpret_cast<const uint4*>(qrow + 16 * kk);
     f32x16 s_t;
 #pragma unroll
     for (int i = 0; i < 16; ++i) s_t[i] = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) s_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op[kk], qb[kk].v, s_t, 0, 0, 0);
+    for (int kk = 0; kk < T::kKk; ++kk) s_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op[kk], qb[kk].v, s_t, 0, 0, 0);
     return s_t;
   };
 
@@ -1171,22 +1229,25 @@ __global__ __launch_bounds__(WAVES * 64) void instr_fused_kernel(Dims dm, View q
   // requests the query rows of the slowest wave (all of them are needed before the first product) arrive
   // when the whole burst is nearly through.  Loads return in order and the compiler counts them, so the
   // first pass then starts on a wave's first key tile while its later ones are still arriving.
-  constexpr int kQLoads = QROWS / (WAVES * 4);  // 16 threads per row, 16 bytes each
+  constexpr int kQStep = WAVES * 64 / T::kSegs;  // rows between a thread's loads: kSegs threads per row, 16 bytes each
+  static_assert(QROWS % kQStep == 0, "whole rounds of staging loads");
+  constexpr int kQLoads = QROWS / kQStep;
+  const int st_row = tid / T::kSegs, st_seg = tid % T::kSegs;
   i32x4 q_in[kQLoads];
 #pragma unroll
   for (int x = 0; x < kQLoads; ++x) {
-    const int f = min(tid / 16 + x * WAVES * 4, total_rows - 1);  // padding rows repeat the last row; never summed
+    const int f = min(st_row + x * kQStep, total_rows - 1);  // padding rows repeat the last row; never summed
     const int hh = f / rows, t = f % rows;
     q_in[x] = *reinterpret_cast<const i32x4*>(unit_ptr(q, b, l, g * dm.G + hh) + static_cast<int64_t>(t) * q.ss +
-                                              8 * (tid % 16));
+                                              8 * st_seg);
   }
   __builtin_amdgcn_sched_barrier(0);  // keep the issue order
-  bf16x8 k_res[KREG > 0 ? KREG : 1][8];
+  bf16x8 k_res[KREG > 0 ? KREG : 1][T::kKk];
   if constexpr (KREG > 0) load_keys(min(kw, tiles - 1), k_res[0]);  // the launcher guarantees tiles <= KW * KREG
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int x = 0; x < kQLoads; ++x)
-    *reinterpret_cast<i32x4*>(&q_s[(tid / 16 + x * WAVES * 4) * kPitchK + 8 * (tid % 16)]) = q_in[x];
+    *reinterpret_cast<i32x4*>(&q_s[(st_row + x * kQStep) * kPitchK + 8 * st_seg]) = q_in[x];
   __syncthreads();
 
   // With resident key tiles the first pass requests tile i + 1 when it starts on tile i: a compute unit
@@ -1205,7 +1266,7 @@ __global__ __launch_bounds__(WAVES * 64) void instr_fused_kernel(Dims dm, View q
       }
     } else {
       for (int kt = kw; kt < tiles; kt += KW) {
-        bf16x8 k_op[8];
+        bf16x8 k_op[T::kKk];
         load_keys(kt, k_op);
         tile_fn(k_op, kt);
       }
@@ -1219,7 +1280,7 @@ __global__ __launch_bounds__(WAVES * 64) void instr_fused_kernel(Dims dm, View q
     m_run[x] = -INFINITY;
     l_run[x] = 0.f;
   }
-  for_my_tiles(std::true_type{}, [&](const bf16x8 (&k_op)[8], int kt) {
+  for_my_tiles(std::true_type{}, [&](const bf16x8 (&k_op)[T::kKk], int kt) {
     const int valid = n - 32 * kt;  // keys of the tile that exist (wave-uniform)
 #pragma unroll
     for (int x = 0; x < QT_PER; ++x) {
@@ -1275,7 +1336,7 @@ __global__ __launch_bounds__(WAVES * 64) void instr_fused_kernel(Dims dm, View q
   float lse2[QT_PER];
 #pragma unroll
   for (int x = 0; x < QT_PER; ++x) lse2[x] = lse_s[32 * (qh * QT_PER + x) + col];
-  for_my_tiles(std::false_type{}, [&](const bf16x8 (&k_op)[8], int kt) {
+  for_my_tiles(std::false_type{}, [&](const bf16x8 (&k_op)[T::kKk], int kt) {
     float acc[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
@@ -1302,20 +1363,21 @@ __global__ __launch_bounds__(WAVES * 64) void instr_fused_kernel(Dims dm, View q
 }
 
 constexpr size_t kFusedLdsBudget = 150 * 1024;  // of the CU's 160 KB
-constexpr int kFusedKeyTilesInRegs = 5;           // 160 of a wave's 256 registers
+template <int D>
+constexpr int fused_key_tiles_in_regs() { return 5 * 128 / D; }  // 160 of a wave's 256 registers
 
-template <int QT_TOTAL, int Q_SPLIT, int WAVES>
+template <int D, int QT_TOTAL, int Q_SPLIT, int WAVES>
 size_t instr_fused_lds_bytes(int n) {
   constexpr int QROWS = QT_TOTAL * 32;
   const int tiles = (n + 31) / 32;
-  return static_cast<size_t>(QROWS) * kPitchK * 2 + static_cast<size_t>(WAVES / Q_SPLIT) * QROWS * 8 + QROWS * 4 +
+  return static_cast<size_t>(QROWS) * Geo<D>::kPitchK * 2 + static_cast<size_t>(WAVES / Q_SPLIT) * QROWS * 8 + QROWS * 4 +
          static_cast<size_t>(Q_SPLIT) * 32 * tiles * 4;
 }
 
-template <int QT_TOTAL, int Q_SPLIT, int WAVES, int KREG>
+template <int D, int QT_TOTAL, int Q_SPLIT, int WAVES, int KREG>
 hipError_t instr_fused_launch(const Dims& dm, View q, int rows, Segments ks, float* score, hipStream_t st) {
-  const size_t lds = instr_fused_lds_bytes<QT_TOTAL, Q_SPLIT, WAVES>(ks.n_c + ks.c);
-  auto kern = instr_fused_kernel<QT_TOTAL, Q_SPLIT, WAVES, KREG>;
+  const size_t lds = instr_fused_lds_bytes<D, QT_TOTAL, Q_SPLIT, WAVES>(ks.n_c + ks.c);
+  auto kern = instr_fused_kernel<D, QT_TOTAL, Q_SPLIT, WAVES, KREG>;
   static LdsLimit limit;
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), static_cast<int>(kFusedLdsBudget));
   if (e != hipSuccess) return e;
@@ -1324,21 +1386,13 @@ hipError_t instr_fused_launch(const Dims& dm, View q, int rows, Segments ks, flo
 }
 
 
-}  // namespace
-
-bool mfma_path_supported(int dtype, const Dims& dm) { return dtype == CITRUS_BF16 && dm.D == D; }
-
-static bool fits_i32(const View& v, int rows) {
+bool fits_i32(const View& v, int rows) {
   return v.ss > 0 && v.ss * static_cast<int64_t>(rows > 0 ? rows : 1) < (int64_t{1} << 31);
 }
 
-bool attn_mfma_emits_cache_lse(const Segments& ks, int causal, View out) {
-  return out.ptr != nullptr && causal != 0 && ks.n_c > 0 && ks.n_c % 32 == 0;
-}
-
-hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
-                            float* lse, float* lse_cache, int key_splits, float2* part, hipStream_t st,
-                            int q_rope_pos0, float rope_base) {
+template <int D>
+hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
+                       float* lse_cache, int key_splits, float2* part, hipStream_t st, int q_rope_pos0, float rope_base) {
   if (lse_cache != nullptr && !attn_mfma_emits_cache_lse(ks, causal, out)) return hipErrorInvalidValue;
   if (q_rope_pos0 >= 0 && out.ptr == nullptr) return hipErrorInvalidValue;  // only the kernel with output rotates
   if (!fits_i32(ks.cache, ks.n_c) || !fits_i32(ks.chunk, ks.c) || !fits_i32(vs.cache, vs.n_c) ||
@@ -1352,38 +1406,95 @@ hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments ks, Segme
   const int row_blocks = (rows + rows_per_block - 1) / rows_per_block;
   const int rb_slots = (causal && key_splits == 1) ? (row_blocks + 1) / 2 : row_blocks;  // paired row blocks
   dim3 grid(rb_slots * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L * key_splits);
-  constexpr int kQStageBytes = kPipeWaves * 32 * kRowBytes;  // dynamic LDS next to the 64 KB of static tiles
+  constexpr int kQStageBytes = kPipeWaves * 32 * Geo<D>::kRowBytes;  // dynamic LDS next to the static tiles
   if (pipe) {
     static LdsLimit limit, limit_rotq;
-    hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_pipe_kernel_w8), kQStageBytes);
-    if (e == hipSuccess) e = raise_lds_limit(limit_rotq, reinterpret_cast<const void*>(attn_pipe_kernel_w8_rotq), kQStageBytes);
+    hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_pipe_kernel_w8<D>), kQStageBytes);
+    if (e == hipSuccess) e = raise_lds_limit(limit_rotq, reinterpret_cast<const void*>(attn_pipe_kernel_w8_rotq<D>), kQStageBytes);
     if (e != hipSuccess) return e;
   }
   if (pipe && q_rope_pos0 >= 0)
-    hipLaunchKernelGGL(attn_pipe_kernel_w8_rotq, grid, dim3(kPipeWaves * 64), kQStageBytes, st, dm, q, rows, ks, vs, causal, out, lse,
+    hipLaunchKernelGGL(attn_pipe_kernel_w8_rotq<D>, grid, dim3(kPipeWaves * 64), kQStageBytes, st, dm, q, rows, ks, vs, causal, out, lse,
                        lse_cache, q_rope_pos0, log2f(rope_base));
   else if (pipe)
-    hipLaunchKernelGGL(attn_pipe_kernel_w8, grid, dim3(kPipeWaves * 64), kQStageBytes, st, dm, q, rows, ks, vs, causal, out, lse,
+    hipLaunchKernelGGL(attn_pipe_kernel_w8<D>, grid, dim3(kPipeWaves * 64), kQStageBytes, st, dm, q, rows, ks, vs, causal, out, lse,
                        lse_cache);
   else
-    hipLaunchKernelGGL(lse_mfma_kernel, grid, dim3(kThreads), 0, st, dm, q, rows, ks, causal, lse, key_splits, part);
+    hipLaunchKernelGGL(lse_mfma_kernel<D>, grid, dim3(kThreads), 0, st, dm, q, rows, ks, causal, lse, key_splits, part);
   return hipGetLastError();
 }
 
-hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
+template <int D>
+hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
                               int key_splits, const float2* part, float* score, hipStream_t st) {
   const int n = ks.n_c + ks.c;
   constexpr int kKeysPerBlock = 32 * kColsumKeyTiles * kColsumWaves;
   dim3 grid((n + kKeysPerBlock - 1) / kKeysPerBlock, dm.Hkv, dm.B * dm.L);
-  constexpr int kLdsBytes = 2 * kColsumQRows * (kPitchK * 2 + 4);  // two buffers of rows and normalisers: 70 KB
+  constexpr int kLdsBytes = 2 * kColsumQRows * (Geo<D>::kPitchK * 2 + 4);  // two buffers of rows and normalisers: 70 KB at 128
   static LdsLimit limit_stepwise, limit_any;
   const bool stepwise = rows % kColsumQRows == 0;
-  const auto kern = stepwise ? colsum_mfma_kernel<true> : colsum_mfma_kernel<false>;
+  const auto kern = stepwise ? colsum_mfma_kernel<D, true> : colsum_mfma_kernel<D, false>;
   const hipError_t e = raise_lds_limit(stepwise ? limit_stepwise : limit_any, reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, grid, dim3(kColsumWaves * 64), kLdsBytes, st, dm, q, rows, ks, causal, lse, key_splits, part,
                      score);
   return hipGetLastError();
+}
+
+template <int D>
+hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, float* workspace, size_t workspace_floats,
+                              float* score, hipStream_t st) {
+  const int n = ks.n_c + ks.c;
+  // a short text over a candidate set that a workgroup's registers can hold one row strip of: one product
+  // per (row, key)
+  if (instr_strip_supported(dm, q, rows, ks, workspace_floats))
+    return launch_instr_strip(dm, q, rows, ks, workspace, workspace_floats, score, st);
+  // otherwise two passes over the keys; few query rows per KV group: one fused launch
+  const int total_rows = dm.G * rows;
+  const int tiles32 = (n + 31) / 32;
+  if (total_rows <= 128 && instr_fused_lds_bytes<D, 4, 1, 8>(n) <= kFusedLdsBudget)
+    return instr_fused_launch<D, 4, 1, 8, 0>(dm, q, rows, ks, score, st);
+  if (total_rows <= 256 && tiles32 <= 8 * fused_key_tiles_in_regs<D>() && instr_fused_lds_bytes<D, 8, 1, 8>(n) <= kFusedLdsBudget)
+    return instr_fused_launch<D, 8, 1, 8, fused_key_tiles_in_regs<D>()>(dm, q, rows, ks, score, st);
+  if (total_rows <= 256 && instr_fused_lds_bytes<D, 8, 2, 16>(n) <= kFusedLdsBudget)
+    return instr_fused_launch<D, 8, 2, 16, 0>(dm, q, rows, ks, score, st);
+  const int tiles = (n + kTileN - 1) / kTileN;
+  int splits = (tiles + 3) / 4;  // about four key tiles per workgroup
+  splits = splits < 1 ? 1 : (splits > kMaxKeySplits ? kMaxKeySplits : splits);
+  const int64_t rows_total = static_cast<int64_t>(dm.B) * dm.L * dm.Hq * rows;
+  if (static_cast<size_t>(2) * splits * rows_total > workspace_floats) return hipErrorInvalidValue;
+  float2* part = reinterpret_cast<float2*>(workspace);
+  View none{nullptr, 0, 0, 0, 0};
+  hipError_t e = attn_launch<D>(dm, q, rows, ks, ks, /*causal=*/0, none, nullptr, nullptr, splits, part, st, -1, 0.f);
+  if (e != hipSuccess) return e;
+  if (splits > 1) {  // one normaliser per row, in place of the first range's pairs
+    hipLaunchKernelGGL(merge_partials_kernel, dim3(static_cast<unsigned>((rows_total + 255) / 256)), dim3(256), 0, st, part,
+                       splits, rows_total);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return colsum_launch<D>(dm, q, rows, ks, /*causal=*/0, nullptr, 1, part, score, st);
+}
+
+}  // namespace
+
+bool mfma_path_supported(int dtype, const Dims& dm) { return dtype == CITRUS_BF16 && (dm.D == 64 || dm.D == 128); }
+
+bool attn_mfma_emits_cache_lse(const Segments& ks, int causal, View out) {
+  return out.ptr != nullptr && causal != 0 && ks.n_c > 0 && ks.n_c % 32 == 0;
+}
+
+hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
+                            float* lse, float* lse_cache, int key_splits, float2* part, hipStream_t st,
+                            int q_rope_pos0, float rope_base) {
+  const auto launch = dm.D == 64 ? attn_launch<64> : attn_launch<128>;
+  return launch(dm, q, rows, ks, vs, causal, out, lse, lse_cache, key_splits, part, st, q_rope_pos0, rope_base);
+}
+
+hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
+                              int key_splits, const float2* part, float* score, hipStream_t st) {
+  const auto launch = dm.D == 64 ? colsum_launch<64> : colsum_launch<128>;
+  return launch(dm, q, rows, ks, causal, lse, key_splits, part, score, st);
 }
 
 // Instruction score in two launches: partial log-sum-exp over ranges of key tiles (enough
@@ -1396,36 +1507,8 @@ size_t instr_score_mfma_workspace_floats(const Dims& dm, int rows, int n) {
 
 hipError_t launch_instr_score_mfma(const Dims& dm, View q, int rows, Segments ks, float* workspace,
                                    size_t workspace_floats, float* score, hipStream_t st) {
-  const int n = ks.n_c + ks.c;
-  // a short text over a candidate set that a workgroup's registers can hold one row strip of: one product
-  // per (row, key)
-  if (instr_strip_supported(dm, q, rows, ks, workspace_floats))
-    return launch_instr_strip(dm, q, rows, ks, workspace, workspace_floats, score, st);
-  // otherwise two passes over the keys; few query rows per KV group: one fused launch
-  const int total_rows = dm.G * rows;
-  const int tiles32 = (n + 31) / 32;
-  if (total_rows <= 128 && instr_fused_lds_bytes<4, 1, 8>(n) <= kFusedLdsBudget)
-    return instr_fused_launch<4, 1, 8, 0>(dm, q, rows, ks, score, st);
-  if (total_rows <= 256 && tiles32 <= 8 * kFusedKeyTilesInRegs && instr_fused_lds_bytes<8, 1, 8>(n) <= kFusedLdsBudget)
-    return instr_fused_launch<8, 1, 8, kFusedKeyTilesInRegs>(dm, q, rows, ks, score, st);
-  if (total_rows <= 256 && instr_fused_lds_bytes<8, 2, 16>(n) <= kFusedLdsBudget)
-    return instr_fused_launch<8, 2, 16, 0>(dm, q, rows, ks, score, st);
-  const int tiles = (n + kTileN - 1) / kTileN;
-  int splits = (tiles + 3) / 4;  // about four key tiles per workgroup
-  splits = splits < 1 ? 1 : (splits > kMaxKeySplits ? kMaxKeySplits : splits);
-  const int64_t rows_total = static_cast<int64_t>(dm.B) * dm.L * dm.Hq * rows;
-  if (static_cast<size_t>(2) * splits * rows_total > workspace_floats) return hipErrorInvalidValue;
-  float2* part = reinterpret_cast<float2*>(workspace);
-  View none{nullptr, 0, 0, 0, 0};
-  hipError_t e = launch_attn_mfma(dm, q, rows, ks, ks, /*causal=*/0, none, nullptr, nullptr, splits, part, st);
-  if (e != hipSuccess) return e;
-  if (splits > 1) {  // one normaliser per row, in place of the first range's pairs
-    hipLaunchKernelGGL(merge_partials_kernel, dim3(static_cast<unsigned>((rows_total + 255) / 256)), dim3(256), 0, st, part,
-                       splits, rows_total);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return launch_colsum_mfma(dm, q, rows, ks, /*causal=*/0, nullptr, 1, part, score, st);
+  const auto launch = dm.D == 64 ? instr_score_launch<64> : instr_score_launch<128>;
+  return launch(dm, q, rows, ks, workspace, workspace_floats, score, st);
 }
 
 }  // namespace citrus

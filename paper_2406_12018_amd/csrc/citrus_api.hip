@@ -158,20 +158,20 @@ citrus_status check_workspace(const citrus_config* c, const void* ws, size_t byt
   return CITRUS_OK;
 }
 
-// ---- dispatch: MFMA kernels where they apply, generic kernels otherwise ----
+// ---- dispatch: MFMA kernels for bf16, vector kernels for f32 ----
 
 hipError_t run_attn(const citrus_config* c, const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal,
                     View out, float* lse, hipStream_t st) {
   if (mfma_path_supported(c->dtype, dm))
     return launch_attn_mfma(dm, q, rows, ks, vs, causal, out, lse, nullptr, 1, nullptr, st);
-  return launch_attn_generic(c->dtype, dm, q, rows, ks, vs, causal, out, lse, st);
+  return launch_attn_f32(dm, q, rows, ks, vs, causal, out, lse, st);
 }
 
 hipError_t run_colsum(const citrus_config* c, const Dims& dm, View q, int rows, Segments ks, int causal,
                       const float* lse, float* score, hipStream_t st) {
   if (mfma_path_supported(c->dtype, dm))
     return launch_colsum_mfma(dm, q, rows, ks, causal, lse, 1, nullptr, score, st);
-  return launch_colsum_generic(c->dtype, dm, q, rows, ks, causal, lse, score, st);
+  return launch_colsum_f32(dm, q, rows, ks, causal, lse, score, st);
 }
 
 // Unchecked bodies shared by the public entry points and the chunk loop.

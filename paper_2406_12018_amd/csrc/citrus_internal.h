@@ -35,16 +35,16 @@ struct Segments {
 
 inline citrus_status hip_status(hipError_t e) { return e == hipSuccess ? CITRUS_OK : CITRUS_ERR_DEVICE; }
 
-// ---- generic VALU kernels (f32 and bf16 element types), attn_generic.hip ----
+// ---- vector kernels of the f32 mode, attn_generic.hip ----
 // rows: number of query rows per head; causal != 0 -> row t sees candidates j <= n_c + t.
 // out may be NULL (log-sum-exp only); lse may be NULL.
-hipError_t launch_attn_generic(int dtype, const Dims& dm, View q, int rows, Segments kseg, Segments vseg, int causal,
-                               View out, float* lse, hipStream_t st);
+hipError_t launch_attn_f32(const Dims& dm, View q, int rows, Segments kseg, Segments vseg, int causal, View out,
+                           float* lse, hipStream_t st);
 // score[b,l,g,j] = sum_{h in g} sum_{t<rows} exp(scale*q.k - lse[b,l,h,t]) (0 where masked)
-hipError_t launch_colsum_generic(int dtype, const Dims& dm, View q, int rows, Segments kseg, int causal,
-                                 const float* lse, float* score, hipStream_t st);
+hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments kseg, int causal, const float* lse,
+                             float* score, hipStream_t st);
 
-// ---- bf16 MFMA kernels (head_dim 128), attn_mfma.hip ----
+// ---- bf16 MFMA kernels (head_dim 64 and 128: every bf16 configuration), attn_mfma.hip ----
 bool mfma_path_supported(int dtype, const Dims& dm);
 // key_splits > 1: log-sum-exp only, one partial (log2-domain maximum, sum) pair per key range
 // and row in part[split][B*L*Hq*rows]; key_splits == 1: out and/or lse (natural log) as given.
@@ -78,7 +78,7 @@ size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n);
 hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments kseg, float* workspace, size_t workspace_floats,
                               float* score, hipStream_t st);
 
-// ---- bf16 MFMA decoding step (head_dim 128), decode_attn.hip ----
+// ---- bf16 MFMA decoding step (at most 32 query heads per KV head), decode_attn.hip ----
 bool decode_mfma_supported(int dtype, const Dims& dm);
 size_t decode_mfma_workspace_floats(const Dims& dm);
 // One query row per head over [cache ; the new token's row] (kseg.c == 1); workspace holds the partial

@@ -487,7 +487,7 @@ static size_t strip_partial_floats(const Dims& dm, int rows, int n) {
 
 bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& ks, size_t workspace_floats) {
   const int n = ks.n_c + ks.c;
-  if (n < 1 || n > kStripMaxKeysLong || rows < 1 || dm.G * rows > kStripMaxRows) return false;
+  if (dm.D != D || n < 1 || n > kStripMaxKeysLong || rows < 1 || dm.G * rows > kStripMaxRows) return false;
   // worth it while the workgroups (one per KV head and strip) fit the chip twice; see the top of this file
   const int strip_rows = (n <= kStripMaxKeysShort && dm.G * rows > 32) ? 64 : 32;
   const int64_t groups = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv * ((dm.G * rows + strip_rows - 1) / strip_rows);

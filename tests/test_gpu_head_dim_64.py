@@ -1,0 +1,94 @@
+"""bf16 with head dimension 64 on the matrix-core kernels: every kernel a step can reach, at the edges of tiles and row
+blocks and on both sides of the scorer's and the decoding step's choices, against the CPU oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2406_12018_amd as api
+from oracle import citrus_oracle as orc
+
+from helpers import assert_close, np64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+D = 64
+
+
+def rand(shape, seed, scale=1.0):
+    g = torch.Generator(device="cpu").manual_seed(seed)
+    return (torch.randn(shape, generator=g, dtype=torch.float32) * scale).to(torch.bfloat16).to(DEV)
+
+
+# B, L, Hq, Hkv, c, n_c, n_i, spread of q and k
+STEPS = [
+    (1, 1, 1, 1, 1, 0, 1, 1.0),         # one key, one row
+    (1, 2, 4, 4, 33, 31, 31, 1.0),      # one head per group: eight row tiles per workgroup, ragged everywhere
+    (1, 1, 6, 2, 64, 64, 32, 1.0),      # three heads per group, tiles that end exactly
+    (2, 1, 8, 2, 129, 127, 64, 1.0),    # a tile that holds the cache / chunk boundary and one past a row block
+    (1, 1, 8, 4, 256, 960, 128, 1.0),   # 256 rows per KV group
+    (1, 1, 8, 1, 128, 1000, 128, 0.5),  # 1024 rows per KV group: two launches, staged rows in whole chunks
+    (1, 1, 7, 1, 95, 3000, 36, 0.5),    # seven heads per group, long ragged cache
+]
+
+
+@pytest.mark.parametrize("shape", STEPS, ids=lambda s: "-".join(str(x) for x in s[:7]))
+def test_step_kernels(shape):
+    B, L, Hq, Hkv, c, n_c, n_i, s = shape
+    print(f"head_dim 64 step {shape}", flush=True)
+    cfg = api.Config(batch=B, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=D, chunk_len=c, budget=n_c + 3, instr_len=n_i)
+    ws = api.alloc_workspace(cfg)
+    q, qi = rand((B, L, Hq, c, D), 1, s), rand((B, L, Hq, n_i, D), 2, s)
+    kc, vc = rand((B, L, Hkv, n_c + 3, D), 3, s), rand((B, L, Hkv, n_c + 3, D), 4)
+    k, v = rand((B, L, Hkv, c, D), 5, s), rand((B, L, Hkv, c, D), 6)
+    lse = torch.empty((B, L, Hq, c), dtype=torch.float32, device=DEV)
+    lm = torch.empty((B, L, Hkv, n_c + c), dtype=torch.float32, device=DEV)
+    out = api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v, lse=lse, lm_score=lm, workspace=ws)
+    score = api.citrus_instr_score(cfg, qi, kc, n_c, k, workspace=ws)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for l in range(L):
+            kcat = np.concatenate([np64(kc[b, l, :, :n_c]), np64(k[b, l])], axis=1)
+            vcat = np.concatenate([np64(vc[b, l, :, :n_c]), np64(v[b, l])], axis=1)
+            o_ref, lse_ref, _ = orc.chunk_attn(np64(q[b, l]), kcat, vcat, n_c)
+            assert_close(np64(out[b, l]), o_ref, "bf16", f"out b{b} l{l}")
+            assert_close(np64(lse[b, l]), lse_ref, "bf16", f"lse b{b} l{l}")
+            assert_close(np64(lm[b, l]), orc.lm_score(np64(q[b, l]), kcat, n_c), "bf16", f"lm_score b{b} l{l}")
+            assert_close(np64(score[b, l]), orc.instr_score(np64(qi[b, l]), kcat), "bf16", f"score b{b} l{l}")
+    assert torch.equal(out, api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v, workspace=ws))
+    assert torch.equal(score, api.citrus_instr_score(cfg, qi, kc, n_c, k, workspace=ws))
+
+
+@pytest.mark.parametrize("G,n", [(1, 0), (4, 31), (8, 32), (7, 700), (4, 2500), (32, 65)])
+def test_decode_step(G, n):
+    """One token over n cached states, in one and in several key ranges."""
+    print(f"head_dim 64 decode G={G} n={n}", flush=True)
+    Hkv = 2
+    cfg = api.Config(batch=1, layers=1, q_heads=G * Hkv, kv_heads=Hkv, head_dim=D, chunk_len=32, budget=n + 2, instr_len=8)
+    ws = api.alloc_workspace(cfg)
+    q, kn, vn = rand((1, 1, G * Hkv, 1, D), 1), rand((1, 1, Hkv, 1, D), 2), rand((1, 1, Hkv, 1, D), 3)
+    kc, vc = rand((1, 1, Hkv, n + 2, D), 4), rand((1, 1, Hkv, n + 2, D), 5)
+    ref, *_ = orc.chunk_attn(np64(q[0, 0]), np.concatenate([np64(kc[0, 0, :, :n]), np64(kn[0, 0])], axis=1),
+                             np.concatenate([np64(vc[0, 0, :, :n]), np64(vn[0, 0])], axis=1), n)
+    out = api.citrus_decode_step(cfg, q, kn, vn, kc, vc, n, workspace=ws)
+    torch.cuda.synchronize()
+    assert_close(np64(out[0, 0]), ref, "bf16", "out")
+    assert torch.equal(kc[:, :, :, n:n + 1], kn) and torch.equal(vc[:, :, :, n:n + 1], vn)
+
+
+@pytest.mark.parametrize("c,n_c", [(40, 0), (70, 90)])
+def test_position_shift_rotates_queries_in_the_attention_kernel(c, n_c):
+    """Two chunks with the position shift against rotated copies made by citrus_rope (itself checked against the oracle)."""
+    base = dict(batch=1, layers=2, q_heads=4, kv_heads=2, head_dim=D, chunk_len=c, budget=max(n_c, 8), instr_len=8)
+    shift, plain = api.Config(position_shift=1, **base), api.Config(cache_capacity=n_c + c, **base)
+    q, k, v = rand((1, 2, 4, c, D), 1), rand((1, 2, 2, c, D), 2), rand((1, 2, 2, c, D), 3)
+    qi, state = rand((1, 2, 4, 8, D), 4), api.DocumentState.allocate(shift)
+    state.k_cache[0][:, :, :, :n_c], state.v_cache[0][:, :, :, :n_c] = rand((1, 2, 2, n_c, D), 5), rand((1, 2, 2, n_c, D), 6)
+    state.cache_len = n_c
+    kc, vc = state.k_cache[0].clone(), state.v_cache[0].clone()
+    out = torch.empty_like(q)
+    api.citrus_process_document(shift, state, api.alloc_workspace(shift), doc=api.resident_doc(shift, q, k, v, qi, out))
+    want = api.citrus_chunk_attn(plain, api.citrus_rope(plain, q, n_c), api.citrus_rope(plain, kc, 0), vc, n_c,
+                                 api.citrus_rope(plain, k, n_c), v)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
