@@ -451,8 +451,8 @@ def citrus_process_document(cfg: Config, state: DocumentState, workspace, *, doc
     if (doc is None) == (provider is None):
         raise ValueError("give exactly one of doc / provider")
     if doc is not None:
-        fn = C.cast(lib.citrus_resident_provider, C.c_void_p)
-        user = C.cast(C.pointer(doc), C.c_void_p)
+        fn = C.c_void_p.from_buffer(lib.citrus_resident_provider)  # the function's address
+        user = C.byref(doc)
         keep = doc
     else:
         def _cb(_user, index, _stream_ptr, io_ptr):
@@ -461,7 +461,8 @@ def citrus_process_document(cfg: Config, state: DocumentState, workspace, *, doc
             except Exception:  # never let an exception cross the C boundary
                 return -1
         keep = PROVIDER(_cb)
-        fn = C.cast(keep, C.c_void_p)
+        # (ctypes.cast would leave a reference cycle behind, and with it whatever the provider holds)
+        fn = C.c_void_p.from_buffer(keep)
         user = None
     arr = lambda ts: (CTensor * 2)(tensor(ts[0]), tensor(ts[1]))
     kc, vc = arr(state.k_cache), arr(state.v_cache)
