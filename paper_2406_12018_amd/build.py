@@ -17,7 +17,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libcitrus.so")
 SOURCES = ["citrus_api.hip", "attn_generic.hip", "attn_mfma.hip", "instr_strip.hip", "decode_attn.hip", "rope.hip", "select_compact.hip", "probe.hip"]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # keep MFMA accumulators in VGPRs: the softmax rescale touches them with vector ALU ops, and
     # AGPR-resident accumulators cost a copy per register and per loop iteration

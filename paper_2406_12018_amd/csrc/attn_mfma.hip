@@ -20,7 +20,9 @@
 // Computing S^T (keys x queries) puts one query per lane, so softmax row
 // reductions are in-lane plus one exchange with lane l ^ 32, and the S^T
 // accumulators are directly the B operand (P^T) of the second product.
+#pragma clang diagnostic ignored "-Winline-asm"
 #include <type_traits>
+#include <utility>
 
 #include "citrus_internal.h"
 #include "rope_math.h"
@@ -155,13 +157,70 @@ __device__ inline void barrier_after_lds_fill() {
   __syncthreads();
 }
 
+// One LDS-direct load (64 lanes x 16 bytes of global memory to 1 KB of consecutive LDS) as asm: the compiler waits
+// for every such load it can see (vmcnt(0)) in front of the next LDS read that might alias it, i.e. a tile requested
+// between the MFMAs of one half step would be waited for at the start of the next, long before the barrier that
+// publishes it.  Loads issued here are waited for by the barrier helpers alone.  lds + LDS_OFF: byte address.
+template <int LDS_OFF>
+__device__ inline void load_lds_unwatched(const i32x4& rsrc, uint32_t lds, int lane_off, int scalar_off) {
+  asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off), "n"(LDS_OFF)
+               : "m0", "scc");
+}
+// Buffer resource of `bytes` bytes at p as the four words the asm above takes.
+__device__ inline i32x4 buffer_words(const void* p, int bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return i32x4{static_cast<int>(a), static_cast<int>(a >> 32) & 0xffff, bytes, kBufferFlags};
+}
+
+// All but the newest LEFT loads of this wave have landed, and then every wave's have (PUBLISH: its LDS accesses are
+// through as well).
+template <int LEFT, bool PUBLISH>
+__device__ inline void wait_loads_and_barrier() {
+  if constexpr (PUBLISH)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LEFT) : "memory");
+  else
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(LEFT) : "memory");
+}
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+// lanes 0..31: first = own lo_half, second = lo_half of lane l + 32; lanes 32..63: first = hi_half of lane l - 32,
+// second = own hi_half
+__device__ inline void swap_halves(uint32_t lo_half, uint32_t hi_half, uint32_t& first, uint32_t& second) {
+  const auto r = __builtin_amdgcn_permlane32_swap(lo_half, hi_half, false, false);
+  first = r[0];
+  second = r[1];
+}
+__device__ inline void lds_writes_and_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// K and V tiles of the attention kernel in LDS.  A 1 KB load instruction fills one block of kR whole rows (a lane group
+// reads one row of global memory: lanes of different rows next to each other would cost the address path a multiple);
+// inside a row, segment seg (16 bytes) is at position seg ^ (kStep x (row / kRowStep % 4)), and blocks are 16 bytes
+// further apart than they are long.  The XOR touches two bits of the segment only, so the operand reads of a lane need
+// four (K) and two (V) base registers, and every address in the key loop is one of them plus a constant: no instruction
+// of the loop forms an address.  Sixteen consecutive rows of one segment (a cycle of a key operand) and four rows of two
+// segments (a 16-lane group of a transpose read) fall into different banks.
+template <int D>
+struct Lay {
+  static constexpr int kR = Geo<D>::kRowsPerLoad;
+  static constexpr int kStep = D == 128 ? 4 : 2, kRowStep = D == 128 ? 1 : 2;
+  static constexpr int kBlock = 1024 + 16;
+  static constexpr int kHalf = 32 / kR * kBlock;  // 32 rows
+  static constexpr int kTile = 2 * kHalf;
+  __device__ static constexpr int swz(int row) { return kStep * (row / kRowStep % 4); }
+  __device__ static constexpr int at(int row, int seg) {
+    return row / kR * kBlock + row % kR * Geo<D>::kRowBytes + (seg ^ swz(row)) * 16;
+  }
+};
+
 // How the waves of a block split (head, 32-row tile) tasks inside one KV group.
 struct TaskShape {
   int heads_per_block;  // 4, 2 or 1 query heads of the group
   int tiles_per_block;  // kWaves / heads_per_block row tiles of 32
 };
 __host__ __device__ inline TaskShape task_shape(int G, int waves = kWaves) {
-  const int hpb = (G % 4 == 0) ? 4 : ((G % 2 == 0) ? 2 : 1);
+  const int hpb = (G % 4 == 0 && waves >= 4) ? 4 : ((G % 2 == 0 && waves >= 2) ? 2 : 1);
   return TaskShape{hpb, waves / hpb};
 }
 
@@ -373,163 +432,223 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
   }  // pass
 }
 
+// Division by a number that is known at launch: n / divisor for 0 <= n < 2^31 by a multiplication.
+struct FastDiv {
+  int divisor;
+  uint32_t mul;
+  int shift;
+  __device__ int quotient(int n) const {
+    return static_cast<int>((__umulhi(static_cast<uint32_t>(n), mul) + static_cast<uint32_t>(n)) >> shift);
+  }
+};
+inline FastDiv fast_div(int d) {
+  FastDiv f{d, 0, 0};
+  while ((int64_t{1} << f.shift) < d) ++f.shift;
+  f.mul = static_cast<uint32_t>(((uint64_t{1} << 32) * ((uint64_t{1} << f.shift) - d)) / d + 1);
+  return f;
+}
+// A tensor as the attention kernel addresses it: everything in bytes.
+struct UnitView {
+  const char* ptr;
+  int64_t sb, sl, sh;
+  int ss;
+};
+inline UnitView unit_view(const View& v) {
+  return UnitView{static_cast<const char*>(v.ptr), 2 * v.sb, 2 * v.sl, 2 * v.sh, static_cast<int>(2 * v.ss)};
+}
+// What a workgroup of the attention kernel works on, prepared on the host: a wave issues one instruction in eight
+// cycles, and with divisions by runtime numbers and per-element strides the set-up took 830 of them.
+struct AttnArgs {
+  UnitView q, out, k_cache, k_chunk, v_cache, v_chunk;
+  int rows, n_c, c, causal, q_heads;
+  int log_heads;   // 2^log_heads query heads of a group per workgroup
+  int row_blocks;  // of a head
+  int per_xcd;     // workgroups per XCD, 0: not a whole number
+  FastDiv slots, head_groups, kv_heads, layers;  // workgroup -> (row block slot, head group, KV head, layer)
+  float c2, inv_c2;  // softmax scale in the log2 domain
+  float *lse, *lse_cache;
+  int q_rope_pos0;
+  float rope_log2_base;
+};
+
 // The same attention, with output, as a software pipeline over half tiles of 32 keys: in step h the
 // MFMAs of S^T(h + 1) = K.Q^T and of O^T += V^T.P^T(h - 1) are issued between the exponentials of
 // half tile h, so that inside ONE wave the matrix pipe, the vector pipe and the LDS reads run at
 // the same time instead of taking turns (the order is fixed with volatile asm statements, see above).
 // K tiles are fetched one 64-key tile further ahead than V tiles; one barrier per 64 keys.
-template <int D, int WAVES, bool ROTATE_Q>
-__device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, int rows, const Segments& ks,
-                                               const Segments& vs, int causal, const View& out, float* lse,
-                                               float* lse_cache, int q_rope_pos0, float rope_log2_base) {
+//
+// What bounds it.  A wave issues at most one instruction, of whatever kind, per 8 cycles (measured: 64 independent
+// v_fma, v_max or s_mov of one wave take 505 to 540 cycles, of two waves of a SIMD the same), so a half step costs a wave
+// 8 cycles per instruction next to the 512 its 16 MFMAs hold the matrix pipe.  The steady half step is therefore kept at
+// 112 to 114 instructions (it had 159 to 190): LDS addresses are register + constant (Lay), a tile lies in one segment
+// and is always fetched (out-of-range rows read as zeros), masks and segment changes sit behind branches that are not
+// taken, the vote on the row maxima is taken a step early, and one wait covers all operands of a product.  Outside the
+// loop it is the same count: set-up from host-made numbers (AttnArgs), output rows through buffer stores.  The two waves
+// of a SIMD meet at a barrier every 64 keys; one of the two (waves 4..7) passes it in front of its vector-only tail, the
+// other behind it, so that their MFMA phases alternate instead of colliding.
+// Measured, 32/8 heads, 512 rows over 768 + 512 states: 64-key tile 3750 -> 3090 cycles (2048 of them MFMA); 32 layers in
+// one launch 330 -> 305 us inside a loop with other kernels, 341 -> 318 us back to back (the chip then clocks at 1.75
+// instead of 2.4 GHz: it is power that bounds a full chip); empty cache 141 -> 128 us; 16 layers of 32/32 heads, 1024
+// rows over 1024 + 1024 states 493 -> 451 us; 64/8 heads, 2048 rows over 4096 + 2048 states 1286 -> 1227 us; head_dim 64,
+// 8 layers 54 -> 49 us.
+template <int D, int WAVES, int KS, bool ROTATE_Q>
+__device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   typedef Geo<D> T;
-  constexpr int kRowBytes = T::kRowBytes, kTileBytes = T::kTileBytes;
-  constexpr bool HAS_PV = true;
-  constexpr int key_splits = 1;
-  float2* const part = nullptr;
-  __shared__ __attribute__((aligned(1024))) char k_s[2 * kTileBytes];  // double-buffered tiles
-  __shared__ __attribute__((aligned(1024))) char v_s[HAS_PV ? 2 * kTileBytes : 16];
-  extern __shared__ __attribute__((aligned(1024))) char q_stage[];  // [WAVES][32 rows][kRowBytes], dynamic
+  typedef Lay<D> Y;
+  constexpr int kRowBytes = T::kRowBytes;
+  static_assert(KS == 1 || KS == 2, "key groups");
+  constexpr int kRowWaves = WAVES / KS;  // waves of a key group: one 32-row tile each
+  // per key group: two K tiles, then two V tiles (double buffers)
+  __shared__ __attribute__((aligned(1024))) char ring[KS * 4 * Y::kTile];
+  // [kRowWaves] query row tiles, laid out like half a key tile.  Two key groups: these pass through the V buffers that
+  // are filled last, and this holds the rows' statistics.
+  extern __shared__ __attribute__((aligned(1024))) char q_stage[];
 
   const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
   const int col = lane % 32, grp = lane / 32;
   constexpr int kR = T::kRowsPerLoad;
-  constexpr int kFillRows = kTileN / WAVES;  // rows of a tile each wave fetches: kR per instruction
-  constexpr int kFillInstr = kFillRows / kR;
-  static_assert(kFillInstr >= 1 && kFillInstr <= 2, "slots between the MFMAs of a step for a wave's fetches");
-  const TaskShape ts = task_shape(dm.G, WAVES);
-  const int head_groups = dm.G / ts.heads_per_block;
-  const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
-  const int row_blocks = (rows + rows_per_block - 1) / rows_per_block;
+  constexpr int kFillRows = kTileN / kRowWaves;         // rows of a tile each wave of the group fetches
+  constexpr int kPer = kFillRows / kR;                  // load instructions per wave and tile
+  constexpr int kSlots = T::kKk / 2;                    // places between the MFMAs of a product that take loads
+  constexpr int kPerSlot = (kPer + kSlots - 1) / kSlots;
+  static_assert(kPer >= 1, "every wave of a group fetches");
+  const int rows_per_block = (kRowWaves >> a.log_heads) * kRowsPerWave;
   // Workgroups are handed to the 8 XCDs round-robin by their linear id.  Remap so that the
   // workgroups of one (document, layer, KV head), which read the same K/V, land on ONE XCD and
   // share its L2; within a unit the row blocks with the longest causal range come first.
-  int logical = blockIdx.x;
-  const int total = gridDim.x;
-  if (total % kXcds == 0) logical = (blockIdx.x % kXcds) * (total / kXcds) + blockIdx.x / kXcds;
-  // With key_splits > 1 (log-sum-exp only) each workgroup covers one contiguous range of key
-  // tiles and writes a partial (running maximum, sum) pair per row; the consumer merges them.
-  const int sp = logical % key_splits;
-  logical /= key_splits;
+  const int logical = a.per_xcd > 0 ? (blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds : blockIdx.x;
   // Causal attention: a workgroup takes the row block with the longest key range still free and then
-  // its mirror image (the shortest), so every workgroup does the same number of key tiles.
-  const bool paired = causal != 0 && key_splits == 1;
-  const int rb_slots = paired ? (row_blocks + 1) / 2 : row_blocks;
-  const int rb_first = row_blocks - 1 - logical % rb_slots;
-  const int rb_second = row_blocks - 1 - rb_first;
+  // its mirror image (the shortest), so every workgroup does the same number of key tiles.  With two key groups
+  // (launches that do not fill the chip) a row block is a workgroup of its own.
+  const bool paired = a.causal != 0 && KS == 1;
+  const int of_slot = a.slots.quotient(logical), of_hg = a.head_groups.quotient(of_slot), of_g = a.kv_heads.quotient(of_hg);
+  const int rb_first = a.row_blocks - 1 - (logical - of_slot * a.slots.divisor);
+  const int rb_second = a.row_blocks - 1 - rb_first;
   const int passes = (paired && rb_second != rb_first) ? 2 : 1;
-  const int hg = (logical / rb_slots) % head_groups;
-  const int g = (logical / (rb_slots * head_groups)) % dm.Hkv;
-  const int bl = logical / (rb_slots * head_groups * dm.Hkv);
-  const int b = bl / dm.L, l = bl % dm.L;
+  const int hg = of_slot - of_hg * a.head_groups.divisor;
+  const int g = of_hg - of_g * a.kv_heads.divisor;
+  const int bl = of_g;
+  const int b = a.layers.quotient(bl), l = bl - b * a.layers.divisor;
   const int wu = __builtin_amdgcn_readfirstlane(w);  // the wave's index as a scalar: what depends on it stays scalar
-  const int h = g * dm.G + hg * ts.heads_per_block + (wu % ts.heads_per_block);
-  const int n_c = ks.n_c;
-  const int n = n_c + ks.c;
+  const int kg = KS == 1 ? 0 : wu / kRowWaves;       // key group: tiles kg, kg + KS, ... of the block's key range
+  const int wr = KS == 1 ? wu : wu % kRowWaves;
+  char* const k_s = ring + kg * 4 * Y::kTile;
+  char* const v_s = k_s + 2 * Y::kTile;
+  const int h = ((g * a.head_groups.divisor + hg) << a.log_heads) + (wr & ((1 << a.log_heads) - 1));
+  const int n_c = a.n_c;
+  auto unit = [&](const UnitView& v, int head) { return v.ptr + (b * v.sb + l * v.sl + head * v.sh); };
 
   // ---- global -> LDS staging of one 64-key tile, without a stop in registers ----
-  // buffer_load ... lds: a wave-level instruction moves 64 x 16 B from per-lane global addresses
-  // to 1 KB of consecutive LDS, i.e. four (head_dim 64: eight) unpadded rows.  The swizzle of a row's
-  // segments (Geo) is realised by the loading lane, which fetches global segment (its LDS position) ^ swz(row).
-  // Rows that fall outside the candidates re-read the last row (finite values; their logits are masked).
-  const int k_ss_cache = static_cast<int>(ks.cache.ss), k_ss_chunk = static_cast<int>(ks.chunk.ss);
-  const int v_ss_cache = static_cast<int>(vs.cache.ss), v_ss_chunk = static_cast<int>(vs.chunk.ss);
-  auto seg_bytes = [](int rows_, int ss_) { return rows_ > 0 ? ((rows_ - 1) * ss_ + D) * 2 : 0; };
-  const __amdgpu_buffer_rsrc_t k_rs_cache = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(unit_ptr(ks.cache, b, l, g)), 0, seg_bytes(n_c, k_ss_cache), kBufferFlags);
-  const __amdgpu_buffer_rsrc_t k_rs_chunk = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(unit_ptr(ks.chunk, b, l, g)), 0, seg_bytes(ks.c, k_ss_chunk), kBufferFlags);
-  const __amdgpu_buffer_rsrc_t v_rs_cache = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(unit_ptr(HAS_PV ? vs.cache : ks.cache, b, l, g)), 0, seg_bytes(n_c, v_ss_cache), kBufferFlags);
-  const __amdgpu_buffer_rsrc_t v_rs_chunk = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(unit_ptr(HAS_PV ? vs.chunk : ks.chunk, b, l, g)), 0, seg_bytes(ks.c, v_ss_chunk), kBufferFlags);
-  const int fill_row_c = kFillRows * wu + lane / T::kSegs;  // tile row this lane fills with instruction 0
-  const int fill_seg16_c = ((lane % T::kSegs) ^ T::swz(lane / T::kSegs)) * 16;  // byte offset of its global segment, before ^ c_i
-  // instruction i covers rows r = kFillRows wu + kR i .. + kR - 1; the lane-independent part of swz(row)
-  auto swz16 = [&](int i) { return T::swz(kFillRows * wu + kR * i) * 16; };
-  typedef __attribute__((address_space(3))) void* lds_void_ptr;
-  auto fill4 = [&](char* lds_tile, __amdgpu_buffer_rsrc_t rs_cache, __amdgpu_buffer_rsrc_t rs_chunk, int ss_cache,
-                   int ss_chunk, int j0) {
-    const bool simple = (j0 + kTileN <= n_c) || (j0 >= n_c && j0 + kTileN <= n);  // block-uniform
-    // the per-lane offsets are recomputed at every fill: hoisted out of the loop they would occupy
-    // registers the pipeline needs (the empty asm hides their loop invariance from the optimiser)
-    int fill_row = fill_row_c, fill_seg16 = fill_seg16_c;
-    hide_loop_invariance(fill_row, fill_seg16);
-    if (simple) {  // the whole tile lies in one segment: one resource, scalar row offsets
-      const bool in_cache = j0 < n_c;
-      const __amdgpu_buffer_rsrc_t rs = in_cache ? rs_cache : rs_chunk;
-      const int ss2 = (in_cache ? ss_cache : ss_chunk) * 2;
-      const int r0 = in_cache ? j0 : j0 - n_c;
-      const int row_off = fill_row * ss2;
+  // buffer_load ... lds: a wave-level instruction moves 64 x 16 B from per-lane global addresses to 1 KB of consecutive
+  // LDS.  The swizzle of a row's segments (Lay) is realised by the loading lane, which fetches global segment
+  // (its position in the LDS row) ^ swz(row).  The candidates are tiled segment by segment, so that every tile lies in one segment and
+  // is fetched with one buffer resource: the cache's whole tiles, the chunk's tiles, the ragged rest of the cache.  Rows behind the end of a segment are out of
+  // the resource's range and read as zeros; their logits are masked.
+  typedef __attribute__((address_space(3))) char* lds_char_ptr;
+  auto lds_addr = [](char* p) { return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char_ptr)p)); };
+  const int fill_row0 = kFillRows * wr;  // first tile row this wave fetches
+  const int fill_row = fill_row0 + lane / T::kSegs, fill_seg16 = ((lane % T::kSegs) ^ Y::swz(lane / T::kSegs)) * 16;
+  const uint32_t fill_lds0 = lds_addr(k_s) + fill_row0 / kR * Y::kBlock;
+  const int cache_tiles = n_c / kTileN;         // whole ones
+  const int ragged = n_c % kTileN ? 1 : 0;      // one more tile, the last of a row block
+  auto tile_of = [&](int i) { return KS * i + kg; };  // the group's i-th tile
+  auto below = [&](int tiles) { return KS == 1 ? tiles : tiles > kg ? (tiles - kg + KS - 1) / KS : 0; };  // group tiles among the first `tiles`
+  const int i_chunk = below(cache_tiles);  // the group's first tile behind the whole cache tiles
+  // One stream of tiles (K or V): the resource of the segment it is in and, per load instruction, the lane's byte offset
+  // of its next tile (row and segment; the range check covers this offset only, so no part of it is a scalar).
+  struct Stream {
+    i32x4 rs;
+    int step;
+    int voff[kPer];
+  };
+  const int k_ss_cache = a.k_cache.ss, k_ss_chunk = a.k_chunk.ss, v_ss_cache = a.v_cache.ss, v_ss_chunk = a.v_chunk.ss;  // bytes
+  auto seg_words = [&](const UnitView& v, int rows_) { return buffer_words(unit(v, g), rows_ > 0 ? (rows_ - 1) * v.ss + 2 * D : 0); };
+  const i32x4 k_rs_cache = seg_words(a.k_cache, n_c), k_rs_chunk = seg_words(a.k_chunk, a.c);
+  const i32x4 v_rs_cache = seg_words(a.v_cache, n_c), v_rs_chunk = seg_words(a.v_chunk, a.c);
+  auto enter = [&](Stream& s, const i32x4& rs, int ss, int first_row) {  // positions the stream at a tile of a segment
+    s.rs = rs;
+    s.step = kTileN * KS * ss;
 #pragma unroll
-      for (int i = 0; i < kFillInstr; ++i)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_ptr)(lds_tile + (kFillRows * wu + kR * i) * kRowBytes), 16,
-                                                 row_off + (fill_seg16 ^ swz16(i)), (r0 + kR * i) * ss2, 0, 0);
-    } else {  // the tile straddles the cache / chunk boundary or the end of the candidates
+    for (int x = 0; x < kPer; ++x) s.voff[x] = (first_row + fill_row + kR * x) * ss + fill_seg16;
+  };
+  // load x of the stream's next tile into the wave's rows of tile buffer BUF (0, 1: K; 2, 3: V)
+  auto issue_one = [&](const Stream& s, auto buf, auto x) {
+    load_lds_unwatched<decltype(buf)::value * Y::kTile + decltype(x)::value * Y::kBlock>(s.rs, fill_lds0, s.voff[decltype(x)::value], 0);
+  };
+  using std::integral_constant;
+  auto fetch = [&](Stream& s, auto buf) {  // the stream's next tile
+    [&]<int... X>(std::integer_sequence<int, X...>) { (issue_one(s, buf, integral_constant<int, X>{}), ...); }(std::make_integer_sequence<int, kPer>{});
+  };
+  auto advance = [&](Stream& s) {
 #pragma unroll
-      for (int i = 0; i < kFillInstr; ++i) {
-        lds_void_ptr dst = (lds_void_ptr)(lds_tile + (kFillRows * wu + kR * i) * kRowBytes);
-        const int seg = fill_seg16 ^ swz16(i);
-        const int j = min(j0 + fill_row + kR * i, n - 1);
-        if (j < n_c)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_cache, dst, 16, j * ss_cache * 2 + seg, 0, 0, 0);
-        else
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_chunk, dst, 16, (j - n_c) * ss_chunk * 2 + seg, 0, 0, 0);
-      }
-    }
+    for (int x = 0; x < kPer; ++x) s.voff[x] += s.step;
   };
 
-  // per-lane LDS read offsets (bytes inside a tile buffer), swizzle included
+  // per-lane LDS read bases (bytes inside a half tile)
   // A operand of S^T: key row `col`, head_dim segment 2 kk + grp
-  const int f_col = T::swz(col);
-  // k_off(kk) = col * kRowBytes + ((2 kk + grp) ^ f_col) * 16 = k_off0 ^ (32 kk): one register instead of eight
-  const int k_off0 = col * kRowBytes + ((grp ^ f_col) * 16);
-  auto k_off = [&](int kk) { return k_off0 ^ (32 * kk); };
+  int k_base[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) k_base[c] = Y::at(col, Y::kStep * c + grp);
+  auto read_row_operand = [&](const char* half_tile, int kk) {
+    const int c = 2 * kk / Y::kStep;
+    return *reinterpret_cast<const uint4*>(half_tile + k_base[c] + (2 * kk - Y::kStep * c) * 16);
+  };
   // V^T operand through transpose reads.  The 16-lane group q16 = lane / 16 serves MFMA rows
   // 16 (q16 % 2) .. +15 for contraction lane group q16 / 2; output row c' of tile r is head_dim
   // 16 r + (c' % 16) + D / 2 (c' / 16).  Source lane s16 points at 4 consecutive head_dim values of key
-  // row 4 (q16 / 2) + s16 / 4 (+ 8 rd + 16 half + 32 mt): segment 2 r + D / 16 (q16 % 2) + (s16 % 4) / 2.
+  // row 4 (q16 / 2) + s16 / 4 (+ 8 rd + 16 half): segment 2 r + D / 16 (q16 % 2) + (s16 % 4) / 2.
   const int s16 = lane % 16, q16 = lane / 16;
-  const int v_cl = (T::kSegs / 2 * (q16 % 2) + (s16 % 4) / 2) ^ T::swz(4 * (q16 / 2) + s16 / 4);
-  // v_off(e), e = 2 r + rd (swz(row) of read rd differs from read 0 by ^ rd), = v_off0 ^ (16 e)
-  const int v_off0 = (4 * (q16 / 2) + s16 / 4) * kRowBytes + (v_cl * 16) + 8 * (s16 % 2);
-  auto v_off = [&](int e) { return v_off0 ^ (16 * e); };
+  int v_base[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+    v_base[c] = Y::at(4 * (q16 / 2) + s16 / 4, T::kSegs / 2 * (q16 % 2) + Y::kStep * c + (s16 % 4) / 2) + 8 * (s16 % 2);
+  // read rd (keys 8 rd .. + 7) of contraction step `half` for output tile r
+  auto read_v_operand = [&](const char* half_tile, int half, int r, int rd) {
+    const int c = 2 * r / Y::kStep;
+    return lds_read_tr16(half_tile + v_base[c] + (16 * half + 8 * rd) / kR * Y::kBlock + (2 * r - Y::kStep * c) * 16);
+  };
 
-  // The first step of a row block multiplies p_prev = 0 with the second half of V buffer 1, which nothing has
-  // filled yet in the first row block: zero it once (0 x garbage could be NaN).  Published by the barrier
-  // in front of the first operand reads.
-  static_assert(WAVES * 64 * 16 >= 32 * kRowBytes, "one 16-byte store per thread covers the half tile");
-  if (WAVES * 64 * 16 == 32 * kRowBytes || 16 * tid < 32 * kRowBytes)
-    *reinterpret_cast<uint4*>(v_s + kTileBytes + 32 * kRowBytes + 16 * tid) = make_uint4(0u, 0u, 0u, 0u);
+  // The first step of a row block multiplies p_prev = 0 with the second half of V buffer 1, which nothing has filled
+  // yet in the first row block, and rows behind the end of a segment are never multiplied with anything but 0: the V
+  // buffers are zeroed once (0 x garbage could be NaN), in front of the first loads into them.
+  auto zero_v = [&](int from, int to) {
+    for (int at = from + 16 * (tid - kg * kRowWaves * 64); at < to; at += 16 * kRowWaves * 64)
+      *reinterpret_cast<uint4*>(v_s + at) = make_uint4(0u, 0u, 0u, 0u);
+  };
+  // two key groups of four row tiles each: the query rows do not fit next to the tiles and pass through V buffer 1
+  constexpr bool kQueryInV = KS * 4 * Y::kTile + kRowWaves * Y::kHalf > 160 * 1024;
+  static_assert(!kQueryInV || kRowWaves * Y::kHalf <= KS * Y::kTile, "the query rows fit one V buffer of each group");
 
   for (int pass = 0; pass < passes; ++pass) {
   const int rb = pass == 0 ? rb_first : rb_second;
-  const int row0 = (rb * ts.tiles_per_block + wu / ts.heads_per_block) * kRowsPerWave;
+  const int row0 = rb * rows_per_block + (wr >> a.log_heads) * kRowsPerWave;
 
-  // last candidate any row of this block / this wave can see
+  // every key group walks the same number of tiles, so the last one of a group may lie past the block's range (its
+  // logits are masked)
+  const int rows = a.rows;
   const int blk_row_last = min(rows, (rb + 1) * rows_per_block) - 1;
-  const int blk_limit = causal ? n_c + blk_row_last : n - 1;
-  const int all_tiles = blk_limit / kTileN + 1;
-  const int tiles_per_split = (all_tiles + key_splits - 1) / key_splits;
-  const int t_begin = sp * tiles_per_split;
-  const int t_end = min(all_tiles, t_begin + tiles_per_split);
-  const bool wave_active = row0 < rows;
-  const int wave_limit_min = causal ? n_c + row0 : n - 1;           // up to it every row sees everything
+  const int ragged_tile = cache_tiles + (a.causal ? blk_row_last : a.c - 1) / kTileN + 1;  // the ragged rest of the cache, or the end
+  const int i_ragged = below(ragged_tile);
+  const int t_end = (ragged_tile + ragged + KS - 1) / KS;
+  // candidates are numbered tile by tile here: chunk state x is candidate chunk0 + x
+  const int chunk0 = cache_tiles * kTileN;
+  const int wave_limit_min = chunk0 + (a.causal ? row0 : a.c - 1);  // up to it every row sees the chunk's states
+  const int first_masked = min((wave_limit_min + 1) / 32, 2 * ragged_tile);  // half tiles from here on may need a mask
 
   // ---- Q^T operand, kept in registers: q_op[kk] = Q[row0 + col][16 kk + 8 grp ..+7] ----
-  // (loaded further down, behind the requests for the first tiles: a lane reads 16-byte pieces of its
-  // own row, 64 scattered pieces per instruction, which keep the address path busy for a while)
   bf16x8 q_op[T::kKk];
   const int t_lane = max(min(row0 + col, rows - 1), 0);
-  const int limit_lane = causal ? n_c + t_lane : n - 1;
+  const int limit_lane = chunk0 + (a.causal ? t_lane : a.c - 1);
 
   // ---- running softmax state: one query per lane ----
-  const float c2 = dm.scale * kLog2e;  // logits are kept in the log2 domain
+  const float c2 = a.c2;  // logits are kept in the log2 domain
   float m_run = -INFINITY, l_run = 0.f;
-  // Optional by-product: each row's log-sum-exp over the cache states alone, i.e. the running
-  // (maximum, sum) pair at the moment the last cache half tile has been added.  Needs the cache to end
-  // on a half-tile boundary (the launcher checks); every row sees every cache state.
-  const int snap_h = lse_cache != nullptr ? n_c / 32 - 1 : -1;
+  float m_sub = 0.f;         // what is subtracted: m_run, or 0 for a row that has seen nothing yet (exp2(-inf) = 0)
+  float m_high = -INFINITY;  // a logit above it moves m_run
+  // Optional by-product: each row's log-sum-exp over the cache states alone, i.e. the running (maximum, sum) pair behind
+  // the group's last cache tile (the launcher asks for it only if the cache ends with a whole tile); every row sees
+  // every cache state.
+  const int snap_i = a.lse_cache != nullptr ? i_chunk - 1 : -1;
   float m_snap = -INFINITY, l_snap = 0.f;
   f32x16 o_acc[T::kOut];
 #pragma unroll
@@ -537,95 +656,41 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 #pragma unroll
     for (int i = 0; i < 16; ++i) o_acc[r][i] = 0.f;
 
-  // fetch of one 64-key tile of K or of V into buffer (tile - t_begin) % 2
-  auto fetch_k = [&](int tile) {
-    fill4(k_s + ((tile - t_begin) & 1) * kTileBytes, k_rs_cache, k_rs_chunk, k_ss_cache, k_ss_chunk, tile * kTileN);
-  };
-  auto fetch_v = [&](int tile) {
-    fill4(v_s + ((tile - t_begin) & 1) * kTileBytes, v_rs_cache, v_rs_chunk, v_ss_cache, v_ss_chunk, tile * kTileN);
-  };
-  // A tile that lies inside one segment is fetched with four instructions that differ only in
-  // scalar operands; such fetches can be issued one by one between the MFMAs of a step.
-  struct FillPlan {
-    __amdgpu_buffer_rsrc_t rs;
-    char* lds;    // first row this wave fills
-    int soff;     // byte offset of instruction 0's first row inside the segment
-    int ss8;      // bytes between the rows of consecutive instructions (kR rows)
-    int row_off;  // per lane: its row inside the instruction's rows, in bytes
-    int seg16;    // per lane: byte offset of its 16-byte segment before the per-instruction swizzle term
-  };
-  // At most two tiles are not: the one that holds the cache / chunk boundary and the one that holds
-  // the end of the candidates.
-  const int straddle_tile = (n_c % kTileN) ? n_c / kTileN : -1;
-  const int ragged_tile = (n % kTileN) ? n / kTileN : -1;
-  auto tile_is_simple = [&](int tile) { return tile != straddle_tile && tile != ragged_tile; };
-  auto plan_fill = [&](char* buffer, int tile, __amdgpu_buffer_rsrc_t rs_cache, __amdgpu_buffer_rsrc_t rs_chunk,
-                       int ss_cache, int ss_chunk) {  // `buffer`: the tile buffer of the right parity
-    const int j0 = tile * kTileN;
-    const bool in_cache = j0 < n_c;
-    const int ss2 = (in_cache ? ss_cache : ss_chunk) * 2;
-    int fill_row = lane / T::kSegs, fill_seg16 = fill_seg16_c;
-    hide_loop_invariance(fill_row, fill_seg16);  // formed per fetch: see fill4
-    FillPlan fp;
-    fp.rs = in_cache ? rs_cache : rs_chunk;
-    fp.lds = buffer + kFillRows * wu * kRowBytes;
-    fp.soff = ((in_cache ? j0 : j0 - n_c) + kFillRows * wu) * ss2;
-    fp.ss8 = kR * ss2;
-    fp.row_off = fill_row * ss2;
-    fp.seg16 = fill_seg16;
-    return fp;
-  };
-  auto fill_one = [&](const FillPlan& fp, int i) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(fp.rs, (lds_void_ptr)(fp.lds + kR * i * kRowBytes), 16,
-                                             fp.row_off + (fp.seg16 ^ swz16(i)),
-                                             fp.soff + i * fp.ss8, 0, 0);
-  };
-
-  const int h_first = 2 * t_begin, h_last = 2 * t_end - 1;  // half tiles of 32 keys (block-uniform)
   f32x16 s_cur;            // logits of the half tile whose probabilities are computed next
   uint32_t p_prev[8];      // bf16 probabilities of the half tile before it, not yet multiplied with V
   Pack8 ka[T::kKk];        // K operand of the next logit product, read one step ahead
-  float mx_cur = 0.f;      // this lane's maximum over s_cur (before masking)
+  float mx_cur;            // this lane's maximum over s_cur (before masking)
+  uint64_t high;           // lanes whose maximum over s_cur (before masking) lies above m_high
 #pragma unroll
   for (int x = 0; x < 8; ++x) p_prev[x] = 0u;
-  auto read_k_ops = [&](int hn_raw) {  // half tile hn_raw, clamped to the last one
-    const int hn = min(hn_raw, h_last);
-    const char* k_t = k_s + (((hn >> 1) - t_begin) & 1) * kTileBytes + (hn & 1) * 32 * kRowBytes;
+  // K operand from a half tile; what is read past the last tile feeds logits that are never used
+  auto read_k_ops = [&](const char* k_t) {
 #pragma unroll
-    for (int kk = 0; kk < T::kKk; ++kk) ka[kk].u = *reinterpret_cast<const uint4*>(k_t + k_off(kk));
+    for (int kk = 0; kk < T::kKk; ++kk) ka[kk].u = read_row_operand(k_t, kk);
   };
 
-  // The same with the buffer parity and the half tile as constants: inside the key loop (unrolled over the
-  // two parities) every LDS address is then a per-lane register plus an immediate offset.  No clamp: what is
-  // read past the last tile feeds logits that are never used.
-  auto read_k_ops_at = [&](auto parity, auto half) {
-    const char* k_t = k_s + decltype(parity)::value * kTileBytes + decltype(half)::value * 32 * kRowBytes;
+  // One half step: finish the softmax of half tile hc (logits in s_cur) while the logits of the next half tile and the
+  // product of the previous one's probabilities with V run on the matrix pipe.  Past either end the neighbour's
+  // product is formed and not used; p_prev is zero before the first step.  v_t: the previous half tile of V.
+  // issue_k(slot) / issue_v(slot) put the loads of the tile being fetched between the MFMAs.
+  auto half_step = [&](int hc, const char* v_t, auto&& issue_k, auto&& issue_v, auto&& before_tail) {
+    if (__builtin_expect(hc >= first_masked, 0)) {  // wave-uniform: the causal edge and the ends of the segments only
+      const int jb = 32 * hc;
+      const bool rest = hc >= 2 * ragged_tile;  // of the cache (with two key groups also what lies behind it)
+      const int lim_rel = (rest ? kTileN * ragged_tile + n_c % kTileN - 1 : limit_lane) - jb - 4 * grp;
 #pragma unroll
-    for (int kk = 0; kk < T::kKk; ++kk) ka[kk].u = *reinterpret_cast<const uint4*>(k_t + k_off(kk));
-  };
-
-  // One step: finish the softmax of half tile h (logits in s_cur) while the logits of h + 1 and the
-  // product P(h - 1).V run on the matrix pipe.  Past either end the neighbour is clamped: the
-  // logits computed past the end are never used, and p_prev is zero before the first step.
-  // With fill_k / fill_v the four fetch instructions of that plan are issued between the MFMAs.
-  // v_t: the V half tile that belongs to half tile hc - 1.
-  auto half_step = [&](int hc, const char* v_t, bool fill_k, bool fill_v, const FillPlan& fk, const FillPlan& fv) {
-    const int jb = 32 * hc;
-    if (jb + 31 > wave_limit_min) {  // wave-uniform: the causal edge and the ragged end only
-      const int lim_rel = limit_lane - jb - 4 * grp;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (8 * (i / 4) + (i % 4) > lim_rel) s_cur[i] = -INFINITY;
+      for (int x = 0; x < 16; ++x)
+        if (8 * (x / 4) + (x % 4) > lim_rel) s_cur[x] = -INFINITY;
       mx_cur = s_cur[0];
 #pragma unroll
-      for (int i = 1; i < 16; ++i) mx_cur = fmaxf(mx_cur, s_cur[i]);
+      for (int x = 1; x < 16; ++x) mx_cur = fmaxf(mx_cur, s_cur[x]);
+      high = __ballot(mx_cur > m_high);
     }
     // Running maximum, kept lazily: softmax is invariant to the subtracted value, so m_run only has
-    // to stay within kMaxSlack (log2 units) of the true row maximum to keep exp2 in range.  The
-    // lane's maximum over the half tile was taken at the end of the previous step.
-    float mx = mx_cur;
-    if (__any(mx * c2 > m_run + kMaxSlack)) {  // wave-uniform and rare after the first tiles
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    // to stay within kMaxSlack (log2 units) of the true row maximum to keep exp2 in range.  The vote on the
+    // lanes' maxima was taken at the end of the previous step.
+    if (__builtin_expect(high != 0, 0)) {  // wave-uniform and rare after the first tiles
+      const float mx = fmaxf(mx_cur, __shfl_xor(mx_cur, 32, 64));
       const float m_new = fmaxf(m_run, mx * c2);
       // 0 on a row's first visible tile (m_run = -inf); 1 for a row that has seen nothing yet
       const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
@@ -635,7 +700,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 #pragma unroll
       for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o_acc[r][i] *= alpha;
+        for (int x = 0; x < 16; ++x) o_acc[r][x] *= alpha;
       // the probabilities still waiting for their product with V were taken against the old maximum
 #pragma unroll
       for (int x = 0; x < 8; ++x) {
@@ -643,12 +708,13 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
         p_prev[x] = pack_bf16x2(lo * alpha, hi * alpha);
       }
       m_run = m_new;
+      m_sub = m_new == -INFINITY ? 0.f : m_new;
+      m_high = (m_new + kMaxSlack) * a.inv_c2;
     }
-    const float m_sub = m_run == -INFINITY ? 0.f : m_run;  // a row that has seen nothing yet: exp2(-inf) = 0
     __builtin_amdgcn_sched_barrier(0);
 
     // O^T += V^T . P^T: contraction step `half` covers keys 16 half .. +15 of the half tile in the slot
-    // order the S^T accumulators have: slot i of lane group grp is key 8 (i / 4) + 4 grp + (i % 4) of
+    // order the S^T accumulators have: slot x of lane group grp is key 8 (x / 4) + 4 grp + (x % 4) of
     // the step, so slots 0..3 / 4..7 are two transpose reads.
     // The V^T operands of the second contraction step are read once half of the K operands are
     // spent (the empty asm with a memory clobber keeps the reads from being hoisted above it):
@@ -659,26 +725,27 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
       for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
         for (int rd = 0; rd < 2; ++rd)
-          va[half][r].h[rd] = lds_read_tr16(v_t + (16 * half + 8 * rd) * kRowBytes + v_off(2 * r + rd));
+          va[half][r].h[rd] = read_v_operand(v_t, half, r, rd);
     };
     read_v_ops(0);
-    // kKk MFMAs of S^T(h + 1), then 2 kOut of O^T: sixteen (head_dim 64: eight).  The exponential of logit x of half
-    // tile h is issued right before MFMA x + 1 (head_dim 64: those of logits 2 x and 2 x + 1).
+    __builtin_amdgcn_s_waitcnt(0xC07F | ((2 * T::kOut) << 8));  // the K operands are here: one wait for all of them
+    // kKk MFMAs of S^T, then 2 kOut of O^T: sixteen (head_dim 64: eight).  The exponential of logit x of half
+    // tile i is issued right before MFMA x + 1 (head_dim 64: those of logits 2 x and 2 x + 1).
     float p[16];
     float mx_nxt = 0.f;
     f32x16 s_nxt = mfma_pinned_first(ka[0].v, q_op[0]);
     constexpr int kExp = 128 / D;  // exponentials per MFMA slot
-    auto exps_then_mfma = [&](int slot, f32x16& acc, const bf16x8& a, const bf16x8& b) {
+    auto exps_then_mfma = [&](int slot, f32x16& acc, const bf16x8& a, const bf16x8& bb) {
       const int x = kExp * slot;
       if constexpr (kExp == 2)
-        exp2x2_then_mfma(fmaf(s_cur[x], c2, -m_sub), fmaf(s_cur[x + 1], c2, -m_sub), p[x], p[x + 1], acc, a, b);
+        exp2x2_then_mfma(fmaf(s_cur[x], c2, -m_sub), fmaf(s_cur[x + 1], c2, -m_sub), p[x], p[x + 1], acc, a, bb);
       else
-        p[x] = exp2_then_mfma(fmaf(s_cur[x], c2, -m_sub), acc, a, b);
+        p[x] = exp2_then_mfma(fmaf(s_cur[x], c2, -m_sub), acc, a, bb);
     };
 #pragma unroll
     for (int kk = 1; kk < T::kKk; ++kk) {
       exps_then_mfma(kk - 1, s_nxt, ka[kk].v, q_op[kk]);
-      if ((kk & 1) && kk / 2 < kFillInstr && fill_k) fill_one(fk, kk / 2);  // block-uniform
+      if (kk & 1) issue_k(kk / 2);
       if (kk == T::kKk / 2) {
         no_memory_motion();
         read_v_ops(1);
@@ -689,11 +756,15 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
       Pack8 pb;
 #pragma unroll
       for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[4 * half + x];
+      if (half == 0)
+        __builtin_amdgcn_s_waitcnt(0xC07F | ((2 * T::kOut) << 8));
+      else
+        __builtin_amdgcn_s_waitcnt(0xC07F);
 #pragma unroll
       for (int r = 0; r < T::kOut; ++r) {
         const int slot = T::kOut * half + r;  // of the second product
         exps_then_mfma(T::kKk - 1 + slot, o_acc[r], va[half][r].v, pb.v);
-        if ((slot & 1) && slot / 2 < kFillInstr && fill_v) fill_one(fv, slot / 2);  // block-uniform
+        if (slot & 1) issue_v(slot / 2);
         // The lane's maximum of the next half tile's logits, one v_max3 per MFMA slot.  s_nxt was
         // completed by the last MFMA of the first product; three further MFMAs have been issued since.
         if (D == 128) {
@@ -703,6 +774,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
         }
       }
     }
+    before_tail();
     if constexpr (kExp == 2) {
       p[14] = exp2_pinned(fmaf(s_cur[14], c2, -m_sub));
       mx_nxt = max3_pinned(s_nxt[0], s_nxt[1], s_nxt[2]);
@@ -712,6 +784,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
     p[15] = exp2_pinned(fmaf(s_cur[15], c2, -m_sub));
     mx_nxt = max3_pinned(mx_nxt, s_nxt[13], s_nxt[14]);
     mx_nxt = fmaxf(mx_nxt, s_nxt[15]);
+    high = __ballot(mx_nxt > m_high);
     // the row sum is taken over the bf16-rounded probabilities, the values P.V uses: one v_dot2
     // with (1, 1) adds a pair
     uint32_t p_cur[8];
@@ -723,10 +796,6 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
                                              __builtin_bit_cast(bf16x2, 0x3f803f80u), psum, false);
     }
     l_run += psum;
-    if (hc == snap_h) {  // block-uniform
-      m_snap = m_run;
-      l_snap = l_run;
-    }
     // keep the probabilities in this block: without a use here the optimiser sinks the exponentials
     // to their first use in the next step, behind the MFMAs they are meant to overlap with
     keep_values_here(p_cur, l_run);
@@ -736,72 +805,97 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
 #pragma unroll
     for (int x = 0; x < 8; ++x) p_prev[x] = p_cur[x];
   };
-  const FillPlan no_plan{};
 
-  if (t_begin < t_end) {  // block-uniform
-  fetch_k(t_begin);
-  fetch_v(t_begin);
-  if (t_begin + 1 < t_end) fetch_k(t_begin + 1);
-  // The wave's 32 query rows come in through LDS as well: whole rows, kR per load
-  // instruction, into the wave's own region (same swizzle as a key tile), from where the B operand is
-  // read like a key operand.  Loading them straight into the operand layout would put 64 scattered
-  // 16-byte pieces into every load instruction.
+  // ---- first requests: K 0, the query rows | V 0, K 1 (the first two are waited for first) ----
+  Stream sk, sv;
+  // a stream enters the next segment at the group's first chunk tile and at the ragged rest of the cache
+  auto reposition = [&](Stream& s, const i32x4& rs_cache, const i32x4& rs_chunk, int ss_cache, int ss_chunk, int i) {
+    if (i >= i_chunk && i < i_ragged)
+      enter(s, rs_chunk, ss_chunk, kTileN * (tile_of(i) - cache_tiles));
+    else
+      enter(s, rs_cache, ss_cache, kTileN * (i < i_chunk ? tile_of(i) : tile_of(i) - ragged_tile + cache_tiles));
+  };
+  int k_switch = -1, v_switch = -1;  // the tile at which the stream enters the next segment
+  auto position_k = [&](int i) {
+    reposition(sk, k_rs_cache, k_rs_chunk, k_ss_cache, k_ss_chunk, i);
+    k_switch = i < i_chunk ? i_chunk : i_ragged;
+  };
+  auto position_v = [&](int i) {
+    reposition(sv, v_rs_cache, v_rs_chunk, v_ss_cache, v_ss_chunk, i);
+    v_switch = i < i_chunk ? i_chunk : i_ragged;
+  };
+  position_k(0);
+  position_v(0);
+  fetch(sk, integral_constant<int, 0>{});
+  advance(sk);
+  // The wave's 32 query rows come in through LDS as well: whole rows, kR per load instruction, laid out like half a
+  // key tile, from where the B operand is read like a key operand.  Loading them straight
+  // into the operand layout would put 64 scattered 16-byte pieces into every load instruction.
+  char* const q_t = kQueryInV ? ring + (wr * 2 / kRowWaves * 4 + 3) * Y::kTile + wr % (kRowWaves / 2) * Y::kHalf
+                              : q_stage + wr * Y::kHalf;
   {
-    const int q_ss2 = static_cast<int>(q.ss) * 2;
-    const __amdgpu_buffer_rsrc_t q_rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(unit_ptr(q, b, l, h)), 0, ((rows - 1) * static_cast<int>(q.ss) + D) * 2, kBufferFlags);
-    int r_in = lane / T::kSegs, pos = lane % T::kSegs;
-    hide_loop_invariance(r_in, pos);
+    const int q_ss2 = a.q.ss;
+    const i32x4 q_rs = buffer_words(unit(a.q, h), (rows - 1) * q_ss2 + 2 * D);
+    const uint32_t q_lds = lds_addr(q_t);
+    int r_in = lane / T::kSegs, seg16 = ((lane % T::kSegs) ^ Y::swz(lane / T::kSegs)) * 16;
+    hide_loop_invariance(r_in, seg16);
 #pragma unroll
-    for (int i = 0; i < 32 / kR; ++i) {
-      const int r = kR * i + r_in;
-      const int f = T::swz(r);
-      const int row = min(row0 + r, rows - 1);  // rows past the end repeat the last one; never stored
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(q_rs, (lds_void_ptr)(q_stage + (32 * wu + kR * i) * kRowBytes), 16,
-                                               max(row, 0) * q_ss2 + ((pos ^ f) * 16), 0, 0, 0);
+    for (int x = 0; x < 32 / kR / KS; ++x) {  // the key groups share the rows and their loads
+      const int i = 32 / kR / KS * kg + x;
+      const int row = min(row0 + kR * i + r_in, rows - 1);  // rows past the end repeat the last one; never stored
+      load_lds_unwatched<0>(q_rs, q_lds + i * Y::kBlock, max(row, 0) * q_ss2 + seg16, 0);
     }
   }
-  barrier_after_lds_fill();  // also: the query rows have landed
+  if (pass == 0) {
+    zero_v(0, kQueryInV ? Y::kTile : 2 * Y::kTile);
+    lds_writes_and_barrier();
+  }
+  fetch(sv, integral_constant<int, 2>{});
+  advance(sv);
+  if (k_switch == 1) position_k(1);
+  fetch(sk, integral_constant<int, 1>{});
+  advance(sk);
+  wait_loads_and_barrier<2 * kPer, true>();  // K 0 and the query rows have landed
   // Position shift: the query rows arrive without rotary embedding and are rotated here, in the staging
-  // region, to position q_rope_pos0 + row, before the operands are read (only a few registers are live at
+  // region, to position a.q_rope_pos0 + row, before the operands are read (only a few registers are live at
   // this point; rotating the operands in registers pushed the whole kernel over its register budget).
   // Element i of a row pairs with element i + D / 2: 16-byte segment sg with segment sg + D / 16.  A lane takes
-  // one (row, sg) of the wave's 32 x D / 16 per round; the wave touches only its own rows, so no barrier.
+  // one (row, sg) of the wave's 32 x D / 16 per round; a wave touches only its row tile's rows.
   if (ROTATE_Q) {
-    char* q_t = q_stage + 32 * wu * kRowBytes;
     constexpr int kPairs = T::kSegs / 2, kRoundRows = 64 / kPairs;
 #pragma unroll 1
-    for (int round = 0; round < 32 / kRoundRows; ++round) {
+    for (int round = kg; round < 32 / kRoundRows; round += KS) {
       const int r = kRoundRows * round + lane / kPairs, sg = lane % kPairs;
-      const int f = T::swz(r);
-      uint4* lo_p = reinterpret_cast<uint4*>(q_t + r * kRowBytes + ((sg ^ f) * 16));
-      uint4* hi_p = reinterpret_cast<uint4*>(q_t + r * kRowBytes + (((sg + kPairs) ^ f) * 16));
+      uint4* lo_p = reinterpret_cast<uint4*>(q_t + Y::at(r, sg));
+      uint4* hi_p = reinterpret_cast<uint4*>(q_t + Y::at(r, sg + kPairs));
       Pack8 lo, hi;
       lo.u = *lo_p;
       hi.u = *hi_p;
-      const int pos = q_rope_pos0 + max(min(row0 + r, rows - 1), 0);
+      const int pos = a.q_rope_pos0 + max(min(row0 + r, rows - 1), 0);
 #pragma unroll
       for (int wd = 0; wd < 4; ++wd) {
         const int i0 = 8 * sg + 2 * wd;
         float s0, c0, s1, c1;
-        rope_sincos_bf16(pos, i0, D, rope_log2_base, s0, c0);
-        rope_sincos_bf16(pos, i0 + 1, D, rope_log2_base, s1, c1);
+        rope_sincos_bf16(pos, i0, D, a.rope_log2_base, s0, c0);
+        rope_sincos_bf16(pos, i0 + 1, D, a.rope_log2_base, s1, c1);
         rope_rotate_words(lo.w[wd], hi.w[wd], c0, s0, c1, s1, lo.w[wd], hi.w[wd]);
       }
       *lo_p = lo.u;
       *hi_p = hi.u;
     }
+    if (KS > 1) lds_writes_and_barrier();  // the groups rotated parts of each other's rows
   }
-  {
-    const char* q_t = q_stage + 32 * wu * kRowBytes;
 #pragma unroll
-    for (int kk = 0; kk < T::kKk; ++kk) {
-      Pack8 p;
-      p.u = *reinterpret_cast<const uint4*>(q_t + k_off(kk));
-      q_op[kk] = p.v;
-    }
+  for (int kk = 0; kk < T::kKk; ++kk) {
+    Pack8 p;
+    p.u = read_row_operand(q_t, kk);
+    q_op[kk] = p.v;
   }
-  read_k_ops(h_first);
+  read_k_ops(k_s);
+  if (kQueryInV) {  // every wave has its query operand: the buffer it came through is zeroed for the first step
+    lds_writes_and_barrier();
+    zero_v(Y::kTile, 2 * Y::kTile);
+  }
 #pragma unroll
   for (int i = 0; i < 16; ++i) s_cur[i] = 0.f;
 #pragma unroll
@@ -810,36 +904,55 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
   mx_cur = s_cur[0];
 #pragma unroll
   for (int i = 1; i < 16; ++i) mx_cur = fmaxf(mx_cur, s_cur[i]);
-  read_k_ops(h_first + 1);
-  // One 64-key tile per call; `parity` is the tile's buffer (t_begin = 0 in this kernel: tile jt lives in
-  // buffer jt % 2), so the loop below alternates two copies of the step whose LDS offsets are constants.
-  static_assert(key_splits == 1, "the tile buffers are addressed by jt % 2");
-  auto tile_step = [&](auto parity, int jt) {
-    constexpr int P = decltype(parity)::value;
-    // P.V of the second half of tile jt - 1 (before the first tile: p_prev = 0 times the zeros written at
-    // kernel start, or times stale finite data in later row blocks)
-    half_step(2 * jt, v_s + (1 - P) * kTileBytes + 32 * kRowBytes, false, false, no_plan, no_plan);
-    // Every wave has read the second half of K tile jt and the last of V tile jt - 1: their buffers
-    // take K tile jt + 2 and V tile jt + 1, which are first read after the next barrier.
-    barrier_after_lds_fill();
-    read_k_ops_at(std::integral_constant<int, 1 - P>{}, std::integral_constant<int, 0>{});  // K tile jt + 1, first half
-    // Tiles inside one segment are fetched from within the step, one instruction between two
-    // MFMAs (plans of tiles that are not wanted are formed but never used); the others here.
-    const bool want_k = jt + 2 < t_end, want_v = jt + 1 < t_end;
-    const bool k_inside = want_k && tile_is_simple(jt + 2), v_inside = want_v && tile_is_simple(jt + 1);
-    if (want_k && !k_inside) fetch_k(jt + 2);
-    if (want_v && !v_inside) fetch_v(jt + 1);
-    const FillPlan fk = plan_fill(k_s + P * kTileBytes, jt + 2, k_rs_cache, k_rs_chunk, k_ss_cache, k_ss_chunk);
-    const FillPlan fv = plan_fill(v_s + (1 - P) * kTileBytes, jt + 1, v_rs_cache, v_rs_chunk, v_ss_cache, v_ss_chunk);
-    half_step(2 * jt + 1, v_s + P * kTileBytes, k_inside, v_inside, fk, fv);
-    read_k_ops_at(std::integral_constant<int, 1 - P>{}, std::integral_constant<int, 1>{});  // K tile jt + 1, second half
+  high = ~uint64_t{0};
+  read_k_ops(k_s + Y::kHalf);
+  if (kQueryInV) lds_writes_and_barrier();
+
+  // One 64-key tile.  `parity` is the tile's buffer (the group's tile i lives in buffer
+  // i % 2), so every LDS address is a per-lane register plus an immediate offset, and nothing branches but for the rare
+  // cases.  It always fetches; what it fetches past the block's range is not read.
+  const bool early = WAVES == 8 && wu >= 4;
+  auto no_issue = [](int) {};
+  auto issue_slot = [&](const Stream& s, auto buf, int slot) {
+    [&]<int... X>(std::integer_sequence<int, X...>) {
+      ((X / kPerSlot == slot ? issue_one(s, buf, integral_constant<int, X>{}) : (void)0), ...);
+    }(std::make_integer_sequence<int, kPer>{});
   };
-  for (int jt = t_begin; jt < t_end; jt += 2) {
-    tile_step(std::integral_constant<int, 0>{}, jt);
-    if (jt + 1 < t_end) tile_step(std::integral_constant<int, 1>{}, jt + 1);
+  auto rare_events = [&](int i) {  // streams that enter another segment
+    if (__builtin_expect(i + 2 == k_switch, 0)) position_k(i + 2);
+    if (__builtin_expect(i + 1 == v_switch, 0)) position_v(i + 1);
+  };
+  auto note_cache = [&](int i) {
+    if (__builtin_expect(i == snap_i, 0)) {
+      m_snap = m_run;
+      l_snap = l_run;
+    }
+  };
+  auto tile_step = [&](auto parity, int i) {
+    constexpr int P = decltype(parity)::value;
+    // P.V of the second half of tile i - 1 (before the first tile: p_prev = 0 times the zeros written above,
+    // or times stale finite data in later row blocks)
+    half_step(2 * tile_of(i), v_s + (1 - P) * Y::kTile + Y::kHalf, no_issue, no_issue, [&] { if (early) wait_loads_and_barrier<0, false>(); });
+    // Every wave has read the second half of K tile i and the last of V tile i - 1: their buffers
+    // take K tile i + 2 and V tile i + 1, which are first read after the next barrier.
+    if (!early) wait_loads_and_barrier<0, false>();
+    read_k_ops(k_s + (1 - P) * Y::kTile);  // K tile i + 1, first half
+    rare_events(i);
+    constexpr integral_constant<int, P> kbuf{};
+    constexpr integral_constant<int, 3 - P> vbuf{};
+    half_step(2 * tile_of(i) + 1, v_s + P * Y::kTile, [&](int slot) { issue_slot(sk, kbuf, slot); },
+              [&](int slot) { issue_slot(sv, vbuf, slot); }, [] {});
+    advance(sk);
+    advance(sv);
+    note_cache(i);
+    read_k_ops(k_s + (1 - P) * Y::kTile + Y::kHalf);  // K tile i + 1, second half
+  };
+  for (int i = 0; i < t_end; i += 2) {
+    tile_step(integral_constant<int, 0>{}, i);
+    if (i + 1 < t_end) tile_step(integral_constant<int, 1>{}, i + 1);
   }
   {  // the product of the last half tile
-    const char* v_t = v_s + ((t_end - 1 - t_begin) & 1) * kTileBytes + 32 * kRowBytes;
+    const char* v_t = v_s + ((t_end - 1) & 1) * Y::kTile + Y::kHalf;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       Pack8 va[T::kOut];
@@ -847,7 +960,7 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
       for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
         for (int rd = 0; rd < 2; ++rd)
-          va[r].h[rd] = lds_read_tr16(v_t + (16 * half + 8 * rd) * kRowBytes + v_off(2 * r + rd));
+          va[r].h[rd] = read_v_operand(v_t, half, r, rd);
       Pack8 pb;
 #pragma unroll
       for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[4 * half + x];
@@ -855,85 +968,125 @@ __device__ __forceinline__ void attn_pipe_body(const Dims& dm, const View& q, in
       for (int r = 0; r < T::kOut; ++r) o_acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[r].v, pb.v, o_acc[r], 0, 0, 0);
     }
   }
-  __syncthreads();  // the buffers are free for the next row block
-  }
+  barrier_after_lds_fill();  // the buffers are free for the output tiles and for the next row block
 
   const float l_snap_tot = l_snap + __shfl_xor(l_snap, 32, 64);
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const int t = row0 + col;
-  if (wave_active && t < rows) {
-  const int64_t row_id = (static_cast<int64_t>(bl) * dm.Hq + h) * rows + t;
-  if (part != nullptr && grp == 0)  // log2 domain; an empty or fully masked range leaves (-inf, 0)
-    part[static_cast<int64_t>(sp) * dm.B * dm.L * dm.Hq * rows + row_id] = make_float2(m_run, l_tot);
-  if (lse_cache != nullptr && grp == 0) lse_cache[row_id] = (m_snap + log2f(l_snap_tot)) * kLn2;
-  if (lse != nullptr && grp == 0) lse[row_id] = (m_run + log2f(l_tot)) * kLn2;
-  }  // row valid
+  const int64_t row_id0 = (static_cast<int64_t>(bl) * a.q_heads + h) * rows;  // of the lse outputs
   // The output tile leaves through LDS: a lane holds 4-element pieces of ONE query row (256 bytes
   // between neighbouring lanes), so direct stores put 64 scattered 8-byte pieces into every store
-  // instruction and keep the compute unit's address path busy for microseconds per row block.  Each
-  // wave parks its 32 x D tile in its own quarter of a K or V buffer pair (free after the barrier above;
-  // 16-byte segments XOR-swizzled by the row so that the column-wise writes spread over the banks)
-  // and stores it back as whole rows.
-  {
-    int colx = col, lanex = lane;
-    hide_loop_invariance(colx, lanex);  // offsets are formed here, per row block, not kept in registers
-    char* o_s = (wu < 4 ? k_s : v_s) + (wu % 4) * (32 * kRowBytes) + colx * kRowBytes;
-    // A lane pair (col, col + 32) shares every 16-byte segment.  The LDS has 32 banks of 4 bytes, and 16 lanes of an
-    // 8-byte write go through per cycle, so the sixteen rows of a cycle have to fall into sixteen 8-byte slots of 128
-    // bytes.  head_dim 128: segment positions p and p + 8 of a row meet in the same banks; the two halves of a segment
-    // are kept swapped where (p / 8) ^ (row / 16) is odd.  head_dim 64: a row has eight positions; the halves are
-    // swapped in every second group of eight rows.
-    constexpr int kSwzRows = T::kSegs;
-    const int c_swz = colx % kSwzRows, half0 = D == 128 ? grp ^ (colx / 16) : grp ^ ((colx / 8) & 1);
+  // instruction and keep the compute unit's address path busy for microseconds per row block.  Rows past the end are
+  // out of the output resource's range and dropped.
+  const int out_ss = a.out.ss;
+  const __amdgpu_buffer_rsrc_t out_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(unit(a.out, h)), 0,
+                                                                          (rows - 1) * out_ss + 2 * D, kBufferFlags);
+  int colx = col, lanex = lane;
+  hide_loop_invariance(colx, lanex);  // offsets are formed here, per row block, not kept in registers
+  if constexpr (KS == 1) {
+    const int t = row0 + col;
+    if (grp == 0 && t < rows) {
+      if (a.lse_cache != nullptr) a.lse_cache[row_id0 + t] = (m_snap + log2f(l_snap_tot)) * kLn2;
+      if (a.lse != nullptr) a.lse[row_id0 + t] = (m_run + log2f(l_tot)) * kLn2;
+    }
+    // Each wave parks its 32 x D tile in its own part of the tile buffers (free after the barrier above; 16-byte
+    // segments XOR-swizzled by the row: column-wise writes spread over the banks) and stores it back as whole rows.  A
+    // lane and its partner l ^ 32 hold the two halves of every segment: a swap gives each of them whole segments.
+    char* const o_tile = ring + wu * (32 * kRowBytes);
+    char* const o_s = o_tile + colx * kRowBytes;
+    const int c_swz = colx % T::kSegs;
     const float inv = 1.f / l_tot;
 #pragma unroll
     for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        // registers 4 i4 .. +3 are rows c' = 8 i4 + 4 grp + 0..3 -> head_dim 16 r + (c' % 16) + D / 2 (c' / 16):
-        // 16-byte segment 2 r + (i4 % 2) + D / 16 (i4 / 2), its half `grp`
-        const int sg = 2 * r + (i4 % 2) + T::kSegs / 2 * (i4 / 2);
-        uint2 wds;
-        wds.x = pack_bf16x2(o_acc[r][4 * i4] * inv, o_acc[r][4 * i4 + 1] * inv);
-        wds.y = pack_bf16x2(o_acc[r][4 * i4 + 2] * inv, o_acc[r][4 * i4 + 3] * inv);
-        const int p = sg ^ c_swz;  // segment position
-        *reinterpret_cast<uint2*>(o_s + p * 16 + 8 * (D == 128 ? half0 ^ (p >> 3) : half0)) = wds;
-      }
-    const char* o_r = (wu < 4 ? k_s : v_s) + (wu % 4) * (32 * kRowBytes) + lanex * 16;  // row lanex / kSegs of a kR-row group
-    const int r_in = lanex / T::kSegs, pos = lanex % T::kSegs;
-    uint16_t* ob = const_cast<uint16_t*>(unit_ptr(out, b, l, h));
+      for (int ip = 0; ip < 2; ++ip) {
+        // registers 4 i4 .. + 3, i4 = 2 ip + x, are rows c' = 8 i4 + 4 grp + 0..3 -> head_dim 16 r + (c' % 16) + D / 2 (c' / 16)
+        uint32_t wd[2][2];
 #pragma unroll
-    for (int i = 0; i < 32 / kR; ++i) {
-      const int r = kR * i + r_in;
-      uint4 piece = *reinterpret_cast<const uint4*>(o_r + kR * i * kRowBytes);
-      const bool swapped = D == 128 ? ((pos >> 3) ^ (i >> 2)) & 1 : i & 1;
-      if (swapped) piece = make_uint4(piece.z, piece.w, piece.x, piece.y);  // halves back in order
-      if (wave_active && row0 + r < rows)
-        *reinterpret_cast<uint4*>(ob + static_cast<int64_t>(row0 + r) * out.ss + 8 * (pos ^ (r % kSwzRows))) = piece;
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 2; ++y)
+            wd[x][y] = pack_bf16x2(o_acc[r][8 * ip + 4 * x + 2 * y] * inv, o_acc[r][8 * ip + 4 * x + 2 * y + 1] * inv);
+        uint4 piece;  // segment 2 r + grp + D / 16 ip
+        swap_halves(wd[0][0], wd[1][0], piece.x, piece.z);
+        swap_halves(wd[0][1], wd[1][1], piece.y, piece.w);
+        *reinterpret_cast<uint4*>(o_s + ((2 * r + T::kSegs / 2 * ip + grp) ^ c_swz) * 16) = piece;
+      }
+    const char* const o_r = o_tile + lanex * 16;  // row lanex / kSegs of a kR-row group
+    const int r_in = lanex / T::kSegs, pos = lanex % T::kSegs;
+    int at = (row0 + r_in) * out_ss;
+#pragma unroll
+    for (int i = 0; i < 32 / kR; ++i, at += kR * out_ss) {
+      const u32x4 piece = *reinterpret_cast<const u32x4*>(o_r + kR * i * kRowBytes);
+      __builtin_amdgcn_raw_buffer_store_b128(piece, out_rs, at + (pos ^ ((kR * i + r_in) % T::kSegs)) * 16, 0, 0);
+    }
+    __syncthreads();  // the parked tiles have been read back: the next row block may fill the buffers
+  } else {
+    // Two key groups: the (maximum, sum, output) of a row tile are in two waves.  Both leave their f32 output rows
+    // in LDS (16-byte segments XOR-swizzled by the row: the column-wise writes and the row-wise reads spread over the
+    // banks); each of them then weighs and adds the two partial rows of sixteen rows and stores them whole.
+    constexpr int kSegs32 = D / 4;  // 16-byte segments of an f32 row
+    static_assert(WAVES * 32 * D * 4 <= KS * 4 * Y::kTile, "the f32 tiles fit the tile buffers");
+    float* const o_s = reinterpret_cast<float*>(ring) + (wu * 32 + colx) * D;
+    float4* const stat = reinterpret_cast<float4*>(q_stage);  // [KS][kRowWaves * 32]; the query rows are spent
+#pragma unroll
+    for (int r = 0; r < T::kOut; ++r)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const int sg = 4 * r + 2 * (i4 % 2) + grp + kSegs32 / 2 * (i4 / 2);
+        *reinterpret_cast<float4*>(o_s + 4 * (sg ^ (colx % kSegs32))) =
+            make_float4(o_acc[r][4 * i4], o_acc[r][4 * i4 + 1], o_acc[r][4 * i4 + 2], o_acc[r][4 * i4 + 3]);
+      }
+    if (grp == 0) stat[wu * 32 + col] = make_float4(m_run, l_tot, m_snap, l_snap_tot);
+    __syncthreads();
+    constexpr int kRowLanes = kSegs32 / 2;  // lane x of a row owns segments x and x + kSegs32 / 2
+    const int x = lanex % kRowLanes;
+#pragma unroll
+    for (int it = 0; it < 16 * kRowLanes / 64; ++it) {
+      const int r = 16 * kg + it * (64 / kRowLanes) + lanex / kRowLanes;  // row of the tile
+      const float4 s0 = stat[wr * 32 + r], s1 = stat[(kRowWaves + wr) * 32 + r];
+      const float m_all = fmaxf(s0.x, s1.x);  // finite: tile 0 is visible to every row
+      float w0 = __builtin_amdgcn_exp2f(s0.x - m_all), w1 = __builtin_amdgcn_exp2f(s1.x - m_all);
+      const float l_all = fmaf(s0.y, w0, s1.y * w1);
+      const float inv = 1.f / l_all;
+      w0 *= inv;
+      w1 *= inv;
+      const float* const o0 = reinterpret_cast<const float*>(ring) + (wr * 32 + r) * D;
+      const float* const o1 = o0 + kRowWaves * 32 * D;
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const int sg = x + y * kRowLanes;
+        const float4 p0 = *reinterpret_cast<const float4*>(o0 + 4 * (sg ^ (r % kSegs32)));
+        const float4 p1 = *reinterpret_cast<const float4*>(o1 + 4 * (sg ^ (r % kSegs32)));
+        const u32x2 wds = {pack_bf16x2(fmaf(p0.x, w0, p1.x * w1), fmaf(p0.y, w0, p1.y * w1)),
+                           pack_bf16x2(fmaf(p0.z, w0, p1.z * w1), fmaf(p0.w, w0, p1.w * w1))};
+        __builtin_amdgcn_raw_buffer_store_b64(wds, out_rs, (row0 + r) * out_ss + sg * 8, 0, 0);
+      }
+      if ((a.lse != nullptr || a.lse_cache != nullptr) && x == 0 && row0 + r < rows) {
+        if (a.lse != nullptr) a.lse[row_id0 + row0 + r] = (m_all + log2f(l_all)) * kLn2;
+        if (a.lse_cache != nullptr) {
+          const float m_c = fmaxf(s0.z, s1.z);
+          const float l_c = s0.w * __builtin_amdgcn_exp2f(s0.z - m_c) + s1.w * __builtin_amdgcn_exp2f(s1.z - m_c);
+          a.lse_cache[row_id0 + row0 + r] = (m_c + log2f(l_c)) * kLn2;
+        }
+      }
     }
   }
-  __syncthreads();  // the parked tiles have been read back: the next row block may fill the buffers
   }  // pass
 }
 
 // Eight waves per workgroup: two 32-row tiles of the four heads of a KV group (or the equivalent
 // split for smaller groups) share every K/V tile, which halves the fetch traffic per MFMA
 // against four waves; one workgroup per CU, two waves per SIMD.
-template <int D>
-__global__ __launch_bounds__(512, D == 128 ? 1 : 2) void attn_pipe_kernel_w8(Dims dm, View q, int rows, Segments ks, Segments vs,
-                                                                            int causal, View out, float* lse,
-                                                                            float* lse_cache) {
-  attn_pipe_body<D, 8, false>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, -1, 0.f);
+template <int D, int WAVES, int KS>
+__global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel(AttnArgs a) {
+  attn_pipe_body<D, WAVES, KS, false>(a);
 }
 // The same kernel for query rows that arrive without rotary embedding (position shift): they are rotated
 // in the LDS staging region before the operands are read.  An instance of its own, so that the kernel
 // above does not carry the extra prologue.
-template <int D>
-__global__ __launch_bounds__(512, D == 128 ? 1 : 2) void attn_pipe_kernel_w8_rotq(Dims dm, View q, int rows, Segments ks,
-                                                                                 Segments vs, int causal, View out, float* lse,
-                                                                                 float* lse_cache, int q_rope_pos0,
-                                                                                 float rope_log2_base) {
-  attn_pipe_body<D, 8, true>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, q_rope_pos0, rope_log2_base);
+template <int D, int WAVES, int KS>
+__global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel_rotq(AttnArgs a) {
+  attn_pipe_body<D, WAVES, KS, true>(a);
 }
 
 // Brings the per-range (maximum, sum) pairs of a row, part[s * rows_total + row], to one normaliser,
@@ -1390,6 +1543,50 @@ bool fits_i32(const View& v, int rows) {
   return v.ss > 0 && v.ss * static_cast<int64_t>(rows > 0 ? rows : 1) < (int64_t{1} << 31);
 }
 
+// Attention with output: one instance of the kernel.
+template <int D, int WAVES, int KS>
+hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
+                            float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+  const TaskShape ts = task_shape(dm.G, WAVES / KS);
+  const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
+  AttnArgs a;
+  a.q = unit_view(q);
+  a.out = unit_view(out);
+  a.k_cache = unit_view(ks.cache);
+  a.k_chunk = unit_view(ks.chunk);
+  a.v_cache = unit_view(vs.cache);
+  a.v_chunk = unit_view(vs.chunk);
+  a.rows = rows;
+  a.n_c = ks.n_c;
+  a.c = ks.c;
+  a.causal = causal;
+  a.q_heads = dm.Hq;
+  a.log_heads = ts.heads_per_block == 4 ? 2 : ts.heads_per_block - 1;
+  a.row_blocks = (rows + rows_per_block - 1) / rows_per_block;
+  const int slots = causal && KS == 1 ? (a.row_blocks + 1) / 2 : a.row_blocks;  // paired row blocks
+  a.slots = fast_div(slots);
+  a.head_groups = fast_div(dm.G / ts.heads_per_block);
+  a.kv_heads = fast_div(dm.Hkv);
+  a.layers = fast_div(dm.L);
+  const int grid = slots * a.head_groups.divisor * dm.Hkv * dm.B * dm.L;
+  a.per_xcd = grid % kXcds == 0 ? grid / kXcds : 0;
+  a.c2 = dm.scale * kLog2e;
+  a.inv_c2 = 1.f / a.c2;
+  a.lse = lse;
+  a.lse_cache = lse_cache;
+  a.q_rope_pos0 = q_rope_pos0;
+  a.rope_log2_base = q_rope_pos0 >= 0 ? log2f(rope_base) : 0.f;
+  // dynamic LDS next to the static tiles: the query rows, later (two key groups) the rows' statistics
+  constexpr int kTileBytes = KS * 4 * Lay<D>::kTile, kQueryBytes = WAVES / KS * Lay<D>::kHalf, kStatBytes = WAVES * 32 * 16;
+  constexpr int kDynBytes = kTileBytes + kQueryBytes > 160 * 1024 ? kStatBytes : (KS > 1 && kStatBytes > kQueryBytes ? kStatBytes : kQueryBytes);
+  static LdsLimit limit, limit_rotq;
+  const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES, KS> : attn_pipe_kernel<D, WAVES, KS>;
+  const hipError_t e = raise_lds_limit(q_rope_pos0 >= 0 ? limit_rotq : limit, reinterpret_cast<const void*>(kern), kDynBytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), kDynBytes, st, a);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
                        float* lse_cache, int key_splits, float2* part, hipStream_t st, int q_rope_pos0, float rope_base) {
@@ -1399,28 +1596,15 @@ hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments v
       !fits_i32(vs.chunk, vs.c))
     return hipErrorInvalidValue;
   if (key_splits < 1 || (key_splits > 1 && (out.ptr != nullptr || part == nullptr))) return hipErrorInvalidValue;
-  constexpr int kPipeWaves = 8;
-  const bool pipe = out.ptr != nullptr;
-  const TaskShape ts = task_shape(dm.G, pipe ? kPipeWaves : kWaves);
+  if (out.ptr != nullptr) {
+    return attn_pipe_launch<D, 8, 1>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+  }
+  const TaskShape ts = task_shape(dm.G, kWaves);
   const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
   const int row_blocks = (rows + rows_per_block - 1) / rows_per_block;
   const int rb_slots = (causal && key_splits == 1) ? (row_blocks + 1) / 2 : row_blocks;  // paired row blocks
-  dim3 grid(rb_slots * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L * key_splits);
-  constexpr int kQStageBytes = kPipeWaves * 32 * Geo<D>::kRowBytes;  // dynamic LDS next to the static tiles
-  if (pipe) {
-    static LdsLimit limit, limit_rotq;
-    hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_pipe_kernel_w8<D>), kQStageBytes);
-    if (e == hipSuccess) e = raise_lds_limit(limit_rotq, reinterpret_cast<const void*>(attn_pipe_kernel_w8_rotq<D>), kQStageBytes);
-    if (e != hipSuccess) return e;
-  }
-  if (pipe && q_rope_pos0 >= 0)
-    hipLaunchKernelGGL(attn_pipe_kernel_w8_rotq<D>, grid, dim3(kPipeWaves * 64), kQStageBytes, st, dm, q, rows, ks, vs, causal, out, lse,
-                       lse_cache, q_rope_pos0, log2f(rope_base));
-  else if (pipe)
-    hipLaunchKernelGGL(attn_pipe_kernel_w8<D>, grid, dim3(kPipeWaves * 64), kQStageBytes, st, dm, q, rows, ks, vs, causal, out, lse,
-                       lse_cache);
-  else
-    hipLaunchKernelGGL(lse_mfma_kernel<D>, grid, dim3(kThreads), 0, st, dm, q, rows, ks, causal, lse, key_splits, part);
+  const dim3 grid(rb_slots * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L * key_splits);
+  hipLaunchKernelGGL(lse_mfma_kernel<D>, grid, dim3(kThreads), 0, st, dm, q, rows, ks, causal, lse, key_splits, part);
   return hipGetLastError();
 }
 
@@ -1481,7 +1665,7 @@ hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, flo
 bool mfma_path_supported(int dtype, const Dims& dm) { return dtype == CITRUS_BF16 && (dm.D == 64 || dm.D == 128); }
 
 bool attn_mfma_emits_cache_lse(const Segments& ks, int causal, View out) {
-  return out.ptr != nullptr && causal != 0 && ks.n_c > 0 && ks.n_c % 32 == 0;
+  return out.ptr != nullptr && causal != 0 && ks.n_c > 0 && ks.n_c % kTileN == 0;
 }
 
 hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
