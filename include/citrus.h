@@ -185,7 +185,7 @@ int32_t citrus_abi_version(void);
  * lse_cache   optional (cache_len >= 1), dense [B, L, Hq, chunk_len] f32: the same
  *             over the cache states alone, i.e. the normaliser of Eq. (1) as
  *             printed; citrus_cache_score takes it.  A by-product of the bf16
- *             kernel when cache_len is a multiple of 32, else one more pass.
+ *             kernel (f32: one more pass over the cache).
  * lm_score    optional, dense [B, L, Hkv, n] f32: chunk-scored importance,
  *             lm_score[b,l,g,j] = sum over heads h of group g and chunk rows t
  *             of the attention probability p[h,t,j] (0 where masked); Eq. (1)

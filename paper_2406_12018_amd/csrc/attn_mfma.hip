@@ -3,7 +3,7 @@
 // multiply-adds reached 7 TFLOP/s: 8 layers of 32/8 heads, a document of 4096 tokens in chunks of 512, budget 768,
 // took 37.8 ms; on these kernels 0.88 ms.)
 //
-//  attn_pipe_kernel_w8 flash-style chunk attention (Section 4.1 step 1; softmax
+//  attn_pipe_kernel    flash-style chunk attention (Section 4.1 step 1; softmax
 //                      with the 1/sqrt(d_k) scaling of Eq. (1)): online softmax
 //                      over 64-key tiles staged in LDS, S^T = K.Q^T and
 //                      O^T = V^T.P^T on v_mfma_f32_32x32x16_bf16.
@@ -184,7 +184,6 @@ __device__ inline void wait_loads_and_barrier() {
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(LEFT) : "memory");
 }
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 // lanes 0..31: first = own lo_half, second = lo_half of lane l + 32; lanes 32..63: first = hi_half of lane l - 32,
 // second = own hi_half
 __device__ inline void swap_halves(uint32_t lo_half, uint32_t hi_half, uint32_t& first, uint32_t& second) {
@@ -224,12 +223,11 @@ __host__ __device__ inline TaskShape task_shape(int G, int waves = kWaves) {
   return TaskShape{hpb, waves / hpb};
 }
 
-// Row normalisers only (no values, no output): the log-sum-exp of every query row over the keys it sees,
-// or, with key_splits > 1, one partial (running maximum, sum) pair per key range and row.  First pass of the
-// two-pass importance scores and of a cache-only normaliser that the attention launch could not emit.
+// Row normalisers only (no values, no output, no mask): one partial (running maximum, sum) pair per key range and
+// row.  First pass of the two-pass importance scores.
 template <int D>
-__global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, int rows, Segments ks, int causal,
-                                                              float* lse, int key_splits, float2* part) {
+__global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, int rows, Segments ks, int key_splits,
+                                                              float2* part) {
   typedef Geo<D> T;
   constexpr int kRowBytes = T::kRowBytes, kTileBytes = T::kTileBytes;
   __shared__ __attribute__((aligned(1024))) char k_s[2 * kTileBytes];  // double-buffered tiles
@@ -242,24 +240,18 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
   const int row_blocks = (rows + rows_per_block - 1) / rows_per_block;
   // Workgroups are handed to the 8 XCDs round-robin by their linear id.  Remap so that the
   // workgroups of one (document, layer, KV head), which read the same K/V, land on ONE XCD and
-  // share its L2; within a unit the row blocks with the longest causal range come first.
+  // share its L2.
   int logical = blockIdx.x;
   const int total = gridDim.x;
   if (total % kXcds == 0) logical = (blockIdx.x % kXcds) * (total / kXcds) + blockIdx.x / kXcds;
-  // With key_splits > 1 each workgroup covers one contiguous range of key
-  // tiles and writes a partial (running maximum, sum) pair per row; the consumer merges them.
+  // Each workgroup covers one contiguous range of key tiles and writes a partial (running maximum, sum) pair per row;
+  // the consumer merges them.
   const int sp = logical % key_splits;
   logical /= key_splits;
-  // Causal attention: a workgroup takes the row block with the longest key range still free and then
-  // its mirror image (the shortest), so every workgroup does the same number of key tiles.
-  const bool paired = causal != 0 && key_splits == 1;
-  const int rb_slots = paired ? (row_blocks + 1) / 2 : row_blocks;
-  const int rb_first = row_blocks - 1 - logical % rb_slots;
-  const int rb_second = row_blocks - 1 - rb_first;
-  const int passes = (paired && rb_second != rb_first) ? 2 : 1;
-  const int hg = (logical / rb_slots) % head_groups;
-  const int g = (logical / (rb_slots * head_groups)) % dm.Hkv;
-  const int bl = logical / (rb_slots * head_groups * dm.Hkv);
+  const int rb = row_blocks - 1 - logical % row_blocks;
+  const int hg = (logical / row_blocks) % head_groups;
+  const int g = (logical / (row_blocks * head_groups)) % dm.Hkv;
+  const int bl = logical / (row_blocks * head_groups * dm.Hkv);
   const int b = bl / dm.L, l = bl % dm.L;
   const int h = g * dm.G + hg * ts.heads_per_block + (w % ts.heads_per_block);
   const int n_c = ks.n_c;
@@ -315,21 +307,13 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
   int k_off[T::kKk];
 #pragma unroll
   for (int kk = 0; kk < T::kKk; ++kk) k_off[kk] = col * kRowBytes + (((2 * kk + grp) ^ f_col) * 16);
-  for (int pass = 0; pass < passes; ++pass) {
-  const int rb = pass == 0 ? rb_first : rb_second;
   const int row0 = (rb * ts.tiles_per_block + w / ts.heads_per_block) * kRowsPerWave;
 
-  // last candidate any row of this block / this wave can see
-  const int blk_row_last = min(rows, (rb + 1) * rows_per_block) - 1;
-  const int blk_limit = causal ? n_c + blk_row_last : n - 1;
-  const int all_tiles = blk_limit / kTileN + 1;
+  const int all_tiles = (n - 1) / kTileN + 1;
   const int tiles_per_split = (all_tiles + key_splits - 1) / key_splits;
   const int t_begin = sp * tiles_per_split;
   const int t_end = min(all_tiles, t_begin + tiles_per_split);
   const bool wave_active = row0 < rows;
-  const int wave_row_last = min(rows, row0 + kRowsPerWave) - 1;
-  const int wave_limit_max = causal ? n_c + wave_row_last : n - 1;  // beyond it the wave sees nothing
-  const int wave_limit_min = causal ? n_c + row0 : n - 1;           // up to it every row sees everything
 
   // ---- Q^T operand, kept in registers: q_op[kk] = Q[row0 + col][16 kk + 8 grp ..+7] ----
   bf16x8 q_op[T::kKk];
@@ -343,7 +327,6 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
       q_op[kk] = p.v;
     }
   }
-  const int limit_lane = causal ? n_c + t_lane : n - 1;
 
   // ---- running softmax state: one query per lane ----
   const float c2 = dm.scale * kLog2e;  // logits are kept in the log2 domain
@@ -361,7 +344,7 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
     // ended that iteration: the next tile can stream into it while this one is computed.
     if (jt + 1 < t_end) fetch_tile(j0 + kTileN, buf ^ 1);
 
-    if (wave_active && j0 <= wave_limit_max) {
+    if (wave_active) {
       // S^T = K . Q^T for 64 keys x 32 queries
       f32x16 s_acc[2];
 #pragma unroll
@@ -383,13 +366,13 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
             s_acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt][kk].v, q_op[4 * kh + kk], s_acc[mt], 0, 0, 0);
       }
 
-      if (j0 + kTileN - 1 > wave_limit_min) {  // wave-uniform: only tiles that touch the causal edge / the tail
+      if (j0 + kTileN > n) {  // wave-uniform: the last tile
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int j = j0 + 32 * mt + 8 * (i / 4) + 4 * grp + (i % 4);
-            if (j > limit_lane) s_acc[mt][i] = -INFINITY;
+            if (j >= n) s_acc[mt][i] = -INFINITY;
           }
       }
       // Running maximum, kept lazily: softmax is invariant to the subtracted value, so m_run only has
@@ -423,13 +406,10 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
 
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const int t = row0 + col;
-  if (wave_active && t < rows) {
-  const int64_t row_id = (static_cast<int64_t>(bl) * dm.Hq + h) * rows + t;
-  if (part != nullptr && grp == 0)  // log2 domain; an empty or fully masked range leaves (-inf, 0)
+  if (wave_active && t < rows && grp == 0) {  // log2 domain; an empty range leaves (-inf, 0)
+    const int64_t row_id = (static_cast<int64_t>(bl) * dm.Hq + h) * rows + t;
     part[static_cast<int64_t>(sp) * dm.B * dm.L * dm.Hq * rows + row_id] = make_float2(m_run, l_tot);
-  if (lse != nullptr && grp == 0) lse[row_id] = (m_run + log2f(l_tot)) * kLn2;
-  }  // row valid
-  }  // pass
+  }
 }
 
 // Division by a number that is known at launch: n / divisor for 0 <= n < 2^31 by a multiplication.
@@ -461,6 +441,7 @@ inline UnitView unit_view(const View& v) {
 struct AttnArgs {
   UnitView q, out, k_cache, k_chunk, v_cache, v_chunk;
   int rows, n_c, c, causal, q_heads;
+  int paired;      // a workgroup takes a row block and its mirror image
   int log_heads;   // 2^log_heads query heads of a group per workgroup
   int row_blocks;  // of a head
   int per_xcd;     // workgroups per XCD, 0: not a whole number
@@ -491,69 +472,59 @@ struct AttnArgs {
 // instead of 2.4 GHz: it is power that bounds a full chip); empty cache 141 -> 128 us; 16 layers of 32/32 heads, 1024
 // rows over 1024 + 1024 states 493 -> 451 us; 64/8 heads, 2048 rows over 4096 + 2048 states 1286 -> 1227 us; head_dim 64,
 // 8 layers 54 -> 49 us.
-template <int D, int WAVES, int KS, bool ROTATE_Q>
+template <int D, int WAVES, bool ROTATE_Q>
 __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   typedef Geo<D> T;
   typedef Lay<D> Y;
   constexpr int kRowBytes = T::kRowBytes;
-  static_assert(KS == 1 || KS == 2, "key groups");
-  constexpr int kRowWaves = WAVES / KS;  // waves of a key group: one 32-row tile each
-  // per key group: two K tiles, then two V tiles (double buffers)
-  __shared__ __attribute__((aligned(1024))) char ring[KS * 4 * Y::kTile];
-  // [kRowWaves] query row tiles, laid out like half a key tile.  Two key groups: these pass through the V buffers that
-  // are filled last, and this holds the rows' statistics.
+  // two K tiles, then two V tiles (double buffers)
+  __shared__ __attribute__((aligned(1024))) char ring[4 * Y::kTile];
+  // [WAVES] query row tiles, laid out like half a key tile
   extern __shared__ __attribute__((aligned(1024))) char q_stage[];
 
   const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
   const int col = lane % 32, grp = lane / 32;
   constexpr int kR = T::kRowsPerLoad;
-  constexpr int kFillRows = kTileN / kRowWaves;         // rows of a tile each wave of the group fetches
+  constexpr int kFillRows = kTileN / WAVES;             // rows of a tile each wave fetches
   constexpr int kPer = kFillRows / kR;                  // load instructions per wave and tile
   constexpr int kSlots = T::kKk / 2;                    // places between the MFMAs of a product that take loads
   constexpr int kPerSlot = (kPer + kSlots - 1) / kSlots;
-  static_assert(kPer >= 1, "every wave of a group fetches");
-  const int rows_per_block = (kRowWaves >> a.log_heads) * kRowsPerWave;
+  static_assert(kPer >= 1, "every wave fetches");
+  const int rows_per_block = (WAVES >> a.log_heads) * kRowsPerWave;
   // Workgroups are handed to the 8 XCDs round-robin by their linear id.  Remap so that the
   // workgroups of one (document, layer, KV head), which read the same K/V, land on ONE XCD and
   // share its L2; within a unit the row blocks with the longest causal range come first.
   const int logical = a.per_xcd > 0 ? (blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds : blockIdx.x;
-  // Causal attention: a workgroup takes the row block with the longest key range still free and then
-  // its mirror image (the shortest), so every workgroup does the same number of key tiles.  With two key groups
-  // (launches that do not fill the chip) a row block is a workgroup of its own.
-  const bool paired = a.causal != 0 && KS == 1;
+  // Causal attention that fills the chip: a workgroup takes the row block with the longest key range still free and
+  // then its mirror image (the shortest), so every workgroup does the same number of key tiles.  In smaller launches
+  // a row block is a workgroup of its own.
   const int of_slot = a.slots.quotient(logical), of_hg = a.head_groups.quotient(of_slot), of_g = a.kv_heads.quotient(of_hg);
   const int rb_first = a.row_blocks - 1 - (logical - of_slot * a.slots.divisor);
   const int rb_second = a.row_blocks - 1 - rb_first;
-  const int passes = (paired && rb_second != rb_first) ? 2 : 1;
+  const int passes = (a.paired && rb_second != rb_first) ? 2 : 1;
   const int hg = of_slot - of_hg * a.head_groups.divisor;
   const int g = of_hg - of_g * a.kv_heads.divisor;
   const int bl = of_g;
   const int b = a.layers.quotient(bl), l = bl - b * a.layers.divisor;
   const int wu = __builtin_amdgcn_readfirstlane(w);  // the wave's index as a scalar: what depends on it stays scalar
-  const int kg = KS == 1 ? 0 : wu / kRowWaves;       // key group: tiles kg, kg + KS, ... of the block's key range
-  const int wr = KS == 1 ? wu : wu % kRowWaves;
-  char* const k_s = ring + kg * 4 * Y::kTile;
+  char* const k_s = ring;
   char* const v_s = k_s + 2 * Y::kTile;
-  const int h = ((g * a.head_groups.divisor + hg) << a.log_heads) + (wr & ((1 << a.log_heads) - 1));
+  const int h = ((g * a.head_groups.divisor + hg) << a.log_heads) + (wu & ((1 << a.log_heads) - 1));
   const int n_c = a.n_c;
   auto unit = [&](const UnitView& v, int head) { return v.ptr + (b * v.sb + l * v.sl + head * v.sh); };
 
   // ---- global -> LDS staging of one 64-key tile, without a stop in registers ----
   // buffer_load ... lds: a wave-level instruction moves 64 x 16 B from per-lane global addresses to 1 KB of consecutive
   // LDS.  The swizzle of a row's segments (Lay) is realised by the loading lane, which fetches global segment
-  // (its position in the LDS row) ^ swz(row).  The candidates are tiled segment by segment, so that every tile lies in one segment and
-  // is fetched with one buffer resource: the cache's whole tiles, the chunk's tiles, the ragged rest of the cache.  Rows behind the end of a segment are out of
+  // (its position in the LDS row) ^ swz(row).  The candidates are tiled segment by segment, the cache first, so that every
+  // tile lies in one segment and is fetched with one buffer resource.  Rows behind the end of a segment are out of
   // the resource's range and read as zeros; their logits are masked.
   typedef __attribute__((address_space(3))) char* lds_char_ptr;
   auto lds_addr = [](char* p) { return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char_ptr)p)); };
-  const int fill_row0 = kFillRows * wr;  // first tile row this wave fetches
+  const int fill_row0 = kFillRows * wu;  // first tile row this wave fetches
   const int fill_row = fill_row0 + lane / T::kSegs, fill_seg16 = ((lane % T::kSegs) ^ Y::swz(lane / T::kSegs)) * 16;
   const uint32_t fill_lds0 = lds_addr(k_s) + fill_row0 / kR * Y::kBlock;
-  const int cache_tiles = n_c / kTileN;         // whole ones
-  const int ragged = n_c % kTileN ? 1 : 0;      // one more tile, the last of a row block
-  auto tile_of = [&](int i) { return KS * i + kg; };  // the group's i-th tile
-  auto below = [&](int tiles) { return KS == 1 ? tiles : tiles > kg ? (tiles - kg + KS - 1) / KS : 0; };  // group tiles among the first `tiles`
-  const int i_chunk = below(cache_tiles);  // the group's first tile behind the whole cache tiles
+  const int cache_tiles = (n_c + kTileN - 1) / kTileN;
   // One stream of tiles (K or V): the resource of the segment it is in and, per load instruction, the lane's byte offset
   // of its next tile (row and segment; the range check covers this offset only, so no part of it is a scalar).
   struct Stream {
@@ -567,7 +538,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   const i32x4 v_rs_cache = seg_words(a.v_cache, n_c), v_rs_chunk = seg_words(a.v_chunk, a.c);
   auto enter = [&](Stream& s, const i32x4& rs, int ss, int first_row) {  // positions the stream at a tile of a segment
     s.rs = rs;
-    s.step = kTileN * KS * ss;
+    s.step = kTileN * ss;
 #pragma unroll
     for (int x = 0; x < kPer; ++x) s.voff[x] = (first_row + fill_row + kR * x) * ss + fill_seg16;
   };
@@ -611,29 +582,23 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   // The first step of a row block multiplies p_prev = 0 with the second half of V buffer 1, which nothing has filled
   // yet in the first row block, and rows behind the end of a segment are never multiplied with anything but 0: the V
   // buffers are zeroed once (0 x garbage could be NaN), in front of the first loads into them.
-  auto zero_v = [&](int from, int to) {
-    for (int at = from + 16 * (tid - kg * kRowWaves * 64); at < to; at += 16 * kRowWaves * 64)
+  auto zero_v = [&] {
+    for (int at = 16 * tid; at < 2 * Y::kTile; at += 16 * WAVES * 64)
       *reinterpret_cast<uint4*>(v_s + at) = make_uint4(0u, 0u, 0u, 0u);
   };
-  // two key groups of four row tiles each: the query rows do not fit next to the tiles and pass through V buffer 1
-  constexpr bool kQueryInV = KS * 4 * Y::kTile + kRowWaves * Y::kHalf > 160 * 1024;
-  static_assert(!kQueryInV || kRowWaves * Y::kHalf <= KS * Y::kTile, "the query rows fit one V buffer of each group");
 
   for (int pass = 0; pass < passes; ++pass) {
   const int rb = pass == 0 ? rb_first : rb_second;
-  const int row0 = rb * rows_per_block + (wr >> a.log_heads) * kRowsPerWave;
+  const int row0 = rb * rows_per_block + (wu >> a.log_heads) * kRowsPerWave;
 
-  // every key group walks the same number of tiles, so the last one of a group may lie past the block's range (its
-  // logits are masked)
   const int rows = a.rows;
   const int blk_row_last = min(rows, (rb + 1) * rows_per_block) - 1;
-  const int ragged_tile = cache_tiles + (a.causal ? blk_row_last : a.c - 1) / kTileN + 1;  // the ragged rest of the cache, or the end
-  const int i_ragged = below(ragged_tile);
-  const int t_end = (ragged_tile + ragged + KS - 1) / KS;
+  const int t_end = cache_tiles + (a.causal ? blk_row_last : a.c - 1) / kTileN + 1;
   // candidates are numbered tile by tile here: chunk state x is candidate chunk0 + x
   const int chunk0 = cache_tiles * kTileN;
   const int wave_limit_min = chunk0 + (a.causal ? row0 : a.c - 1);  // up to it every row sees the chunk's states
-  const int first_masked = min((wave_limit_min + 1) / 32, 2 * ragged_tile);  // half tiles from here on may need a mask
+  const int chunk_masked = (wave_limit_min + 1) / 32;               // half tiles of the chunk from here on may need a mask
+  int next_masked = n_c % kTileN ? n_c / 32 : chunk_masked;         // the next half tile that may need one
 
   // ---- Q^T operand, kept in registers: q_op[kk] = Q[row0 + col][16 kk + 8 grp ..+7] ----
   bf16x8 q_op[T::kKk];
@@ -646,9 +611,8 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   float m_sub = 0.f;         // what is subtracted: m_run, or 0 for a row that has seen nothing yet (exp2(-inf) = 0)
   float m_high = -INFINITY;  // a logit above it moves m_run
   // Optional by-product: each row's log-sum-exp over the cache states alone, i.e. the running (maximum, sum) pair behind
-  // the group's last cache tile (the launcher asks for it only if the cache ends with a whole tile); every row sees
-  // every cache state.
-  const int snap_i = a.lse_cache != nullptr ? i_chunk - 1 : -1;
+  // the last cache tile; every row sees every cache state.
+  const int snap_i = a.lse_cache != nullptr ? cache_tiles - 1 : -1;
   float m_snap = -INFINITY, l_snap = 0.f;
   f32x16 o_acc[T::kOut];
 #pragma unroll
@@ -674,10 +638,9 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   // product is formed and not used; p_prev is zero before the first step.  v_t: the previous half tile of V.
   // issue_k(slot) / issue_v(slot) put the loads of the tile being fetched between the MFMAs.
   auto half_step = [&](int hc, const char* v_t, auto&& issue_k, auto&& issue_v, auto&& before_tail) {
-    if (__builtin_expect(hc >= first_masked, 0)) {  // wave-uniform: the causal edge and the ends of the segments only
-      const int jb = 32 * hc;
-      const bool rest = hc >= 2 * ragged_tile;  // of the cache (with two key groups also what lies behind it)
-      const int lim_rel = (rest ? kTileN * ragged_tile + n_c % kTileN - 1 : limit_lane) - jb - 4 * grp;
+    if (__builtin_expect(hc >= next_masked, 0)) {  // wave-uniform: the causal edge and the ends of the segments only
+      const int lim_rel = (hc < 2 * cache_tiles ? n_c - 1 : limit_lane) - 32 * hc - 4 * grp;
+      if (hc + 1 >= 2 * cache_tiles) next_masked = chunk_masked;
 #pragma unroll
       for (int x = 0; x < 16; ++x)
         if (8 * (x / 4) + (x % 4) > lim_rel) s_cur[x] = -INFINITY;
@@ -808,31 +771,21 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
 
   // ---- first requests: K 0, the query rows | V 0, K 1 (the first two are waited for first) ----
   Stream sk, sv;
-  // a stream enters the next segment at the group's first chunk tile and at the ragged rest of the cache
-  auto reposition = [&](Stream& s, const i32x4& rs_cache, const i32x4& rs_chunk, int ss_cache, int ss_chunk, int i) {
-    if (i >= i_chunk && i < i_ragged)
-      enter(s, rs_chunk, ss_chunk, kTileN * (tile_of(i) - cache_tiles));
-    else
-      enter(s, rs_cache, ss_cache, kTileN * (i < i_chunk ? tile_of(i) : tile_of(i) - ragged_tile + cache_tiles));
-  };
-  int k_switch = -1, v_switch = -1;  // the tile at which the stream enters the next segment
-  auto position_k = [&](int i) {
-    reposition(sk, k_rs_cache, k_rs_chunk, k_ss_cache, k_ss_chunk, i);
-    k_switch = i < i_chunk ? i_chunk : i_ragged;
-  };
-  auto position_v = [&](int i) {
-    reposition(sv, v_rs_cache, v_rs_chunk, v_ss_cache, v_ss_chunk, i);
-    v_switch = i < i_chunk ? i_chunk : i_ragged;
-  };
-  position_k(0);
-  position_v(0);
+  auto k_to_chunk = [&] { enter(sk, k_rs_chunk, k_ss_chunk, 0); };  // in front of tile cache_tiles
+  auto v_to_chunk = [&] { enter(sv, v_rs_chunk, v_ss_chunk, 0); };
+  if (cache_tiles > 0) {
+    enter(sk, k_rs_cache, k_ss_cache, 0);
+    enter(sv, v_rs_cache, v_ss_cache, 0);
+  } else {
+    k_to_chunk();
+    v_to_chunk();
+  }
   fetch(sk, integral_constant<int, 0>{});
   advance(sk);
   // The wave's 32 query rows come in through LDS as well: whole rows, kR per load instruction, laid out like half a
   // key tile, from where the B operand is read like a key operand.  Loading them straight
   // into the operand layout would put 64 scattered 16-byte pieces into every load instruction.
-  char* const q_t = kQueryInV ? ring + (wr * 2 / kRowWaves * 4 + 3) * Y::kTile + wr % (kRowWaves / 2) * Y::kHalf
-                              : q_stage + wr * Y::kHalf;
+  char* const q_t = q_stage + wu * Y::kHalf;
   {
     const int q_ss2 = a.q.ss;
     const i32x4 q_rs = buffer_words(unit(a.q, h), (rows - 1) * q_ss2 + 2 * D);
@@ -840,19 +793,18 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     int r_in = lane / T::kSegs, seg16 = ((lane % T::kSegs) ^ Y::swz(lane / T::kSegs)) * 16;
     hide_loop_invariance(r_in, seg16);
 #pragma unroll
-    for (int x = 0; x < 32 / kR / KS; ++x) {  // the key groups share the rows and their loads
-      const int i = 32 / kR / KS * kg + x;
+    for (int i = 0; i < 32 / kR; ++i) {
       const int row = min(row0 + kR * i + r_in, rows - 1);  // rows past the end repeat the last one; never stored
       load_lds_unwatched<0>(q_rs, q_lds + i * Y::kBlock, max(row, 0) * q_ss2 + seg16, 0);
     }
   }
   if (pass == 0) {
-    zero_v(0, kQueryInV ? Y::kTile : 2 * Y::kTile);
+    zero_v();
     lds_writes_and_barrier();
   }
   fetch(sv, integral_constant<int, 2>{});
   advance(sv);
-  if (k_switch == 1) position_k(1);
+  if (cache_tiles == 1) k_to_chunk();
   fetch(sk, integral_constant<int, 1>{});
   advance(sk);
   wait_loads_and_barrier<2 * kPer, true>();  // K 0 and the query rows have landed
@@ -864,7 +816,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   if (ROTATE_Q) {
     constexpr int kPairs = T::kSegs / 2, kRoundRows = 64 / kPairs;
 #pragma unroll 1
-    for (int round = kg; round < 32 / kRoundRows; round += KS) {
+    for (int round = 0; round < 32 / kRoundRows; ++round) {
       const int r = kRoundRows * round + lane / kPairs, sg = lane % kPairs;
       uint4* lo_p = reinterpret_cast<uint4*>(q_t + Y::at(r, sg));
       uint4* hi_p = reinterpret_cast<uint4*>(q_t + Y::at(r, sg + kPairs));
@@ -883,7 +835,6 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       *lo_p = lo.u;
       *hi_p = hi.u;
     }
-    if (KS > 1) lds_writes_and_barrier();  // the groups rotated parts of each other's rows
   }
 #pragma unroll
   for (int kk = 0; kk < T::kKk; ++kk) {
@@ -892,10 +843,6 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     q_op[kk] = p.v;
   }
   read_k_ops(k_s);
-  if (kQueryInV) {  // every wave has its query operand: the buffer it came through is zeroed for the first step
-    lds_writes_and_barrier();
-    zero_v(Y::kTile, 2 * Y::kTile);
-  }
 #pragma unroll
   for (int i = 0; i < 16; ++i) s_cur[i] = 0.f;
 #pragma unroll
@@ -906,9 +853,8 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   for (int i = 1; i < 16; ++i) mx_cur = fmaxf(mx_cur, s_cur[i]);
   high = ~uint64_t{0};
   read_k_ops(k_s + Y::kHalf);
-  if (kQueryInV) lds_writes_and_barrier();
 
-  // One 64-key tile.  `parity` is the tile's buffer (the group's tile i lives in buffer
+  // One 64-key tile.  `parity` is the tile's buffer (tile i lives in buffer
   // i % 2), so every LDS address is a per-lane register plus an immediate offset, and nothing branches but for the rare
   // cases.  It always fetches; what it fetches past the block's range is not read.
   const bool early = WAVES == 8 && wu >= 4;
@@ -918,9 +864,9 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       ((X / kPerSlot == slot ? issue_one(s, buf, integral_constant<int, X>{}) : (void)0), ...);
     }(std::make_integer_sequence<int, kPer>{});
   };
-  auto rare_events = [&](int i) {  // streams that enter another segment
-    if (__builtin_expect(i + 2 == k_switch, 0)) position_k(i + 2);
-    if (__builtin_expect(i + 1 == v_switch, 0)) position_v(i + 1);
+  auto rare_events = [&](int i) {
+    if (__builtin_expect(i + 2 == cache_tiles, 0)) k_to_chunk();
+    if (__builtin_expect(i + 1 == cache_tiles, 0)) v_to_chunk();
   };
   auto note_cache = [&](int i) {
     if (__builtin_expect(i == snap_i, 0)) {
@@ -932,7 +878,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     constexpr int P = decltype(parity)::value;
     // P.V of the second half of tile i - 1 (before the first tile: p_prev = 0 times the zeros written above,
     // or times stale finite data in later row blocks)
-    half_step(2 * tile_of(i), v_s + (1 - P) * Y::kTile + Y::kHalf, no_issue, no_issue, [&] { if (early) wait_loads_and_barrier<0, false>(); });
+    half_step(2 * i, v_s + (1 - P) * Y::kTile + Y::kHalf, no_issue, no_issue, [&] { if (early) wait_loads_and_barrier<0, false>(); });
     // Every wave has read the second half of K tile i and the last of V tile i - 1: their buffers
     // take K tile i + 2 and V tile i + 1, which are first read after the next barrier.
     if (!early) wait_loads_and_barrier<0, false>();
@@ -940,7 +886,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     rare_events(i);
     constexpr integral_constant<int, P> kbuf{};
     constexpr integral_constant<int, 3 - P> vbuf{};
-    half_step(2 * tile_of(i) + 1, v_s + P * Y::kTile, [&](int slot) { issue_slot(sk, kbuf, slot); },
+    half_step(2 * i + 1, v_s + P * Y::kTile, [&](int slot) { issue_slot(sk, kbuf, slot); },
               [&](int slot) { issue_slot(sv, vbuf, slot); }, [] {});
     advance(sk);
     advance(sv);
@@ -982,111 +928,63 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
                                                                           (rows - 1) * out_ss + 2 * D, kBufferFlags);
   int colx = col, lanex = lane;
   hide_loop_invariance(colx, lanex);  // offsets are formed here, per row block, not kept in registers
-  if constexpr (KS == 1) {
-    const int t = row0 + col;
-    if (grp == 0 && t < rows) {
-      if (a.lse_cache != nullptr) a.lse_cache[row_id0 + t] = (m_snap + log2f(l_snap_tot)) * kLn2;
-      if (a.lse != nullptr) a.lse[row_id0 + t] = (m_run + log2f(l_tot)) * kLn2;
-    }
-    // Each wave parks its 32 x D tile in its own part of the tile buffers (free after the barrier above; 16-byte
-    // segments XOR-swizzled by the row: column-wise writes spread over the banks) and stores it back as whole rows.  A
-    // lane and its partner l ^ 32 hold the two halves of every segment: a swap gives each of them whole segments.
-    char* const o_tile = ring + wu * (32 * kRowBytes);
-    char* const o_s = o_tile + colx * kRowBytes;
-    const int c_swz = colx % T::kSegs;
-    const float inv = 1.f / l_tot;
-#pragma unroll
-    for (int r = 0; r < T::kOut; ++r)
-#pragma unroll
-      for (int ip = 0; ip < 2; ++ip) {
-        // registers 4 i4 .. + 3, i4 = 2 ip + x, are rows c' = 8 i4 + 4 grp + 0..3 -> head_dim 16 r + (c' % 16) + D / 2 (c' / 16)
-        uint32_t wd[2][2];
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int y = 0; y < 2; ++y)
-            wd[x][y] = pack_bf16x2(o_acc[r][8 * ip + 4 * x + 2 * y] * inv, o_acc[r][8 * ip + 4 * x + 2 * y + 1] * inv);
-        uint4 piece;  // segment 2 r + grp + D / 16 ip
-        swap_halves(wd[0][0], wd[1][0], piece.x, piece.z);
-        swap_halves(wd[0][1], wd[1][1], piece.y, piece.w);
-        *reinterpret_cast<uint4*>(o_s + ((2 * r + T::kSegs / 2 * ip + grp) ^ c_swz) * 16) = piece;
-      }
-    const char* const o_r = o_tile + lanex * 16;  // row lanex / kSegs of a kR-row group
-    const int r_in = lanex / T::kSegs, pos = lanex % T::kSegs;
-    int at = (row0 + r_in) * out_ss;
-#pragma unroll
-    for (int i = 0; i < 32 / kR; ++i, at += kR * out_ss) {
-      const u32x4 piece = *reinterpret_cast<const u32x4*>(o_r + kR * i * kRowBytes);
-      __builtin_amdgcn_raw_buffer_store_b128(piece, out_rs, at + (pos ^ ((kR * i + r_in) % T::kSegs)) * 16, 0, 0);
-    }
-    __syncthreads();  // the parked tiles have been read back: the next row block may fill the buffers
-  } else {
-    // Two key groups: the (maximum, sum, output) of a row tile are in two waves.  Both leave their f32 output rows
-    // in LDS (16-byte segments XOR-swizzled by the row: the column-wise writes and the row-wise reads spread over the
-    // banks); each of them then weighs and adds the two partial rows of sixteen rows and stores them whole.
-    constexpr int kSegs32 = D / 4;  // 16-byte segments of an f32 row
-    static_assert(WAVES * 32 * D * 4 <= KS * 4 * Y::kTile, "the f32 tiles fit the tile buffers");
-    float* const o_s = reinterpret_cast<float*>(ring) + (wu * 32 + colx) * D;
-    float4* const stat = reinterpret_cast<float4*>(q_stage);  // [KS][kRowWaves * 32]; the query rows are spent
-#pragma unroll
-    for (int r = 0; r < T::kOut; ++r)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const int sg = 4 * r + 2 * (i4 % 2) + grp + kSegs32 / 2 * (i4 / 2);
-        *reinterpret_cast<float4*>(o_s + 4 * (sg ^ (colx % kSegs32))) =
-            make_float4(o_acc[r][4 * i4], o_acc[r][4 * i4 + 1], o_acc[r][4 * i4 + 2], o_acc[r][4 * i4 + 3]);
-      }
-    if (grp == 0) stat[wu * 32 + col] = make_float4(m_run, l_tot, m_snap, l_snap_tot);
-    __syncthreads();
-    constexpr int kRowLanes = kSegs32 / 2;  // lane x of a row owns segments x and x + kSegs32 / 2
-    const int x = lanex % kRowLanes;
-#pragma unroll
-    for (int it = 0; it < 16 * kRowLanes / 64; ++it) {
-      const int r = 16 * kg + it * (64 / kRowLanes) + lanex / kRowLanes;  // row of the tile
-      const float4 s0 = stat[wr * 32 + r], s1 = stat[(kRowWaves + wr) * 32 + r];
-      const float m_all = fmaxf(s0.x, s1.x);  // finite: tile 0 is visible to every row
-      float w0 = __builtin_amdgcn_exp2f(s0.x - m_all), w1 = __builtin_amdgcn_exp2f(s1.x - m_all);
-      const float l_all = fmaf(s0.y, w0, s1.y * w1);
-      const float inv = 1.f / l_all;
-      w0 *= inv;
-      w1 *= inv;
-      const float* const o0 = reinterpret_cast<const float*>(ring) + (wr * 32 + r) * D;
-      const float* const o1 = o0 + kRowWaves * 32 * D;
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-        const int sg = x + y * kRowLanes;
-        const float4 p0 = *reinterpret_cast<const float4*>(o0 + 4 * (sg ^ (r % kSegs32)));
-        const float4 p1 = *reinterpret_cast<const float4*>(o1 + 4 * (sg ^ (r % kSegs32)));
-        const u32x2 wds = {pack_bf16x2(fmaf(p0.x, w0, p1.x * w1), fmaf(p0.y, w0, p1.y * w1)),
-                           pack_bf16x2(fmaf(p0.z, w0, p1.z * w1), fmaf(p0.w, w0, p1.w * w1))};
-        __builtin_amdgcn_raw_buffer_store_b64(wds, out_rs, (row0 + r) * out_ss + sg * 8, 0, 0);
-      }
-      if ((a.lse != nullptr || a.lse_cache != nullptr) && x == 0 && row0 + r < rows) {
-        if (a.lse != nullptr) a.lse[row_id0 + row0 + r] = (m_all + log2f(l_all)) * kLn2;
-        if (a.lse_cache != nullptr) {
-          const float m_c = fmaxf(s0.z, s1.z);
-          const float l_c = s0.w * __builtin_amdgcn_exp2f(s0.z - m_c) + s1.w * __builtin_amdgcn_exp2f(s1.z - m_c);
-          a.lse_cache[row_id0 + row0 + r] = (m_c + log2f(l_c)) * kLn2;
-        }
-      }
-    }
+  const int t = row0 + col;
+  if (grp == 0 && t < rows) {
+    if (a.lse_cache != nullptr) a.lse_cache[row_id0 + t] = (m_snap + log2f(l_snap_tot)) * kLn2;
+    if (a.lse != nullptr) a.lse[row_id0 + t] = (m_run + log2f(l_tot)) * kLn2;
   }
+  // Each wave parks its 32 x D tile in its own part of the tile buffers (free after the barrier above; 16-byte
+  // segments XOR-swizzled by the row: column-wise writes spread over the banks) and stores it back as whole rows.  A
+  // lane and its partner l ^ 32 hold the two halves of every segment: a swap gives each of them whole segments.
+  char* const o_tile = ring + wu * (32 * kRowBytes);
+  char* const o_s = o_tile + colx * kRowBytes;
+  const int c_swz = colx % T::kSegs;
+  const float inv = 1.f / l_tot;
+#pragma unroll
+  for (int r = 0; r < T::kOut; ++r)
+#pragma unroll
+    for (int ip = 0; ip < 2; ++ip) {
+      // registers 4 i4 .. + 3, i4 = 2 ip + x, are rows c' = 8 i4 + 4 grp + 0..3 -> head_dim 16 r + (c' % 16) + D / 2 (c' / 16)
+      uint32_t wd[2][2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+          wd[x][y] = pack_bf16x2(o_acc[r][8 * ip + 4 * x + 2 * y] * inv, o_acc[r][8 * ip + 4 * x + 2 * y + 1] * inv);
+      uint4 piece;  // segment 2 r + grp + D / 16 ip
+      swap_halves(wd[0][0], wd[1][0], piece.x, piece.z);
+      swap_halves(wd[0][1], wd[1][1], piece.y, piece.w);
+      *reinterpret_cast<uint4*>(o_s + ((2 * r + T::kSegs / 2 * ip + grp) ^ c_swz) * 16) = piece;
+    }
+  const char* const o_r = o_tile + lanex * 16;  // row lanex / kSegs of a kR-row group
+  const int r_in = lanex / T::kSegs, pos = lanex % T::kSegs;
+  int at = (row0 + r_in) * out_ss;
+#pragma unroll
+  for (int i = 0; i < 32 / kR; ++i, at += kR * out_ss) {
+    const u32x4 piece = *reinterpret_cast<const u32x4*>(o_r + kR * i * kRowBytes);
+    __builtin_amdgcn_raw_buffer_store_b128(piece, out_rs, at + (pos ^ ((kR * i + r_in) % T::kSegs)) * 16, 0, 0);
+  }
+  __syncthreads();  // the parked tiles have been read back: the next row block may fill the buffers
   }  // pass
 }
 
-// Eight waves per workgroup: two 32-row tiles of the four heads of a KV group (or the equivalent
+// Eight waves, launches that fill the chip: two 32-row tiles of the four heads of a KV group (or the equivalent
 // split for smaller groups) share every K/V tile, which halves the fetch traffic per MFMA
 // against four waves; one workgroup per CU, two waves per SIMD.
-template <int D, int WAVES, int KS>
+// Four waves, smaller launches: half of the rows per workgroup and one wave per SIMD, which has the matrix pipe to itself
+// (attn_launch has the line between the two).  A row's sums run over the same tiles in the same order in either: its
+// bits do not depend on the size of the launch.  (Splitting the keys of a row between two pairs of waves as well gave
+// 19.8 instead of 24.4 us at 32/8 heads, 512 rows over 768 + 512 states, but other bits.)
+template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel(AttnArgs a) {
-  attn_pipe_body<D, WAVES, KS, false>(a);
+  attn_pipe_body<D, WAVES, false>(a);
 }
 // The same kernel for query rows that arrive without rotary embedding (position shift): they are rotated
 // in the LDS staging region before the operands are read.  An instance of its own, so that the kernel
 // above does not carry the extra prologue.
-template <int D, int WAVES, int KS>
+template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel_rotq(AttnArgs a) {
-  attn_pipe_body<D, WAVES, KS, true>(a);
+  attn_pipe_body<D, WAVES, true>(a);
 }
 
 // Brings the per-range (maximum, sum) pairs of a row, part[s * rows_total + row], to one normaliser,
@@ -1544,10 +1442,10 @@ bool fits_i32(const View& v, int rows) {
 }
 
 // Attention with output: one instance of the kernel.
-template <int D, int WAVES, int KS>
-hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
-                            float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
-  const TaskShape ts = task_shape(dm.G, WAVES / KS);
+template <int D, int WAVES>
+hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, bool paired, View out,
+                            float* lse, float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+  const TaskShape ts = task_shape(dm.G, WAVES);
   const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
   AttnArgs a;
   a.q = unit_view(q);
@@ -1563,7 +1461,8 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segme
   a.q_heads = dm.Hq;
   a.log_heads = ts.heads_per_block == 4 ? 2 : ts.heads_per_block - 1;
   a.row_blocks = (rows + rows_per_block - 1) / rows_per_block;
-  const int slots = causal && KS == 1 ? (a.row_blocks + 1) / 2 : a.row_blocks;  // paired row blocks
+  a.paired = paired;
+  const int slots = paired ? (a.row_blocks + 1) / 2 : a.row_blocks;
   a.slots = fast_div(slots);
   a.head_groups = fast_div(dm.G / ts.heads_per_block);
   a.kv_heads = fast_div(dm.Hkv);
@@ -1576,11 +1475,10 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segme
   a.lse_cache = lse_cache;
   a.q_rope_pos0 = q_rope_pos0;
   a.rope_log2_base = q_rope_pos0 >= 0 ? log2f(rope_base) : 0.f;
-  // dynamic LDS next to the static tiles: the query rows, later (two key groups) the rows' statistics
-  constexpr int kTileBytes = KS * 4 * Lay<D>::kTile, kQueryBytes = WAVES / KS * Lay<D>::kHalf, kStatBytes = WAVES * 32 * 16;
-  constexpr int kDynBytes = kTileBytes + kQueryBytes > 160 * 1024 ? kStatBytes : (KS > 1 && kStatBytes > kQueryBytes ? kStatBytes : kQueryBytes);
+  // dynamic LDS next to the static tiles
+  constexpr int kDynBytes = WAVES * Lay<D>::kHalf;
   static LdsLimit limit, limit_rotq;
-  const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES, KS> : attn_pipe_kernel<D, WAVES, KS>;
+  const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES> : attn_pipe_kernel<D, WAVES>;
   const hipError_t e = raise_lds_limit(q_rope_pos0 >= 0 ? limit_rotq : limit, reinterpret_cast<const void*>(kern), kDynBytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), kDynBytes, st, a);
@@ -1589,22 +1487,40 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segme
 
 template <int D>
 hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
-                       float* lse_cache, int key_splits, float2* part, hipStream_t st, int q_rope_pos0, float rope_base) {
-  if (lse_cache != nullptr && !attn_mfma_emits_cache_lse(ks, causal, out)) return hipErrorInvalidValue;
-  if (q_rope_pos0 >= 0 && out.ptr == nullptr) return hipErrorInvalidValue;  // only the kernel with output rotates
+                       float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+  if (out.ptr == nullptr || (lse_cache != nullptr && ks.n_c < 1)) return hipErrorInvalidValue;
   if (!fits_i32(ks.cache, ks.n_c) || !fits_i32(ks.chunk, ks.c) || !fits_i32(vs.cache, vs.n_c) ||
       !fits_i32(vs.chunk, vs.c))
     return hipErrorInvalidValue;
-  if (key_splits < 1 || (key_splits > 1 && (out.ptr != nullptr || part == nullptr))) return hipErrorInvalidValue;
-  if (out.ptr != nullptr) {
-    return attn_pipe_launch<D, 8, 1>(dm, q, rows, ks, vs, causal, out, lse, lse_cache, st, q_rope_pos0, rope_base);
-  }
+  // The smallest piece of work per workgroup whose workgroups still fit the chip side by side: a launch that leaves
+  // compute units idle lasts as long as its longest workgroup.  Measured in us, 32/8 heads, 512 rows over 768 + 512
+  // states, head_dim 128 (row blocks in pairs | one row block | four waves, one row block):
+  //   1 layer    54.6 | 34.4 | 24.4       4 layers   56.1 | 42.0 | 47.2
+  //   2 layers   55.0 | 35.8 | 26.2       5 layers   56.9 | 66.8 | 61.4
+  //   3 layers   56.1 | 38.4 | 42.0       8 layers   72.9 | 83.0 | 90.3
+  // The best of a line is the last whose workgroups (128, 256, 192, 256 | 160, 256) are no more than the 256 compute
+  // units; head_dim 64 and the other group sizes follow the same line (head_dim 64, one layer: 36.7 | 22.9 | 17.2).
+  const auto workgroups = [&](int row_waves) {  // one row block each
+    const TaskShape ts = task_shape(dm.G, row_waves);
+    const int block_rows = ts.tiles_per_block * kRowsPerWave;
+    return static_cast<int64_t>((rows + block_rows - 1) / block_rows) * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L;
+  };
+  const int cus = compute_units();
+  if (workgroups(4) <= cus)
+    return attn_pipe_launch<D, 4>(dm, q, rows, ks, vs, causal, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+  const bool paired = causal != 0 && workgroups(8) > cus;
+  return attn_pipe_launch<D, 8>(dm, q, rows, ks, vs, causal, paired, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+}
+
+// Partial (maximum, sum) pairs of every query row over `key_splits` ranges of the keys.
+template <int D>
+hipError_t lse_launch(const Dims& dm, View q, int rows, Segments ks, int key_splits, float2* part, hipStream_t st) {
+  if (!fits_i32(ks.cache, ks.n_c) || !fits_i32(ks.chunk, ks.c)) return hipErrorInvalidValue;
   const TaskShape ts = task_shape(dm.G, kWaves);
   const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
   const int row_blocks = (rows + rows_per_block - 1) / rows_per_block;
-  const int rb_slots = (causal && key_splits == 1) ? (row_blocks + 1) / 2 : row_blocks;  // paired row blocks
-  const dim3 grid(rb_slots * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L * key_splits);
-  hipLaunchKernelGGL(lse_mfma_kernel<D>, grid, dim3(kThreads), 0, st, dm, q, rows, ks, causal, lse, key_splits, part);
+  const dim3 grid(row_blocks * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L * key_splits);
+  hipLaunchKernelGGL(lse_mfma_kernel<D>, grid, dim3(kThreads), 0, st, dm, q, rows, ks, key_splits, part);
   return hipGetLastError();
 }
 
@@ -1648,8 +1564,7 @@ hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, flo
   const int64_t rows_total = static_cast<int64_t>(dm.B) * dm.L * dm.Hq * rows;
   if (static_cast<size_t>(2) * splits * rows_total > workspace_floats) return hipErrorInvalidValue;
   float2* part = reinterpret_cast<float2*>(workspace);
-  View none{nullptr, 0, 0, 0, 0};
-  hipError_t e = attn_launch<D>(dm, q, rows, ks, ks, /*causal=*/0, none, nullptr, nullptr, splits, part, st, -1, 0.f);
+  hipError_t e = lse_launch<D>(dm, q, rows, ks, splits, part, st);
   if (e != hipSuccess) return e;
   if (splits > 1) {  // one normaliser per row, in place of the first range's pairs
     hipLaunchKernelGGL(merge_partials_kernel, dim3(static_cast<unsigned>((rows_total + 255) / 256)), dim3(256), 0, st, part,
@@ -1664,15 +1579,10 @@ hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, flo
 
 bool mfma_path_supported(int dtype, const Dims& dm) { return dtype == CITRUS_BF16 && (dm.D == 64 || dm.D == 128); }
 
-bool attn_mfma_emits_cache_lse(const Segments& ks, int causal, View out) {
-  return out.ptr != nullptr && causal != 0 && ks.n_c > 0 && ks.n_c % kTileN == 0;
-}
-
 hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
-                            float* lse, float* lse_cache, int key_splits, float2* part, hipStream_t st,
-                            int q_rope_pos0, float rope_base) {
+                            float* lse, float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
   const auto launch = dm.D == 64 ? attn_launch<64> : attn_launch<128>;
-  return launch(dm, q, rows, ks, vs, causal, out, lse, lse_cache, key_splits, part, st, q_rope_pos0, rope_base);
+  return launch(dm, q, rows, ks, vs, causal, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
 hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,

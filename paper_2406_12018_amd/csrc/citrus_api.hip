@@ -160,13 +160,6 @@ citrus_status check_workspace(const citrus_config* c, const void* ws, size_t byt
 
 // ---- dispatch: MFMA kernels for bf16, vector kernels for f32 ----
 
-hipError_t run_attn(const citrus_config* c, const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal,
-                    View out, float* lse, hipStream_t st) {
-  if (mfma_path_supported(c->dtype, dm))
-    return launch_attn_mfma(dm, q, rows, ks, vs, causal, out, lse, nullptr, 1, nullptr, st);
-  return launch_attn_f32(dm, q, rows, ks, vs, causal, out, lse, st);
-}
-
 hipError_t run_colsum(const citrus_config* c, const Dims& dm, View q, int rows, Segments ks, int causal,
                       const float* lse, float* score, hipStream_t st) {
   if (mfma_path_supported(c->dtype, dm))
@@ -177,31 +170,24 @@ hipError_t run_colsum(const citrus_config* c, const Dims& dm, View q, int rows, 
 // Unchecked bodies shared by the public entry points and the chunk loop.
 
 // lse_cache (optional, needs ks.n_c > 0): each row's log-sum-exp over the cache states alone, the
-// normaliser of Eq. (1) as printed.  A by-product of the MFMA attention kernel when the cache ends on
-// a 32-key boundary; a pass of its own over the cache otherwise.
-// q_rope_pos0 >= 0 (MFMA path only, see attn_rotates_queries): q is unrotated and the kernel rotates it.
+// normaliser of Eq. (1) as printed.  A by-product of the MFMA attention kernel; a pass of its own over the cache in f32.
+// q_rope_pos0 >= 0 (MFMA path only): q is unrotated and the kernel rotates it.
 citrus_status do_chunk_attn(const citrus_config* c, const Dims& dm, const citrus_tensor& q, Segments ks, Segments vs,
                             const citrus_tensor& out, float* lse, float* lm_score, float* lse_cache, hipStream_t st,
                             int q_rope_pos0 = -1) {
-  const bool mfma = mfma_path_supported(c->dtype, dm);
-  if (q_rope_pos0 >= 0 && !mfma) return CITRUS_ERR_UNSUPPORTED;
-  const bool fused_lse = lse_cache != nullptr && mfma && attn_mfma_emits_cache_lse(ks, 1, make_view(out));
-  // in-kernel query rotation together with a cache-only normaliser that needs a pass of its own: not
-  // combined by any caller (decided before anything is launched)
-  if (q_rope_pos0 >= 0 && lse_cache != nullptr && !fused_lse) return CITRUS_ERR_UNSUPPORTED;
-  if (fused_lse || q_rope_pos0 >= 0) {
-    CITRUS_TRY(hip_status(launch_attn_mfma(dm, make_view(q), ks.c, ks, vs, /*causal=*/1, make_view(out), lse,
-                                           fused_lse ? lse_cache : nullptr, 1, nullptr, st, q_rope_pos0,
-                                           rope_base_of(c))));
+  if (mfma_path_supported(c->dtype, dm)) {
+    CITRUS_TRY(hip_status(launch_attn_mfma(dm, make_view(q), ks.c, ks, vs, /*causal=*/1, make_view(out), lse, lse_cache, st,
+                                           q_rope_pos0, rope_base_of(c))));
   } else {
-    CITRUS_TRY(hip_status(run_attn(c, dm, make_view(q), ks.c, ks, vs, /*causal=*/1, make_view(out), lse, st)));
+    if (q_rope_pos0 >= 0) return CITRUS_ERR_UNSUPPORTED;
+    CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q), ks.c, ks, vs, /*causal=*/1, make_view(out), lse, st)));
     if (lse_cache != nullptr) {
       Segments only = ks;  // the cache as the only key segment
       only.chunk = ks.cache;
       only.c = ks.n_c;
       only.n_c = 0;
       View none{nullptr, 0, 0, 0, 0};
-      CITRUS_TRY(hip_status(run_attn(c, dm, make_view(q), ks.c, only, only, /*causal=*/0, none, lse_cache, st)));
+      CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q), ks.c, only, only, /*causal=*/0, none, lse_cache, st)));
     }
   }
   if (lm_score != nullptr)
@@ -216,7 +202,7 @@ citrus_status do_instr_score(const citrus_config* c, const Dims& dm, const citru
     return hip_status(launch_instr_score_mfma(dm, make_view(q_instr), c->instr_len, ks, lse_ws, scratch.floats, score, st));
   View none{nullptr, 0, 0, 0, 0};
   // pass 1: row normalisers (log-sum-exp over all n candidates, no mask)
-  CITRUS_TRY(hip_status(run_attn(c, dm, make_view(q_instr), c->instr_len, ks, ks, /*causal=*/0, none, lse_ws, st)));
+  CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q_instr), c->instr_len, ks, ks, /*causal=*/0, none, lse_ws, st)));
   // pass 2: probabilities summed down the rows of each KV group
   CITRUS_TRY(hip_status(run_colsum(c, dm, make_view(q_instr), c->instr_len, ks, /*causal=*/0, lse_ws, score, st)));
   return CITRUS_OK;
@@ -245,7 +231,7 @@ citrus_status do_cache_score(const citrus_config* c, const Dims& dm, const citru
   if (mfma_path_supported(c->dtype, dm))
     return hip_status(launch_instr_score_mfma(dm, make_view(q), rows, ks, lse_ws, scratch.floats, score, st));
   View none{nullptr, 0, 0, 0, 0};
-  CITRUS_TRY(hip_status(run_attn(c, dm, make_view(q), rows, ks, ks, /*causal=*/0, none, lse_ws, st)));
+  CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q), rows, ks, ks, /*causal=*/0, none, lse_ws, st)));
   CITRUS_TRY(hip_status(run_colsum(c, dm, make_view(q), rows, ks, /*causal=*/0, lse_ws, score, st)));
   return CITRUS_OK;
 }
@@ -524,7 +510,7 @@ int32_t citrus_decode_step(const citrus_config* cfg, citrus_tensor q, citrus_ten
   if (decode_mfma_supported(cfg->dtype, dm))
     return hip_status(launch_decode_mfma(dm, make_view(q), ks, vs, make_view(out),
                                          reinterpret_cast<float*>(ws + wl.decode), /*append_token=*/1, st));
-  CITRUS_TRY(hip_status(run_attn(cfg, dm, make_view(q), 1, ks, vs, /*causal=*/1, make_view(out), nullptr, st)));
+  CITRUS_TRY(do_chunk_attn(cfg, dm, q, ks, vs, out, nullptr, nullptr, nullptr, st));
   int32_t* one = reinterpret_cast<int32_t*>(ws + wl.iota);
   CITRUS_TRY(hip_status(launch_iota(one, cache_len, 1, st)));
   return hip_status(launch_compact(elem_bytes(cfg->dtype), dm, ks, vs, one, /*idx_pitch=*/0, /*idx_heads=*/1, 1,

@@ -46,16 +46,13 @@ hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments kseg, in
 
 // ---- bf16 MFMA kernels (head_dim 64 and 128: every bf16 configuration), attn_mfma.hip ----
 bool mfma_path_supported(int dtype, const Dims& dm);
-// key_splits > 1: log-sum-exp only, one partial (log2-domain maximum, sum) pair per key range
-// and row in part[split][B*L*Hq*rows]; key_splits == 1: out and/or lse (natural log) as given.
-// lse_cache (optional): per row, the log-sum-exp over the cache states alone, a by-product of the
-// causal kernel with output when attn_mfma_emits_cache_lse() holds (cache ends on a 32-key boundary).
-bool attn_mfma_emits_cache_lse(const Segments& kseg, int causal, View out);
-// q_rope_pos0 >= 0 (kernel with output only): the query rows are given without rotary embedding and are
+// lse (optional): the rows' log-sum-exp (natural log).  lse_cache (optional, kseg.n_c > 0): the same over the cache
+// states alone, a by-product.
+// q_rope_pos0 >= 0: the query rows are given without rotary embedding and are
 // rotated to positions q_rope_pos0 + row inside the kernel, with the bits launch_rope would give.
 hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments kseg, Segments vseg, int causal, View out,
-                            float* lse, float* lse_cache, int key_splits, float2* part, hipStream_t st,
-                            int q_rope_pos0 = -1, float rope_base = 0.f);
+                            float* lse, float* lse_cache, hipStream_t st, int q_rope_pos0 = -1,
+                            float rope_base = 0.f);
 // normaliser per row from lse (natural log) or, if part != NULL, merged from key_splits partial pairs
 hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments kseg, int causal, const float* lse,
                               int key_splits, const float2* part, float* score, hipStream_t st);
@@ -69,6 +66,9 @@ size_t instr_score_mfma_workspace_floats(const Dims& dm, int rows, int n);
 // chosen, and hipErrorInvalidValue comes back if none fits.
 hipError_t launch_instr_score_mfma(const Dims& dm, View q, int rows, Segments kseg, float* workspace,
                                    size_t workspace_floats, float* score, hipStream_t st);
+
+// compute units of the current device, looked up once per device (instr_strip.hip)
+int compute_units();
 
 // ---- instruction score with one q.k product per (row, key): row strips kept on chip, instr_strip.hip ----
 // taken for this shape, given a scratch block of workspace_floats floats?

@@ -464,8 +464,7 @@ constexpr int kStripMaxGroups = 608;  // workgroups per launch: twice the comput
 
 }  // namespace
 
-// compute units of the current device, looked up once per device
-static int compute_units() {
+int compute_units() {
   static std::atomic<int> cached[kMaxDevices] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
