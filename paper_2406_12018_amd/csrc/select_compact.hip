@@ -7,6 +7,7 @@ namespace {
 
 constexpr int kSelThreads = 256;
 constexpr int kSelWaves = kSelThreads / 64;
+constexpr int kWideThreads = 1024;
 
 // Order-preserving map float -> uint32 (larger float <=> larger key).  -0 is
 // folded onto +0 first so that equal values get equal keys.
@@ -125,21 +126,36 @@ __global__ __launch_bounds__(kSelThreads) void topk_kernel(const float* score, i
   }
 }
 
+// Inclusive prefix sum over the 64 lanes with data-parallel-primitive moves: six dependent vector adds, where
+// __shfl_up would make six round trips through the LDS unit.
+__device__ __forceinline__ int wave_prefix_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1: lanes without a source add 0
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // The same selection for a unit whose keys fit the workgroup's registers (n <= ITEMS * THREADS): the scores
-// are read once (candidate i * THREADS + tid is item i of thread tid), the four radix passes run on the
-// registers with three barriers each (two histograms take turns, so clearing one needs no barrier of its own;
-// the first 256 threads own the bins), and the ordered emission takes two barriers in all: per row of THREADS
-// candidates and wave, the number of threshold-equal and then of kept candidates goes to LDS, and a
-// candidate's rank is the sum of the counts in front of it.  Exactly the result of topk_kernel.
-template <int ITEMS, int THREADS>
+// are read once (candidate i * THREADS + tid is item i of thread tid), the radix passes run on the registers, and
+// the ordered emission counts the kept candidates per row of THREADS candidates and wave in LDS; a candidate's
+// position is the sum of the counts in front of it.  Exactly the result of topk_kernel.
+//
+// What bounds it: a chain of dependent steps (a launch that writes the identity takes 3.2 us), so the chain is kept
+// short.  Every pass has a histogram of its own, cleared at the start, and every wave reads the whole histogram and
+// finds the bin by itself: one barrier per pass.  A pass whose bin is kept as a whole is the last one (scores
+// that differ need two or three of the four), and threshold-equal candidates are ranked only where some of them
+// are left out.
+// Measured against four passes of three barriers with a shuffled scan, kernel trace: 8 units of 1280 candidates 6.9 ->
+// 5.1 us, 128 units 8.1 -> 5.8 us.
+template <int ITEMS, int THREADS, bool SUM_HEADS>
 __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_sum, int n, int k, int forced,
                                                int32_t* idx) {
-  constexpr int WAVES = THREADS / 64, kBins = 256, kBinWaves = kBins / 64;
-  static_assert(THREADS >= kBins && ITEMS <= 32, "thread t < 256 owns bin t; one bit per item");
-  __shared__ int hist[2][kBins];
-  __shared__ uint32_t s_prefix;
-  __shared__ int s_need;
-  __shared__ int wave_tot[kBinWaves];
+  constexpr int WAVES = THREADS / 64, kBins = 256, kPasses = 4;
+  static_assert(THREADS >= kBins && ITEMS <= 32, "thread t < 256 clears bin t; one bit per item");
+  __shared__ __attribute__((aligned(16))) int hist[kPasses][kBins];
   __shared__ int row_cnt[2][ITEMS][WAVES];
   const int unit = blockIdx.x, tid = threadIdx.x, lane = tid % 64, w = tid / 64;
   const float* base = score + static_cast<int64_t>(unit) * heads_to_sum * n;
@@ -150,53 +166,70 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
     return;
   }
 
-  uint32_t key[ITEMS];
+  if (tid < kBins) {
 #pragma unroll
-  for (int i = 0; i < ITEMS; ++i) {
-    const int j = i * THREADS + tid;
-    key[i] = j < n ? unit_key(base, heads_to_sum, n, forced, j) : 0u;
+    for (int pass = 0; pass < kPasses; ++pass) hist[pass][tid] = 0;
   }
-  if (tid < kBins) hist[0][tid] = 0;
+  uint32_t key[ITEMS];
+  if constexpr (SUM_HEADS) {
+    // Layer-wise selection: the sums grow head by head (the order of unit_score) for all of a thread's candidates at a
+    // time, with about 32 loads in flight; one candidate after the other, each head's load was waited for on its own.
+    float sum[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) sum[i] = base[min(i * THREADS + tid, n - 1)];
+#pragma unroll(ITEMS <= 2 ? 16 : 4)
+    for (int g = 1; g < heads_to_sum; ++g) {
+      const float* head = base + static_cast<int64_t>(g) * n;
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) sum[i] += head[min(i * THREADS + tid, n - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) key[i] = i * THREADS + tid < forced ? 0xffffffffu : order_key(sum[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const int j = i * THREADS + tid;
+      key[i] = j < n ? unit_key(base, 1, n, forced, j) : 0u;
+    }
+  }
   __syncthreads();
 
   uint32_t prefix = 0;  // bits of T fixed so far (high bits)
   int need = k;         // rank of T among the keys that match the prefix
+  bool whole = false;   // every key that matches the prefix is kept
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
+  for (int pass = 0; pass < kPasses; ++pass) {
+    if (whole) break;  // block-uniform
     const int shift = 24 - 8 * pass;
-    int* h = hist[pass & 1];
-    if (tid < kBins) hist[(pass + 1) & 1][tid] = 0;  // the next pass's histogram; its last readers passed two barriers ago
     const uint32_t hi_mask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
-      if (i * THREADS + tid < n && (key[i] & hi_mask) == prefix) atomicAdd(&h[(key[i] >> shift) & 0xff], 1);
+      if (i * THREADS + tid < n && (key[i] & hi_mask) == prefix) atomicAdd(&hist[pass][(key[i] >> shift) & 0xff], 1);
     __syncthreads();
-    // thread t < 256 owns bin t: keys in higher bins = suffix sum (wave shuffles + one LDS hop)
-    int own = 0, incl = 0;
-    if (w < kBinWaves) {  // wave-uniform
-      own = h[tid];
-      incl = own;
+    // lane x holds the four bins from 4 (63 - x) up: the sum over the lanes in front counts the keys in higher bins
+    const int4 own = *reinterpret_cast<const int4*>(&hist[pass][4 * (63 - lane)]);
+    const int sum = own.x + own.y + own.z + own.w;
+    const int incl = wave_prefix_sum(sum);
+    const uint64_t hit = __ballot(incl - sum < need && need <= incl);  // exactly one lane: 1 <= need <= all keys
+    const int at = __builtin_ctzll(hit);
+    need -= __builtin_amdgcn_readlane(incl - sum, at);
+    int bin = 4 * (63 - at) + 3;
+    int in_bin = __builtin_amdgcn_readlane(own.w, at);
+    const int lower[3] = {own.z, own.y, own.x};
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_down(incl, o, 64);
-        if (lane + o < 64) incl += v;
+    for (int x = 0; x < 3; ++x)
+      if (need > in_bin) {
+        need -= in_bin;
+        --bin;
+        in_bin = __builtin_amdgcn_readlane(lower[x], at);
       }
-      if (lane == 0) wave_tot[w] = incl;
-    }
-    __syncthreads();
-    if (w < kBinWaves) {
-      int above = incl - own;
-      for (int x = w + 1; x < kBinWaves; ++x) above += wave_tot[x];
-      if (above < need && need <= above + own) {  // exactly one bin
-        s_prefix = prefix | (static_cast<uint32_t>(tid) << shift);
-        s_need = need - above;
-      }
-    }
-    __syncthreads();
-    prefix = s_prefix;
-    need = s_need;
+    prefix |= static_cast<uint32_t>(bin) << shift;
+    whole = need == in_bin;
   }
-  const uint32_t thr = prefix;  // key of the k-th best candidate; `need` of the candidates with that key are kept
+  // Keys above `thr` are kept; of the keys equal to it the first `need`.  Where the last bin is kept as a whole, thr
+  // lies just below it (prefix > 0: all n > k keys match prefix 0 and lie in bins from 0 up).
+  const uint32_t thr = whole ? prefix - 1u : prefix;
+  if (whole) need = 0;
 
   // set bits of a ballot below this lane (v_mbcnt: no per-lane mask to keep in registers)
   auto lanes_below = [](uint64_t ballot) {
@@ -207,34 +240,41 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
   uint32_t rank_in_row[(ITEMS + 3) / 4] = {};
   auto set_rank = [&](int i, int r) { rank_in_row[i / 4] = (rank_in_row[i / 4] & ~(0xffu << (8 * (i % 4)))) | (static_cast<uint32_t>(r) << (8 * (i % 4))); };
   auto get_rank = [&](int i) { return static_cast<int>((rank_in_row[i / 4] >> (8 * (i % 4))) & 0xffu); };
+  uint32_t keep_bits = 0;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (i * THREADS + tid < n && key[i] > thr) keep_bits |= 1u << i;
+  if (need > 0) {  // block-uniform: some, not all, of the threshold-equal candidates
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      if (i * THREADS >= n) break;  // block-uniform
+      const bool eq = i * THREADS + tid < n && key[i] == thr;
+      const uint64_t ballot = __ballot(eq);
+      set_rank(i, lanes_below(ballot));
+      if (lane == 0) row_cnt[0][i][w] = __popcll(ballot);
+    }
+    __syncthreads();
+    int eq_before = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      if (i * THREADS >= n) break;
+      int eq_rank = eq_before + get_rank(i);
+#pragma unroll
+      for (int x = 0; x < WAVES; ++x) {
+        const int c = row_cnt[0][i][x];
+        if (x < w) eq_rank += c;
+        eq_before += c;
+      }
+      if (i * THREADS + tid < n && key[i] == thr && eq_rank < need) keep_bits |= 1u << i;
+      __builtin_amdgcn_sched_barrier(0);  // one row's counts in registers at a time (see the register budget below)
+    }
+  }
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
     if (i * THREADS >= n) break;  // block-uniform
-    const bool eq = i * THREADS + tid < n && key[i] == thr;
-    const uint64_t ballot = __ballot(eq);
-    set_rank(i, lanes_below(ballot));
-    if (lane == 0) row_cnt[0][i][w] = __popcll(ballot);
-  }
-  __syncthreads();
-  uint32_t keep_bits = 0;
-  int eq_before = 0;
-#pragma unroll
-  for (int i = 0; i < ITEMS; ++i) {
-    if (i * THREADS >= n) break;
-    int eq_rank = eq_before + get_rank(i);
-#pragma unroll
-    for (int x = 0; x < WAVES; ++x) {
-      const int c = row_cnt[0][i][x];
-      if (x < w) eq_rank += c;
-      eq_before += c;
-    }
-    const bool in = i * THREADS + tid < n;
-    const bool keep = in && (key[i] > thr || (key[i] == thr && eq_rank < need));
-    const uint64_t ballot = __ballot(keep);
+    const uint64_t ballot = __ballot((keep_bits >> i) & 1u);
     set_rank(i, lanes_below(ballot));
     if (lane == 0) row_cnt[1][i][w] = __popcll(ballot);
-    keep_bits |= keep ? (1u << i) : 0u;
-    __builtin_amdgcn_sched_barrier(0);  // one row's counts in registers at a time (see the register budget below)
   }
   __syncthreads();
   int kept_before = 0;
@@ -253,21 +293,13 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
   }
 }
 
-// Six keys per thread (up to 1536 candidates: the Mistral-7B shape's 1280) fit 32 registers with one wave per
-// SIMD: next to two waves of the chunk-attention kernel (240 registers each) a SIMD has 32 left, and with them
-// these workgroups run beside an attention launch (the second-stream form of the chunk loop) instead of waiting
-// for a compute unit of their own.  Eight keys need 34.
-__global__ __launch_bounds__(kSelThreads) void topk_regs6_kernel(const float* score, int heads_to_sum, int n, int k,
-                                                                int forced, int32_t* idx) {
-  topk_regs_body<6, kSelThreads>(score, heads_to_sum, n, k, forced, idx);
-}
-__global__ __launch_bounds__(kSelThreads) void topk_regs8_kernel(const float* score, int heads_to_sum, int n, int k,
-                                                                int forced, int32_t* idx) {
-  topk_regs_body<8, kSelThreads>(score, heads_to_sum, n, k, forced, idx);
-}
-__global__ __launch_bounds__(kSelThreads) void topk_regs24_kernel(const float* score, int heads_to_sum, int n, int k,
-                                                                 int forced, int32_t* idx) {
-  topk_regs_body<24, kSelThreads>(score, heads_to_sum, n, k, forced, idx);
+// Eight keys per thread (up to 2048 candidates) fit 32 registers with one wave per SIMD: next to two waves of the
+// chunk-attention kernel (240 registers each) a SIMD has 32 left, and with them these workgroups run beside an
+// attention launch (the second-stream form of the chunk loop) instead of waiting for a compute unit of their own.
+template <int ITEMS, int THREADS, bool SUM_HEADS>
+__global__ __launch_bounds__(THREADS) void topk_regs_kernel(const float* score, int heads_to_sum, int n, int k, int forced,
+                                                           int32_t* idx) {
+  topk_regs_body<ITEMS, THREADS, SUM_HEADS>(score, heads_to_sum, n, k, forced, idx);
 }
 
 __global__ void iota_kernel(int32_t* p, int base, int count) {
@@ -350,14 +382,24 @@ hipError_t compact_launch(int elem_bytes, const Dims& dm, Segments ks, Segments 
 hipError_t launch_topk(const float* score, int units, int heads_to_sum, int n, int k, int forced, int32_t* idx,
                        hipStream_t st) {
   forced = min(forced, k);
-  if (n <= 6 * kSelThreads)
-    hipLaunchKernelGGL(topk_regs6_kernel, dim3(units), dim3(kSelThreads), 0, st, score, heads_to_sum, n, k, forced, idx);
-  else if (n <= 8 * kSelThreads)
-    hipLaunchKernelGGL(topk_regs8_kernel, dim3(units), dim3(kSelThreads), 0, st, score, heads_to_sum, n, k, forced, idx);
-  else if (n <= 24 * kSelThreads)
-    hipLaunchKernelGGL(topk_regs24_kernel, dim3(units), dim3(kSelThreads), 0, st, score, heads_to_sum, n, k, forced, idx);
-  else
-    hipLaunchKernelGGL(topk_kernel, dim3(units), dim3(kSelThreads), 0, st, score, heads_to_sum, n, k, forced, idx);
+  // Four times the threads where a unit's chain is long and the units fit the chip side by side (32 units of 6144
+  // candidates: 17.9 us with 256 threads, 10.6 with 1024; with more units the chip is full either way), and for the sums
+  // over a layer's heads, a read of heads_to_sum * n floats through one compute unit that needs its loads in flight
+  // (16 units of 32 heads x 2048 candidates: 70 us candidate by candidate, 62 head by head, 12.7 with 1024 threads).
+  const bool sum_heads = heads_to_sum > 1;
+  auto kern = topk_kernel;
+  int threads = kSelThreads;
+  if (n <= 2 * kWideThreads) {
+    kern = sum_heads ? topk_regs_kernel<2, kWideThreads, true> : topk_regs_kernel<8, kSelThreads, false>;
+    threads = sum_heads ? kWideThreads : kSelThreads;
+  } else if (n <= 6 * kWideThreads) {
+    const bool wide = units <= compute_units();
+    kern = sum_heads ? topk_regs_kernel<6, kWideThreads, true>
+           : wide    ? topk_regs_kernel<6, kWideThreads, false>
+                     : topk_regs_kernel<24, kSelThreads, false>;
+    threads = sum_heads || wide ? kWideThreads : kSelThreads;
+  }
+  hipLaunchKernelGGL(kern, dim3(units), dim3(threads), 0, st, score, heads_to_sum, n, k, forced, idx);
   return hipGetLastError();
 }
 
