@@ -191,8 +191,10 @@ int32_t citrus_abi_version(void);
  *             of the attention probability p[h,t,j] (0 where masked); Eq. (1)
  *             with s = the chunk, as a sum (divide by chunk_len*G for the mean).
  *             Needs lse: if lse is NULL the workspace is used for it.
- * Compute: bf16 inputs, f32 accumulation, probabilities rounded to bf16 before
- * the P.V product, bf16 output; f32 mode computes in f32 throughout.
+ * Compute: bf16 inputs, f32 accumulation, bf16 output; head_dim 128: probabilities
+ * rounded to bf16 before the P.V product and in the row sums; head_dim 64: f32 row
+ * sums, probabilities as two bf16 parts (17 bits) in the product; f32 mode computes
+ * in f32 throughout.
  */
 int32_t citrus_chunk_attn(const citrus_config* cfg, citrus_tensor q, citrus_tensor k_cache, citrus_tensor v_cache,
                           int32_t cache_len, citrus_tensor k_chunk, citrus_tensor v_chunk, int32_t chunk_len,

@@ -1,7 +1,7 @@
 // bf16 MFMA kernels for head_dim 64 and 128 on gfx950 (CDNA4): templates over the head dimension.
 // (head_dim 64 ran on one-wavefront-per-row vector kernels before, whose serial chain of key loads and f32
 // multiply-adds reached 7 TFLOP/s: 8 layers of 32/8 heads, a document of 4096 tokens in chunks of 512, budget 768,
-// took 37.8 ms; on these kernels 0.88 ms.)
+// took 37.8 ms; on these kernels 0.93 ms, 0.81 with probabilities rounded to bf16.)
 //
 //  attn_pipe_kernel    flash-style chunk attention (Section 4.1 step 1; softmax
 //                      with the 1/sqrt(d_k) scaling of Eq. (1)): online softmax
@@ -24,6 +24,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "bf16_math.h"
 #include "citrus_internal.h"
 #include "rope_math.h"
 
@@ -34,7 +35,6 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short i16x4;
 
 constexpr int kWaves = 4;               // one wave per SIMD and block; two or more blocks share a CU
@@ -59,6 +59,10 @@ struct Geo {
   static constexpr int kRowsPerLoad = 1024 / kRowBytes;  // rows one wave-level LDS-direct load moves
   static constexpr int kKk = D / 16;                     // contraction steps of K.Q^T
   static constexpr int kOut = D / 32;                    // 32-row tiles of O^T
+  // bf16 parts of a probability in P.V.  One (the probability rounded to bf16) at 128.  Two at 64, where the results keep
+  // the accuracy of f32 probabilities: what is left of their error is the rounding of the output (relative error
+  // against f64 over 512 rows x 1280 states 0.00166, of the rounded f64 result 0.00166, with one part 0.00234).
+  static constexpr int kParts = D == 64 ? 2 : 1;
   static constexpr int kPitchK = D + 8;                  // padded row pitch (bf16) of query rows staged by ordinary writes
   __device__ static constexpr int swz(int row) {
     return D == 128 ? (2 * (row % 8)) ^ ((row / 8) % 2) : (2 * ((row / 2) % 4)) ^ ((row / 8) % 2) ^ (4 * (row % 2));
@@ -74,12 +78,6 @@ union Pack8 {
   uint32_t w[4];
   i16x4 h[2];
 };
-
-__device__ inline uint32_t pack_bf16x2(float lo, float hi) {
-  f32x2 f = {lo, hi};
-  bf16x2 b = __builtin_convertvector(f, bf16x2);  // round to nearest even
-  return __builtin_bit_cast(uint32_t, b);
-}
 
 __device__ inline const uint16_t* unit_ptr(const View& v, int b, int l, int h) {
   return static_cast<const uint16_t*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh);
@@ -621,12 +619,14 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     for (int i = 0; i < 16; ++i) o_acc[r][i] = 0.f;
 
   f32x16 s_cur;            // logits of the half tile whose probabilities are computed next
-  uint32_t p_prev[8];      // bf16 probabilities of the half tile before it, not yet multiplied with V
+  uint32_t p_prev[T::kParts][8];  // bf16 probabilities (parts) of the half tile before it, not yet multiplied with V
   Pack8 ka[T::kKk];        // K operand of the next logit product, read one step ahead
   float mx_cur;            // this lane's maximum over s_cur (before masking)
   uint64_t high;           // lanes whose maximum over s_cur (before masking) lies above m_high
 #pragma unroll
-  for (int x = 0; x < 8; ++x) p_prev[x] = 0u;
+  for (int y = 0; y < T::kParts; ++y)
+#pragma unroll
+    for (int x = 0; x < 8; ++x) p_prev[y][x] = 0u;
   // K operand from a half tile; what is read past the last tile feeds logits that are never used
   auto read_k_ops = [&](const char* k_t) {
 #pragma unroll
@@ -667,8 +667,15 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       // the probabilities still waiting for their product with V were taken against the old maximum
 #pragma unroll
       for (int x = 0; x < 8; ++x) {
-        const float lo = __uint_as_float(p_prev[x] << 16), hi = __uint_as_float(p_prev[x] & 0xffff0000u);
-        p_prev[x] = pack_bf16x2(lo * alpha, hi * alpha);
+        const uint32_t pw = p_prev[0][x];
+        const float lo = __uint_as_float(pw << 16), hi = __uint_as_float(pw & 0xffff0000u);
+        if constexpr (T::kParts == 2) {
+          const uint32_t rw = p_prev[1][x];
+          split_bf16x2((lo + __uint_as_float(rw << 16)) * alpha, (hi + __uint_as_float(rw & 0xffff0000u)) * alpha,
+                       p_prev[0][x], p_prev[1][x]);
+        } else {
+          p_prev[0][x] = pack_bf16x2(lo * alpha, hi * alpha);
+        }
       }
       m_run = m_new;
       m_sub = m_new == -INFINITY ? 0.f : m_new;
@@ -692,15 +699,15 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     };
     read_v_ops(0);
     __builtin_amdgcn_s_waitcnt(0xC07F | ((2 * T::kOut) << 8));  // the K operands are here: one wait for all of them
-    // kKk MFMAs of S^T, then 2 kOut of O^T: sixteen (head_dim 64: eight).  The exponential of logit x of half
-    // tile i is issued right before MFMA x + 1 (head_dim 64: those of logits 2 x and 2 x + 1).
+    // kKk MFMAs of S^T, then 2 kOut kParts of O^T: sixteen (head_dim 64: twelve).  The exponential of logit x of half
+    // tile i is issued right before MFMA x + 1 (head_dim 64: two each before the first kPairs of them).
     float p[16];
     float mx_nxt = 0.f;
     f32x16 s_nxt = mfma_pinned_first(ka[0].v, q_op[0]);
-    constexpr int kExp = 128 / D;  // exponentials per MFMA slot
+    constexpr int kPairs = D == 64 ? 5 : 0;
     auto exps_then_mfma = [&](int slot, f32x16& acc, const bf16x8& a, const bf16x8& bb) {
-      const int x = kExp * slot;
-      if constexpr (kExp == 2)
+      const int x = slot < kPairs ? 2 * slot : slot + kPairs;
+      if (slot < kPairs)
         exp2x2_then_mfma(fmaf(s_cur[x], c2, -m_sub), fmaf(s_cur[x + 1], c2, -m_sub), p[x], p[x + 1], acc, a, bb);
       else
         p[x] = exp2_then_mfma(fmaf(s_cur[x], c2, -m_sub), acc, a, bb);
@@ -716,57 +723,66 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     }
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      Pack8 pb;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[4 * half + x];
-      if (half == 0)
-        __builtin_amdgcn_s_waitcnt(0xC07F | ((2 * T::kOut) << 8));
-      else
-        __builtin_amdgcn_s_waitcnt(0xC07F);
+      for (int y = 0; y < T::kParts; ++y) {
+        Pack8 pb;
 #pragma unroll
-      for (int r = 0; r < T::kOut; ++r) {
-        const int slot = T::kOut * half + r;  // of the second product
-        exps_then_mfma(T::kKk - 1 + slot, o_acc[r], va[half][r].v, pb.v);
-        if (slot & 1) issue_v(slot / 2);
-        // The lane's maximum of the next half tile's logits, one v_max3 per MFMA slot.  s_nxt was
-        // completed by the last MFMA of the first product; three further MFMAs have been issued since.
-        if (D == 128) {
-          const int y = slot - 2;  // 0 .. 5
-          if (y == 0) mx_nxt = max3_pinned(s_nxt[0], s_nxt[1], s_nxt[2]);
-          if (y > 0) mx_nxt = max3_pinned(mx_nxt, s_nxt[2 * y + 1], s_nxt[2 * y + 2]);
+        for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[y][4 * half + x];
+        if (y == 0 && half == 0) __builtin_amdgcn_s_waitcnt(0xC07F | ((2 * T::kOut) << 8));
+        if (y == 0 && half == 1) __builtin_amdgcn_s_waitcnt(0xC07F);
+#pragma unroll
+        for (int r = 0; r < T::kOut; ++r) {
+          const int slot = T::kOut * (T::kParts * half + y) + r;  // of the second product: 0 .. 7
+          exps_then_mfma(T::kKk - 1 + slot, o_acc[r], va[half][r].v, pb.v);
+          if (slot & 1) issue_v(slot / 2);
+          // The lane's maximum of the next half tile's logits, one v_max3 per MFMA slot.  s_nxt was
+          // completed by the last MFMA of the first product; three further MFMAs have been issued since.
+          const int m3 = slot - 2;  // 0 .. 5
+          if (m3 == 0) mx_nxt = max3_pinned(s_nxt[0], s_nxt[1], s_nxt[2]);
+          if (m3 > 0) mx_nxt = max3_pinned(mx_nxt, s_nxt[2 * m3 + 1], s_nxt[2 * m3 + 2]);
         }
       }
     }
     before_tail();
-    if constexpr (kExp == 2) {
-      p[14] = exp2_pinned(fmaf(s_cur[14], c2, -m_sub));
-      mx_nxt = max3_pinned(s_nxt[0], s_nxt[1], s_nxt[2]);
-#pragma unroll
-      for (int y = 1; y < 6; ++y) mx_nxt = max3_pinned(mx_nxt, s_nxt[2 * y + 1], s_nxt[2 * y + 2]);
-    }
-    p[15] = exp2_pinned(fmaf(s_cur[15], c2, -m_sub));
+    if constexpr (kPairs == 0) p[15] = exp2_pinned(fmaf(s_cur[15], c2, -m_sub));
     mx_nxt = max3_pinned(mx_nxt, s_nxt[13], s_nxt[14]);
     mx_nxt = fmaxf(mx_nxt, s_nxt[15]);
     high = __ballot(mx_nxt > m_high);
-    // the row sum is taken over the bf16-rounded probabilities, the values P.V uses: one v_dot2
-    // with (1, 1) adds a pair
-    uint32_t p_cur[8];
-    float psum = 0.f;
+    uint32_t p_cur[T::kParts][8];
+    if constexpr (T::kParts == 2) {
+      float psum[2] = {p[0], p[1]};
 #pragma unroll
-    for (int x = 0; x < 8; ++x) {
-      p_cur[x] = pack_bf16x2(p[2 * x], p[2 * x + 1]);
-      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p_cur[x]),
-                                             __builtin_bit_cast(bf16x2, 0x3f803f80u), psum, false);
+      for (int x = 0; x < 8; ++x) {
+        split_bf16x2(p[2 * x], p[2 * x + 1], p_cur[0][x], p_cur[1][x]);
+        if (x > 0) {
+          psum[0] += p[2 * x];
+          psum[1] += p[2 * x + 1];
+        }
+      }
+      l_run += psum[0] + psum[1];
+    } else {
+      // the row sum is taken over the bf16-rounded probabilities, the values P.V uses: one v_dot2
+      // with (1, 1) adds a pair
+      float psum = 0.f;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        p_cur[0][x] = pack_bf16x2(p[2 * x], p[2 * x + 1]);
+        psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p_cur[0][x]),
+                                               __builtin_bit_cast(bf16x2, 0x3f803f80u), psum, false);
+      }
+      l_run += psum;
     }
-    l_run += psum;
     // keep the probabilities in this block: without a use here the optimiser sinks the exponentials
     // to their first use in the next step, behind the MFMAs they are meant to overlap with
-    keep_values_here(p_cur, l_run);
+#pragma unroll
+    for (int y = 0; y < T::kParts; ++y) keep_values_here(p_cur[y], l_run);
     __builtin_amdgcn_sched_barrier(0);
     s_cur = s_nxt;
     mx_cur = mx_nxt;
 #pragma unroll
-    for (int x = 0; x < 8; ++x) p_prev[x] = p_cur[x];
+    for (int y = 0; y < T::kParts; ++y)
+#pragma unroll
+      for (int x = 0; x < 8; ++x) p_prev[y][x] = p_cur[y][x];
   };
 
   // ---- first requests: K 0, the query rows | V 0, K 1 (the first two are waited for first) ----
@@ -907,11 +923,14 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
 #pragma unroll
         for (int rd = 0; rd < 2; ++rd)
           va[r].h[rd] = read_v_operand(v_t, half, r, rd);
-      Pack8 pb;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[4 * half + x];
+      for (int y = 0; y < T::kParts; ++y) {
+        Pack8 pb;
 #pragma unroll
-      for (int r = 0; r < T::kOut; ++r) o_acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[r].v, pb.v, o_acc[r], 0, 0, 0);
+        for (int x = 0; x < 4; ++x) pb.w[x] = p_prev[y][4 * half + x];
+#pragma unroll
+        for (int r = 0; r < T::kOut; ++r) o_acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[r].v, pb.v, o_acc[r], 0, 0, 0);
+      }
     }
   }
   barrier_after_lds_fill();  // the buffers are free for the output tiles and for the next row block

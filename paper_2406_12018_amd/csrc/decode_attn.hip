@@ -14,6 +14,7 @@
 //     chunk-attention kernels use (one query per lane, transpose reads for V^T);
 //   * the waves' partial (maximum, sum, output) triples are merged through LDS at the end; with
 //     more than one key range per unit a small second kernel merges the ranges.
+#include "bf16_math.h"
 #include "citrus_internal.h"
 
 namespace citrus {
@@ -22,7 +23,6 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short i16x4;
 
 constexpr int kTileKeys = 32;             // keys per wave tile = rows of one MFMA
@@ -41,6 +41,7 @@ struct Geo {
   static constexpr int kRowsPerLoad = 1024 / kRowBytes;
   static constexpr int kLoadsPerTile = 2 * kTileKeys / kRowsPerLoad;  // 16 (8) instructions of 1 KB
   static constexpr int kKk = D / 16, kOut = D / 32;
+  static constexpr int kParts = D == 64 ? 2 : 1;  // bf16 parts of a probability in P.V, as in the chunk-attention kernels
   __device__ static constexpr int swz(int row) {
     return D == 128 ? (2 * (row % 8)) ^ ((row / 8) % 2) : (2 * ((row / 2) % 4)) ^ ((row / 8) % 2) ^ (4 * (row % 2));
   }
@@ -52,12 +53,6 @@ union Pack8 {
   uint32_t w[4];
   i16x4 h[2];
 };
-
-__device__ inline uint32_t pack_bf16x2(float lo, float hi) {
-  f32x2 f = {lo, hi};
-  bf16x2 b = __builtin_convertvector(f, bf16x2);  // round to nearest even
-  return __builtin_bit_cast(uint32_t, b);
-}
 
 __device__ inline const uint16_t* unit_ptr(const View& v, int b, int l, int h) {
   return static_cast<const uint16_t*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh);
@@ -349,16 +344,21 @@ __device__ __forceinline__ void decode_attn_body(const Dims& dm, const View& q, 
         for (int i = 0; i < 16; ++i) o_acc[r][i] *= alpha;
       m_run = m_new;
     }
-    uint32_t p_pk[8];
+    uint32_t p_pk[T::kParts][8];
     float psum = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const float p0 = __builtin_amdgcn_exp2f(fmaf(s_acc[2 * i], c2, -m_run));
       const float p1 = __builtin_amdgcn_exp2f(fmaf(s_acc[2 * i + 1], c2, -m_run));
-      p_pk[i] = pack_bf16x2(p0, p1);
-      // the row sum is taken over the bf16-rounded probabilities, the values P.V uses
-      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p_pk[i]),
-                                             __builtin_bit_cast(bf16x2, 0x3f803f80u), psum, false);
+      if constexpr (T::kParts == 2) {
+        split_bf16x2(p0, p1, p_pk[0][i], p_pk[1][i]);
+        psum += p0 + p1;
+      } else {
+        p_pk[0][i] = pack_bf16x2(p0, p1);
+        // the row sum is taken over the bf16-rounded probabilities, the values P.V uses
+        psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, p_pk[0][i]),
+                                               __builtin_bit_cast(bf16x2, 0x3f803f80u), psum, false);
+      }
     }
     l_run += psum;
 
@@ -372,11 +372,14 @@ __device__ __forceinline__ void decode_attn_body(const Dims& dm, const View& q, 
         for (int e = 0; e < 2 * T::kOut; ++e) addr[e] = v_t + 16 * half * kRowBytes + v_off[e];
         lds_read_v_operands(av, addr);
       }
-      Pack8 pb;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) pb.w[x] = p_pk[4 * half + x];
+      for (int y = 0; y < T::kParts; ++y) {
+        Pack8 pb;
 #pragma unroll
-      for (int r = 0; r < T::kOut; ++r) o_acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[r].v, pb.v, o_acc[r], 0, 0, 0);
+        for (int x = 0; x < 4; ++x) pb.w[x] = p_pk[y][4 * half + x];
+#pragma unroll
+        for (int r = 0; r < T::kOut; ++r) o_acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[r].v, pb.v, o_acc[r], 0, 0, 0);
+      }
     }
   }
 

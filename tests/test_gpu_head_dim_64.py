@@ -92,3 +92,58 @@ def test_position_shift_rotates_queries_in_the_attention_kernel(c, n_c):
                                  api.citrus_rope(plain, k, n_c), v)
     torch.cuda.synchronize()
     assert torch.equal(out, want)
+
+
+def f64_attention(q, k, v, cached):
+    """causal outputs over [cached states ; chunk] of one layer, log-sum-exps and column sums, in f64"""
+    q, k, v = q.double(), k.double(), v.double()
+    group = q.shape[0] // k.shape[0]
+    logits = q @ k.repeat_interleave(group, 0).transpose(-1, -2).contiguous() / D ** 0.5
+    seen = torch.arange(k.shape[1])[None, :] <= cached + torch.arange(q.shape[1])[:, None]
+    logits = logits.masked_fill(~seen, -torch.inf)
+    p = torch.softmax(logits, -1)
+    return p @ v.repeat_interleave(group, 0), torch.logsumexp(logits, -1), p.reshape(k.shape[0], -1, k.shape[1]).sum(1)
+
+
+def relative(x, ref):
+    return float((x.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("layers", [1, 24])  # four waves per workgroup, eight in pairs of row blocks
+@pytest.mark.parametrize("c,n_c,scale", [(64, 0, 2.0), (129, 100, 1.0), (300, 700, 0.5)])
+def test_probabilities_keep_f32_accuracy(c, n_c, scale, layers):
+    """Probabilities and row sums are f32 numbers, so the outputs are off by little more than their own rounding to bf16
+    (the two bf16 parts of a probability leave 2^-18 of it against the rounding's 2^-9; 1 % allows for 2^-9 / 100) and
+    the f32 results by f32's: with |logit| < 40, an exponent in log2 units carries 40 * 1.44 * 2^-24 = 3.4e-6 of rounding,
+    once in the sum and once in the normaliser.  Probabilities rounded to bf16 leave 1.1 to 1.4 times the rounding in the
+    outputs and 2e-4 or more in the log-sum-exps."""
+    print(f"head_dim 64 accuracy c={c} n_c={n_c} layers={layers}", flush=True)
+    Hq, Hkv = 8, 2
+    cfg = api.Config(batch=1, layers=layers, q_heads=Hq, kv_heads=Hkv, head_dim=D, chunk_len=c, budget=max(n_c, 1), instr_len=8,
+                     cache_capacity=n_c + 2)
+    ws = api.alloc_workspace(cfg)
+    q, k, v = rand((1, layers, Hq, c, D), 1), rand((1, layers, Hkv, c, D), 2, scale), rand((1, layers, Hkv, c, D), 3)
+    kc, vc = rand((1, layers, Hkv, n_c + 2, D), 4, scale), rand((1, layers, Hkv, n_c + 2, D), 5)
+    q[..., D // 2 - 1] = 4.0  # importance that all queries share: rows with a few heavy states
+    lse = torch.empty((1, layers, Hq, c), dtype=torch.float32, device=DEV)
+    lm = torch.empty((1, layers, Hkv, n_c + c), dtype=torch.float32, device=DEV)
+    lse_cache = torch.empty_like(lse) if n_c else None
+    out = api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v, lse=lse, lm_score=lm, lse_cache=lse_cache, workspace=ws)
+    one = api.citrus_decode_step(cfg, q[:, :, :, :1].contiguous(), k[:, :, :, :1].contiguous(), v[:, :, :, :1].contiguous(),
+                                 kc, vc, n_c, workspace=ws)
+    torch.cuda.synchronize()
+    host = lambda x: x[0].cpu()
+    for l in {0, layers - 1}:
+        kcat = torch.cat([host(kc)[l, :, :n_c], host(k)[l]], 1)
+        vcat = torch.cat([host(vc)[l, :, :n_c], host(v)[l]], 1)
+        want, want_lse, want_lm = f64_attention(host(q)[l], kcat, vcat, n_c)
+        rounding = relative(want.bfloat16(), want)
+        assert relative(host(out)[l], want) < 1.01 * rounding
+        assert float((host(lse)[l].double() - want_lse).abs().max()) < 7e-6
+        assert relative(host(lm)[l], want_lm) < 7e-6
+        first = want[:, :1]
+        assert relative(host(one)[l], first) < 1.01 * relative(first.bfloat16(), first) + 1e-5
+        if n_c:
+            cached = torch.logsumexp(host(q)[l].double() @ kcat[:, :n_c].double().repeat_interleave(Hq // Hkv, 0)
+                                     .transpose(-1, -2).contiguous() / D ** 0.5, -1)
+            assert float((host(lse_cache)[l].double() - cached).abs().max()) < 7e-6
