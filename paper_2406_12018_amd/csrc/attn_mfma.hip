@@ -431,9 +431,15 @@ struct UnitView {
   int64_t sb, sl, sh;
   int ss;
 };
-inline UnitView unit_view(const View& v) {
-  return UnitView{static_cast<const char*>(v.ptr), 2 * v.sb, 2 * v.sl, 2 * v.sh, static_cast<int>(2 * v.ss)};
+// rows: sequence rows of a unit.  They span less than 2 GiB (checked at the entry points), so from two rows on the stride
+// is an int; the stride of a single row has no such bound and means nothing.
+inline UnitView unit_view(const View& v, int rows, int head_dim) {
+  return UnitView{static_cast<const char*>(v.ptr), 2 * v.sb, 2 * v.sl, 2 * v.sh,
+                  rows > 1 ? static_cast<int>(2 * v.ss) : 2 * head_dim};
 }
+// Byte offset outside every unit: the range check of a buffer resource drops a store to it and reads zeros from it.  Rows
+// behind the last one are sent there; their own offset, row x stride modulo 2^32, may lie inside the unit again.
+constexpr uint32_t kOutside = 0x80000000u;
 // What a workgroup of the attention kernel works on, prepared on the host: a wave issues one instruction in eight
 // cycles, and with divisions by runtime numbers and per-element strides the set-up took 830 of them.
 struct AttnArgs {
@@ -527,18 +533,24 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   // of its next tile (row and segment; the range check covers this offset only, so no part of it is a scalar).
   struct Stream {
     i32x4 rs;
-    int step;
-    int voff[kPer];
+    uint32_t step;
+    uint32_t voff[kPer];
   };
   const int k_ss_cache = a.k_cache.ss, k_ss_chunk = a.k_chunk.ss, v_ss_cache = a.v_cache.ss, v_ss_chunk = a.v_chunk.ss;  // bytes
   auto seg_words = [&](const UnitView& v, int rows_) { return buffer_words(unit(v, g), rows_ > 0 ? (rows_ - 1) * v.ss + 2 * D : 0); };
   const i32x4 k_rs_cache = seg_words(a.k_cache, n_c), k_rs_chunk = seg_words(a.k_chunk, a.c);
   const i32x4 v_rs_cache = seg_words(a.v_cache, n_c), v_rs_chunk = seg_words(a.v_chunk, a.c);
-  auto enter = [&](Stream& s, const i32x4& rs, int ss, int first_row) {  // positions the stream at a tile of a segment
+  // Positions the stream at the first tile of a segment.  Of the tiles that are read only the last holds rows behind the
+  // segment's end.  If that is the first tile, their offsets are set here; else they are the sum of two numbers of at
+  // most 2^31, an offset inside and the step, and so at least the resource's size without a wrap.
+  auto enter = [&](Stream& s, const i32x4& rs, int ss, int seg_rows) {
     s.rs = rs;
-    s.step = kTileN * ss;
+    s.step = ss < (1 << 25) ? static_cast<uint32_t>(kTileN * ss) : kOutside;
 #pragma unroll
-    for (int x = 0; x < kPer; ++x) s.voff[x] = (first_row + fill_row + kR * x) * ss + fill_seg16;
+    for (int x = 0; x < kPer; ++x) {
+      const int row = fill_row + kR * x;
+      s.voff[x] = row < seg_rows ? static_cast<uint32_t>(row) * static_cast<uint32_t>(ss) + static_cast<uint32_t>(fill_seg16) : kOutside;
+    }
   };
   // load x of the stream's next tile into the wave's rows of tile buffer BUF (0, 1: K; 2, 3: V)
   auto issue_one = [&](const Stream& s, auto buf, auto x) {
@@ -787,11 +799,11 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
 
   // ---- first requests: K 0, the query rows | V 0, K 1 (the first two are waited for first) ----
   Stream sk, sv;
-  auto k_to_chunk = [&] { enter(sk, k_rs_chunk, k_ss_chunk, 0); };  // in front of tile cache_tiles
-  auto v_to_chunk = [&] { enter(sv, v_rs_chunk, v_ss_chunk, 0); };
+  auto k_to_chunk = [&] { enter(sk, k_rs_chunk, k_ss_chunk, a.c); };  // in front of tile cache_tiles
+  auto v_to_chunk = [&] { enter(sv, v_rs_chunk, v_ss_chunk, a.c); };
   if (cache_tiles > 0) {
-    enter(sk, k_rs_cache, k_ss_cache, 0);
-    enter(sv, v_rs_cache, v_ss_cache, 0);
+    enter(sk, k_rs_cache, k_ss_cache, n_c);
+    enter(sv, v_rs_cache, v_ss_cache, n_c);
   } else {
     k_to_chunk();
     v_to_chunk();
@@ -941,7 +953,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   // The output tile leaves through LDS: a lane holds 4-element pieces of ONE query row (256 bytes
   // between neighbouring lanes), so direct stores put 64 scattered 8-byte pieces into every store
   // instruction and keep the compute unit's address path busy for microseconds per row block.  Rows past the end are
-  // out of the output resource's range and dropped.
+  // sent out of the output resource's range and dropped.
   const int out_ss = a.out.ss;
   const __amdgpu_buffer_rsrc_t out_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(unit(a.out, h)), 0,
                                                                           (rows - 1) * out_ss + 2 * D, kBufferFlags);
@@ -957,7 +969,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   // lane and its partner l ^ 32 hold the two halves of every segment: a swap gives each of them whole segments.
   char* const o_tile = ring + wu * (32 * kRowBytes);
   char* const o_s = o_tile + colx * kRowBytes;
-  const int c_swz = colx % T::kSegs;
+  const int c_swz = static_cast<uint32_t>(colx) % T::kSegs;
   const float inv = 1.f / l_tot;
 #pragma unroll
   for (int r = 0; r < T::kOut; ++r)
@@ -976,12 +988,15 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       *reinterpret_cast<uint4*>(o_s + ((2 * r + T::kSegs / 2 * ip + grp) ^ c_swz) * 16) = piece;
     }
   const char* const o_r = o_tile + lanex * 16;  // row lanex / kSegs of a kR-row group
-  const int r_in = lanex / T::kSegs, pos = lanex % T::kSegs;
-  int at = (row0 + r_in) * out_ss;
+  const int r_in = static_cast<uint32_t>(lanex) / T::kSegs, pos = static_cast<uint32_t>(lanex) % T::kSegs;
+  static_assert((kR & (kR - 1)) == 0 && kR <= T::kSegs, "row kR i + r_in modulo kSegs is (kR i modulo kSegs) ^ r_in");
+  const int seg16 = (pos ^ r_in) * 16, rows_left = rows - row0 - r_in;
+  uint32_t at = static_cast<uint32_t>(row0 + r_in) * static_cast<uint32_t>(out_ss);
 #pragma unroll
-  for (int i = 0; i < 32 / kR; ++i, at += kR * out_ss) {
+  for (int i = 0; i < 32 / kR; ++i, at += kR * static_cast<uint32_t>(out_ss)) {
     const u32x4 piece = *reinterpret_cast<const u32x4*>(o_r + kR * i * kRowBytes);
-    __builtin_amdgcn_raw_buffer_store_b128(piece, out_rs, at + (pos ^ ((kR * i + r_in) % T::kSegs)) * 16, 0, 0);
+    const uint32_t row_at = kR * i < rows_left ? at : kOutside;
+    __builtin_amdgcn_raw_buffer_store_b128(piece, out_rs, row_at + (seg16 ^ (kR * i % T::kSegs * 16)), 0, 0);
   }
   __syncthreads();  // the parked tiles have been read back: the next row block may fill the buffers
   }  // pass
@@ -1467,12 +1482,12 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segme
   const TaskShape ts = task_shape(dm.G, WAVES);
   const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
   AttnArgs a;
-  a.q = unit_view(q);
-  a.out = unit_view(out);
-  a.k_cache = unit_view(ks.cache);
-  a.k_chunk = unit_view(ks.chunk);
-  a.v_cache = unit_view(vs.cache);
-  a.v_chunk = unit_view(vs.chunk);
+  a.q = unit_view(q, rows, D);
+  a.out = unit_view(out, rows, D);
+  a.k_cache = unit_view(ks.cache, ks.n_c, D);
+  a.k_chunk = unit_view(ks.chunk, ks.c, D);
+  a.v_cache = unit_view(vs.cache, vs.n_c, D);
+  a.v_chunk = unit_view(vs.chunk, vs.c, D);
   a.rows = rows;
   a.n_c = ks.n_c;
   a.c = ks.c;

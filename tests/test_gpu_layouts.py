@@ -93,3 +93,35 @@ def test_token_major_equals_head_major(dtype, d, Hq, Hkv, c, n_c, n_i):
             assert torch.equal(a, results[1][name]), name
             assert torch.equal(a, results[2][name]), f"{name} (padded strides)"
     assert padded.untouched(), "elements outside a padded view were written"
+
+
+def spread(t, mib):
+    """Same values of a [1, 1, 1, S, d] tensor, rows `mib` MiB apart, NaN in between: (allocation, view)."""
+    S, d = t.shape[3:]
+    stride = mib * 2 ** 19
+    big = torch.full(((S - 1) * stride + d,), float("nan"), dtype=t.dtype, device=t.device)
+    view = torch.as_strided(big, (1, 1, 1, S, d), (d, d, d, stride, 1))
+    view.copy_(t)
+    return big, view
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rows,mib", [(60, 33), (29, 68), (3, 512), (2, 1024), (1, 2048)])
+def test_rows_far_apart(rows, mib, d):
+    """Rows of a unit that nearly span the 2 GiB the library takes.  A tile holds rows past the last one, whose offset
+    (row x stride modulo 2^32) lies between the real rows again: row 125 of the 128-row block of 60 rows at 33 MiB, row 61
+    of the 64-key tile of 29 rows at 68 MiB.  Nothing may be stored there, and nothing read from there may reach a result."""
+    print(f"rows {rows} x {mib} MiB d{d}", flush=True)
+    cfg = api.Config(batch=1, layers=1, q_heads=1, kv_heads=1, head_dim=d, chunk_len=rows, budget=rows, instr_len=8,
+                     cache_capacity=rows + 1)
+    shape = (1, 1, 1, rows, d)
+    q, k, v, kc, vc = (rand(shape, torch.bfloat16, s) for s in range(5))
+    want = api.citrus_chunk_attn(cfg, q, kc, vc, rows, k, v)
+    for wide in ("out", "q", "k", "v", "k_cache", "v_cache"):
+        t = dict(q=q, k=k, v=v, k_cache=kc, v_cache=vc, out=torch.zeros_like(q))
+        big, t[wide] = spread(t[wide], mib)
+        api.citrus_chunk_attn(cfg, t["q"], t["k_cache"], t["v_cache"], rows, t["k"], t["v"], out=t["out"])
+        torch.cuda.synchronize()
+        assert torch.equal(t["out"], want), wide
+        assert int(torch.isnan(big).sum()) == big.numel() - rows * d, f"{wide}: written between the rows"
+        del big, t
