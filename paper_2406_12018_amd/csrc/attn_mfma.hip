@@ -24,6 +24,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "attn_row.h"
 #include "bf16_math.h"
 #include "citrus_internal.h"
 #include "rope_math.h"
@@ -450,7 +451,7 @@ struct AttnArgs {
   int row_blocks;  // of a head
   int per_xcd;     // workgroups per XCD, 0: not a whole number
   FastDiv slots, head_groups, kv_heads, layers;  // workgroup -> (row block slot, head group, KV head, layer)
-  float c2, inv_c2;  // softmax scale in the log2 domain
+  float scale, c2, inv_c2;  // softmax scale, and in the log2 domain
   float *lse, *lse_cache;
   int q_rope_pos0;
   float rope_log2_base;
@@ -959,11 +960,6 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
                                                                           (rows - 1) * out_ss + 2 * D, kBufferFlags);
   int colx = col, lanex = lane;
   hide_loop_invariance(colx, lanex);  // offsets are formed here, per row block, not kept in registers
-  const int t = row0 + col;
-  if (grp == 0 && t < rows) {
-    if (a.lse_cache != nullptr) a.lse_cache[row_id0 + t] = (m_snap + log2f(l_snap_tot)) * kLn2;
-    if (a.lse != nullptr) a.lse[row_id0 + t] = (m_run + log2f(l_tot)) * kLn2;
-  }
   // Each wave parks its 32 x D tile in its own part of the tile buffers (free after the barrier above; 16-byte
   // segments XOR-swizzled by the row: column-wise writes spread over the banks) and stores it back as whole rows.  A
   // lane and its partner l ^ 32 hold the two halves of every segment: a swap gives each of them whole segments.
@@ -971,6 +967,8 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   char* const o_s = o_tile + colx * kRowBytes;
   const int c_swz = static_cast<uint32_t>(colx) % T::kSegs;
   const float inv = 1.f / l_tot;
+  float lse = (m_run + log2f(l_tot)) * kLn2;
+  float zero = 0.f;  // NaN where an output of the lane is not finite
 #pragma unroll
   for (int r = 0; r < T::kOut; ++r)
 #pragma unroll
@@ -981,12 +979,46 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int y = 0; y < 2; ++y)
-          wd[x][y] = pack_bf16x2(o_acc[r][8 * ip + 4 * x + 2 * y] * inv, o_acc[r][8 * ip + 4 * x + 2 * y + 1] * inv);
+        {
+          const float lo = o_acc[r][8 * ip + 4 * x + 2 * y] * inv, hi = o_acc[r][8 * ip + 4 * x + 2 * y + 1] * inv;
+          if constexpr (D == 64) zero = fmaf(hi, 0.f, fmaf(lo, 0.f, zero));
+          wd[x][y] = pack_bf16x2(lo, hi);
+        }
       uint4 piece;  // segment 2 r + grp + D / 16 ip
       swap_halves(wd[0][0], wd[1][0], piece.x, piece.z);
       swap_halves(wd[0][1], wd[1][1], piece.y, piece.w);
       *reinterpret_cast<uint4*>(o_s + ((2 * r + T::kSegs / 2 * ip + grp) ^ c_swz) * 16) = piece;
     }
+  if constexpr (D == 64) {  // rows that are not finite once more, see attn_row.h; the query rows are still in q_t
+    const uint64_t lanes = __ballot(zero != 0.f);
+    uint32_t again = static_cast<uint32_t>(lanes | (lanes >> 32));
+    if (__builtin_expect(again != 0, 0)) {  // wave-uniform
+      auto row_of = [&](const UnitView& cache, const UnitView& chunk) {
+        const char *const in_cache = unit(cache, g), *const in_chunk = unit(chunk, g);
+        const int64_t ss_cache = cache.ss, ss_chunk = chunk.ss;
+        return [=](int j) {
+          return reinterpret_cast<const uint16_t*>(j < n_c ? in_cache + j * ss_cache : in_chunk + (j - n_c) * ss_chunk);
+        };
+      };
+      for (; again != 0; again &= again - 1) {
+        const int r = __builtin_ctz(again), t = row0 + r;
+        if (t >= rows) break;
+        const float q_e = bf16_to_f32(*reinterpret_cast<const uint16_t*>(q_t + Y::at(r, lane / 8) + lane % 8 * 2));
+        float lse_r;
+        const float o = attn_row_64(q_e, n_c + (a.causal ? t : a.c - 1), a.scale, row_of(a.k_cache, a.k_chunk),
+                                    row_of(a.v_cache, a.v_chunk), lse_r);
+        *reinterpret_cast<uint16_t*>(o_tile + r * kRowBytes + ((lane / 8) ^ (r % T::kSegs)) * 16 + lane % 8 * 2) =
+            static_cast<uint16_t>(pack_bf16x2(o, 0.f));
+        if (col == r && !(fabsf(lse) < INFINITY)) lse = lse_r;
+      }
+      no_memory_motion();
+    }
+  }
+  const int t = row0 + col;
+  if (grp == 0 && t < rows) {
+    if (a.lse_cache != nullptr) a.lse_cache[row_id0 + t] = (m_snap + log2f(l_snap_tot)) * kLn2;
+    if (a.lse != nullptr) a.lse[row_id0 + t] = lse;
+  }
   const char* const o_r = o_tile + lanex * 16;  // row lanex / kSegs of a kR-row group
   const int r_in = static_cast<uint32_t>(lanex) / T::kSegs, pos = static_cast<uint32_t>(lanex) % T::kSegs;
   static_assert((kR & (kR - 1)) == 0 && kR <= T::kSegs, "row kR i + r_in modulo kSegs is (kR i modulo kSegs) ^ r_in");
@@ -1503,6 +1535,7 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segme
   a.layers = fast_div(dm.L);
   const int grid = slots * a.head_groups.divisor * dm.Hkv * dm.B * dm.L;
   a.per_xcd = grid % kXcds == 0 ? grid / kXcds : 0;
+  a.scale = dm.scale;
   a.c2 = dm.scale * kLog2e;
   a.inv_c2 = 1.f / a.c2;
   a.lse = lse;

@@ -14,6 +14,7 @@
 //     chunk-attention kernels use (one query per lane, transpose reads for V^T);
 //   * the waves' partial (maximum, sum, output) triples are merged through LDS at the end; with
 //     more than one key range per unit a small second kernel merges the ranges.
+#include "attn_row.h"
 #include "bf16_math.h"
 #include "citrus_internal.h"
 
@@ -166,6 +167,27 @@ struct Partials {
   float2* ml;  // [splits][B*L*Hq]
   float* o;    // [splits][B*L*Hq][D]
 };
+
+// One element of a query row's output, final.  head_dim 64, where a wave holds a row: if an element is not finite, the
+// row is computed once more (see attn_row.h).
+template <int D>
+__device__ __forceinline__ uint16_t final_element(const Dims& dm, const View& q, const Segments& ks, const Segments& vs, int b,
+                                                  int l, int h, int d, float value) {
+  if constexpr (D == 64) {
+    if (__any(!(fabsf(value) < INFINITY))) {
+      const int g = h / dm.G;
+      auto row_of = [&](const Segments& sg) {
+        const uint16_t *const in_cache = unit_ptr(sg.cache, b, l, g), *const in_chunk = unit_ptr(sg.chunk, b, l, g);
+        const int64_t ss_cache = sg.cache.ss, ss_chunk = sg.chunk.ss;
+        const int n_c = sg.n_c;
+        return [=](int j) { return j < n_c ? in_cache + j * ss_cache : in_chunk + (j - n_c) * ss_chunk; };
+      };
+      float lse;
+      value = attn_row_64(bf16_to_f32(unit_ptr(q, b, l, h)[d]), ks.n_c + ks.c - 1, dm.scale, row_of(ks), row_of(vs), lse);
+    }
+  }
+  return static_cast<uint16_t>(pack_bf16x2(value, 0.f) & 0xffffu);
+}
 
 template <int D, int WAVES>
 __device__ __forceinline__ void decode_attn_body(const Dims& dm, const View& q, const Segments& ks, const Segments& vs,
@@ -418,8 +440,7 @@ __device__ __forceinline__ void decode_attn_body(const Dims& dm, const View& q, 
     const int h = g * dm.G + hq;
     if (key_splits == 1) {
       uint16_t* op = const_cast<uint16_t*>(unit_ptr(out, b, l, h));
-      const uint32_t pk = pack_bf16x2(o_all / l_all, 0.f);
-      op[d] = static_cast<uint16_t>(pk & 0xffffu);
+      op[d] = final_element<D>(dm, q, ks, vs, b, l, h, d, o_all / l_all);
     } else {
       const int64_t row = static_cast<int64_t>(sp) * dm.B * dm.L * dm.Hq + static_cast<int64_t>(bl) * dm.Hq + h;
       part.o[row * D + d] = o_all;
@@ -440,7 +461,8 @@ __global__ __launch_bounds__(64 * kWaves) void decode_attn_kernel(Dims dm, View 
 
 // Merge of the key ranges: one thread per (document, layer, query head, head_dim element).
 template <int D>
-__global__ __launch_bounds__(256) void decode_merge_kernel(Dims dm, View out, int key_splits, Partials part) {
+__global__ __launch_bounds__(256) void decode_merge_kernel(Dims dm, View q, Segments ks, Segments vs, View out, int key_splits,
+                                                          Partials part) {
   const int64_t rows = static_cast<int64_t>(dm.B) * dm.L * dm.Hq;
   const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e >= rows * D) return;
@@ -457,8 +479,8 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(Dims dm, View out, in
   }
   const int h = static_cast<int>(row % dm.Hq);
   const int bl = static_cast<int>(row / dm.Hq);
-  uint16_t* op = const_cast<uint16_t*>(unit_ptr(out, bl / dm.L, bl % dm.L, h));
-  op[d] = static_cast<uint16_t>(pack_bf16x2(o_all / l_all, 0.f) & 0xffffu);
+  const int b = bl / dm.L, l = bl % dm.L;
+  const_cast<uint16_t*>(unit_ptr(out, b, l, h))[d] = final_element<D>(dm, q, ks, vs, b, l, h, d, o_all / l_all);
 }
 
 // Key ranges per unit.  A unit's keys are split over several workgroups only when there are fewer units
@@ -491,8 +513,8 @@ hipError_t decode_launch(const Dims& dm, View q, Segments ks, Segments vs, View 
   e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   const int64_t elems = rows * D;
-  hipLaunchKernelGGL(decode_merge_kernel<D>, dim3(static_cast<unsigned>((elems + 255) / 256)), dim3(256), 0, st, dm, out,
-                     splits, part);
+  hipLaunchKernelGGL(decode_merge_kernel<D>, dim3(static_cast<unsigned>((elems + 255) / 256)), dim3(256), 0, st, dm, q,
+                     ks, vs, out, splits, part);
   return hipGetLastError();
 }
 

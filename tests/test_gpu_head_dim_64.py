@@ -147,3 +147,58 @@ def test_probabilities_keep_f32_accuracy(c, n_c, scale, layers):
             cached = torch.logsumexp(host(q)[l].double() @ kcat[:, :n_c].double().repeat_interleave(Hq // Hkv, 0)
                                      .transpose(-1, -2).contiguous() / D ** 0.5, -1)
             assert float((host(lse_cache)[l].double() - cached).abs().max()) < 7e-6
+
+
+@pytest.mark.parametrize("layers", [1, 24])  # four waves per workgroup, eight in pairs of row blocks
+@pytest.mark.parametrize("c,n_c", [(33, 0), (129, 100), (300, 65)])
+def test_infinite_values_reach_only_rows_that_see_them(c, n_c, layers):
+    """An infinite value (one in the cache, one in the chunk, one in the last state) makes the element infinite in the rows
+    that see it and nothing else; rows that do not see a NaN key are untouched by it.  Finite elements keep the bound of
+    the accuracy test."""
+    print(f"head_dim 64 infinities c={c} n_c={n_c} layers={layers}", flush=True)
+    Hq, Hkv, mid = 8, 2, c // 2
+    cfg = api.Config(batch=1, layers=layers, q_heads=Hq, kv_heads=Hkv, head_dim=D, chunk_len=c, budget=max(n_c, 1), instr_len=8,
+                     cache_capacity=n_c + 2)
+    q, k, v = rand((1, layers, Hq, c, D), 1), rand((1, layers, Hkv, c, D), 2), rand((1, layers, Hkv, c, D), 3)
+    kc, vc = rand((1, layers, Hkv, n_c + 2, D), 4), rand((1, layers, Hkv, n_c + 2, D), 5)
+    host = lambda x: x[0].cpu()
+    cat = lambda old, new: torch.cat([host(old)[-1, :, :n_c], host(new)[-1]], 1)
+    want, want_lse, _ = f64_attention(host(q)[-1], cat(kc, k), cat(vc, v), n_c)
+    clean = api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v)
+    v[..., mid, 5], v[..., c - 1, 63] = torch.inf, torch.nan
+    if n_c:
+        vc[..., n_c - 1, 0] = -torch.inf
+        want[..., 0] = -torch.inf
+    want[:, mid:, 5], want[:, c - 1:, 63] = torch.inf, torch.nan
+    lse = torch.empty((1, layers, Hq, c), dtype=torch.float32, device=DEV)
+    out = api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v, lse=lse)
+    k[..., c - 1, 7] = torch.nan
+    hidden = api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v)
+    torch.cuda.synchronize()
+    got, finite = host(out)[-1].double(), want.isfinite()
+    assert torch.equal(got.isposinf(), want.isposinf()) and torch.equal(got.isneginf(), want.isneginf())
+    assert torch.equal(got.isnan(), want.isnan())
+    assert relative(got[finite], want[finite]) < 1.01 * relative(want[finite].bfloat16(), want[finite])
+    assert float((host(lse)[-1].double() - want_lse).abs().max()) < 7e-6
+    assert torch.equal(hidden[:, :, :, :c - 1].nan_to_num(7.0), out[:, :, :, :c - 1].nan_to_num(7.0))
+    assert bool(hidden[:, :, :, c - 1].isnan().all())
+    again = api.citrus_chunk_attn(cfg, q, kc, rand(vc.shape, 5), n_c, rand(k.shape, 2), rand(v.shape, 3))
+    assert torch.equal(again, clean)
+
+
+@pytest.mark.parametrize("G,n", [(4, 31), (7, 700), (4, 2500)])  # one key range, several
+def test_infinite_values_in_a_decoding_step(G, n):
+    print(f"head_dim 64 decode, infinities G={G} n={n}", flush=True)
+    Hkv = 2
+    cfg = api.Config(batch=1, layers=1, q_heads=G * Hkv, kv_heads=Hkv, head_dim=D, chunk_len=32, budget=n + 2, instr_len=8)
+    q, kn, vn = rand((1, 1, G * Hkv, 1, D), 1), rand((1, 1, Hkv, 1, D), 2), rand((1, 1, Hkv, 1, D), 3)
+    kc, vc = rand((1, 1, Hkv, n + 2, D), 4), rand((1, 1, Hkv, n + 2, D), 5)
+    cat = lambda old, new: torch.cat([old[0, 0, :, :n], new[0, 0]], 1).cpu()
+    want, *_ = f64_attention(q[0, 0].cpu(), cat(kc, kn), cat(vc, vn), n)
+    vc[0, 0, 0, n // 2, 9], vn[0, 0, 0, 0, 60] = torch.inf, -torch.inf
+    want[:G, :, 9], want[:G, :, 60] = torch.inf, -torch.inf
+    out = api.citrus_decode_step(cfg, q, kn, vn, kc, vc, n, workspace=api.alloc_workspace(cfg))
+    got, finite = out[0, 0].cpu().double(), want.isfinite()
+    assert torch.equal(got.isposinf(), want.isposinf()) and torch.equal(got.isneginf(), want.isneginf())
+    assert not bool(got.isnan().any())
+    assert relative(got[finite], want[finite]) < 1.01 * relative(want[finite].bfloat16(), want[finite])
