@@ -150,7 +150,12 @@ __device__ __forceinline__ int wave_prefix_sum(int v) {
 // are left out.
 // Measured against four passes of three barriers with a shuffled scan, kernel trace: 8 units of 1280 candidates 6.9 ->
 // 5.1 us, 128 units 8.1 -> 5.8 us.
-template <int ITEMS, int THREADS, bool SUM_HEADS>
+// How a workgroup forms the values it ranks: one head's scores, or the sums over a layer's heads.  The sums grow in head
+// order (unit_score), either for all of a thread's candidates at a time, with about 32 loads in flight, or one candidate
+// after the other, which waits for every load but needs no thread without a candidate.
+enum class Scores { kOneHead, kSumByHead, kSumByCandidate };
+
+template <int ITEMS, int THREADS, Scores FORM>
 __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_sum, int n, int k, int forced,
                                                int32_t* idx) {
   constexpr int WAVES = THREADS / 64, kBins = 256, kPasses = 4;
@@ -171,9 +176,7 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
     for (int pass = 0; pass < kPasses; ++pass) hist[pass][tid] = 0;
   }
   uint32_t key[ITEMS];
-  if constexpr (SUM_HEADS) {
-    // Layer-wise selection: the sums grow head by head (the order of unit_score) for all of a thread's candidates at a
-    // time, with about 32 loads in flight; one candidate after the other, each head's load was waited for on its own.
+  if constexpr (FORM == Scores::kSumByHead) {
     float sum[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) sum[i] = base[min(i * THREADS + tid, n - 1)];
@@ -189,7 +192,7 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
       const int j = i * THREADS + tid;
-      key[i] = j < n ? unit_key(base, 1, n, forced, j) : 0u;
+      key[i] = j < n ? unit_key(base, FORM == Scores::kOneHead ? 1 : heads_to_sum, n, forced, j) : 0u;
     }
   }
   __syncthreads();
@@ -296,10 +299,10 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
 // Eight keys per thread (up to 2048 candidates) fit 32 registers with one wave per SIMD: next to two waves of the
 // chunk-attention kernel (240 registers each) a SIMD has 32 left, and with them these workgroups run beside an
 // attention launch (the second-stream form of the chunk loop) instead of waiting for a compute unit of their own.
-template <int ITEMS, int THREADS, bool SUM_HEADS>
+template <int ITEMS, int THREADS, Scores FORM>
 __global__ __launch_bounds__(THREADS) void topk_regs_kernel(const float* score, int heads_to_sum, int n, int k, int forced,
                                                            int32_t* idx) {
-  topk_regs_body<ITEMS, THREADS, SUM_HEADS>(score, heads_to_sum, n, k, forced, idx);
+  topk_regs_body<ITEMS, THREADS, FORM>(score, heads_to_sum, n, k, forced, idx);
 }
 
 __global__ void iota_kernel(int32_t* p, int base, int count) {
@@ -386,18 +389,31 @@ hipError_t launch_topk(const float* score, int units, int heads_to_sum, int n, i
   // candidates: 17.9 us with 256 threads, 10.6 with 1024; with more units the chip is full either way), and for the sums
   // over a layer's heads, a read of heads_to_sum * n floats through one compute unit that needs its loads in flight
   // (16 units of 32 heads x 2048 candidates: 70 us candidate by candidate, 62 head by head, 12.7 with 1024 threads).
-  const bool sum_heads = heads_to_sum > 1;
+  // Two such workgroups fit a compute unit.  With more units than that the chip is full, threads without a candidate are
+  // time lost, and short sums go candidate by candidate on 256 threads.  us with 1024 | 256 threads: 1024 units of 32
+  // heads x 100 candidates 14.1 | 6.9, 8 x 500 11.2 | 7.5, 8 x 1000 14.0 | 14.4, 8 x 2048 20.3 | 25.1; six times the
+  // compute units: 8 x 1000 20.2 | 16.9, 16 x 1000 30.1 | 28.6, 8 x 2048 29.0 | 29.6.  Up to two rounds of workgroups:
+  // 512 units of 2 x 300 4.8 | 4.2, of 8 x 1280 7.1 | 9.1.
+  constexpr Scores kOne = Scores::kOneHead, kByHead = Scores::kSumByHead, kByCandidate = Scores::kSumByCandidate;
+  const int cus = compute_units();
+  const bool sums = heads_to_sum > 1;
+  const int short_most = units > 5 * cus ? 16384 : n <= 2 * kWideThreads ? 8192 : 6144;
+  const bool short_sums = sums && units > 2 * cus && static_cast<int64_t>(heads_to_sum) * n <= short_most;
   auto kern = topk_kernel;
   int threads = kSelThreads;
   if (n <= 2 * kWideThreads) {
-    kern = sum_heads ? topk_regs_kernel<2, kWideThreads, true> : topk_regs_kernel<8, kSelThreads, false>;
-    threads = sum_heads ? kWideThreads : kSelThreads;
+    kern = short_sums ? topk_regs_kernel<8, kSelThreads, kByCandidate>
+           : sums     ? topk_regs_kernel<2, kWideThreads, kByHead>
+                      : topk_regs_kernel<8, kSelThreads, kOne>;
+    threads = sums && !short_sums ? kWideThreads : kSelThreads;
   } else if (n <= 6 * kWideThreads) {
-    const bool wide = units <= compute_units();
-    kern = sum_heads ? topk_regs_kernel<6, kWideThreads, true>
-           : wide    ? topk_regs_kernel<6, kWideThreads, false>
-                     : topk_regs_kernel<24, kSelThreads, false>;
-    threads = sum_heads || wide ? kWideThreads : kSelThreads;
+    const bool wide = sums ? !short_sums : units <= cus;
+    kern = short_sums                      ? topk_regs_kernel<24, kSelThreads, kByCandidate>
+           : sums && n <= 3 * kWideThreads ? topk_regs_kernel<3, kWideThreads, kByHead>
+           : sums                          ? topk_regs_kernel<6, kWideThreads, kByHead>
+           : wide                          ? topk_regs_kernel<6, kWideThreads, kOne>
+                                           : topk_regs_kernel<24, kSelThreads, kOne>;
+    threads = wide ? kWideThreads : kSelThreads;
   }
   hipLaunchKernelGGL(kern, dim3(units), dim3(threads), 0, st, score, heads_to_sum, n, k, forced, idx);
   return hipGetLastError();
