@@ -10,33 +10,24 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kRowsPerBlock = 4;  // one wavefront per query row
 
-// Logit: the type the q.k products are accumulated and the maximum / normaliser subtracted in.  The f32
+// The type the q.k products are accumulated and the maximum / normaliser subtracted in.  The f32
 // mode promises 1e-5 against an f64 reference: with logits of a few tens an f32 dot product and subtraction
-// alone leave a relative error of that order in the probability, so f32 inputs use f64 there.
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-  typedef double Logit;
-  static constexpr int kVec = 4;  // elements per 16-byte load
-  __device__ static void load16(const float* p, float* dst) {
-    float4 v = *reinterpret_cast<const float4*>(p);
-    dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-  }
-  __device__ static float load1(const float* p) { return *p; }
-  __device__ static void store1(float* p, float v) { *p = v; }
-};
-template <typename T>
-__device__ inline const T* row_ptr(const View& v, int b, int l, int h, int s) {
-  return static_cast<const T*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh + static_cast<int64_t>(s) * v.ss);
+// alone leave a relative error of that order in the probability.
+typedef double Logit;
+
+constexpr int kVec = 4;  // elements per 16-byte load
+__device__ inline void load16(const float* p, float* dst) {
+  float4 v = *reinterpret_cast<const float4*>(p);
+  dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+}
+__device__ inline const float* row_ptr(const View& v, int b, int l, int h, int s) {
+  return static_cast<const float*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh + static_cast<int64_t>(s) * v.ss);
 }
 
 // candidate j -> its row in the cache or the chunk segment
-template <typename T>
-__device__ inline const T* cand_ptr(const Segments& sg, int b, int l, int g, int j) {
-  return j < sg.n_c ? row_ptr<T>(sg.cache, b, l, g, j) : row_ptr<T>(sg.chunk, b, l, g, j - sg.n_c);
+__device__ inline const float* cand_ptr(const Segments& sg, int b, int l, int g, int j) {
+  return j < sg.n_c ? row_ptr(sg.cache, b, l, g, j) : row_ptr(sg.chunk, b, l, g, j - sg.n_c);
 }
-
-__device__ inline float mad(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ inline double mad(double a, double b, double c) { return fma(a, b, c); }
 
 __device__ inline float wave_max(float v) {
 #pragma unroll
@@ -58,11 +49,10 @@ __device__ inline float wave_sum(float v) {
 // nothing): 8 layers of 32/8 heads, head_dim 128, 1000 states 668 -> 516 us; 2 layers of 8/8 heads, head_dim 64,
 // 3000 states 1108 -> 987 us.
 constexpr int kValueRows = 16;
-template <typename T, int D>
-__global__ __launch_bounds__(kWave* kRowsPerBlock) void attn_generic_kernel(Dims dm, View q, int rows, Segments ks,
+template <int D>
+__global__ __launch_bounds__(kWave* kRowsPerBlock) void attn_f32_kernel(Dims dm, View q, int rows, Segments ks,
                                                                            Segments vs, int causal, View out,
                                                                            float* lse) {
-  typedef typename Elem<T>::Logit Logit;
   __shared__ __attribute__((aligned(16))) Logit q_s[kRowsPerBlock][D];
   __shared__ __attribute__((aligned(16))) float p_s[kRowsPerBlock][kWave];
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -78,8 +68,8 @@ __global__ __launch_bounds__(kWave* kRowsPerBlock) void attn_generic_kernel(Dims
   constexpr int E = D / kWave;                   // output dims per lane
   constexpr int kKeyElems = D < 64 ? D : 64;     // elements of a key in flight per lane
 
-  const T* qp = row_ptr<T>(q, b, l, h, t);
-  for (int e = lane; e < D; e += kWave) q_s[w][e] = static_cast<Logit>(Elem<T>::load1(qp + e));
+  const float* qp = row_ptr(q, b, l, h, t);
+  for (int e = lane; e < D; e += kWave) q_s[w][e] = static_cast<Logit>(qp[e]);
   __syncthreads();
 
   float m = -INFINITY, lsum = 0.f, acc[E];
@@ -90,9 +80,9 @@ __global__ __launch_bounds__(kWave* kRowsPerBlock) void attn_generic_kernel(Dims
   auto load_values = [&](int j, float (&v)[kValueRows][E]) {
 #pragma unroll
     for (int u = 0; u < kValueRows; ++u) {
-      const T* vp = cand_ptr<T>(vs, b, l, g, min(j + u, limit));
+      const float* vp = cand_ptr(vs, b, l, g, min(j + u, limit));
 #pragma unroll
-      for (int e = 0; e < E; ++e) v[u][e] = Elem<T>::load1(vp + lane + e * kWave);
+      for (int e = 0; e < E; ++e) v[u][e] = vp[lane + e * kWave];
     }
   };
 
@@ -103,15 +93,15 @@ __global__ __launch_bounds__(kWave* kRowsPerBlock) void attn_generic_kernel(Dims
     if (out.ptr != nullptr && j0 <= limit) load_values(j0, v_now);
     Logit s = -INFINITY;
     if (valid) {
-      const T* kp = cand_ptr<T>(ks, b, l, g, j);
+      const float* kp = cand_ptr(ks, b, l, g, j);
       Logit dot = 0;
 #pragma unroll
       for (int e0 = 0; e0 < D; e0 += kKeyElems) {
         float kv[kKeyElems];
 #pragma unroll
-        for (int e = 0; e < kKeyElems; e += Elem<T>::kVec) Elem<T>::load16(kp + e0 + e, kv + e);
+        for (int e = 0; e < kKeyElems; e += kVec) load16(kp + e0 + e, kv + e);
 #pragma unroll
-        for (int e = 0; e < kKeyElems; ++e) dot = mad(q_s[w][e0 + e], static_cast<Logit>(kv[e]), dot);
+        for (int e = 0; e < kKeyElems; ++e) dot = fma(q_s[w][e0 + e], static_cast<Logit>(kv[e]), dot);
       }
       s = dot * static_cast<Logit>(dm.scale);
     }
@@ -148,10 +138,10 @@ __global__ __launch_bounds__(kWave* kRowsPerBlock) void attn_generic_kernel(Dims
 
   if (!row_ok) return;
   if (out.ptr != nullptr) {
-    T* op = const_cast<T*>(row_ptr<T>(out, b, l, h, t));
+    float* op = const_cast<float*>(row_ptr(out, b, l, h, t));
     const float inv = 1.f / lsum;
 #pragma unroll
-    for (int e = 0; e < E; ++e) Elem<T>::store1(op + lane + e * kWave, acc[e] * inv);
+    for (int e = 0; e < E; ++e) op[lane + e * kWave] = acc[e] * inv;
   }
   if (lse != nullptr && lane == 0)
     lse[(static_cast<int64_t>(blockIdx.z) * dm.Hq + h) * rows + t] = m + logf(lsum);
@@ -169,10 +159,9 @@ constexpr int kColsumTile = kColsumWaves * kColsumRows;
 // Loops that are mostly this kernel, same bits: 3 layers of 14/2 heads, head_dim 64, two caches 5990 -> 1423 us;
 // 4 layers of 16/4 heads, head_dim 128, 128 instruction rows 8010 -> 3978 us.  The smallest (4 heads, 32 rows,
 // 72 states a step; 26 of its 52 us were here) 858 -> 525 us a document.
-template <typename T, int D>
-__global__ __launch_bounds__(kWave* kColsumWaves) void colsum_generic_kernel(Dims dm, View q, int rows, Segments ks,
+template <int D>
+__global__ __launch_bounds__(kWave* kColsumWaves) void colsum_f32_kernel(Dims dm, View q, int rows, Segments ks,
                                                                             int causal, const float* lse, float* score) {
-  typedef typename Elem<T>::Logit Logit;
   __shared__ __attribute__((aligned(16))) Logit q_s[kColsumTile][D];
   __shared__ float p_s[2][kColsumTile][kWave];
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -183,9 +172,9 @@ __global__ __launch_bounds__(kWave* kColsumWaves) void colsum_generic_kernel(Dim
 
   float kreg[D];
   {
-    const T* kp = cand_ptr<T>(ks, b, l, g, key_ok ? j : n - 1);
+    const float* kp = cand_ptr(ks, b, l, g, key_ok ? j : n - 1);
 #pragma unroll
-    for (int e = 0; e < D; e += Elem<T>::kVec) Elem<T>::load16(kp + e, kreg + e);
+    for (int e = 0; e < D; e += kVec) load16(kp + e, kreg + e);
   }
   // first chunk row that sees candidate j (cache candidates are seen by every row)
   const int t_first = (causal && j >= ks.n_c) ? j - ks.n_c : 0;
@@ -201,10 +190,10 @@ __global__ __launch_bounds__(kWave* kColsumWaves) void colsum_generic_kernel(Dim
       const int h = g * dm.G + r / rows;
       t[x] = r % rows;
       lse_r[x] = lse[(static_cast<int64_t>(blockIdx.z) * dm.Hq + h) * rows + t[x]];
-      const T* qp = row_ptr<T>(q, b, l, h, t[x]);
+      const float* qp = row_ptr(q, b, l, h, t[x]);
 #pragma unroll
       for (int e = 0; e < D; e += kWave)
-        q_s[w * kColsumRows + x][e + lane] = static_cast<Logit>(Elem<T>::load1(qp + e + lane));
+        q_s[w * kColsumRows + x][e + lane] = static_cast<Logit>(qp[e + lane]);
     }
     // a wave reads only the rows it has written
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -220,7 +209,7 @@ __global__ __launch_bounds__(kWave* kColsumWaves) void colsum_generic_kernel(Dim
     for (int e = 0; e < D; ++e)
 #pragma unroll
       for (int x = 0; x < kColsumRows; ++x)
-        dot[x] = mad(q_s[w * kColsumRows + x][e], static_cast<Logit>(kreg[e]), dot[x]);
+        dot[x] = fma(q_s[w * kColsumRows + x][e], static_cast<Logit>(kreg[e]), dot[x]);
 #pragma unroll
     for (int x = 0; x < kColsumRows; ++x) {
       const float p = expf(static_cast<float>(dot[x] * static_cast<Logit>(dm.scale) - static_cast<Logit>(lse_r[x])));
@@ -237,21 +226,21 @@ __global__ __launch_bounds__(kWave* kColsumWaves) void colsum_generic_kernel(Dim
   if (w == 0 && key_ok) score[(static_cast<int64_t>(blockIdx.z) * dm.Hkv + g) * n + j] = sum;
 }
 
-template <typename T, int D>
-hipError_t attn_launch_t(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
+template <int D>
+hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
                          float* lse, hipStream_t st) {
   dim3 grid((rows + kRowsPerBlock - 1) / kRowsPerBlock, dm.Hq, dm.B * dm.L);
-  hipLaunchKernelGGL((attn_generic_kernel<T, D>), grid, dim3(kWave * kRowsPerBlock), 0, st, dm, q, rows, ks, vs,
+  hipLaunchKernelGGL(attn_f32_kernel<D>, grid, dim3(kWave * kRowsPerBlock), 0, st, dm, q, rows, ks, vs,
                      causal, out, lse);
   return hipGetLastError();
 }
 
-template <typename T, int D>
-hipError_t colsum_launch_t(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
+template <int D>
+hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
                            float* score, hipStream_t st) {
   const int n = ks.n_c + ks.c;
   dim3 grid((n + kWave - 1) / kWave, dm.Hkv, dm.B * dm.L);
-  hipLaunchKernelGGL((colsum_generic_kernel<T, D>), grid, dim3(kWave * kColsumWaves), 0, st, dm, q, rows, ks, causal,
+  hipLaunchKernelGGL(colsum_f32_kernel<D>, grid, dim3(kWave * kColsumWaves), 0, st, dm, q, rows, ks, causal,
                      lse, score);
   return hipGetLastError();
 }
@@ -260,14 +249,14 @@ hipError_t colsum_launch_t(const Dims& dm, View q, int rows, Segments ks, int ca
 
 hipError_t launch_attn_f32(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
                            hipStream_t st) {
-  return dm.D == 64 ? attn_launch_t<float, 64>(dm, q, rows, ks, vs, causal, out, lse, st)
-                    : attn_launch_t<float, 128>(dm, q, rows, ks, vs, causal, out, lse, st);
+  return dm.D == 64 ? attn_launch<64>(dm, q, rows, ks, vs, causal, out, lse, st)
+                    : attn_launch<128>(dm, q, rows, ks, vs, causal, out, lse, st);
 }
 
 hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse, float* score,
                              hipStream_t st) {
-  return dm.D == 64 ? colsum_launch_t<float, 64>(dm, q, rows, ks, causal, lse, score, st)
-                    : colsum_launch_t<float, 128>(dm, q, rows, ks, causal, lse, score, st);
+  return dm.D == 64 ? colsum_launch<64>(dm, q, rows, ks, causal, lse, score, st)
+                    : colsum_launch<128>(dm, q, rows, ks, causal, lse, score, st);
 }
 
 }  // namespace citrus

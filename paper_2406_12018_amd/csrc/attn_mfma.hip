@@ -100,11 +100,6 @@ __device__ inline i16x4 lds_read_tr16(const char* p) {
 // state a non-transcendental consumer needs, and no vector instruction may read an MFMA result
 // sooner than the MFMA takes to complete (callers keep a whole MFMA group in between).
 typedef __attribute__((ext_vector_type(4))) int i32x4;
-__device__ inline void mfma_pinned(f32x16& acc, const bf16x8& a, const bf16x8& b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
-               : "+v"(acc)
-               : "v"(__builtin_bit_cast(i32x4, a)), "v"(__builtin_bit_cast(i32x4, b)));
-}
 __device__ inline f32x16 mfma_pinned_first(const bf16x8& a, const bf16x8& b) {  // accumulator starts at zero
   f32x16 d;
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0"
@@ -140,7 +135,19 @@ __device__ inline void exp2x2_then_mfma(float x0, float x1, float& y0, float& y1
 }
 
 // Small fences for the optimiser, as functions so that kernel templates hold no asm of their own.
-__device__ inline void hide_loop_invariance(int& a, int& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+// -inf where n < 0, else x: three vector instructions.  (Sixteen comparisons whose results wait in scalar registers made
+// the masked half step 40 instructions longer and spilled other scalars around it.)
+__device__ inline float minus_inf_if_negative(int n, float x) {
+  const int all_ones = n >> 31;
+  asm("v_bfi_b32 %0, %1, %2, %0" : "+v"(x) : "v"(all_ones), "s"(0xff800000u));
+  return x;
+}
+// the same number, of which the compiler knows nothing: what is formed from it is formed here, not ahead of a loop and
+// kept in a register through it
+__device__ inline uint32_t formed_here(uint32_t x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 __device__ inline void keep_values_here(uint32_t (&p)[8], float& l) {
   asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(p[5]), "+v"(p[6]), "+v"(p[7]), "+v"(l));
 }
@@ -170,7 +177,9 @@ __device__ inline void load_lds_unwatched(const i32x4& rsrc, uint32_t lds, int l
 // Buffer resource of `bytes` bytes at p as the four words the asm above takes.
 __device__ inline i32x4 buffer_words(const void* p, int bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(p);
-  return i32x4{static_cast<int>(a), static_cast<int>(a >> 32) & 0xffff, bytes, kBufferFlags};
+  i32x4 words = {static_cast<int>(a), static_cast<int>(a >> 32) & 0xffff, bytes, kBufferFlags};
+  asm volatile("" : "+s"(words));  // one value: known to be constant, the last word was moved in place in front of each use
+  return words;
 }
 
 // All but the newest LEFT loads of this wave have landed, and then every wave's have (PUBLISH: its LDS accesses are
@@ -223,7 +232,8 @@ __host__ __device__ inline TaskShape task_shape(int G, int waves = kWaves) {
 }
 
 // Row normalisers only (no values, no output, no mask): one partial (running maximum, sum) pair per key range and
-// row.  First pass of the two-pass importance scores.
+// row; with a single range the normaliser itself, as merge_partials_kernel leaves it.  First pass of the two-pass
+// importance scores.
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, int rows, Segments ks, int key_splits,
                                                               float2* part) {
@@ -407,7 +417,8 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
   const int t = row0 + col;
   if (wave_active && t < rows && grp == 0) {  // log2 domain; an empty range leaves (-inf, 0)
     const int64_t row_id = (static_cast<int64_t>(bl) * dm.Hq + h) * rows + t;
-    part[static_cast<int64_t>(sp) * dm.B * dm.L * dm.Hq * rows + row_id] = make_float2(m_run, l_tot);
+    part[static_cast<int64_t>(sp) * dm.B * dm.L * dm.Hq * rows + row_id] =
+        key_splits == 1 ? make_float2(m_run + log2f(l_tot), 1.f) : make_float2(m_run, l_tot);
   }
 }
 
@@ -431,21 +442,23 @@ struct UnitView {
   const char* ptr;
   int64_t sb, sl, sh;
   int ss;
+  uint32_t tile_step;  // of kTileN rows; kOutside if that is 2 GiB or more
 };
-// rows: sequence rows of a unit.  They span less than 2 GiB (checked at the entry points), so from two rows on the stride
-// is an int; the stride of a single row has no such bound and means nothing.
-inline UnitView unit_view(const View& v, int rows, int head_dim) {
-  return UnitView{static_cast<const char*>(v.ptr), 2 * v.sb, 2 * v.sl, 2 * v.sh,
-                  rows > 1 ? static_cast<int>(2 * v.ss) : 2 * head_dim};
-}
 // Byte offset outside every unit: the range check of a buffer resource drops a store to it and reads zeros from it.  Rows
 // behind the last one are sent there; their own offset, row x stride modulo 2^32, may lie inside the unit again.
 constexpr uint32_t kOutside = 0x80000000u;
+// rows: sequence rows of a unit.  They span less than 2 GiB (checked at the entry points), so from two rows on the stride
+// is an int; the stride of a single row has no such bound and means nothing.
+inline UnitView unit_view(const View& v, int rows, int head_dim) {
+  const int ss = rows > 1 ? static_cast<int>(2 * v.ss) : 2 * head_dim;
+  return UnitView{static_cast<const char*>(v.ptr), 2 * v.sb, 2 * v.sl, 2 * v.sh, ss,
+                  ss < static_cast<int>(kOutside / kTileN) ? static_cast<uint32_t>(kTileN * ss) : kOutside};
+}
 // What a workgroup of the attention kernel works on, prepared on the host: a wave issues one instruction in eight
 // cycles, and with divisions by runtime numbers and per-element strides the set-up took 830 of them.
 struct AttnArgs {
   UnitView q, out, k_cache, k_chunk, v_cache, v_chunk;
-  int rows, n_c, c, causal, q_heads;
+  int n_c, c, q_heads;  // c: chunk states and query rows
   int paired;      // a workgroup takes a row block and its mirror image
   int log_heads;   // 2^log_heads query heads of a group per workgroup
   int row_blocks;  // of a head
@@ -489,6 +502,11 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
 
   const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
   const int col = lane % 32, grp = lane / 32;
+  // The instance that rotates its queries is at the limit of its registers: it forms what the rare branches of the key loop
+  // need of the lane's number there (227 registers; 256 and some in scratch otherwise: 16 layers, a document of 4000
+  // tokens, 3.28 against 3.12 ms).  The other instances keep these numbers: 243 registers, and documents 0.3 to 0.6 %
+  // faster than with 217.
+  auto when_needed = [](uint32_t x) { return ROTATE_Q ? formed_here(x) : x; };
   constexpr int kR = T::kRowsPerLoad;
   constexpr int kFillRows = kTileN / WAVES;             // rows of a tile each wave fetches
   constexpr int kPer = kFillRows / kR;                  // load instructions per wave and tile
@@ -527,7 +545,6 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   typedef __attribute__((address_space(3))) char* lds_char_ptr;
   auto lds_addr = [](char* p) { return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char_ptr)p)); };
   const int fill_row0 = kFillRows * wu;  // first tile row this wave fetches
-  const int fill_row = fill_row0 + lane / T::kSegs, fill_seg16 = ((lane % T::kSegs) ^ Y::swz(lane / T::kSegs)) * 16;
   const uint32_t fill_lds0 = lds_addr(k_s) + fill_row0 / kR * Y::kBlock;
   const int cache_tiles = (n_c + kTileN - 1) / kTileN;
   // One stream of tiles (K or V): the resource of the segment it is in and, per load instruction, the lane's byte offset
@@ -537,20 +554,21 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     uint32_t step;
     uint32_t voff[kPer];
   };
-  const int k_ss_cache = a.k_cache.ss, k_ss_chunk = a.k_chunk.ss, v_ss_cache = a.v_cache.ss, v_ss_chunk = a.v_chunk.ss;  // bytes
   auto seg_words = [&](const UnitView& v, int rows_) { return buffer_words(unit(v, g), rows_ > 0 ? (rows_ - 1) * v.ss + 2 * D : 0); };
   const i32x4 k_rs_cache = seg_words(a.k_cache, n_c), k_rs_chunk = seg_words(a.k_chunk, a.c);
   const i32x4 v_rs_cache = seg_words(a.v_cache, n_c), v_rs_chunk = seg_words(a.v_chunk, a.c);
   // Positions the stream at the first tile of a segment.  Of the tiles that are read only the last holds rows behind the
   // segment's end.  If that is the first tile, their offsets are set here; else they are the sum of two numbers of at
   // most 2^31, an offset inside and the step, and so at least the resource's size without a wrap.
-  auto enter = [&](Stream& s, const i32x4& rs, int ss, int seg_rows) {
+  auto enter = [&](Stream& s, const i32x4& rs, const UnitView& v, int seg_rows) {
     s.rs = rs;
-    s.step = ss < (1 << 25) ? static_cast<uint32_t>(kTileN * ss) : kOutside;
+    s.step = v.tile_step;
+    const uint32_t lanex = when_needed(lane);
+    const int fill_row = fill_row0 + lanex / T::kSegs, fill_seg16 = ((lanex % T::kSegs) ^ Y::swz(lanex / T::kSegs)) * 16;
 #pragma unroll
     for (int x = 0; x < kPer; ++x) {
       const int row = fill_row + kR * x;
-      s.voff[x] = row < seg_rows ? static_cast<uint32_t>(row) * static_cast<uint32_t>(ss) + static_cast<uint32_t>(fill_seg16) : kOutside;
+      s.voff[x] = row < seg_rows ? static_cast<uint32_t>(row) * static_cast<uint32_t>(v.ss) + static_cast<uint32_t>(fill_seg16) : kOutside;
     }
   };
   // load x of the stream's next tile into the wave's rows of tile buffer BUF (0, 1: K; 2, 3: V)
@@ -602,19 +620,17 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   const int rb = pass == 0 ? rb_first : rb_second;
   const int row0 = rb * rows_per_block + (wu >> a.log_heads) * kRowsPerWave;
 
-  const int rows = a.rows;
+  const int rows = a.c;
   const int blk_row_last = min(rows, (rb + 1) * rows_per_block) - 1;
-  const int t_end = cache_tiles + (a.causal ? blk_row_last : a.c - 1) / kTileN + 1;
+  const int t_end = cache_tiles + blk_row_last / kTileN + 1;
   // candidates are numbered tile by tile here: chunk state x is candidate chunk0 + x
   const int chunk0 = cache_tiles * kTileN;
-  const int wave_limit_min = chunk0 + (a.causal ? row0 : a.c - 1);  // up to it every row sees the chunk's states
+  const int wave_limit_min = chunk0 + row0;       // up to it every row sees the chunk's states
   const int chunk_masked = (wave_limit_min + 1) / 32;               // half tiles of the chunk from here on may need a mask
   int next_masked = n_c % kTileN ? n_c / 32 : chunk_masked;         // the next half tile that may need one
 
   // ---- Q^T operand, kept in registers: q_op[kk] = Q[row0 + col][16 kk + 8 grp ..+7] ----
   bf16x8 q_op[T::kKk];
-  const int t_lane = max(min(row0 + col, rows - 1), 0);
-  const int limit_lane = chunk0 + (a.causal ? t_lane : a.c - 1);
 
   // ---- running softmax state: one query per lane ----
   const float c2 = a.c2;  // logits are kept in the log2 domain
@@ -652,11 +668,12 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   // issue_k(slot) / issue_v(slot) put the loads of the tile being fetched between the MFMAs.
   auto half_step = [&](int hc, const char* v_t, auto&& issue_k, auto&& issue_v, auto&& before_tail) {
     if (__builtin_expect(hc >= next_masked, 0)) {  // wave-uniform: the causal edge and the ends of the segments only
-      const int lim_rel = (hc < 2 * cache_tiles ? n_c - 1 : limit_lane) - 32 * hc - 4 * grp;
+      const uint32_t lanex = when_needed(lane);
+      const int limit_lane = chunk0 + min(row0 + static_cast<int>(lanex % 32), rows - 1);
+      const int lim_rel = (hc < 2 * cache_tiles ? n_c - 1 : limit_lane) - 32 * hc - 4 * static_cast<int>(lanex / 32);
       if (hc + 1 >= 2 * cache_tiles) next_masked = chunk_masked;
 #pragma unroll
-      for (int x = 0; x < 16; ++x)
-        if (8 * (x / 4) + (x % 4) > lim_rel) s_cur[x] = -INFINITY;
+      for (int x = 0; x < 16; ++x) s_cur[x] = minus_inf_if_negative(lim_rel - (8 * (x / 4) + (x % 4)), s_cur[x]);
       mx_cur = s_cur[0];
 #pragma unroll
       for (int x = 1; x < 16; ++x) mx_cur = fmaxf(mx_cur, s_cur[x]);
@@ -800,11 +817,11 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
 
   // ---- first requests: K 0, the query rows | V 0, K 1 (the first two are waited for first) ----
   Stream sk, sv;
-  auto k_to_chunk = [&] { enter(sk, k_rs_chunk, k_ss_chunk, a.c); };  // in front of tile cache_tiles
-  auto v_to_chunk = [&] { enter(sv, v_rs_chunk, v_ss_chunk, a.c); };
+  auto k_to_chunk = [&] { enter(sk, k_rs_chunk, a.k_chunk, a.c); };  // in front of tile cache_tiles
+  auto v_to_chunk = [&] { enter(sv, v_rs_chunk, a.v_chunk, a.c); };
   if (cache_tiles > 0) {
-    enter(sk, k_rs_cache, k_ss_cache, n_c);
-    enter(sv, v_rs_cache, v_ss_cache, n_c);
+    enter(sk, k_rs_cache, a.k_cache, n_c);
+    enter(sv, v_rs_cache, a.v_cache, n_c);
   } else {
     k_to_chunk();
     v_to_chunk();
@@ -819,8 +836,8 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
     const int q_ss2 = a.q.ss;
     const i32x4 q_rs = buffer_words(unit(a.q, h), (rows - 1) * q_ss2 + 2 * D);
     const uint32_t q_lds = lds_addr(q_t);
-    int r_in = lane / T::kSegs, seg16 = ((lane % T::kSegs) ^ Y::swz(lane / T::kSegs)) * 16;
-    hide_loop_invariance(r_in, seg16);
+    const uint32_t lanex = formed_here(lane);
+    const int r_in = lanex / T::kSegs, seg16 = ((lanex % T::kSegs) ^ Y::swz(lanex / T::kSegs)) * 16;
 #pragma unroll
     for (int i = 0; i < 32 / kR; ++i) {
       const int row = min(row0 + kR * i + r_in, rows - 1);  // rows past the end repeat the last one; never stored
@@ -958,14 +975,13 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   const int out_ss = a.out.ss;
   const __amdgpu_buffer_rsrc_t out_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(unit(a.out, h)), 0,
                                                                           (rows - 1) * out_ss + 2 * D, kBufferFlags);
-  int colx = col, lanex = lane;
-  hide_loop_invariance(colx, lanex);  // offsets are formed here, per row block, not kept in registers
+  const uint32_t lanex = formed_here(lane), colx = ROTATE_Q ? lanex % 32 : formed_here(col), grpx = ROTATE_Q ? lanex / 32 : grp;
   // Each wave parks its 32 x D tile in its own part of the tile buffers (free after the barrier above; 16-byte
   // segments XOR-swizzled by the row: column-wise writes spread over the banks) and stores it back as whole rows.  A
   // lane and its partner l ^ 32 hold the two halves of every segment: a swap gives each of them whole segments.
   char* const o_tile = ring + wu * (32 * kRowBytes);
   char* const o_s = o_tile + colx * kRowBytes;
-  const int c_swz = static_cast<uint32_t>(colx) % T::kSegs;
+  const int c_swz = colx % T::kSegs;
   const float inv = 1.f / l_tot;
   float lse = (m_run + log2f(l_tot)) * kLn2;
   float zero = 0.f;  // NaN where an output of the lane is not finite
@@ -987,7 +1003,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       uint4 piece;  // segment 2 r + grp + D / 16 ip
       swap_halves(wd[0][0], wd[1][0], piece.x, piece.z);
       swap_halves(wd[0][1], wd[1][1], piece.y, piece.w);
-      *reinterpret_cast<uint4*>(o_s + ((2 * r + T::kSegs / 2 * ip + grp) ^ c_swz) * 16) = piece;
+      *reinterpret_cast<uint4*>(o_s + ((2 * r + T::kSegs / 2 * ip + grpx) ^ c_swz) * 16) = piece;
     }
   if constexpr (D == 64) {  // rows that are not finite once more, see attn_row.h; the query rows are still in q_t
     const uint64_t lanes = __ballot(zero != 0.f);
@@ -1003,24 +1019,24 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       for (; again != 0; again &= again - 1) {
         const int r = __builtin_ctz(again), t = row0 + r;
         if (t >= rows) break;
-        const float q_e = bf16_to_f32(*reinterpret_cast<const uint16_t*>(q_t + Y::at(r, lane / 8) + lane % 8 * 2));
+        const float q_e = bf16_to_f32(*reinterpret_cast<const uint16_t*>(q_t + Y::at(r, lanex / 8) + lanex % 8 * 2));
         float lse_r;
-        const float o = attn_row_64(q_e, n_c + (a.causal ? t : a.c - 1), a.scale, row_of(a.k_cache, a.k_chunk),
+        const float o = attn_row_64(q_e, n_c + t, a.scale, row_of(a.k_cache, a.k_chunk),
                                     row_of(a.v_cache, a.v_chunk), lse_r);
-        *reinterpret_cast<uint16_t*>(o_tile + r * kRowBytes + ((lane / 8) ^ (r % T::kSegs)) * 16 + lane % 8 * 2) =
+        *reinterpret_cast<uint16_t*>(o_tile + r * kRowBytes + ((lanex / 8) ^ (r % T::kSegs)) * 16 + lanex % 8 * 2) =
             static_cast<uint16_t>(pack_bf16x2(o, 0.f));
-        if (col == r && !(fabsf(lse) < INFINITY)) lse = lse_r;
+        if (static_cast<int>(colx) == r && !(fabsf(lse) < INFINITY)) lse = lse_r;
       }
       no_memory_motion();
     }
   }
-  const int t = row0 + col;
-  if (grp == 0 && t < rows) {
+  const int t = row0 + static_cast<int>(ROTATE_Q ? colx : col);
+  if (grpx == 0 && t < rows) {
     if (a.lse_cache != nullptr) a.lse_cache[row_id0 + t] = (m_snap + log2f(l_snap_tot)) * kLn2;
     if (a.lse != nullptr) a.lse[row_id0 + t] = lse;
   }
   const char* const o_r = o_tile + lanex * 16;  // row lanex / kSegs of a kR-row group
-  const int r_in = static_cast<uint32_t>(lanex) / T::kSegs, pos = static_cast<uint32_t>(lanex) % T::kSegs;
+  const int r_in = lanex / T::kSegs, pos = lanex % T::kSegs;
   static_assert((kR & (kR - 1)) == 0 && kR <= T::kSegs, "row kR i + r_in modulo kSegs is (kR i modulo kSegs) ^ r_in");
   const int seg16 = (pos ^ r_in) * 16, rows_left = rows - row0 - r_in;
   uint32_t at = static_cast<uint32_t>(row0 + r_in) * static_cast<uint32_t>(out_ss);
@@ -1054,8 +1070,7 @@ __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void att
 }
 
 // Brings the per-range (maximum, sum) pairs of a row, part[s * rows_total + row], to one normaliser,
-// left in part[row] as (log-sum-exp in the log2 domain, 1): a pair that the column-sum kernel reads like
-// any single range.  Done once per row here rather than by every workgroup of the column-sum launch
+// left in part[row] as (log-sum-exp in the log2 domain, 1).  Done once per row here rather than by every workgroup of the column-sum launch
 // (one per 256 keys), each of which walked the ranges with dependent loads in front of every chunk.
 __global__ __launch_bounds__(256) void merge_partials_kernel(float2* part, int key_splits, int64_t rows_total) {
   const int64_t row = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -1087,8 +1102,8 @@ constexpr int kColsumQRows = 128;   // query rows per LDS chunk
 // per compute unit need).
 template <int D, bool STEPWISE>
 __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims dm, View q, int rows, Segments ks,
-                                                                        int causal, const float* lse, int key_splits,
-                                                                        const float2* part, float* score) {
+                                                                        int causal, const float* norm, int norm_pitch,
+                                                                        float to_log2, float* score) {
   typedef Geo<D> T;
   constexpr int kPitchK = T::kPitchK;
   // two staging buffers of query rows and their normalisers (log2 domain, +inf for padding rows)
@@ -1130,7 +1145,6 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
     for (int i = 0; i < 16; ++i) acc[kt][i] = 0.f;
 
   const int total_rows = dm.G * rows;  // flattened (head in group, row)
-  const int64_t part_stride = static_cast<int64_t>(dm.B) * dm.L * dm.Hq * rows;
   // The rows of chunk c + 1 are requested (into registers) before the products of chunk c start and
   // written to the other buffer afterwards: one barrier per chunk, no exposed load latency.
   // A thread stages 16 bytes of rows st_row + kStageStep x of a chunk.  STEPWISE: every chunk lies inside one head
@@ -1168,21 +1182,7 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
       }
     }
     float v = INFINITY;  // padding rows contribute exp2(-inf) = 0
-    if (tid < kColsumQRows && f0 + tid < total_rows) {
-      const int64_t row_id = lse_row0 + f0 + tid;
-      if (part != nullptr) {  // merge the per-range (maximum, sum) pairs
-        float m = -INFINITY;
-        for (int s = 0; s < key_splits; ++s) m = fmaxf(m, part[s * part_stride + row_id].x);
-        float lsum = 0.f;
-        for (int s = 0; s < key_splits; ++s) {
-          const float2 ps = part[s * part_stride + row_id];
-          lsum += ps.y * exp2f(ps.x - m);
-        }
-        v = m + log2f(lsum);
-      } else {
-        v = lse[row_id] * kLog2e;
-      }
-    }
+    if (tid < kColsumQRows && f0 + tid < total_rows) v = norm[(lse_row0 + f0 + tid) * norm_pitch] * to_log2;
     lse_in = v;
   };
   request_chunk(0);
@@ -1509,10 +1509,10 @@ bool fits_i32(const View& v, int rows) {
 
 // Attention with output: one instance of the kernel.
 template <int D, int WAVES>
-hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, bool paired, View out,
-                            float* lse, float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+hipError_t attn_pipe_launch(const Dims& dm, View q, Segments ks, Segments vs, bool paired, View out, float* lse,
+                            float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
   const TaskShape ts = task_shape(dm.G, WAVES);
-  const int rows_per_block = ts.tiles_per_block * kRowsPerWave;
+  const int rows_per_block = ts.tiles_per_block * kRowsPerWave, rows = ks.c;
   AttnArgs a;
   a.q = unit_view(q, rows, D);
   a.out = unit_view(out, rows, D);
@@ -1520,10 +1520,8 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segme
   a.k_chunk = unit_view(ks.chunk, ks.c, D);
   a.v_cache = unit_view(vs.cache, vs.n_c, D);
   a.v_chunk = unit_view(vs.chunk, vs.c, D);
-  a.rows = rows;
   a.n_c = ks.n_c;
   a.c = ks.c;
-  a.causal = causal;
   a.q_heads = dm.Hq;
   a.log_heads = ts.heads_per_block == 4 ? 2 : ts.heads_per_block - 1;
   a.row_blocks = (rows + rows_per_block - 1) / rows_per_block;
@@ -1553,8 +1551,8 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, int rows, Segments ks, Segme
 }
 
 template <int D>
-hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
-                       float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View out, float* lse, float* lse_cache,
+                       hipStream_t st, int q_rope_pos0, float rope_base) {
   if (out.ptr == nullptr || (lse_cache != nullptr && ks.n_c < 1)) return hipErrorInvalidValue;
   if (!fits_i32(ks.cache, ks.n_c) || !fits_i32(ks.chunk, ks.c) || !fits_i32(vs.cache, vs.n_c) ||
       !fits_i32(vs.chunk, vs.c))
@@ -1570,13 +1568,13 @@ hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments v
   const auto workgroups = [&](int row_waves) {  // one row block each
     const TaskShape ts = task_shape(dm.G, row_waves);
     const int block_rows = ts.tiles_per_block * kRowsPerWave;
-    return static_cast<int64_t>((rows + block_rows - 1) / block_rows) * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L;
+    return static_cast<int64_t>((ks.c + block_rows - 1) / block_rows) * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L;
   };
   const int cus = compute_units();
   if (workgroups(4) <= cus)
-    return attn_pipe_launch<D, 4>(dm, q, rows, ks, vs, causal, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
-  const bool paired = causal != 0 && workgroups(8) > cus;
-  return attn_pipe_launch<D, 8>(dm, q, rows, ks, vs, causal, paired, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+    return attn_pipe_launch<D, 4>(dm, q, ks, vs, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+  const bool paired = workgroups(8) > cus;
+  return attn_pipe_launch<D, 8>(dm, q, ks, vs, paired, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
 // Partial (maximum, sum) pairs of every query row over `key_splits` ranges of the keys.
@@ -1591,9 +1589,10 @@ hipError_t lse_launch(const Dims& dm, View q, int rows, Segments ks, int key_spl
   return hipGetLastError();
 }
 
+// norm[row * norm_pitch]: the rows' normalisers; times to_log2 they are in the log2 domain.
 template <int D>
-hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
-                              int key_splits, const float2* part, float* score, hipStream_t st) {
+hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int causal, const float* norm, int norm_pitch,
+                         float to_log2, float* score, hipStream_t st) {
   const int n = ks.n_c + ks.c;
   constexpr int kKeysPerBlock = 32 * kColsumKeyTiles * kColsumWaves;
   dim3 grid((n + kKeysPerBlock - 1) / kKeysPerBlock, dm.Hkv, dm.B * dm.L);
@@ -1603,7 +1602,7 @@ hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int caus
   const auto kern = stepwise ? colsum_mfma_kernel<D, true> : colsum_mfma_kernel<D, false>;
   const hipError_t e = raise_lds_limit(stepwise ? limit_stepwise : limit_any, reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(kColsumWaves * 64), kLdsBytes, st, dm, q, rows, ks, causal, lse, key_splits, part,
+  hipLaunchKernelGGL(kern, grid, dim3(kColsumWaves * 64), kLdsBytes, st, dm, q, rows, ks, causal, norm, norm_pitch, to_log2,
                      score);
   return hipGetLastError();
 }
@@ -1639,23 +1638,23 @@ hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, flo
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return colsum_launch<D>(dm, q, rows, ks, /*causal=*/0, nullptr, 1, part, score, st);
+  return colsum_launch<D>(dm, q, rows, ks, /*causal=*/0, workspace, 2, 1.f, score, st);
 }
 
 }  // namespace
 
 bool mfma_path_supported(int dtype, const Dims& dm) { return dtype == CITRUS_BF16 && (dm.D == 64 || dm.D == 128); }
 
-hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
-                            float* lse, float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+hipError_t launch_attn_mfma(const Dims& dm, View q, Segments ks, Segments vs, View out, float* lse, float* lse_cache,
+                            hipStream_t st, int q_rope_pos0, float rope_base) {
   const auto launch = dm.D == 64 ? attn_launch<64> : attn_launch<128>;
-  return launch(dm, q, rows, ks, vs, causal, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+  return launch(dm, q, ks, vs, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
-hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
-                              int key_splits, const float2* part, float* score, hipStream_t st) {
+hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse, float* score,
+                              hipStream_t st) {
   const auto launch = dm.D == 64 ? colsum_launch<64> : colsum_launch<128>;
-  return launch(dm, q, rows, ks, causal, lse, key_splits, part, score, st);
+  return launch(dm, q, rows, ks, causal, lse, 1, kLog2e, score, st);
 }
 
 // Instruction score in two launches: partial log-sum-exp over ranges of key tiles (enough

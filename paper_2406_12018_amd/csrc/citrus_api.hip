@@ -163,7 +163,7 @@ citrus_status check_workspace(const citrus_config* c, const void* ws, size_t byt
 hipError_t run_colsum(const citrus_config* c, const Dims& dm, View q, int rows, Segments ks, int causal,
                       const float* lse, float* score, hipStream_t st) {
   if (mfma_path_supported(c->dtype, dm))
-    return launch_colsum_mfma(dm, q, rows, ks, causal, lse, 1, nullptr, score, st);
+    return launch_colsum_mfma(dm, q, rows, ks, causal, lse, score, st);
   return launch_colsum_f32(dm, q, rows, ks, causal, lse, score, st);
 }
 
@@ -176,8 +176,8 @@ citrus_status do_chunk_attn(const citrus_config* c, const Dims& dm, const citrus
                             const citrus_tensor& out, float* lse, float* lm_score, float* lse_cache, hipStream_t st,
                             int q_rope_pos0 = -1) {
   if (mfma_path_supported(c->dtype, dm)) {
-    CITRUS_TRY(hip_status(launch_attn_mfma(dm, make_view(q), ks.c, ks, vs, /*causal=*/1, make_view(out), lse, lse_cache, st,
-                                           q_rope_pos0, rope_base_of(c))));
+    CITRUS_TRY(hip_status(launch_attn_mfma(dm, make_view(q), ks, vs, make_view(out), lse, lse_cache, st, q_rope_pos0,
+                                           rope_base_of(c))));
   } else {
     if (q_rope_pos0 >= 0) return CITRUS_ERR_UNSUPPORTED;
     CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q), ks.c, ks, vs, /*causal=*/1, make_view(out), lse, st)));

@@ -46,16 +46,16 @@ hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments kseg, in
 
 // ---- bf16 MFMA kernels (head_dim 64 and 128: every bf16 configuration), attn_mfma.hip ----
 bool mfma_path_supported(int dtype, const Dims& dm);
+// The chunk's kseg.c query rows over [cache ; chunk], row t over candidates j <= n_c + t.
 // lse (optional): the rows' log-sum-exp (natural log).  lse_cache (optional, kseg.n_c > 0): the same over the cache
 // states alone, a by-product.
 // q_rope_pos0 >= 0: the query rows are given without rotary embedding and are
 // rotated to positions q_rope_pos0 + row inside the kernel, with the bits launch_rope would give.
-hipError_t launch_attn_mfma(const Dims& dm, View q, int rows, Segments kseg, Segments vseg, int causal, View out,
-                            float* lse, float* lse_cache, hipStream_t st, int q_rope_pos0 = -1,
-                            float rope_base = 0.f);
-// normaliser per row from lse (natural log) or, if part != NULL, merged from key_splits partial pairs
-hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments kseg, int causal, const float* lse,
-                              int key_splits, const float2* part, float* score, hipStream_t st);
+hipError_t launch_attn_mfma(const Dims& dm, View q, Segments kseg, Segments vseg, View out, float* lse, float* lse_cache,
+                            hipStream_t st, int q_rope_pos0 = -1, float rope_base = 0.f);
+// lse: the rows' normalisers (natural log)
+hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments kseg, int causal, const float* lse, float* score,
+                              hipStream_t st);
 // Most ranges of key tiles a two-launch score splits the keys of a row into (one workgroup per range).
 constexpr int kMaxKeySplits = 8;
 // Floats of scratch that cover every launch_instr_score_mfma call with at most `rows` query rows per head over
