@@ -66,21 +66,31 @@ def test_small_launches(shape, head_dim):
     assert torch.equal(out[:, -1:], alone), "the last layer alone"
 
 
-@pytest.mark.parametrize("layers", [1, 11], ids=["four_waves", "eight_waves"])
-def test_rotated_queries(layers):
+# layers, rows per step, budget: 33 and 65 rows make one and two row blocks of eight waves, 130 three (a pair and a rest);
+# budgets are the second step's cached states, most of them no multiple of a 64-key tile
+ROTATED = [(1, 33, 40), (11, 65, 40), (32, 65, 70), (16, 130, 100), (16, 130, 128)]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("layers,c,budget", ROTATED, ids=["four_waves", "eight_waves", "pairs", "pairs_and_a_rest", "whole_tiles"])
+def test_rotated_queries(layers, c, budget, head_dim):
     """Position shift: the kernels that rotate their query rows against the rotation as a call of its own."""
-    c = 65 if layers == 11 else 33
-    cfg = api.Config(batch=1, layers=layers, q_heads=32, kv_heads=8, head_dim=128, chunk_len=c, budget=40, instr_len=4,
+    print(f"rotated queries {layers} layers {c} rows budget {budget} head_dim {head_dim}", flush=True)
+    cfg = api.Config(batch=1, layers=layers, q_heads=32, kv_heads=8, head_dim=head_dim, chunk_len=c, budget=budget, instr_len=4,
                      position_shift=1)
-    q, k, v = rand((1, layers, 32, 2 * c, 128), 1), rand((1, layers, 8, 2 * c, 128), 2), rand((1, layers, 8, 2 * c, 128), 3)
-    qi, out, state = rand((2, 1, layers, 32, 4, 128), 4), torch.empty_like(q), api.DocumentState.allocate(cfg)
+    rows = 3 * c
+    q, k, v = rand((1, layers, 32, rows, head_dim), 1), rand((1, layers, 8, rows, head_dim), 2), rand((1, layers, 8, rows, head_dim), 3)
+    qi, out, state = rand((3, 1, layers, 32, 4, head_dim), 4), torch.empty_like(q), api.DocumentState.allocate(cfg)
     ws = api.alloc_workspace(cfg)
-    api.citrus_process_document(cfg, state, ws, doc=api.resident_doc(cfg, q, k, v, qi, out), max_chunks=1)
+    doc = api.resident_doc(cfg, q, k, v, qi, out)
+    api.citrus_process_document(cfg, state, ws, doc=doc, max_chunks=2)
     n_c = state.cache_len
+    assert n_c == budget
     kc, vc = state.k_cache[state.buffer_index].clone(), state.v_cache[state.buffer_index].clone()
-    api.citrus_process_document(cfg, state, ws, doc=api.resident_doc(cfg, q, k, v, qi, out), first_chunk=1)
+    api.citrus_process_document(cfg, state, ws, doc=doc, first_chunk=2)
     plain = api.Config(**{**cfg.__dict__, "position_shift": 0})
-    q_r = api.citrus_rope(cfg, q[..., c:, :].contiguous(), n_c)
-    k_r, kc_r = api.citrus_rope(cfg, k[..., c:, :].contiguous(), n_c), api.citrus_rope(cfg, kc, 0)
-    ref = api.citrus_chunk_attn(plain, q_r, kc_r, vc, n_c, k_r, v[..., c:, :].contiguous())
-    assert_close(np64(out[..., c:, :]), np64(ref), "bf16", "rotated queries")
+    last = slice(2 * c, None)
+    q_r = api.citrus_rope(cfg, q[..., last, :].contiguous(), n_c)
+    k_r, kc_r = api.citrus_rope(cfg, k[..., last, :].contiguous(), n_c), api.citrus_rope(cfg, kc, 0)
+    ref = api.citrus_chunk_attn(plain, q_r, kc_r, vc, n_c, k_r, v[..., last, :].contiguous())
+    assert torch.equal(out[..., last, :], ref)
