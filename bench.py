@@ -32,7 +32,7 @@ PEAK_HBM_GBS = 8000.0
 # HBM bytes per chunk-attention launch measured offline with rocprofv3 --pmc
 # (FETCH_SIZE and WRITE_SIZE runs, scaled by a copy kernel of known size); see
 # profiles/.  None until a measurement for that workload exists.
-MEASURED_TRAFFIC_BYTES = {"cfg2_mistral7b": 562.0e6}
+MEASURED_TRAFFIC_BYTES = {"cfg2_mistral7b": 574.5e6}
 
 
 class HipEvents:
@@ -260,7 +260,8 @@ def main():
                          "automatically when the resident document would not fit")
     ap.add_argument("--overlap", action="store_true",
                     help="single-cache modes: run selection and gather next to the chunk attention on a second stream "
-                         "(2-3 %% more tokens/s; the attention launch itself then shares the chip and takes 9 %% longer)")
+                         "(the attention launch shares the chip with them; measured 1 %% slower than one stream, "
+                         "equal to it with --graph)")
     ap.add_argument("--graph", action="store_true",
                     help="record one document's launches into a HIP graph and time its replays (resident documents); "
                          "the chunk-attention launch duration then comes from untimed eager documents")
@@ -483,7 +484,7 @@ def main():
         roofline_other.append(ent)
         roofline_other.append(hbm_entry("compact_kernel (K/V gather)", "a4", compact_ms, compact_by,
                                         "same events, around the gather launch"))
-        roofline_other.append({"kernel": "topk_regs{6,8,24}_kernel / topk_kernel (selection)", "step": "a3", "bound": "latency",
+        roofline_other.append({"kernel": "topk_regs_kernel / topk_kernel (selection)", "step": "a3", "bound": "latency",
                                "avg_launch_ms": round(sum(select_ms) / len(select_ms), 5),
                                "note": "a chain of barrier-separated LDS passes over a few KB per unit: no roofline fraction"})
 
@@ -510,8 +511,8 @@ def main():
                    "document (dense timing; not the document's own values)",
                    "streams": "selection + gather next to the chunk attention on a second stream" if overlap else "one",
                    "launch": "one HIP graph per document, replayed" if graph else "eager"},
-        "roofline": {"kernel": ("attn_pipe_kernel_w8_rotq + the rope launches of the step (the events bracket both)"
-                                if w.position_shift else "attn_pipe_kernel_w8 (chunk attention)"), "bound": "mfma",
+        "roofline": {"kernel": ("attn_pipe_kernel_rotq + the rope launches of the step (the events bracket both)"
+                                if w.position_shift else "attn_pipe_kernel (chunk attention)"), "bound": "mfma",
                      "achieved": round(achieved, 2), "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_MFMA_TFLOPS, 4),
                      "frac_of_measured_peak": (round(achieved / peaks["mfma_only_bf16_TFLOPs"], 4)

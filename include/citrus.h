@@ -465,8 +465,7 @@ int32_t citrus_resident_provider(void* user, int32_t chunk_index, void* hip_stre
  *                 modes (INSTR, SHARED) a step then runs its instruction score first, and its selection
  *                 and gather on side->stream NEXT TO its chunk attention on hip_stream: neither reads
  *                 what the other writes (the attention reads the current buffer of the pair and the
- *                 chunk, the gather writes the other buffer), and the gather's waves fit beside the
- *                 attention's on a compute unit.  fork_event orders the side stream behind the
+ *                 chunk, the gather writes the other buffer).  fork_event orders the side stream behind the
  *                 instruction score, join_event orders hip_stream behind the gather before the next
  *                 step; on return everything the call enqueued is ordered before later work on
  *                 hip_stream.  Results are bit-identical with and without it.  Phase events 6 and 7 are

@@ -1,7 +1,7 @@
 // bf16 MFMA kernels for head_dim 64 and 128 on gfx950 (CDNA4): templates over the head dimension.
 // (head_dim 64 ran on one-wavefront-per-row vector kernels before, whose serial chain of key loads and f32
 // multiply-adds reached 7 TFLOP/s: 8 layers of 32/8 heads, a document of 4096 tokens in chunks of 512, budget 768,
-// took 37.8 ms; on these kernels 0.93 ms, 0.81 with probabilities rounded to bf16.)
+// took 37.6 ms; on these kernels 0.93 ms, 0.81 with probabilities rounded to bf16.)
 //
 //  attn_pipe_kernel    flash-style chunk attention (Section 4.1 step 1; softmax
 //                      with the 1/sqrt(d_k) scaling of Eq. (1)): online softmax
@@ -206,8 +206,10 @@ __device__ inline void lds_writes_and_barrier() { asm volatile("s_waitcnt lgkmcn
 // inside a row, segment seg (16 bytes) is at position seg ^ (kStep x (row / kRowStep % 4)), and blocks are 16 bytes
 // further apart than they are long.  The XOR touches two bits of the segment only, so the operand reads of a lane need
 // four (K) and two (V) base registers, and every address in the key loop is one of them plus a constant: no instruction
-// of the loop forms an address.  Sixteen consecutive rows of one segment (a cycle of a key operand) and four rows of two
-// segments (a 16-lane group of a transpose read) fall into different banks.
+// of the loop forms an address.  Sixteen consecutive rows of one segment (a cycle of a key operand) fall into different
+// banks, and so do the four rows of two segments of a 16-lane group of a transpose read; but two such groups go through
+// the LDS at a time, and at head_dim 128 rows r and r ^ 2 of the two meet in the same banks: two extra LDS cycles per
+// transpose read (SQ_LDS_BANK_CONFLICT, 31 % of the cycles the LDS works, which is 41 % of the launch's).
 template <int D>
 struct Lay {
   static constexpr int kR = Geo<D>::kRowsPerLoad;
@@ -477,19 +479,19 @@ struct AttnArgs {
 // K tiles are fetched one 64-key tile further ahead than V tiles; one barrier per 64 keys.
 //
 // What bounds it.  A wave issues at most one instruction, of whatever kind, per 8 cycles (measured: 64 independent
-// v_fma, v_max or s_mov of one wave take 505 to 540 cycles, of two waves of a SIMD the same), so a half step costs a wave
-// 8 cycles per instruction next to the 512 its 16 MFMAs hold the matrix pipe.  The steady half step is therefore kept at
-// 112 to 114 instructions (it had 159 to 190): LDS addresses are register + constant (Lay), a tile lies in one segment
-// and is always fetched (out-of-range rows read as zeros), masks and segment changes sit behind branches that are not
-// taken, the vote on the row maxima is taken a step early, and one wait covers all operands of a product.  Outside the
-// loop it is the same count: set-up from host-made numbers (AttnArgs), output rows through buffer stores.  The two waves
-// of a SIMD meet at a barrier every 64 keys; one of the two (waves 4..7) passes it in front of its vector-only tail, the
-// other behind it, so that their MFMA phases alternate instead of colliding.
-// Measured, 32/8 heads, 512 rows over 768 + 512 states: 64-key tile 3750 -> 3090 cycles (2048 of them MFMA); 32 layers in
-// one launch 330 -> 305 us inside a loop with other kernels, 341 -> 318 us back to back (the chip then clocks at 1.75
-// instead of 2.4 GHz: it is power that bounds a full chip); empty cache 141 -> 128 us; 16 layers of 32/32 heads, 1024
-// rows over 1024 + 1024 states 493 -> 451 us; 64/8 heads, 2048 rows over 4096 + 2048 states 1286 -> 1227 us; head_dim 64,
-// 8 layers 54 -> 49 us.
+// v_fma, v_max or s_mov of one wave take 505 to 540 cycles, of two waves of a SIMD the same), next to the 32 that an MFMA
+// holds the matrix pipe.  A 64-key tile is therefore kept at 245 instructions per wave, 32 of them MFMAs: LDS addresses are
+// register + constant (Lay), a tile lies in one segment and is always fetched (out-of-range rows read as zeros), masks and
+// segment changes sit behind branches that are not taken, the vote on the row maxima is taken a step early, and one wait
+// covers all operands of a product.  Outside the loop it is the same count: set-up from host-made numbers (AttnArgs),
+// output rows through buffer stores.  The two waves of a SIMD meet at a barrier every 64 keys; one of the two (waves 4..7)
+// passes it in front of its vector-only tail, the other behind it, so that their MFMA phases alternate.
+// Counters over a document of 32 layers, 32/8 heads, 512 rows over up to 768 + 512 states: the matrix pipe is busy 51 % of
+// the cycles (44 % before), the vector port 45 %, waves wait for an issue slot 43 % and at a counter or barrier 23 % of
+// their time; 527 k cycles in 271 us are 1.94 GHz, the clock a loop of MFMAs alone runs at: power takes the other fifth.
+// Launches inside a loop with other kernels: 330 -> 305 us (steady state, 32 layers); empty cache 141 -> 128 us; back to
+// back 16 layers of 32/32 heads, 1024 rows over 1024 + 1024 states 493 -> 451 us; 64/8 heads, 2048 rows over 4096 + 2048
+// states 1286 -> 1227 us.  head_dim 64, two bf16 parts per probability: 8 layers of 32/8 heads back to back 59 us.
 template <int D, int WAVES, bool ROTATE_Q>
 __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   typedef Geo<D> T;

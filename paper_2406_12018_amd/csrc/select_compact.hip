@@ -269,7 +269,7 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
         eq_before += c;
       }
       if (i * THREADS + tid < n && key[i] == thr && eq_rank < need) keep_bits |= 1u << i;
-      __builtin_amdgcn_sched_barrier(0);  // one row's counts in registers at a time (see the register budget below)
+      __builtin_amdgcn_sched_barrier(0);  // one row's counts in registers at a time
     }
   }
 #pragma unroll
@@ -296,9 +296,8 @@ __device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_
   }
 }
 
-// Eight keys per thread (up to 2048 candidates) fit 32 registers with one wave per SIMD: next to two waves of the
-// chunk-attention kernel (240 registers each) a SIMD has 32 left, and with them these workgroups run beside an
-// attention launch (the second-stream form of the chunk loop) instead of waiting for a compute unit of their own.
+// (The instance with eight keys per thread takes 31 registers.  Two waves of the chunk-attention kernel leave a SIMD 16, so
+// on a second stream these workgroups wait for a compute unit of their own, as they do on the attention's stream.)
 template <int ITEMS, int THREADS, Scores FORM>
 __global__ __launch_bounds__(THREADS) void topk_regs_kernel(const float* score, int heads_to_sum, int n, int k, int forced,
                                                            int32_t* idx) {
