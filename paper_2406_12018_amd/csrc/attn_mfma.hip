@@ -1021,12 +1021,13 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       for (; again != 0; again &= again - 1) {
         const int r = __builtin_ctz(again), t = row0 + r;
         if (t >= rows) break;
-        const float q_e = bf16_to_f32(*reinterpret_cast<const uint16_t*>(q_t + Y::at(r, lanex / 8) + lanex % 8 * 2));
         float lse_r;
-        const float o = attn_row_64(q_e, n_c + t, a.scale, row_of(a.k_cache, a.k_chunk),
-                                    row_of(a.v_cache, a.v_chunk), lse_r);
-        *reinterpret_cast<uint16_t*>(o_tile + r * kRowBytes + ((lanex / 8) ^ (r % T::kSegs)) * 16 + lanex % 8 * 2) =
-            static_cast<uint16_t>(pack_bf16x2(o, 0.f));
+        const Floats8 o = attn_row_64(bf16x8_to_f32(*reinterpret_cast<const uint4*>(q_t + Y::at(r, lanex % 8))), n_c + t, a.scale,
+                                      row_of(a.k_cache, a.k_chunk), row_of(a.v_cache, a.v_chunk), lse_r);
+        if (lanex < 8)
+          *reinterpret_cast<uint4*>(o_tile + r * kRowBytes + (lanex ^ (r % T::kSegs)) * 16) =
+              make_uint4(pack_bf16x2(o.x[0], o.x[1]), pack_bf16x2(o.x[2], o.x[3]), pack_bf16x2(o.x[4], o.x[5]),
+                         pack_bf16x2(o.x[6], o.x[7]));
         if (static_cast<int>(colx) == r && !(fabsf(lse) < INFINITY)) lse = lse_r;
       }
       no_memory_motion();

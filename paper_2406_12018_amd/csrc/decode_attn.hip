@@ -183,7 +183,13 @@ __device__ __forceinline__ uint16_t final_element(const Dims& dm, const View& q,
         return [=](int j) { return j < n_c ? in_cache + j * ss_cache : in_chunk + (j - n_c) * ss_chunk; };
       };
       float lse;
-      value = attn_row_64(bf16_to_f32(unit_ptr(q, b, l, h)[d]), ks.n_c + ks.c - 1, dm.scale, row_of(ks), row_of(vs), lse);
+      const uint4 q_piece = reinterpret_cast<const uint4*>(unit_ptr(q, b, l, h))[d % 8];
+      const Floats8 o = attn_row_64(bf16x8_to_f32(q_piece), ks.n_c + ks.c - 1, dm.scale, row_of(ks), row_of(vs), lse);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {  // element d is number d % 8 of the lanes with piece d / 8
+        const float at = __shfl(o.x[x], d / 8, 64);
+        if (d % 8 == x) value = at;
+      }
     }
   }
   return static_cast<uint16_t>(pack_bf16x2(value, 0.f) & 0xffffu);
