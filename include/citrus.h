@@ -459,7 +459,9 @@ int32_t citrus_resident_provider(void* user, int32_t chunk_index, void* hip_stre
  *                 unless DUAL), 5 after the instruction score, 6 after the
  *                 selection, 7 after the compaction.  A NULL entry is skipped (every
  *                 recorded event costs a few microseconds of stream time).  For
- *                 per-phase timing only.
+ *                 per-phase timing only.  A selection and its gather are one launch where they can
+ *                 be, and those of DUAL's two caches one launch behind the instruction score, unless
+ *                 an event that lies between them is asked for.
  * side            optional (NULL: every launch goes to hip_stream in the order a1 .. a4).  A second stream
  *                 of the same device and two events, all created by the caller.  In the single-cache
  *                 modes (INSTR, SHARED) a step then runs its instruction score first, and its selection

@@ -1612,12 +1612,12 @@ hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int caus
 
 template <int D>
 hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, float* workspace, size_t workspace_floats,
-                              float* score, hipStream_t st) {
+                              float* score, hipStream_t st, ScoreSums* sums) {
   const int n = ks.n_c + ks.c;
   // a short text over a candidate set that a workgroup's registers can hold one row strip of: one product
   // per (row, key)
   if (instr_strip_supported(dm, q, rows, ks, workspace_floats))
-    return launch_instr_strip(dm, q, rows, ks, workspace, workspace_floats, score, st);
+    return launch_instr_strip(dm, q, rows, ks, workspace, workspace_floats, score, st, sums);
   // otherwise two passes over the keys; few query rows per KV group: one fused launch
   const int total_rows = dm.G * rows;
   const int tiles32 = (n + 31) / 32;
@@ -1669,9 +1669,9 @@ size_t instr_score_mfma_workspace_floats(const Dims& dm, int rows, int n) {
 }
 
 hipError_t launch_instr_score_mfma(const Dims& dm, View q, int rows, Segments ks, float* workspace,
-                                   size_t workspace_floats, float* score, hipStream_t st) {
+                                   size_t workspace_floats, float* score, hipStream_t st, ScoreSums* sums) {
   const auto launch = dm.D == 64 ? instr_score_launch<64> : instr_score_launch<128>;
-  return launch(dm, q, rows, ks, workspace, workspace_floats, score, st);
+  return launch(dm, q, rows, ks, workspace, workspace_floats, score, st, sums);
 }
 
 }  // namespace citrus

@@ -105,7 +105,7 @@ struct Scratch {
 
 // Workspace layout (all blocks kAlign-aligned).
 struct Workspace {
-  size_t lse_chunk, lse_instr, lse_cache, score, score_lm, idx, idx_lm, iota, decode, k_rot, k_rot_lm, q_rot, qi_rot, total;
+  size_t lse_chunk, lse_instr, lse_cache, score, score_lm, idx, idx_lm, decode, k_rot, k_rot_lm, q_rot, qi_rot, total;
 };
 
 // A cache evicted by the document's own chunks exists (DUAL's second cache, or the only one of STANDARD)
@@ -137,7 +137,6 @@ Workspace workspace_layout(const citrus_config* c) {
   w.score_lm = off;  off += dual ? align_up(units_kv * n_max * sizeof(float)) : 0;
   w.idx = off;       off += align_up(units_kv * c->budget * sizeof(int32_t));
   w.idx_lm = off;    off += dual ? align_up(units_kv * c->budget_lm * sizeof(int32_t)) : 0;
-  w.iota = off;      off += align_up(c->chunk_len * sizeof(int32_t));
   {
     const Dims dm = dims_of(c);
     w.decode = off;  off += decode_mfma_supported(c->dtype, dm) ? align_up(decode_mfma_workspace_floats(dm) * sizeof(float)) : 0;
@@ -195,11 +194,13 @@ citrus_status do_chunk_attn(const citrus_config* c, const Dims& dm, const citrus
   return CITRUS_OK;
 }
 
+// sums (optional): the scores may be left as partial sums that it then describes.
 citrus_status do_instr_score(const citrus_config* c, const Dims& dm, const citrus_tensor& q_instr, Segments ks,
-                             Scratch scratch, float* score, hipStream_t st) {
+                             Scratch scratch, float* score, hipStream_t st, ScoreSums* sums = nullptr) {
   float* const lse_ws = scratch.ptr;
+  if (sums != nullptr) *sums = ScoreSums{score, 1};
   if (mfma_path_supported(c->dtype, dm))
-    return hip_status(launch_instr_score_mfma(dm, make_view(q_instr), c->instr_len, ks, lse_ws, scratch.floats, score, st));
+    return hip_status(launch_instr_score_mfma(dm, make_view(q_instr), c->instr_len, ks, lse_ws, scratch.floats, score, st, sums));
   View none{nullptr, 0, 0, 0, 0};
   // pass 1: row normalisers (log-sum-exp over all n candidates, no mask)
   CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q_instr), c->instr_len, ks, ks, /*causal=*/0, none, lse_ws, st)));
@@ -223,13 +224,14 @@ Segments cache_only(const citrus_tensor& cache, int cache_len) {
 // The cache is handed to the kernels as the only key segment.
 citrus_status do_cache_score(const citrus_config* c, const Dims& dm, const citrus_tensor& q, int rows,
                              const citrus_tensor& k_cache, int cache_len, const float* lse_given, Scratch scratch,
-                             float* score, hipStream_t st) {
+                             float* score, hipStream_t st, ScoreSums* sums = nullptr) {
   float* const lse_ws = scratch.ptr;
+  if (sums != nullptr) *sums = ScoreSums{score, 1};
   const Segments ks = cache_only(k_cache, cache_len);
   if (lse_given != nullptr)  // the normalisers are known: only the column sums are left
     return hip_status(run_colsum(c, dm, make_view(q), rows, ks, /*causal=*/0, lse_given, score, st));
   if (mfma_path_supported(c->dtype, dm))
-    return hip_status(launch_instr_score_mfma(dm, make_view(q), rows, ks, lse_ws, scratch.floats, score, st));
+    return hip_status(launch_instr_score_mfma(dm, make_view(q), rows, ks, lse_ws, scratch.floats, score, st, sums));
   View none{nullptr, 0, 0, 0, 0};
   CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q), rows, ks, ks, /*causal=*/0, none, lse_ws, st)));
   CITRUS_TRY(hip_status(run_colsum(c, dm, make_view(q), rows, ks, /*causal=*/0, lse_ws, score, st)));
@@ -247,8 +249,24 @@ citrus_status do_topk(const citrus_config* c, const float* score, int n, int k, 
 citrus_status do_compact(const citrus_config* c, const Dims& dm, Segments ks, Segments vs, const int32_t* idx,
                          int idx_pitch, int m, const citrus_tensor& k_new, const citrus_tensor& v_new,
                          hipStream_t st) {
-  return hip_status(launch_compact(elem_bytes(c->dtype), dm, ks, vs, idx, idx_pitch, sel_heads(c), m,
-                                   make_view(k_new), make_view(v_new), st));
+  return hip_status(launch_compact(elem_bytes(c->dtype), dm, ks, vs, idx, idx_pitch, sel_heads(c), m, /*appended=*/0,
+                                   make_view(k_new), make_view(v_new), nullptr, 0, nullptr, 0, st));
+}
+
+// May a selection and its gather be one launch?  Selections per KV head, over candidates a workgroup can hold.
+bool one_launch(const citrus_config* c, int n) { return c->select_mode == CITRUS_SELECT_PER_KV_HEAD && evict_in_one_launch(n); }
+
+// The two as launches of their own: layer-wise selections, more candidates, and callers that time them apart.  The scores
+// are in `score` (e.score.sums == 1).
+citrus_status do_select(const citrus_config* c, const Dims& dm, const Eviction& e, float* score, hipStream_t st) {
+  if (e.n < 1) return CITRUS_OK;
+  if (e.acc != nullptr) CITRUS_TRY(hip_status(launch_score_add(dm, score, e.acc, e.n, e.ks.n_c, e.acc_pitch, st)));
+  return do_topk(c, score, e.n, e.k, e.idx, st);
+}
+citrus_status do_gather(const citrus_config* c, const Dims& dm, const Eviction& e, hipStream_t st) {
+  const int kept = e.n < e.k ? e.n : e.k;
+  return hip_status(launch_compact(elem_bytes(c->dtype), dm, e.ks, e.vs, e.idx, e.k, sel_heads(c), kept, e.appended, e.k_new,
+                                   e.v_new, e.acc_new != nullptr ? e.score.ptr : nullptr, e.n, e.acc_new, e.acc_pitch, st));
 }
 
 // A dense [B, L, heads, rows, d] tensor at `ptr`.
@@ -310,11 +328,14 @@ citrus_status do_evict_cache(const citrus_config* cfg, const citrus_tensor& q, i
                              const citrus_tensor& v_cache, int cache_len, int k, const citrus_tensor& k_new,
                              const citrus_tensor& v_new, int32_t* idx, Scratch scratch, float* score, hipStream_t st) {
   const Dims dm = dims_of(cfg);
-  const int m = cache_len < k ? cache_len : k;
-  if (cache_len > k) CITRUS_TRY(do_cache_score(cfg, dm, q, rows, k_cache, cache_len, nullptr, scratch, score, st));
-  CITRUS_TRY(do_topk(cfg, score, cache_len, k, idx, st));
-  const Segments ks = cache_only(k_cache, cache_len), vs = cache_only(v_cache, cache_len);
-  return do_compact(cfg, dm, ks, vs, idx, k, m, k_new, v_new, st);
+  const bool fused = one_launch(cfg, cache_len);
+  Eviction e{cache_only(k_cache, cache_len), cache_only(v_cache, cache_len), {score, 1}, cache_len, k, cfg->start_size, 0,
+             idx, make_view(k_new), make_view(v_new), nullptr, nullptr, 0};
+  if (cache_len > k)
+    CITRUS_TRY(do_cache_score(cfg, dm, q, rows, k_cache, cache_len, nullptr, scratch, score, st, fused ? &e.score : nullptr));
+  if (fused) return hip_status(launch_evict(elem_bytes(cfg->dtype), dm, &e, 1, st));
+  CITRUS_TRY(do_select(cfg, dm, e, score, st));
+  return do_gather(cfg, dm, e, st);
 }
 
 // ---- device scratch that lives in the library's own image, for callers that cannot allocate ----
@@ -511,11 +532,10 @@ int32_t citrus_decode_step(const citrus_config* cfg, citrus_tensor q, citrus_ten
     return hip_status(launch_decode_mfma(dm, make_view(q), ks, vs, make_view(out),
                                          reinterpret_cast<float*>(ws + wl.decode), /*append_token=*/1, st));
   CITRUS_TRY(do_chunk_attn(cfg, dm, q, ks, vs, out, nullptr, nullptr, nullptr, st));
-  int32_t* one = reinterpret_cast<int32_t*>(ws + wl.iota);
-  CITRUS_TRY(hip_status(launch_iota(one, cache_len, 1, st)));
-  return hip_status(launch_compact(elem_bytes(cfg->dtype), dm, ks, vs, one, /*idx_pitch=*/0, /*idx_heads=*/1, 1,
+  return hip_status(launch_compact(elem_bytes(cfg->dtype), dm, ks, vs, nullptr, /*idx_pitch=*/0, /*idx_heads=*/1, /*kept=*/0,
+                                   /*appended=*/1,
                                    make_view(rows_from(k_cache, cache_len, cfg->dtype)),
-                                   make_view(rows_from(v_cache, cache_len, cfg->dtype)), st));
+                                   make_view(rows_from(v_cache, cache_len, cfg->dtype)), nullptr, 0, nullptr, 0, st));
 }
 
 int32_t citrus_score_accumulate(const citrus_config* cfg, float* score, int32_t n, const float* acc,
@@ -640,7 +660,6 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
   float* lse_chunk = reinterpret_cast<float*>(ws + wl.lse_chunk);
   const Scratch lse_instr{reinterpret_cast<float*>(ws + wl.lse_instr), score_scratch_floats(cfg, cfg->instr_len)};
   float* lse_cache = reinterpret_cast<float*>(ws + wl.lse_cache);
-  int32_t* iota_ws = reinterpret_cast<int32_t*>(ws + wl.iota);
   float* score = reinterpret_cast<float*>(ws + wl.score);
   float* score_lm = reinterpret_cast<float*>(ws + wl.score_lm);
   int32_t* idx_ws = reinterpret_cast<int32_t*>(ws + wl.idx);
@@ -660,6 +679,22 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       (void)hipEventRecord(static_cast<hipEvent_t>(phase_events[step * CITRUS_EVENTS_PER_STEP + phase]), stream);
   };
   auto mark = [&](int step, int phase) { mark_on(st, step, phase); };
+  // Is event `phase` of this step, which lies between two launches that can be one, asked for?  Then they stay apart.
+  auto timed = [&](int phase) {
+    return phase_events != nullptr && phase_events[done * CITRUS_EVENTS_PER_STEP + phase] != nullptr;
+  };
+  // Selection and gather of one cache; `phase` is the event between them.
+  auto evict = [&](const Eviction& e, float* scores, bool fused, int phase, hipStream_t stream) -> citrus_status {
+    if (fused) {
+      CITRUS_TRY(hip_status(launch_evict(elem_bytes(cfg->dtype), dm, &e, 1, stream)));
+    } else {
+      CITRUS_TRY(do_select(cfg, dm, e, scores, stream));
+      mark_on(stream, done, phase);
+      CITRUS_TRY(do_gather(cfg, dm, e, stream));
+    }
+    mark_on(stream, done, phase + 1);
+    return CITRUS_OK;
+  };
 
   // One step of a cache that the document's own chunks evict (Section 4.1): the second cache of DUAL, the
   // only cache of STANDARD.  Marks phases 1..4.
@@ -671,7 +706,8 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
     float* score;
     int32_t* idx;  // where this step's selection goes (pitch = budget)
   };
-  auto chunk_evicted_step = [&](const ChunkEvicted& t, const citrus_chunk_io& io_in, int c) -> citrus_status {
+  // later (optional): the step's eviction is left to the caller, who makes it one launch with another.
+  auto chunk_evicted_step = [&](const ChunkEvicted& t, const citrus_chunk_io& io_in, int c, Eviction* later) -> citrus_status {
     const int n_old = *t.len, from = *t.cur, to = from ^ 1;
     const Segments kl = segments(t.k[from], n_old, io_in.k, c), vl = segments(t.v[from], n_old, io_in.v, c);
     // What the chunk's attention and its scores read.  With the position shift: copies rotated to the
@@ -693,40 +729,31 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       kl_att = segments(k_rot, n_old, k_rot_chunk, c);
       k_cache_att = k_rot;
     }
+    int n_ranked = n_old + c;
     if (paper_order) {
       // the order Section 4.1 prints: encode the chunk given the cache (it still holds the whole previous
       // chunk), evict the cache by the chunk's attention to it, then put the chunk in
-      const int kept = n_old < t.budget ? n_old : t.budget;
       const bool evicts = n_old > t.budget;
       // the rows' normalisers over the cache alone come out of the attention launch
       CITRUS_TRY(do_chunk_attn(cfg, dm, io.q, kl_att, vl, io.out, nullptr, nullptr, evicts ? lse_cache : nullptr, st));
       mark(done, 1);
       if (evicts) CITRUS_TRY(do_cache_score(cfg, dm, io.q, c, k_cache_att, n_old, lse_cache, Scratch{nullptr, 0}, t.score, st));
-      mark(done, 2);
-      if (n_old > 0) CITRUS_TRY(do_topk(cfg, t.score, n_old, t.budget, t.idx, st));
-      mark(done, 3);
-      // kept cache states first, then the chunk's states behind them (positions n_old .. of the candidates)
-      if (kept > 0) CITRUS_TRY(do_compact(cfg, dm, kl, vl, t.idx, t.budget, kept, t.k[to], t.v[to], st));
-      CITRUS_TRY(hip_status(launch_iota(iota_ws, n_old, c, st)));
-      CITRUS_TRY(hip_status(launch_compact(elem_bytes(cfg->dtype), dm, kl, vl, iota_ws, /*idx_pitch=*/0,
-                                           /*idx_heads=*/1, c, make_view(rows_from(t.k[to], kept, cfg->dtype)),
-                                           make_view(rows_from(t.v[to], kept, cfg->dtype)), st)));
-      mark(done, 4);
-      *t.len = kept + c;
+      n_ranked = n_old;  // kept cache states first, then the chunk's states behind them
     } else {
       // the chunk attends over [cache ; chunk] and scores all of it itself; eviction in the same step
-      const int n_new = n_old + c;
-      const int kept = n_new < t.budget ? n_new : t.budget;
       CITRUS_TRY(do_chunk_attn(cfg, dm, io.q, kl_att, vl, io.out, lse_chunk, nullptr, nullptr, st));
       mark(done, 1);
       CITRUS_TRY(hip_status(run_colsum(cfg, dm, make_view(io.q), c, kl_att, /*causal=*/1, lse_chunk, t.score, st)));
-      mark(done, 2);
-      CITRUS_TRY(do_topk(cfg, t.score, n_new, t.budget, t.idx, st));
-      mark(done, 3);
-      CITRUS_TRY(do_compact(cfg, dm, kl, vl, t.idx, t.budget, kept, t.k[to], t.v[to], st));
-      mark(done, 4);
-      *t.len = kept;
     }
+    mark(done, 2);
+    const int kept = n_ranked < t.budget ? n_ranked : t.budget, appended = n_old + c - n_ranked;
+    const Eviction e{kl, vl, {t.score, 1}, n_ranked, t.budget, cfg->start_size, appended, t.idx, make_view(t.k[to]),
+                     make_view(t.v[to]), nullptr, nullptr, 0};
+    if (later != nullptr)
+      *later = e;
+    else
+      CITRUS_TRY(evict(e, t.score, one_launch(cfg, n_ranked) && !timed(3), 3, st));
+    *t.len = kept + appended;
     *t.cur = to;
     return CITRUS_OK;
   };
@@ -750,7 +777,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       // Standard CSE alone: the instruction takes no part in the encoding of the document
       int32_t* idx = idx_history ? idx_history + static_cast<size_t>(done) * units_sel * cfg->budget : idx_ws;
       const ChunkEvicted t{k_cache, v_cache, &n_c, &cur, cfg->budget, score, idx};
-      if ((status = chunk_evicted_step(t, io, c)) != CITRUS_OK) break;
+      if ((status = chunk_evicted_step(t, io, c, nullptr)) != CITRUS_OK) break;
       for (int p = 5; p <= 7; ++p) mark(done, p);
       continue;
     }
@@ -785,21 +812,14 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       ks_att = segments(k_rot, n_c, k_rot_chunk, c);
     }
     int32_t* idx = idx_history ? idx_history + static_cast<size_t>(done) * units_sel * cfg->budget : idx_ws;
-    // instruction score, selection and gather of the instruction (or only) cache; the last two on `sel_st`
+    const bool fused = one_launch(cfg, n) && !timed(6);
+    Eviction own{ks, vs, {score, 1}, n, cfg->budget, cfg->start_size, 0, idx, make_view(k_cache[cur ^ 1]),
+                 make_view(v_cache[cur ^ 1]), accumulated ? acc_score[cur] : nullptr, accumulated ? acc_score[cur ^ 1] : nullptr,
+                 cfg->cache_capacity};
+    // instruction score of the instruction (or only) cache
     auto score_step = [&]() -> citrus_status {
-      CITRUS_TRY(do_instr_score(cfg, dm, qi_att, ks_att, lse_instr, score, st));
-      if (accumulated) CITRUS_TRY(hip_status(launch_score_add(dm, score, acc_score[cur], n, n_c, cfg->cache_capacity, st)));
+      CITRUS_TRY(do_instr_score(cfg, dm, qi_att, ks_att, lse_instr, score, st, fused ? &own.score : nullptr));
       mark(done, 5);
-      return CITRUS_OK;
-    };
-    auto select_gather_step = [&](hipStream_t sel_st) -> citrus_status {
-      CITRUS_TRY(do_topk(cfg, score, n, cfg->budget, idx, sel_st));
-      mark_on(sel_st, done, 6);
-      CITRUS_TRY(do_compact(cfg, dm, ks, vs, idx, cfg->budget, m, k_cache[cur ^ 1], v_cache[cur ^ 1], sel_st));
-      if (accumulated)
-        CITRUS_TRY(hip_status(launch_score_gather(dm, score, idx, acc_score[cur ^ 1], n, m, cfg->budget, sel_heads(cfg),
-                                                  cfg->cache_capacity, sel_st)));
-      mark_on(sel_st, done, 7);
       return CITRUS_OK;
     };
     if (overlap) {
@@ -809,7 +829,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       // From here on the side stream may hold work of this step.  Whatever fails below, hip_stream is ordered
       // behind that work before the call returns: the next step, and whatever the caller enqueues after the
       // call, reads the buffer the gather fills.
-      status = select_gather_step(st_side);
+      status = evict(own, score, fused, 6, st_side);
       const hipError_t joined = hipEventRecord(static_cast<hipEvent_t>(side->join_event), st_side);
       if (status == CITRUS_OK) {
         status = do_chunk_attn(cfg, dm, q_att, ks_att, vs, io.out, nullptr, nullptr, nullptr, st, q_rope_pos0);
@@ -824,10 +844,13 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       }
       if (status != CITRUS_OK) break;
     } else {
+      Eviction lm;
+      bool together = false;  // DUAL: the two caches' evictions share a launch
       if (dual) {
         int32_t* idx_lm = idx_history_lm ? idx_history_lm + static_cast<size_t>(done) * units_sel * cfg->budget_lm : idx_lm_ws;
         const ChunkEvicted t{k_cache_lm, v_cache_lm, &n_c_lm, &cur_lm, cfg->budget_lm, score_lm, idx_lm};
-        if ((status = chunk_evicted_step(t, io, c)) != CITRUS_OK) break;
+        together = fused && one_launch(cfg, n_c_lm + c) && !timed(3) && !timed(4) && !timed(5);
+        if ((status = chunk_evicted_step(t, io, c, together ? &lm : nullptr)) != CITRUS_OK) break;
       } else {
         if ((status = do_chunk_attn(cfg, dm, q_att, ks_att, vs, io.out, nullptr, nullptr, nullptr, st, q_rope_pos0)) !=
             CITRUS_OK)
@@ -835,7 +858,14 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
         for (int p = 1; p <= 4; ++p) mark(done, p);
       }
       if ((status = score_step()) != CITRUS_OK) break;
-      if ((status = select_gather_step(st)) != CITRUS_OK) break;
+      if (together) {
+        const Eviction both[2] = {lm, own};
+        status = hip_status(launch_evict(elem_bytes(cfg->dtype), dm, both, 2, st));
+        mark(done, 7);
+      } else {
+        status = evict(own, score, fused, 6, st);
+      }
+      if (status != CITRUS_OK) break;
     }
     cur ^= 1;
     n_c = m;

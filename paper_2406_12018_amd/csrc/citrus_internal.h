@@ -33,6 +33,12 @@ struct Segments {
   int c;        // chunk rows
 };
 
+// Scores of B*L*Hkv units: candidate j of unit u has the sum over x < sums, in this order, of ptr[(u * sums + x) * n + j].
+struct ScoreSums {
+  const float* ptr;
+  int sums;
+};
+
 inline citrus_status hip_status(hipError_t e) { return e == hipSuccess ? CITRUS_OK : CITRUS_ERR_DEVICE; }
 
 // ---- vector kernels of the f32 mode, attn_generic.hip ----
@@ -64,8 +70,10 @@ constexpr int kMaxKeySplits = 8;
 size_t instr_score_mfma_workspace_floats(const Dims& dm, int rows, int n);
 // `workspace_floats`: what the block behind `workspace` holds; a kernel whose scratch does not fit is not
 // chosen, and hipErrorInvalidValue comes back if none fits.
+// sums (optional): what it points to is {score, 1}; a kernel that forms partial sums per key may leave them in the
+// workspace and describe them there instead of adding them up to `score`.
 hipError_t launch_instr_score_mfma(const Dims& dm, View q, int rows, Segments kseg, float* workspace,
-                                   size_t workspace_floats, float* score, hipStream_t st);
+                                   size_t workspace_floats, float* score, hipStream_t st, ScoreSums* sums = nullptr);
 
 // compute units of the current device, looked up once per device (instr_strip.hip)
 int compute_units();
@@ -76,7 +84,7 @@ bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segmen
 // largest scratch any supported launch with at most `rows` rows and at most n keys writes (0: none is supported)
 size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n);
 hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments kseg, float* workspace, size_t workspace_floats,
-                              float* score, hipStream_t st);
+                              float* score, hipStream_t st, ScoreSums* sums = nullptr);
 
 // ---- bf16 MFMA decoding step (at most 32 query heads per KV head), decode_attn.hip ----
 bool decode_mfma_supported(int dtype, const Dims& dm);
@@ -128,15 +136,33 @@ inline hipError_t raise_lds_limit(LdsLimit& state, const void* kernel, int bytes
 // units = B*L*Hsel; score rows are [units*(per_layer?Hkv:1)] x n.
 hipError_t launch_topk(const float* score, int units, int heads_to_sum, int n, int k, int forced, int32_t* idx,
                        hipStream_t st);
-// p[i] = base + i for i < count
-hipError_t launch_iota(int32_t* p, int base, int count, hipStream_t st);
 // score [B*L*Hkv][n] += acc [B*L*Hkv][acc_pitch] on the first n_c candidates
 hipError_t launch_score_add(const Dims& dm, float* score, const float* acc, int n, int n_c, int acc_pitch,
                             hipStream_t st);
 // acc_new [B*L*Hkv][acc_pitch]: row r < m takes score[idx[r]] (idx as in launch_compact)
 hipError_t launch_score_gather(const Dims& dm, const float* score, const int32_t* idx, float* acc_new, int n, int m,
                                int idx_pitch, int idx_heads, int acc_pitch, hipStream_t st);
+// Output rows 0 .. kept - 1: the candidates idx names; behind them the last `appended` candidates in order.
+// acc_new (optional) [B*L*Hkv][acc_pitch]: row r < kept also takes score[idx[r]] of score [B*L*Hkv][n].
 hipError_t launch_compact(int elem_bytes, const Dims& dm, Segments kseg, Segments vseg, const int32_t* idx,
-                          int idx_pitch, int idx_heads, int m, View k_new, View v_new, hipStream_t st);
+                          int idx_pitch, int idx_heads, int kept, int appended, View k_new, View v_new,
+                          const float* score, int n, float* acc_new, int acc_pitch, hipStream_t st);
+
+// The eviction of one cache, a selection per KV head: of the first n candidates of [cache ; chunk] the k best stay, in
+// order, followed by the last `appended` candidates.
+struct Eviction {
+  Segments ks, vs;
+  ScoreSums score;  // not read while n <= k
+  int n, k, forced, appended;
+  int32_t* idx;     // optional, pitch k
+  View k_new, v_new;
+  const float* acc;  // optional: sums that the cache's states carry (added to their scores) ...
+  float* acc_new;    // ... and that the kept states take along; [B*L*Hkv][acc_pitch]
+  int acc_pitch;
+};
+// may launch_evict rank n candidates?
+bool evict_in_one_launch(int n);
+// One or two evictions in one launch.
+hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int count, hipStream_t st);
 
 }  // namespace citrus

@@ -439,7 +439,8 @@ constexpr int strip_lds_bytes() {
 }
 
 template <int ROW_TILES, int TPW>
-hipError_t strip_launch(const Dims& dm, View q, int rows, Segments ks, float* part, float* score, hipStream_t st) {
+hipError_t strip_launch(const Dims& dm, View q, int rows, Segments ks, float* part, float* score, hipStream_t st,
+                        ScoreSums* sums) {
   const int n = ks.n_c + ks.c;
   const int strips = (dm.G * rows + 32 * ROW_TILES - 1) / (32 * ROW_TILES);
   const int units = dm.B * dm.L * dm.Hkv;
@@ -451,6 +452,10 @@ hipError_t strip_launch(const Dims& dm, View q, int rows, Segments ks, float* pa
   hipLaunchKernelGGL(kern, dim3(units * strips), dim3(kThreads), lds, st, dm, q, rows, ks, strips, part);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (sums != nullptr) {  // the consumer adds the strips' columns itself
+    *sums = ScoreSums{part, 2 * strips};
+    return hipSuccess;
+  }
   const int64_t total = static_cast<int64_t>(units) * n;
   hipLaunchKernelGGL(strip_sum_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, st, part, strips, n,
                      total, score);
@@ -516,12 +521,12 @@ size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n) {
 }
 
 hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments ks, float* workspace, size_t workspace_floats,
-                              float* score, hipStream_t st) {
+                              float* score, hipStream_t st, ScoreSums* sums) {
   const int n = ks.n_c + ks.c;
   if (!instr_strip_supported(dm, q, rows, ks, workspace_floats)) return hipErrorInvalidValue;
-  if (n <= kStripMaxKeysShort && dm.G * rows > 32) return strip_launch<2, 5>(dm, q, rows, ks, workspace, score, st);
-  if (n <= kStripMaxKeysShort) return strip_launch<1, 5>(dm, q, rows, ks, workspace, score, st);
-  return strip_launch<1, 10>(dm, q, rows, ks, workspace, score, st);
+  if (n <= kStripMaxKeysShort && dm.G * rows > 32) return strip_launch<2, 5>(dm, q, rows, ks, workspace, score, st, sums);
+  if (n <= kStripMaxKeysShort) return strip_launch<1, 5>(dm, q, rows, ks, workspace, score, st, sums);
+  return strip_launch<1, 10>(dm, q, rows, ks, workspace, score, st, sums);
 }
 
 }  // namespace citrus

@@ -1,5 +1,7 @@
 // Selection (Eq. (2)-(3): keep the k highest importance scores) and compaction
 // (Eq. (3), (5): the evicted cache holds exactly the selected states).
+#include <algorithm>
+
 #include "citrus_internal.h"
 
 namespace citrus {
@@ -138,175 +140,185 @@ __device__ __forceinline__ int wave_prefix_sum(int v) {
   return v;
 }
 
-// The same selection for a unit whose keys fit the workgroup's registers (n <= ITEMS * THREADS): the scores
-// are read once (candidate i * THREADS + tid is item i of thread tid), the radix passes run on the registers, and
-// the ordered emission counts the kept candidates per row of THREADS candidates and wave in LDS; a candidate's
-// position is the sum of the counts in front of it.  Exactly the result of topk_kernel.
-//
-// What bounds it: a chain of dependent steps (a launch that writes the identity takes 3.2 us), so the chain is kept
-// short.  Every pass has a histogram of its own, cleared at the start, and every wave reads the whole histogram and
-// finds the bin by itself: one barrier per pass.  A pass whose bin is kept as a whole is the last one (scores
-// that differ need two or three of the four), and threshold-equal candidates are ranked only where some of them
-// are left out.
-// Measured against four passes of three barriers with a shuffled scan, kernel trace: 8 units of 1280 candidates 6.9 ->
-// 5.1 us, 128 units 8.1 -> 5.8 us.
-// How a workgroup forms the values it ranks: one head's scores, or the sums over a layer's heads.  The sums grow in head
-// order (unit_score), either for all of a thread's candidates at a time, with about 32 loads in flight, or one candidate
-// after the other, which waits for every load but needs no thread without a candidate.
+// How a workgroup forms the values it ranks: one head's scores, or sums of several rows of scores (a layer's heads, the
+// partial sums of a head).  The sums grow in row order (unit_score), either for all of a thread's candidates at a time,
+// with several rows' loads in flight, or one candidate after the other, which waits for every load but needs no thread
+// without a candidate.
 enum class Scores { kOneHead, kSumByHead, kSumByCandidate };
 
-template <int ITEMS, int THREADS, Scores FORM>
-__device__ __forceinline__ void topk_regs_body(const float* score, int heads_to_sum, int n, int k, int forced,
-                                               int32_t* idx) {
-  constexpr int WAVES = THREADS / 64, kBins = 256, kPasses = 4;
-  static_assert(THREADS >= kBins && ITEMS <= 32, "thread t < 256 clears bin t; one bit per item");
-  __shared__ __attribute__((aligned(16))) int hist[kPasses][kBins];
-  __shared__ int row_cnt[2][ITEMS][WAVES];
-  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid % 64, w = tid / 64;
-  const float* base = score + static_cast<int64_t>(unit) * heads_to_sum * n;
-  int32_t* out = idx + static_cast<int64_t>(unit) * k;
+// Radix passes of BITS bits: a large radix needs fewer passes, each a chain of dependent steps, and spreads the votes of
+// scores that share their exponents over more bins; every wave reads the whole histogram, which bounds it.
+template <int THREADS>
+struct Radix {
+  static constexpr int kBits = THREADS <= 256 ? 11 : 10;
+  static constexpr int kPasses = (32 + kBits - 1) / kBits;
+  static constexpr int kBins = 1 << kBits;
+  __host__ __device__ static constexpr int shift(int pass) { return 32 - kBits * (pass + 1) > 0 ? 32 - kBits * (pass + 1) : 0; }
+};
+__device__ __forceinline__ int padded(int j) { return j + (j >> 3); }  // candidates apart by 8 in different banks
 
-  if (n <= k) {  // nothing to evict: keep every candidate
-    for (int j = tid; j < n; j += THREADS) out[j] = j;
-    return;
-  }
+// LDS of a selection.
+template <int ITEMS, int THREADS>
+struct SelectLds {
+  alignas(16) int hist[Radix<THREADS>::kPasses][Radix<THREADS>::kBins];
+  uint32_t key[ITEMS * THREADS + ITEMS * THREADS / 8];
+  alignas(16) int total[2][THREADS / 64];
+};
 
-  if (tid < kBins) {
-#pragma unroll
-    for (int pass = 0; pass < kPasses; ++pass) hist[pass][tid] = 0;
-  }
-  uint32_t key[ITEMS];
+// The same selection for a unit whose keys fit the workgroup's registers (n <= ITEMS * THREADS).  The scores are read once;
+// the keys change hands through LDS so that a thread ranks consecutive candidates and the ordered emission is one prefix
+// sum over the threads.  Exactly the result of topk_kernel.
+//
+// base: the unit's [rows][n] values.  acc (optional): a candidate j < n_acc carries acc[j] from earlier steps, added
+// to its value.  n > k.  emit(position, candidate) is called once for each kept candidate.
+//
+// What bounds it: a chain of dependent steps (a launch that writes the identity takes 3.2 us), so the chain is kept
+// short.  Every pass has a histogram of its own, cleared at the start, and every wave finds the bin by itself: one barrier
+// per pass.  A pass whose bin is kept as a whole is the last one (scores that differ need two), and
+// threshold-equal candidates are ranked only where some of them are left out.
+template <int ITEMS, int THREADS, Scores FORM, typename Emit>
+__device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS>& lds, const float* base, int rows, int n, int k,
+                                               int forced, const float* acc, int n_acc, Emit&& emit) {
+  typedef Radix<THREADS> R;
+  constexpr int WAVES = THREADS / 64, kLaneBins = R::kBins / 64, kRowsInFlight = 8;
+  static_assert(ITEMS <= 32, "one bit per item");
+  const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
+
+  // ---- keys: read in the scores' order, handed over through LDS ----
+  auto put = [&](int j, float value) {
+    if (j < n) lds.key[padded(j)] = j < forced ? 0xffffffffu : order_key(value);
+  };
   if constexpr (FORM == Scores::kSumByHead) {
     float sum[ITEMS];
+    for (int g0 = 0; g0 < rows; g0 += kRowsInFlight) {
+      float v[kRowsInFlight][ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) sum[i] = base[min(i * THREADS + tid, n - 1)];
-#pragma unroll(ITEMS <= 2 ? 16 : 4)
-    for (int g = 1; g < heads_to_sum; ++g) {
-      const float* head = base + static_cast<int64_t>(g) * n;
+      for (int x = 0; x < kRowsInFlight; ++x)
 #pragma unroll
-      for (int i = 0; i < ITEMS; ++i) sum[i] += head[min(i * THREADS + tid, n - 1)];
+        for (int i = 0; i < ITEMS; ++i)
+          v[x][i] = base[static_cast<int64_t>(min(g0 + x, rows - 1)) * n + min(i * THREADS + tid, n - 1)];
+#pragma unroll
+      for (int x = 0; x < kRowsInFlight; ++x)
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+          if (x == 0)
+            sum[i] = g0 == 0 ? v[0][i] : sum[i] + v[0][i];
+          else
+            sum[i] = g0 + x < rows ? sum[i] + v[x][i] : sum[i];
+        }
+    }
+    if (acc != nullptr) {
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i)
+        if (i * THREADS + tid < n_acc) sum[i] += acc[i * THREADS + tid];
     }
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) key[i] = i * THREADS + tid < forced ? 0xffffffffu : order_key(sum[i]);
+    for (int i = 0; i < ITEMS; ++i) put(i * THREADS + tid, sum[i]);
   } else {
+    float value[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
       const int j = i * THREADS + tid;
-      key[i] = j < n ? unit_key(base, FORM == Scores::kOneHead ? 1 : heads_to_sum, n, forced, j) : 0u;
+      value[i] = j < n ? unit_score(base, FORM == Scores::kOneHead ? 1 : rows, n, j) : 0.f;
     }
+    if (acc != nullptr) {
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i)
+        if (i * THREADS + tid < n_acc) value[i] += acc[i * THREADS + tid];
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) put(i * THREADS + tid, value[i]);
   }
+  for (int x = tid; x < R::kPasses * R::kBins / 4; x += THREADS)
+    reinterpret_cast<int4*>(&lds.hist[0][0])[x] = make_int4(0, 0, 0, 0);
   __syncthreads();
+  // thread t ranks candidates t * per .. t * per + per - 1
+  const int per = (n + THREADS - 1) / THREADS, j0 = tid * per, mine = min(per, n - j0);  // mine <= 0: none
+  uint32_t key[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) key[i] = i < mine ? lds.key[padded(j0 + i)] : 0u;
 
   uint32_t prefix = 0;  // bits of T fixed so far (high bits)
   int need = k;         // rank of T among the keys that match the prefix
   bool whole = false;   // every key that matches the prefix is kept
 #pragma unroll
-  for (int pass = 0; pass < kPasses; ++pass) {
+  for (int pass = 0; pass < R::kPasses; ++pass) {
     if (whole) break;  // block-uniform
-    const int shift = 24 - 8 * pass;
-    const uint32_t hi_mask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
+    const int shift = R::shift(pass);
+    const uint32_t hi_mask = pass == 0 ? 0u : 0xffffffffu << R::shift(pass - 1 < 0 ? 0 : pass - 1);
+    const uint32_t bin_mask = pass == 0 ? R::kBins - 1 : (1u << (R::shift(pass - 1 < 0 ? 0 : pass - 1) - shift)) - 1u;
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
-      if (i * THREADS + tid < n && (key[i] & hi_mask) == prefix) atomicAdd(&hist[pass][(key[i] >> shift) & 0xff], 1);
+      if (i < mine && (key[i] & hi_mask) == prefix) atomicAdd(&lds.hist[pass][(key[i] >> shift) & bin_mask], 1);
     __syncthreads();
-    // lane x holds the four bins from 4 (63 - x) up: the sum over the lanes in front counts the keys in higher bins
-    const int4 own = *reinterpret_cast<const int4*>(&hist[pass][4 * (63 - lane)]);
-    const int sum = own.x + own.y + own.z + own.w;
-    const int incl = wave_prefix_sum(sum);
-    const uint64_t hit = __ballot(incl - sum < need && need <= incl);  // exactly one lane: 1 <= need <= all keys
-    const int at = __builtin_ctzll(hit);
-    need -= __builtin_amdgcn_readlane(incl - sum, at);
-    int bin = 4 * (63 - at) + 3;
-    int in_bin = __builtin_amdgcn_readlane(own.w, at);
-    const int lower[3] = {own.z, own.y, own.x};
+    // lane x holds bins kLaneBins (63 - x) ..: the sum over the lanes in front counts the keys in higher bins.  The lanes
+    // take their pieces in different orders: neighbouring lanes' bins lie in the same banks.
+    const int4* const own = reinterpret_cast<const int4*>(&lds.hist[pass][kLaneBins * (63 - lane)]);
+    int sum = 0;
 #pragma unroll
-    for (int x = 0; x < 3; ++x)
-      if (need > in_bin) {
-        need -= in_bin;
-        --bin;
-        in_bin = __builtin_amdgcn_readlane(lower[x], at);
-      }
-    prefix |= static_cast<uint32_t>(bin) << shift;
-    whole = need == in_bin;
+    for (int x = 0; x < kLaneBins / 4; ++x) {
+      const int4 v = own[(x + lane) % (kLaneBins / 4)];
+      sum += v.x + v.y + v.z + v.w;
+    }
+    int incl = wave_prefix_sum(sum);
+    int at = __builtin_ctzll(__ballot(incl - sum < need && need <= incl));  // exactly one lane: 1 <= need <= all keys
+    need -= __builtin_amdgcn_readlane(incl - sum, at);
+    // the same within that lane's bins, one per lane, the highest first
+    const int top = kLaneBins * (63 - at) + kLaneBins - 1;
+    const int own1 = lane < kLaneBins ? lds.hist[pass][top - lane] : 0;
+    incl = wave_prefix_sum(own1);
+    at = __builtin_ctzll(__ballot(incl - own1 < need && need <= incl));
+    need -= __builtin_amdgcn_readlane(incl - own1, at);
+    prefix |= static_cast<uint32_t>(top - at) << shift;
+    whole = need == __builtin_amdgcn_readlane(own1, at);
   }
   // Keys above `thr` are kept; of the keys equal to it the first `need`.  Where the last bin is kept as a whole, thr
   // lies just below it (prefix > 0: all n > k keys match prefix 0 and lie in bins from 0 up).
   const uint32_t thr = whole ? prefix - 1u : prefix;
   if (whole) need = 0;
 
-  // set bits of a ballot below this lane (v_mbcnt: no per-lane mask to keep in registers)
-  auto lanes_below = [](uint64_t ballot) {
-    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(ballot >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(ballot), 0u)));
+  // candidates of the threads in front (list 0: threshold-equal ones, 1: kept ones)
+  auto in_front = [&](int list, int count) {
+    const int incl = wave_prefix_sum(count);
+    if (lane == 63) lds.total[list][w] = incl;
+    __syncthreads();
+    int before = incl - count;
+#pragma unroll
+    for (int x = 0; x < WAVES; ++x) {
+      const int c = lds.total[list][x];
+      before += x < w ? c : 0;
+    }
+    return before;
   };
-  // candidates of the same row and wave in front of this one (threshold-equal first, then kept): 0 .. 63, a byte each
-  uint32_t rank_in_row[(ITEMS + 3) / 4] = {};
-  auto set_rank = [&](int i, int r) { rank_in_row[i / 4] = (rank_in_row[i / 4] & ~(0xffu << (8 * (i % 4)))) | (static_cast<uint32_t>(r) << (8 * (i % 4))); };
-  auto get_rank = [&](int i) { return static_cast<int>((rank_in_row[i / 4] >> (8 * (i % 4))) & 0xffu); };
   uint32_t keep_bits = 0;
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i)
-    if (i * THREADS + tid < n && key[i] > thr) keep_bits |= 1u << i;
+    if (i < mine && key[i] > thr) keep_bits |= 1u << i;
   if (need > 0) {  // block-uniform: some, not all, of the threshold-equal candidates
+    uint32_t eq_bits = 0;
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      if (i * THREADS >= n) break;  // block-uniform
-      const bool eq = i * THREADS + tid < n && key[i] == thr;
-      const uint64_t ballot = __ballot(eq);
-      set_rank(i, lanes_below(ballot));
-      if (lane == 0) row_cnt[0][i][w] = __popcll(ballot);
-    }
-    __syncthreads();
-    int eq_before = 0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      if (i * THREADS >= n) break;
-      int eq_rank = eq_before + get_rank(i);
-#pragma unroll
-      for (int x = 0; x < WAVES; ++x) {
-        const int c = row_cnt[0][i][x];
-        if (x < w) eq_rank += c;
-        eq_before += c;
-      }
-      if (i * THREADS + tid < n && key[i] == thr && eq_rank < need) keep_bits |= 1u << i;
-      __builtin_amdgcn_sched_barrier(0);  // one row's counts in registers at a time
-    }
+    for (int i = 0; i < ITEMS; ++i)
+      if (i < mine && key[i] == thr) eq_bits |= 1u << i;
+    int left = need - in_front(0, __popc(eq_bits));
+    for (; eq_bits != 0 && left > 0; eq_bits &= eq_bits - 1, --left) keep_bits |= eq_bits & -eq_bits;
   }
+  int pos = in_front(1, __popc(keep_bits));
 #pragma unroll
-  for (int i = 0; i < ITEMS; ++i) {
-    if (i * THREADS >= n) break;  // block-uniform
-    const uint64_t ballot = __ballot((keep_bits >> i) & 1u);
-    set_rank(i, lanes_below(ballot));
-    if (lane == 0) row_cnt[1][i][w] = __popcll(ballot);
-  }
-  __syncthreads();
-  int kept_before = 0;
-#pragma unroll
-  for (int i = 0; i < ITEMS; ++i) {
-    if (i * THREADS >= n) break;
-    int pos = kept_before + get_rank(i);
-#pragma unroll
-    for (int x = 0; x < WAVES; ++x) {
-      const int c = row_cnt[1][i][x];
-      if (x < w) pos += c;
-      kept_before += c;
-    }
-    if (keep_bits & (1u << i)) out[pos] = i * THREADS + tid;
-    __builtin_amdgcn_sched_barrier(0);
-  }
+  for (int i = 0; i < ITEMS; ++i)
+    if (keep_bits & (1u << i)) emit(pos++, j0 + i);
 }
 
-// (The instance with eight keys per thread takes 31 registers.  Two waves of the chunk-attention kernel leave a SIMD 16, so
-// on a second stream these workgroups wait for a compute unit of their own, as they do on the attention's stream.)
 template <int ITEMS, int THREADS, Scores FORM>
 __global__ __launch_bounds__(THREADS) void topk_regs_kernel(const float* score, int heads_to_sum, int n, int k, int forced,
                                                            int32_t* idx) {
-  topk_regs_body<ITEMS, THREADS, FORM>(score, heads_to_sum, n, k, forced, idx);
-}
-
-__global__ void iota_kernel(int32_t* p, int base, int count) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) p[i] = base + i;
+  __shared__ SelectLds<ITEMS, THREADS> lds;
+  const float* base = score + static_cast<int64_t>(blockIdx.x) * heads_to_sum * n;
+  int32_t* out = idx + static_cast<int64_t>(blockIdx.x) * k;
+  if (n <= k) {  // nothing to evict: keep every candidate
+    for (int j = threadIdx.x; j < n; j += THREADS) out[j] = j;
+    return;
+  }
+  topk_regs_body<ITEMS, THREADS, FORM>(lds, base, heads_to_sum, n, k, forced, nullptr, 0, [&](int pos, int j) { out[pos] = j; });
 }
 
 // Accumulated scores: the sum a cache state carries is added to this step's score of the same candidate
@@ -331,52 +343,159 @@ __global__ __launch_bounds__(256) void score_gather_kernel(const float* score, c
   acc_new[u * acc_pitch + r] = score[u * n + j];
 }
 
-// Row gather: every thread moves 16 bytes of a K row and 16 bytes of a V row.
-template <int ROW_BYTES>
-__global__ __launch_bounds__(256) void compact_kernel(Dims dm, Segments ks, Segments vs, int elem_bytes,
-                                                      const int32_t* idx, int idx_pitch, int idx_heads, int m,
-                                                      View k_new, View v_new) {
-  constexpr int kLanesPerRow = ROW_BYTES / 16;
-  constexpr int kRowsPerBlock = 256 / kLanesPerRow;
-  const int g = blockIdx.y, b = blockIdx.z / dm.L, l = blockIdx.z % dm.L;
-  const int r = blockIdx.x * kRowsPerBlock + threadIdx.x / kLanesPerRow;
-  const int seg = threadIdx.x % kLanesPerRow;
-  if (r >= m) return;
-  const int gi = idx_heads == 1 ? 0 : g;
-  int j = idx[(static_cast<int64_t>(blockIdx.z) * idx_heads + gi) * idx_pitch + r];
-  j = max(0, min(j, ks.n_c + ks.c - 1));  // a bad index must never become an out-of-bounds read
-  const int64_t unit_cache_k = b * ks.cache.sb + l * ks.cache.sl + g * ks.cache.sh;
-  const int64_t unit_chunk_k = b * ks.chunk.sb + l * ks.chunk.sl + g * ks.chunk.sh;
-  const int64_t unit_cache_v = b * vs.cache.sb + l * vs.cache.sl + g * vs.cache.sh;
-  const int64_t unit_chunk_v = b * vs.chunk.sb + l * vs.chunk.sl + g * vs.chunk.sh;
-  const char* ksrc;
-  const char* vsrc;
-  if (j < ks.n_c) {
-    ksrc = static_cast<const char*>(ks.cache.ptr) + (unit_cache_k + static_cast<int64_t>(j) * ks.cache.ss) * elem_bytes;
-    vsrc = static_cast<const char*>(vs.cache.ptr) + (unit_cache_v + static_cast<int64_t>(j) * vs.cache.ss) * elem_bytes;
-  } else {
-    const int jc = j - ks.n_c;
-    ksrc = static_cast<const char*>(ks.chunk.ptr) + (unit_chunk_k + static_cast<int64_t>(jc) * ks.chunk.ss) * elem_bytes;
-    vsrc = static_cast<const char*>(vs.chunk.ptr) + (unit_chunk_v + static_cast<int64_t>(jc) * vs.chunk.ss) * elem_bytes;
-  }
-  char* kdst = static_cast<char*>(const_cast<void*>(k_new.ptr)) +
-               (b * k_new.sb + l * k_new.sl + g * k_new.sh + static_cast<int64_t>(r) * k_new.ss) * elem_bytes;
-  char* vdst = static_cast<char*>(const_cast<void*>(v_new.ptr)) +
-               (b * v_new.sb + l * v_new.sl + g * v_new.sh + static_cast<int64_t>(r) * v_new.ss) * elem_bytes;
-  const uint4 kv = reinterpret_cast<const uint4*>(ksrc)[seg];
-  const uint4 vv = reinterpret_cast<const uint4*>(vsrc)[seg];
-  reinterpret_cast<uint4*>(kdst)[seg] = kv;
-  reinterpret_cast<uint4*>(vdst)[seg] = vv;
+// ---- the eviction's gather ----
+// A tensor as the gathers address it: everything in bytes.
+struct ByteView {
+  char* ptr;
+  int64_t sb, sl, sh, ss;
+};
+inline ByteView byte_view(const View& v, int esize) {
+  return ByteView{static_cast<char*>(const_cast<void*>(v.ptr)), v.sb * esize, v.sl * esize, v.sh * esize, v.ss * esize};
+}
+__device__ inline char* unit_base(const ByteView& v, int b, int l, int g) { return v.ptr + (b * v.sb + l * v.sl + g * v.sh); }
+
+// The rows of one unit that a gather moves: candidate j < n_c is cache row j, else chunk row j - n_c; output row r.
+struct UnitRows {
+  const char *k_cache, *k_chunk, *v_cache, *v_chunk;
+  char *k_new, *v_new;
+  int64_t ks_cache, ks_chunk, vs_cache, vs_chunk, ks_new, vs_new;  // row strides
+  int n_c, n;  // cache rows, candidates
+};
+struct GatherViews {
+  ByteView k_cache, k_chunk, v_cache, v_chunk, k_new, v_new;
+  int n_c, n;
+  int log_lanes;  // log2 of the 16-byte pieces of a row
+};
+__device__ inline UnitRows unit_rows(const GatherViews& a, int b, int l, int g) {
+  return UnitRows{unit_base(a.k_cache, b, l, g), unit_base(a.k_chunk, b, l, g), unit_base(a.v_cache, b, l, g),
+                  unit_base(a.v_chunk, b, l, g), unit_base(a.k_new, b, l, g),   unit_base(a.v_new, b, l, g),
+                  a.k_cache.ss, a.k_chunk.ss, a.v_cache.ss, a.v_chunk.ss, a.k_new.ss, a.v_new.ss, a.n_c, a.n};
+}
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;  // stays in registers, where an array of the struct uint4 does not
+// 16 bytes (piece `seg`) of candidate j's key and value row
+__device__ inline void load_row(const UnitRows& u, int j, int seg, u32x4& kv, u32x4& vv) {
+  j = max(0, min(j, u.n - 1));  // a bad index must never become an out-of-bounds read
+  // both addresses, then the choice: a choice between fields would become a load of the chosen field
+  const char *const k_a = u.k_cache + j * u.ks_cache, *const k_b = u.k_chunk + (j - u.n_c) * u.ks_chunk;
+  const char *const v_a = u.v_cache + j * u.vs_cache, *const v_b = u.v_chunk + (j - u.n_c) * u.vs_chunk;
+  const bool cached = j < u.n_c;
+  kv = reinterpret_cast<const u32x4*>(cached ? k_a : k_b)[seg];
+  vv = reinterpret_cast<const u32x4*>(cached ? v_a : v_b)[seg];
+}
+__device__ inline void store_row(const UnitRows& u, int r, int seg, const u32x4& kv, const u32x4& vv) {
+  reinterpret_cast<u32x4*>(u.k_new + r * u.ks_new)[seg] = kv;
+  reinterpret_cast<u32x4*>(u.v_new + r * u.vs_new)[seg] = vv;
 }
 
-template <int ROW_BYTES>
-hipError_t compact_launch(int elem_bytes, const Dims& dm, Segments ks, Segments vs, const int32_t* idx,
-                          int idx_pitch, int idx_heads, int m, View k_new, View v_new, hipStream_t st) {
-  constexpr int kRowsPerBlock = 256 / (ROW_BYTES / 16);
-  dim3 grid((m + kRowsPerBlock - 1) / kRowsPerBlock, dm.Hkv, dm.B * dm.L);
-  hipLaunchKernelGGL((compact_kernel<ROW_BYTES>), grid, dim3(256), 0, st, dm, ks, vs, elem_bytes, idx, idx_pitch,
-                     idx_heads, m, k_new, v_new);
-  return hipGetLastError();
+// Row gather: every thread moves 16 bytes of a K row and of a V row.  Output row r < kept is candidate idx[r]; the rows
+// behind them are the candidates from append_from on.
+struct CompactArgs {
+  GatherViews v;
+  const int32_t* idx;
+  int idx_pitch, idx_heads, kept, rows, append_from, L;
+  // accumulated scores (optional): the kept states take their sums along
+  const float* score;
+  float* acc_new;
+  int n, acc_pitch;
+};
+__global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
+  const int g = blockIdx.y, b = blockIdx.z / a.L, l = blockIdx.z % a.L;
+  const int r = (blockIdx.x * 256 + threadIdx.x) >> a.v.log_lanes;
+  const int seg = threadIdx.x & ((1 << a.v.log_lanes) - 1);
+  if (r >= a.rows) return;
+  const int gi = a.idx_heads == 1 ? 0 : g;
+  const int j = r < a.kept ? a.idx[(static_cast<int64_t>(blockIdx.z) * a.idx_heads + gi) * a.idx_pitch + r] : a.append_from + r - a.kept;
+  const UnitRows u = unit_rows(a.v, b, l, g);
+  u32x4 kv, vv;
+  load_row(u, j, seg, kv, vv);
+  store_row(u, r, seg, kv, vv);
+  if (a.acc_new != nullptr && seg == 0 && r < a.kept) {
+    const int64_t unit = static_cast<int64_t>(blockIdx.z) * gridDim.y + g;
+    a.acc_new[unit * a.acc_pitch + r] = a.score[unit * a.n + max(0, min(j, a.n - 1))];
+  }
+}
+
+// Selection and gather of a step in one launch: one head's selection per (document, layer, KV head), cut into `parts`
+// workgroups that each repeat the selection and move `part_rows` of the rows it keeps.  Up to two evictions (the two
+// caches of DUAL) share a launch.
+// What bounds it: in small launches the chain arguments -> scores -> passes -> rows, four trips to memory of about 1 us
+// each and 1.5 us of passes; the launches it replaces (sum of partial scores, selection, gather) took at least 4.4 us each
+// whatever they did.  One layer of 32/8 heads, 1280 candidates, budget 768: 14.3 us in three launches, 9.0 in one.  Large
+// ones are bound by memory and take what two launches took (256 units: 39.8 us against 6.7 + 33.0).  A document with two
+// caches of 128 units each: 5147 -> 4944 us, four launches of a step in one.
+struct EvictJob {
+  GatherViews v;
+  const float* score;  // [units][sums][n]
+  int sums, n, k, forced;   // the candidates that are ranked
+  int kept, rows, append_from;  // output rows: the kept candidates, then candidates append_from ..
+  int parts, part_rows, L, Hkv;
+  int32_t* idx;        // optional, [units][k]
+  const float* acc;    // optional: sums of earlier steps, [units][acc_pitch]
+  float* acc_new;
+  int acc_pitch;
+};
+struct EvictArgs {
+  EvictJob job[2];
+  int first_blocks;  // workgroups of job 0
+};
+constexpr int kGatherRows = 4;  // rows of a thread in flight
+
+template <int ITEMS, int THREADS, Scores FORM>
+__global__ __launch_bounds__(THREADS) void evict_kernel(EvictArgs args) {
+  extern __shared__ int32_t sel[];  // the candidates of this part's kept rows
+  __shared__ SelectLds<ITEMS, THREADS> lds;
+  const bool second = static_cast<int>(blockIdx.x) >= args.first_blocks;
+  const EvictJob& a = args.job[second];
+  const int block = second ? blockIdx.x - args.first_blocks : blockIdx.x;
+  const int unit = block / a.parts, part = block - unit * a.parts;
+  const int r0 = part * a.part_rows, r1 = min(r0 + a.part_rows, a.rows), s1 = min(r1, a.kept);  // rows r0 .. s1 are selected
+  const int tid = threadIdx.x;
+  const int bl = unit / a.Hkv, g = unit - bl * a.Hkv, b = bl / a.L, l = bl - b * a.L;
+  const float* const base = a.score + static_cast<int64_t>(unit) * a.sums * a.n;
+  const float* const acc = a.acc != nullptr ? a.acc + static_cast<int64_t>(unit) * a.acc_pitch : nullptr;
+  if (r0 < s1) {  // block-uniform
+    if (a.n <= a.k) {
+      for (int r = r0 + tid; r < s1; r += THREADS) sel[r - r0] = r;
+    } else {
+      topk_regs_body<ITEMS, THREADS, FORM>(lds, base, a.sums, a.n, a.k, a.forced, acc, a.v.n_c, [&](int pos, int j) {
+        if (pos >= r0 && pos < s1) sel[pos - r0] = j;
+      });
+    }
+    __syncthreads();
+    if (a.idx != nullptr) {
+      int32_t* const out = a.idx + static_cast<int64_t>(unit) * a.k;
+      for (int r = r0 + tid; r < s1; r += THREADS) out[r] = sel[r - r0];
+    }
+    if (a.acc_new != nullptr) {
+      float* const out = a.acc_new + static_cast<int64_t>(unit) * a.acc_pitch;
+      for (int r = r0 + tid; r < s1; r += THREADS) {
+        const int j = sel[r - r0];
+        float s = unit_score(base, a.sums, a.n, j);
+        if (j < a.v.n_c) s += acc[j];
+        out[r] = s;
+      }
+    }
+  }
+  const UnitRows u = unit_rows(a.v, b, l, g);
+  const int seg = tid & ((1 << a.v.log_lanes) - 1), step = THREADS >> a.v.log_lanes;
+  for (int r = r0 + (tid >> a.v.log_lanes); r < r1; r += kGatherRows * step) {
+    u32x4 kv[kGatherRows], vv[kGatherRows];
+#pragma unroll
+    for (int x = 0; x < kGatherRows; ++x) {
+      const int rx = min(r + x * step, r1 - 1);
+      load_row(u, rx < a.kept ? sel[rx - r0] : a.append_from + rx - a.kept, seg, kv[x], vv[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < kGatherRows; ++x)
+      if (r + x * step < r1) store_row(u, r + x * step, seg, kv[x], vv[x]);
+  }
+}
+
+GatherViews gather_views(int elem_bytes, const Dims& dm, const Segments& ks, const Segments& vs, const View& k_new, const View& v_new) {
+  const int lanes = dm.D * elem_bytes / 16;  // 8, 16 or 32
+  return GatherViews{byte_view(ks.cache, elem_bytes), byte_view(ks.chunk, elem_bytes), byte_view(vs.cache, elem_bytes),
+                     byte_view(vs.chunk, elem_bytes), byte_view(k_new, elem_bytes),    byte_view(v_new, elem_bytes),
+                     ks.n_c, ks.n_c + ks.c, lanes == 8 ? 3 : lanes == 16 ? 4 : 5};
 }
 
 }  // namespace
@@ -418,11 +537,6 @@ hipError_t launch_topk(const float* score, int units, int heads_to_sum, int n, i
   return hipGetLastError();
 }
 
-hipError_t launch_iota(int32_t* p, int base, int count, hipStream_t st) {
-  hipLaunchKernelGGL(iota_kernel, dim3((count + 255) / 256), dim3(256), 0, st, p, base, count);
-  return hipGetLastError();
-}
-
 hipError_t launch_score_add(const Dims& dm, float* score, const float* acc, int n, int n_c, int acc_pitch,
                             hipStream_t st) {
   if (n_c <= 0) return hipSuccess;
@@ -439,14 +553,84 @@ hipError_t launch_score_gather(const Dims& dm, const float* score, const int32_t
 }
 
 hipError_t launch_compact(int elem_bytes, const Dims& dm, Segments ks, Segments vs, const int32_t* idx,
-                          int idx_pitch, int idx_heads, int m, View k_new, View v_new, hipStream_t st) {
-  const int row_bytes = dm.D * elem_bytes;
-  switch (row_bytes) {
-    case 128: return compact_launch<128>(elem_bytes, dm, ks, vs, idx, idx_pitch, idx_heads, m, k_new, v_new, st);
-    case 256: return compact_launch<256>(elem_bytes, dm, ks, vs, idx, idx_pitch, idx_heads, m, k_new, v_new, st);
-    case 512: return compact_launch<512>(elem_bytes, dm, ks, vs, idx, idx_pitch, idx_heads, m, k_new, v_new, st);
-    default: return hipErrorInvalidValue;
+                          int idx_pitch, int idx_heads, int kept, int appended, View k_new, View v_new,
+                          const float* score, int n, float* acc_new, int acc_pitch, hipStream_t st) {
+  CompactArgs a;
+  a.v = gather_views(elem_bytes, dm, ks, vs, k_new, v_new);
+  a.idx = idx;
+  a.idx_pitch = idx_pitch;
+  a.idx_heads = idx_heads;
+  a.kept = kept;
+  a.rows = kept + appended;
+  a.append_from = ks.n_c + ks.c - appended;
+  a.L = dm.L;
+  a.score = score;
+  a.n = n;
+  a.acc_new = acc_new;
+  a.acc_pitch = acc_pitch;
+  const int rows_per_block = 256 >> a.v.log_lanes;
+  hipLaunchKernelGGL(compact_kernel, dim3((a.rows + rows_per_block - 1) / rows_per_block, dm.Hkv, dm.B * dm.L), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+bool evict_in_one_launch(int n) { return n <= 6 * kWideThreads; }
+
+hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int count, hipStream_t st) {
+  if (count < 1 || count > 2) return hipErrorInvalidValue;
+  EvictArgs args;
+  const int units = dm.B * dm.L * dm.Hkv;
+  int blocks = 0, lds = 0, n_max = 0;
+  bool sums = false;
+  for (int x = 0; x < count; ++x) {
+    EvictJob& a = args.job[x];
+    a.v = gather_views(elem_bytes, dm, e[x].ks, e[x].vs, e[x].k_new, e[x].v_new);
+    a.score = e[x].score.ptr;
+    a.sums = e[x].score.sums;
+    a.n = e[x].n;
+    a.k = e[x].k;
+    a.forced = std::min(e[x].forced, e[x].k);
+    a.kept = std::min(e[x].n, e[x].k);
+    a.rows = a.kept + e[x].appended;
+    a.append_from = e[x].ks.n_c + e[x].ks.c - e[x].appended;
+    a.L = dm.L;
+    a.Hkv = dm.Hkv;
+    a.idx = e[x].idx;
+    a.acc = e[x].acc;
+    a.acc_new = e[x].acc_new;
+    a.acc_pitch = e[x].acc_pitch;
+    if (a.n > a.k) {
+      n_max = std::max(n_max, a.n);
+      sums = sums || a.sums > 1;
+    }
   }
+  // Workgroups of a job: two of 256 threads to a compute unit, one of 1024 (32 units of 6144 candidates, budget 4096, with
+  // 256 | 1024 workgroups of 1024 threads: 29 | 48 us; two caches of 128 units, 256 threads: 256 | 512 | 1024
+  // workgroups 4966 | 4944 | 5035 us a document), each with at least a wavefront's rows.
+  const bool wide = n_max > 8 * kSelThreads;
+  const int groups = wide ? compute_units() : 2 * compute_units();
+  for (int x = 0; x < count; ++x) {
+    EvictJob& a = args.job[x];
+    a.parts = std::min((a.rows + 15) / 16, (groups + units - 1) / units);
+    a.part_rows = (a.rows + a.parts - 1) / a.parts;
+    a.parts = (a.rows + a.part_rows - 1) / a.part_rows;
+    if (x == 0) args.first_blocks = units * a.parts;
+    blocks += units * a.parts;
+    lds = std::max(lds, static_cast<int>(std::min(a.part_rows, a.kept) * sizeof(int32_t)));
+  }
+  if (count == 1) args.job[1] = args.job[0];
+  constexpr Scores kOne = Scores::kOneHead, kSums = Scores::kSumByHead;
+  auto kern = sums ? evict_kernel<2, kSelThreads, kSums> : evict_kernel<2, kSelThreads, kOne>;
+  int threads = kSelThreads;
+  if (wide) {
+    kern = sums ? evict_kernel<6, kWideThreads, kSums> : evict_kernel<6, kWideThreads, kOne>;
+    threads = kWideThreads;
+  } else if (n_max > 5 * kSelThreads) {
+    kern = sums ? evict_kernel<8, kSelThreads, kSums> : evict_kernel<8, kSelThreads, kOne>;
+  } else if (n_max > 2 * kSelThreads) {
+    kern = sums ? evict_kernel<5, kSelThreads, kSums> : evict_kernel<5, kSelThreads, kOne>;
+  }
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), lds, st, args);
+  return hipGetLastError();
 }
 
 }  // namespace citrus
