@@ -27,62 +27,16 @@
 #include "attn_row.h"
 #include "bf16_math.h"
 #include "citrus_internal.h"
+#include "mfma_common.h"
 #include "rope_math.h"
 
 
 namespace citrus {
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) short i16x4;
-
 constexpr int kWaves = 4;               // one wave per SIMD and block; two or more blocks share a CU
 constexpr int kThreads = kWaves * 64;
 constexpr int kRowsPerWave = 32;        // one 32-query column tile per wave
-constexpr int kTileN = 64;              // keys per LDS tile
-constexpr int kXcds = 8;
-constexpr int kBufferFlags = 0x00020000;  // raw buffer resource word 3 on CDNA: 32-bit data format, no swizzle
-
-// Geometry of K/V tiles in LDS for one head dimension (64 or 128).  Rows are unpadded; the 16-byte segment `seg` of
-// tile row `row` lives at segment position seg ^ swz(row), which keeps both read patterns (key rows as an operand,
-// transpose reads of value columns) free of bank conflicts.  swz is linear under XOR in the row's bits, so the
-// swizzle of a sum of disjoint bit ranges is the XOR of their swizzles, and 16 rows leave it unchanged.
-//   128: a row spans the 256 bytes of a 16-byte read cycle: sixteen consecutive rows take sixteen positions.
-//   64:  two rows span them: eight rows of one parity take the eight positions of a row, and the four rows of a
-//        transpose read (8-byte pieces of two neighbouring segments each) fall into four different 32-byte pairs.
-template <int D>
-struct Geo {
-  static constexpr int kSegs = D / 8;                    // 16-byte segments of a row
-  static constexpr int kRowBytes = 2 * D;
-  static constexpr int kTileBytes = kTileN * kRowBytes;
-  static constexpr int kRowsPerLoad = 1024 / kRowBytes;  // rows one wave-level LDS-direct load moves
-  static constexpr int kKk = D / 16;                     // contraction steps of K.Q^T
-  static constexpr int kOut = D / 32;                    // 32-row tiles of O^T
-  // bf16 parts of a probability in P.V.  One (the probability rounded to bf16) at 128.  Two at 64, where the results keep
-  // the accuracy of f32 probabilities: what is left of their error is the rounding of the output (relative error
-  // against f64 over 512 rows x 1280 states 0.00166, of the rounded f64 result 0.00166, with one part 0.00234).
-  static constexpr int kParts = D == 64 ? 2 : 1;
-  static constexpr int kPitchK = D + 8;                  // padded row pitch (bf16) of query rows staged by ordinary writes
-  __device__ static constexpr int swz(int row) {
-    return D == 128 ? (2 * (row % 8)) ^ ((row / 8) % 2) : (2 * ((row / 2) % 4)) ^ ((row / 8) % 2) ^ (4 * (row % 2));
-  }
-};
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kMaxSlack = 8.0f;  // probabilities stay below 2^8: exact in f32, same relative rounding in bf16
-
-union Pack8 {
-  bf16x8 v;
-  uint4 u;
-  uint32_t w[4];
-  i16x4 h[2];
-};
-
-__device__ inline const uint16_t* unit_ptr(const View& v, int b, int l, int h) {
-  return static_cast<const uint16_t*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh);
-}
 
 // LDS transpose read (ds_read_b64_tr_b16).  Within each group of 16 lanes, lane s passes the
 // address of 4 consecutive bf16 and lane i receives element (i % 4) of lanes i/4, 4 + i/4,
@@ -99,7 +53,6 @@ __device__ inline i16x4 lds_read_tr16(const char* p) {
 // them, so the software-managed hazards are handled here: v_exp_f32 is followed by the one wait
 // state a non-transcendental consumer needs, and no vector instruction may read an MFMA result
 // sooner than the MFMA takes to complete (callers keep a whole MFMA group in between).
-typedef __attribute__((ext_vector_type(4))) int i32x4;
 __device__ inline f32x16 mfma_pinned_first(const bf16x8& a, const bf16x8& b) {  // accumulator starts at zero
   f32x16 d;
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0"
@@ -424,21 +377,6 @@ __global__ __launch_bounds__(kThreads, 2) void lse_mfma_kernel(Dims dm, View q, 
   }
 }
 
-// Division by a number that is known at launch: n / divisor for 0 <= n < 2^31 by a multiplication.
-struct FastDiv {
-  int divisor;
-  uint32_t mul;
-  int shift;
-  __device__ int quotient(int n) const {
-    return static_cast<int>((__umulhi(static_cast<uint32_t>(n), mul) + static_cast<uint32_t>(n)) >> shift);
-  }
-};
-inline FastDiv fast_div(int d) {
-  FastDiv f{d, 0, 0};
-  while ((int64_t{1} << f.shift) < d) ++f.shift;
-  f.mul = static_cast<uint32_t>(((uint64_t{1} << 32) * ((uint64_t{1} << f.shift) - d)) / d + 1);
-  return f;
-}
 // A tensor as the attention kernel addresses it: everything in bytes.
 struct UnitView {
   const char* ptr;
@@ -1262,23 +1200,6 @@ __global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims 
       const int j = j0 + 32 * kt + 8 * (i / 4) + 4 * grp + (i % 4);
       if (col == 0 && j < n) score[(static_cast<int64_t>(bl) * dm.Hkv + g) * n + j] = v;
     }
-}
-
-// Sum of 16 per-lane values over the 32 lanes that share lane / 32, in 16 exchanges: each step
-// halves the values a lane still carries (the lane keeps the half its own bit selects and takes
-// the partner's partial sum of the same half).  On return lane c holds, for value index c / 2,
-// the total over its 32 lanes.
-__device__ inline float reduce16_over32(const float (&v)[16], int col) {
-  float a[8], b[4], c[2];
-  const bool u16 = col & 16, u8 = col & 8, u4 = col & 4, u2 = col & 2;
-#pragma unroll
-  for (int x = 0; x < 8; ++x) a[x] = (u16 ? v[x + 8] : v[x]) + __shfl_xor(u16 ? v[x] : v[x + 8], 16, 64);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) b[x] = (u8 ? a[x + 4] : a[x]) + __shfl_xor(u8 ? a[x] : a[x + 4], 8, 64);
-#pragma unroll
-  for (int x = 0; x < 2; ++x) c[x] = (u4 ? b[x + 2] : b[x]) + __shfl_xor(u4 ? b[x] : b[x + 2], 4, 64);
-  const float d = (u2 ? c[1] : c[0]) + __shfl_xor(u2 ? c[0] : c[1], 2, 64);
-  return d + __shfl_xor(d, 1, 64);
 }
 
 // Instruction score (Eq. (1), summed form) in ONE launch for KV groups whose query rows

@@ -1,0 +1,46 @@
+"""The single-product instruction score at the edges of its instances: strips of 32 and 64 rows with a remainder, key tiles a wave
+does not have, caches that end inside a tile, more rows than one head's; against f64.
+
+Tolerance: a logit is a sum of D bf16 products in f32, off by at most D 2^-24 sum |q k|; with normal inputs sum |q k| is about
+0.64 D, which times scale and log2 e makes D = 128: 8e-5, D = 64: 3e-5 of a weight, and the sums over rows and keys keep it."""
+
+import pytest
+import torch
+
+import paper_2406_12018_amd as api
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+# layers, query heads, KV heads, rows, cache, chunk
+CASES = [
+    (1, 1, 1, 1, 0, 1),
+    (1, 2, 1, 16, 0, 33),        # one strip, one wave with a second tile
+    (1, 4, 2, 17, 31, 226),      # 68 rows; 257 keys; a cache that ends inside a tile
+    (1, 4, 1, 8, 1000, 280),     # 1280 keys
+    (1, 4, 1, 9, 1000, 281),     # 1281: ten tiles per wave
+    (1, 8, 2, 64, 2000, 560),    # 2560
+    (1, 8, 2, 64, 2000, 561),    # two passes
+    (5, 32, 8, 51, 300, 213),    # 204 rows: 32-row strips no longer fit side by side, 64-row strips with a rest of 12
+    (1, 64, 2, 128, 500, 37),    # 4096 rows per KV head
+    (1, 64, 2, 129, 500, 37),    # 4128: two passes
+    (40, 8, 8, 40, 100, 50),     # one head per KV head, 320 KV heads
+]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(x) for x in c))
+def test_scores_against_f64(case, head_dim):
+    L, Hq, Hkv, rows, n_c, c = case
+    print(f"strip scores {case} head_dim {head_dim}", flush=True)
+    g = torch.Generator(device="cpu").manual_seed(5)
+    mk = lambda *shape: torch.randn(shape, generator=g).to(torch.bfloat16).to(DEV)
+    q, kc, k = mk(1, L, Hq, rows, head_dim), mk(1, L, Hkv, n_c + 3, head_dim), mk(1, L, Hkv, c, head_dim)
+    cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=c, budget=n_c + 3, instr_len=rows)
+    ws = api.alloc_workspace(cfg)
+    score = api.citrus_instr_score(cfg, q, kc, n_c, k, workspace=ws)
+    assert torch.equal(score, api.citrus_instr_score(cfg, q, kc, n_c, k, workspace=ws))
+    keys = torch.cat([kc[:, :, :, :n_c], k], dim=3).double()
+    qs = q.double().reshape(1, L, Hkv, Hq // Hkv * rows, head_dim)
+    want = torch.softmax(torch.matmul(qs, keys.transpose(-1, -2).contiguous()) / head_dim ** 0.5, dim=-1).sum(dim=-2)
+    torch.testing.assert_close(score.double(), want, rtol=8e-5 if head_dim == 128 else 3e-5, atol=1e-7)
