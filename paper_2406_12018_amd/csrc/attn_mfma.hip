@@ -21,6 +21,7 @@
 // reductions are in-lane plus one exchange with lane l ^ 32, and the S^T
 // accumulators are directly the B operand (P^T) of the second product.
 #pragma clang diagnostic ignored "-Winline-asm"
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -29,6 +30,7 @@
 #include "citrus_internal.h"
 #include "mfma_common.h"
 #include "rope_math.h"
+#include "strip_score.h"
 
 
 namespace citrus {
@@ -104,7 +106,6 @@ __device__ inline uint32_t formed_here(uint32_t x) {
 __device__ inline void keep_values_here(uint32_t (&p)[8], float& l) {
   asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(p[5]), "+v"(p[6]), "+v"(p[7]), "+v"(l));
 }
-__device__ inline void no_memory_motion() { asm volatile("" ::: "memory"); }
 // enough wait states for every MFMA issued through the pinned helpers above to have written its result
 __device__ inline void wait_for_pinned_mfmas() { asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory"); }
 
@@ -430,23 +431,24 @@ struct AttnArgs {
 // Launches inside a loop with other kernels: 330 -> 305 us (steady state, 32 layers); empty cache 141 -> 128 us; back to
 // back 16 layers of 32/32 heads, 1024 rows over 1024 + 1024 states 493 -> 451 us; 64/8 heads, 2048 rows over 4096 + 2048
 // states 1286 -> 1227 us.  head_dim 64, two bf16 parts per probability: 8 layers of 32/8 heads back to back 59 us.
-template <int D, int WAVES, bool ROTATE_Q>
-__device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
+// block: the workgroup's number among a's.  ring: two K tiles, then two V tiles (double buffers).  q_stage: WAVES query row
+// tiles, laid out like half a key tile.
+template <int D>
+constexpr int attn_ring_bytes() { return 4 * Lay<D>::kTile; }
+template <int D, int WAVES>
+constexpr int attn_stage_bytes() { return WAVES * Lay<D>::kHalf; }
+template <int D, int WAVES, bool ROTATE_Q, bool SAVE_REGISTERS = ROTATE_Q>
+__device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int block, char* const ring, char* const q_stage) {
   typedef Geo<D> T;
   typedef Lay<D> Y;
   constexpr int kRowBytes = T::kRowBytes;
-  // two K tiles, then two V tiles (double buffers)
-  __shared__ __attribute__((aligned(1024))) char ring[4 * Y::kTile];
-  // [WAVES] query row tiles, laid out like half a key tile
-  extern __shared__ __attribute__((aligned(1024))) char q_stage[];
-
   const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
   const int col = lane % 32, grp = lane / 32;
   // The instance that rotates its queries is at the limit of its registers: it forms what the rare branches of the key loop
   // need of the lane's number there (227 registers; 256 and some in scratch otherwise: 16 layers, a document of 4000
   // tokens, 3.28 against 3.12 ms).  The other instances keep these numbers: 243 registers, and documents 0.3 to 0.6 %
   // faster than with 217.
-  auto when_needed = [](uint32_t x) { return ROTATE_Q ? formed_here(x) : x; };
+  auto when_needed = [](uint32_t x) { return SAVE_REGISTERS ? formed_here(x) : x; };
   constexpr int kR = T::kRowsPerLoad;
   constexpr int kFillRows = kTileN / WAVES;             // rows of a tile each wave fetches
   constexpr int kPer = kFillRows / kR;                  // load instructions per wave and tile
@@ -457,7 +459,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   // Workgroups are handed to the 8 XCDs round-robin by their linear id.  Remap so that the
   // workgroups of one (document, layer, KV head), which read the same K/V, land on ONE XCD and
   // share its L2; within a unit the row blocks with the longest causal range come first.
-  const int logical = a.per_xcd > 0 ? (blockIdx.x % kXcds) * a.per_xcd + blockIdx.x / kXcds : blockIdx.x;
+  const int logical = a.per_xcd > 0 ? (block % kXcds) * a.per_xcd + block / kXcds : block;
   // Causal attention that fills the chip: a workgroup takes the row block with the longest key range still free and
   // then its mirror image (the shortest), so every workgroup does the same number of key tiles.  In smaller launches
   // a row block is a workgroup of its own.
@@ -915,7 +917,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
   const int out_ss = a.out.ss;
   const __amdgpu_buffer_rsrc_t out_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(unit(a.out, h)), 0,
                                                                           (rows - 1) * out_ss + 2 * D, kBufferFlags);
-  const uint32_t lanex = formed_here(lane), colx = ROTATE_Q ? lanex % 32 : formed_here(col), grpx = ROTATE_Q ? lanex / 32 : grp;
+  const uint32_t lanex = formed_here(lane), colx = SAVE_REGISTERS ? lanex % 32 : formed_here(col), grpx = SAVE_REGISTERS ? lanex / 32 : grp;
   // Each wave parks its 32 x D tile in its own part of the tile buffers (free after the barrier above; 16-byte
   // segments XOR-swizzled by the row: column-wise writes spread over the banks) and stores it back as whole rows.  A
   // lane and its partner l ^ 32 hold the two halves of every segment: a swap gives each of them whole segments.
@@ -971,7 +973,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
       no_memory_motion();
     }
   }
-  const int t = row0 + static_cast<int>(ROTATE_Q ? colx : col);
+  const int t = row0 + static_cast<int>(SAVE_REGISTERS ? colx : col);
   if (grpx == 0 && t < rows) {
     if (a.lse_cache != nullptr) a.lse_cache[row_id0 + t] = (m_snap + log2f(l_snap_tot)) * kLn2;
     if (a.lse != nullptr) a.lse[row_id0 + t] = lse;
@@ -1000,14 +1002,33 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a) {
 // 19.8 instead of 24.4 us at 32/8 heads, 512 rows over 768 + 512 states, but other bits.)
 template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel(AttnArgs a) {
-  attn_pipe_body<D, WAVES, false>(a);
+  __shared__ __attribute__((aligned(1024))) char ring[attn_ring_bytes<D>()];
+  extern __shared__ __attribute__((aligned(1024))) char q_stage[];
+  attn_pipe_body<D, WAVES, false>(a, blockIdx.x, ring, q_stage);
 }
 // The same kernel for query rows that arrive without rotary embedding (position shift): they are rotated
 // in the LDS staging region before the operands are read.  An instance of its own, so that the kernel
 // above does not carry the extra prologue.
 template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel_rotq(AttnArgs a) {
-  attn_pipe_body<D, WAVES, true>(a);
+  __shared__ __attribute__((aligned(1024))) char ring[attn_ring_bytes<D>()];
+  extern __shared__ __attribute__((aligned(1024))) char q_stage[];
+  attn_pipe_body<D, WAVES, true>(a, blockIdx.x, ring, q_stage);
+}
+
+// Chunk attention and instruction score of a step in one launch: neither reads what the other writes, and a small step
+// leaves compute units idle in both.  The workgroups have the score's eight waves; those of the attention use four.
+// What bounds it: the attention's chain, behind which the score disappears.  One layer of 32/8 heads, 512 rows and 64
+// instruction rows over 768 + 512 states: 22.4 + 9.2 us in two launches, 23.4 in one; a document of it 641 -> 500 us.
+template <int D, bool ROTATE_Q, int TPW>
+__global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a, int attn_blocks, StripArgs s) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  if (static_cast<int>(blockIdx.x) < attn_blocks) {
+    if (threadIdx.x >= kThreads) return;  // an ended wave counts at no barrier
+    attn_pipe_body<D, kWaves, ROTATE_Q, true>(a, blockIdx.x, smem, smem + attn_ring_bytes<D>());
+  } else {
+    strip_score_body<D, 1, TPW, ROTATE_Q>(s, blockIdx.x - attn_blocks, smem);
+  }
 }
 
 // Brings the per-range (maximum, sum) pairs of a row, part[s * rows_total + row], to one normaliser,
@@ -1431,10 +1452,10 @@ bool fits_i32(const View& v, int rows) {
   return v.ss > 0 && v.ss * static_cast<int64_t>(rows > 0 ? rows : 1) < (int64_t{1} << 31);
 }
 
-// Attention with output: one instance of the kernel.
+// What the kernel needs to know of a launch, and its workgroups.
 template <int D, int WAVES>
-hipError_t attn_pipe_launch(const Dims& dm, View q, Segments ks, Segments vs, bool paired, View out, float* lse,
-                            float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+AttnArgs attn_args(const Dims& dm, View q, Segments ks, Segments vs, bool paired, View out, float* lse,
+                   float* lse_cache, int q_rope_pos0, float rope_base, int* blocks) {
   const TaskShape ts = task_shape(dm.G, WAVES);
   const int rows_per_block = ts.tiles_per_block * kRowsPerWave, rows = ks.c;
   AttnArgs a;
@@ -1464,8 +1485,16 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, Segments ks, Segments vs, bo
   a.lse_cache = lse_cache;
   a.q_rope_pos0 = q_rope_pos0;
   a.rope_log2_base = q_rope_pos0 >= 0 ? log2f(rope_base) : 0.f;
-  // dynamic LDS next to the static tiles
-  constexpr int kDynBytes = WAVES * Lay<D>::kHalf;
+  *blocks = grid;
+  return a;
+}
+
+template <int D, int WAVES>
+hipError_t attn_pipe_launch(const Dims& dm, View q, Segments ks, Segments vs, bool paired, View out, float* lse,
+                            float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
+  int grid = 0;
+  const AttnArgs a = attn_args<D, WAVES>(dm, q, ks, vs, paired, out, lse, lse_cache, q_rope_pos0, rope_base, &grid);
+  constexpr int kDynBytes = attn_stage_bytes<D, WAVES>();  // next to the static ring
   static LdsLimit limit, limit_rotq;
   const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES> : attn_pipe_kernel<D, WAVES>;
   const hipError_t e = raise_lds_limit(q_rope_pos0 >= 0 ? limit_rotq : limit, reinterpret_cast<const void*>(kern), kDynBytes);
@@ -1474,13 +1503,38 @@ hipError_t attn_pipe_launch(const Dims& dm, View q, Segments ks, Segments vs, bo
   return hipGetLastError();
 }
 
+// Workgroups of a launch with one row block each.
+int64_t attn_workgroups(const Dims& dm, int rows, int waves) {
+  const TaskShape ts = task_shape(dm.G, waves);
+  const int block_rows = ts.tiles_per_block * kRowsPerWave;
+  return static_cast<int64_t>((rows + block_rows - 1) / block_rows) * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L;
+}
+
+bool attn_segments_fit(const Segments& ks, const Segments& vs) {
+  return fits_i32(ks.cache, ks.n_c) && fits_i32(ks.chunk, ks.c) && fits_i32(vs.cache, vs.n_c) && fits_i32(vs.chunk, vs.c);
+}
+
+template <int D, bool ROTATE_Q, int TPW>
+hipError_t attn_score_launch(const Dims& dm, View q, Segments ks, Segments vs, View out, int q_rope_pos0, float rope_base,
+                             View q_instr, int instr_rows, float* part, int* strips, hipStream_t st) {
+  int blocks = 0;
+  const AttnArgs a = attn_args<D, kWaves>(dm, q, ks, vs, false, out, nullptr, nullptr, q_rope_pos0, rope_base, &blocks);
+  const StripArgs s = strip_args(dm, q_instr, instr_rows, ks, 32, part);
+  *strips = s.strips;
+  constexpr int kLdsBytes = std::max(attn_ring_bytes<D>() + attn_stage_bytes<D, kWaves>(), strip_lds_bytes<D, 1>());
+  const auto kern = attn_score_kernel<D, ROTATE_Q, TPW>;
+  static LdsLimit limit;
+  const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), kLdsBytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(blocks + dm.B * dm.L * dm.Hkv * s.strips), dim3(kStripThreads), kLdsBytes, st, a, blocks, s);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View out, float* lse, float* lse_cache,
                        hipStream_t st, int q_rope_pos0, float rope_base) {
   if (out.ptr == nullptr || (lse_cache != nullptr && ks.n_c < 1)) return hipErrorInvalidValue;
-  if (!fits_i32(ks.cache, ks.n_c) || !fits_i32(ks.chunk, ks.c) || !fits_i32(vs.cache, vs.n_c) ||
-      !fits_i32(vs.chunk, vs.c))
-    return hipErrorInvalidValue;
+  if (!attn_segments_fit(ks, vs)) return hipErrorInvalidValue;
   // The smallest piece of work per workgroup whose workgroups still fit the chip side by side: a launch that leaves
   // compute units idle lasts as long as its longest workgroup.  Measured in us, 32/8 heads, 512 rows over 768 + 512
   // states, head_dim 128 (row blocks in pairs | one row block | four waves, one row block):
@@ -1489,11 +1543,7 @@ hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View ou
   //   3 layers   56.1 | 38.4 | 42.0       8 layers   72.9 | 83.0 | 90.3
   // The best of a line is the last whose workgroups (128, 256, 192, 256 | 160, 256) are no more than the 256 compute
   // units; head_dim 64 and the other group sizes follow the same line (head_dim 64, one layer: 36.7 | 22.9 | 17.2).
-  const auto workgroups = [&](int row_waves) {  // one row block each
-    const TaskShape ts = task_shape(dm.G, row_waves);
-    const int block_rows = ts.tiles_per_block * kRowsPerWave;
-    return static_cast<int64_t>((ks.c + block_rows - 1) / block_rows) * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L;
-  };
+  const auto workgroups = [&](int waves) { return attn_workgroups(dm, ks.c, waves); };
   const int cus = compute_units();
   if (workgroups(4) <= cus)
     return attn_pipe_launch<D, 4>(dm, q, ks, vs, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
@@ -1573,6 +1623,29 @@ hipError_t launch_attn_mfma(const Dims& dm, View q, Segments ks, Segments vs, Vi
                             hipStream_t st, int q_rope_pos0, float rope_base) {
   const auto launch = dm.D == 64 ? attn_launch<64> : attn_launch<128>;
   return launch(dm, q, ks, vs, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+}
+
+// Worth it, and possible, while the workgroups of both fit the chip side by side.
+bool attn_score_in_one_launch(const Dims& dm, const Segments& ks, const Segments& vs, const View& q_instr, int instr_rows,
+                              size_t workspace_floats) {
+  const int64_t strips = (static_cast<int64_t>(dm.G) * instr_rows + 31) / 32;
+  return attn_workgroups(dm, ks.c, kWaves) + strips * dm.Hkv * dm.B * dm.L <= compute_units() && attn_segments_fit(ks, vs) &&
+         instr_strip_supported(dm, q_instr, instr_rows, ks, workspace_floats);
+}
+
+hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments ks, Segments vs, View out, int q_rope_pos0, float rope_base,
+                                  View q_instr, int instr_rows, float* workspace, float* score, hipStream_t st,
+                                  ScoreSums* sums) {
+  const bool rotate = q_rope_pos0 >= 0, shorter = ks.n_c + ks.c <= kStripMaxKeysShort;
+  auto launch = dm.D == 128 ? (rotate ? (shorter ? attn_score_launch<128, true, 5> : attn_score_launch<128, true, 10>)
+                                      : (shorter ? attn_score_launch<128, false, 5> : attn_score_launch<128, false, 10>))
+                            : (rotate ? (shorter ? attn_score_launch<64, true, 5> : attn_score_launch<64, true, 10>)
+                                      : (shorter ? attn_score_launch<64, false, 5> : attn_score_launch<64, false, 10>));
+  const int total = dm.G * instr_rows;
+  float* const part = total <= 32 ? score : workspace;  // one strip: its column is the score
+  int strips = 0;
+  const hipError_t e = launch(dm, q, ks, vs, out, q_rope_pos0, rope_base, q_instr, instr_rows, part, &strips, st);
+  return e != hipSuccess ? e : finish_strip_scores(dm, part, strips, ks.n_c + ks.c, score, st, sums);
 }
 
 hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse, float* score,

@@ -846,18 +846,27 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
     } else {
       Eviction lm;
       bool together = false;  // DUAL: the two caches' evictions share a launch
+      bool scored = false;
       if (dual) {
         int32_t* idx_lm = idx_history_lm ? idx_history_lm + static_cast<size_t>(done) * units_sel * cfg->budget_lm : idx_lm_ws;
         const ChunkEvicted t{k_cache_lm, v_cache_lm, &n_c_lm, &cur_lm, cfg->budget_lm, score_lm, idx_lm};
         together = fused && one_launch(cfg, n_c_lm + c) && !timed(3) && !timed(4) && !timed(5);
         if ((status = chunk_evicted_step(t, io, c, together ? &lm : nullptr)) != CITRUS_OK) break;
+      } else if (mfma_path_supported(cfg->dtype, dm) && !timed(1) && !timed(2) && !timed(3) && !timed(4) &&
+                 attn_score_in_one_launch(dm, ks_att, vs, make_view(qi_att), cfg->instr_len, lse_instr.floats)) {
+        scored = true;
+        status = hip_status(launch_attn_score_mfma(dm, make_view(q_att), ks_att, vs, make_view(io.out), q_rope_pos0,
+                                                   rope_base_of(cfg), make_view(qi_att), cfg->instr_len, lse_instr.ptr, score,
+                                                   st, fused ? &own.score : nullptr));
+        if (status != CITRUS_OK) break;
+        mark(done, 5);
       } else {
         if ((status = do_chunk_attn(cfg, dm, q_att, ks_att, vs, io.out, nullptr, nullptr, nullptr, st, q_rope_pos0)) !=
             CITRUS_OK)
           break;
         for (int p = 1; p <= 4; ++p) mark(done, p);
       }
-      if ((status = score_step()) != CITRUS_OK) break;
+      if (!scored && (status = score_step()) != CITRUS_OK) break;
       if (together) {
         const Eviction both[2] = {lm, own};
         status = hip_status(launch_evict(elem_bytes(cfg->dtype), dm, both, 2, st));

@@ -86,6 +86,19 @@ size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n);
 hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments kseg, float* workspace, size_t workspace_floats,
                               float* score, hipStream_t st, ScoreSums* sums = nullptr);
 
+// What a strip kernel's partial columns still need: nothing for one strip (its column is `score`), a description for a
+// caller who adds them, else a launch that does.
+hipError_t finish_strip_scores(const Dims& dm, const float* part, int strips, int n, float* score, hipStream_t st,
+                               ScoreSums* sums);
+
+// ---- chunk attention and instruction score of a small step in one launch, attn_mfma.hip ----
+// The same bits as the two launches.  Both read [cache ; chunk]; q_instr: instr_rows rows per head.
+bool attn_score_in_one_launch(const Dims& dm, const Segments& kseg, const Segments& vseg, const View& q_instr, int instr_rows,
+                              size_t workspace_floats);
+hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments kseg, Segments vseg, View out, int q_rope_pos0,
+                                  float rope_base, View q_instr, int instr_rows, float* workspace, float* score,
+                                  hipStream_t st, ScoreSums* sums);
+
 // ---- bf16 MFMA decoding step (at most 32 query heads per KV head), decode_attn.hip ----
 bool decode_mfma_supported(int dtype, const Dims& dm);
 size_t decode_mfma_workspace_floats(const Dims& dm);

@@ -60,19 +60,9 @@ hipError_t strip_launch(const Dims& dm, View q, int rows, Segments ks, float* pa
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(units * strips), dim3(kStripThreads), lds, st, a);
   e = hipGetLastError();
-  if (e != hipSuccess || strips == 1) return e;
-  if (sums != nullptr) {  // the consumer adds the strips' columns itself
-    *sums = ScoreSums{part, strips};
-    return hipSuccess;
-  }
-  const int64_t total = static_cast<int64_t>(units) * n;
-  hipLaunchKernelGGL(strip_sum_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, st, part, strips, n,
-                     total, score);
-  return hipGetLastError();
+  return e != hipSuccess ? e : finish_strip_scores(dm, a.part, strips, n, score, st, sums);
 }
 
-constexpr int kStripMaxKeysShort = kStripWaves * 5 * kStripKeys;  // 1280: five key tiles per wave
-constexpr int kStripMaxKeysLong = kStripWaves * 10 * kStripKeys;  // 2560: 32-row strips, ten key tiles per wave
 constexpr int kStripMaxRows = 4096;  // instruction rows per KV group: bounds a selection's sums over the strips
 
 }  // namespace
@@ -87,6 +77,19 @@ int compute_units() {
     cached[dev].store(cus, std::memory_order_relaxed);
   }
   return cus;
+}
+
+hipError_t finish_strip_scores(const Dims& dm, const float* part, int strips, int n, float* score, hipStream_t st,
+                               ScoreSums* sums) {
+  if (strips == 1) return hipSuccess;  // the only strip's column is the score
+  if (sums != nullptr) {  // the consumer adds the strips' columns itself
+    *sums = ScoreSums{part, strips};
+    return hipSuccess;
+  }
+  const int64_t total = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv * n;
+  hipLaunchKernelGGL(strip_sum_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, st, part, strips, n,
+                     total, score);
+  return hipGetLastError();
 }
 
 // Rows of a strip: 32 while such strips fit the compute units side by side (more workgroups, each with half the work), else

@@ -59,6 +59,9 @@ __device__ inline const uint16_t* unit_ptr(const View& v, int b, int l, int h) {
   return static_cast<const uint16_t*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh);
 }
 
+// a fence for the optimiser
+__device__ inline void no_memory_motion() { asm volatile("" ::: "memory"); }
+
 // Division by a number that is known at launch: n / divisor for 0 <= n < 2^31 by a multiplication.
 struct FastDiv {
   int divisor;

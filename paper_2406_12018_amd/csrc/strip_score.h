@@ -9,6 +9,8 @@ namespace {
 constexpr int kStripKeys = 32;   // keys per tile
 constexpr int kStripWaves = 8;
 constexpr int kStripThreads = kStripWaves * 64;
+constexpr int kStripMaxKeysShort = kStripWaves * 5 * kStripKeys;  // 1280: five key tiles per wave
+constexpr int kStripMaxKeysLong = kStripWaves * 10 * kStripKeys;  // 2560: 32-row strips, ten key tiles per wave
 
 // What a workgroup of the score works on, prepared on the host.
 struct StripArgs {
@@ -86,7 +88,9 @@ constexpr int strip_lds_bytes() {
 }
 
 // ROW_TILES: 32-row tiles per strip; TPW: key tiles a wave can hold (n <= 8 * TPW * 32).  smem: strip_lds_bytes.
-template <int D, int ROW_TILES, int TPW>
+// Kernels cannot share an instance (the compiler's host pass accepts a body with LDS-direct loads once): KERNEL tells those of
+// a translation unit apart.
+template <int D, int ROW_TILES, int TPW, int KERNEL = 0>
 __device__ __forceinline__ void strip_score_body(const StripArgs& a, int block, char* smem) {
   typedef StripGeo<D> T;
   constexpr int kStripRows = 32 * ROW_TILES;
@@ -147,10 +151,10 @@ __device__ __forceinline__ void strip_score_body(const StripArgs& a, int block, 
         lds_void_ptr kd = (lds_void_ptr)(k_t + T::kR * i * T::kRowBytes);
         const int j = min(j0 + T::kR * i + fill_row, n - 1);
         if (j < n_c) __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rs_cache, kd, 16, j * k_ss_cache * 2 + seg, 0, 0, 0);
-        asm volatile("" ::: "memory");
+        no_memory_motion();
         if (j >= n_c)
           __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rs_chunk, kd, 16, (j - n_c) * k_ss_chunk * 2 + seg, 0, 0, 0);
-        asm volatile("" ::: "memory");
+        no_memory_motion();
       }
     }
   };
@@ -185,7 +189,7 @@ __device__ __forceinline__ void strip_score_body(const StripArgs& a, int block, 
     wait_all_but_newest<0>();
   }
   __builtin_amdgcn_s_barrier();  // every wave's part of the strip has landed (each wave has waited for its own)
-  asm volatile("" ::: "memory");
+  no_memory_motion();
 
   // Operands of a tile's 32 rows: lane's row col, segment 2 kk + grp, at position segment ^ swz(col) of the row.  The tile
   // begins at a multiple of a row, so the address of segment 2 kk is that of segment 0 with 32 kk exclusive-ored.
