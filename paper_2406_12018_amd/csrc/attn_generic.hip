@@ -1,247 +1,468 @@
-// Vector-ALU attention kernels of the f32 mode (bf16 runs on the matrix-core kernels for every head
-// dimension).  They follow the same definitions as the fast path: softmax attention with the 1/sqrt(d_k) scaling
-// of Eq. (1) (Section 4.1 step 1), and the summed form of Eq. (1) for the
-// importance scores.
+// Attention kernels of the f32 mode (bf16 has its own for every head dimension), on the f64 matrix instructions.  They
+// follow the same definitions as the fast path: softmax attention with the 1/sqrt(d_k) scaling of Eq. (1) (Section 4.1
+// step 1), and the summed form of Eq. (1) for the importance scores.
+//
+// Precision.  The mode promises 1e-5 against an f64 reference: with logits of a few tens an f32 dot product and
+// subtraction alone leave a relative error of that order in the probability.  So both products are formed and added in
+// f64; probabilities, row sums and what leaves a wave are f32.
+//
+// Layout of v_mfma_f64_16x16x4_f64 (wave64): A holds row l % 16, contraction slot l / 16; B column l % 16, the same slot;
+// C/D register i holds row 4 i + l / 16, column l % 16.  S^T = K.Q^T puts one query per lane, and its register i is
+// the B operand (P^T) of step i of O^T = V^T.P^T.  A float4 of a row gives four operands: the contraction over head_dim, and
+// the rows of O^T, may run in any order.
+//
+// What bounds it: these launches are small, and a workgroup's time is its chain of dependent steps (memory 1 us, sixteen
+// to thirty-two MFMAs of 58 cycles, exchange through LDS).  So the eight waves of a workgroup share sixteen query rows and split
+// the keys.  Against one wavefront per query row on the vector units, keys one by one: 4 heads, 32 rows over 96 states, 8
+// instruction rows, head_dim 64: 15.0 + 5 + 7.6 us in three launches, 8.8 in one (a document of 512 tokens 527 -> 235 us);
+// documents of 32/8 heads, head_dim 128, 128 rows over 384 states 1599 -> 431 us, 8/1 heads in 16 layers, 512 rows over 1280
+// states 11651 -> 2204 us; decoding 8 layers of 32/8 heads, 1000 states, 4 tokens 512 -> 227 us.  Errors against f64 are the
+// same or smaller (outputs 9e-8 to 1.2e-7 instead of 1.2e-7 to 7e-7).
+#include <algorithm>
+
 #include "citrus_internal.h"
 
 namespace citrus {
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
 constexpr int kWave = 64;
-constexpr int kRowsPerBlock = 4;  // one wavefront per query row
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * kWave;
+constexpr int kTile = 16;  // query rows of a workgroup; keys of a wave's tile
 
-// The type the q.k products are accumulated and the maximum / normaliser subtracted in.  The f32
-// mode promises 1e-5 against an f64 reference: with logits of a few tens an f32 dot product and subtraction
-// alone leave a relative error of that order in the probability.
-typedef double Logit;
-
-constexpr int kVec = 4;  // elements per 16-byte load
-__device__ inline void load16(const float* p, float* dst) {
-  float4 v = *reinterpret_cast<const float4*>(p);
-  dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-}
 __device__ inline const float* row_ptr(const View& v, int b, int l, int h, int s) {
   return static_cast<const float*>(v.ptr) + (b * v.sb + l * v.sl + h * v.sh + static_cast<int64_t>(s) * v.ss);
 }
-
-// candidate j -> its row in the cache or the chunk segment
+// candidate j -> its row in the cache or the chunk segment (both addresses, then the choice)
 __device__ inline const float* cand_ptr(const Segments& sg, int b, int l, int g, int j) {
-  return j < sg.n_c ? row_ptr(sg.cache, b, l, g, j) : row_ptr(sg.chunk, b, l, g, j - sg.n_c);
+  const float* const in_cache = row_ptr(sg.cache, b, l, g, j);
+  const float* const in_chunk = row_ptr(sg.chunk, b, l, g, j - sg.n_c);
+  return j < sg.n_c ? in_cache : in_chunk;
+}
+__device__ inline f64x4 mfma(double a, double b, const f64x4& c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+// exchange over the four lanes of a column
+__device__ inline float column_max(float v) {
+  v = fmaxf(v, __shfl_xor(v, 16, kWave));
+  return fmaxf(v, __shfl_xor(v, 32, kWave));
+}
+__device__ inline float column_sum(float v) {
+  v += __shfl_xor(v, 16, kWave);
+  return v + __shfl_xor(v, 32, kWave);
 }
 
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
-}
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
-}
-
-// One wavefront per query row; lanes split the keys of a 64-key tile for the
-// logits and split head_dim for the output accumulation.
-// A launch of the f32 mode has few wavefronts, so a row's chain of dependent loads is its time.  A lane
-// requests 256 bytes of its key at once, the value rows come kValueRows at a time, the first of them before
-// the logits and the next while one batch is added; the sums keep their order.
-// Same bits as one load after the other.  Decoding step, 4 tokens (a workgroup's wavefronts without a row load
-// nothing): 8 layers of 32/8 heads, head_dim 128, 1000 states 668 -> 516 us; 2 layers of 8/8 heads, head_dim 64,
-// 3000 states 1108 -> 987 us.
-constexpr int kValueRows = 16;
+// The lane's part of sixteen rows as an operand: four elements of its row (l % 16) per 16 of head_dim, from 4 (l / 16).
 template <int D>
-__global__ __launch_bounds__(kWave* kRowsPerBlock) void attn_f32_kernel(Dims dm, View q, int rows, Segments ks,
-                                                                           Segments vs, int causal, View out,
-                                                                           float* lse) {
-  __shared__ __attribute__((aligned(16))) Logit q_s[kRowsPerBlock][D];
-  __shared__ __attribute__((aligned(16))) float p_s[kRowsPerBlock][kWave];
-  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int h = blockIdx.y, b = blockIdx.z / dm.L, l = blockIdx.z % dm.L, g = h / dm.G;
-  const int n = ks.n_c + ks.c;
-  const int t_raw = blockIdx.x * kRowsPerBlock + w;
-  const bool row_ok = t_raw < rows;
-  const int t = row_ok ? t_raw : rows - 1;
-  // last visible candidate; a wavefront without a row sees none and loads none
-  const int limit = !row_ok ? -1 : causal ? ks.n_c + t : n - 1;
-  const int t_blk_last = min(rows - 1, blockIdx.x * kRowsPerBlock + kRowsPerBlock - 1);
-  const int blk_limit = causal ? ks.n_c + t_blk_last : n - 1;
-  constexpr int E = D / kWave;                   // output dims per lane
-  constexpr int kKeyElems = D < 64 ? D : 64;     // elements of a key in flight per lane
+struct Operand {
+  f32x4 x[D / 16];
+};
+template <int D>
+__device__ inline void load_operand(Operand<D>& o, const float* row, int lane) {
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x) o.x[x] = *reinterpret_cast<const f32x4*>(row + 16 * x + 4 * (lane / 16));
+}
+// logits of sixteen keys x sixteen queries, unscaled; two chains
+template <int D>
+__device__ inline f64x4 products(const Operand<D>& k, const Operand<D>& q) {
+  f64x4 s[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      s[c % 2] = mfma(static_cast<double>(k.x[x][c]), static_cast<double>(q.x[x][c]), s[c % 2]);
+  return s[0] + s[1];
+}
 
-  const float* qp = row_ptr(q, b, l, h, t);
-  for (int e = lane; e < D; e += kWave) q_s[w][e] = static_cast<Logit>(qp[e]);
-  __syncthreads();
+struct AttnF32Args {
+  Dims dm;
+  View q, out;
+  int rows, causal;
+  Segments ks, vs;
+  float* lse;
+  int row_blocks;
+};
 
-  float m = -INFINITY, lsum = 0.f, acc[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = 0.f;
+template <int D>
+constexpr int attn_f32_lds_bytes() { return kWaves * kTile * (D + 4) * 4 + 2 * kWaves * kTile * 4; }
 
-  // value rows j .. j + kValueRows - 1; those the row does not see repeat the last one it sees and are not added
-  auto load_values = [&](int j, float (&v)[kValueRows][E]) {
-#pragma unroll
-    for (int u = 0; u < kValueRows; ++u) {
-      const float* vp = cand_ptr(vs, b, l, g, min(j + u, limit));
-#pragma unroll
-      for (int e = 0; e < E; ++e) v[u][e] = vp[lane + e * kWave];
-    }
-  };
+// Sixteen query rows of one head.  out and lse are optional.
+template <int D>
+__device__ __forceinline__ void attn_f32_body(const AttnF32Args& a, int block, char* smem) {
+  constexpr int kPitch = D + 4, kCols = D / 64;  // float4 columns of O^T per lane
+  float* const o_s = reinterpret_cast<float*>(smem);  // [waves][16][kPitch]
+  float* const m_s = o_s + kWaves * kTile * kPitch;   // [waves][16]
+  float* const l_s = m_s + kWaves * kTile;
+  const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int col = lane % 16, quad = lane / 16;
+  const int rb = block % a.row_blocks, hb = block / a.row_blocks;
+  const int h = hb % a.dm.Hq, bl = hb / a.dm.Hq, b = bl / a.dm.L, l = bl % a.dm.L, g = h / a.dm.G;
+  const int n_c = a.ks.n_c, n = n_c + a.ks.c;
+  const int row0 = rb * kTile, t = min(row0 + col, a.rows - 1);  // rows past the end repeat the last one and are not stored
+  const int limit = a.causal ? n_c + t : n - 1;                  // last candidate the lane's row sees
+  const int first_limit = a.causal ? n_c + row0 : n - 1;         // ... and every row of the block
+  const int last_limit = a.causal ? n_c + min(row0 + kTile, a.rows) - 1 : n - 1;
+  const int tiles = last_limit / kTile + 1;
+  const bool values = a.out.ptr != nullptr;
+  const double scale = static_cast<double>(a.dm.scale);
 
-  for (int j0 = 0; j0 <= blk_limit; j0 += kWave) {
-    const int j = j0 + lane;
-    const bool valid = j <= limit;
-    float v_now[kValueRows][E];
-    if (out.ptr != nullptr && j0 <= limit) load_values(j0, v_now);
-    Logit s = -INFINITY;
-    if (valid) {
-      const float* kp = cand_ptr(ks, b, l, g, j);
-      Logit dot = 0;
+  Operand<D> q;
+  load_operand(q, row_ptr(a.q, b, l, h, t), lane);
+  float m = -INFINITY, lsum = 0.f;
+  f64x4 acc[kCols][4];  // [hh][c], register i: head_dim 64 hh + 16 i + 4 quad + c
 #pragma unroll
-      for (int e0 = 0; e0 < D; e0 += kKeyElems) {
-        float kv[kKeyElems];
+  for (int hh = 0; hh < kCols; ++hh)
 #pragma unroll
-        for (int e = 0; e < kKeyElems; e += kVec) load16(kp + e0 + e, kv + e);
+    for (int c = 0; c < 4; ++c) acc[hh][c] = f64x4{0, 0, 0, 0};
+
+  for (int kt = w; kt < tiles; kt += kWaves) {
+    const int j0 = kt * kTile;
+    Operand<D> k;
+    load_operand(k, cand_ptr(a.ks, b, l, g, min(j0 + col, n - 1)), lane);
+    f32x4 v[4][kCols];  // values of keys j0 + 4 i + quad, head_dim 64 hh + 4 col .. + 3
+    if (values) {
 #pragma unroll
-        for (int e = 0; e < kKeyElems; ++e) dot = fma(q_s[w][e0 + e], static_cast<Logit>(kv[e]), dot);
+      for (int i = 0; i < 4; ++i) {
+        const float* const vp = cand_ptr(a.vs, b, l, g, min(j0 + 4 * i + quad, n - 1));
+#pragma unroll
+        for (int hh = 0; hh < kCols; ++hh) v[i][hh] = *reinterpret_cast<const f32x4*>(vp + 64 * hh + 4 * col);
       }
-      s = dot * static_cast<Logit>(dm.scale);
+    }
+    f64x4 s = products(k, q);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[i] *= scale;
+      if (j0 + 4 * i + quad <= limit) mx = fmaxf(mx, static_cast<float>(s[i]));
     }
     // the running maximum is an f32 value; it only has to be the same number wherever it is subtracted
-    const float m_new = fmaxf(m, wave_max(static_cast<float>(s)));
-    // tile 0 always holds candidate 0, which every row sees, so m_new is finite where there is a row
-    const float p = valid ? expf(static_cast<float>(s - static_cast<Logit>(m_new))) : 0.f;
-    const float corr = expf(m - m_new);
-    lsum = lsum * corr + wave_sum(p);
-    m = m_new;
-    p_s[w][lane] = p;
-    __syncthreads();
-    if (out.ptr != nullptr) {
+    const float m_new = fmaxf(m, column_max(mx));
+    if (__any(m_new != m)) {  // wave-uniform
+      const float corr = m_new == m ? 1.f : expf(m - m_new);
+      lsum *= corr;
 #pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] *= corr;
-      const int cnt = min(kWave, limit + 1 - j0);  // may be <= 0 for rows that see nothing here
-      for (int jj = 0; jj < cnt; jj += kValueRows) {
-        float v_next[kValueRows][E];
-        if (jj + kValueRows < cnt) load_values(j0 + jj + kValueRows, v_next);
+      for (int hh = 0; hh < kCols; ++hh)
 #pragma unroll
-        for (int u = 0; u < kValueRows; ++u) {
-          const float pj = p_s[w][jj + u];
+        for (int c = 0; c < 4; ++c) acc[hh][c] *= static_cast<double>(corr);
+      m = m_new;
+    }
+    const double m_sub = m == -INFINITY ? 0.0 : static_cast<double>(m);  // a row that has seen nothing yet
+    float p[4];
 #pragma unroll
-          for (int e = 0; e < E; ++e) acc[e] = jj + u < cnt ? fmaf(pj, v_now[u][e], acc[e]) : acc[e];
+    for (int i = 0; i < 4; ++i) {
+      p[i] = j0 + 4 * i + quad <= limit ? expf(static_cast<float>(s[i] - m_sub)) : 0.f;
+      lsum += p[i];
+    }
+    if (!values) continue;
+    // A value that is not finite must not reach a row that does not see its key, and a product with probability 0 would
+    // carry it there.
+    bool finite = true;
+    if (j0 + kTile - 1 > first_limit) {  // wave-uniform: some row does not see some key of the tile
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int hh = 0; hh < kCols; ++hh)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) finite = finite && fabsf(v[i][hh][c]) < INFINITY;
+      finite = __all(finite);
+    }
+    if (__builtin_expect(finite, 1)) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int hh = 0; hh < kCols; ++hh)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[hh][c] = mfma(static_cast<double>(v[i][hh][c]), static_cast<double>(p[i]), acc[hh][c]);
+    } else {
+      for (int key = 0; key < kTile; ++key) {  // one key after the other, to the rows that see it
+        float pk = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float pi = __shfl(p[i], col + 16 * (key % 4), kWave);
+          pk = key / 4 == i ? pi : pk;
         }
+        if (j0 + key > last_limit) break;
+        const float* const vp = cand_ptr(a.vs, b, l, g, j0 + key);
 #pragma unroll
-        for (int u = 0; u < kValueRows; ++u)
+        for (int hh = 0; hh < kCols; ++hh)
 #pragma unroll
-          for (int e = 0; e < E; ++e) v_now[u][e] = v_next[u][e];
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (j0 + key <= limit)
+                acc[hh][c][i] = fma(static_cast<double>(pk), static_cast<double>(vp[64 * hh + 16 * i + 4 * quad + c]), acc[hh][c][i]);
       }
     }
-    __syncthreads();
   }
 
-  if (!row_ok) return;
-  if (out.ptr != nullptr) {
-    float* op = const_cast<float*>(row_ptr(out, b, l, h, t));
-    const float inv = 1.f / lsum;
+  lsum = column_sum(lsum);
+  if (quad == 0) {
+    m_s[w * kTile + col] = m;
+    l_s[w * kTile + col] = lsum;
+  }
+  if (values) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) op[lane + e * kWave] = acc[e] * inv;
-  }
-  if (lse != nullptr && lane == 0)
-    lse[(static_cast<int64_t>(blockIdx.z) * dm.Hq + h) * rows + t] = m + logf(lsum);
-}
-
-constexpr int kColsumWaves = 8;
-constexpr int kColsumRows = 4;  // query rows per wave and step
-constexpr int kColsumTile = kColsumWaves * kColsumRows;
-
-// A workgroup owns 64 candidate keys, one per lane, and takes the KV group's query rows 32 at a time: each
-// of its eight waves four rows, whose dot products are four independent chains (one thread per key that
-// walked all rows alone was a single chain of G * rows * head_dim dependent f64 operations).  The
-// probabilities meet in LDS, where the first wave adds them while the others go on.  The sum runs in a fixed
-// order (heads, then rows), so it is reproducible.
-// Loops that are mostly this kernel, same bits: 3 layers of 14/2 heads, head_dim 64, two caches 5990 -> 1423 us;
-// 4 layers of 16/4 heads, head_dim 128, 128 instruction rows 8010 -> 3978 us.  The smallest (4 heads, 32 rows,
-// 72 states a step; 26 of its 52 us were here) 858 -> 525 us a document.
-template <int D>
-__global__ __launch_bounds__(kWave* kColsumWaves) void colsum_f32_kernel(Dims dm, View q, int rows, Segments ks,
-                                                                            int causal, const float* lse, float* score) {
-  __shared__ __attribute__((aligned(16))) Logit q_s[kColsumTile][D];
-  __shared__ float p_s[2][kColsumTile][kWave];
-  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int g = blockIdx.y, b = blockIdx.z / dm.L, l = blockIdx.z % dm.L;
-  const int n = ks.n_c + ks.c;
-  const int j = blockIdx.x * kWave + lane;
-  const bool key_ok = j < n;
-
-  float kreg[D];
-  {
-    const float* kp = cand_ptr(ks, b, l, g, key_ok ? j : n - 1);
+    for (int hh = 0; hh < kCols; ++hh)
 #pragma unroll
-    for (int e = 0; e < D; e += kVec) load16(kp + e, kreg + e);
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<f32x4*>(o_s + (w * kTile + col) * kPitch + 64 * hh + 16 * i + 4 * quad) =
+            f32x4{static_cast<float>(acc[hh][0][i]), static_cast<float>(acc[hh][1][i]), static_cast<float>(acc[hh][2][i]),
+                  static_cast<float>(acc[hh][3][i])};
   }
-  // first chunk row that sees candidate j (cache candidates are seen by every row)
-  const int t_first = (causal && j >= ks.n_c) ? j - ks.n_c : 0;
-
-  const int total = dm.G * rows;  // row r of the group is row r % rows of its head r / rows
+  __syncthreads();
+  // thread: query row r, four elements of its output; the waves' parts in a fixed order
+  const int r = tid / (kThreads / kTile), e = tid % (kThreads / kTile) * 4;
+  if (row0 + r >= a.rows) return;
+  float mw[kWaves], mm = -INFINITY;
+#pragma unroll
+  for (int x = 0; x < kWaves; ++x) {
+    mw[x] = m_s[x * kTile + r];
+    mm = fmaxf(mm, mw[x]);
+  }
   float sum = 0.f;
-  for (int r0 = 0, buf = 0; r0 < total; r0 += kColsumTile, buf ^= 1) {
-    int t[kColsumRows];
-    float lse_r[kColsumRows];
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int x = 0; x < kColsumRows; ++x) {
-      const int r = min(r0 + w * kColsumRows + x, total - 1);  // rows past the end are computed and not added
-      const int h = g * dm.G + r / rows;
-      t[x] = r % rows;
-      lse_r[x] = lse[(static_cast<int64_t>(blockIdx.z) * dm.Hq + h) * rows + t[x]];
-      const float* qp = row_ptr(q, b, l, h, t[x]);
-#pragma unroll
-      for (int e = 0; e < D; e += kWave)
-        q_s[w * kColsumRows + x][e + lane] = static_cast<Logit>(qp[e + lane]);
-    }
-    // a wave reads only the rows it has written
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if constexpr (D > 64) {  // the key stays f32: kept as f64 across the loop it would spill
-#pragma unroll
-      for (int e = 0; e < D; ++e) asm volatile("" : "+v"(kreg[e]));
-    }
-    Logit dot[kColsumRows];
-#pragma unroll
-    for (int x = 0; x < kColsumRows; ++x) dot[x] = 0;
-#pragma unroll
-    for (int e = 0; e < D; ++e)
-#pragma unroll
-      for (int x = 0; x < kColsumRows; ++x)
-        dot[x] = fma(q_s[w * kColsumRows + x][e], static_cast<Logit>(kreg[e]), dot[x]);
-#pragma unroll
-    for (int x = 0; x < kColsumRows; ++x) {
-      const float p = expf(static_cast<float>(dot[x] * static_cast<Logit>(dm.scale) - static_cast<Logit>(lse_r[x])));
-      p_s[buf][w * kColsumRows + x][lane] = t[x] >= t_first ? p : 0.f;
-    }
-    // the first wave reads this buffer before the next barrier, the others write it again after that one
-    __syncthreads();
-    if (w == 0) {
-      const int rn = min(kColsumTile, total - r0);
-#pragma unroll
-      for (int x = 0; x < kColsumTile; ++x) sum += x < rn ? p_s[buf][x][lane] : 0.f;
-    }
+  for (int x = 0; x < kWaves; ++x) {
+    if (mw[x] == -INFINITY && mm != -INFINITY) continue;  // a wave without a key the row sees
+    const float f = expf(mw[x] - mm);
+    sum += l_s[x * kTile + r] * f;
+    if (values && e < D) o += *reinterpret_cast<const f32x4*>(o_s + (x * kTile + r) * kPitch + e) * f;
   }
-  if (w == 0 && key_ok) score[(static_cast<int64_t>(blockIdx.z) * dm.Hkv + g) * n + j] = sum;
+  if (values && e < D) {
+    const float inv = 1.f / sum;
+    *reinterpret_cast<f32x4*>(const_cast<float*>(row_ptr(a.out, b, l, h, row0 + r)) + e) = o * inv;
+  }
+  if (a.lse != nullptr && e == 0) a.lse[(static_cast<int64_t>(bl) * a.dm.Hq + h) * a.rows + row0 + r] = mm + logf(sum);
 }
 
 template <int D>
-hipError_t attn_launch(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out,
-                         float* lse, hipStream_t st) {
-  dim3 grid((rows + kRowsPerBlock - 1) / kRowsPerBlock, dm.Hq, dm.B * dm.L);
-  hipLaunchKernelGGL(attn_f32_kernel<D>, grid, dim3(kWave * kRowsPerBlock), 0, st, dm, q, rows, ks, vs,
-                     causal, out, lse);
+__global__ __launch_bounds__(kThreads) void attn_f32_kernel(AttnF32Args a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  attn_f32_body<D>(a, blockIdx.x, smem);
+}
+
+// Column sums: score[g, j] = sum over the query rows of the KV group of exp(s - lse).  A workgroup owns two tiles of sixteen
+// keys; four waves per tile split the rows (head after head, flattened), whose sums meet in LDS in a fixed order.
+constexpr int kColsumKeyTiles = 2, kColsumSplits = kWaves / kColsumKeyTiles;
+template <int D>
+__global__ __launch_bounds__(kThreads) void colsum_f32_kernel(Dims dm, View q, int rows, Segments ks, int causal,
+                                                              const float* lse, float* score) {
+  __shared__ float part[kWaves][kTile];
+  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int col = lane % 16, quad = lane / 16;
+  const int g = blockIdx.y, b = blockIdx.z / dm.L, l = blockIdx.z % dm.L;
+  const int n_c = ks.n_c, n = n_c + ks.c;
+  const int j0 = (blockIdx.x * kColsumKeyTiles + w / kColsumSplits) * kTile, split = w % kColsumSplits;
+  const int total = dm.G * rows, row_tiles = (total + kTile - 1) / kTile;
+  const double scale = static_cast<double>(dm.scale);
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  if (j0 < n) {  // wave-uniform
+    Operand<D> k;
+    load_operand(k, cand_ptr(ks, b, l, g, min(j0 + col, n - 1)), lane);
+    auto row_of = [&](int rt, int& t) {  // flattened row rt * 16 + col: row t of a head; rows past the end repeat the last
+      const int r = min(rt * kTile + col, total - 1), hh = r / rows;
+      t = r - hh * rows;
+      return g * dm.G + hh;
+    };
+    Operand<D> q_next;
+    float lse_next = 0.f;
+    int t_next = 0;
+    auto request = [&](int rt) {
+      const int h = row_of(min(rt, row_tiles - 1), t_next);
+      load_operand(q_next, row_ptr(q, b, l, h, t_next), lane);
+      lse_next = lse[(static_cast<int64_t>(blockIdx.z) * dm.Hq + h) * rows + t_next];
+    };
+    request(split);
+    for (int rt = split; rt < row_tiles; rt += kColsumSplits) {
+      const Operand<D> qo = q_next;
+      const double norm = static_cast<double>(lse_next);
+      const int t = t_next;
+      request(rt + kColsumSplits);
+      const f64x4 s = products(k, qo);
+      const int limit = rt * kTile + col >= total ? -1 : causal ? n_c + t : n - 1;  // a row past the end sees nothing
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p = expf(static_cast<float>(s[i] * scale - norm));
+        acc[i] += j0 + 4 * i + quad <= limit ? p : 0.f;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {  // over the sixteen rows of a tile = lanes of a quad
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) acc[i] += __shfl_xor(acc[i], o, kWave);
+    if (col == 0) part[w][4 * i + quad] = acc[i];
+  }
+  __syncthreads();
+  if (threadIdx.x < kColsumKeyTiles * kTile) {
+    const int kt = threadIdx.x / kTile, x = threadIdx.x % kTile;
+    const int j = (blockIdx.x * kColsumKeyTiles + kt) * kTile + x;
+    float v = part[kt * kColsumSplits][x];
+#pragma unroll
+    for (int y = 1; y < kColsumSplits; ++y) v += part[kt * kColsumSplits + y][x];
+    if (j < n) score[(static_cast<int64_t>(blockIdx.z) * dm.Hkv + g) * n + j] = v;
+  }
+}
+
+// Instruction score of a KV group whose logits fit the registers of a workgroup (512 keys; 64 rows, at head_dim 128 32): products once,
+// normalisers through LDS, column sums.  No mask.
+struct ScoreF32Args {
+  Dims dm;
+  View q;
+  int rows;
+  Segments ks;
+  float* score;
+};
+constexpr int kScoreKeyTiles = 4;  // key tiles of a wave
+template <int D>
+constexpr int score_row_tiles() { return 256 / D; }
+bool score_f32_fits(const Dims& dm, int rows, int n) {
+  const int row_tiles = dm.D == 64 ? score_row_tiles<64>() : score_row_tiles<128>();
+  return static_cast<int64_t>(dm.G) * rows <= row_tiles * kTile && n <= kScoreKeyTiles * kWaves * kTile;
+}
+constexpr int kScoreF32LdsBytes = kWaves * score_row_tiles<64>() * kTile * 8;
+
+template <int D>
+__device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int unit, char* smem) {
+  constexpr int kScoreRowTiles = score_row_tiles<D>();
+  float2* const stats = reinterpret_cast<float2*>(smem);  // [waves][row tiles][16]: maximum, sum
+  const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int col = lane % 16, quad = lane / 16;
+  const int g = unit % a.dm.Hkv, bl = unit / a.dm.Hkv, b = bl / a.dm.L, l = bl % a.dm.L;
+  const int n = a.ks.n_c + a.ks.c, tiles = (n + kTile - 1) / kTile;
+  const int total = a.dm.G * a.rows, row_tiles = (total + kTile - 1) / kTile;
+  const double scale = static_cast<double>(a.dm.scale);
+  Operand<D> q[kScoreRowTiles];
+#pragma unroll
+  for (int rt = 0; rt < kScoreRowTiles; ++rt) {
+    if (rt >= row_tiles) break;  // uniform
+    const int r = min(rt * kTile + col, total - 1), hh = r / a.rows;
+    load_operand(q[rt], row_ptr(a.q, b, l, g * a.dm.G + hh, r - hh * a.rows), lane);
+  }
+  f64x4 s[kScoreKeyTiles][kScoreRowTiles];
+  float m[kScoreRowTiles];
+#pragma unroll
+  for (int rt = 0; rt < kScoreRowTiles; ++rt) m[rt] = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kScoreKeyTiles; ++i) {
+    const int j0 = (w + kWaves * i) * kTile;
+    if (j0 >= n) break;  // wave-uniform
+    Operand<D> k;
+    load_operand(k, cand_ptr(a.ks, b, l, g, min(j0 + col, n - 1)), lane);
+#pragma unroll
+    for (int rt = 0; rt < kScoreRowTiles; ++rt) {
+      if (rt >= row_tiles) break;
+      s[i][rt] = products(k, q[rt]);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        s[i][rt][x] *= scale;
+        if (j0 + 4 * x + quad < n) m[rt] = fmaxf(m[rt], static_cast<float>(s[i][rt][x]));
+      }
+    }
+  }
+  auto sum_over_keys = [&](int rt, double base) {  // of exp(s - base) over the wave's keys of the lane's row
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < kScoreKeyTiles; ++i) {
+      const int j0 = (w + kWaves * i) * kTile;
+      if (j0 >= n) break;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        v += j0 + 4 * x + quad < n ? expf(static_cast<float>(s[i][rt][x] - base)) : 0.f;
+    }
+    return column_sum(v);
+  };
+#pragma unroll
+  for (int rt = 0; rt < kScoreRowTiles; ++rt) {
+    if (rt >= row_tiles) break;
+    const float mr = column_max(m[rt]);
+    const float lr = sum_over_keys(rt, mr == -INFINITY ? 0.0 : static_cast<double>(mr));
+    if (quad == 0) stats[(w * kScoreRowTiles + rt) * kTile + col] = make_float2(mr, lr);
+  }
+  __syncthreads();
+  float acc[kScoreKeyTiles][4];
+#pragma unroll
+  for (int i = 0; i < kScoreKeyTiles; ++i)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[i][x] = 0.f;
+#pragma unroll
+  for (int rt = 0; rt < kScoreRowTiles; ++rt) {
+    if (rt >= row_tiles) break;
+    float2 ps[kWaves];
+    float mm = -INFINITY, lsum = 0.f;
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) {
+      ps[x] = stats[(x * kScoreRowTiles + rt) * kTile + col];
+      mm = fmaxf(mm, ps[x].x);
+    }
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) lsum += ps[x].x == -INFINITY && mm != -INFINITY ? 0.f : ps[x].y * expf(ps[x].x - mm);
+    const double norm = static_cast<double>(mm + logf(lsum));
+    const bool real_row = rt * kTile + col < total;
+#pragma unroll
+    for (int i = 0; i < kScoreKeyTiles; ++i) {
+      if ((w + kWaves * i) * kTile >= n) break;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const float p = expf(static_cast<float>(s[i][rt][x] - norm));
+        acc[i][x] += real_row ? p : 0.f;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kScoreKeyTiles; ++i) {
+    const int j0 = (w + kWaves * i) * kTile;
+    if (j0 >= n) break;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      float v = acc[i][x];
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+      const int j = j0 + 4 * x + quad;
+      if (col == 0 && j < n) a.score[static_cast<int64_t>(unit) * n + j] = v;
+    }
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads) void score_f32_kernel(ScoreF32Args a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  score_f32_body<D>(a, blockIdx.x, smem);
+}
+// A step's attention and instruction score in one launch; neither reads what the other writes.
+template <int D>
+__global__ __launch_bounds__(kThreads) void attn_score_f32_kernel(AttnF32Args a, ScoreF32Args s, int score_blocks) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (static_cast<int>(blockIdx.x) < score_blocks)
+    score_f32_body<D>(s, blockIdx.x, smem);
+  else
+    attn_f32_body<D>(a, blockIdx.x - score_blocks, smem);
+}
+
+AttnF32Args attn_f32_args(const Dims& dm, const View& q, int rows, const Segments& ks, const Segments& vs, int causal,
+                          const View& out, float* lse) {
+  return AttnF32Args{dm, q, out, rows, causal, ks, vs, lse, (rows + kTile - 1) / kTile};
+}
+int attn_f32_blocks(const AttnF32Args& a) { return a.row_blocks * a.dm.Hq * a.dm.B * a.dm.L; }
+
+template <int D>
+hipError_t attn_f32_launch(const AttnF32Args& a, hipStream_t st) {
+  static LdsLimit limit;
+  const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_f32_kernel<D>), attn_f32_lds_bytes<D>());
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(attn_f32_kernel<D>, dim3(attn_f32_blocks(a)), dim3(kThreads), attn_f32_lds_bytes<D>(), st, a);
   return hipGetLastError();
 }
 
 template <int D>
-hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse,
-                           float* score, hipStream_t st) {
-  const int n = ks.n_c + ks.c;
-  dim3 grid((n + kWave - 1) / kWave, dm.Hkv, dm.B * dm.L);
-  hipLaunchKernelGGL(colsum_f32_kernel<D>, grid, dim3(kWave * kColsumWaves), 0, st, dm, q, rows, ks, causal,
-                     lse, score);
+hipError_t attn_score_f32_launch(const AttnF32Args& a, const ScoreF32Args& s, hipStream_t st) {
+  constexpr int kLdsBytes = std::max(attn_f32_lds_bytes<D>(), kScoreF32LdsBytes);
+  static LdsLimit limit;
+  const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_score_f32_kernel<D>), kLdsBytes);
+  if (e != hipSuccess) return e;
+  const int units = s.dm.B * s.dm.L * s.dm.Hkv;
+  hipLaunchKernelGGL(attn_score_f32_kernel<D>, dim3(units + attn_f32_blocks(a)), dim3(kThreads), kLdsBytes, st, a, s, units);
   return hipGetLastError();
 }
 
@@ -249,14 +470,39 @@ hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int caus
 
 hipError_t launch_attn_f32(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
                            hipStream_t st) {
-  return dm.D == 64 ? attn_launch<64>(dm, q, rows, ks, vs, causal, out, lse, st)
-                    : attn_launch<128>(dm, q, rows, ks, vs, causal, out, lse, st);
+  const AttnF32Args a = attn_f32_args(dm, q, rows, ks, vs, causal, out, lse);
+  return dm.D == 64 ? attn_f32_launch<64>(a, st) : attn_f32_launch<128>(a, st);
 }
 
 hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse, float* score,
                              hipStream_t st) {
-  return dm.D == 64 ? colsum_launch<64>(dm, q, rows, ks, causal, lse, score, st)
-                    : colsum_launch<128>(dm, q, rows, ks, causal, lse, score, st);
+  const int n = ks.n_c + ks.c, keys = kColsumKeyTiles * kTile;
+  const auto kern = dm.D == 64 ? colsum_f32_kernel<64> : colsum_f32_kernel<128>;
+  hipLaunchKernelGGL(kern, dim3((n + keys - 1) / keys, dm.Hkv, dm.B * dm.L), dim3(kThreads), 0, st, dm, q, rows, ks, causal,
+                     lse, score);
+  return hipGetLastError();
+}
+
+hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments ks, float* lse_scratch, float* score, hipStream_t st) {
+  if (score_f32_fits(dm, rows, ks.n_c + ks.c)) {
+    const ScoreF32Args a{dm, q, rows, ks, score};
+    const auto kern = dm.D == 64 ? score_f32_kernel<64> : score_f32_kernel<128>;
+    hipLaunchKernelGGL(kern, dim3(dm.B * dm.L * dm.Hkv), dim3(kThreads), kScoreF32LdsBytes, st, a);
+    return hipGetLastError();
+  }
+  // pass 1: row normalisers (log-sum-exp over all candidates, no mask); pass 2: probabilities summed down the rows of each KV group
+  const View none{nullptr, 0, 0, 0, 0};
+  const hipError_t e = launch_attn_f32(dm, q, rows, ks, ks, /*causal=*/0, none, lse_scratch, st);
+  return e != hipSuccess ? e : launch_colsum_f32(dm, q, rows, ks, /*causal=*/0, lse_scratch, score, st);
+}
+
+bool attn_score_f32_in_one_launch(const Dims& dm, int instr_rows, int n) { return score_f32_fits(dm, instr_rows, n); }
+
+hipError_t launch_attn_score_f32(const Dims& dm, View q, Segments ks, Segments vs, View out, View q_instr, int instr_rows,
+                                 float* score, hipStream_t st) {
+  const AttnF32Args a = attn_f32_args(dm, q, ks.c, ks, vs, /*causal=*/1, out, nullptr);
+  const ScoreF32Args s{dm, q_instr, instr_rows, ks, score};
+  return dm.D == 64 ? attn_score_f32_launch<64>(a, s, st) : attn_score_f32_launch<128>(a, s, st);
 }
 
 }  // namespace citrus

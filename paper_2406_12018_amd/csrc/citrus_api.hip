@@ -201,12 +201,15 @@ citrus_status do_instr_score(const citrus_config* c, const Dims& dm, const citru
   if (sums != nullptr) *sums = ScoreSums{score, 1};
   if (mfma_path_supported(c->dtype, dm))
     return hip_status(launch_instr_score_mfma(dm, make_view(q_instr), c->instr_len, ks, lse_ws, scratch.floats, score, st, sums));
-  View none{nullptr, 0, 0, 0, 0};
-  // pass 1: row normalisers (log-sum-exp over all n candidates, no mask)
-  CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q_instr), c->instr_len, ks, ks, /*causal=*/0, none, lse_ws, st)));
-  // pass 2: probabilities summed down the rows of each KV group
-  CITRUS_TRY(hip_status(run_colsum(c, dm, make_view(q_instr), c->instr_len, ks, /*causal=*/0, lse_ws, score, st)));
-  return CITRUS_OK;
+  return hip_status(launch_instr_score_f32(dm, make_view(q_instr), c->instr_len, ks, lse_ws, score, st));
+}
+
+// May a step's chunk attention and its instruction score be one launch?
+bool attn_and_score_fit(const citrus_config* c, const Dims& dm, const Segments& ks, const Segments& vs,
+                        const citrus_tensor& q_instr, const Scratch& scratch) {
+  if (mfma_path_supported(c->dtype, dm))
+    return attn_score_in_one_launch(dm, ks, vs, make_view(q_instr), c->instr_len, scratch.floats);
+  return attn_score_f32_in_one_launch(dm, c->instr_len, ks.n_c + ks.c);
 }
 
 // A cache as the only key segment (the kernels take [cache ; chunk]; the chunk part is empty here and
@@ -232,10 +235,7 @@ citrus_status do_cache_score(const citrus_config* c, const Dims& dm, const citru
     return hip_status(run_colsum(c, dm, make_view(q), rows, ks, /*causal=*/0, lse_given, score, st));
   if (mfma_path_supported(c->dtype, dm))
     return hip_status(launch_instr_score_mfma(dm, make_view(q), rows, ks, lse_ws, scratch.floats, score, st, sums));
-  View none{nullptr, 0, 0, 0, 0};
-  CITRUS_TRY(hip_status(launch_attn_f32(dm, make_view(q), rows, ks, ks, /*causal=*/0, none, lse_ws, st)));
-  CITRUS_TRY(hip_status(run_colsum(c, dm, make_view(q), rows, ks, /*causal=*/0, lse_ws, score, st)));
-  return CITRUS_OK;
+  return hip_status(launch_instr_score_f32(dm, make_view(q), rows, ks, lse_ws, score, st));
 }
 
 int sel_heads(const citrus_config* c) { return c->select_mode == CITRUS_SELECT_PER_LAYER ? 1 : c->kv_heads; }
@@ -852,12 +852,15 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
         const ChunkEvicted t{k_cache_lm, v_cache_lm, &n_c_lm, &cur_lm, cfg->budget_lm, score_lm, idx_lm};
         together = fused && one_launch(cfg, n_c_lm + c) && !timed(3) && !timed(4) && !timed(5);
         if ((status = chunk_evicted_step(t, io, c, together ? &lm : nullptr)) != CITRUS_OK) break;
-      } else if (mfma_path_supported(cfg->dtype, dm) && !timed(1) && !timed(2) && !timed(3) && !timed(4) &&
-                 attn_score_in_one_launch(dm, ks_att, vs, make_view(qi_att), cfg->instr_len, lse_instr.floats)) {
+      } else if (!timed(1) && !timed(2) && !timed(3) && !timed(4) && attn_and_score_fit(cfg, dm, ks_att, vs, qi_att, lse_instr)) {
         scored = true;
-        status = hip_status(launch_attn_score_mfma(dm, make_view(q_att), ks_att, vs, make_view(io.out), q_rope_pos0,
-                                                   rope_base_of(cfg), make_view(qi_att), cfg->instr_len, lse_instr.ptr, score,
-                                                   st, fused ? &own.score : nullptr));
+        if (cfg->dtype == CITRUS_F32)
+          status = hip_status(launch_attn_score_f32(dm, make_view(q_att), ks_att, vs, make_view(io.out), make_view(qi_att),
+                                                    cfg->instr_len, score, st));
+        else
+          status = hip_status(launch_attn_score_mfma(dm, make_view(q_att), ks_att, vs, make_view(io.out), q_rope_pos0,
+                                                     rope_base_of(cfg), make_view(qi_att), cfg->instr_len, lse_instr.ptr, score,
+                                                     st, fused ? &own.score : nullptr));
         if (status != CITRUS_OK) break;
         mark(done, 5);
       } else {

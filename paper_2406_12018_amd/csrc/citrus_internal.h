@@ -41,7 +41,7 @@ struct ScoreSums {
 
 inline citrus_status hip_status(hipError_t e) { return e == hipSuccess ? CITRUS_OK : CITRUS_ERR_DEVICE; }
 
-// ---- vector kernels of the f32 mode, attn_generic.hip ----
+// ---- kernels of the f32 mode, attn_generic.hip ----
 // rows: number of query rows per head; causal != 0 -> row t sees candidates j <= n_c + t.
 // out may be NULL (log-sum-exp only); lse may be NULL.
 hipError_t launch_attn_f32(const Dims& dm, View q, int rows, Segments kseg, Segments vseg, int causal, View out,
@@ -49,6 +49,14 @@ hipError_t launch_attn_f32(const Dims& dm, View q, int rows, Segments kseg, Segm
 // score[b,l,g,j] = sum_{h in g} sum_{t<rows} exp(scale*q.k - lse[b,l,h,t]) (0 where masked)
 hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments kseg, int causal, const float* lse,
                              float* score, hipStream_t st);
+
+// score[b,l,g,j] = sum_{h in g} sum_{t<rows} softmax_j(scale*q.k); lse_scratch: B*L*Hq*rows floats
+hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments kseg, float* lse_scratch, float* score,
+                                  hipStream_t st);
+// The causal attention of kseg.c rows and the instruction score in one launch, with the bits of the two.
+bool attn_score_f32_in_one_launch(const Dims& dm, int instr_rows, int n);
+hipError_t launch_attn_score_f32(const Dims& dm, View q, Segments kseg, Segments vseg, View out, View q_instr, int instr_rows,
+                                 float* score, hipStream_t st);
 
 // ---- bf16 MFMA kernels (head_dim 64 and 128: every bf16 configuration), attn_mfma.hip ----
 bool mfma_path_supported(int dtype, const Dims& dm);
