@@ -125,8 +125,13 @@ def _lib():
     return lib
 
 
+class _ConfigStruct:
+    """What Config keeps beside its fields: the C structure last made of them and the values it was made of."""
+    __slots__ = ("_values", "_struct")
+
+
 @dataclass
-class Config:
+class Config(_ConfigStruct):
     batch: int
     layers: int
     q_heads: int
@@ -159,6 +164,12 @@ class Config:
                 self.cache_capacity = max(self.budget, self.budget_lm)
 
     def c(self) -> CConfig:
+        values = tuple(self.__dict__.values())  # the fields as they are now
+        if getattr(self, "_values", None) != values:
+            self._struct, self._values = self._make_struct(), values
+        return self._struct
+
+    def _make_struct(self) -> CConfig:
         return CConfig(self.batch, self.layers, self.q_heads, self.kv_heads, self.head_dim, self.chunk_len,
                        self.budget, self.budget_lm, self.instr_len, self.cache_capacity, self.dtype,
                        self.cache_mode, self.select_mode, self.start_size, self.lm_ordering, self.score_mode, self.position_shift, self.rope_base,
@@ -188,19 +199,26 @@ def tensor(t: Optional[torch.Tensor]) -> CTensor:
     """[B, L, H, S, d] torch tensor (d contiguous) -> citrus_tensor."""
     if t is None:
         return CTensor(None, 0, 0, 0, 0)
-    if t.dim() != 5 or t.stride(4) != 1:
+    strides = t.stride()
+    if len(strides) != 5 or strides[4] != 1:
         raise ValueError("expected a [B, L, H, S, d] tensor with contiguous last axis")
-    return CTensor(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2), t.stride(3))
+    return CTensor(t.data_ptr(), strides[0], strides[1], strides[2], strides[3])
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
+# The handle of the current stream without the Stream object around it (2.7 us per call), where torch offers it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(status: int, where: str):
@@ -340,8 +358,10 @@ def citrus_score_gather(cfg: Config, score, idx, m: int, acc_new, stream=None, n
 
 def citrus_topk_select(cfg: Config, score, k: int, idx=None, stream=None, n: Optional[int] = None):
     n = score.shape[-1] if n is None else n
-    if idx is None:
-        idx = torch.full((cfg.batch, cfg.layers, cfg.sel_heads, k), -1, dtype=torch.int32, device=score.device)
+    if idx is None:  # positions behind the last candidate stay -1; where there are none, every position is written
+        shape = (cfg.batch, cfg.layers, cfg.sel_heads, k)
+        idx = (torch.empty(shape, dtype=torch.int32, device=score.device) if n >= k else
+               torch.full(shape, -1, dtype=torch.int32, device=score.device))
     cc = cfg.c()
     st = _lib().citrus_topk_select(C.byref(cc), _ptr(score), n, k, _ptr(idx), None, 0, _stream(stream))
     _check(st, "citrus_topk_select")
