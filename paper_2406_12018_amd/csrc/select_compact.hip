@@ -439,6 +439,8 @@ struct EvictArgs {
   int first_blocks;  // workgroups of job 0
 };
 constexpr int kGatherRows = 4;  // rows of a thread in flight
+// narrow instances stay within the LDS a launch may have without asking, whatever they keep (up to 6144 rows)
+static_assert(sizeof(SelectLds<8, kSelThreads>) + 6 * kWideThreads * sizeof(int32_t) <= 65536);
 
 template <int ITEMS, int THREADS, Scores FORM>
 __global__ __launch_bounds__(THREADS) void evict_kernel(EvictArgs args) {
@@ -628,6 +630,14 @@ hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int c
     kern = sums ? evict_kernel<8, kSelThreads, kSums> : evict_kernel<8, kSelThreads, kOne>;
   } else if (n_max > 2 * kSelThreads) {
     kern = sums ? evict_kernel<5, kSelThreads, kSums> : evict_kernel<5, kSelThreads, kOne>;
+  }
+  // One part per unit (more units than compute units) of a budget above 5344 rows: the selection's LDS and the kept rows
+  // together are more than the 64 KB a launch may have without asking.
+  constexpr int kUnasked = 65536;
+  if (wide && static_cast<int>(sizeof(SelectLds<6, kWideThreads>)) + lds > kUnasked) {
+    static LdsLimit limit[2];
+    const hipError_t e = raise_lds_limit(limit[sums], reinterpret_cast<const void*>(kern), lds);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), lds, st, args);
   return hipGetLastError();
