@@ -330,7 +330,7 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int unit, 
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int col = lane % 16, quad = lane / 16;
   const int g = unit % a.dm.Hkv, bl = unit / a.dm.Hkv, b = bl / a.dm.L, l = bl % a.dm.L;
-  const int n = a.ks.n_c + a.ks.c, tiles = (n + kTile - 1) / kTile;
+  const int n = a.ks.n_c + a.ks.c;
   const int total = a.dm.G * a.rows, row_tiles = (total + kTile - 1) / kTile;
   const double scale = static_cast<double>(a.dm.scale);
   Operand<D> q[kScoreRowTiles];
