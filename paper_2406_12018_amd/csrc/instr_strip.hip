@@ -109,9 +109,14 @@ bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segmen
   // 85 | 117; 2560 keys, 32 layers (2048) 101 | 106; up to eight.  With one strip per KV head the two-pass kernel has one
   // workgroup per KV head too, and at head_dim 64 fits more of them: 700 keys, 16 rows, 32 layers (256) 11.6 | 13.9, 64
   // layers (512) 23.1 | 20.1.
+  // Four 64-row strips per KV head against one round of the two-pass kernel with its 256 rows: up to three workgroups per
+  // compute unit.  us per document of 4096 tokens, strips | two passes: 25 layers (800 workgroups) 2531 | 2484, 28 layers
+  // (896) 2590 | 2559, 32 layers (1024), 640 keys 2328 | 2282; with two strips per KV head the two are level (512 units,
+  // 128 rows: 2317 | 2284, 3167 | 3206), and 512 rows take the two-pass path two launches (128 units: 2577 | 2749).
   const int per_strip = strip_rows(dm, rows, n);
   const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, strips = (dm.G * rows + per_strip - 1) / per_strip;
-  const int rounds = dm.D == 128 ? 4 : strips > 1 ? 8 : 1;
+  const bool one_round = per_strip == 64 && dm.G * rows <= 256 && units <= compute_units();
+  const int rounds = dm.D == 128 ? (one_round ? 3 : 4) : strips > 1 ? 8 : 1;
   if (units * strips > rounds * compute_units()) return false;
   if (static_cast<size_t>(units * strips) * n > workspace_floats) return false;  // the caller's block was sized for less
   // per-lane byte offsets into the group's instruction rows and into a key segment are 32-bit

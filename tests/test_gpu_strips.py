@@ -24,6 +24,9 @@ CASES = [
     (5, 32, 8, 51, 300, 213),    # 204 rows: 32-row strips no longer fit side by side, 64-row strips with a rest of 12
     (1, 64, 2, 128, 500, 37),    # 4096 rows per KV head
     (1, 64, 2, 129, 500, 37),    # 4128: two passes
+    (24, 32, 8, 64, 100, 60),    # 192 KV heads of four strips: strips
+    (25, 32, 8, 64, 100, 60),    # 200: one round of the two-pass kernel at head_dim 128
+    (32, 32, 8, 49, 100, 61),    # 256 of 196 rows
     (40, 8, 8, 40, 100, 50),     # one head per KV head, 320 KV heads
 ]
 
