@@ -224,7 +224,8 @@ __device__ __forceinline__ void attn_f32_body(const AttnF32Args& a, int block, c
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int x = 0; x < kWaves; ++x) {
-    if (mw[x] == -INFINITY && mm != -INFINITY) continue;  // a wave without a key the row sees
+    // A wave without a key the row sees adds 0 * 0.  So does one whose logits are all -inf, and one whose logits are NaN
+    // (which a maximum passes over) adds its NaN: no part is left out.
     const float f = expf(mw[x] - mm);
     sum += l_s[x * kTile + r] * f;
     if (values && e < D) o += *reinterpret_cast<const f32x4*>(o_s + (x * kTile + r) * kPitch + e) * f;
@@ -397,7 +398,7 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int unit, 
       mm = fmaxf(mm, ps[x].x);
     }
 #pragma unroll
-    for (int x = 0; x < kWaves; ++x) lsum += ps[x].x == -INFINITY && mm != -INFINITY ? 0.f : ps[x].y * expf(ps[x].x - mm);
+    for (int x = 0; x < kWaves; ++x) lsum += ps[x].y * expf(ps[x].x - mm);  // a wave's NaN is not left out, as in attn_f32_body
     const double norm = static_cast<double>(mm + logf(lsum));
     const bool real_row = rt * kTile + col < total;
 #pragma unroll

@@ -74,3 +74,23 @@ def test_step_against_f64(case, head_dim):
         assert not got[:, :, :, c // 2:, 3].isfinite().any()
         others = [x for x in range(head_dim) if x != 3]
         close(got[:, :, :, c // 2:][..., others], torch.matmul(p, v_all)[:, :, :, c // 2:][..., others])
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("n_c,c", [(0, 33), (0, 17), (40, 1), (96, 33), (500, 40)], ids=str)
+def test_a_key_that_is_nan_reaches_every_row_that_sees_it(n_c, c, head_dim):
+    """The last key is the only one of its tile, and in the smaller cases of its wave: a maximum passes over NaN, the sums must
+    not.  A row's softmax over a NaN logit is NaN throughout; the rows in front of the key do not see it."""
+    print(f"f32 NaN key {n_c} + {c} head_dim {head_dim}", flush=True)
+    g = torch.Generator(device="cpu").manual_seed(3)
+    mk = lambda *shape: torch.randn(shape, generator=g).to(DEV)
+    q, qi, k, v = mk(1, 1, 4, c, head_dim), mk(1, 1, 4, 8, head_dim), mk(1, 1, 2, c, head_dim), mk(1, 1, 2, c, head_dim)
+    kc, vc = mk(1, 1, 2, n_c + 1, head_dim), mk(1, 1, 2, n_c + 1, head_dim)
+    k[:, :, :, -1, 5] = float("nan")
+    cfg = api.Config(batch=1, layers=1, q_heads=4, kv_heads=2, head_dim=head_dim, chunk_len=c, budget=n_c + 1, instr_len=8, dtype=api.F32)
+    ws = api.alloc_workspace(cfg)
+    lse = torch.empty((1, 1, 4, c), device=DEV)
+    out = api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v, lse=lse, workspace=ws)
+    assert out[:, :, :, -1].isnan().all() and lse[:, :, :, -1].isnan().all()
+    assert out[:, :, :, :-1].isfinite().all() and lse[:, :, :, :-1].isfinite().all()
+    assert api.citrus_instr_score(cfg, qi, kc, n_c, k, workspace=ws).isnan().all()
