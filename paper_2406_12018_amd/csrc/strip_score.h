@@ -81,6 +81,13 @@ __device__ inline void wait_all_but_newest() {
   asm volatile("" ::: "memory");
 }
 
+// 2^(reference - maximum).  A part without a key has the reference -inf and counts 0 times its sum of 0; so has a part whose
+// logits are NaN (a maximum passes over them), and its NaN has to reach the row's sum.  A row without any finite logit
+// has the maximum -inf and a sum of 0 or NaN: its weights come out NaN, as a softmax gives.
+__device__ inline float against_max(float reference, float maximum) {
+  return reference == maximum ? 1.f : __builtin_amdgcn_exp2f(reference - maximum);
+}
+
 template <int D, int ROW_TILES>
 constexpr int strip_lds_bytes() {
   typedef StripGeo<D> T;
@@ -300,7 +307,7 @@ __device__ __forceinline__ void strip_score_body(const StripArgs& a, int block, 
     float lsum = 0.f;
 #pragma unroll
     for (int x = 0; x < kStripWaves; ++x)  // fixed order: every lane of the row gets the same bits
-      lsum += ps[x].x == -INFINITY ? 0.f : ps[x].y * __builtin_amdgcn_exp2f(ps[x].x - mm);
+      lsum += ps[x].y * against_max(ps[x].x, mm);
     m_row[rt] = mm;
     const bool real_row = strip * kStripRows + 32 * rt + col < total_rows;
     inv_row[rt] = real_row ? 1.f / lsum : 0.f;  // padding rows carry no weight
@@ -315,7 +322,7 @@ __device__ __forceinline__ void strip_score_body(const StripArgs& a, int block, 
     float v[16];
 #pragma unroll
     for (int rt = 0; rt < ROW_TILES; ++rt) {
-      const float f = ref[i][rt] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ref[i][rt] - m_row[rt]) * inv_row[rt];
+      const float f = against_max(ref[i][rt], m_row[rt]) * inv_row[rt];
 #pragma unroll
       for (int x = 0; x < 16; ++x) {
         const float p = e[i][rt][x] * f;

@@ -47,3 +47,24 @@ def test_scores_against_f64(case, head_dim):
     qs = q.double().reshape(1, L, Hkv, Hq // Hkv * rows, head_dim)
     want = torch.softmax(torch.matmul(qs, keys.transpose(-1, -2).contiguous()) / head_dim ** 0.5, dim=-1).sum(dim=-2)
     torch.testing.assert_close(score.double(), want, rtol=8e-5 if head_dim == 128 else 3e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), float("-inf")], ids=str)
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("rows,n_c,c", [(8, 0, 33), (8, 160, 40), (64, 1200, 70), (16, 0, 1)], ids=str)
+def test_logits_that_are_not_finite(rows, n_c, c, head_dim, bad):
+    """The last key's logits are not finite; in the first case they are all its wave has.  A row whose logit is NaN or +inf there
+    has no weight anywhere that is a number, as a softmax in f64 has it; -inf is a weight of 0 unless there is no other key."""
+    print(f"strip scores, last key {bad}, {rows} rows, {n_c} + {c} head_dim {head_dim}", flush=True)
+    g = torch.Generator(device="cpu").manual_seed(9)
+    mk = lambda *shape: torch.randn(shape, generator=g).to(torch.bfloat16).to(DEV)
+    q, kc, k = mk(1, 1, 4, rows, head_dim), mk(1, 1, 2, n_c + 1, head_dim), mk(1, 1, 2, c, head_dim)
+    q[..., 3] = q[..., 3].abs() + 0.5  # one sign: the logits are `bad` for every row
+    k[:, :, :, -1, 3] = bad
+    cfg = api.Config(batch=1, layers=1, q_heads=4, kv_heads=2, head_dim=head_dim, chunk_len=c, budget=n_c + 1, instr_len=rows)
+    score = api.citrus_instr_score(cfg, q, kc, n_c, k, workspace=api.alloc_workspace(cfg))
+    if bad == float("-inf") and n_c + c > 1:
+        assert (score[..., -1] == 0).all() and score.isfinite().all()
+        torch.testing.assert_close(score.double().sum(-1), torch.full((1, 1, 2), 2.0 * rows, device=DEV, dtype=torch.double), rtol=1e-5, atol=0)
+    else:
+        assert score.isnan().all()
