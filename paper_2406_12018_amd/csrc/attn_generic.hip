@@ -240,7 +240,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnF32Args& a, int block, c
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_f32_kernel(AttnF32Args a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  attn_f32_body<D>(a, blockIdx.x, smem);
+  attn_f32_body<D>(a, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), smem);
 }
 
 // Column sums: score[g, j] = sum over the query rows of the KV group of exp(s - lse).  A workgroup owns two tiles of sixteen
@@ -429,7 +429,7 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int unit, 
 template <int D>
 __global__ __launch_bounds__(kThreads) void score_f32_kernel(ScoreF32Args a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  score_f32_body<D>(a, blockIdx.x, smem);
+  score_f32_body<D>(a, blockIdx.x + gridDim.x * blockIdx.y, smem);
 }
 // A step's attention and instruction score in one launch; neither reads what the other writes.
 template <int D>
@@ -445,14 +445,16 @@ AttnF32Args attn_f32_args(const Dims& dm, const View& q, int rows, const Segment
                           const View& out, float* lse) {
   return AttnF32Args{dm, q, out, rows, causal, ks, vs, lse, (rows + kTile - 1) / kTile};
 }
-int attn_f32_blocks(const AttnF32Args& a) { return a.row_blocks * a.dm.Hq * a.dm.B * a.dm.L; }
+// A grid's dimension has less than 2^32 work-items: one of workgroups x heads x layers has more dimensions than one.
+dim3 attn_f32_grid(const AttnF32Args& a) { return dim3(a.row_blocks, a.dm.Hq, a.dm.B * a.dm.L); }
+int64_t attn_f32_blocks(const Dims& dm, int rows) { return static_cast<int64_t>((rows + kTile - 1) / kTile) * dm.Hq * dm.B * dm.L; }
 
 template <int D>
 hipError_t attn_f32_launch(const AttnF32Args& a, hipStream_t st) {
   static LdsLimit limit;
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_f32_kernel<D>), attn_f32_lds_bytes<D>());
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_f32_kernel<D>, dim3(attn_f32_blocks(a)), dim3(kThreads), attn_f32_lds_bytes<D>(), st, a);
+  hipLaunchKernelGGL(attn_f32_kernel<D>, attn_f32_grid(a), dim3(kThreads), attn_f32_lds_bytes<D>(), st, a);
   return hipGetLastError();
 }
 
@@ -463,7 +465,8 @@ hipError_t attn_score_f32_launch(const AttnF32Args& a, const ScoreF32Args& s, hi
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_score_f32_kernel<D>), kLdsBytes);
   if (e != hipSuccess) return e;
   const int units = s.dm.B * s.dm.L * s.dm.Hkv;
-  hipLaunchKernelGGL(attn_score_f32_kernel<D>, dim3(units + attn_f32_blocks(a)), dim3(kThreads), kLdsBytes, st, a, s, units);
+  const int blocks = units + static_cast<int>(attn_f32_blocks(a.dm, a.rows));
+  hipLaunchKernelGGL(attn_score_f32_kernel<D>, dim3(blocks), dim3(kThreads), kLdsBytes, st, a, s, units);
   return hipGetLastError();
 }
 
@@ -488,7 +491,7 @@ hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments ks,
   if (score_f32_fits(dm, rows, ks.n_c + ks.c)) {
     const ScoreF32Args a{dm, q, rows, ks, score};
     const auto kern = dm.D == 64 ? score_f32_kernel<64> : score_f32_kernel<128>;
-    hipLaunchKernelGGL(kern, dim3(dm.B * dm.L * dm.Hkv), dim3(kThreads), kScoreF32LdsBytes, st, a);
+    hipLaunchKernelGGL(kern, dim3(dm.Hkv, dm.B * dm.L), dim3(kThreads), kScoreF32LdsBytes, st, a);
     return hipGetLastError();
   }
   // pass 1: row normalisers (log-sum-exp over all candidates, no mask); pass 2: probabilities summed down the rows of each KV group
@@ -497,7 +500,10 @@ hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments ks,
   return e != hipSuccess ? e : launch_colsum_f32(dm, q, rows, ks, /*causal=*/0, lse_scratch, score, st);
 }
 
-bool attn_score_f32_in_one_launch(const Dims& dm, int instr_rows, int n) { return score_f32_fits(dm, instr_rows, n); }
+bool attn_score_f32_in_one_launch(const Dims& dm, int rows, int instr_rows, int n) {
+  constexpr int64_t kMostBlocks = (int64_t{1} << 32) / kThreads - 1;  // of a one-dimensional grid
+  return score_f32_fits(dm, instr_rows, n) && attn_f32_blocks(dm, rows) + static_cast<int64_t>(dm.B) * dm.L * dm.Hkv <= kMostBlocks;
+}
 
 hipError_t launch_attn_score_f32(const Dims& dm, View q, Segments ks, Segments vs, View out, View q_instr, int instr_rows,
                                  float* score, hipStream_t st) {

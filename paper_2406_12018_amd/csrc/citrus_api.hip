@@ -209,7 +209,7 @@ bool attn_and_score_fit(const citrus_config* c, const Dims& dm, const Segments& 
                         const citrus_tensor& q_instr, const Scratch& scratch) {
   if (mfma_path_supported(c->dtype, dm))
     return attn_score_in_one_launch(dm, ks, vs, make_view(q_instr), c->instr_len, scratch.floats);
-  return attn_score_f32_in_one_launch(dm, c->instr_len, ks.n_c + ks.c);
+  return attn_score_f32_in_one_launch(dm, ks.c, c->instr_len, ks.n_c + ks.c);
 }
 
 // A cache as the only key segment (the kernels take [cache ; chunk]; the chunk part is empty here and

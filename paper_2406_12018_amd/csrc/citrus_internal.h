@@ -54,7 +54,7 @@ hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments kseg, in
 hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments kseg, float* lse_scratch, float* score,
                                   hipStream_t st);
 // The causal attention of kseg.c rows and the instruction score in one launch, with the bits of the two.
-bool attn_score_f32_in_one_launch(const Dims& dm, int instr_rows, int n);
+bool attn_score_f32_in_one_launch(const Dims& dm, int rows, int instr_rows, int n);
 hipError_t launch_attn_score_f32(const Dims& dm, View q, Segments kseg, Segments vseg, View out, View q_instr, int instr_rows,
                                  float* score, hipStream_t st);
 

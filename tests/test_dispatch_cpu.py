@@ -1,0 +1,119 @@
+"""Host side of the library without a GPU: which kernels a call launches, with which grids and LDS, and what is left when a
+launch fails.  The calls run in a child process in which fake_hip.cpp stands in front of the HIP runtime; nothing reaches a
+device.  This file is the child's program too."""
+
+import ctypes as C
+import inspect
+import json
+import os
+import re
+import subprocess
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+# ---- in the child ----
+class Fake:
+    """What the binding reads of a tensor: an address and strides (those of a dense one)."""
+
+    def __init__(self, *shape, at=1 << 20, strides=None):
+        self.shape, self.at = shape, at
+        self.strides = strides or tuple(_product(shape[i + 1:]) for i in range(len(shape)))
+
+    def stride(self, i=None):
+        return self.strides if i is None else self.strides[i]
+
+    def dim(self):
+        return len(self.shape)
+
+    def __getitem__(self, i):  # of the first axis
+        return Fake(*self.shape[1:], at=self.at + i * self.strides[0] * 4, strides=self.strides[1:])
+
+    def data_ptr(self):
+        return self.at
+
+    def numel(self):
+        return _product(self.shape)
+
+
+def _product(xs):
+    p = 1
+    for x in xs:
+        p *= x
+    return p
+
+
+class Recorder:
+    def __init__(self, lib):
+        self.lib = lib
+        lib.fake_log.restype = C.c_char_p
+
+    def __call__(self, call, fail_at=-1):
+        """The launches of a call: [kernel, grid, workgroup, dynamic LDS], and ["lds", bytes, kernel] for a raised limit."""
+        self.lib.fake_reset(fail_at)
+        call()
+        out = []
+        for line in self.lib.fake_log().decode().splitlines():
+            if line.startswith("lds "):
+                _, size, name = line.split(" ", 2)
+                out.append(["lds", int(size), short(name)])
+            else:
+                grid, block, shared, name = re.fullmatch(r"launch \[(.*?)\] \[(.*?)\] (\d+) (.*)", line).groups()
+                out.append([short(name), [int(x) for x in grid.split()], [int(x) for x in block.split()], int(shared)])
+        return out
+
+
+def short(name):
+    """`evict_kernel<6, 1024, ...>` of a demangled signature."""
+    name = re.sub(r"^void ", "", name).replace("citrus::(anonymous namespace)::", "")
+    return name[:name.rindex("(")] if name.endswith(")") else name
+
+
+def workspace(api, cfg, spare=0):
+    return Fake(api.workspace_bytes(cfg) + spare, at=1 << 30)
+
+
+# ---- in the test ----
+def in_child(body, tmp_path, **kw):
+    """Runs `body(api, launches, **kw)` of this file in a child and returns what it returns."""
+    shim = str(tmp_path / "fake_hip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", shim, os.path.join(ROOT, "tests", "fake_hip.cpp")])
+    done = subprocess.run([sys.executable, os.path.abspath(__file__), shim, body.__name__, json.dumps(kw)], cwd=ROOT,
+                          stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
+    assert done.returncode == 0, done.stderr[-3000:]
+    return json.loads(done.stdout.splitlines()[-1])
+
+
+def f32_of_many_heads(api, launches):
+    """The most heads a configuration may have: 65535 layers of 129 heads, one query row each."""
+    L, H = 65535, 129
+    cfg = api.Config(batch=1, layers=L, q_heads=H, kv_heads=H, head_dim=64, chunk_len=1, budget=4, instr_len=1, dtype=api.F32)
+    q, cache, ws = Fake(1, L, H, 1, 64), Fake(1, L, H, 4, 64, at=1 << 21), workspace(api, cfg)
+    state = api.DocumentState([cache, Fake(1, L, H, 4, 64, at=1 << 22)], [cache, Fake(1, L, H, 4, 64, at=1 << 22)])
+    doc = api.resident_doc(cfg, q, q, q, Fake(1, 1, L, H, 1, 64), q)
+    return [launches(lambda: api.citrus_chunk_attn(cfg, q, cache, cache, 3, q, q, out=q, stream=0)),
+            launches(lambda: api.citrus_decode_step(cfg, q, q, q, cache, cache, 3, out=q, workspace=ws, stream=0)),
+            launches(lambda: api.citrus_instr_score(cfg, q, cache, 3, q, score=q, workspace=ws, stream=0)),
+            launches(lambda: api.citrus_process_document(cfg, state, ws, doc=doc, stream=0))]
+
+
+def test_f32_launches_of_many_heads_stay_within_a_grid(tmp_path):
+    """8.45 million heads of a row each: more than 2^32 work-items if the grid were one-dimensional."""
+    attn, decode, score, document = in_child(f32_of_many_heads, tmp_path)
+    names = lambda launches: [x[0] for x in launches if x[0] != "lds"]
+    assert names(attn) == ["attn_f32_kernel<64>"] and names(decode) == ["attn_f32_kernel<64>", "compact_kernel"]
+    assert names(score) == ["score_f32_kernel<64>"] and names(document)[:2] == ["attn_f32_kernel<64>", "score_f32_kernel<64>"]
+    for launch in attn + decode + score + document:
+        if launch[0] in ("attn_f32_kernel<64>", "score_f32_kernel<64>"):
+            assert _product(launch[1]) == 65535 * 129
+
+
+if __name__ == "__main__":
+    fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
+    sys.path.insert(0, ROOT)
+    import paper_2406_12018_amd as api_
+
+    body_ = globals()[sys.argv[2]]
+    assert inspect.isfunction(body_)
+    print(json.dumps(body_(api_, Recorder(fake), **json.loads(sys.argv[3]))))
