@@ -439,8 +439,9 @@ struct EvictArgs {
   int first_blocks;  // workgroups of job 0
 };
 constexpr int kGatherRows = 4;  // rows of a thread in flight
-// narrow instances stay within the LDS a launch may have without asking, whatever they keep (up to 6144 rows)
-static_assert(sizeof(SelectLds<8, kSelThreads>) + 6 * kWideThreads * sizeof(int32_t) <= 65536);
+constexpr int kMostKeptBytes = 6 * kWideThreads * sizeof(int32_t);  // the candidates of the rows that a unit keeps
+// narrow instances stay within the LDS a launch may have without asking, whatever they keep
+static_assert(sizeof(SelectLds<8, kSelThreads>) + kMostKeptBytes <= 65536);
 
 template <int ITEMS, int THREADS, Scores FORM>
 __global__ __launch_bounds__(THREADS) void evict_kernel(EvictArgs args) {
@@ -636,7 +637,7 @@ hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int c
   constexpr int kUnasked = 65536;
   if (wide && static_cast<int>(sizeof(SelectLds<6, kWideThreads>)) + lds > kUnasked) {
     static LdsLimit limit[2];
-    const hipError_t e = raise_lds_limit(limit[sums], reinterpret_cast<const void*>(kern), lds);
+    const hipError_t e = raise_lds_limit(limit[sums], reinterpret_cast<const void*>(kern), kMostKeptBytes);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(threads), lds, st, args);

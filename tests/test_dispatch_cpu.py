@@ -109,6 +109,26 @@ def test_f32_launches_of_many_heads_stay_within_a_grid(tmp_path):
             assert _product(launch[1]) == 65535 * 129
 
 
+def evictions_of_large_budgets(api, launches, budgets):
+    out = []
+    for k in budgets:
+        L, H, n, d = 40, 8, 6144, 64
+        cfg = api.Config(batch=1, layers=L, q_heads=H, kv_heads=H, head_dim=d, chunk_len=8, budget=k, instr_len=2, cache_capacity=n)
+        q, cache, new, ws = Fake(1, L, H, 2, d), Fake(1, L, H, n, d), Fake(1, L, H, k, d, at=1 << 22), workspace(api, cfg)
+        out += launches(lambda: api.citrus_evict_cache(cfg, q, cache, cache, n, k, new, new, workspace=ws, stream=0))
+    return out
+
+
+def test_a_kernel_asks_for_one_lds_limit_whatever_the_budget(tmp_path):
+    """Two threads that ask for different limits could lower each other's: the smaller may arrive last."""
+    calls = in_child(evictions_of_large_budgets, tmp_path, budgets=[5400, 5700, 6100])
+    asked = [x for x in calls if x[0] == "lds" and "evict_kernel" in x[2]]
+    used = [x[3] for x in calls if "evict_kernel" in x[0]]
+    assert sorted(set(used)) == [4 * k for k in (5400, 5700, 6100)]
+    assert len({x[1] for x in asked}) == 1 and asked[0][1] >= max(used)
+    assert len({x[2] for x in asked}) == len(asked)  # once per kernel
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)
