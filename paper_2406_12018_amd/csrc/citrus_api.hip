@@ -749,10 +749,11 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
     const int kept = n_ranked < t.budget ? n_ranked : t.budget, appended = n_old + c - n_ranked;
     const Eviction e{kl, vl, {t.score, 1}, n_ranked, t.budget, cfg->start_size, appended, t.idx, make_view(t.k[to]),
                      make_view(t.v[to]), nullptr, nullptr, 0};
-    if (later != nullptr)
+    if (later != nullptr) {  // the cache moves on when the caller has launched it
       *later = e;
-    else
-      CITRUS_TRY(evict(e, t.score, one_launch(cfg, n_ranked) && !timed(3), 3, st));
+      return CITRUS_OK;
+    }
+    CITRUS_TRY(evict(e, t.score, one_launch(cfg, n_ranked) && !timed(3), 3, st));
     *t.len = kept + appended;
     *t.cur = to;
     return CITRUS_OK;
@@ -873,6 +874,10 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       if (together) {
         const Eviction both[2] = {lm, own};
         status = hip_status(launch_evict(elem_bytes(cfg->dtype), dm, both, 2, st));
+        if (status == CITRUS_OK) {
+          n_c_lm = (lm.n < lm.k ? lm.n : lm.k) + lm.appended;
+          cur_lm ^= 1;
+        }
         mark(done, 7);
       } else {
         status = evict(own, score, fused, 6, st);

@@ -129,6 +129,39 @@ def test_a_kernel_asks_for_one_lds_limit_whatever_the_budget(tmp_path):
     assert len({x[2] for x in asked}) == len(asked)  # once per kernel
 
 
+def two_caches_with_a_failing_launch(api, launches):
+    """A document of two chunks; the launch that fails, and what the call then leaves."""
+    H, d, c, k = 4, 64, 32, 48
+    cfg = api.Config(batch=1, layers=1, q_heads=H, kv_heads=H, head_dim=d, chunk_len=c, budget=k, budget_lm=k, instr_len=8,
+                     cache_mode=api.CACHE_DUAL)
+    q, cache, ws = Fake(1, 1, H, 2 * c, d), lambda i: Fake(1, 1, H, k, d, at=(4 + i) << 20), workspace(api, cfg)
+    doc = api.resident_doc(cfg, q, q, q, Fake(2, 1, 1, H, 8, d), q)
+    out = []
+    for fail_at in range(-1, 8):
+        state = api.DocumentState([cache(0), cache(1)], [cache(2), cache(3)], k_cache_lm=[cache(4), cache(5)], v_cache_lm=[cache(6), cache(7)])
+
+        def call():
+            try:
+                api.citrus_process_document(cfg, state, ws, doc=doc, stream=0)
+            except api.CitrusError as e:
+                assert e.status == 5
+        names = [x[0] for x in launches(call, fail_at) if x[0] != "lds"]
+        out.append([names, state.cache_len, state.buffer_index, state.cache_len_lm, state.buffer_index_lm])
+    return out
+
+
+def test_a_failed_step_leaves_both_caches_in_front_of_it(tmp_path):
+    """The caches' evictions share the step's last launch.  A cache whose eviction was not launched has not moved on: its other
+    buffer holds nothing."""
+    whole, *failing = in_child(two_caches_with_a_failing_launch, tmp_path)
+    per_step = len(whole[0]) // 2
+    assert whole[0][per_step - 1].startswith("evict_kernel") and whole[1:] == [48, 0, 48, 0]
+    assert len(failing) == 2 * per_step
+    for fail_at, (names, *state) in enumerate(failing):
+        assert names == whole[0][:fail_at]
+        assert state == ([0, 0, 0, 0] if fail_at < per_step else [32, 1, 32, 1]), fail_at
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)
