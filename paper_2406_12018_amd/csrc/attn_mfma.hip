@@ -1587,7 +1587,7 @@ hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, flo
   const int n = ks.n_c + ks.c;
   // a short text over a candidate set that a workgroup's registers can hold one row strip of: one product
   // per (row, key)
-  if (instr_strip_supported(dm, q, rows, ks, workspace_floats))
+  if (instr_strip_supported(dm, q, rows, ks))
     return launch_instr_strip(dm, q, rows, ks, workspace, workspace_floats, score, st, sums);
   // otherwise two passes over the keys; few query rows per KV group: one fused launch
   const int total_rows = dm.G * rows;
@@ -1626,11 +1626,10 @@ hipError_t launch_attn_mfma(const Dims& dm, View q, Segments ks, Segments vs, Vi
 }
 
 // Worth it, and possible, while the workgroups of both fit the chip side by side.
-bool attn_score_in_one_launch(const Dims& dm, const Segments& ks, const Segments& vs, const View& q_instr, int instr_rows,
-                              size_t workspace_floats) {
+bool attn_score_in_one_launch(const Dims& dm, const Segments& ks, const Segments& vs, const View& q_instr, int instr_rows) {
   const int64_t strips = (static_cast<int64_t>(dm.G) * instr_rows + 31) / 32;
   return attn_workgroups(dm, ks.c, kWaves) + strips * dm.Hkv * dm.B * dm.L <= compute_units() && attn_segments_fit(ks, vs) &&
-         instr_strip_supported(dm, q_instr, instr_rows, ks, workspace_floats);
+         instr_strip_supported(dm, q_instr, instr_rows, ks);
 }
 
 hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments ks, Segments vs, View out, int q_rope_pos0, float rope_base,

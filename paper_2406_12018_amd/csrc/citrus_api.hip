@@ -97,7 +97,7 @@ citrus_status check_lengths(const citrus_config* c, int cache_len, int chunk_len
   return CITRUS_OK;
 }
 
-// A block of float scratch and what it holds: the scorer picks its kernel by what fits.
+// A block of float scratch and what it holds.
 struct Scratch {
   float* ptr;
   size_t floats;
@@ -206,9 +206,8 @@ citrus_status do_instr_score(const citrus_config* c, const Dims& dm, const citru
 
 // May a step's chunk attention and its instruction score be one launch?
 bool attn_and_score_fit(const citrus_config* c, const Dims& dm, const Segments& ks, const Segments& vs,
-                        const citrus_tensor& q_instr, const Scratch& scratch) {
-  if (mfma_path_supported(c->dtype, dm))
-    return attn_score_in_one_launch(dm, ks, vs, make_view(q_instr), c->instr_len, scratch.floats);
+                        const citrus_tensor& q_instr) {
+  if (mfma_path_supported(c->dtype, dm)) return attn_score_in_one_launch(dm, ks, vs, make_view(q_instr), c->instr_len);
   return attn_score_f32_in_one_launch(dm, ks.c, c->instr_len, ks.n_c + ks.c);
 }
 
@@ -853,7 +852,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
         const ChunkEvicted t{k_cache_lm, v_cache_lm, &n_c_lm, &cur_lm, cfg->budget_lm, score_lm, idx_lm};
         together = fused && one_launch(cfg, n_c_lm + c) && !timed(3) && !timed(4) && !timed(5);
         if ((status = chunk_evicted_step(t, io, c, together ? &lm : nullptr)) != CITRUS_OK) break;
-      } else if (!timed(1) && !timed(2) && !timed(3) && !timed(4) && attn_and_score_fit(cfg, dm, ks_att, vs, qi_att, lse_instr)) {
+      } else if (!timed(1) && !timed(2) && !timed(3) && !timed(4) && attn_and_score_fit(cfg, dm, ks_att, vs, qi_att)) {
         scored = true;
         if (cfg->dtype == CITRUS_F32)
           status = hip_status(launch_attn_score_f32(dm, make_view(q_att), ks_att, vs, make_view(io.out), make_view(qi_att),

@@ -76,8 +76,8 @@ constexpr int kMaxKeySplits = 8;
 // at most n keys (the launcher picks its kernel by the call's own shape, and the kernels' needs do not grow
 // together: a block sized for the largest shape alone could be too small for a smaller one).
 size_t instr_score_mfma_workspace_floats(const Dims& dm, int rows, int n);
-// `workspace_floats`: what the block behind `workspace` holds; a kernel whose scratch does not fit is not
-// chosen, and hipErrorInvalidValue comes back if none fits.
+// `workspace_floats`: what the block behind `workspace` holds; the kernel is chosen by the call's shape alone, and
+// hipErrorInvalidValue comes back if its scratch does not fit.
 // sums (optional): what it points to is {score, 1}; a kernel that forms partial sums per key may leave them in the
 // workspace and describe them there instead of adding them up to `score`.
 hipError_t launch_instr_score_mfma(const Dims& dm, View q, int rows, Segments kseg, float* workspace,
@@ -87,8 +87,8 @@ hipError_t launch_instr_score_mfma(const Dims& dm, View q, int rows, Segments ks
 int compute_units();
 
 // ---- instruction score with one q.k product per (row, key): row strips kept on chip, instr_strip.hip ----
-// taken for this shape, given a scratch block of workspace_floats floats?
-bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& kseg, size_t workspace_floats);
+// taken for this shape?
+bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& kseg);
 // largest scratch any supported launch with at most `rows` rows and at most n keys writes (0: none is supported)
 size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n);
 hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments kseg, float* workspace, size_t workspace_floats,
@@ -101,8 +101,7 @@ hipError_t finish_strip_scores(const Dims& dm, const float* part, int strips, in
 
 // ---- chunk attention and instruction score of a small step in one launch, attn_mfma.hip ----
 // The same bits as the two launches.  Both read [cache ; chunk]; q_instr: instr_rows rows per head.
-bool attn_score_in_one_launch(const Dims& dm, const Segments& kseg, const Segments& vseg, const View& q_instr, int instr_rows,
-                              size_t workspace_floats);
+bool attn_score_in_one_launch(const Dims& dm, const Segments& kseg, const Segments& vseg, const View& q_instr, int instr_rows);
 hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments kseg, Segments vseg, View out, int q_rope_pos0,
                                   float rope_base, View q_instr, int instr_rows, float* workspace, float* score,
                                   hipStream_t st, ScoreSums* sums);

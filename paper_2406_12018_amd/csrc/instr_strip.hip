@@ -99,7 +99,7 @@ static int strip_rows(const Dims& dm, int rows, int n) {
   return n <= kStripMaxKeysShort && dm.G * rows > 32 && groups32 > compute_units() ? 64 : 32;
 }
 
-bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& ks, size_t workspace_floats) {
+bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& ks) {
   const int n = ks.n_c + ks.c;
   if (n < 1 || n > kStripMaxKeysLong || rows < 1 || dm.G * rows > kStripMaxRows) return false;
   // Against the two-pass kernels, us with strips | two passes, 32/8 heads.  head_dim 128, 64 instruction rows, 1280 keys (64-row
@@ -118,7 +118,9 @@ bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segmen
   const bool one_round = per_strip == 64 && dm.G * rows <= 256 && units <= compute_units();
   const int rounds = dm.D == 128 ? (one_round ? 3 : 4) : strips > 1 ? 8 : 1;
   if (units * strips > rounds * compute_units()) return false;
-  if (static_cast<size_t>(units * strips) * n > workspace_floats) return false;  // the caller's block was sized for less
+  // The columns of several strips have to fit the scratch that a call of this shape has wherever it is made (one strip's
+  // column is the score): what is launched, and so the bits, follow from the call alone and not from the block behind it.
+  if (strips > 1 && static_cast<size_t>(units * strips) * n > instr_score_mfma_workspace_floats(dm, rows, n)) return false;
   // per-lane byte offsets into the group's instruction rows and into a key segment are 32-bit
   constexpr int64_t kSpan = int64_t{1} << 31;
   if (q.sh < 0 || q.ss <= 0 || ((dm.G - 1) * q.sh + (rows - 1) * q.ss + dm.D) * 2 >= kSpan) return false;
@@ -129,7 +131,8 @@ bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segmen
 size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n) {
   // Sized without a device query (the size of a workspace must not depend on where it is asked for): two columns per 32
   // rows, for up to 512 rows of a KV group and while 64-row strips make no more than 608 workgroups.  A larger call takes
-  // strips where the block is large enough for its columns all the same.
+  // strips where the scratch of the two-pass kernels, 16 floats per instruction row, holds its columns (512 keys with strips of
+  // 32 rows, 1024 with 64) or where it needs none.
   constexpr size_t kRows = 512, kGroups = 608;
   const size_t units = static_cast<size_t>(dm.B) * dm.L * dm.Hkv;
   if (units < 1 || units > kGroups || dm.G < 1 || static_cast<size_t>(dm.G) > kRows || rows < 1 || n < 1) return 0;
@@ -145,7 +148,8 @@ size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n) {
 hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments ks, float* workspace, size_t workspace_floats,
                               float* score, hipStream_t st, ScoreSums* sums) {
   const int n = ks.n_c + ks.c;
-  if (!instr_strip_supported(dm, q, rows, ks, workspace_floats)) return hipErrorInvalidValue;
+  if (!instr_strip_supported(dm, q, rows, ks)) return hipErrorInvalidValue;
+  if (workspace_floats < instr_score_mfma_workspace_floats(dm, rows, n)) return hipErrorInvalidValue;
   const bool tall = strip_rows(dm, rows, n) == 64, shorter = n <= kStripMaxKeysShort;
   auto launch = tall ? strip_launch<128, 2, 5> : shorter ? strip_launch<128, 1, 5> : strip_launch<128, 1, 10>;
   if (dm.D == 64) launch = tall ? strip_launch<64, 2, 5> : shorter ? strip_launch<64, 1, 5> : strip_launch<64, 1, 10>;

@@ -10,6 +10,8 @@ import re
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -160,6 +162,46 @@ def test_a_failed_step_leaves_both_caches_in_front_of_it(tmp_path):
     for fail_at, (names, *state) in enumerate(failing):
         assert names == whole[0][:fail_at]
         assert state == ([0, 0, 0, 0] if fail_at < per_step else [32, 1, 32, 1]), fail_at
+
+
+def scores(api, launches, shapes):
+    return [scores_of_one_shape(api, launches, *shape) for shape in shapes]
+
+
+def scores_of_one_shape(api, launches, L, Hq, Hkv, rows, n, head_dim):
+    """The same scores through every entry point that computes them, with workspaces of several sizes."""
+    q, cache, new = Fake(1, L, Hq, rows, head_dim), Fake(1, L, Hkv, n, head_dim), Fake(1, L, Hkv, 1, head_dim, at=1 << 22)
+    chunk = Fake(1, L, Hkv, n - 1, head_dim)
+    out = []
+    for capacity, instr_len in ((n, rows), (4 * n, rows), (n, 3 * rows), (n, rows + 700)):
+        cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=n, budget=1, instr_len=instr_len,
+                         cache_capacity=capacity)
+        ws = workspace(api, cfg)
+        out += [launches(lambda: api.citrus_cache_score(cfg, q, cache, n, score=q, workspace=ws, stream=0)),
+                launches(lambda: api.citrus_evict_cache(cfg, q, cache, cache, n, 1, new, new, workspace=ws, stream=0))]
+        if instr_len == rows:
+            out.append(launches(lambda: api.citrus_instr_score(cfg, q, cache, 1, chunk, score=q, workspace=ws, stream=0)))
+        try:
+            out.append(launches(lambda: api.citrus_evict_cache_static(cfg, q, cache, cache, n, 1, new, new, stream=0)))
+        except api.CitrusError as e:
+            assert e.status == 4  # more than the static array
+    return [[x for x in calls if x[0] != "lds" and not x[0].startswith(("evict_kernel", "strip_sum_kernel"))] for calls in out]
+
+
+SHAPES = [  # layers, query heads, KV heads, rows, candidates
+    (1, 64, 2, 128, 512), (1, 64, 2, 128, 513), (1, 64, 2, 128, 640),  # 4096 rows per KV head: 16 floats of scratch a row hold 512 keys
+    (4, 32, 2, 128, 1024), (4, 32, 2, 128, 1025), (4, 32, 2, 128, 1280),  # 2048 rows, strips of 64
+    (32, 32, 32, 64, 1280), (32, 32, 8, 64, 1280), (80, 8, 8, 40, 90), (1, 32, 8, 64, 2560), (16, 32, 8, 128, 2000)]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_the_scorer_follows_from_the_call_alone(head_dim, tmp_path):
+    """Not from the size of the scratch behind it: the entry points promise the same bits."""
+    shapes = [[*shape, head_dim] for shape in SHAPES]
+    for shape, (first, *others) in zip(shapes, in_child(scores, tmp_path, shapes=shapes)):
+        assert len(first) >= 1 and len(others) >= 9
+        for calls in others:
+            assert calls == first, shape
 
 
 if __name__ == "__main__":
