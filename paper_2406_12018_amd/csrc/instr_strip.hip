@@ -99,25 +99,47 @@ static int strip_rows(const Dims& dm, int rows, int n) {
   return n <= kStripMaxKeysShort && dm.G * rows > 32 && groups32 > compute_units() ? 64 : 32;
 }
 
+// Workgroups per compute unit up to which the strips of G * rows instruction rows per KV head are taken: where they are as fast as
+// the two-pass kernels, or nearly.  Both were measured for 8 to 4096 KV heads, 1 to 4096 rows and 40 to 2560 keys, the sum over
+// the strips included.  us with strips | two passes (KV heads):
+//   up to 32 rows, one strip: ahead at every number of KV heads, head_dim 128, 1280 keys 11.2 | 24.4 (64), 261 | 380 (4096); the
+//     lines lie where the larger groups' once did and could move out.
+//   up to 64: one strip of 64 or two of 32.  head_dim 128: 1280 keys 78.5 | 104 (1024), but 40 keys 10.2 | 9.0 (512) and 96
+//     keys 19.9 | 17.9 (1024), where a strip's fixed cost shows.  head_dim 64: ahead while the strips fit side by side, 1000 keys 11.9 | 16.1 (128).
+//   up to 128: the two-pass kernel has one workgroup per KV head, the strips two to four.  head_dim 128, 700 keys 14.7 | 22.7
+//     (128), 26.6 | 25.9 (256); 96 rows 25.8 | 22.5 (256); 1600 keys 27.8 | 37.1 (128), 50.8 | 43.5 (256), 2560 keys
+//     54.3 | 57.7 (192).  head_dim 64, 2000 keys 47.9 | 39.4 (256).
+//   up to 256: the two-pass kernel holds the keys in registers, at head_dim 128 all of them, and is through in one round while the
+//     KV heads fit side by side: 1280 keys 32.0 | 43.8 (128), 44.3 | 46.6 (192), 59.6 | 54.2 (256); 160 rows, 700 keys 34.7 | 28.0
+//     (256).  head_dim 64, where that instance spills: 90.5 | 108 (512); 2560 keys 78.8 | 90.6 (192), 104 | 94.9 (256).
+//   more: two launches against one.  head_dim 128, 512 rows, 1280 keys 58.8 | 75.3 (128); head_dim 64 88.6 | 93.6 (64, 2048 rows),
+//     4 x 128 rows, 2000 keys 50.3 | 43.6 (64), but 8 x 64 rows, 2560 keys 33.6 | 37.3 (32): the first launch takes a head's rows
+//     128 at a time; head_dim 128, 4 x 256 rows, 2000 keys 65.4 | 58.7 (32).
+// A strip of 64 rows works on 64 also where fewer are left (full_strips: none or up to 31 wanting); the two-pass kernels work on
+// tiles of 32.
+static int strip_rounds(const Dims& dm, int rows, int n, int64_t units) {
+  const int total = dm.G * rows;
+  const bool wide_head = dm.D == 128, full_strips = (total + 31) / 32 % 2 == 0, crowded = units > compute_units();
+  if (total <= 32) return wide_head ? 4 : 1;
+  if (n <= kStripMaxKeysShort) {
+    if (total <= 64) return wide_head && n >= 64 ? (n >= 256 ? 4 : 3) : 1;
+    if (total <= 128) return wide_head && full_strips && n >= 700 ? 3 : 1;
+    if (total <= 256) return !wide_head ? 8 : crowded ? 4 : full_strips && n >= 300 ? 3 : 2;
+    return !wide_head && (n >= 1000 || total >= 2048) ? 8 : 4;
+  }
+  if (total <= 64) return wide_head ? 4 : 2;
+  if (total <= 128) return wide_head && crowded ? 4 : full_strips && n >= 2000 ? 3 : 2;
+  if (total <= 256) return wide_head ? 4 : 6;
+  if (wide_head) return total <= 512 ? 4 : 2;
+  return rows >= 128 ? 1 : total <= 384 ? 5 : 2;
+}
+
 bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& ks) {
   const int n = ks.n_c + ks.c;
   if (n < 1 || n > kStripMaxKeysLong || rows < 1 || dm.G * rows > kStripMaxRows) return false;
-  // Against the two-pass kernels, us with strips | two passes, 32/8 heads.  head_dim 128, 64 instruction rows, 1280 keys (64-row
-  // strips; workgroups in brackets): 1 layer (64) 13.1 | 39, 16 layers (512) 32 | 42, 32 layers (1024) 56.9 | 57.8; 2560 keys,
-  // 32-row strips: 16 layers (1024) 67 | 85, 32 layers (2048) 110 | 114.  So up to four workgroups per compute unit.
-  // head_dim 64, where two workgroups share a compute unit: 8 layers 15 | 51, 32 layers (1024) 46 | 62, 64 layers (2048)
-  // 85 | 117; 2560 keys, 32 layers (2048) 101 | 106; up to eight.  With one strip per KV head the two-pass kernel has one
-  // workgroup per KV head too, and at head_dim 64 fits more of them: 700 keys, 16 rows, 32 layers (256) 11.6 | 13.9, 64
-  // layers (512) 23.1 | 20.1.
-  // Four 64-row strips per KV head against one round of the two-pass kernel with its 256 rows: up to three workgroups per
-  // compute unit.  us per document of 4096 tokens, strips | two passes: 25 layers (800 workgroups) 2531 | 2484, 28 layers
-  // (896) 2590 | 2559, 32 layers (1024), 640 keys 2328 | 2282; with two strips per KV head the two are level (512 units,
-  // 128 rows: 2317 | 2284, 3167 | 3206), and 512 rows take the two-pass path two launches (128 units: 2577 | 2749).
   const int per_strip = strip_rows(dm, rows, n);
   const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, strips = (dm.G * rows + per_strip - 1) / per_strip;
-  const bool one_round = per_strip == 64 && dm.G * rows <= 256 && units <= compute_units();
-  const int rounds = dm.D == 128 ? (one_round ? 3 : 4) : strips > 1 ? 8 : 1;
-  if (units * strips > rounds * compute_units()) return false;
+  if (units * strips > static_cast<int64_t>(strip_rounds(dm, rows, n, units)) * compute_units()) return false;
   // The columns of several strips have to fit the scratch that a call of this shape has wherever it is made (one strip's
   // column is the score): what is launched, and so the bits, follow from the call alone and not from the block behind it.
   if (strips > 1 && static_cast<size_t>(units * strips) * n > instr_score_mfma_workspace_floats(dm, rows, n)) return false;
