@@ -9,6 +9,7 @@ library is missing or an entry point fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 from dataclasses import dataclass
 from typing import Callable, Optional, Sequence
@@ -125,13 +126,11 @@ def _lib():
     return lib
 
 
-class _ConfigStruct:
-    """What Config keeps beside its fields: the C structure last made of them and the values it was made of."""
-    __slots__ = ("_values", "_struct")
+_config_fields = operator.attrgetter(*(name for name, _ in CConfig._fields_))
 
 
 @dataclass
-class Config(_ConfigStruct):
+class Config:
     batch: int
     layers: int
     q_heads: int
@@ -164,16 +163,8 @@ class Config(_ConfigStruct):
                 self.cache_capacity = max(self.budget, self.budget_lm)
 
     def c(self) -> CConfig:
-        values = tuple(self.__dict__.values())  # the fields as they are now
-        if getattr(self, "_values", None) != values:
-            self._struct, self._values = self._make_struct(), values
-        return self._struct
-
-    def _make_struct(self) -> CConfig:
-        return CConfig(self.batch, self.layers, self.q_heads, self.kv_heads, self.head_dim, self.chunk_len,
-                       self.budget, self.budget_lm, self.instr_len, self.cache_capacity, self.dtype,
-                       self.cache_mode, self.select_mode, self.start_size, self.lm_ordering, self.score_mode, self.position_shift, self.rope_base,
-                       self.softmax_scale)
+        """A structure of the fields as they are now, the caller's own."""
+        return CConfig(*_config_fields(self))
 
     @property
     def torch_dtype(self) -> torch.dtype:

@@ -1,8 +1,10 @@
 """The C-ABI library loads, exports every symbol the header declares, and turns
 bad arguments into error codes on the host without touching a device.  CPU only."""
 
+import copy
 import ctypes as C
 import os
+import pickle
 import re
 
 import pytest
@@ -39,6 +41,23 @@ def cfg(**kw):
     base = dict(batch=1, layers=1, q_heads=4, kv_heads=2, head_dim=64, chunk_len=32, budget=64, instr_len=8, dtype=B.F32)
     base.update(kw)
     return B.Config(**base)
+
+
+def test_a_configuration_hands_out_a_structure_of_its_own():
+    """What a caller writes into it stays there; the fields are read at every call, also the ones set after the last."""
+    c = cfg()
+    first = c.c()
+    as_made = bytes(first)
+    first.budget = 7
+    assert bytes(c.c()) == as_made and c.c() is not c.c()
+    c.budget, c.softmax_scale, c.note = 48, 0.25, "not a field"
+    assert (c.c().budget, c.c().softmax_scale) == (48, 0.25)
+    assert [getattr(c.c(), n) for n, _ in B.CConfig._fields_] == [getattr(c, n) for n, _ in B.CConfig._fields_]
+    for copied in (copy.copy(c), pickle.loads(pickle.dumps(c))):
+        assert copied == c and bytes(copied.c()) == bytes(c.c())
+    c.budget = 48.0
+    with pytest.raises(TypeError):  # also where the number was used before
+        c.c()
 
 
 def test_status_strings():
