@@ -1,6 +1,7 @@
 // Selection (Eq. (2)-(3): keep the k highest importance scores) and compaction
 // (Eq. (3), (5): the evicted cache holds exactly the selected states).
 #include <algorithm>
+#include <type_traits>
 
 #include "citrus_internal.h"
 
@@ -147,10 +148,11 @@ __device__ __forceinline__ int wave_prefix_sum(int v) {
 enum class Scores { kOneHead, kSumByHead, kSumByCandidate };
 
 // Radix passes of BITS bits: a large radix needs fewer passes, each a chain of dependent steps, and spreads the votes of
-// scores that share their exponents over more bins; every wave reads the whole histogram, which bounds it.
-template <int THREADS>
+// scores that share their exponents over more bins; the histograms are cleared, every wave reads a whole one in each pass, and
+// their LDS (24 KB at 11 bits, 4 KB at 8) is what the units side by side on a compute unit share.
+template <int BITS>
 struct Radix {
-  static constexpr int kBits = THREADS <= 256 ? 11 : 10;
+  static constexpr int kBits = BITS;
   static constexpr int kPasses = (32 + kBits - 1) / kBits;
   static constexpr int kBins = 1 << kBits;
   __host__ __device__ static constexpr int shift(int pass) { return 32 - kBits * (pass + 1) > 0 ? 32 - kBits * (pass + 1) : 0; }
@@ -158,9 +160,9 @@ struct Radix {
 __device__ __forceinline__ int padded(int j) { return j + (j >> 3); }  // candidates apart by 8 in different banks
 
 // LDS of a selection.
-template <int ITEMS, int THREADS>
+template <int ITEMS, int THREADS, int BITS>
 struct SelectLds {
-  alignas(16) int hist[Radix<THREADS>::kPasses][Radix<THREADS>::kBins];
+  alignas(16) int hist[Radix<BITS>::kPasses][Radix<BITS>::kBins];
   uint32_t key[ITEMS * THREADS + ITEMS * THREADS / 8];
   alignas(16) int total[2][THREADS / 64];
 };
@@ -176,11 +178,11 @@ struct SelectLds {
 // short.  Every pass has a histogram of its own, cleared at the start, and every wave finds the bin by itself: one barrier
 // per pass.  A pass whose bin is kept as a whole is the last one (scores that differ need two), and
 // threshold-equal candidates are ranked only where some of them are left out.
-template <int ITEMS, int THREADS, Scores FORM, typename Emit>
-__device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS>& lds, const float* base, int rows, int n, int k,
+template <int ITEMS, int THREADS, int BITS, Scores FORM, typename Emit>
+__device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS, BITS>& lds, const float* base, int rows, int n, int k,
                                                int forced, const float* acc, int n_acc, Emit&& emit) {
-  typedef Radix<THREADS> R;
-  constexpr int WAVES = THREADS / 64, kLaneBins = R::kBins / 64, kRowsInFlight = 8;
+  typedef Radix<BITS> R;
+  constexpr int WAVES = THREADS / 64, kLaneBins = R::kBins / 64;
   static_assert(ITEMS <= 32, "one bit per item");
   const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
 
@@ -190,15 +192,16 @@ __device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS>& lds, c
   };
   if constexpr (FORM == Scores::kSumByHead) {
     float sum[ITEMS];
-    for (int g0 = 0; g0 < rows; g0 += kRowsInFlight) {
-      float v[kRowsInFlight][ITEMS];
+    auto add_rows = [&](auto in_flight, int g0) {  // up to so many rows from g0 on
+      constexpr int kRows = decltype(in_flight)::value;
+      float v[kRows][ITEMS];
 #pragma unroll
-      for (int x = 0; x < kRowsInFlight; ++x)
+      for (int x = 0; x < kRows; ++x)
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
           v[x][i] = base[static_cast<int64_t>(min(g0 + x, rows - 1)) * n + min(i * THREADS + tid, n - 1)];
 #pragma unroll
-      for (int x = 0; x < kRowsInFlight; ++x)
+      for (int x = 0; x < kRows; ++x)
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
           if (x == 0)
@@ -206,7 +209,10 @@ __device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS>& lds, c
           else
             sum[i] = g0 + x < rows ? sum[i] + v[x][i] : sum[i];
         }
-    }
+    };
+    int g0 = 0;
+    for (; rows - g0 > 2; g0 += 8) add_rows(std::integral_constant<int, 8>{}, g0);
+    if (g0 < rows) add_rows(std::integral_constant<int, 2>{}, g0);
     if (acc != nullptr) {
 #pragma unroll
       for (int i = 0; i < ITEMS; ++i)
@@ -308,17 +314,20 @@ __device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS>& lds, c
     if (keep_bits & (1u << i)) emit(pos++, j0 + i);
 }
 
-template <int ITEMS, int THREADS, Scores FORM>
+template <int ITEMS, int THREADS, Scores FORM, int BITS>
 __global__ __launch_bounds__(THREADS) void topk_regs_kernel(const float* score, int heads_to_sum, int n, int k, int forced,
                                                            int32_t* idx) {
-  __shared__ SelectLds<ITEMS, THREADS> lds;
+  __shared__ SelectLds<ITEMS, THREADS, BITS> lds;
   const float* base = score + static_cast<int64_t>(blockIdx.x) * heads_to_sum * n;
   int32_t* out = idx + static_cast<int64_t>(blockIdx.x) * k;
   if (n <= k) {  // nothing to evict: keep every candidate
     for (int j = threadIdx.x; j < n; j += THREADS) out[j] = j;
     return;
   }
-  topk_regs_body<ITEMS, THREADS, FORM>(lds, base, heads_to_sum, n, k, forced, nullptr, 0, [&](int pos, int j) { out[pos] = j; });
+  // a thread's kept candidates are neighbours in `out`: they go there through LDS, so that neighbouring lanes write neighbours
+  topk_regs_body<ITEMS, THREADS, BITS, FORM>(lds, base, heads_to_sum, n, k, forced, nullptr, 0, [&](int pos, int j) { lds.key[pos] = j; });
+  __syncthreads();
+  for (int r = threadIdx.x; r < k; r += THREADS) out[r] = lds.key[r];
 }
 
 // Accumulated scores: the sum a cache state carries is added to this step's score of the same candidate
@@ -439,14 +448,16 @@ struct EvictArgs {
   int first_blocks;  // workgroups of job 0
 };
 constexpr int kGatherRows = 4;  // rows of a thread in flight
+template <int THREADS>
+constexpr int kEvictBits = THREADS <= 256 ? 11 : 10;
 constexpr int kMostKeptBytes = 6 * kWideThreads * sizeof(int32_t);  // the candidates of the rows that a unit keeps
 // narrow instances stay within the LDS a launch may have without asking, whatever they keep
-static_assert(sizeof(SelectLds<8, kSelThreads>) + kMostKeptBytes <= 65536);
+static_assert(sizeof(SelectLds<8, kSelThreads, kEvictBits<kSelThreads>>) + kMostKeptBytes <= 65536);
 
 template <int ITEMS, int THREADS, Scores FORM>
 __global__ __launch_bounds__(THREADS) void evict_kernel(EvictArgs args) {
   extern __shared__ int32_t sel[];  // the candidates of this part's kept rows
-  __shared__ SelectLds<ITEMS, THREADS> lds;
+  __shared__ SelectLds<ITEMS, THREADS, kEvictBits<THREADS>> lds;
   const bool second = static_cast<int>(blockIdx.x) >= args.first_blocks;
   const EvictJob& a = args.job[second];
   const int block = second ? blockIdx.x - args.first_blocks : blockIdx.x;
@@ -460,7 +471,7 @@ __global__ __launch_bounds__(THREADS) void evict_kernel(EvictArgs args) {
     if (a.n <= a.k) {
       for (int r = r0 + tid; r < s1; r += THREADS) sel[r - r0] = r;
     } else {
-      topk_regs_body<ITEMS, THREADS, FORM>(lds, base, a.sums, a.n, a.k, a.forced, acc, a.v.n_c, [&](int pos, int j) {
+      topk_regs_body<ITEMS, THREADS, kEvictBits<THREADS>, FORM>(lds, base, a.sums, a.n, a.k, a.forced, acc, a.v.n_c, [&](int pos, int j) {
         if (pos >= r0 && pos < s1) sel[pos - r0] = j;
       });
     }
@@ -506,35 +517,50 @@ GatherViews gather_views(int elem_bytes, const Dims& dm, const Segments& ks, con
 hipError_t launch_topk(const float* score, int units, int heads_to_sum, int n, int k, int forced, int32_t* idx,
                        hipStream_t st) {
   forced = min(forced, k);
-  // Four times the threads where a unit's chain is long and the units fit the chip side by side (32 units of 6144
-  // candidates: 17.9 us with 256 threads, 10.6 with 1024; with more units the chip is full either way), and for the sums
-  // over a layer's heads, a read of heads_to_sum * n floats through one compute unit that needs its loads in flight
-  // (16 units of 32 heads x 2048 candidates: 70 us candidate by candidate, 62 head by head, 12.7 with 1024 threads).
-  // Two such workgroups fit a compute unit.  With more units than that the chip is full, threads without a candidate are
-  // time lost, and short sums go candidate by candidate on 256 threads.  us with 1024 | 256 threads: 1024 units of 32
-  // heads x 100 candidates 14.1 | 6.9, 8 x 500 11.2 | 7.5, 8 x 1000 14.0 | 14.4, 8 x 2048 20.3 | 25.1; six times the
-  // compute units: 8 x 1000 20.2 | 16.9, 16 x 1000 30.1 | 28.6, 8 x 2048 29.0 | 29.6.  Up to two rounds of workgroups:
-  // 512 units of 2 x 300 4.8 | 4.2, of 8 x 1280 7.1 | 9.1.
+  // Four times the threads where a unit's chain is long and the units fit the chip side by side, and for the sums over a layer's
+  // heads, a read of heads_to_sum * n floats through one compute unit that needs its loads in flight (16 units of 32 heads x
+  // 2048 candidates: 70 us candidate by candidate, 62 head by head, 12.7 with 1024 threads).  Two such workgroups fit a
+  // compute unit.  From that number of units the chip is full, threads without a candidate are time lost, and short
+  // sums go candidate by candidate on 256 threads.  us with 1024 threads | 256: 512 units of 2 heads x 300 candidates
+  // 6.2 | 4.5, 4 x 1280 8.7 | 7.3, 8 x 1280 8.8 | 9.2; 1024 units of 8 x 500 10.7 | 9.1, 8 x 1000 13.9 | 14.4, 8 x 2048 20.4 |
+  // 27.5, 2 x 3000 18.5 | 20.0; 2048 units of 8 x 1280 28.1 | 26.0, 8 x 2048 33.5 | 39.0.
+  //
+  // The radix: what a large one saves in passes shows where a unit has many candidates, what it costs in LDS where there are
+  // many units of few.  us with 8 | 11 bits (1024 threads: 10), scores over six octaves: 8 units of 300 candidates 3.5 | 3.5, of
+  // 1280 4.8 | 4.4, of 6144 8.4 | 7.8; 1024 units of 100 3.9 | 4.5, of 640 5.7 | 5.8, of 1280 7.6 | 6.8; 4096 units of 300 8.8 |
+  // 11.7, of 640 13.0 | 14.6, of 1280 19.2 | 18.2.  Sums of 8 heads: 256 units of 640 5.5 | 6.1, of 2048 7.2 | 7.1, of 4096
+  // 10.7 | 9.7; 1024 of 640 8.6 | 7.8; 4096 of 640 28 | 37.
+  // (An instance whose threads hold more candidates than there are, and positions written by every thread for itself, took 1.2
+  // to 1.9 times as long: 4096 units of 100 candidates 14.3 us, of 6144 132 instead of 88.)
   constexpr Scores kOne = Scores::kOneHead, kByHead = Scores::kSumByHead, kByCandidate = Scores::kSumByCandidate;
   const int cus = compute_units();
   const bool sums = heads_to_sum > 1;
-  const int short_most = units > 5 * cus ? 16384 : n <= 2 * kWideThreads ? 8192 : 6144;
-  const bool short_sums = sums && units > 2 * cus && static_cast<int64_t>(heads_to_sum) * n <= short_most;
+  const int short_most = units > 5 * cus ? 10240 : units > 2 * cus ? 8192 : 5120;
+  const bool short_sums = sums && n <= 2 * kWideThreads && units >= 2 * cus && static_cast<int64_t>(heads_to_sum) * n <= short_most;
+  const bool wide = sums ? !short_sums : n > 2 * kWideThreads && units <= cus;
   auto kern = topk_kernel;
   int threads = kSelThreads;
-  if (n <= 2 * kWideThreads) {
-    kern = short_sums ? topk_regs_kernel<8, kSelThreads, kByCandidate>
-           : sums     ? topk_regs_kernel<2, kWideThreads, kByHead>
-                      : topk_regs_kernel<8, kSelThreads, kOne>;
-    threads = sums && !short_sums ? kWideThreads : kSelThreads;
-  } else if (n <= 6 * kWideThreads) {
-    const bool wide = sums ? !short_sums : units <= cus;
-    kern = short_sums                      ? topk_regs_kernel<24, kSelThreads, kByCandidate>
-           : sums && n <= 3 * kWideThreads ? topk_regs_kernel<3, kWideThreads, kByHead>
-           : sums                          ? topk_regs_kernel<6, kWideThreads, kByHead>
-           : wide                          ? topk_regs_kernel<6, kWideThreads, kOne>
-                                           : topk_regs_kernel<24, kSelThreads, kOne>;
+  if (n <= 6 * kWideThreads) {
     threads = wide ? kWideThreads : kSelThreads;
+    if (short_sums)
+      kern = n <= 2 * kSelThreads ? topk_regs_kernel<2, kSelThreads, kByCandidate, 8>
+             : units > 4 * cus    ? (n <= 5 * kSelThreads ? topk_regs_kernel<5, kSelThreads, kByCandidate, 8>
+                                                          : topk_regs_kernel<8, kSelThreads, kByCandidate, 8>)
+             : n <= 5 * kSelThreads ? topk_regs_kernel<5, kSelThreads, kByCandidate, 11>
+                                    : topk_regs_kernel<8, kSelThreads, kByCandidate, 11>;
+    else if (sums)
+      kern = n <= kWideThreads       ? topk_regs_kernel<1, kWideThreads, kByHead, 8>
+             : n <= 2 * kWideThreads ? (n <= 6 * kSelThreads ? topk_regs_kernel<2, kWideThreads, kByHead, 8>
+                                                             : topk_regs_kernel<2, kWideThreads, kByHead, 10>)
+             : n <= 3 * kWideThreads ? topk_regs_kernel<3, kWideThreads, kByHead, 10>
+                                     : topk_regs_kernel<6, kWideThreads, kByHead, 10>;
+    else
+      kern = wide                    ? topk_regs_kernel<6, kWideThreads, kOne, 10>
+             : n <= 2 * kSelThreads  ? topk_regs_kernel<2, kSelThreads, kOne, 8>
+             : n <= 3 * kSelThreads  ? topk_regs_kernel<3, kSelThreads, kOne, 8>
+             : n <= 5 * kSelThreads  ? topk_regs_kernel<5, kSelThreads, kOne, 11>
+             : n <= 2 * kWideThreads ? topk_regs_kernel<8, kSelThreads, kOne, 11>
+                                     : topk_regs_kernel<24, kSelThreads, kOne, 11>;
   }
   hipLaunchKernelGGL(kern, dim3(units), dim3(threads), 0, st, score, heads_to_sum, n, k, forced, idx);
   return hipGetLastError();
@@ -635,7 +661,7 @@ hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int c
   // One part per unit (more units than compute units) of a budget above 5344 rows: the selection's LDS and the kept rows
   // together are more than the 64 KB a launch may have without asking.
   constexpr int kUnasked = 65536;
-  if (wide && static_cast<int>(sizeof(SelectLds<6, kWideThreads>)) + lds > kUnasked) {
+  if (wide && static_cast<int>(sizeof(SelectLds<6, kWideThreads, kEvictBits<kWideThreads>>)) + lds > kUnasked) {
     static LdsLimit limit[2];
     const hipError_t e = raise_lds_limit(limit[sums], reinterpret_cast<const void*>(kern), kMostKeptBytes);
     if (e != hipSuccess) return e;

@@ -55,8 +55,18 @@ def test_selection(n, kind):
 @pytest.mark.parametrize("layers,heads,n,per_layer", [
     (88, 3, 2049, False), (88, 3, 6144, False),                  # more units than compute units
     (520, 2, 2, True), (520, 3, 257, True), (520, 4, 2048, True),  # more than two rounds of them, short sums
-    (520, 2, 2049, True), (520, 2, 3072, True), (1300, 2, 6144, True),
-    (520, 5, 2048, True), (520, 3, 2049, True),                  # longer sums
+    (520, 5, 2048, True), (520, 3, 2049, True), (520, 2, 2049, True), (520, 2, 3072, True), (1300, 2, 6144, True),  # longer ones
 ])
 def test_selection_of_many_units(layers, heads, n, per_layer, kind):
+    check(layers, heads, n, kind, per_layer)
+
+
+@pytest.mark.parametrize("kind", ["spread", "close", "ties", "equal"])
+@pytest.mark.parametrize("layers,heads,n,per_layer", [
+    (1, 2, 511, False), (1, 2, 512, False), (1, 2, 513, False), (2, 1, 768, False), (2, 1, 769, False), (2, 1, 1281, False),
+    (3, 2, 1023, True), (3, 2, 1024, True), (3, 2, 1025, True), (3, 2, 1536, True), (3, 2, 1537, True),
+    (520, 2, 512, True), (520, 2, 513, True), (520, 3, 1281, True),    # short sums
+    (1300, 2, 512, True), (1300, 2, 513, True), (1300, 3, 1280, True),  # of more than five units per compute unit
+])
+def test_selection_where_the_candidates_per_thread_and_the_radix_change(layers, heads, n, per_layer, kind):
     check(layers, heads, n, kind, per_layer)
