@@ -252,8 +252,11 @@ citrus_status do_compact(const citrus_config* c, const Dims& dm, Segments ks, Se
                                    make_view(k_new), make_view(v_new), nullptr, 0, nullptr, 0, st));
 }
 
-// May a selection and its gather be one launch?  Selections per KV head, over candidates a workgroup can hold.
-bool one_launch(const citrus_config* c, int n) { return c->select_mode == CITRUS_SELECT_PER_KV_HEAD && evict_in_one_launch(n); }
+// May a selection of k of n candidates and its gather be one launch?  Selections per KV head, over candidates a workgroup can hold.
+bool one_launch(const citrus_config* c, int n, int k, int appended = 0) {
+  return c->select_mode == CITRUS_SELECT_PER_KV_HEAD &&
+         evict_in_one_launch(elem_bytes(c->dtype), dims_of(c), n, (n < k ? n : k) + appended);
+}
 
 // The two as launches of their own: layer-wise selections, more candidates, and callers that time them apart.  The scores
 // are in `score` (e.score.sums == 1).
@@ -327,7 +330,7 @@ citrus_status do_evict_cache(const citrus_config* cfg, const citrus_tensor& q, i
                              const citrus_tensor& v_cache, int cache_len, int k, const citrus_tensor& k_new,
                              const citrus_tensor& v_new, int32_t* idx, Scratch scratch, float* score, hipStream_t st) {
   const Dims dm = dims_of(cfg);
-  const bool fused = one_launch(cfg, cache_len);
+  const bool fused = one_launch(cfg, cache_len, k);
   Eviction e{cache_only(k_cache, cache_len), cache_only(v_cache, cache_len), {score, 1}, cache_len, k, cfg->start_size, 0,
              idx, make_view(k_new), make_view(v_new), nullptr, nullptr, 0};
   if (cache_len > k)
@@ -752,7 +755,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       *later = e;
       return CITRUS_OK;
     }
-    CITRUS_TRY(evict(e, t.score, one_launch(cfg, n_ranked) && !timed(3), 3, st));
+    CITRUS_TRY(evict(e, t.score, one_launch(cfg, n_ranked, t.budget, appended) && !timed(3), 3, st));
     *t.len = kept + appended;
     *t.cur = to;
     return CITRUS_OK;
@@ -812,7 +815,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       ks_att = segments(k_rot, n_c, k_rot_chunk, c);
     }
     int32_t* idx = idx_history ? idx_history + static_cast<size_t>(done) * units_sel * cfg->budget : idx_ws;
-    const bool fused = one_launch(cfg, n) && !timed(6);
+    const bool fused = one_launch(cfg, n, cfg->budget) && !timed(6);
     Eviction own{ks, vs, {score, 1}, n, cfg->budget, cfg->start_size, 0, idx, make_view(k_cache[cur ^ 1]),
                  make_view(v_cache[cur ^ 1]), accumulated ? acc_score[cur] : nullptr, accumulated ? acc_score[cur ^ 1] : nullptr,
                  cfg->cache_capacity};
@@ -850,7 +853,8 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
       if (dual) {
         int32_t* idx_lm = idx_history_lm ? idx_history_lm + static_cast<size_t>(done) * units_sel * cfg->budget_lm : idx_lm_ws;
         const ChunkEvicted t{k_cache_lm, v_cache_lm, &n_c_lm, &cur_lm, cfg->budget_lm, score_lm, idx_lm};
-        together = fused && one_launch(cfg, n_c_lm + c) && !timed(3) && !timed(4) && !timed(5);
+        const bool lm_fused = paper_order ? one_launch(cfg, n_c_lm, cfg->budget_lm, c) : one_launch(cfg, n_c_lm + c, cfg->budget_lm);
+        together = fused && lm_fused && !timed(3) && !timed(4) && !timed(5);
         if ((status = chunk_evicted_step(t, io, c, together ? &lm : nullptr)) != CITRUS_OK) break;
       } else if (!timed(1) && !timed(2) && !timed(3) && !timed(4) && attn_and_score_fit(cfg, dm, ks_att, vs, qi_att)) {
         scored = true;

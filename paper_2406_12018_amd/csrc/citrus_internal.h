@@ -180,8 +180,8 @@ struct Eviction {
   float* acc_new;    // ... and that the kept states take along; [B*L*Hkv][acc_pitch]
   int acc_pitch;
 };
-// may launch_evict rank n candidates?
-bool evict_in_one_launch(int n);
+// May, and should, the eviction of a cache that keeps `rows` rows per head, ranking n candidates, be one launch?
+bool evict_in_one_launch(int elem_bytes, const Dims& dm, int n, int rows);
 // One or two evictions in one launch.
 hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int count, hipStream_t st);
 

@@ -602,7 +602,18 @@ hipError_t launch_compact(int elem_bytes, const Dims& dm, Segments ks, Segments 
   return hipGetLastError();
 }
 
-bool evict_in_one_launch(int n) { return n <= 6 * kWideThreads; }
+bool evict_in_one_launch(int elem_bytes, const Dims& dm, int n, int rows) {
+  if (n > 6 * kWideThreads) return false;
+  // The launch that is saved is worth some microseconds.  Its gather is held up where it is bound by memory: workgroups that have
+  // just selected all start to move rows together, and 1024 of their threads take a compute unit at a time.  us with two
+  // launches | one, a score of one row per head included: head_dim 128 in bf16, 512 units, 400 rows (105 MB read) 56.5 | 58.2,
+  // 200 rows 35.1 | 33.8; 512 units, 1536 rows 222 | 237; 2048 units, 768 rows 512 | 526.  head_dim 64: 256 units, 1536 rows
+  // (101 MB) 54.3 | 52.7, 4096 units, 400 rows 269 | 267, but of 6144 candidates 256 units, 4096 rows (268 MB) 164 | 181.  More
+  // than four units per compute unit of few rows: 4096 units, 31 of 2560 458 | 480.
+  const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, row_bytes = static_cast<int64_t>(dm.D) * elem_bytes;
+  const bool wide = n > 8 * kSelThreads, much = 2 * units * rows * row_bytes >= 96 << 20;
+  return !(much && (wide || row_bytes >= 256)) && !(wide && units > 4 * compute_units());
+}
 
 hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int count, hipStream_t st) {
   if (count < 1 || count > 2) return hipErrorInvalidValue;
@@ -658,8 +669,8 @@ hipError_t launch_evict(int elem_bytes, const Dims& dm, const Eviction* e, int c
   } else if (n_max > 2 * kSelThreads) {
     kern = sums ? evict_kernel<5, kSelThreads, kSums> : evict_kernel<5, kSelThreads, kOne>;
   }
-  // One part per unit (more units than compute units) of a budget above 5344 rows: the selection's LDS and the kept rows
-  // together are more than the 64 KB a launch may have without asking.
+  // One part per unit of a budget above 5344 rows, as on a part of the chip: the selection's LDS and the kept rows together are
+  // more than the 64 KB a launch may have without asking.
   constexpr int kUnasked = 65536;
   if (wide && static_cast<int>(sizeof(SelectLds<6, kWideThreads, kEvictBits<kWideThreads>>)) + lds > kUnasked) {
     static LdsLimit limit[2];

@@ -20,7 +20,7 @@ std::string log_text;
 dim3 call_grid, call_block;
 size_t call_shared;
 void* call_stream;
-int launches = 0, fail_at = -1, last_error = 0;
+int launches = 0, fail_at = -1, last_error = 0, compute_units = 256;
 alignas(256) char device_array[256];
 
 void note(const char* what, const std::string& text) { log_text += std::string(what) + " " + text + "\n"; }
@@ -37,6 +37,7 @@ std::string kernel_name(const void* host) {
 
 extern "C" {
 void fake_reset(int n) { log_text.clear(); launches = 0; fail_at = n; last_error = 0; }
+void fake_compute_units(int n) { compute_units = n; }  // before the first call
 const char* fake_log() { return log_text.c_str(); }
 
 void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
@@ -62,7 +63,7 @@ int hipLaunchKernel(const void* host, dim3 grid, dim3 block, void**, size_t shar
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 int hipFuncSetAttribute(const void* host, int, int value) { note("lds", std::to_string(value) + " " + kernel_name(host)); return 0; }
 int hipGetDevice(int* device) { *device = 0; return 0; }
-int hipDeviceGetAttribute(int* value, int, int) { *value = 256; return 0; }  // compute units
+int hipDeviceGetAttribute(int* value, int, int) { *value = compute_units; return 0; }
 int hipGetSymbolAddress(void** address, const void*) { *address = device_array; return 0; }
 int hipEventRecord(void*, void*) { return 0; }
 int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }

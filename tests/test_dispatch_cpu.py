@@ -112,9 +112,10 @@ def test_f32_launches_of_many_heads_stay_within_a_grid(tmp_path):
 
 
 def evictions_of_large_budgets(api, launches, budgets):
+    launches.lib.fake_compute_units(32)  # a part of the chip: one workgroup holds all that a unit keeps
     out = []
     for k in budgets:
-        L, H, n, d = 40, 8, 6144, 64
+        L, H, n, d = 5, 8, 6144, 64
         cfg = api.Config(batch=1, layers=L, q_heads=H, kv_heads=H, head_dim=d, chunk_len=8, budget=k, instr_len=2, cache_capacity=n)
         q, cache, new, ws = Fake(1, L, H, 2, d), Fake(1, L, H, n, d), Fake(1, L, H, k, d, at=1 << 22), workspace(api, cfg)
         out += launches(lambda: api.citrus_evict_cache(cfg, q, cache, cache, n, k, new, new, workspace=ws, stream=0))
@@ -202,6 +203,27 @@ def test_the_scorer_follows_from_the_call_alone(head_dim, tmp_path):
         assert len(first) >= 1 and len(others) >= 9
         for calls in others:
             assert calls == first, shape
+
+
+def evictions(api, launches, shapes):
+    out = []
+    for L, head_dim, n, k in shapes:
+        H = 8
+        cfg = api.Config(batch=1, layers=L, q_heads=H, kv_heads=H, head_dim=head_dim, chunk_len=8, budget=k, instr_len=1, cache_capacity=n)
+        q, cache, new, ws = Fake(1, L, H, 1, head_dim), Fake(1, L, H, n, head_dim), Fake(1, L, H, k, head_dim, at=1 << 22), workspace(api, cfg)
+        calls = launches(lambda: api.citrus_evict_cache(cfg, q, cache, cache, n, k, new, new, workspace=ws, stream=0))
+        out.append([x[0].split("<")[0] for x in calls if x[0] != "lds"])
+    return out
+
+
+def test_evictions_that_memory_bounds_are_two_launches(tmp_path):
+    shapes = {(32, 128, 1280, 765): 1, (32, 128, 1280, 768): 2,    # 96 MB of keys and values
+              (32, 64, 2048, 1536): 1, (32, 64, 2049, 1536): 2,    # rows of 128 bytes: only with 1024 threads
+              (128, 64, 2560, 31): 1, (129, 64, 2560, 31): 2,      # four units per compute unit
+              (1, 128, 6144, 4096): 1, (1, 128, 6145, 4096): 2}
+    for (shape, count), names in zip(shapes.items(), in_child(evictions, tmp_path, shapes=[list(x) for x in shapes])):
+        assert names[-count:] == (["evict_kernel"] if count == 1 else ["topk_regs_kernel" if shape[2] <= 6144 else "topk_kernel",
+                                                                       "compact_kernel"]), shape
 
 
 if __name__ == "__main__":

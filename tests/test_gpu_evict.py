@@ -29,7 +29,9 @@ CASES = [
     (1, 4, 1, 128, 16, 2049, 1999, 0, "bf16"),  # 1024 threads
     (1, 8, 2, 128, 64, 2560, 31, 5, "bf16"),
     (3, 4, 2, 128, 16, 6144, 4096, 0, "bf16"),
-    (32, 8, 8, 64, 2, 6144, 6100, 0, "bf16"),  # one part of a unit, more LDS than a launch has without asking
+    (32, 8, 8, 64, 2, 6144, 6100, 0, "bf16"),  # two launches: more rows than one is worth
+    (32, 8, 8, 64, 2, 6144, 1400, 0, "bf16"),  # one part of a unit, 1024 threads
+    (32, 8, 8, 128, 2, 1280, 765, 0, "bf16"), (32, 8, 8, 128, 2, 1280, 768, 0, "bf16"),  # the sides of 96 MB
     (1, 2, 1, 128, 16, 6145, 777, 0, "bf16"),   # too many for one launch
     (40, 16, 8, 128, 8, 90, 33, 0, "bf16"),     # more units than workgroups wanted
     (1, 4, 2, 128, 3, 100, 100, 0, "bf16"),     # nothing leaves
