@@ -12,7 +12,7 @@
 // the rows of O^T, may run in any order.
 //
 // What bounds it: these launches are small, and a workgroup's time is its chain of dependent steps (memory 1 us, sixteen
-// to thirty-two MFMAs of 58 cycles, exchange through LDS).  So the eight waves of a workgroup share sixteen query rows and split
+// to thirty-two MFMAs of 58 cycles, exchange through LDS).  So the waves of a workgroup share sixteen query rows and split
 // the keys.  Against one wavefront per query row on the vector units, keys one by one: 4 heads, 32 rows over 96 states, 8
 // instruction rows, head_dim 64: 15.0 + 5 + 7.6 us in three launches, 8.8 in one (a document of 512 tokens 527 -> 235 us);
 // documents of 32/8 heads, head_dim 128, 128 rows over 384 states 1599 -> 431 us, 8/1 heads in 16 layers, 512 rows over 1280
@@ -84,20 +84,19 @@ struct AttnF32Args {
   int row_blocks;
 };
 
-template <int D>
-constexpr int attn_f32_lds_bytes() { return kWaves * kTile * (D + 4) * 4 + 2 * kWaves * kTile * 4; }
+template <int D, int WAVES>
+constexpr int attn_f32_lds_bytes() { return WAVES * kTile * (D + 4) * 4 + 2 * WAVES * kTile * 4; }
 
-// Sixteen query rows of one head.  out and lse are optional.
-template <int D>
-__device__ __forceinline__ void attn_f32_body(const AttnF32Args& a, int block, char* smem) {
+// Sixteen query rows, block rb of head h in (document, layer) bl.  out and lse are optional.
+template <int D, int WAVES>
+__device__ __forceinline__ void attn_f32_body(const AttnF32Args& a, int rb, int h, int bl, char* smem) {
   constexpr int kPitch = D + 4, kCols = D / 64;  // float4 columns of O^T per lane
   float* const o_s = reinterpret_cast<float*>(smem);  // [waves][16][kPitch]
-  float* const m_s = o_s + kWaves * kTile * kPitch;   // [waves][16]
-  float* const l_s = m_s + kWaves * kTile;
+  float* const m_s = o_s + WAVES * kTile * kPitch;    // [waves][16]
+  float* const l_s = m_s + WAVES * kTile;
   const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int col = lane % 16, quad = lane / 16;
-  const int rb = block % a.row_blocks, hb = block / a.row_blocks;
-  const int h = hb % a.dm.Hq, bl = hb / a.dm.Hq, b = bl / a.dm.L, l = bl % a.dm.L, g = h / a.dm.G;
+  const int b = bl / a.dm.L, l = bl % a.dm.L, g = h / a.dm.G;
   const int n_c = a.ks.n_c, n = n_c + a.ks.c;
   const int row0 = rb * kTile, t = min(row0 + col, a.rows - 1);  // rows past the end repeat the last one and are not stored
   const int limit = a.causal ? n_c + t : n - 1;                  // last candidate the lane's row sees
@@ -116,7 +115,7 @@ __device__ __forceinline__ void attn_f32_body(const AttnF32Args& a, int block, c
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[hh][c] = f64x4{0, 0, 0, 0};
 
-  for (int kt = w; kt < tiles; kt += kWaves) {
+  for (int kt = w; kt < tiles; kt += WAVES) {
     const int j0 = kt * kTile;
     Operand<D> k;
     load_operand(k, cand_ptr(a.ks, b, l, g, min(j0 + col, n - 1)), lane);
@@ -211,36 +210,38 @@ __device__ __forceinline__ void attn_f32_body(const AttnF32Args& a, int block, c
                   static_cast<float>(acc[hh][3][i])};
   }
   __syncthreads();
-  // thread: query row r, four elements of its output; the waves' parts in a fixed order
-  const int r = tid / (kThreads / kTile), e = tid % (kThreads / kTile) * 4;
-  if (row0 + r >= a.rows) return;
-  float mw[kWaves], mm = -INFINITY;
+  // query row r, four elements of its output; the waves' parts in a fixed order
+  for (int x = tid; x < kTile * (D / 4); x += WAVES * kWave) {
+    const int r = x / (D / 4), e = x % (D / 4) * 4;
+    if (row0 + r >= a.rows) break;
+    float mw[WAVES], mm = -INFINITY;
 #pragma unroll
-  for (int x = 0; x < kWaves; ++x) {
-    mw[x] = m_s[x * kTile + r];
-    mm = fmaxf(mm, mw[x]);
-  }
-  float sum = 0.f;
-  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int y = 0; y < WAVES; ++y) {
+      mw[y] = m_s[y * kTile + r];
+      mm = fmaxf(mm, mw[y]);
+    }
+    float sum = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int x = 0; x < kWaves; ++x) {
-    // A wave without a key the row sees adds 0 * 0.  So does one whose logits are all -inf, and one whose logits are NaN
-    // (which a maximum passes over) adds its NaN: no part is left out.
-    const float f = expf(mw[x] - mm);
-    sum += l_s[x * kTile + r] * f;
-    if (values && e < D) o += *reinterpret_cast<const f32x4*>(o_s + (x * kTile + r) * kPitch + e) * f;
+    for (int y = 0; y < WAVES; ++y) {
+      // A wave without a key the row sees adds 0 * 0.  So does one whose logits are all -inf, and one whose logits are NaN
+      // (which a maximum passes over) adds its NaN: no part is left out.
+      const float f = expf(mw[y] - mm);
+      sum += l_s[y * kTile + r] * f;
+      if (values) o += *reinterpret_cast<const f32x4*>(o_s + (y * kTile + r) * kPitch + e) * f;
+    }
+    if (values) {
+      const float inv = 1.f / sum;
+      *reinterpret_cast<f32x4*>(const_cast<float*>(row_ptr(a.out, b, l, h, row0 + r)) + e) = o * inv;
+    }
+    if (a.lse != nullptr && e == 0) a.lse[(static_cast<int64_t>(bl) * a.dm.Hq + h) * a.rows + row0 + r] = mm + logf(sum);
   }
-  if (values && e < D) {
-    const float inv = 1.f / sum;
-    *reinterpret_cast<f32x4*>(const_cast<float*>(row_ptr(a.out, b, l, h, row0 + r)) + e) = o * inv;
-  }
-  if (a.lse != nullptr && e == 0) a.lse[(static_cast<int64_t>(bl) * a.dm.Hq + h) * a.rows + row0 + r] = mm + logf(sum);
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) void attn_f32_kernel(AttnF32Args a) {
+template <int D, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void attn_f32_kernel(AttnF32Args a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  attn_f32_body<D>(a, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), smem);
+  attn_f32_body<D, WAVES>(a, blockIdx.x, blockIdx.y, blockIdx.z, smem);
 }
 
 // Column sums: score[g, j] = sum over the query rows of the KV group of exp(s - lse).  A workgroup owns two tiles of sixteen
@@ -325,12 +326,12 @@ bool score_f32_fits(const Dims& dm, int rows, int n) {
 constexpr int kScoreF32LdsBytes = kWaves * score_row_tiles<64>() * kTile * 8;
 
 template <int D>
-__device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int unit, char* smem) {
+__device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int g, int bl, char* smem) {
   constexpr int kScoreRowTiles = score_row_tiles<D>();
   float2* const stats = reinterpret_cast<float2*>(smem);  // [waves][row tiles][16]: maximum, sum
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int col = lane % 16, quad = lane / 16;
-  const int g = unit % a.dm.Hkv, bl = unit / a.dm.Hkv, b = bl / a.dm.L, l = bl % a.dm.L;
+  const int b = bl / a.dm.L, l = bl % a.dm.L;
   const int n = a.ks.n_c + a.ks.c;
   const int total = a.dm.G * a.rows, row_tiles = (total + kTile - 1) / kTile;
   const double scale = static_cast<double>(a.dm.scale);
@@ -421,7 +422,7 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int unit, 
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
       const int j = j0 + 4 * x + quad;
-      if (col == 0 && j < n) a.score[static_cast<int64_t>(unit) * n + j] = v;
+      if (col == 0 && j < n) a.score[(static_cast<int64_t>(bl) * a.dm.Hkv + g) * n + j] = v;
     }
   }
 }
@@ -429,16 +430,20 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int unit, 
 template <int D>
 __global__ __launch_bounds__(kThreads) void score_f32_kernel(ScoreF32Args a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  score_f32_body<D>(a, blockIdx.x + gridDim.x * blockIdx.y, smem);
+  score_f32_body<D>(a, blockIdx.x, blockIdx.y, smem);
 }
 // A step's attention and instruction score in one launch; neither reads what the other writes.
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_score_f32_kernel(AttnF32Args a, ScoreF32Args s, int score_blocks) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  if (static_cast<int>(blockIdx.x) < score_blocks)
-    score_f32_body<D>(s, blockIdx.x, smem);
-  else
-    attn_f32_body<D>(a, blockIdx.x - score_blocks, smem);
+  int block = blockIdx.x;
+  if (block < score_blocks) {
+    score_f32_body<D>(s, block % s.dm.Hkv, block / s.dm.Hkv, smem);
+  } else {
+    block -= score_blocks;
+    const int hb = block / a.row_blocks;
+    attn_f32_body<D, kWaves>(a, block % a.row_blocks, hb % a.dm.Hq, hb / a.dm.Hq, smem);
+  }
 }
 
 AttnF32Args attn_f32_args(const Dims& dm, const View& q, int rows, const Segments& ks, const Segments& vs, int causal,
@@ -449,18 +454,37 @@ AttnF32Args attn_f32_args(const Dims& dm, const View& q, int rows, const Segment
 dim3 attn_f32_grid(const AttnF32Args& a) { return dim3(a.row_blocks, a.dm.Hq, a.dm.B * a.dm.L); }
 int64_t attn_f32_blocks(const Dims& dm, int rows) { return static_cast<int64_t>((rows + kTile - 1) / kTile) * dm.Hq * dm.B * dm.L; }
 
-template <int D>
+// Waves of a workgroup, which split the keys of its sixteen rows.  Eight while two workgroups of eight to a compute unit have room
+// for all of them: the chain over the keys is the time.  In larger launches the other workgroups fill the chip, and
+// waves that have few keys or none, their LDS and the exchange at the end are what is left of it.  us with one | two | four |
+// eight waves (and with one wave on the vector units per row), one row per head, workgroups in brackets.  head_dim 64, 6
+// states 7.5 | 7.8 | 11.0 | 18.0 (8.9) (1024), 23 | 35 | 49 | 117 (35) (8192); 65 states 15.1 | 14.6 | 11.8 | 15.6 (12.2) (512), 17.5 |
+// 16.5 | 18.0 | 28.4 (14.6) (1024), 27.8 | 32.4 | 30.9 | 53.5 (27.8) (2048); 1001 states 134 | 111 | 65 | 71 (97) (512), 244 | 258 |
+// 210 | 256 (224) (2048).  head_dim 128, 65 states 22 | 17 | 22 | 23 (18) (512), 40 | 55 | 78 | 79 (48) (2048); 1001 states 200 |
+// 113 | 116 | 111 (129) (512), 380 | 446 | 463 | 423 (440) (2048); 3001 states 752 | 651 |
+// 659 | 601 (837) (1024); 128 rows over 384 states 547 | 665 | 736 | 721 (8192).
+int attn_f32_waves(const Dims& dm, int rows, int n) {
+  const int64_t blocks = attn_f32_blocks(dm, rows);
+  const int cus = compute_units(), tiles = (n + kTile - 1) / kTile;
+  if (blocks < 2 * cus) return kWaves;
+  if (dm.D == 64) return tiles <= 2 || blocks >= 16 * cus || (tiles <= 8 && blocks >= 4 * cus) ? 1 : 4;
+  return tiles <= 1 || blocks >= 8 * cus ? 1 : tiles > 48 ? kWaves : 2;
+}
+
+template <int D, int WAVES>
 hipError_t attn_f32_launch(const AttnF32Args& a, hipStream_t st) {
+  constexpr int kLdsBytes = attn_f32_lds_bytes<D, WAVES>();
+  const auto kern = attn_f32_kernel<D, WAVES>;
   static LdsLimit limit;
-  const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_f32_kernel<D>), attn_f32_lds_bytes<D>());
+  const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_f32_kernel<D>, attn_f32_grid(a), dim3(kThreads), attn_f32_lds_bytes<D>(), st, a);
+  hipLaunchKernelGGL(kern, attn_f32_grid(a), dim3(WAVES * kWave), kLdsBytes, st, a);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t attn_score_f32_launch(const AttnF32Args& a, const ScoreF32Args& s, hipStream_t st) {
-  constexpr int kLdsBytes = std::max(attn_f32_lds_bytes<D>(), kScoreF32LdsBytes);
+  constexpr int kLdsBytes = std::max(attn_f32_lds_bytes<D, kWaves>(), kScoreF32LdsBytes);
   static LdsLimit limit;
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_score_f32_kernel<D>), kLdsBytes);
   if (e != hipSuccess) return e;
@@ -475,7 +499,10 @@ hipError_t attn_score_f32_launch(const AttnF32Args& a, const ScoreF32Args& s, hi
 hipError_t launch_attn_f32(const Dims& dm, View q, int rows, Segments ks, Segments vs, int causal, View out, float* lse,
                            hipStream_t st) {
   const AttnF32Args a = attn_f32_args(dm, q, rows, ks, vs, causal, out, lse);
-  return dm.D == 64 ? attn_f32_launch<64>(a, st) : attn_f32_launch<128>(a, st);
+  const int waves = attn_f32_waves(dm, rows, ks.n_c + ks.c);
+  const auto launch = dm.D == 64 ? (waves == 8 ? attn_f32_launch<64, 8> : waves == 4 ? attn_f32_launch<64, 4> : attn_f32_launch<64, 1>)
+                                 : (waves == 8 ? attn_f32_launch<128, 8> : waves == 2 ? attn_f32_launch<128, 2> : attn_f32_launch<128, 1>);
+  return launch(a, st);
 }
 
 hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse, float* score,
@@ -501,8 +528,7 @@ hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments ks,
 }
 
 bool attn_score_f32_in_one_launch(const Dims& dm, int rows, int instr_rows, int n) {
-  constexpr int64_t kMostBlocks = (int64_t{1} << 32) / kThreads - 1;  // of a one-dimensional grid
-  return score_f32_fits(dm, instr_rows, n) && attn_f32_blocks(dm, rows) + static_cast<int64_t>(dm.B) * dm.L * dm.Hkv <= kMostBlocks;
+  return score_f32_fits(dm, instr_rows, n) && attn_f32_waves(dm, rows, n) == kWaves;  // the score's workgroups have eight
 }
 
 hipError_t launch_attn_score_f32(const Dims& dm, View q, Segments ks, Segments vs, View out, View q_instr, int instr_rows,

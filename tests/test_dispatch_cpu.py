@@ -104,10 +104,10 @@ def test_f32_launches_of_many_heads_stay_within_a_grid(tmp_path):
     """8.45 million heads of a row each: more than 2^32 work-items if the grid were one-dimensional."""
     attn, decode, score, document = in_child(f32_of_many_heads, tmp_path)
     names = lambda launches: [x[0] for x in launches if x[0] != "lds"]
-    assert names(attn) == ["attn_f32_kernel<64>"] and names(decode) == ["attn_f32_kernel<64>", "compact_kernel"]
-    assert names(score) == ["score_f32_kernel<64>"] and names(document)[:2] == ["attn_f32_kernel<64>", "score_f32_kernel<64>"]
+    assert names(attn) == ["attn_f32_kernel<64, 1>"] and names(decode) == ["attn_f32_kernel<64, 1>", "compact_kernel"]
+    assert names(score) == ["score_f32_kernel<64>"] and names(document)[:2] == ["attn_f32_kernel<64, 1>", "score_f32_kernel<64>"]
     for launch in attn + decode + score + document:
-        if launch[0] in ("attn_f32_kernel<64>", "score_f32_kernel<64>"):
+        if launch[0] in ("attn_f32_kernel<64, 1>", "score_f32_kernel<64>"):
             assert _product(launch[1]) == 65535 * 129
 
 

@@ -22,6 +22,9 @@ CASES = [
     (1, 4, 1, 1, 511, 17),      # 512 keys, 68 rows
     (1, 2, 2, 64, 449, 5),      # 513 keys
     (1, 3, 3, 31, 700, 40),
+    # from 512 workgroups of sixteen rows on: fewer waves, by the number of keys, and more of them at 1024, 2048 and 4096
+    (16, 32, 8, 1, 30, 2), (16, 32, 8, 1, 32, 2), (16, 16, 4, 17, 200, 3), (16, 32, 8, 1, 14, 2), (16, 32, 8, 1, 16, 2),
+    (32, 32, 8, 1, 127, 2), (32, 32, 8, 1, 130, 2), (64, 16, 16, 20, 33, 1), (64, 32, 16, 33, 40, 1),
 ]
 
 
