@@ -226,6 +226,23 @@ def test_evictions_that_memory_bounds_are_two_launches(tmp_path):
                                                                        "compact_kernel"]), shape
 
 
+def strip_cases(api, launches, cases):
+    out = []
+    for L, Hq, Hkv, rows, n_c, c, head_dim in cases:
+        cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=c, budget=n_c + 3, instr_len=rows)
+        q, k, ws = Fake(1, L, Hq, rows, head_dim), Fake(1, L, Hkv, n_c + 3, head_dim), workspace(api, cfg)
+        calls = launches(lambda: api.citrus_instr_score(cfg, q, k, n_c, Fake(1, L, Hkv, c, head_dim), score=q, workspace=ws, stream=0))
+        out.append("S" if any("instr_strip_kernel" in x[0] for x in calls) else "T")
+    return out
+
+
+def test_the_strip_tests_run_the_kernel_they_name(tmp_path):
+    from test_gpu_strips import CASES
+    cases = [[*case[:6], head_dim] for case in CASES for head_dim in (64, 128)]
+    ran = in_child(strip_cases, tmp_path, cases=cases)
+    assert [a + b for a, b in zip(ran[::2], ran[1::2])] == [case[6] for case in CASES]
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)

@@ -1,6 +1,7 @@
-"""Selection and gather in one launch: every instance of the kernel at the edges of its range (candidates per thread, parts of
-a unit with a remainder, one and several partial sums), against the same steps issued one by one, bit for bit.  What is
-compared with is itself compared with the oracle in test_gpu_parity.py."""
+"""The eviction of one cache: every instance of the kernel that selects and gathers in one launch at the edges of its range
+(candidates per thread, parts of a unit with a remainder, one and several partial sums), and what lies beyond it, against the same
+steps issued one by one, bit for bit.  What is compared with is itself compared with the oracle in test_gpu_parity.py.  Two
+caches, appended rows and carried sums: test_gpu_fused_launches.py."""
 
 import pytest
 import torch
@@ -22,6 +23,7 @@ CASES = [
     (1, 4, 1, 64, 8, 96, 64, 0, "f32"),
     (1, 4, 2, 128, 3, 511, 500, 4, "bf16"),    # two candidates per thread, the last thread's one
     (1, 4, 2, 64, 3, 512, 17, 0, "bf16"),
+    (1, 4, 2, 128, 17, 512, 300, 0, "bf16"), (2, 8, 2, 64, 64, 257, 200, 3, "bf16"),  # two per thread; partial sums
     (1, 8, 2, 128, 64, 513, 512, 0, "bf16"),   # five per thread; partial sums
     (1, 32, 8, 128, 64, 1280, 768, 2, "bf16"),
     (2, 32, 8, 128, 64, 1281, 1280, 0, "bf16"),  # eight per thread; one state leaves

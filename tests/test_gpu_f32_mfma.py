@@ -4,6 +4,8 @@ single-launch score, and with values that are not finite where some rows do not 
 Tolerance of the mode: 1e-5.  Logits are exact to f64; a probability keeps the rounding of its f32 argument, 2^-24 of |s - max| in
 the exponent, and of f32 sums."""
 
+import dataclasses
+
 import pytest
 import torch
 
@@ -63,11 +65,15 @@ def test_step_against_f64(case, head_dim):
     close(lse, want_lse)
     close(lm, p.sum(dim=3).unflatten(2, (Hkv, Hq // Hkv)).sum(dim=3))
     close(score, want_score)
-    # one chunk of a document: attention and score in one launch where they can be, the same bits
+    # one chunk of a document: attention and score in one launch where they can be, outputs and selection by the same bits
     out_doc = torch.empty_like(out)
-    state = api.DocumentState.allocate(cfg)
-    api.citrus_process_document(cfg, state, ws, doc=api.resident_doc(cfg, q, k, v, qi, out_doc))
+    some = dataclasses.replace(cfg, budget=max(1, c // 2), cache_capacity=0)
+    state = api.DocumentState.allocate(some)
+    api.citrus_process_document(some, state, ws, doc=api.resident_doc(cfg, q, k, v, qi, out_doc))
     assert torch.equal(out_doc, api.citrus_chunk_attn(cfg, q, kc, vc, 0, k, v))
+    kept = api.citrus_topk_select(cfg, api.citrus_instr_score(cfg, qi, kc, 0, k, workspace=ws), some.budget)
+    rows_of = kept.long()[..., None].expand(-1, -1, -1, -1, head_dim)
+    assert torch.equal(state.current()[0], torch.gather(k, 3, rows_of)) and torch.equal(state.current()[1], torch.gather(v, 3, rows_of))
     # a value that is not finite reaches the rows that see its key, and no other
     for bad in (float("inf"), float("nan")):
         v2 = v.clone()

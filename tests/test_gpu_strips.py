@@ -12,29 +12,33 @@ import paper_2406_12018_amd as api
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
-# layers, query heads, KV heads, rows, cache, chunk
+# layers, query heads, KV heads, rows, cache, chunk; what runs at head dimension 64 and 128: strips or two passes
+# (test_dispatch_cpu.py checks that it does)
 CASES = [
-    (1, 1, 1, 1, 0, 1),
-    (1, 2, 1, 16, 0, 33),        # one strip, one wave with a second tile
-    (1, 4, 2, 17, 31, 226),      # 68 rows; 257 keys; a cache that ends inside a tile
-    (1, 4, 1, 8, 1000, 280),     # 1280 keys
-    (1, 4, 1, 9, 1000, 281),     # 1281: ten tiles per wave
-    (1, 8, 2, 64, 2000, 560),    # 2560
-    (1, 8, 2, 64, 2000, 561),    # two passes
-    (5, 32, 8, 51, 300, 213),    # 204 rows: 32-row strips no longer fit side by side, 64-row strips with a rest of 12
-    (1, 64, 2, 128, 500, 37),    # 4096 rows per KV head
-    (1, 64, 2, 129, 500, 37),    # 4128: two passes
-    (24, 32, 8, 64, 100, 60),    # 192 KV heads of four strips: strips
-    (25, 32, 8, 64, 100, 60),    # 200: one round of the two-pass kernel at head_dim 128
-    (32, 32, 8, 49, 100, 61),    # 256 of 196 rows
-    (40, 8, 8, 40, 100, 50),     # one head per KV head, 320 KV heads
+    (1, 1, 1, 1, 0, 1, "SS"),
+    (1, 2, 1, 16, 0, 33, "SS"),        # one strip, one wave with a second tile
+    (1, 4, 2, 17, 31, 226, "SS"),      # 68 rows; 257 keys; a cache that ends inside a tile
+    (1, 4, 1, 8, 1000, 280, "SS"),     # 1280 keys
+    (1, 4, 1, 9, 1000, 281, "SS"),     # 1281: ten tiles per wave
+    (1, 8, 2, 64, 2000, 560, "SS"),    # 2560
+    (1, 8, 2, 64, 2000, 561, "TT"),
+    (5, 32, 8, 51, 300, 213, "SS"),    # 204 rows: 32-row strips no longer fit side by side, 64-row strips with a rest of 12
+    (1, 64, 2, 128, 475, 37, "SS"),    # 4096 rows per KV head, 512 keys: as many as the scratch holds
+    (1, 64, 2, 128, 476, 37, "TT"),
+    (1, 64, 2, 129, 400, 37, "TT"),    # 4128 rows
+    (24, 32, 8, 64, 250, 60, "SS"),    # 192 KV heads of four strips of 64
+    (25, 32, 8, 64, 250, 60, "ST"),    # 200: one round of the two-pass kernel at head_dim 128
+    (32, 32, 8, 49, 100, 61, "ST"),    # 256 of 196 rows
+    (40, 8, 8, 40, 100, 50, "TS"),     # one strip per KV head, 320 KV heads
+    (16, 32, 8, 32, 1000, 281, "SS"), (17, 32, 8, 32, 1000, 281, "TT"),  # 128 rows, 1281 keys: two strips per compute unit
+    (2, 8, 2, 256, 1000, 281, "SS"), (8, 8, 2, 256, 1000, 281, "TS"),    # 1024 rows of four heads
 ]
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(x) for x in c))
 def test_scores_against_f64(case, head_dim):
-    L, Hq, Hkv, rows, n_c, c = case
+    L, Hq, Hkv, rows, n_c, c, _ = case
     print(f"strip scores {case} head_dim {head_dim}", flush=True)
     g = torch.Generator(device="cpu").manual_seed(5)
     mk = lambda *shape: torch.randn(shape, generator=g).to(torch.bfloat16).to(DEV)
