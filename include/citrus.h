@@ -130,7 +130,7 @@ typedef struct {
   int32_t layers;         /* L                                               >= 1;  B*L <= 65535 */
   int32_t q_heads;        /* Hq, a multiple of kv_heads, <= 65535; and B*L*Hq*ceil(max(chunk_len, instr_len)/32)
                              < 2^28 (the largest launch: 8 workgroups per 32 rows of a head), and
-                             Hq/Hkv*max(chunk_len, instr_len) < 2^31 (the rows of a KV head); else CITRUS_ERR_SHAPE */
+                             Hq/Hkv*max(chunk_len, instr_len) <= 2^31 - 65536 (the rows of a KV head); else CITRUS_ERR_SHAPE */
   int32_t kv_heads;       /* Hkv                                             >= 1 */
   int32_t head_dim;       /* d: 64 or 128.  bf16 runs on matrix-core (MFMA) kernels, f32 on plain vector kernels,
                              which are meant for tests and small shapes                                   */

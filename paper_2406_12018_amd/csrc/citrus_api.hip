@@ -28,8 +28,8 @@ citrus_status check_config(const citrus_config* c) {
     const int64_t rows_max = c->chunk_len > c->instr_len ? c->chunk_len : c->instr_len;
     const int64_t blocks = static_cast<int64_t>(c->batch) * c->layers * c->q_heads * ((rows_max + 31) / 32) * kMaxKeySplits;
     if (blocks >= (int64_t{1} << 31)) return CITRUS_ERR_SHAPE;
-    // the scores number a KV head's query rows (its heads' rows, one after the other) in 32 bits
-    if (c->q_heads / c->kv_heads * rows_max >= (int64_t{1} << 31)) return CITRUS_ERR_SHAPE;
+    // the scores number a KV head's query rows (its heads' rows, one after the other) in 32 bits, rounded up to their tiles
+    if (c->q_heads / c->kv_heads * rows_max > (int64_t{1} << 31) - 65536) return CITRUS_ERR_SHAPE;
   }
   if (c->cache_mode != CITRUS_CACHE_INSTR && c->cache_mode != CITRUS_CACHE_SHARED &&
       c->cache_mode != CITRUS_CACHE_DUAL && c->cache_mode != CITRUS_CACHE_STANDARD)

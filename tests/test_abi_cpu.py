@@ -74,9 +74,10 @@ def test_status_strings():
     # the largest launch (8 workgroups per 32 rows of every head) has to stay a 31-bit grid
     ({"batch": 64, "layers": 1000, "q_heads": 4096, "kv_heads": 512, "chunk_len": 64}, False),
     ({"batch": 64, "layers": 1000, "q_heads": 2048, "kv_heads": 512, "chunk_len": 64}, True),
-    # the query rows of a KV head are numbered in 31 bits: 65535 heads of 32768 rows are, of 32769 are not
-    ({"q_heads": 65535, "kv_heads": 1, "instr_len": 32768}, True), ({"q_heads": 65535, "kv_heads": 1, "instr_len": 32769}, False),
+    # the query rows of a KV head are numbered in 31 bits, rounded up to tiles
+    ({"q_heads": 65535, "kv_heads": 1, "instr_len": 32767}, True), ({"q_heads": 65535, "kv_heads": 1, "instr_len": 32768}, False),
     ({"q_heads": 65535, "kv_heads": 1, "chunk_len": 32769}, False), ({"q_heads": 65534, "kv_heads": 2, "instr_len": 32769}, True),
+    ({"q_heads": 1, "kv_heads": 1, "instr_len": 2 ** 31 - 65536}, True), ({"q_heads": 1, "kv_heads": 1, "instr_len": 2 ** 31 - 1}, False),
     ({"cache_mode": B.CACHE_DUAL, "budget_lm": 16, "lm_ordering": B.LM_EVICT_THEN_APPEND}, True),
     # the evict-then-append cache keeps a whole chunk beside the budget
     ({"cache_mode": B.CACHE_DUAL, "budget_lm": 48, "lm_ordering": B.LM_EVICT_THEN_APPEND, "cache_capacity": 64}, False),
