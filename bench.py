@@ -525,7 +525,10 @@ def main():
         "roofline_other": roofline_other,
         "peaks_measured": peaks,
         "phase_ms_per_step": phase_ms,
-        "phase_note": "phases: one extra untimed document with all events; roofline: events around every chunk-attention "
+        "phase_note": "phases and roofline_other: untimed documents with all events, which keep launches apart that a step merges "
+                      "without them (selection and gather below 96 MB of kept keys and values: evict_kernel; chunk attention and "
+                      "instruction score of a small step: attn_score_kernel, which the event behind the attention in the timed region "
+                      "keeps apart too); roofline: events around every chunk-attention "
                       + ("launch of the untimed eager documents (the timed region replays a graph without events)" if graph
                          else "launch of the timed region") + ("; select and compact run concurrently with chunk_attn (their times "
                                                       "are not additive)" if overlap else ""),

@@ -132,8 +132,8 @@ typedef struct {
                              < 2^28 (the largest launch: 8 workgroups per 32 rows of a head), and
                              Hq/Hkv*max(chunk_len, instr_len) <= 2^31 - 65536 (the rows of a KV head); else CITRUS_ERR_SHAPE */
   int32_t kv_heads;       /* Hkv                                             >= 1 */
-  int32_t head_dim;       /* d: 64 or 128.  bf16 runs on matrix-core (MFMA) kernels, f32 on plain vector kernels,
-                             which are meant for tests and small shapes                                   */
+  int32_t head_dim;       /* d: 64 or 128.  bf16 runs on the bf16 matrix instructions, f32 on the f64 ones: a mode
+                             of full precision, meant for tests and small shapes                          */
   int32_t chunk_len;      /* l_s: maximum chunk length c                     >= 1 */
   int32_t budget;         /* k: states kept in the (instruction) cache       >= 1 */
   int32_t budget_lm;      /* DUAL: budget of the language-modelling cache; else ignored */
@@ -460,9 +460,11 @@ int32_t citrus_resident_provider(void* user, int32_t chunk_index, void* hip_stre
  *                 unless DUAL), 5 after the instruction score, 6 after the
  *                 selection, 7 after the compaction.  A NULL entry is skipped (every
  *                 recorded event costs a few microseconds of stream time).  For
- *                 per-phase timing only.  A selection and its gather are one launch where they can
- *                 be, and those of DUAL's two caches one launch behind the instruction score, unless
- *                 an event that lies between them is asked for.
+ *                 per-phase timing only.  Events between two steps keep their launches apart that are
+ *                 merged otherwise (same results): 1 to 4 the chunk attention and the instruction
+ *                 score of a small step in the single-cache modes, 3 and 6 a selection and its gather,
+ *                 and 3, 4, 5 and 6 the evictions of DUAL's two caches, one launch behind the
+ *                 instruction score.
  * side            optional (NULL: every launch goes to hip_stream in the order a1 .. a4).  A second stream
  *                 of the same device and two events, all created by the caller.  In the single-cache
  *                 modes (INSTR, SHARED) a step then runs its instruction score first, and its selection

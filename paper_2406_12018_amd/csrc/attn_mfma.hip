@@ -999,7 +999,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int bloc
 // Four waves, smaller launches: half of the rows per workgroup and one wave per SIMD, which has the matrix pipe to itself
 // (attn_launch has the line between the two).  A row's sums run over the same tiles in the same order in either: its
 // bits do not depend on the size of the launch.  (Splitting the keys of a row between two pairs of waves as well gave
-// 19.8 instead of 24.4 us at 32/8 heads, 512 rows over 768 + 512 states, but other bits.)
+// 19.8 instead of 24.4 us at 32/8 heads, 512 rows over 768 + 512 states; with it a row's bits would follow the launch.)
 template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char ring[attn_ring_bytes<D>()];
@@ -1019,7 +1019,7 @@ __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void att
 // Chunk attention and instruction score of a step in one launch: neither reads what the other writes, and a small step
 // leaves compute units idle in both.  The workgroups have the score's eight waves; those of the attention use four.
 // What bounds it: the attention's chain, behind which the score disappears.  One layer of 32/8 heads, 512 rows and 64
-// instruction rows over 768 + 512 states: 22.4 + 9.2 us in two launches, 23.4 in one; a document of it 641 -> 500 us.
+// instruction rows over 768 + 512 states: 22.4 + 9.2 us in two launches, 23.4 in one; a document of it, 7941 tokens, 525 us.
 template <int D, bool ROTATE_Q, int TPW>
 __global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a, int attn_blocks, StripArgs s) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];

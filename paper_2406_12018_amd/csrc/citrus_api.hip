@@ -159,7 +159,7 @@ citrus_status check_workspace(const citrus_config* c, const void* ws, size_t byt
   return CITRUS_OK;
 }
 
-// ---- dispatch: MFMA kernels for bf16, vector kernels for f32 ----
+// ---- dispatch: kernels on the bf16 matrix instructions for bf16, on the f64 ones for f32 ----
 
 hipError_t run_colsum(const citrus_config* c, const Dims& dm, View q, int rows, Segments ks, int causal,
                       const float* lse, float* score, hipStream_t st) {

@@ -172,7 +172,7 @@ hipError_t launch_compact(int elem_bytes, const Dims& dm, Segments kseg, Segment
 // order, followed by the last `appended` candidates.
 struct Eviction {
   Segments ks, vs;
-  ScoreSums score;  // not read while n <= k
+  ScoreSums score;  // not read while n <= k, unless acc_new is given: the kept states then take their sums along
   int n, k, forced, appended;
   int32_t* idx;     // optional, pitch k
   View k_new, v_new;

@@ -430,8 +430,8 @@ __global__ __launch_bounds__(256) void compact_kernel(CompactArgs a) {
 // What bounds it: in small launches the chain arguments -> scores -> passes -> rows, four trips to memory of about 1 us
 // each and 1.5 us of passes; the launches it replaces (sum of partial scores, selection, gather) took at least 4.4 us each
 // whatever they did.  One layer of 32/8 heads, 1280 candidates, budget 768: 14.3 us in three launches, 9.0 in one.  Large
-// ones are bound by memory and take what two launches took (256 units: 39.8 us against 6.7 + 33.0).  A document with two
-// caches of 128 units each: 5147 -> 4944 us, four launches of a step in one.
+// ones are bound by memory and no faster than two launches (256 units 39.8 us against 6.7 + 33.0): evict_in_one_launch has the
+// line.  A document with two caches of 128 units each, four launches of a step in one: 4.85 ms.
 struct EvictJob {
   GatherViews v;
   const float* score;  // [units][sums][n]
