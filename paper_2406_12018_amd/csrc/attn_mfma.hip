@@ -8,9 +8,7 @@
 //                      over 64-key tiles staged in LDS, S^T = K.Q^T and
 //                      O^T = V^T.P^T on v_mfma_f32_32x32x16_bf16.
 //  lse_mfma_kernel     the rows' log-sum-exp alone (first pass of the two-pass
-//                      importance scores).
-//  colsum_mfma_kernel  summed form of Eq. (1): probabilities exp(s - lse)
-//                      added down the query rows of a KV group, per key.
+//                      importance scores; the second is colsum.hip).
 //
 // Layout facts used throughout (wave64, v_mfma_f32_32x32x16_bf16):
 //   A operand: lane l holds row (l % 32), contraction slots 8*(l / 32) .. +7
@@ -20,7 +18,6 @@
 // Computing S^T (keys x queries) puts one query per lane, so softmax row
 // reductions are in-lane plus one exchange with lane l ^ 32, and the S^T
 // accumulators are directly the B operand (P^T) of the second product.
-#pragma clang diagnostic ignored "-Winline-asm"
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -29,6 +26,7 @@
 #include "bf16_math.h"
 #include "citrus_internal.h"
 #include "mfma_common.h"
+#include "mfma_pipe.h"
 #include "rope_math.h"
 #include "strip_score.h"
 
@@ -49,19 +47,6 @@ __device__ inline i16x4 lds_read_tr16(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
 }
 
-// Instructions whose issue ORDER matters (a software pipeline that overlaps the matrix pipe with
-// the exponentials inside one wave) are written as volatile asm statements: the compiler keeps
-// volatile statements in source order and allocates their registers, but does not see inside
-// them, so the software-managed hazards are handled here: v_exp_f32 is followed by the one wait
-// state a non-transcendental consumer needs, and no vector instruction may read an MFMA result
-// sooner than the MFMA takes to complete (callers keep a whole MFMA group in between).
-__device__ inline f32x16 mfma_pinned_first(const bf16x8& a, const bf16x8& b) {  // accumulator starts at zero
-  f32x16 d;
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0"
-               : "=&v"(d)
-               : "v"(__builtin_bit_cast(i32x4, a)), "v"(__builtin_bit_cast(i32x4, b)));
-  return d;
-}
 __device__ inline float exp2_pinned(float x) {
   float y;
   asm volatile("v_exp_f32 %0, %1\n\ts_nop 0" : "=v"(y) : "v"(x));
@@ -106,9 +91,6 @@ __device__ inline uint32_t formed_here(uint32_t x) {
 __device__ inline void keep_values_here(uint32_t (&p)[8], float& l) {
   asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(p[5]), "+v"(p[6]), "+v"(p[7]), "+v"(l));
 }
-// enough wait states for every MFMA issued through the pinned helpers above to have written its result
-__device__ inline void wait_for_pinned_mfmas() { asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory"); }
-
 // Barrier that publishes tiles streamed into LDS by buffer_load ... lds.  Those writes are tracked
 // by the issuing wave's vector-memory counter only, and the fence inside __syncthreads() covers
 // ordinary LDS traffic: every wave has to drain its own loads before it arrives.
@@ -117,34 +99,6 @@ __device__ inline void barrier_after_lds_fill() {
   __syncthreads();
 }
 
-// One LDS-direct load (64 lanes x 16 bytes of global memory to 1 KB of consecutive LDS) as asm: the compiler waits
-// for every such load it can see (vmcnt(0)) in front of the next LDS read that might alias it, i.e. a tile requested
-// between the MFMAs of one half step would be waited for at the start of the next, long before the barrier that
-// publishes it.  Loads issued here are waited for by the barrier helpers alone.  lds + LDS_OFF: byte address.
-template <int LDS_OFF>
-__device__ inline void load_lds_unwatched(const i32x4& rsrc, uint32_t lds, int lane_off, int scalar_off) {
-  asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off), "n"(LDS_OFF)
-               : "m0", "scc");
-}
-// Buffer resource of `bytes` bytes at p as the four words the asm above takes.
-__device__ inline i32x4 buffer_words(const void* p, int bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  i32x4 words = {static_cast<int>(a), static_cast<int>(a >> 32) & 0xffff, bytes, kBufferFlags};
-  asm volatile("" : "+s"(words));  // one value: known to be constant, the last word was moved in place in front of each use
-  return words;
-}
-
-// All but the newest LEFT loads of this wave have landed, and then every wave's have (PUBLISH: its LDS accesses are
-// through as well).
-template <int LEFT, bool PUBLISH>
-__device__ inline void wait_loads_and_barrier() {
-  if constexpr (PUBLISH)
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LEFT) : "memory");
-  else
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(LEFT) : "memory");
-}
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 // lanes 0..31: first = own lo_half, second = lo_half of lane l + 32; lanes 32..63: first = hi_half of lane l - 32,
 // second = own hi_half
@@ -153,29 +107,6 @@ __device__ inline void swap_halves(uint32_t lo_half, uint32_t hi_half, uint32_t&
   first = r[0];
   second = r[1];
 }
-__device__ inline void lds_writes_and_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// K and V tiles of the attention kernel in LDS.  A 1 KB load instruction fills one block of kR whole rows (a lane group
-// reads one row of global memory: lanes of different rows next to each other would cost the address path a multiple);
-// inside a row, segment seg (16 bytes) is at position seg ^ (kStep x (row / kRowStep % 4)), and blocks are 16 bytes
-// further apart than they are long.  The XOR touches two bits of the segment only, so the operand reads of a lane need
-// four (K) and two (V) base registers, and every address in the key loop is one of them plus a constant: no instruction
-// of the loop forms an address.  Sixteen consecutive rows of one segment (a cycle of a key operand) fall into different
-// banks, and so do the four rows of two segments of a 16-lane group of a transpose read; but two such groups go through
-// the LDS at a time, and at head_dim 128 rows r and r ^ 2 of the two meet in the same banks: two extra LDS cycles per
-// transpose read (SQ_LDS_BANK_CONFLICT, 31 % of the cycles the LDS works, which is 41 % of the launch's).
-template <int D>
-struct Lay {
-  static constexpr int kR = Geo<D>::kRowsPerLoad;
-  static constexpr int kStep = D == 128 ? 4 : 2, kRowStep = D == 128 ? 1 : 2;
-  static constexpr int kBlock = 1024 + 16;
-  static constexpr int kHalf = 32 / kR * kBlock;  // 32 rows
-  static constexpr int kTile = 2 * kHalf;
-  __device__ static constexpr int swz(int row) { return kStep * (row / kRowStep % 4); }
-  __device__ static constexpr int at(int row, int seg) {
-    return row / kR * kBlock + row % kR * Geo<D>::kRowBytes + (seg ^ swz(row)) * 16;
-  }
-};
 
 // How the waves of a block split (head, 32-row tile) tasks inside one KV group.
 struct TaskShape {
@@ -1051,178 +982,6 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(float2* part, int k
   part[row] = make_float2(m + log2f(lsum), 1.f);
 }
 
-// Summed form of Eq. (1): score[g, j] = sum over the query rows of the KV group of
-// exp(s - lse).  One wave per 32 candidate keys, which stay in registers as the A operand; the
-// group's query rows (all its heads, flattened) are staged through LDS in chunks of 128 rows and
-// stream by as B operands.  Per-lane partial sums are reduced across the 32 query lanes once at
-// the end, in a fixed order: no atomics, bit-reproducible.
-constexpr int kColsumWaves = 8;
-constexpr int kColsumKeyTiles = 1;  // 32-key tiles per wave: a workgroup covers 256 keys per staged Q chunk
-constexpr int kColsumQRows = 128;   // query rows per LDS chunk
-// STEPWISE: rows is a multiple of kColsumQRows, so every chunk of staged rows is full and lies inside one
-// head (an instance of its own: both address paths in one kernel cost the registers that two workgroups
-// per compute unit need).
-template <int D, bool STEPWISE>
-__global__ __launch_bounds__(kColsumWaves * 64, 4) void colsum_mfma_kernel(Dims dm, View q, int rows, Segments ks,
-                                                                        int causal, const float* norm, int norm_pitch,
-                                                                        float to_log2, float* score) {
-  typedef Geo<D> T;
-  constexpr int kPitchK = T::kPitchK;
-  // two staging buffers of query rows and their normalisers (log2 domain, +inf for padding rows)
-  extern __shared__ __attribute__((aligned(16))) char colsum_smem[];
-  uint16_t* const q_sb = reinterpret_cast<uint16_t*>(colsum_smem);                        // [2][kColsumQRows][kPitchK]
-  float* const lse_sb = reinterpret_cast<float*>(q_sb + 2 * kColsumQRows * kPitchK);      // [2][kColsumQRows]
-  const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
-  const int col = lane % 32, grp = lane / 32;
-  const int g = blockIdx.y, bl = blockIdx.z, b = bl / dm.L, l = bl % dm.L;
-  const int n_c = ks.n_c, n = n_c + ks.c;
-  const int j0 = (blockIdx.x * kColsumWaves + w) * (32 * kColsumKeyTiles);
-  const bool wave_has_keys = j0 < n;
-  const int j_last = j0 + 32 * kColsumKeyTiles - 1;
-
-  bf16x8 k_op[kColsumKeyTiles][T::kKk];
-  // bases and strides are read once: a per-lane choice between the two structs' fields would compile to a
-  // per-lane load of the chosen field from the argument block
-  const uint16_t* const k_cache_u = unit_ptr(ks.cache, b, l, g) + 8 * grp;
-  const uint16_t* const k_chunk_u = unit_ptr(ks.chunk, b, l, g) + 8 * grp;
-  const int64_t k_ss_cache = ks.cache.ss, k_ss_chunk = ks.chunk.ss;
-#pragma unroll
-  for (int kt = 0; kt < kColsumKeyTiles; ++kt) {
-    const int j = min(j0 + 32 * kt + col, n - 1);
-    const bool in_cache = j < n_c;
-    const int64_t off = in_cache ? j * k_ss_cache : (j - n_c) * k_ss_chunk;
-    const uint16_t* kp = (in_cache ? k_cache_u : k_chunk_u) + off;
-#pragma unroll
-    for (int kk = 0; kk < T::kKk; ++kk) {
-      Pack8 p;
-      p.u = *reinterpret_cast<const uint4*>(kp + 16 * kk);
-      k_op[kt][kk] = p.v;
-    }
-  }
-  const float c2 = dm.scale * kLog2e;
-  float acc[kColsumKeyTiles][16];
-#pragma unroll
-  for (int kt = 0; kt < kColsumKeyTiles; ++kt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[kt][i] = 0.f;
-
-  const int total_rows = dm.G * rows;  // flattened (head in group, row)
-  // The rows of chunk c + 1 are requested (into registers) before the products of chunk c start and
-  // written to the other buffer afterwards: one barrier per chunk, no exposed load latency.
-  // A thread stages 16 bytes of rows st_row + kStageStep x of a chunk.  STEPWISE: every chunk lies inside one head
-  // and is full, so its first row is a wave-uniform pointer that moves on by adds, and a thread's part of the
-  // address never changes; dividing the flattened row index by `rows` for every load cost more vector
-  // instructions per chunk than three of its four products.
-  constexpr int kStageStep = kColsumWaves * 64 / T::kSegs;  // rows between a thread's loads: kSegs threads per row, 16 bytes each
-  constexpr int kStageLoads = kColsumQRows / kStageStep;
-  const int st_row = tid / T::kSegs, st_seg = tid % T::kSegs;
-  i32x4 q_in[kStageLoads];
-  float lse_in = INFINITY;
-  const int64_t lse_row0 = (static_cast<int64_t>(bl) * dm.Hq + g * dm.G) * rows;  // the group's heads are consecutive
-  const uint32_t q_thread_off = (st_row * static_cast<uint32_t>(q.ss) + 8 * st_seg) * 2;  // bytes; a head's rows span < 2 GiB
-  int stage_head = 0, stage_row = 0;  // where the next requested chunk starts (block-uniform)
-  auto request_chunk = [&](int f0) {
-    if constexpr (STEPWISE) {
-      const uint16_t* const base = unit_ptr(q, b, l, g * dm.G + stage_head) + static_cast<int64_t>(stage_row) * q.ss;
-#pragma unroll
-      for (int x = 0; x < kStageLoads; ++x) {  // scalar base per load + one 32-bit per-thread byte offset
-        const char* const base_x = reinterpret_cast<const char*>(base + x * kStageStep * q.ss);
-        q_in[x] = *reinterpret_cast<const i32x4*>(base_x + q_thread_off);
-      }
-      stage_row += kColsumQRows;
-      if (stage_row == rows) {
-        stage_row = 0;
-        ++stage_head;
-      }
-    } else {
-#pragma unroll
-      for (int x = 0; x < kStageLoads; ++x) {
-        const int f = min(f0 + st_row + x * kStageStep, total_rows - 1);
-        const int hh = f / rows, t = f % rows;
-        q_in[x] = *reinterpret_cast<const i32x4*>(unit_ptr(q, b, l, g * dm.G + hh) + static_cast<int64_t>(t) * q.ss +
-                                                  8 * st_seg);
-      }
-    }
-    float v = INFINITY;  // padding rows contribute exp2(-inf) = 0
-    if (tid < kColsumQRows && f0 + tid < total_rows) v = norm[(lse_row0 + f0 + tid) * norm_pitch] * to_log2;
-    lse_in = v;
-  };
-  request_chunk(0);
-  int buf = 0;
-  int chunk_row = 0;  // STEPWISE: row of its head at which the chunk being multiplied starts
-  for (int f0 = 0; f0 < total_rows; f0 += kColsumQRows, buf ^= 1) {
-    const int f_cnt = min(kColsumQRows, total_rows - f0);
-    uint16_t* const q_s = q_sb + buf * (kColsumQRows * kPitchK);
-    float* const lse_s = lse_sb + buf * kColsumQRows;
-    // this buffer was last read two chunks ago, and every wave has passed the previous chunk's barrier since
-#pragma unroll
-    for (int x = 0; x < kStageLoads; ++x)
-      *reinterpret_cast<i32x4*>(&q_s[(st_row + x * kStageStep) * kPitchK + 8 * st_seg]) = q_in[x];
-    if (tid < kColsumQRows) lse_s[tid] = lse_in;
-    if (f0 + kColsumQRows < total_rows) request_chunk(f0 + kColsumQRows);  // block-uniform
-    __syncthreads();
-    if (wave_has_keys) {
-      for (int qt = 0; qt * 32 < f_cnt; ++qt) {
-        const int tile_row = STEPWISE ? chunk_row + 32 * qt : (f0 + 32 * qt) % rows;  // wave-uniform
-        if (causal) {  // wave-uniform: skip query tiles none of whose rows sees any key of this wave
-          const int t_first = tile_row;
-          const int t_last = t_first + 31 >= rows ? rows - 1 : t_first + 31;  // a tile that wraps reaches a head's end
-          if (n_c + t_last < j0) continue;
-        }
-        Pack8 qb[T::kKk];
-        const uint16_t* qrow = &q_s[(32 * qt + col) * kPitchK + 8 * grp];
-#pragma unroll
-        for (int kk = 0; kk < T::kKk; ++kk) qb[kk].u = *reinterpret_cast<const uint4*>(qrow + 16 * kk);
-        const float lse2 = lse_s[32 * qt + col];
-        // A mask is needed only where a key of this wave can be invisible to a row of this tile:
-        // past the last candidate, or (causal) a chunk key later than the tile's first row.  The
-        // flattened rows of one 32-row tile span at most two heads; t_lo is the smallest chunk row.
-        const int f_first = f0 + 32 * qt;
-        int t_lo = tile_row;
-        if (t_lo + 31 >= rows) t_lo = 0;                            // tile wraps into the next head
-        const bool need_mask = (j_last >= n) || (causal && j_last > n_c + t_lo);
-        int limit = n - 1;
-        if (need_mask && causal) limit = n_c + (STEPWISE ? tile_row + col : (f_first + col) % rows);
-#pragma unroll
-        for (int kt = 0; kt < kColsumKeyTiles; ++kt) {
-          f32x16 s_t;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s_t[i] = 0.f;
-#pragma unroll
-          for (int kk = 0; kk < T::kKk; ++kk)
-            s_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op[kt][kk], qb[kk].v, s_t, 0, 0, 0);
-          if (need_mask) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const int j = j0 + 32 * kt + 8 * (i / 4) + 4 * grp + (i % 4);
-              const float p = __builtin_amdgcn_exp2f(fmaf(s_t[i], c2, -lse2));
-              acc[kt][i] += (j <= limit) ? p : 0.f;
-            }
-          } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[kt][i] += __builtin_amdgcn_exp2f(fmaf(s_t[i], c2, -lse2));
-          }
-        }
-      }
-    }
-    if (STEPWISE) {
-      chunk_row += kColsumQRows;
-      if (chunk_row == rows) chunk_row = 0;
-    }
-  }
-  if (!wave_has_keys) return;
-#pragma unroll
-  for (int kt = 0; kt < kColsumKeyTiles; ++kt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      float v = acc[kt][i];
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      const int j = j0 + 32 * kt + 8 * (i / 4) + 4 * grp + (i % 4);
-      if (col == 0 && j < n) score[(static_cast<int64_t>(bl) * dm.Hkv + g) * n + j] = v;
-    }
-}
-
 // Instruction score (Eq. (1), summed form) in ONE launch for KV groups whose query rows
 // (instruction rows x heads of the group, flattened) fit one LDS chunk: a workgroup owns one
 // (document, layer, KV head).  All its query rows sit in LDS; wave (kw, qh) walks key tiles
@@ -1563,24 +1322,6 @@ hipError_t lse_launch(const Dims& dm, View q, int rows, Segments ks, int key_spl
   return hipGetLastError();
 }
 
-// norm[row * norm_pitch]: the rows' normalisers; times to_log2 they are in the log2 domain.
-template <int D>
-hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int causal, const float* norm, int norm_pitch,
-                         float to_log2, float* score, hipStream_t st) {
-  const int n = ks.n_c + ks.c;
-  constexpr int kKeysPerBlock = 32 * kColsumKeyTiles * kColsumWaves;
-  dim3 grid((n + kKeysPerBlock - 1) / kKeysPerBlock, dm.Hkv, dm.B * dm.L);
-  constexpr int kLdsBytes = 2 * kColsumQRows * (Geo<D>::kPitchK * 2 + 4);  // two buffers of rows and normalisers: 70 KB at 128
-  static LdsLimit limit_stepwise, limit_any;
-  const bool stepwise = rows % kColsumQRows == 0;
-  const auto kern = stepwise ? colsum_mfma_kernel<D, true> : colsum_mfma_kernel<D, false>;
-  const hipError_t e = raise_lds_limit(stepwise ? limit_stepwise : limit_any, reinterpret_cast<const void*>(kern), kLdsBytes);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(kColsumWaves * 64), kLdsBytes, st, dm, q, rows, ks, causal, norm, norm_pitch, to_log2,
-                     score);
-  return hipGetLastError();
-}
-
 template <int D>
 hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, float* workspace, size_t workspace_floats,
                               float* score, hipStream_t st, ScoreSums* sums) {
@@ -1612,7 +1353,7 @@ hipError_t instr_score_launch(const Dims& dm, View q, int rows, Segments ks, flo
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return colsum_launch<D>(dm, q, rows, ks, /*causal=*/0, workspace, 2, 1.f, score, st);
+  return launch_colsum_mfma(dm, q, rows, ks, /*causal=*/0, workspace, 2, 1.f, score, st);
 }
 
 }  // namespace
@@ -1645,12 +1386,6 @@ hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments ks, Segments 
   int strips = 0;
   const hipError_t e = launch(dm, q, ks, vs, out, q_rope_pos0, rope_base, q_instr, instr_rows, part, &strips, st);
   return e != hipSuccess ? e : finish_strip_scores(dm, part, strips, ks.n_c + ks.c, score, st, sums);
-}
-
-hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int causal, const float* lse, float* score,
-                              hipStream_t st) {
-  const auto launch = dm.D == 64 ? colsum_launch<64> : colsum_launch<128>;
-  return launch(dm, q, rows, ks, causal, lse, 1, kLog2e, score, st);
 }
 
 // Instruction score in two launches: partial log-sum-exp over ranges of key tiles (enough

@@ -164,7 +164,7 @@ citrus_status check_workspace(const citrus_config* c, const void* ws, size_t byt
 hipError_t run_colsum(const citrus_config* c, const Dims& dm, View q, int rows, Segments ks, int causal,
                       const float* lse, float* score, hipStream_t st) {
   if (mfma_path_supported(c->dtype, dm))
-    return launch_colsum_mfma(dm, q, rows, ks, causal, lse, score, st);
+    return launch_colsum_mfma(dm, q, rows, ks, causal, lse, 1, 1.4426950408889634f, score, st);
   return launch_colsum_f32(dm, q, rows, ks, causal, lse, score, st);
 }
 

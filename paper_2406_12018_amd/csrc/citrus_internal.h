@@ -67,9 +67,9 @@ bool mfma_path_supported(int dtype, const Dims& dm);
 // rotated to positions q_rope_pos0 + row inside the kernel, with the bits launch_rope would give.
 hipError_t launch_attn_mfma(const Dims& dm, View q, Segments kseg, Segments vseg, View out, float* lse, float* lse_cache,
                             hipStream_t st, int q_rope_pos0 = -1, float rope_base = 0.f);
-// lse: the rows' normalisers (natural log)
-hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments kseg, int causal, const float* lse, float* score,
-                              hipStream_t st);
+// Column sums, colsum.hip.  norm[row * norm_pitch]: the rows' normalisers; times to_log2 they are in the log2 domain.
+hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments kseg, int causal, const float* norm, int norm_pitch,
+                              float to_log2, float* score, hipStream_t st);
 // Most ranges of key tiles a two-launch score splits the keys of a row into (one workgroup per range).
 constexpr int kMaxKeySplits = 8;
 // Floats of scratch that cover every launch_instr_score_mfma call with at most `rows` query rows per head over

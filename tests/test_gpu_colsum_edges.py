@@ -1,0 +1,89 @@
+"""Column sums with known normalisers at the edges of their tiles: rows of several heads in one tile, ragged chunks of rows,
+blocks of 128 and of 256 keys, the causal mask; against float64.
+
+Tolerance: a weight is exp2 of a difference of two numbers below 64 that carry rounding errors of a few 2^-24 each (and a
+product sum of at most 128 exact bf16 products): below 5e-5 relative; a sum of positive weights keeps that."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2406_12018_amd as api
+
+from helpers import np64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def rand(shape, seed):
+    g = torch.Generator(device="cpu").manual_seed(seed)
+    return torch.randn(shape, generator=g, dtype=torch.float32).to(torch.bfloat16).to(DEV)
+
+
+def logits(q, k, G, d):
+    return np.einsum("hqd,hkd->hqk", np64(q), np.repeat(np64(k), G, axis=0)) / np.sqrt(d)
+
+
+def by_group(w, Hkv):  # [Hq, rows, keys] -> [Hkv, keys]
+    return w.reshape(Hkv, -1, w.shape[-1]).sum(1)
+
+
+# L, Hq, Hkv, rows, keys; compute units take 128 keys per workgroup while that is the shorter sum of turns
+SHAPES = [(1, 1, 1, 1, 1), (1, 3, 1, 31, 63), (2, 8, 2, 33, 65), (1, 7, 1, 5, 129), (1, 4, 2, 257, 127), (3, 14, 2, 100, 300),
+          (1, 8, 1, 512, 257), (40, 8, 8, 64, 256), (64, 8, 8, 40, 200), (60, 4, 4, 256, 300)]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+def test_cache_score_with_given_normalisers(shape, head_dim):
+    L, Hq, Hkv, rows, n = shape
+    print(f"column sums {shape} head_dim {head_dim}", flush=True)
+    cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=rows, budget=n, instr_len=4)
+    q, k = rand((1, L, Hq, rows, head_dim), 1), rand((1, L, Hkv, n, head_dim), 2)
+    lse = torch.empty((1, L, Hq, rows), dtype=torch.float32, device=DEV)
+    want = np.empty((L, Hkv, n))
+    for l in range(L):
+        s = logits(q[0, l], k[0, l], Hq // Hkv, head_dim)
+        m = s.max(-1, keepdims=True)
+        norm = (m + np.log(np.exp(s - m).sum(-1, keepdims=True))).astype(np.float32)
+        lse[0, l] = torch.from_numpy(norm[..., 0])
+        want[l] = by_group(np.exp(s - norm.astype(np.float64)), Hkv)
+    score = api.citrus_cache_score(cfg, q, k, n, lse_cache=lse)
+    np.testing.assert_allclose(np64(score[0]), want, rtol=5e-5, atol=1e-9)
+    assert torch.equal(score, api.citrus_cache_score(cfg, q, k, n, lse_cache=lse))
+
+
+# L, Hq, Hkv, rows, cached states: chunks of rows none of which sees a key of the block, tiles that wrap, blocks of both sizes
+CAUSAL = [(1, 2, 1, 1, 0), (1, 4, 1, 33, 0), (1, 3, 1, 97, 31), (2, 8, 2, 300, 70), (1, 4, 2, 600, 0), (1, 8, 1, 640, 130),
+          (64, 8, 8, 130, 100), (40, 8, 8, 300, 0)]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("shape", CAUSAL, ids=lambda s: "-".join(map(str, s)))
+def test_importance_of_the_chunk(shape, head_dim):
+    """Also with a row that sees a NaN: its normaliser is NaN, and so is what it gives to the keys that it sees; the keys
+    behind it are seen by rows that see the NaN as well, and those in front of it get nothing from its row alone."""
+    L, Hq, Hkv, c, n_c = shape
+    print(f"causal column sums {shape} head_dim {head_dim}", flush=True)
+    cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=c, budget=n_c + 1, instr_len=4)
+    q, k, v = rand((1, L, Hq, c, head_dim), 1), rand((1, L, Hkv, c, head_dim), 2), rand((1, L, Hkv, c, head_dim), 3)
+    kc, vc = rand((1, L, Hkv, n_c + 1, head_dim), 4), rand((1, L, Hkv, n_c + 1, head_dim), 5)
+
+    def run(q):
+        lse, score = torch.empty((1, L, Hq, c), dtype=torch.float32, device=DEV), torch.empty((1, L, Hkv, n_c + c), dtype=torch.float32, device=DEV)
+        api.citrus_chunk_attn(cfg, q, kc, vc, n_c, k, v, lse=lse, lm_score=score)
+        return lse, score
+
+    lse, score = run(q)
+    visible = np.arange(n_c + c)[None, None, :] <= n_c + np.arange(c)[None, :, None]
+    for l in sorted({0, L - 1}):
+        s = logits(q[0, l], torch.cat([kc[0, l, :, :n_c], k[0, l]], dim=1), Hq // Hkv, head_dim)
+        w = np.where(visible, np.exp(s - np64(lse[0, l])[..., None]), 0.0)
+        np.testing.assert_allclose(np64(score[0, l]), by_group(w, Hkv), rtol=5e-5, atol=1e-9)
+    bad = c // 2  # one query row of head 0 is NaN: so is its normaliser
+    q_bad = q.clone()
+    q_bad[0, 0, 0, bad] = float("nan")
+    _, score_bad = run(q_bad)
+    assert score_bad[0, 0, 0, :n_c + bad + 1].isnan().all()
+    assert not score_bad[0, 0, 0, n_c + bad + 1:].isnan().any() and torch.equal(score_bad[0, :, 1:], score[0, :, 1:])
