@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "citrus_internal.h"
+#include "evict_body.h"
 
 namespace citrus {
 namespace {
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(kThreads) void colsum_f32_kernel(Dims dm, View q, i
 }
 
 // Instruction score of a KV group whose logits fit the registers of a workgroup (512 keys; 64 rows, at head_dim 128 32): products once,
-// normalisers through LDS, column sums.  No mask.
+// normalisers through LDS, column sums (to out).  No mask.
 struct ScoreF32Args {
   Dims dm;
   View q;
@@ -326,7 +327,7 @@ bool score_f32_fits(const Dims& dm, int rows, int n) {
 constexpr int kScoreF32LdsBytes = kWaves * score_row_tiles<64>() * kTile * 8;
 
 template <int D>
-__device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int g, int bl, char* smem) {
+__device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int g, int bl, char* smem, float* out) {
   constexpr int kScoreRowTiles = score_row_tiles<D>();
   float2* const stats = reinterpret_cast<float2*>(smem);  // [waves][row tiles][16]: maximum, sum
   const int lane = threadIdx.x % kWave, w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -422,7 +423,7 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int g, int
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
       const int j = j0 + 4 * x + quad;
-      if (col == 0 && j < n) a.score[(static_cast<int64_t>(bl) * a.dm.Hkv + g) * n + j] = v;
+      if (col == 0 && j < n) out[j] = v;
     }
   }
 }
@@ -430,15 +431,39 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int g, int
 template <int D>
 __global__ __launch_bounds__(kThreads) void score_f32_kernel(ScoreF32Args a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  score_f32_body<D>(a, blockIdx.x, blockIdx.y, smem);
+  score_f32_body<D>(a, blockIdx.x, blockIdx.y, smem,
+                    a.score + (static_cast<int64_t>(blockIdx.y) * a.dm.Hkv + blockIdx.x) * (a.ks.n_c + a.ks.c));
 }
-// A step's attention and instruction score in one launch; neither reads what the other writes.
+// A step's attention and instruction score in one launch; neither reads what the other writes.  A unit's scores come from one
+// workgroup, which then evicts the unit as well (the rows go to the other buffer, which nothing here reads): behind the
+// attention's chain both disappear.  4 heads, 32 rows over 96 states, 8 instruction
+// rows, head_dim 64: 13.8 us a step in two launches, 13.0 in one; 12.7 of them the score's workgroup.
+constexpr int kTailRows = 8;  // rows of a thread in flight
+constexpr int kTailScores = std::max<int>(kScoreF32LdsBytes, sizeof(SelectLds<1, kThreads, 8>) + kThreads * sizeof(int32_t));
 template <int D>
-__global__ __launch_bounds__(kThreads) void attn_score_f32_kernel(AttnF32Args a, ScoreF32Args s, int score_blocks) {
+__global__ __launch_bounds__(kThreads) void attn_score_f32_kernel(AttnF32Args a, ScoreF32Args s, int score_blocks, StepTail t) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  typedef SelectLds<1, kThreads, 8> Lds;  // 512 candidates
+  static_assert(kScoreKeyTiles * kWaves * kTile <= kThreads);
   int block = blockIdx.x;
   if (block < score_blocks) {
-    score_f32_body<D>(s, block % s.dm.Hkv, block / s.dm.Hkv, smem);
+    Lds& lds = *reinterpret_cast<Lds*>(smem);
+    int32_t* const sel = reinterpret_cast<int32_t*>(smem + sizeof(Lds));
+    float* const scores = reinterpret_cast<float*>(smem + kTailScores);  // what the selection reads does not leave the workgroup
+    int unit = block, r0 = 0;
+    if (t.then == Then::kGather) {
+      unit = block / t.job.parts;
+      r0 = (block - unit * t.job.parts) * t.job.part_rows;
+    } else {
+      const int g = block % s.dm.Hkv, bl = block / s.dm.Hkv, n = s.ks.n_c + s.ks.c;
+      score_f32_body<D>(s, g, bl, smem, scores);
+      __syncthreads();
+      if (t.then == Then::kNothing) {
+        if (static_cast<int>(threadIdx.x) < n) s.score[static_cast<int64_t>(block) * n + threadIdx.x] = scores[threadIdx.x];
+        return;
+      }
+    }
+    evict_rows<1, kThreads, 8, Scores::kOneHead, kTailRows>(t.job, unit, scores, r0, min(r0 + t.job.part_rows, t.job.rows), lds, sel);
   } else {
     block -= score_blocks;
     const int hb = block / a.row_blocks;
@@ -483,14 +508,22 @@ hipError_t attn_f32_launch(const AttnF32Args& a, hipStream_t st) {
 }
 
 template <int D>
-hipError_t attn_score_f32_launch(const AttnF32Args& a, const ScoreF32Args& s, hipStream_t st) {
+hipError_t attn_score_f32_launch(const AttnF32Args& a, const ScoreF32Args& s, const Eviction* evict, hipStream_t st) {
   constexpr int kLdsBytes = std::max(attn_f32_lds_bytes<D, kWaves>(), kScoreF32LdsBytes);
+  static_assert(kTailScores + kThreads * sizeof(float) <= kLdsBytes);
   static LdsLimit limit;
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(attn_score_f32_kernel<D>), kLdsBytes);
   if (e != hipSuccess) return e;
-  const int units = s.dm.B * s.dm.L * s.dm.Hkv;
-  const int blocks = units + static_cast<int>(attn_f32_blocks(a.dm, a.rows));
-  hipLaunchKernelGGL(attn_score_f32_kernel<D>, dim3(blocks), dim3(kThreads), kLdsBytes, st, a, s, units);
+  const int units = s.dm.B * s.dm.L * s.dm.Hkv, attn_blocks = static_cast<int>(attn_f32_blocks(a.dm, a.rows));
+  StepTail t;
+  t.then = Then::kNothing;
+  if (evict != nullptr) {
+    t.job = evict_job(sizeof(float), s.dm, *evict);
+    t.then = gather_only(*evict) ? Then::kGather : Then::kEvict;
+    if (t.then == Then::kGather) cut_in_parts(t.job, 32, (2 * compute_units() - attn_blocks) / units);
+  }
+  const int score_blocks = t.then == Then::kGather ? units * t.job.parts : units;
+  hipLaunchKernelGGL(attn_score_f32_kernel<D>, dim3(score_blocks + attn_blocks), dim3(kThreads), kLdsBytes, st, a, s, score_blocks, t);
   return hipGetLastError();
 }
 
@@ -527,15 +560,21 @@ hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments ks,
   return e != hipSuccess ? e : launch_colsum_f32(dm, q, rows, ks, /*causal=*/0, lse_scratch, score, st);
 }
 
+// One workgroup moves a unit's rows: from 128 KB on the launch that shares them out is faster.  us a step apart | one launch,
+// bytes kept: 57 KB 16.1 | 15.2, 123 KB 25.8 | 25.3, 227 KB 26.7 | 28.5, 251 KB 30.3 | 32.1.
+bool step_f32_in_one_launch(const Dims& dm, const Eviction& e) {
+  return gather_only(e) || 2 * static_cast<int64_t>(std::min(e.n, e.k)) * dm.D * static_cast<int>(sizeof(float)) <= 128 << 10;
+}
+
 bool attn_score_f32_in_one_launch(const Dims& dm, int rows, int instr_rows, int n) {
   return score_f32_fits(dm, instr_rows, n) && attn_f32_waves(dm, rows, n) == kWaves;  // the score's workgroups have eight
 }
 
 hipError_t launch_attn_score_f32(const Dims& dm, View q, Segments ks, Segments vs, View out, View q_instr, int instr_rows,
-                                 float* score, hipStream_t st) {
+                                 float* score, const Eviction* evict, hipStream_t st) {
   const AttnF32Args a = attn_f32_args(dm, q, ks.c, ks, vs, /*causal=*/1, out, nullptr);
   const ScoreF32Args s{dm, q_instr, instr_rows, ks, score};
-  return dm.D == 64 ? attn_score_f32_launch<64>(a, s, st) : attn_score_f32_launch<128>(a, s, st);
+  return dm.D == 64 ? attn_score_f32_launch<64>(a, s, evict, st) : attn_score_f32_launch<128>(a, s, evict, st);
 }
 
 }  // namespace citrus

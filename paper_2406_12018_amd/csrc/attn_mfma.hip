@@ -25,6 +25,7 @@
 #include "attn_row.h"
 #include "bf16_math.h"
 #include "citrus_internal.h"
+#include "evict_body.h"
 #include "mfma_common.h"
 #include "mfma_pipe.h"
 #include "rope_math.h"
@@ -951,15 +952,55 @@ __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void att
 // leaves compute units idle in both.  The workgroups have the score's eight waves; those of the attention use four.
 // What bounds it: the attention's chain, behind which the score disappears.  One layer of 32/8 heads, 512 rows and 64
 // instruction rows over 768 + 512 states: 22.4 + 9.2 us in two launches, 23.4 in one; a document of it, 7941 tokens, 525 us.
+// The eviction by those scores can be part of the launch too: the workgroup that is the last of its unit's strips to have
+// written its column selects and moves the unit's rows (into the other buffer, which nothing here reads).  No workgroup waits
+// for another one.  The document above 406 us instead of 525; 8/4 heads, 43 rows and 86 instruction rows over 463 + 430 states, a
+// step 24.3 -> 17.7.
+constexpr int kTailRows = 8;  // rows of a thread in flight: one workgroup moves all rows of a unit
+template <int TPW>
+using TailLds = SelectLds<TPW * kStripWaves * kStripKeys / kStripThreads + 1, kStripThreads, 11>;
 template <int D, bool ROTATE_Q, int TPW>
-__global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a, int attn_blocks, StripArgs s) {
+__global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a, int attn_blocks, StripArgs s, StepTail t) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
+  __shared__ int last;
   if (static_cast<int>(blockIdx.x) < attn_blocks) {
     if (threadIdx.x >= kThreads) return;  // an ended wave counts at no barrier
     attn_pipe_body<D, kWaves, ROTATE_Q, true>(a, blockIdx.x, smem, smem + attn_ring_bytes<D>());
-  } else {
-    strip_score_body<D, 1, TPW, ROTATE_Q>(s, blockIdx.x - attn_blocks, smem);
+    return;
   }
+  const int block = blockIdx.x - attn_blocks;
+  constexpr int kItems = TPW * kStripWaves * kStripKeys / kStripThreads + 1;
+  TailLds<TPW>& lds = *reinterpret_cast<TailLds<TPW>*>(smem);
+  int32_t* const sel = reinterpret_cast<int32_t*>(smem + sizeof(TailLds<TPW>));
+  int unit = 0, r0 = 0;
+  if (t.then == Then::kGather) {
+    unit = block / t.job.parts;
+    r0 = (block - unit * t.job.parts) * t.job.part_rows;
+  } else {
+    unit = strip_score_body<D, 1, TPW, ROTATE_Q>(s, block, smem);
+    if (t.then == Then::kNothing) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's part of the column is in the cache that its XCD shares
+    __syncthreads();
+    if (s.strips > 1) {
+      if (threadIdx.x == 0) {
+        __threadfence();  // ... and now where every XCD finds it
+        last = atomicAdd(t.tickets + unit, 1) == s.strips - 1;
+        if (last) atomicExch(t.tickets + unit, 0);
+      }
+      __syncthreads();
+      if (!last) return;
+      __threadfence();  // the other strips' columns are read from where they wrote them
+    }
+  }
+  const int r1 = min(r0 + t.job.part_rows, t.job.rows);
+  if (t.job.sums > 1)
+    evict_rows<kItems, kStripThreads, 11, Scores::kSumByHead, kTailRows>(t.job, unit, unit_scores(t.job, unit), r0, r1, lds, sel);
+  else
+    evict_rows<kItems, kStripThreads, 11, Scores::kOneHead, kTailRows>(t.job, unit, unit_scores(t.job, unit), r0, r1, lds, sel);
+}
+__global__ __launch_bounds__(256) void clear_tickets_kernel(int32_t* tickets, int count) {
+  const int x = blockIdx.x * 256 + threadIdx.x;
+  if (x < count) tickets[x] = 0;
 }
 
 // Brings the per-range (maximum, sum) pairs of a row, part[s * rows_total + row], to one normaliser,
@@ -1275,17 +1316,31 @@ bool attn_segments_fit(const Segments& ks, const Segments& vs) {
 
 template <int D, bool ROTATE_Q, int TPW>
 hipError_t attn_score_launch(const Dims& dm, View q, Segments ks, Segments vs, View out, int q_rope_pos0, float rope_base,
-                             View q_instr, int instr_rows, float* part, int* strips, hipStream_t st) {
+                             View q_instr, int instr_rows, float* part, int* strips, const Eviction* evict,
+                             int32_t* tickets, hipStream_t st) {
   int blocks = 0;
   const AttnArgs a = attn_args<D, kWaves>(dm, q, ks, vs, false, out, nullptr, nullptr, q_rope_pos0, rope_base, &blocks);
   const StripArgs s = strip_args(dm, q_instr, instr_rows, ks, 32, part);
   *strips = s.strips;
   constexpr int kLdsBytes = std::max(attn_ring_bytes<D>() + attn_stage_bytes<D, kWaves>(), strip_lds_bytes<D, 1>());
+  static_assert(sizeof(TailLds<TPW>) + TPW * kStripWaves * kStripKeys * sizeof(int32_t) <= kLdsBytes);
+  const int units = dm.B * dm.L * dm.Hkv;
+  StepTail t;
+  t.then = Then::kNothing;
+  if (evict != nullptr) {
+    Eviction e = *evict;
+    e.score = ScoreSums{part, s.strips};
+    t.job = evict_job(sizeof(uint16_t), dm, e);
+    t.tickets = tickets;
+    t.then = gather_only(e) ? Then::kGather : Then::kEvict;
+    if (t.then == Then::kGather) cut_in_parts(t.job, 32, (compute_units() - blocks) / units);
+  }
   const auto kern = attn_score_kernel<D, ROTATE_Q, TPW>;
   static LdsLimit limit;
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(blocks + dm.B * dm.L * dm.Hkv * s.strips), dim3(kStripThreads), kLdsBytes, st, a, blocks, s);
+  const int score_blocks = units * (t.then == Then::kGather ? t.job.parts : s.strips);
+  hipLaunchKernelGGL(kern, dim3(blocks + score_blocks), dim3(kStripThreads), kLdsBytes, st, a, blocks, s, t);
   return hipGetLastError();
 }
 
@@ -1373,9 +1428,24 @@ bool attn_score_in_one_launch(const Dims& dm, const Segments& ks, const Segments
          instr_strip_supported(dm, q_instr, instr_rows, ks);
 }
 
+// Several strips per unit: the last workgroup's chain (write back, count, read the columns) is longer than a launch of its own
+// where the attention is over sooner.  us a step, apart | one launch, tiles of 64 keys: 2 tiles, 5 strips 12.7 | 13.8; 3 tiles, 9
+// strips 14.6 | 14.3; 4 tiles, 4 strips 15.2 | 13.9; 13 tiles, 2 strips 23.1 | 19.5; 20 tiles, 8 strips 33.6 | 26.5; one strip ahead
+// everywhere, 2 tiles 12.7 | 10.1, 14 tiles 24.1 | 19.3.
+bool step_in_one_launch(const Dims& dm, const Segments& ks, int instr_rows, const Eviction& e) {
+  const auto tiles = [](int rows) { return (rows + kTileN - 1) / kTileN; };
+  return gather_only(e) || dm.G * instr_rows <= 32 || tiles(ks.n_c) + tiles(ks.c) > 2;
+}
+bool step_needs_tickets(const Dims& dm, int instr_rows, const Eviction& e) { return dm.G * instr_rows > 32 && !gather_only(e); }
+hipError_t launch_clear_tickets(const Dims& dm, int32_t* tickets, hipStream_t st) {
+  const int units = dm.B * dm.L * dm.Hkv;
+  hipLaunchKernelGGL(clear_tickets_kernel, dim3((units + 255) / 256), dim3(256), 0, st, tickets, units);
+  return hipGetLastError();
+}
+
 hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments ks, Segments vs, View out, int q_rope_pos0, float rope_base,
                                   View q_instr, int instr_rows, float* workspace, float* score, hipStream_t st,
-                                  ScoreSums* sums) {
+                                  ScoreSums* sums, const Eviction* evict, int32_t* tickets) {
   const bool rotate = q_rope_pos0 >= 0, shorter = ks.n_c + ks.c <= kStripMaxKeysShort;
   auto launch = dm.D == 128 ? (rotate ? (shorter ? attn_score_launch<128, true, 5> : attn_score_launch<128, true, 10>)
                                       : (shorter ? attn_score_launch<128, false, 5> : attn_score_launch<128, false, 10>))
@@ -1384,8 +1454,8 @@ hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments ks, Segments 
   const int total = dm.G * instr_rows;
   float* const part = total <= 32 ? score : workspace;  // one strip: its column is the score
   int strips = 0;
-  const hipError_t e = launch(dm, q, ks, vs, out, q_rope_pos0, rope_base, q_instr, instr_rows, part, &strips, st);
-  return e != hipSuccess ? e : finish_strip_scores(dm, part, strips, ks.n_c + ks.c, score, st, sums);
+  const hipError_t e = launch(dm, q, ks, vs, out, q_rope_pos0, rope_base, q_instr, instr_rows, part, &strips, evict, tickets, st);
+  return e != hipSuccess || evict != nullptr ? e : finish_strip_scores(dm, part, strips, ks.n_c + ks.c, score, st, sums);
 }
 
 // Instruction score in two launches: partial log-sum-exp over ranges of key tiles (enough

@@ -670,6 +670,9 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
   int32_t* idx_lm_ws = reinterpret_cast<int32_t*>(ws + wl.idx_lm);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const size_t units_sel = static_cast<size_t>(cfg->batch) * cfg->layers * sel_heads(cfg);
+  // One-launch steps count a unit's workgroups here; the block is the one of modes whose chunks score themselves, which have no such steps.
+  int32_t* const tickets = reinterpret_cast<int32_t*>(ws + wl.lse_chunk);
+  bool tickets_clear = false;
 
   int n_c = *cache_len, cur = *buffer_index;
   int n_c_lm = dual ? *cache_len_lm : 0, cur_lm = dual ? *buffer_index_lm : 0;
@@ -851,7 +854,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
     } else {
       Eviction lm;
       bool together = false;  // DUAL: the two caches' evictions share a launch
-      bool scored = false;
+      bool scored = false, evicted = false;
       if (dual) {
         int32_t* idx_lm = idx_history_lm ? idx_history_lm + static_cast<size_t>(done) * units_sel * cfg->budget_lm : idx_lm_ws;
         const ChunkEvicted t{k_cache_lm, v_cache_lm, &n_c_lm, &cur_lm, cfg->budget_lm, score_lm, idx_lm};
@@ -860,13 +863,21 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
         if ((status = chunk_evicted_step(t, io, c, together ? &lm : nullptr)) != CITRUS_OK) break;
       } else if (!timed(1) && !timed(2) && !timed(3) && !timed(4) && attn_and_score_fit(cfg, dm, ks_att, vs, qi_att)) {
         scored = true;
-        if (cfg->dtype == CITRUS_F32)
+        // ... and the eviction by these scores, unless the caller asks for an event in front of it or within it
+        if (cfg->dtype == CITRUS_F32) {
+          evicted = fused && !timed(5) && step_f32_in_one_launch(dm, own);
           status = hip_status(launch_attn_score_f32(dm, make_view(q_att), ks_att, vs, make_view(io.out), make_view(qi_att),
-                                                    cfg->instr_len, score, st));
-        else
+                                                    cfg->instr_len, score, evicted ? &own : nullptr, st));
+        } else {
+          evicted = fused && !timed(5) && step_in_one_launch(dm, ks_att, cfg->instr_len, own);
+          if (evicted && !tickets_clear && step_needs_tickets(dm, cfg->instr_len, own)) {
+            if ((status = hip_status(launch_clear_tickets(dm, tickets, st))) != CITRUS_OK) break;
+            tickets_clear = true;
+          }
           status = hip_status(launch_attn_score_mfma(dm, make_view(q_att), ks_att, vs, make_view(io.out), q_rope_pos0,
                                                      rope_base_of(cfg), make_view(qi_att), cfg->instr_len, lse_instr.ptr, score,
-                                                     st, fused ? &own.score : nullptr));
+                                                     st, fused ? &own.score : nullptr, evicted ? &own : nullptr, tickets));
+        }
         if (status != CITRUS_OK) break;
         mark(done, 5);
       } else {
@@ -883,6 +894,8 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
           n_c_lm = (lm.n < lm.k ? lm.n : lm.k) + lm.appended;
           cur_lm ^= 1;
         }
+        mark(done, 7);
+      } else if (evicted) {
         mark(done, 7);
       } else {
         status = evict(own, score, fused, 6, st);

@@ -39,6 +39,18 @@ struct ScoreSums {
   int sums;
 };
 
+// The eviction of one cache, a selection per KV head: of the first n candidates of [cache ; chunk] the k best stay, in
+// order, followed by the last `appended` candidates.
+struct Eviction {
+  Segments ks, vs;
+  ScoreSums score;  // not read while n <= k, unless acc_new is given: the kept states then take their sums along
+  int n, k, forced, appended;
+  int32_t* idx;     // optional, pitch k
+  View k_new, v_new;
+  const float* acc;  // optional: sums that the cache's states carry (added to their scores) ...
+  float* acc_new;    // ... and that the kept states take along; [B*L*Hkv][acc_pitch]
+  int acc_pitch;
+};
 inline citrus_status hip_status(hipError_t e) { return e == hipSuccess ? CITRUS_OK : CITRUS_ERR_DEVICE; }
 
 // ---- kernels of the f32 mode, attn_generic.hip ----
@@ -53,10 +65,13 @@ hipError_t launch_colsum_f32(const Dims& dm, View q, int rows, Segments kseg, in
 // score[b,l,g,j] = sum_{h in g} sum_{t<rows} softmax_j(scale*q.k); lse_scratch: B*L*Hq*rows floats
 hipError_t launch_instr_score_f32(const Dims& dm, View q, int rows, Segments kseg, float* lse_scratch, float* score,
                                   hipStream_t st);
-// The causal attention of kseg.c rows and the instruction score in one launch, with the bits of the two.
+// The causal attention of kseg.c rows and the instruction score in one launch, with the bits of the two.  evict (optional): the
+// eviction by these scores as well.
 bool attn_score_f32_in_one_launch(const Dims& dm, int rows, int instr_rows, int n);
+// May, and should, the launch evict by its scores as well?
+bool step_f32_in_one_launch(const Dims& dm, const Eviction& evict);
 hipError_t launch_attn_score_f32(const Dims& dm, View q, Segments kseg, Segments vseg, View out, View q_instr, int instr_rows,
-                                 float* score, hipStream_t st);
+                                 float* score, const Eviction* evict, hipStream_t st);
 
 // ---- bf16 MFMA kernels (head_dim 64 and 128: every bf16 configuration), attn_mfma.hip ----
 bool mfma_path_supported(int dtype, const Dims& dm);
@@ -102,9 +117,16 @@ hipError_t finish_strip_scores(const Dims& dm, const float* part, int strips, in
 // ---- chunk attention and instruction score of a small step in one launch, attn_mfma.hip ----
 // The same bits as the two launches.  Both read [cache ; chunk]; q_instr: instr_rows rows per head.
 bool attn_score_in_one_launch(const Dims& dm, const Segments& kseg, const Segments& vseg, const View& q_instr, int instr_rows);
+// May, and should, the launch evict by its scores as well?
+bool step_in_one_launch(const Dims& dm, const Segments& kseg, int instr_rows, const Eviction& evict);
+// evict (optional): the eviction by these scores, made by the launch (tickets: B*L*Hkv of them, zero; zero again afterwards).
+// Otherwise sums as in launch_instr_score_mfma.
 hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments kseg, Segments vseg, View out, int q_rope_pos0,
                                   float rope_base, View q_instr, int instr_rows, float* workspace, float* score,
-                                  hipStream_t st, ScoreSums* sums);
+                                  hipStream_t st, ScoreSums* sums, const Eviction* evict, int32_t* tickets);
+// Does that launch need its tickets?
+bool step_needs_tickets(const Dims& dm, int instr_rows, const Eviction& evict);
+hipError_t launch_clear_tickets(const Dims& dm, int32_t* tickets, hipStream_t st);
 
 // ---- bf16 MFMA decoding step (at most 32 query heads per KV head), decode_attn.hip ----
 bool decode_mfma_supported(int dtype, const Dims& dm);
@@ -168,18 +190,6 @@ hipError_t launch_compact(int elem_bytes, const Dims& dm, Segments kseg, Segment
                           int idx_pitch, int idx_heads, int kept, int appended, View k_new, View v_new,
                           const float* score, int n, float* acc_new, int acc_pitch, hipStream_t st);
 
-// The eviction of one cache, a selection per KV head: of the first n candidates of [cache ; chunk] the k best stay, in
-// order, followed by the last `appended` candidates.
-struct Eviction {
-  Segments ks, vs;
-  ScoreSums score;  // not read while n <= k, unless acc_new is given: the kept states then take their sums along
-  int n, k, forced, appended;
-  int32_t* idx;     // optional, pitch k
-  View k_new, v_new;
-  const float* acc;  // optional: sums that the cache's states carry (added to their scores) ...
-  float* acc_new;    // ... and that the kept states take along; [B*L*Hkv][acc_pitch]
-  int acc_pitch;
-};
 // May, and should, the eviction of a cache that keeps `rows` rows per head, ranking n candidates, be one launch?
 bool evict_in_one_launch(int elem_bytes, const Dims& dm, int n, int rows);
 // One or two evictions in one launch.

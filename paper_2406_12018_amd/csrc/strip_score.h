@@ -96,9 +96,9 @@ constexpr int strip_lds_bytes() {
 
 // ROW_TILES: 32-row tiles per strip; TPW: key tiles a wave can hold (n <= 8 * TPW * 32).  smem: strip_lds_bytes.
 // Kernels cannot share an instance (the compiler's host pass accepts a body with LDS-direct loads once): KERNEL tells those of
-// a translation unit apart.
+// a translation unit apart.  Returns the unit.
 template <int D, int ROW_TILES, int TPW, int KERNEL = 0>
-__device__ __forceinline__ void strip_score_body(const StripArgs& a, int block, char* smem) {
+__device__ __forceinline__ int strip_score_body(const StripArgs& a, int block, char* smem) {
   typedef StripGeo<D> T;
   constexpr int kStripRows = 32 * ROW_TILES;
   // query operands stay in registers where the weights leave room
@@ -333,6 +333,7 @@ __device__ __forceinline__ void strip_score_body(const StripArgs& a, int block, 
     const int x = col >> 1, j = kStripKeys * kt + 8 * (x / 4) + 4 * grp + (x % 4);
     if ((col & 1) == 0 && j < n) dst[j] = tot;
   }
+  return unit;
 }
 
 }  // namespace

@@ -243,6 +243,36 @@ def test_the_strip_tests_run_the_kernel_they_name(tmp_path):
     assert [a + b for a, b in zip(ran[::2], ran[1::2])] == [case[6] for case in CASES]
 
 
+def one_launch_steps(api, launches, cases):
+    """Documents of three chunks: the launches behind which a step ends."""
+    out = []
+    for f32, G, Hkv, d, c, k, rows in cases:
+        cfg = api.Config(batch=1, layers=1, q_heads=G * Hkv, kv_heads=Hkv, head_dim=d, chunk_len=c, budget=k, instr_len=rows,
+                         dtype=api.F32 if f32 else api.BF16)
+        q, cache = Fake(1, 1, G * Hkv, 3 * c, d), lambda i: Fake(1, 1, Hkv, k, d, at=(4 + i) << 20)
+        doc = api.resident_doc(cfg, q, Fake(1, 1, Hkv, 3 * c, d), Fake(1, 1, Hkv, 3 * c, d), Fake(3, 1, 1, G * Hkv, rows, d), q)
+        state = api.DocumentState([cache(0), cache(1)], [cache(2), cache(3)])
+        calls = launches(lambda: api.citrus_process_document(cfg, state, workspace(api, cfg), doc=doc, stream=0))
+        out.append([x[0].split("<")[0] for x in calls if x[0] != "lds"])
+    return out
+
+
+def test_steps_that_are_one_launch(tmp_path):
+    """The counters of a unit's workgroups are cleared once per call, in front of the first step that counts."""
+    bf16, f32, clear, evict = "attn_score_kernel", "attn_score_f32_kernel", "clear_tickets_kernel", "evict_kernel"
+    cases = {(0, 4, 8, 128, 512, 768, 64): [bf16, clear, bf16, bf16],       # the first step keeps all of its states
+             (0, 4, 8, 128, 512, 400, 64): [clear, bf16, bf16, bf16],
+             (0, 4, 8, 128, 512, 2048, 64): [bf16, bf16, bf16],
+             (0, 1, 8, 128, 32, 30, 32): [bf16, bf16, bf16],                # one strip per unit: nothing to count
+             (0, 4, 8, 128, 32, 40, 64): [bf16, bf16, evict, bf16, evict],  # two tiles of 64 keys
+             (0, 4, 8, 128, 64, 70, 64): [bf16, bf16, evict, clear, bf16],  # two, then three
+             (1, 4, 1, 64, 32, 64, 8): [f32, f32, f32],
+             (1, 2, 1, 128, 100, 128, 8): [f32, f32, f32],                  # 128 KB of a unit stay
+             (1, 2, 1, 128, 100, 129, 8): [f32, f32, evict, f32, evict]}
+    for (case, want), got in zip(cases.items(), in_child(one_launch_steps, tmp_path, cases=[list(c) for c in cases])):
+        assert got == want, case
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)
