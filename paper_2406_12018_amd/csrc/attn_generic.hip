@@ -22,6 +22,7 @@
 
 #include "citrus_internal.h"
 #include "evict_body.h"
+#include "lanes.h"
 
 namespace citrus {
 namespace {
@@ -46,12 +47,16 @@ __device__ inline const float* cand_ptr(const Segments& sg, int b, int l, int g,
 __device__ inline f64x4 mfma(double a, double b, const f64x4& c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 // exchange over the four lanes of a column
 __device__ inline float column_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16, kWave));
-  return fmaxf(v, __shfl_xor(v, 32, kWave));
+  float a, b;
+  both_of_rows(v, a, b);
+  both_of_halves(fmaxf(a, b), a, b);
+  return fmaxf(a, b);
 }
 __device__ inline float column_sum(float v) {
-  v += __shfl_xor(v, 16, kWave);
-  return v + __shfl_xor(v, 32, kWave);
+  float a, b;
+  both_of_rows(v, a, b);
+  both_of_halves(a + b, a, b);
+  return a + b;
 }
 
 // The lane's part of sixteen rows as an operand: four elements of its row (l % 16) per 16 of head_dim, from 4 (l / 16).
@@ -293,8 +298,7 @@ __global__ __launch_bounds__(kThreads) void colsum_f32_kernel(Dims dm, View q, i
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {  // over the sixteen rows of a tile = lanes of a quad
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) acc[i] += __shfl_xor(acc[i], o, kWave);
+    acc[i] = row_sum(acc[i]);
     if (col == 0) part[w][4 * i + quad] = acc[i];
   }
   __syncthreads();
@@ -419,9 +423,7 @@ __device__ __forceinline__ void score_f32_body(const ScoreF32Args& a, int g, int
     if (j0 >= n) break;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-      float v = acc[i][x];
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+      const float v = row_sum(acc[i][x]);
       const int j = j0 + 4 * x + quad;
       if (col == 0 && j < n) out[j] = v;
     }

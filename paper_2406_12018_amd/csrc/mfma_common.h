@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "citrus_internal.h"
+#include "lanes.h"
 
 namespace citrus {
 namespace {
@@ -76,22 +77,6 @@ inline FastDiv fast_div(int d) {
   while ((int64_t{1} << f.shift) < d) ++f.shift;
   f.mul = static_cast<uint32_t>(((uint64_t{1} << 32) * ((uint64_t{1} << f.shift) - d)) / d + 1);
   return f;
-}
-// Sum of 16 per-lane values over the 32 lanes that share lane / 32, in 16 exchanges: each step
-// halves the values a lane still carries (the lane keeps the half its own bit selects and takes
-// the partner's partial sum of the same half).  On return lane c holds, for value index c / 2,
-// the total over its 32 lanes.
-__device__ inline float reduce16_over32(const float (&v)[16], int col) {
-  float a[8], b[4], c[2];
-  const bool u16 = col & 16, u8 = col & 8, u4 = col & 4, u2 = col & 2;
-#pragma unroll
-  for (int x = 0; x < 8; ++x) a[x] = (u16 ? v[x + 8] : v[x]) + __shfl_xor(u16 ? v[x] : v[x + 8], 16, 64);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) b[x] = (u8 ? a[x + 4] : a[x]) + __shfl_xor(u8 ? a[x] : a[x + 4], 8, 64);
-#pragma unroll
-  for (int x = 0; x < 2; ++x) c[x] = (u4 ? b[x + 2] : b[x]) + __shfl_xor(u4 ? b[x] : b[x + 2], 4, 64);
-  const float d = (u2 ? c[1] : c[0]) + __shfl_xor(u2 ? c[0] : c[1], 2, 64);
-  return d + __shfl_xor(d, 1, 64);
 }
 
 }  // namespace
