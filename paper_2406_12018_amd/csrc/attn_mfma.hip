@@ -341,6 +341,8 @@ struct AttnArgs {
   float *lse, *lse_cache;
   int q_rope_pos0;
   float rope_log2_base;
+  FastDiv group;  // MIXED: query heads of a group
+  int tasks;      // MIXED: (32-row tile, head) pairs of a unit
 };
 
 // The same attention, with output, as a software pipeline over half tiles of 32 keys: in step h the
@@ -369,7 +371,13 @@ template <int D>
 constexpr int attn_ring_bytes() { return 4 * Lay<D>::kTile; }
 template <int D, int WAVES>
 constexpr int attn_stage_bytes() { return WAVES * Lay<D>::kHalf; }
-template <int D, int WAVES, bool ROTATE_Q, bool SAVE_REGISTERS = ROTATE_Q>
+// MIXED: a block is the next WAVES pairs of a 32-row tile and a head, the heads of a tile next to each other, whichever they are.
+// Otherwise its waves are 4, 2 or 1 heads, whichever divides the group, and row tiles of these: a group of 7 heads then
+// takes 256 rows of a head at a time, of which a chunk of 300 rows has 300 in 512.  MIXED holds more scalars through the key loop
+// (readlanes in it, 3 to 6 % where nothing is wasted), so it is taken where it makes fewer blocks: us, 8 layers of 28/4 heads, 300 rows
+// over 700 states 61.9 | 52.9, 16 layers, 100 rows over 200 states 29.5 | 18.4, 8 layers of 24/8 heads, 333 rows over 500 states
+// 50.5 | 48.8.
+template <int D, int WAVES, bool ROTATE_Q, bool SAVE_REGISTERS = ROTATE_Q, bool MIXED = false>
 __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int block, char* const ring, char* const q_stage) {
   typedef Geo<D> T;
   typedef Lay<D> Y;
@@ -406,7 +414,7 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int bloc
   const int wu = __builtin_amdgcn_readfirstlane(w);  // the wave's index as a scalar: what depends on it stays scalar
   char* const k_s = ring;
   char* const v_s = k_s + 2 * Y::kTile;
-  const int h = ((g * a.head_groups.divisor + hg) << a.log_heads) + (wu & ((1 << a.log_heads) - 1));
+  const int h_of_wave = ((g * a.head_groups.divisor + hg) << a.log_heads) + (wu & ((1 << a.log_heads) - 1));
   const int n_c = a.n_c;
   auto unit = [&](const UnitView& v, int head) { return v.ptr + (b * v.sb + l * v.sl + head * v.sh); };
 
@@ -492,10 +500,14 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int bloc
 
   for (int pass = 0; pass < passes; ++pass) {
   const int rb = pass == 0 ? rb_first : rb_second;
-  const int row0 = rb * rows_per_block + (wu >> a.log_heads) * kRowsPerWave;
+  // MIXED: a task behind the last one has rows behind the last one
+  const int task = rb * WAVES + wu, tile = MIXED ? a.group.quotient(task) : 0;
+  const int h = MIXED ? (g - tile) * a.group.divisor + task : h_of_wave;
+  const int row0 = MIXED ? tile * kRowsPerWave : rb * rows_per_block + (wu >> a.log_heads) * kRowsPerWave;
 
   const int rows = a.c;
-  const int blk_row_last = min(rows, (rb + 1) * rows_per_block) - 1;
+  const int rows_until = MIXED ? (a.group.quotient(min((rb + 1) * WAVES, a.tasks) - 1) + 1) * kRowsPerWave : (rb + 1) * rows_per_block;
+  const int blk_row_last = min(rows, rows_until) - 1;
   const int t_end = cache_tiles + blk_row_last / kTileN + 1;
   // candidates are numbered tile by tile here: chunk state x is candidate chunk0 + x
   const int chunk0 = cache_tiles * kTileN;
@@ -932,20 +944,20 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int bloc
 // (attn_launch has the line between the two).  A row's sums run over the same tiles in the same order in either: its
 // bits do not depend on the size of the launch.  (Splitting the keys of a row between two pairs of waves as well gave
 // 19.8 instead of 24.4 us at 32/8 heads, 512 rows over 768 + 512 states; with it a row's bits would follow the launch.)
-template <int D, int WAVES>
+template <int D, int WAVES, bool MIXED>
 __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char ring[attn_ring_bytes<D>()];
   extern __shared__ __attribute__((aligned(1024))) char q_stage[];
-  attn_pipe_body<D, WAVES, false>(a, blockIdx.x, ring, q_stage);
+  attn_pipe_body<D, WAVES, false, false, MIXED>(a, blockIdx.x, ring, q_stage);
 }
 // The same kernel for query rows that arrive without rotary embedding (position shift): they are rotated
 // in the LDS staging region before the operands are read.  An instance of its own, so that the kernel
 // above does not carry the extra prologue.
-template <int D, int WAVES>
+template <int D, int WAVES, bool MIXED>
 __global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel_rotq(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char ring[attn_ring_bytes<D>()];
   extern __shared__ __attribute__((aligned(1024))) char q_stage[];
-  attn_pipe_body<D, WAVES, true>(a, blockIdx.x, ring, q_stage);
+  attn_pipe_body<D, WAVES, true, true, MIXED>(a, blockIdx.x, ring, q_stage);
 }
 
 // Chunk attention and instruction score of a step in one launch: neither reads what the other writes, and a small step
@@ -1253,7 +1265,7 @@ bool fits_i32(const View& v, int rows) {
 }
 
 // What the kernel needs to know of a launch, and its workgroups.
-template <int D, int WAVES>
+template <int D, int WAVES, bool MIXED = false>
 AttnArgs attn_args(const Dims& dm, View q, Segments ks, Segments vs, bool paired, View out, float* lse,
                    float* lse_cache, int q_rope_pos0, float rope_base, int* blocks) {
   const TaskShape ts = task_shape(dm.G, WAVES);
@@ -1270,10 +1282,13 @@ AttnArgs attn_args(const Dims& dm, View q, Segments ks, Segments vs, bool paired
   a.q_heads = dm.Hq;
   a.log_heads = ts.heads_per_block == 4 ? 2 : ts.heads_per_block - 1;
   a.row_blocks = (rows + rows_per_block - 1) / rows_per_block;
+  a.tasks = dm.G * ((rows + kRowsPerWave - 1) / kRowsPerWave);
+  a.group = fast_div(dm.G);
+  if (MIXED) a.row_blocks = (a.tasks + WAVES - 1) / WAVES;
   a.paired = paired;
   const int slots = paired ? (a.row_blocks + 1) / 2 : a.row_blocks;
   a.slots = fast_div(slots);
-  a.head_groups = fast_div(dm.G / ts.heads_per_block);
+  a.head_groups = fast_div(MIXED ? 1 : dm.G / ts.heads_per_block);
   a.kv_heads = fast_div(dm.Hkv);
   a.layers = fast_div(dm.L);
   const int grid = slots * a.head_groups.divisor * dm.Hkv * dm.B * dm.L;
@@ -1289,14 +1304,14 @@ AttnArgs attn_args(const Dims& dm, View q, Segments ks, Segments vs, bool paired
   return a;
 }
 
-template <int D, int WAVES>
+template <int D, int WAVES, bool MIXED>
 hipError_t attn_pipe_launch(const Dims& dm, View q, Segments ks, Segments vs, bool paired, View out, float* lse,
                             float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
   int grid = 0;
-  const AttnArgs a = attn_args<D, WAVES>(dm, q, ks, vs, paired, out, lse, lse_cache, q_rope_pos0, rope_base, &grid);
+  const AttnArgs a = attn_args<D, WAVES, MIXED>(dm, q, ks, vs, paired, out, lse, lse_cache, q_rope_pos0, rope_base, &grid);
   constexpr int kDynBytes = attn_stage_bytes<D, WAVES>();  // next to the static ring
   static LdsLimit limit, limit_rotq;
-  const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES> : attn_pipe_kernel<D, WAVES>;
+  const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES, MIXED> : attn_pipe_kernel<D, WAVES, MIXED>;
   const hipError_t e = raise_lds_limit(q_rope_pos0 >= 0 ? limit_rotq : limit, reinterpret_cast<const void*>(kern), kDynBytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), kDynBytes, st, a);
@@ -1308,6 +1323,12 @@ int64_t attn_workgroups(const Dims& dm, int rows, int waves) {
   const TaskShape ts = task_shape(dm.G, waves);
   const int block_rows = ts.tiles_per_block * kRowsPerWave;
   return static_cast<int64_t>((rows + block_rows - 1) / block_rows) * (dm.G / ts.heads_per_block) * dm.Hkv * dm.B * dm.L;
+}
+
+// The same for eight waves whose heads are mixed.
+int64_t attn_workgroups_mixed(const Dims& dm, int rows) {
+  constexpr int kWide = 8;
+  return (static_cast<int64_t>(dm.G) * ((rows + kRowsPerWave - 1) / kRowsPerWave) + kWide - 1) / kWide * dm.Hkv * dm.B * dm.L;
 }
 
 bool attn_segments_fit(const Segments& ks, const Segments& vs) {
@@ -1360,9 +1381,11 @@ hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View ou
   const auto workgroups = [&](int waves) { return attn_workgroups(dm, ks.c, waves); };
   const int cus = compute_units();
   if (workgroups(4) <= cus)
-    return attn_pipe_launch<D, 4>(dm, q, ks, vs, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
-  const bool paired = workgroups(8) > cus;
-  return attn_pipe_launch<D, 8>(dm, q, ks, vs, paired, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+    return attn_pipe_launch<D, 4, false>(dm, q, ks, vs, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+  const bool mixed = attn_workgroups_mixed(dm, ks.c) < workgroups(8);
+  const bool paired = (mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8)) > cus;
+  const auto launch = mixed ? attn_pipe_launch<D, 8, true> : attn_pipe_launch<D, 8, false>;
+  return launch(dm, q, ks, vs, paired, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
 // Partial (maximum, sum) pairs of every query row over `key_splits` ranges of the keys.
