@@ -944,17 +944,19 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int bloc
 // (attn_launch has the line between the two).  A row's sums run over the same tiles in the same order in either: its
 // bits do not depend on the size of the launch.  (Splitting the keys of a row between two pairs of waves as well gave
 // 19.8 instead of 24.4 us at 32/8 heads, 512 rows over 768 + 512 states; with it a row's bits would follow the launch.)
-template <int D, int WAVES, bool MIXED>
-__global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel(AttnArgs a) {
+// PER_SIMD: waves per SIMD that the registers are left for.  Three at head_dim 64 with four waves a workgroup (157 registers),
+// three workgroups to a compute unit: smaller pieces, where the larger ones leave the last turn nearly empty.
+template <int D, int WAVES, bool MIXED, int PER_SIMD>
+__global__ __launch_bounds__(WAVES * 64, PER_SIMD) void attn_pipe_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char ring[attn_ring_bytes<D>()];
   extern __shared__ __attribute__((aligned(1024))) char q_stage[];
-  attn_pipe_body<D, WAVES, false, false, MIXED>(a, blockIdx.x, ring, q_stage);
+  attn_pipe_body<D, WAVES, false, (PER_SIMD > 2), MIXED>(a, blockIdx.x, ring, q_stage);
 }
 // The same kernel for query rows that arrive without rotary embedding (position shift): they are rotated
 // in the LDS staging region before the operands are read.  An instance of its own, so that the kernel
 // above does not carry the extra prologue.
-template <int D, int WAVES, bool MIXED>
-__global__ __launch_bounds__(WAVES * 64, D == 128 || WAVES < 8 ? 1 : 2) void attn_pipe_kernel_rotq(AttnArgs a) {
+template <int D, int WAVES, bool MIXED, int PER_SIMD>
+__global__ __launch_bounds__(WAVES * 64, PER_SIMD) void attn_pipe_kernel_rotq(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) char ring[attn_ring_bytes<D>()];
   extern __shared__ __attribute__((aligned(1024))) char q_stage[];
   attn_pipe_body<D, WAVES, true, true, MIXED>(a, blockIdx.x, ring, q_stage);
@@ -1304,14 +1306,14 @@ AttnArgs attn_args(const Dims& dm, View q, Segments ks, Segments vs, bool paired
   return a;
 }
 
-template <int D, int WAVES, bool MIXED>
+template <int D, int WAVES, bool MIXED, int PER_SIMD = D == 128 || WAVES < 8 ? 1 : 2>
 hipError_t attn_pipe_launch(const Dims& dm, View q, Segments ks, Segments vs, bool paired, View out, float* lse,
                             float* lse_cache, hipStream_t st, int q_rope_pos0, float rope_base) {
   int grid = 0;
   const AttnArgs a = attn_args<D, WAVES, MIXED>(dm, q, ks, vs, paired, out, lse, lse_cache, q_rope_pos0, rope_base, &grid);
   constexpr int kDynBytes = attn_stage_bytes<D, WAVES>();  // next to the static ring
   static LdsLimit limit, limit_rotq;
-  const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES, MIXED> : attn_pipe_kernel<D, WAVES, MIXED>;
+  const auto kern = q_rope_pos0 >= 0 ? attn_pipe_kernel_rotq<D, WAVES, MIXED, PER_SIMD> : attn_pipe_kernel<D, WAVES, MIXED, PER_SIMD>;
   const hipError_t e = raise_lds_limit(q_rope_pos0 >= 0 ? limit_rotq : limit, reinterpret_cast<const void*>(kern), kDynBytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES * 64), kDynBytes, st, a);
@@ -1384,8 +1386,26 @@ hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View ou
     return attn_pipe_launch<D, 4, false>(dm, q, ks, vs, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
   const bool mixed = attn_workgroups_mixed(dm, ks.c) < workgroups(8);
   const bool paired = (mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8)) > cus;
-  const auto launch = mixed ? attn_pipe_launch<D, 8, true> : attn_pipe_launch<D, 8, false>;
-  return launch(dm, q, ks, vs, paired, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+  auto launch = mixed ? attn_pipe_launch<D, 8, true> : attn_pipe_launch<D, 8, false>;
+  bool in_pairs = paired;
+  if constexpr (D == 64) {
+    // Workgroups of four waves that leave the registers for three of them on a compute unit, one block each: taken where the pairs'
+    // last turn wastes more of the chip.  Turns are counted in blocks (of half the size for four waves; a block left over
+    // makes pairs end unevenly).  us, pairs | three to a compute unit, 512 rows over 768 states of 32/8 heads: 5 layers 52.5 | 49.4, 8
+    // 62.1 | 64, 9 109.9 | 71.9, 10 109 | 82, 12 109.7 | 94.3, 16 121 | 124, 32 235 | 235; 28/4 heads, 300 rows over 1000 states, 16
+    // layers 135 | 97 (in 256 rows of a head at a time); 8/8 heads, 700 rows over 900 states, 40 layers 213 | 154; 16/8 heads, 333
+    // rows over 500 states, 20 layers 82.5 | 84.6.
+    const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, blocks = mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8);
+    const auto turns = [](int64_t work, int64_t places) { return (work + places - 1) / places; };
+    const int64_t in_pairs_turns = blocks / units % 2 == 0 ? 2 * turns(blocks / 2, cus) : turns(blocks, cus) + 1;
+    const double of_pairs = static_cast<double>(blocks) / (in_pairs_turns * cus);
+    const double of_three = static_cast<double>(workgroups(4)) / (turns(workgroups(4), 3 * cus) * 3 * cus);
+    if (paired && of_three > of_pairs + 0.05) {
+      launch = attn_pipe_launch<64, 4, false, 3>;
+      in_pairs = false;
+    }
+  }
+  return launch(dm, q, ks, vs, in_pairs, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
 // Partial (maximum, sum) pairs of every query row over `key_splits` ranges of the keys.
