@@ -1385,27 +1385,30 @@ hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View ou
   if (workgroups(4) <= cus)
     return attn_pipe_launch<D, 4, false>(dm, q, ks, vs, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
   const bool mixed = attn_workgroups_mixed(dm, ks.c) < workgroups(8);
-  const bool paired = (mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8)) > cus;
+  const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, blocks = mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8);
+  // Beyond that pairs keep the causal work even, and singles leave less of the chip idle in the last turn.  Turns are counted in
+  // blocks; where a block is left over pairs end unevenly.  us in pairs | single, 512 rows over 768 states of 32/8 heads: 5 layers
+  // 70.7 | 72.4, 9 123 | 104, 10 121 | 107, 12 124 | 118, 15 138 | 143, 17 186 | 166, 20 195 | 191, 24 221 | 240, 32 297 | 310, 33 329 |
+  // 319; 700 rows over 200 states, 12 layers 123 | 104; 32/32 heads, 1024 rows over 1024 states, 5 layers 180 | 165; head_dim 64,
+  // 16/8 heads, 333 rows over 500 states, 20 layers 83.7 | 52.5.
+  const auto turns = [](int64_t work, int64_t places) { return (work + places - 1) / places; };
+  const int64_t pairs_turns = blocks / units % 2 == 0 ? 2 * turns(blocks / 2, cus) : turns(blocks, cus) + 1;
   auto launch = mixed ? attn_pipe_launch<D, 8, true> : attn_pipe_launch<D, 8, false>;
-  bool in_pairs = paired;
+  bool paired = blocks > cus && pairs_turns <= turns(blocks, cus);
   if constexpr (D == 64) {
-    // Workgroups of four waves that leave the registers for three of them on a compute unit, one block each: taken where the pairs'
-    // last turn wastes more of the chip.  Turns are counted in blocks (of half the size for four waves; a block left over
-    // makes pairs end unevenly).  us, pairs | three to a compute unit, 512 rows over 768 states of 32/8 heads: 5 layers 52.5 | 49.4, 8
-    // 62.1 | 64, 9 109.9 | 71.9, 10 109 | 82, 12 109.7 | 94.3, 16 121 | 124, 32 235 | 235; 28/4 heads, 300 rows over 1000 states, 16
-    // layers 135 | 97 (in 256 rows of a head at a time); 8/8 heads, 700 rows over 900 states, 40 layers 213 | 154; 16/8 heads, 333
-    // rows over 500 states, 20 layers 82.5 | 84.6.
-    const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, blocks = mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8);
-    const auto turns = [](int64_t work, int64_t places) { return (work + places - 1) / places; };
-    const int64_t in_pairs_turns = blocks / units % 2 == 0 ? 2 * turns(blocks / 2, cus) : turns(blocks, cus) + 1;
-    const double of_pairs = static_cast<double>(blocks) / (in_pairs_turns * cus);
+    // Workgroups of four waves that leave the registers for three of them on a compute unit, one block (of half the size) each: taken
+    // where the pairs' last turn wastes more of the chip.  us, pairs | three to a compute unit, 512 rows over 768 states of 32/8
+    // heads: 5 layers 52.5 | 49.4, 8 62.1 | 64, 9 109.9 | 71.9, 10 109 | 82, 12 109.7 | 94.3, 16 121 | 124, 32 235 | 235; 28/4
+    // heads, 300 rows over 1000 states, 16 layers 135 | 97 (in 256 rows of a head at a time); 8/8 heads, 700 rows over 900 states,
+    // 40 layers 213 | 154.
+    const double of_pairs = static_cast<double>(blocks) / (pairs_turns * cus);
     const double of_three = static_cast<double>(workgroups(4)) / (turns(workgroups(4), 3 * cus) * 3 * cus);
-    if (paired && of_three > of_pairs + 0.05) {
+    if (blocks > cus && of_three > of_pairs + 0.05) {
       launch = attn_pipe_launch<64, 4, false, 3>;
-      in_pairs = false;
+      paired = false;
     }
   }
-  return launch(dm, q, ks, vs, in_pairs, out, lse, lse_cache, st, q_rope_pos0, rope_base);
+  return launch(dm, q, ks, vs, paired, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
 // Partial (maximum, sum) pairs of every query row over `key_splits` ranges of the keys.
