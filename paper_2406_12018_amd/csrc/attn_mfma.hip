@@ -965,24 +965,24 @@ __global__ __launch_bounds__(WAVES * 64, PER_SIMD) void attn_pipe_kernel_rotq(At
 // Chunk attention and instruction score of a step in one launch: neither reads what the other writes, and a small step
 // leaves compute units idle in both.  The workgroups have the score's eight waves; those of the attention use four.
 // What bounds it: the attention's chain, behind which the score disappears.  One layer of 32/8 heads, 512 rows and 64
-// instruction rows over 768 + 512 states: 22.4 + 9.2 us in two launches, 23.4 in one; a document of it, 7941 tokens, 525 us.
+// instruction rows over 768 + 512 states: 22.4 + 9.2 us in two launches, 23.4 in one.
 // The eviction by those scores can be part of the launch too: the workgroup that is the last of its unit's strips to have
 // written its column selects and moves the unit's rows (into the other buffer, which nothing here reads).  No workgroup waits
-// for another one.  The document above 406 us instead of 525; 8/4 heads, 43 rows and 86 instruction rows over 463 + 430 states, a
-// step 24.3 -> 17.7.
+// for another one.  A document of such a layer, 7941 tokens, 525 -> 360 us; 8/4 heads, 43 rows and 86 instruction rows over 463 +
+// 430 states, a step 24.3 -> 17.7.
 constexpr int kTailRows = 8;  // rows of a thread in flight: one workgroup moves all rows of a unit
 template <int TPW>
 using TailLds = SelectLds<TPW * kStripWaves * kStripKeys / kStripThreads + 1, kStripThreads, 11>;
 template <int D, bool ROTATE_Q, int TPW>
-__global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a, int attn_blocks, StripArgs s, StepTail t) {
+__global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a, int score_blocks, StripArgs s, StepTail t) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int last;
-  if (static_cast<int>(blockIdx.x) < attn_blocks) {
+  const int block = blockIdx.x;
+  if (block >= score_blocks) {
     if (threadIdx.x >= kThreads) return;  // an ended wave counts at no barrier
-    attn_pipe_body<D, kWaves, ROTATE_Q, true>(a, blockIdx.x, smem, smem + attn_ring_bytes<D>());
+    attn_pipe_body<D, kWaves, ROTATE_Q, true>(a, block - score_blocks, smem, smem + attn_ring_bytes<D>());
     return;
   }
-  const int block = blockIdx.x - attn_blocks;
   constexpr int kItems = TPW * kStripWaves * kStripKeys / kStripThreads + 1;
   TailLds<TPW>& lds = *reinterpret_cast<TailLds<TPW>*>(smem);
   int32_t* const sel = reinterpret_cast<int32_t*>(smem + sizeof(TailLds<TPW>));
@@ -991,24 +991,25 @@ __global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a
     unit = block / t.job.parts;
     r0 = (block - unit * t.job.parts) * t.job.part_rows;
   } else {
-    unit = strip_score_body<D, 1, TPW, ROTATE_Q>(s, block, smem);
+    unit = strip_score_body<D, 1, TPW, ROTATE_Q, true>(s, block, smem);
     if (t.then == Then::kNothing) return;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's part of the column is in the cache that its XCD shares
+    // The wave's part of the column has been written through.  (A fence would write back all that its XCD has not yet,
+    // the attention's output among it: 16 layers of 8/4 heads, 176 rows over 153 states, two strips a unit, 33.7 us a step with
+    // fences, 21.4 without.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (s.strips > 1) {
       if (threadIdx.x == 0) {
-        __threadfence();  // ... and now where every XCD finds it
-        last = atomicAdd(t.tickets + unit, 1) == s.strips - 1;
-        if (last) atomicExch(t.tickets + unit, 0);
+        last = __hip_atomic_fetch_add(t.tickets + unit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == s.strips - 1;
+        if (last) __hip_atomic_store(t.tickets + unit, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       __syncthreads();
       if (!last) return;
-      __threadfence();  // the other strips' columns are read from where they wrote them
     }
   }
   const int r1 = min(r0 + t.job.part_rows, t.job.rows);
   if (t.job.sums > 1)
-    evict_rows<kItems, kStripThreads, 11, Scores::kSumByHead, kTailRows>(t.job, unit, unit_scores(t.job, unit), r0, r1, lds, sel);
+    evict_rows<kItems, kStripThreads, 11, Scores::kSumShared, kTailRows>(t.job, unit, unit_scores(t.job, unit), r0, r1, lds, sel);
   else
     evict_rows<kItems, kStripThreads, 11, Scores::kOneHead, kTailRows>(t.job, unit, unit_scores(t.job, unit), r0, r1, lds, sel);
 }
@@ -1363,7 +1364,7 @@ hipError_t attn_score_launch(const Dims& dm, View q, Segments ks, Segments vs, V
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
   const int score_blocks = units * (t.then == Then::kGather ? t.job.parts : s.strips);
-  hipLaunchKernelGGL(kern, dim3(blocks + score_blocks), dim3(kStripThreads), kLdsBytes, st, a, blocks, s, t);
+  hipLaunchKernelGGL(kern, dim3(blocks + score_blocks), dim3(kStripThreads), kLdsBytes, st, a, score_blocks, s, t);
   return hipGetLastError();
 }
 
@@ -1467,21 +1468,17 @@ hipError_t launch_attn_mfma(const Dims& dm, View q, Segments ks, Segments vs, Vi
   return launch(dm, q, ks, vs, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
-// Worth it, and possible, while the workgroups of both fit the chip side by side.
+// Taken where the attention's workgroups of four waves fit the chip side by side, whatever the score's add to them up to half as many
+// again: those come first, and the shorter blocks of the attention follow them.  us a step, apart | one launch (attention's |
+// score's workgroups): 32/8 heads, 512 rows over 768 states, 2 layers 47.0 | 39.5 (256 | 128); 64/8 heads, head_dim 64, 274 rows over
+// 195 states 25.0 | 16.4 (144 | 144); 8/4 heads, head_dim 64, 98 rows over 65 states, 16 layers 20.6 | 12.6 (256 | 128); 32/4 heads, head_dim 64, 49
+// rows over 82 states, 12 layers 20.0 | 18.8 (192 | 432), but 7/1 heads, 53 rows over 61 states, 16 layers 19.1 | 21.4 (112 | 480).
 bool attn_score_in_one_launch(const Dims& dm, const Segments& ks, const Segments& vs, const View& q_instr, int instr_rows) {
   const int64_t strips = (static_cast<int64_t>(dm.G) * instr_rows + 31) / 32;
-  return attn_workgroups(dm, ks.c, kWaves) + strips * dm.Hkv * dm.B * dm.L <= compute_units() && attn_segments_fit(ks, vs) &&
+  return attn_workgroups(dm, ks.c, kWaves) <= compute_units() && 2 * strips * dm.Hkv * dm.B * dm.L <= 3 * compute_units() && attn_segments_fit(ks, vs) &&
          instr_strip_supported(dm, q_instr, instr_rows, ks);
 }
 
-// Several strips per unit: the last workgroup's chain (write back, count, read the columns) is longer than a launch of its own
-// where the attention is over sooner.  us a step, apart | one launch, tiles of 64 keys: 2 tiles, 5 strips 12.7 | 13.8; 3 tiles, 9
-// strips 14.6 | 14.3; 4 tiles, 4 strips 15.2 | 13.9; 13 tiles, 2 strips 23.1 | 19.5; 20 tiles, 8 strips 33.6 | 26.5; one strip ahead
-// everywhere, 2 tiles 12.7 | 10.1, 14 tiles 24.1 | 19.3.
-bool step_in_one_launch(const Dims& dm, const Segments& ks, int instr_rows, const Eviction& e) {
-  const auto tiles = [](int rows) { return (rows + kTileN - 1) / kTileN; };
-  return gather_only(e) || dm.G * instr_rows <= 32 || tiles(ks.n_c) + tiles(ks.c) > 2;
-}
 bool step_needs_tickets(const Dims& dm, int instr_rows, const Eviction& e) { return dm.G * instr_rows > 32 && !gather_only(e); }
 hipError_t launch_clear_tickets(const Dims& dm, int32_t* tickets, hipStream_t st) {
   const int units = dm.B * dm.L * dm.Hkv;

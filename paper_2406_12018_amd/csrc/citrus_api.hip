@@ -869,7 +869,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
           status = hip_status(launch_attn_score_f32(dm, make_view(q_att), ks_att, vs, make_view(io.out), make_view(qi_att),
                                                     cfg->instr_len, score, evicted ? &own : nullptr, st));
         } else {
-          evicted = fused && !timed(5) && step_in_one_launch(dm, ks_att, cfg->instr_len, own);
+          evicted = fused && !timed(5);
           if (evicted && !tickets_clear && step_needs_tickets(dm, cfg->instr_len, own)) {
             if ((status = hip_status(launch_clear_tickets(dm, tickets, st))) != CITRUS_OK) break;
             tickets_clear = true;

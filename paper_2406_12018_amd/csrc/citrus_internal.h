@@ -117,8 +117,6 @@ hipError_t finish_strip_scores(const Dims& dm, const float* part, int strips, in
 // ---- chunk attention and instruction score of a small step in one launch, attn_mfma.hip ----
 // The same bits as the two launches.  Both read [cache ; chunk]; q_instr: instr_rows rows per head.
 bool attn_score_in_one_launch(const Dims& dm, const Segments& kseg, const Segments& vseg, const View& q_instr, int instr_rows);
-// May, and should, the launch evict by its scores as well?
-bool step_in_one_launch(const Dims& dm, const Segments& kseg, int instr_rows, const Eviction& evict);
 // evict (optional): the eviction by these scores, made by the launch (tickets: B*L*Hkv of them, zero; zero again afterwards).
 // Otherwise sums as in launch_instr_score_mfma.
 hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments kseg, Segments vseg, View out, int q_rope_pos0,

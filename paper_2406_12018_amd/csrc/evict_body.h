@@ -22,9 +22,16 @@ __device__ inline uint32_t order_key(float f) {
 
 // The value a selection unit ranks for candidate j: one head's score, or the
 // sum over the layer's KV heads taken in head order (layer-wise eviction).
+// SHARED: other workgroups of this launch have written the scores (store_shared), maybe on another XCD.
+template <bool SHARED = false>
+__device__ inline float load_score(const float* p) {
+  if constexpr (SHARED) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return *p;
+}
+template <bool SHARED = false>
 __device__ inline float unit_score(const float* base, int heads_to_sum, int n, int j) {
-  float s = base[j];
-  for (int g = 1; g < heads_to_sum; ++g) s += base[static_cast<int64_t>(g) * n + j];
+  float s = load_score<SHARED>(base + j);
+  for (int g = 1; g < heads_to_sum; ++g) s += load_score<SHARED>(base + static_cast<int64_t>(g) * n + j);
   return s;
 }
 
@@ -44,7 +51,7 @@ __device__ __forceinline__ int wave_prefix_sum(int v) {
 // partial sums of a head).  The sums grow in row order (unit_score), either for all of a thread's candidates at a time,
 // with several rows' loads in flight, or one candidate after the other, which waits for every load but needs no thread
 // without a candidate.
-enum class Scores { kOneHead, kSumByHead, kSumByCandidate };
+enum class Scores { kOneHead, kSumByHead, kSumByCandidate, kSumShared };  // kSumShared: kSumByHead of what this launch writes
 
 // Radix passes of BITS bits: a large radix needs fewer passes, each a chain of dependent steps, and spreads the votes of
 // scores that share their exponents over more bins; the histograms are cleared, every wave reads a whole one in each pass, and
@@ -89,7 +96,7 @@ __device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS, BITS>& 
   auto put = [&](int j, float value) {
     if (j < n) lds.key[padded(j)] = j < forced ? 0xffffffffu : order_key(value);
   };
-  if constexpr (FORM == Scores::kSumByHead) {
+  if constexpr (FORM == Scores::kSumByHead || FORM == Scores::kSumShared) {
     float sum[ITEMS];
     auto add_rows = [&](auto in_flight, int g0) {  // up to so many rows from g0 on
       constexpr int kRows = decltype(in_flight)::value;
@@ -98,7 +105,7 @@ __device__ __forceinline__ void topk_regs_body(SelectLds<ITEMS, THREADS, BITS>& 
       for (int x = 0; x < kRows; ++x)
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
-          v[x][i] = base[static_cast<int64_t>(min(g0 + x, rows - 1)) * n + min(i * THREADS + tid, n - 1)];
+          v[x][i] = load_score<FORM == Scores::kSumShared>(base + static_cast<int64_t>(min(g0 + x, rows - 1)) * n + min(i * THREADS + tid, n - 1));
 #pragma unroll
       for (int x = 0; x < kRows; ++x)
 #pragma unroll
@@ -298,7 +305,7 @@ __device__ __forceinline__ void evict_rows(const EvictJob& a, int unit, const fl
       float* const out = a.acc_new + static_cast<int64_t>(unit) * a.acc_pitch;
       for (int r = r0 + tid; r < s1; r += THREADS) {
         const int j = sel[r - r0];
-        float s = unit_score(base, a.sums, a.n, j);
+        float s = unit_score<FORM == Scores::kSumShared>(base, a.sums, a.n, j);
         if (j < a.v.n_c) s += acc[j];
         out[r] = s;
       }

@@ -97,7 +97,8 @@ constexpr int strip_lds_bytes() {
 // ROW_TILES: 32-row tiles per strip; TPW: key tiles a wave can hold (n <= 8 * TPW * 32).  smem: strip_lds_bytes.
 // Kernels cannot share an instance (the compiler's host pass accepts a body with LDS-direct loads once): KERNEL tells those of
 // a translation unit apart.  Returns the unit.
-template <int D, int ROW_TILES, int TPW, int KERNEL = 0>
+// SHARED: the columns of several strips are read in the same launch: their stores write through to where every XCD finds them.
+template <int D, int ROW_TILES, int TPW, int KERNEL = 0, bool SHARED = false>
 __device__ __forceinline__ int strip_score_body(const StripArgs& a, int block, char* smem) {
   typedef StripGeo<D> T;
   constexpr int kStripRows = 32 * ROW_TILES;
@@ -331,7 +332,12 @@ __device__ __forceinline__ int strip_score_body(const StripArgs& a, int block, c
     }
     const float tot = reduce16_over32(v, col);  // value index col / 2 -> key 8 (x / 4) + 4 grp + (x % 4)
     const int x = col >> 1, j = kStripKeys * kt + 8 * (x / 4) + 4 * grp + (x % 4);
-    if ((col & 1) == 0 && j < n) dst[j] = tot;
+    if ((col & 1) == 0 && j < n) {
+      if (SHARED && a.strips > 1)
+        __hip_atomic_store(dst + j, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        dst[j] = tot;
+    }
   }
   return unit;
 }

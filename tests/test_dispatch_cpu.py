@@ -260,12 +260,16 @@ def one_launch_steps(api, launches, cases):
 def test_steps_that_are_one_launch(tmp_path):
     """The counters of a unit's workgroups are cleared once per call, in front of the first step that counts."""
     bf16, f32, clear, evict = "attn_score_kernel", "attn_score_f32_kernel", "clear_tickets_kernel", "evict_kernel"
+    attn, strips = "attn_pipe_kernel", "instr_strip_kernel"
     cases = {(0, 4, 8, 128, 512, 768, 64): [bf16, clear, bf16, bf16],       # the first step keeps all of its states
              (0, 4, 8, 128, 512, 400, 64): [clear, bf16, bf16, bf16],
              (0, 4, 8, 128, 512, 2048, 64): [bf16, bf16, bf16],
              (0, 1, 8, 128, 32, 30, 32): [bf16, bf16, bf16],                # one strip per unit: nothing to count
-             (0, 4, 8, 128, 32, 40, 64): [bf16, bf16, evict, bf16, evict],  # two tiles of 64 keys
-             (0, 4, 8, 128, 64, 70, 64): [bf16, bf16, evict, clear, bf16],  # two, then three
+             (0, 4, 8, 128, 32, 40, 64): [bf16, clear, bf16, bf16],
+             (0, 4, 32, 128, 64, 70, 96): [bf16, clear, bf16, bf16],        # 384 strips
+             (0, 4, 33, 128, 64, 70, 96): [attn, strips, evict] * 3,        # 396
+             (0, 4, 8, 128, 1024, 800, 8): [bf16, bf16, bf16],              # 256 workgroups of the attention
+             (0, 4, 8, 128, 1025, 800, 8): [attn, strips, evict] * 3,
              (1, 4, 1, 64, 32, 64, 8): [f32, f32, f32],
              (1, 2, 1, 128, 100, 128, 8): [f32, f32, f32],                  # 128 KB of a unit stay
              (1, 2, 1, 128, 100, 129, 8): [f32, f32, evict, f32, evict]}

@@ -20,6 +20,9 @@ CASES = [
     ("bf16", 1, 4, 1, 64, 700, 4000, 1860, 30, dict(start_size=3)),  # 2560, the most
     ("bf16", 1, 8, 1, 128, 200, 1100, 300, 21, dict(score_mode=api.SCORE_ACCUMULATED)),  # sums of the first step are carried on
     ("bf16", 3, 8, 2, 128, 96, 500, 150, 16, dict(position_shift=1)),
+    ("bf16", 1, 21, 3, 128, 150, 900, 200, 33, {}),             # eight strips of each of three units: over all XCDs
+    ("bf16", 5, 20, 5, 64, 100, 700, 130, 40, {}),
+    ("bf16", 16, 8, 4, 64, 98, 500, 65, 40, {}),                # 256 workgroups of the attention behind 192 of the score
     ("f32", 1, 4, 1, 64, 32, 300, 64, 8, {}),
     ("f32", 2, 4, 2, 128, 60, 300, 125, 9, dict(start_size=2)),
     ("f32", 1, 2, 2, 64, 212, 900, 300, 30, dict(score_mode=api.SCORE_ACCUMULATED)),  # 512 candidates, 150 KB kept: gather apart
