@@ -51,6 +51,8 @@ struct Eviction {
   float* acc_new;    // ... and that the kept states take along; [B*L*Hkv][acc_pitch]
   int acc_pitch;
 };
+// Every candidate stays, and no scores are carried on: none are formed.
+inline bool gather_only(const Eviction& e) { return e.n <= e.k && e.acc_new == nullptr; }
 inline citrus_status hip_status(hipError_t e) { return e == hipSuccess ? CITRUS_OK : CITRUS_ERR_DEVICE; }
 
 // ---- kernels of the f32 mode, attn_generic.hip ----

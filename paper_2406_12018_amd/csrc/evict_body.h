@@ -371,9 +371,6 @@ inline void cut_in_parts(EvictJob& a, int least, int most) {
   a.parts = (a.rows + a.part_rows - 1) / a.part_rows;
 }
 
-// Every candidate stays, and no scores are carried on: none are formed.
-inline bool gather_only(const Eviction& e) { return e.n <= e.k && e.acc_new == nullptr; }
-
 // What the score's workgroups of a merged launch do besides: nothing, the eviction of their unit once its scores are there
 // (kEvict), or only the gather, where every candidate stays (kGather: job.parts workgroups per unit).
 enum class Then { kNothing, kEvict, kGather };
