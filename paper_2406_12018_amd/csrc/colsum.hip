@@ -8,8 +8,7 @@
 namespace citrus {
 namespace {
 
-constexpr int kColWaves = 8;
-constexpr int kColThreads = kColWaves * 64;
+constexpr int kRowShares = 2;  // waves that share out the rows of a workgroup's keys
 
 // N logits of a lane (2 or 4): weight exp2(s c2 - lse) each, added to its key's sum, around one MFMA in whose shadow the
 // vector instructions run.  One statement, so that the order is what is written; the MFMA is the wait state behind the
@@ -79,8 +78,9 @@ struct ColsumArgs {
 };
 
 // Keys stay, rows stream.  A wave holds 64 keys (two 32-key tiles) as operands in registers; the group's query rows (all
-// its heads, flattened) go through LDS in chunks of eight steps.  Of the eight waves KG share out the keys and 8 / KG the
-// steps of a chunk; what the latter summed meets in LDS at the end in a fixed order: no atomics, bit-reproducible.
+// its heads, flattened) go through LDS in chunks of a step per wave.  Of the 2 KG waves KG share out the keys and two the
+// steps, the even and the odd ones of the group's rows whatever KG is; what these two summed meets in LDS at the end: no
+// atomics, and a score's bits follow from its rows and not from the launch.
 // What bounds it: at head_dim 128 a SIMD spends 32 cycles of matrix pipe on an MFMA and about 42 on issuing it with its share
 // of the vector work (two multiply-adds of 4.3 cycles, two exponentials of 8.2, two adds of 2.3), and a launch that fills the
 // chip draws so much power that the clock falls to 1.6 to 1.8 GHz: registers full of such MFMAs and vector instructions
@@ -89,17 +89,18 @@ struct ColsumArgs {
 // the ports); an LDS operand feeds two MFMAs; keys and rows come in through LDS as whole rows; loads go between the MFMAs;
 // the mask's arithmetic is left out for waves whose keys every row sees.
 // us, earlier kernel (32 keys a wave, four waves per SIMD, rows staged through registers) | this one; 32/8 heads, 512 rows,
-// 1280 keys: 1 layer 39.6 | 22.5, 4 layers 46.0 | 37.3, 8 layers 68.3 | 67.3, 16 layers 115.7 | 114.4; 500 rows, 1000 keys,
-// 16 layers 96.9 | 82.1; 28/4 heads, 700 rows, 900 keys, 3 layers 128 | 48.4; causal, 512 rows behind 768 states, 1 layer
-// 41.5 | 24.1, 16 layers 101.6 | 94.9.  head_dim 64, where the vector port is the bound, 8 layers 52.1 | 49.3, 16 layers 80.1 | 81.7.
+// 1280 keys: 1 layer 39.8 | 29.2, 4 layers 46.1 | 36.7, 8 layers 66.7 | 67.4, 16 layers 107.7 | 102.2; 500 rows, 1000 keys,
+// 16 layers 89.7 | 72.6; 28/4 heads, 700 rows, 900 keys, 3 layers 126 | 72.7; causal, 512 rows behind 768 states, 1 layer
+// 41.8 | 31.2, 16 layers 98.4 | 91.3.  head_dim 64, where the vector port is the bound, 8 layers 51.8 | 42, 16 layers 76.5 | 71.
 template <int D, int KG>
-__global__ __launch_bounds__(kColThreads, 2) void colsum_mfma_kernel(ColsumArgs a) {
+__global__ __launch_bounds__(64 * kRowShares * KG, 2) void colsum_mfma_kernel(ColsumArgs a) {
   typedef Geo<D> T;
   typedef Lay<D> Y;
   constexpr int QT = 128 / D;                  // 32-row tiles of a step: eight MFMAs per key tile and step
-  constexpr int RS = kColWaves / KG;           // waves that share out the steps of a chunk
-  constexpr int kChunkRows = 8 * 32 * QT;      // eight steps; a wave stages one of them
-  constexpr int kStage = 8 * QT * Y::kHalf;    // bytes of a staged chunk
+  constexpr int RS = kRowShares;
+  constexpr int kSteps = RS * KG;                 // of a chunk; a wave stages one of them
+  constexpr int kChunkRows = kSteps * 32 * QT;
+  constexpr int kStage = kSteps * QT * Y::kHalf;  // bytes of a staged chunk
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   char* const q_s = smem;                                           // [2] chunks
   float* const lse_s = reinterpret_cast<float*>(smem + 2 * kStage); // [2][kChunkRows], log2 domain, +inf for padding rows
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(kColThreads, 2) void colsum_mfma_kernel(ColsumArgs 
   auto stage_rest = [&]() __attribute__((always_inline)) {
     while (stage_left > 0) stage_one();
   };
-  constexpr int kStageLoads = 32 * QT / kR, kStagePerStep = kStageLoads * RS / 8;
+  constexpr int kStageLoads = 32 * QT / kR, kStagePerStep = kStageLoads * RS / kSteps;
   auto begin_stage = [&](int f0, int buf) __attribute__((always_inline)) {
     const int f = f0 + 32 * QT * w, hh = a.head_rows.quotient(f), t = f - hh * rows;
     const uint32_t dst = lds_q + buf * kStage + w * QT * Y::kHalf;
@@ -186,8 +187,8 @@ __global__ __launch_bounds__(kColThreads, 2) void colsum_mfma_kernel(ColsumArgs 
     if (tid < kChunkRows) lse_s[buf * kChunkRows + tid] = lse_in;
     wait_loads_and_barrier<0, true>();
   };
-  static_assert(8 % (2 * RS) == 0, "pairs of steps");
-  static_assert(kChunkRows <= kColThreads, "a thread per normaliser of a chunk");
+  static_assert(kSteps % (2 * RS) == 0, "pairs of steps");
+  static_assert(kChunkRows <= 64 * RS * KG, "a thread per normaliser of a chunk");
 
   // ---- the wave's keys: row operand of key j0 + 32 kt + col, kept in registers.  They come in through LDS as well, in the
   // second chunk's place: whole rows per load instruction, once for the waves that share them ----
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(kColThreads, 2) void colsum_mfma_kernel(ColsumArgs 
   int f0 = next_chunk(0);
   begin_stage(f0, 0);
   stage_rest();
-  constexpr int kKeysPerWave = 64 * KG / kColWaves;  // that a wave brings in
+  constexpr int kKeysPerWave = 64 / RS;  // that a wave brings in
   const uint32_t lds_k = lds_q + kStage;
   {
     const uint16_t* const k_cache = unit_ptr(a.ks.cache, b, l, g);
@@ -402,10 +403,10 @@ __global__ __launch_bounds__(kColThreads, 2) void colsum_mfma_kernel(ColsumArgs 
   }
 }
 
-template <int D>
+template <int D, int KG>
 constexpr int colsum_lds_bytes() {
   constexpr int QT = 128 / D;
-  return 2 * (8 * QT * Lay<D>::kHalf + 8 * 32 * QT * 4);
+  return 2 * kRowShares * KG * QT * (Lay<D>::kHalf + 32 * 4);
 }
 
 template <int D, int KG>
@@ -436,10 +437,10 @@ hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int caus
   a.score = score;
   static LdsLimit limit;
   const auto kern = colsum_mfma_kernel<D, KG>;
-  constexpr int lds = colsum_lds_bytes<D>();
+  constexpr int lds = colsum_lds_bytes<D, KG>();
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(a.key_blocks * dm.Hkv, dm.B * dm.L), dim3(kColThreads), lds, st, a);
+  hipLaunchKernelGGL(kern, dim3(a.key_blocks * dm.Hkv, dm.B * dm.L), dim3(64 * kRowShares * KG), lds, st, a);
   return hipGetLastError();
 }
 
@@ -449,11 +450,18 @@ hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int
                               float to_log2, float* score, hipStream_t st) {
   const int n = ks.n_c + ks.c;
   const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv;
-  // A workgroup of 256 keys takes about 1.6 times as long as one of 128 (1 and 2 layers of 32/8 heads, 512 rows, 1280 keys: 33.4
-  // | 22.5 us, 34.2 | 24.0), and with LDS for one of them a compute unit takes workgroups in turns: the shorter sum of
-  // turns.  256 | 128 keys: 4 layers 37.3 | 45.6, 8 layers 72.3 | 67.3, 12 layers 79.7 | 90.6, 32 layers 197 | 223.
-  const auto turns = [&](int keys) { return ((n + keys - 1) / keys * units + compute_units() - 1) / compute_units(); };
-  const bool small = turns(128) * 5 < turns(256) * 8;
+  // Workgroups of eight waves and 256 keys, one to a compute unit, or of four and 128, two to a compute unit.  Those fill a last
+  // turn more evenly, and one alone on its compute unit takes 0.65 of the time of two; where every turn is full they take 1.08 times
+  // as long (rows pass the LDS twice as often).  So: the shorter sum of turns.  us, 256 | 128 keys, 32/8 heads, 512 rows, 1280 keys:
+  // 1 layer 32.8 | 29.2, 4 layers 36.3 | 41.0, 8 layers 69.5 | 67.3, 12 layers 73.1 | 79.6, 16 layers 102 | 102, 32 layers 178 | 190;
+  // 8/8 heads, 200 rows, 300 keys, 40 layers 24.4 | 18.0; head_dim 64: 1 layer 26.2 | 20.2, 4 layers 28.4 | 30.7, 8 layers 51.4 |
+  // 42.7, 16 layers 78.7 | 70.6, 32 layers 132 | 132.  (Eight waves on 128 keys, four to the rows, are faster where the chip is nearly
+  // empty, 22 us for one layer, but add the rows in another order: a score would depend on the launch it is part of.)
+  const auto blocks = [&](int keys) { return (n + keys - 1) / keys * units; };
+  const int64_t pairs = 2 * int64_t{compute_units()}, left = blocks(128) % pairs;
+  const int64_t turns128 = 100 * (blocks(128) / pairs) + (left == 0 ? 0 : 2 * left <= pairs ? 65 : 100);
+  const int64_t turns256 = 100 * ((blocks(256) + compute_units() - 1) / compute_units());
+  const bool small = 108 * turns128 < 100 * turns256;
   auto launch = small ? colsum_launch<128, 2> : colsum_launch<128, 4>;
   if (dm.D == 64) launch = small ? colsum_launch<64, 2> : colsum_launch<64, 4>;
   return launch(dm, q, rows, ks, causal, norm, norm_pitch, to_log2, score, st);

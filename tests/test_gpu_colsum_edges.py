@@ -29,7 +29,7 @@ def by_group(w, Hkv):  # [Hq, rows, keys] -> [Hkv, keys]
     return w.reshape(Hkv, -1, w.shape[-1]).sum(1)
 
 
-# L, Hq, Hkv, rows, keys; compute units take 128 keys per workgroup while that is the shorter sum of turns
+# L, Hq, Hkv, rows, keys; 128 keys per workgroup while that is the shorter sum of turns
 SHAPES = [(1, 1, 1, 1, 1), (1, 3, 1, 31, 63), (2, 8, 2, 33, 65), (1, 7, 1, 5, 129), (1, 4, 2, 257, 127), (3, 14, 2, 100, 300),
           (1, 8, 1, 512, 257), (40, 8, 8, 64, 256), (64, 8, 8, 40, 200), (60, 4, 4, 256, 300)]
 
@@ -52,6 +52,20 @@ def test_cache_score_with_given_normalisers(shape, head_dim):
     score = api.citrus_cache_score(cfg, q, k, n, lse_cache=lse)
     np.testing.assert_allclose(np64(score[0]), want, rtol=5e-5, atol=1e-9)
     assert torch.equal(score, api.citrus_cache_score(cfg, q, k, n, lse_cache=lse))
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("shape", [(64, 8, 8, 40, 200), (16, 32, 8, 500, 1000)], ids=lambda s: "-".join(map(str, s)))
+def test_a_units_bits_do_not_depend_on_the_launch(shape, head_dim):
+    """One layer alone, in blocks of 128 keys, and in a launch that fills the chip with blocks of 256."""
+    L, Hq, Hkv, rows, n = shape
+    print(f"column sums alone {shape} head_dim {head_dim}", flush=True)
+    make = lambda layers: api.Config(batch=1, layers=layers, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=rows, budget=n, instr_len=4)
+    q, k = rand((1, L, Hq, rows, head_dim), 1), rand((1, L, Hkv, n, head_dim), 2)
+    lse = 6 + torch.rand((1, L, Hq, rows), device=DEV)
+    score = api.citrus_cache_score(make(L), q, k, n, lse_cache=lse)
+    for l in (0, L - 1):
+        assert torch.equal(score[:, l:l + 1], api.citrus_cache_score(make(1), q[:, l:l + 1], k[:, l:l + 1], n, lse_cache=lse[:, l:l + 1].contiguous()))
 
 
 # L, Hq, Hkv, rows, cached states: chunks of rows none of which sees a key of the block, tiles that wrap, blocks of both sizes
