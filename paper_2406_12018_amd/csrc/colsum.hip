@@ -403,6 +403,110 @@ __global__ __launch_bounds__(64 * kRowShares * KG, 2) void colsum_mfma_kernel(Co
   }
 }
 
+// The same sums where a causal launch is long and its rows, 128 at a time within a head, come from memory: waves of 32 keys, four
+// to a SIMD, that form products and weights in turn and pass over single tiles of rows that see none of their keys.  Blocks of
+// one unit then lose step with each other, which costs the kernel above, with one chunk of rows in flight, more than this one.  us, the
+// kernel above | this one, 32/8 heads, 512 rows behind 768 states: 64 layers 371 | 324, 256 layers 1582 | 1280, head_dim 64, 128 layers 524 |
+// 438; up to 16 layers it is the slower one.  The order of a
+// sum's rows is the same: the bits are too.
+constexpr int kManyThreads = 512, kManyRows = 128;
+template <int D>
+constexpr int kManyLds = 2 * kManyRows * (Geo<D>::kPitchK * 2 + 4);
+template <int D>
+__global__ __launch_bounds__(kManyThreads, 4) void colsum_many_kernel(ColsumArgs a) {
+  typedef Geo<D> T;
+  constexpr int kPitchK = T::kPitchK, kTilesPerStep = 128 / D;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  uint16_t* const q_sb = reinterpret_cast<uint16_t*>(smem);                        // [2][kManyRows][kPitchK]
+  float* const lse_sb = reinterpret_cast<float*>(q_sb + 2 * kManyRows * kPitchK);  // [2][kManyRows], log2 domain
+  const int tid = threadIdx.x, lane = tid % 64, w = tid / 64;
+  const int col = lane % 32, grp = lane / 32;
+  const int g = blockIdx.y, bl = blockIdx.z, b = bl / a.L, l = bl % a.L;
+  const int n_c = a.ks.n_c, n = n_c + a.ks.c, rows = a.rows;
+  const int j0 = (blockIdx.x * (kManyThreads / 64) + w) * 32;
+  const bool wave_has_keys = j0 < n;
+
+  bf16x8 k_op[T::kKk];
+  {
+    const uint16_t* const k_cache = unit_ptr(a.ks.cache, b, l, g);
+    const uint16_t* const k_chunk = unit_ptr(a.ks.chunk, b, l, g);
+    const int j = min(j0 + col, n - 1);
+    const uint16_t* const key = (j < n_c ? k_cache + j * a.ks.cache.ss : k_chunk + (j - n_c) * a.ks.chunk.ss) + 8 * grp;
+#pragma unroll
+    for (int kk = 0; kk < T::kKk; ++kk) k_op[kk] = *reinterpret_cast<const bf16x8*>(key + 16 * kk);
+  }
+  float acc[2][16];  // steps of even and of odd number
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
+
+  // A thread stages 16 bytes of some rows of a chunk; the next chunk's are in registers while a chunk is multiplied.
+  constexpr int kStep = kManyThreads / T::kSegs, kLoads = kManyRows / kStep;
+  const int st_row = tid / T::kSegs, st_seg = tid % T::kSegs;
+  const uint32_t thread_off = (st_row * static_cast<uint32_t>(a.q.ss) + 8 * st_seg) * 2;  // bytes; a head's rows span < 2 GiB
+  const float* const norm = a.norm + (static_cast<int64_t>(bl) * a.Hq + g * a.G) * rows * a.norm_pitch;
+  const int total_rows = a.G * rows;
+  i32x4 q_in[kLoads];
+  float lse_in = 0.f;
+  int stage_head = 0, stage_row = 0;  // block-uniform
+  auto request_chunk = [&](int f0) {
+    const uint16_t* const base = unit_ptr(a.q, b, l, g * a.G + stage_head) + static_cast<int64_t>(stage_row) * a.q.ss;
+#pragma unroll
+    for (int x = 0; x < kLoads; ++x)
+      q_in[x] = *reinterpret_cast<const i32x4*>(reinterpret_cast<const char*>(base + x * kStep * a.q.ss) + thread_off);
+    stage_row += kManyRows;
+    if (stage_row == rows) {
+      stage_row = 0;
+      ++stage_head;
+    }
+    if (tid < kManyRows) lse_in = norm[static_cast<int64_t>(f0 + tid) * a.norm_pitch] * a.to_log2;
+  };
+  request_chunk(0);
+  int buf = 0, chunk_row = 0;
+  for (int f0 = 0; f0 < total_rows; f0 += kManyRows, buf ^= 1) {
+    uint16_t* const q_s = q_sb + buf * (kManyRows * kPitchK);
+    float* const lse_s = lse_sb + buf * kManyRows;
+    // this buffer was last read two chunks ago, and every wave has passed the previous chunk's barrier since
+#pragma unroll
+    for (int x = 0; x < kLoads; ++x) *reinterpret_cast<i32x4*>(&q_s[(st_row + x * kStep) * kPitchK + 8 * st_seg]) = q_in[x];
+    if (tid < kManyRows) lse_s[tid] = lse_in;
+    if (f0 + kManyRows < total_rows) request_chunk(f0 + kManyRows);  // block-uniform
+    __syncthreads();
+    if (wave_has_keys) {
+#pragma unroll
+      for (int qt = 0; qt < kManyRows / 32; ++qt) {
+        float(&sum)[16] = acc[qt / kTilesPerStep % 2];
+        const int tile_row = chunk_row + 32 * qt;  // wave-uniform
+        if (n_c + tile_row + 31 < j0) continue;    // no row of the tile sees a key of this wave
+        f32x16 s_t;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s_t[i] = 0.f;
+        const uint16_t* const q_row = &q_s[(32 * qt + col) * kPitchK + 8 * grp];
+#pragma unroll
+        for (int kk = 0; kk < T::kKk; ++kk)
+          s_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op[kk], *reinterpret_cast<const bf16x8*>(q_row + 16 * kk), s_t, 0, 0, 0);
+        const float lse2 = lse_s[32 * qt + col];
+        if (j0 + 31 > n_c + tile_row) {  // a key of the wave that a row of the tile does not see
+          const int last = n_c + tile_row + col - j0 - 4 * grp;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(s_t[i], a.c2, -lse2));
+            sum[i] += 8 * (i / 4) + i % 4 <= last ? p : 0.f;
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum[i] += __builtin_amdgcn_exp2f(fmaf(s_t[i], a.c2, -lse2));
+        }
+      }
+    }
+    chunk_row += kManyRows;
+    if (chunk_row == rows) chunk_row = 0;
+  }
+  if (!wave_has_keys) return;
+  const float even = reduce16_over32(acc[0], col), odd = reduce16_over32(acc[1], col);
+  const int i = col >> 1, j = j0 + 8 * (i / 4) + 4 * grp + i % 4;
+  if ((col & 1) == 0 && j < n) a.score[(static_cast<int64_t>(bl) * a.Hkv + g) * n + j] = even + odd;
+}
+
 template <int D, int KG>
 constexpr int colsum_lds_bytes() {
   constexpr int QT = 128 / D;
@@ -435,6 +539,13 @@ hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int caus
   a.norm = norm;
   a.norm_pitch = norm_pitch;
   a.score = score;
+  if (causal && rows % kManyRows == 0 && int64_t{units} * dm.G * rows > 3 << 17) {
+    static LdsLimit limit;
+    const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(colsum_many_kernel<D>), kManyLds<D>);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(colsum_many_kernel<D>, dim3((n + 255) / 256, dm.Hkv, dm.B * dm.L), dim3(kManyThreads), kManyLds<D>, st, a);
+    return hipGetLastError();
+  }
   static LdsLimit limit;
   const auto kern = colsum_mfma_kernel<D, KG>;
   constexpr int lds = colsum_lds_bytes<D, KG>();

@@ -101,3 +101,24 @@ def test_importance_of_the_chunk(shape, head_dim):
     _, score_bad = run(q_bad)
     assert score_bad[0, 0, 0, :n_c + bad + 1].isnan().all()
     assert not score_bad[0, 0, 0, n_c + bad + 1:].isnan().any() and torch.equal(score_bad[0, :, 1:], score[0, :, 1:])
+
+
+@pytest.mark.parametrize("L, Hq, Hkv, c, n_c, head_dim", [(129, 32, 8, 128, 70, 128), (70, 32, 4, 256, 100, 128), (130, 32, 8, 256, 33, 64)])
+def test_importance_in_a_long_launch(L, Hq, Hkv, c, n_c, head_dim):
+    """More than 393216 query rows, 128 at a time within a head, take the kernel of short waves: the bits of a layer alone."""
+    print(f"long causal launch {L, Hq, Hkv, c, n_c, head_dim}", flush=True)
+    assert L * Hq * c > 3 << 17
+    g = torch.Generator(device=DEV).manual_seed(5)
+    make = lambda h, rows: torch.randn((1, L, h, rows, head_dim), generator=g, device=DEV).to(torch.bfloat16)
+    q, k, v, kc, vc = make(Hq, c), make(Hkv, c), make(Hkv, c), make(Hkv, n_c), make(Hkv, n_c)
+
+    def run(l0, l1):
+        cfg = api.Config(batch=1, layers=l1 - l0, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=c, budget=n_c, instr_len=4)
+        lse, score = torch.empty((1, l1 - l0, Hq, c), device=DEV), torch.empty((1, l1 - l0, Hkv, n_c + c), device=DEV)
+        api.citrus_chunk_attn(cfg, q[:, l0:l1], kc[:, l0:l1], vc[:, l0:l1], n_c, k[:, l0:l1], v[:, l0:l1], lse=lse, lm_score=score)
+        return lse, score
+
+    lse, score = run(0, L)
+    for l in (0, L - 1):
+        lse_alone, alone = run(l, l + 1)
+        assert torch.equal(lse[:, l:l + 1], lse_alone) and torch.equal(score[:, l:l + 1], alone)
