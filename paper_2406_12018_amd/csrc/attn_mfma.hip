@@ -973,7 +973,7 @@ __global__ __launch_bounds__(WAVES * 64, PER_SIMD) void attn_pipe_kernel_rotq(At
 constexpr int kTailRows = 8;  // rows of a thread in flight: one workgroup moves all rows of a unit
 template <int TPW>
 using TailLds = SelectLds<TPW * kStripWaves * kStripKeys / kStripThreads + 1, kStripThreads, 11>;
-template <int D, bool ROTATE_Q, int TPW>
+template <int D, bool ROTATE_Q, int ROW_TILES, int TPW>
 __global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a, int score_blocks, StripArgs s, StepTail t) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __shared__ int last;
@@ -991,7 +991,7 @@ __global__ __launch_bounds__(kStripThreads, 1) void attn_score_kernel(AttnArgs a
     unit = block / t.job.parts;
     r0 = (block - unit * t.job.parts) * t.job.part_rows;
   } else {
-    unit = strip_score_body<D, 1, TPW, ROTATE_Q, true>(s, block, smem);
+    unit = strip_score_body<D, ROW_TILES, TPW, ROTATE_Q, true>(s, block, smem);
     if (t.then == Then::kNothing) return;
     // The wave's part of the column has been written through.  (A fence would write back all that its XCD has not yet,
     // the attention's output among it: 16 layers of 8/4 heads, 176 rows over 153 states, two strips a unit, 33.7 us a step with
@@ -1338,15 +1338,13 @@ bool attn_segments_fit(const Segments& ks, const Segments& vs) {
   return fits_i32(ks.cache, ks.n_c) && fits_i32(ks.chunk, ks.c) && fits_i32(vs.cache, vs.n_c) && fits_i32(vs.chunk, vs.c);
 }
 
-template <int D, bool ROTATE_Q, int TPW>
+template <int D, bool ROTATE_Q, int ROW_TILES, int TPW>
 hipError_t attn_score_launch(const Dims& dm, View q, Segments ks, Segments vs, View out, int q_rope_pos0, float rope_base,
-                             View q_instr, int instr_rows, float* part, int* strips, const Eviction* evict,
-                             int32_t* tickets, hipStream_t st) {
+                             View q_instr, int instr_rows, float* part, const Eviction* evict, int32_t* tickets, hipStream_t st) {
   int blocks = 0;
   const AttnArgs a = attn_args<D, kWaves>(dm, q, ks, vs, false, out, nullptr, nullptr, q_rope_pos0, rope_base, &blocks);
-  const StripArgs s = strip_args(dm, q_instr, instr_rows, ks, 32, part);
-  *strips = s.strips;
-  constexpr int kLdsBytes = std::max(attn_ring_bytes<D>() + attn_stage_bytes<D, kWaves>(), strip_lds_bytes<D, 1>());
+  const StripArgs s = strip_args(dm, q_instr, instr_rows, ks, 32 * ROW_TILES, part);
+  constexpr int kLdsBytes = std::max(attn_ring_bytes<D>() + attn_stage_bytes<D, kWaves>(), strip_lds_bytes<D, ROW_TILES>());
   static_assert(sizeof(TailLds<TPW>) + TPW * kStripWaves * kStripKeys * sizeof(int32_t) <= kLdsBytes);
   const int units = dm.B * dm.L * dm.Hkv;
   StepTail t;
@@ -1359,7 +1357,7 @@ hipError_t attn_score_launch(const Dims& dm, View q, Segments ks, Segments vs, V
     t.then = gather_only(e) ? Then::kGather : Then::kEvict;
     if (t.then == Then::kGather) cut_in_parts(t.job, 32, (compute_units() - blocks) / units);
   }
-  const auto kern = attn_score_kernel<D, ROTATE_Q, TPW>;
+  const auto kern = attn_score_kernel<D, ROTATE_Q, ROW_TILES, TPW>;
   static LdsLimit limit;
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), kLdsBytes);
   if (e != hipSuccess) return e;
@@ -1468,37 +1466,52 @@ hipError_t launch_attn_mfma(const Dims& dm, View q, Segments ks, Segments vs, Vi
   return launch(dm, q, ks, vs, out, lse, lse_cache, st, q_rope_pos0, rope_base);
 }
 
-// Taken where the attention's workgroups of four waves fit the chip side by side, whatever the score's add to them up to half as many
-// again: those come first, and the shorter blocks of the attention follow them.  us a step, apart | one launch (attention's |
+// Taken where the attention's workgroups of four waves fit the chip side by side, whatever the score's 32-row strips add to them up to half
+// as many again: those come first, and the shorter blocks of the attention follow them.  us a step, apart | one launch (attention's |
 // score's workgroups): 32/8 heads, 512 rows over 768 states, 2 layers 47.0 | 39.5 (256 | 128); 64/8 heads, head_dim 64, 274 rows over
-// 195 states 25.0 | 16.4 (144 | 144); 8/4 heads, head_dim 64, 98 rows over 65 states, 16 layers 20.6 | 12.6 (256 | 128); 32/4 heads, head_dim 64, 49
-// rows over 82 states, 12 layers 20.0 | 18.8 (192 | 432), but 7/1 heads, 53 rows over 61 states, 16 layers 19.1 | 21.4 (112 | 480).
+// 195 states 25.0 | 16.4 (144 | 144); 8/4 heads, head_dim 64, 98 rows over 65 states, 16 layers 20.6 | 12.6 (256 | 128).  Over 140 shapes of
+// the range (1 to 40 layers, chunks of 32 to 1000, up to 256 | 384) one launch with the eviction in it is 0.97 to 1.64 times as fast; the
+// slowest is 14/2 heads, 16 layers, 59 rows over 84 states 20.4 | 21.1 (224 | 256).  Further out it is not always: 7/1 heads, 53 rows
+// over 61 states, 16 layers 19.1 | 21.4 (112 | 480).
 bool attn_score_in_one_launch(const Dims& dm, const Segments& ks, const Segments& vs, const View& q_instr, int instr_rows) {
   const int64_t strips = (static_cast<int64_t>(dm.G) * instr_rows + 31) / 32;
   return attn_workgroups(dm, ks.c, kWaves) <= compute_units() && 2 * strips * dm.Hkv * dm.B * dm.L <= 3 * compute_units() && attn_segments_fit(ks, vs) &&
          instr_strip_supported(dm, q_instr, instr_rows, ks);
 }
 
-bool step_needs_tickets(const Dims& dm, int instr_rows, const Eviction& e) { return dm.G * instr_rows > 32 && !gather_only(e); }
+static int strips_of(const Dims& dm, int instr_rows, int n) {
+  const int per_strip = instr_strip_rows(dm, instr_rows, n);
+  return (dm.G * instr_rows + per_strip - 1) / per_strip;
+}
+bool step_needs_tickets(const Dims& dm, int instr_rows, int n, const Eviction& e) {
+  return strips_of(dm, instr_rows, n) > 1 && !gather_only(e);
+}
 hipError_t launch_clear_tickets(const Dims& dm, int32_t* tickets, hipStream_t st) {
   const int units = dm.B * dm.L * dm.Hkv;
   hipLaunchKernelGGL(clear_tickets_kernel, dim3((units + 255) / 256), dim3(256), 0, st, tickets, units);
   return hipGetLastError();
 }
 
+// The strips are those of the launch of the score alone, in number and in height: its rule has checked that their columns fit the
+// scratch, and a score's bits are the same.
 hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments ks, Segments vs, View out, int q_rope_pos0, float rope_base,
-                                  View q_instr, int instr_rows, float* workspace, float* score, hipStream_t st,
-                                  ScoreSums* sums, const Eviction* evict, int32_t* tickets) {
-  const bool rotate = q_rope_pos0 >= 0, shorter = ks.n_c + ks.c <= kStripMaxKeysShort;
-  auto launch = dm.D == 128 ? (rotate ? (shorter ? attn_score_launch<128, true, 5> : attn_score_launch<128, true, 10>)
-                                      : (shorter ? attn_score_launch<128, false, 5> : attn_score_launch<128, false, 10>))
-                            : (rotate ? (shorter ? attn_score_launch<64, true, 5> : attn_score_launch<64, true, 10>)
-                                      : (shorter ? attn_score_launch<64, false, 5> : attn_score_launch<64, false, 10>));
-  const int total = dm.G * instr_rows;
-  float* const part = total <= 32 ? score : workspace;  // one strip: its column is the score
-  int strips = 0;
-  const hipError_t e = launch(dm, q, ks, vs, out, q_rope_pos0, rope_base, q_instr, instr_rows, part, &strips, evict, tickets, st);
-  return e != hipSuccess || evict != nullptr ? e : finish_strip_scores(dm, part, strips, ks.n_c + ks.c, score, st, sums);
+                                  View q_instr, int instr_rows, float* workspace, size_t workspace_floats, float* score,
+                                  hipStream_t st, ScoreSums* sums, const Eviction* evict, int32_t* tickets) {
+  const int n = ks.n_c + ks.c, strips = strips_of(dm, instr_rows, n);
+  if (strips > 1 && static_cast<size_t>(dm.B) * dm.L * dm.Hkv * strips * n > workspace_floats) return hipErrorInvalidValue;
+  const auto choose = [&](auto head_dim, auto rotate) {
+    constexpr int D = decltype(head_dim)::value;
+    constexpr bool R = decltype(rotate)::value;
+    if (instr_strip_rows(dm, instr_rows, n) == 64) return attn_score_launch<D, R, 2, 5>;
+    return n <= kStripMaxKeysShort ? attn_score_launch<D, R, 1, 5> : attn_score_launch<D, R, 1, 10>;
+  };
+  const std::integral_constant<int, 64> d64;
+  const std::integral_constant<int, 128> d128;
+  auto launch = dm.D == 128 ? choose(d128, std::false_type()) : choose(d64, std::false_type());
+  if (q_rope_pos0 >= 0) launch = dm.D == 128 ? choose(d128, std::true_type()) : choose(d64, std::true_type());
+  float* const part = strips == 1 ? score : workspace;  // one strip: its column is the score
+  const hipError_t e = launch(dm, q, ks, vs, out, q_rope_pos0, rope_base, q_instr, instr_rows, part, evict, tickets, st);
+  return e != hipSuccess || evict != nullptr ? e : finish_strip_scores(dm, part, strips, n, score, st, sums);
 }
 
 // Instruction score in two launches: partial log-sum-exp over ranges of key tiles (enough

@@ -870,13 +870,14 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
                                                     cfg->instr_len, score, evicted ? &own : nullptr, st));
         } else {
           evicted = fused && !timed(5);
-          if (evicted && !tickets_clear && step_needs_tickets(dm, cfg->instr_len, own)) {
+          if (evicted && !tickets_clear && step_needs_tickets(dm, cfg->instr_len, n, own)) {
             if ((status = hip_status(launch_clear_tickets(dm, tickets, st))) != CITRUS_OK) break;
             tickets_clear = true;
           }
           status = hip_status(launch_attn_score_mfma(dm, make_view(q_att), ks_att, vs, make_view(io.out), q_rope_pos0,
-                                                     rope_base_of(cfg), make_view(qi_att), cfg->instr_len, lse_instr.ptr, score,
-                                                     st, fused ? &own.score : nullptr, evicted ? &own : nullptr, tickets));
+                                                     rope_base_of(cfg), make_view(qi_att), cfg->instr_len, lse_instr.ptr,
+                                                     lse_instr.floats, score, st, fused ? &own.score : nullptr,
+                                                     evicted ? &own : nullptr, tickets));
         }
         if (status != CITRUS_OK) break;
         mark(done, 5);

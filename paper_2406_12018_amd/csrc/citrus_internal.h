@@ -106,6 +106,7 @@ int compute_units();
 // ---- instruction score with one q.k product per (row, key): row strips kept on chip, instr_strip.hip ----
 // taken for this shape?
 bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& kseg);
+int instr_strip_rows(const Dims& dm, int rows, int n);  // of a strip: 32 or 64
 // largest scratch any supported launch with at most `rows` rows and at most n keys writes (0: none is supported)
 size_t instr_strip_workspace_floats(const Dims& dm, int rows, int n);
 hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments kseg, float* workspace, size_t workspace_floats,
@@ -120,12 +121,12 @@ hipError_t finish_strip_scores(const Dims& dm, const float* part, int strips, in
 // The same bits as the two launches.  Both read [cache ; chunk]; q_instr: instr_rows rows per head.
 bool attn_score_in_one_launch(const Dims& dm, const Segments& kseg, const Segments& vseg, const View& q_instr, int instr_rows);
 // evict (optional): the eviction by these scores, made by the launch (tickets: B*L*Hkv of them, zero; zero again afterwards).
-// Otherwise sums as in launch_instr_score_mfma.
+// Otherwise sums as in launch_instr_score_mfma.  hipErrorInvalidValue if the strips' columns do not fit workspace_floats.
 hipError_t launch_attn_score_mfma(const Dims& dm, View q, Segments kseg, Segments vseg, View out, int q_rope_pos0,
-                                  float rope_base, View q_instr, int instr_rows, float* workspace, float* score,
-                                  hipStream_t st, ScoreSums* sums, const Eviction* evict, int32_t* tickets);
-// Does that launch need its tickets?
-bool step_needs_tickets(const Dims& dm, int instr_rows, const Eviction& evict);
+                                  float rope_base, View q_instr, int instr_rows, float* workspace, size_t workspace_floats,
+                                  float* score, hipStream_t st, ScoreSums* sums, const Eviction* evict, int32_t* tickets);
+// Does that launch need its tickets?  (n: the step's candidates)
+bool step_needs_tickets(const Dims& dm, int instr_rows, int n, const Eviction& evict);
 hipError_t launch_clear_tickets(const Dims& dm, int32_t* tickets, hipStream_t st);
 
 // ---- bf16 MFMA decoding step (at most 32 query heads per KV head), decode_attn.hip ----

@@ -94,7 +94,7 @@ hipError_t finish_strip_scores(const Dims& dm, const float* part, int strips, in
 
 // Rows of a strip: 32 while such strips fit the compute units side by side (more workgroups, each with half the work), else
 // 64 where a wave can hold them.
-static int strip_rows(const Dims& dm, int rows, int n) {
+int instr_strip_rows(const Dims& dm, int rows, int n) {
   const int64_t groups32 = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv * ((dm.G * rows + 31) / 32);
   return n <= kStripMaxKeysShort && dm.G * rows > 32 && groups32 > compute_units() ? 64 : 32;
 }
@@ -137,7 +137,7 @@ static int strip_rounds(const Dims& dm, int rows, int n, int64_t units) {
 bool instr_strip_supported(const Dims& dm, const View& q, int rows, const Segments& ks) {
   const int n = ks.n_c + ks.c;
   if (n < 1 || n > kStripMaxKeysLong || rows < 1 || dm.G * rows > kStripMaxRows) return false;
-  const int per_strip = strip_rows(dm, rows, n);
+  const int per_strip = instr_strip_rows(dm, rows, n);
   const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, strips = (dm.G * rows + per_strip - 1) / per_strip;
   if (units * strips > static_cast<int64_t>(strip_rounds(dm, rows, n, units)) * compute_units()) return false;
   // The columns of several strips have to fit the scratch that a call of this shape has wherever it is made (one strip's
@@ -172,7 +172,7 @@ hipError_t launch_instr_strip(const Dims& dm, View q, int rows, Segments ks, flo
   const int n = ks.n_c + ks.c;
   if (!instr_strip_supported(dm, q, rows, ks)) return hipErrorInvalidValue;
   if (workspace_floats < instr_score_mfma_workspace_floats(dm, rows, n)) return hipErrorInvalidValue;
-  const bool tall = strip_rows(dm, rows, n) == 64, shorter = n <= kStripMaxKeysShort;
+  const bool tall = instr_strip_rows(dm, rows, n) == 64, shorter = n <= kStripMaxKeysShort;
   auto launch = tall ? strip_launch<128, 2, 5> : shorter ? strip_launch<128, 1, 5> : strip_launch<128, 1, 10>;
   if (dm.D == 64) launch = tall ? strip_launch<64, 2, 5> : shorter ? strip_launch<64, 1, 5> : strip_launch<64, 1, 10>;
   return launch(dm, q, rows, ks, workspace, score, st, sums);

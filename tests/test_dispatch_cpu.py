@@ -47,8 +47,8 @@ def _product(xs):
 
 
 class Recorder:
-    def __init__(self, lib):
-        self.lib = lib
+    def __init__(self, lib, lib_under_test=None):
+        self.lib, self.lib_under_test = lib, lib_under_test
         lib.fake_log.restype = C.c_char_p
 
     def __call__(self, call, fail_at=-1):
@@ -277,6 +277,58 @@ def test_steps_that_are_one_launch(tmp_path):
         assert got == want, case
 
 
+def merged_steps(api, launches, shapes):
+    """Documents of three chunks whose last step evicts, as they run and with every event asked for (launches apart): grids of the
+    step's attention and score launches, what the score's columns need and what the block behind them holds, in floats."""
+    class Dims(C.Structure):
+        _fields_ = [(x, C.c_int) for x in ("B", "L", "Hq", "Hkv", "G", "D")] + [("scale", C.c_float)]
+
+    block = launches.lib_under_test._ZN6citrus33instr_score_mfma_workspace_floatsERKNS_4DimsEii
+    block.restype, block.argtypes = C.c_size_t, [C.POINTER(Dims), C.c_int, C.c_int]
+    out = []
+    for L, Hq, Hkv, d, c, k, rows in shapes:
+        cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=d, chunk_len=c, budget=k, instr_len=rows)
+        q, kv = Fake(1, L, Hq, 3 * c, d), Fake(1, L, Hkv, 3 * c, d)
+        cache = lambda i: Fake(1, L, Hkv, k, d, at=(4 + i) << 20)
+        doc = api.resident_doc(cfg, q, kv, kv, Fake(3, 1, L, Hq, rows, d), q)
+
+        def last_step(events):
+            state = api.DocumentState([cache(0), cache(1)], [cache(2), cache(3)])
+            api.citrus_process_document(cfg, state, workspace(api, cfg), doc=doc, max_chunks=2, stream=0)
+            calls = launches(lambda: api.citrus_process_document(cfg, state, workspace(api, cfg), doc=doc, first_chunk=2, stream=0,
+                                                                 phase_events=events))
+            grids = lambda name: [_product(x[1]) for x in calls if x[0].startswith(name)]
+            return grids("attn_score_kernel<"), grids("attn_pipe_kernel<"), grids("instr_strip_kernel<")
+
+        merged = last_step(None)[0]
+        if not merged:
+            continue
+        _, attn, strips = last_step((C.c_void_p * (3 * api.binding.EVENTS_PER_STEP))(*[1] * (3 * api.binding.EVENTS_PER_STEP)))
+        held = block(Dims(1, L, Hq, Hkv, Hq // Hkv, d, 1.0), rows, cfg.cache_capacity + c)
+        out.append([[L, Hq, Hkv, d, c, k, rows], merged, attn, strips, min(2 * c, k) + c, held])
+    return out
+
+
+def test_a_merged_step_takes_the_strips_of_the_score_alone(tmp_path):
+    """As many, so of the same height (the same bits), and their columns fit the scratch block, which is checked for those."""
+    import random
+    rng = random.Random(3)
+    shapes = [(1, 64, 8, 128, 512, 768, rows) for rows in (128, 160, 192)]
+    shapes += [(1, 40, 5, 128, 512, 768, 256), (1, 32, 8, 128, 512, 768, 320), (1, 56, 8, 128, 300, 700, 200),
+               (1, 48, 6, 64, 256, 700, 256), (5, 8, 1, 128, 500, 500, 256), (1, 128, 32, 128, 64, 70, 96)]
+    crowded = len(shapes)
+    while len(shapes) < 300:
+        L, G, Hkv, d = rng.choice([1, 2, 5, 16]), rng.choice([1, 2, 3, 4, 7, 8]), rng.choice([1, 2, 4, 8, 16, 32]), rng.choice([64, 128])
+        c, rows = rng.randint(16, 600), rng.randint(1, 320)
+        shapes.append((L, G * Hkv, Hkv, d, c, rng.randint(c // 2, 2 * c), rows))
+    steps = in_child(merged_steps, tmp_path, shapes=shapes)
+    assert len(steps) >= 60 and all(list(shape) in [x[0] for x in steps] for shape in shapes[:crowded])
+    for shape, merged, attn, strips, n, held in steps:
+        L, Hkv = shape[0], shape[2]
+        assert merged == [attn[0] + strips[0]], shape
+        assert strips[0] == L * Hkv or strips[0] * n <= held, shape
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)
@@ -284,4 +336,4 @@ if __name__ == "__main__":
 
     body_ = globals()[sys.argv[2]]
     assert inspect.isfunction(body_)
-    print(json.dumps(body_(api_, Recorder(fake), **json.loads(sys.argv[3]))))
+    print(json.dumps(body_(api_, Recorder(fake, api_.binding._lib()), **json.loads(sys.argv[3]))))

@@ -23,6 +23,10 @@ CASES = [
     ("bf16", 1, 21, 3, 128, 150, 900, 200, 33, {}),             # eight strips of each of three units: over all XCDs
     ("bf16", 5, 20, 5, 64, 100, 700, 130, 40, {}),
     ("bf16", 16, 8, 4, 64, 98, 500, 65, 40, {}),                # 256 workgroups of the attention behind 192 of the score
+    ("bf16", 1, 128, 32, 128, 64, 300, 70, 96, {}),             # 384 strips of 32 rows would be more than the compute units: 64 rows each
+    ("bf16", 1, 64, 8, 128, 512, 2000, 768, 192, {}),           # the same, 1280 candidates
+    ("bf16", 33, 16, 4, 64, 32, 150, 60, 12, {}),               # one strip of 64 rows per unit, 48 of them there
+    ("bf16", 1, 48, 6, 64, 256, 1100, 700, 256, dict(position_shift=1)),
     ("f32", 1, 4, 1, 64, 32, 300, 64, 8, {}),
     ("f32", 2, 4, 2, 128, 60, 300, 125, 9, dict(start_size=2)),
     ("f32", 1, 2, 2, 64, 212, 900, 300, 30, dict(score_mode=api.SCORE_ACCUMULATED)),  # 512 candidates, 150 KB kept: gather apart

@@ -183,3 +183,17 @@ def test_document_loop_writes_only_what_it_owns(name):
     assert state.cache_len == state2.cache_len and state.buffer_index == state2.buffer_index
     ka, kb = state.current()[0], state2.current()[0]
     assert torch.equal(ka, kb)
+
+
+@pytest.mark.parametrize("L, Hq, Hkv, d, chunk, budget, n_i, shift",
+                         [(1, 64, 8, 128, 512, 768, 160, 0), (1, 64, 8, 128, 512, 768, 192, 0), (1, 40, 5, 128, 512, 768, 256, 0),
+                          (5, 8, 1, 128, 500, 500, 256, 1), (1, 48, 6, 64, 256, 700, 256, 0)])
+def test_columns_of_a_merged_step_stay_in_their_block(L, Hq, Hkv, d, chunk, budget, n_i, shift):
+    """A step in one launch whose strips of 32 instruction rows would be more than the compute units."""
+    print(f"merged step {L, Hq, Hkv, d, chunk, budget, n_i}", flush=True)
+    cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=d, chunk_len=chunk, budget=budget, instr_len=n_i, position_shift=shift)
+    T, dt, gw = 4 * chunk, torch.bfloat16, Guarded(cfg)
+    q, k, v = rand((1, L, Hq, T, d), dt, 1), rand((1, L, Hkv, T, d), dt, 2), rand((1, L, Hkv, T, d), dt, 3)
+    qi, out = rand((4, 1, L, Hq, n_i, d), dt, 4), torch.empty((1, L, Hq, T, d), dtype=dt, device=DEV)
+    api.citrus_process_document(cfg, api.DocumentState.allocate(cfg), gw.ws, doc=api.resident_doc(cfg, q, k, v, qi, out))
+    gw.check("merged step")
