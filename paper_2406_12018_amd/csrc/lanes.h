@@ -10,8 +10,9 @@
 namespace citrus {
 namespace {
 
-// What lane f(l) holds, f an exchange within rows of 16 lanes (each its own inverse).
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror8 = 0x141, kXor8 = 0x128;  // l ^ 1, l ^ 2, l ^ 7, l ^ 8
+// What lane f(l) holds, f a move within rows of 16 lanes.
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kXor7 = 0x141, kXor8 = 0x128;  // l ^ 1, l ^ 2, ...
+constexpr int kBack4 = 0x124;  // lane l - 4 of the row (its own inverse where lanes 8 apart hold the same)
 template <int F>
 __device__ __forceinline__ float from_lane(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), F, 0xf, 0xf, true));
@@ -32,10 +33,11 @@ __device__ __forceinline__ void both_of_halves(float v, float& a, float& b) {
   a = __int_as_float(r[0]);
   b = __int_as_float(r[1]);
 }
+// Sums grow in one order, lanes 16, 8, 4, 2 and 1 apart: which of two nearly equal scores is the larger one depends on it.
 // over the 16 lanes of a row
 __device__ __forceinline__ float row_sum(float v) {
   v += from_lane<kXor8>(v);
-  v += from_lane<kMirror8>(v);
+  v += from_lane<kBack4>(v);  // l ^ 4, or l ^ 12, which holds the same
   v += from_lane<kXor2>(v);
   return v + from_lane<kXor1>(v);
 }
@@ -56,7 +58,7 @@ __device__ __forceinline__ float reduce16_over32(const float (&v)[16], int col) 
 #pragma unroll
   for (int x = 0; x < 4; ++x) b[x] = (u8 ? a[x + 4] : a[x]) + from_lane<kXor8>(u8 ? a[x] : a[x + 4]);
 #pragma unroll
-  for (int x = 0; x < 2; ++x) c[x] = (u4 ? b[x + 2] : b[x]) + from_lane<kMirror8>(u4 ? b[x] : b[x + 2]);
+  for (int x = 0; x < 2; ++x) c[x] = (u4 ? b[x + 2] : b[x]) + from_lane<kXor3>(from_lane<kXor7>(u4 ? b[x] : b[x + 2]));
   const float d = (u2 ? c[1] : c[0]) + from_lane<kXor2>(u2 ? c[0] : c[1]);
   return d + from_lane<kXor1>(d);
 }
