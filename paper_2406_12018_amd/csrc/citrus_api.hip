@@ -671,6 +671,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const size_t units_sel = static_cast<size_t>(cfg->batch) * cfg->layers * sel_heads(cfg);
   // One-launch steps count a unit's workgroups here; the block is the one of modes whose chunks score themselves, which have no such steps.
+  // A launch leaves the counters zero; they are cleared in front of the first, and behind every provider that may enqueue work of its own.
   int32_t* const tickets = reinterpret_cast<int32_t*>(ws + wl.lse_chunk);
   bool tickets_clear = false;
 
@@ -772,6 +773,7 @@ int32_t citrus_process_document(const citrus_config* cfg, citrus_chunk_provider 
     const int32_t rc = next(user, first_chunk + done, hip_stream, &io);
     if (rc == 1) break;
     if (rc != 0) { status = CITRUS_ERR_PROVIDER; break; }
+    if (next != citrus_resident_provider) tickets_clear = false;  // what it has enqueued may have used the workspace
     const int c = io.chunk_len;
     if (c < 1 || c > cfg->chunk_len) { status = CITRUS_ERR_SHAPE; break; }
     if ((status = check_tensor(cfg, io.q, c, false)) != CITRUS_OK) break;

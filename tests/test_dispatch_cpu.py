@@ -329,6 +329,28 @@ def test_a_merged_step_takes_the_strips_of_the_score_alone(tmp_path):
         assert strips[0] == L * Hkv or strips[0] * n <= held, shape
 
 
+def one_launch_steps_of_a_provider(api, launches):
+    G, Hkv, d, c, k, rows = 4, 8, 128, 32, 40, 64
+    cfg = api.Config(batch=1, layers=1, q_heads=G * Hkv, kv_heads=Hkv, head_dim=d, chunk_len=c, budget=k, instr_len=rows)
+    q, kv, qi, cache = Fake(1, 1, G * Hkv, c, d), Fake(1, 1, Hkv, c, d), Fake(1, 1, G * Hkv, rows, d), lambda i: Fake(1, 1, Hkv, k, d, at=(4 + i) << 20)
+    state = api.DocumentState([cache(0), cache(1)], [cache(2), cache(3)])
+
+    def provider(i, io):
+        if i == 4:
+            return 1
+        io.q, io.out, io.q_instr, io.chunk_len = api.binding.tensor(q), api.binding.tensor(q), api.binding.tensor(qi), c
+        io.k, io.v = api.binding.tensor(kv), api.binding.tensor(kv)
+        return 0
+    calls = launches(lambda: api.citrus_process_document(cfg, state, workspace(api, cfg), provider=provider, stream=0))
+    return [x[0].split("<")[0] for x in calls if x[0] != "lds"]
+
+
+def test_counters_are_cleared_behind_a_provider(tmp_path):
+    """What a provider enqueues may use the call's workspace: the counters of a step are cleared behind it."""
+    step = ["clear_tickets_kernel", "attn_score_kernel"]
+    assert in_child(one_launch_steps_of_a_provider, tmp_path) == step[1:] + step * 3  # the first step keeps all: nothing is counted
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)

@@ -3,6 +3,7 @@ and several, both numbers of key tiles, the most candidates, first steps that ke
 bits as the launches apart, twice over one workspace; a second document of another size on it finds its counters as it needs them."""
 
 import pytest
+import torch
 
 import paper_2406_12018_amd as api
 from test_gpu_fused_launches import test_merged_launches_give_the_bits_of_the_launches_apart as same_bits
@@ -38,3 +39,34 @@ CASES = [
 def test_step_in_one_launch(case):
     same_bits(case)
     same_bits(case)
+
+
+def test_a_provider_that_uses_the_workspace():
+    """Behind the provider's own calls on the call's workspace a step finds its counters as it needs them."""
+    print("provider on the workspace", flush=True)
+    H, Hkv, d, c, budget, rows, steps = 16, 4, 128, 64, 100, 40, 5
+    cfg = api.Config(batch=1, layers=2, q_heads=H, kv_heads=Hkv, head_dim=d, chunk_len=c, budget=budget, instr_len=rows)
+    g = torch.Generator(device="cpu").manual_seed(4)
+    mk = lambda *shape: torch.randn(shape, generator=g).to(torch.bfloat16).to("cuda")
+    q, k, v, qi = mk(1, 2, H, steps * c, d), mk(1, 2, Hkv, steps * c, d), mk(1, 2, Hkv, steps * c, d), mk(steps, 1, 2, H, rows, d)
+    ws, runs = api.alloc_workspace(cfg), []
+    lm_score = torch.empty((1, 2, Hkv, c), dtype=torch.float32, device="cuda")
+    for used in (False, True):
+        out, state = torch.empty_like(q), api.DocumentState.allocate(cfg)
+        for t in (*state.k_cache, *state.v_cache):
+            t.zero_()
+
+        def provider(i, io):
+            if i == steps:
+                return 1
+            qc, kc, vc, oc = (t[:, :, :, i * c:(i + 1) * c] for t in (q, k, v, out))
+            if used:
+                api.citrus_chunk_attn(cfg, qc, None, None, 0, kc, vc, lm_score=lm_score, workspace=ws)
+            io.q, io.k, io.v, io.out = (api.binding.tensor(t) for t in (qc, kc, vc, oc))
+            io.q_instr, io.chunk_len = api.binding.tensor(qi[i]), c
+            return 0
+        assert api.citrus_process_document(cfg, state, ws, provider=provider) == steps
+        torch.cuda.synchronize()
+        runs.append([out, *(t.clone() for t in state.current())])
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
