@@ -575,7 +575,10 @@ __device__ __forceinline__ void attn_pipe_body(const AttnArgs& a, const int bloc
       const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= alpha;
       // the last P.V MFMAs of the previous step may still be in flight and the compiler cannot see them
-      wait_for_pinned_mfmas();
+      if constexpr (T::kOut == 4)
+        wait_for_pinned_mfmas(o_acc[0], o_acc[1], o_acc[2], o_acc[3]);
+      else
+        wait_for_pinned_mfmas(o_acc[0], o_acc[1]);
 #pragma unroll
       for (int r = 0; r < T::kOut; ++r)
 #pragma unroll

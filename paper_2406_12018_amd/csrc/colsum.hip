@@ -280,8 +280,14 @@ __global__ __launch_bounds__(64 * kRowShares * KG, 2) void colsum_mfma_kernel(Co
   };
   // Logits that the mask hides become -inf.  A row whose normaliser is NaN, or -inf, gives NaN to the keys it sees and
   // nothing to the others: the NaN moves from the normaliser into the visible logits.
+  auto wait_for_logits = [&](f32x16 (&s)[2][QT]) __attribute__((always_inline)) {
+    if constexpr (QT == 1)
+      wait_for_pinned_mfmas(s[0][0], s[1][0]);
+    else
+      wait_for_pinned_mfmas(s[0][0], s[0][1], s[1][0], s[1][1]);
+  };
   auto hide = [&](f32x16 (&s)[2][QT], int f) __attribute__((always_inline)) {
-    wait_for_pinned_mfmas();
+    wait_for_logits(s);
 #pragma unroll
     for (int y = 0; y < QT; ++y) {
       const bool known = lse_old[y] > -INFINITY;
@@ -372,7 +378,7 @@ __global__ __launch_bounds__(64 * kRowShares * KG, 2) void colsum_mfma_kernel(Co
     }
   }
   if (has_keys) {  // the weights of the last step
-    wait_for_pinned_mfmas();
+    wait_for_logits(s_t[1]);
     if (f_old >= 0) hide(s_t[1], f_old);
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)

@@ -23,9 +23,15 @@ __device__ inline f32x16 mfma_pinned_first(const bf16x8& a, const bf16x8& b) {  
                : "v"(__builtin_bit_cast(i32x4, a)), "v"(__builtin_bit_cast(i32x4, b)));
   return d;
 }
-// enough wait states for every MFMA issued through the pinned helpers above to have written its result
-__device__ inline void wait_for_pinned_mfmas() { asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory"); }
-
+// Enough wait states for every MFMA issued through the pinned helpers above to have written its result.  What is read behind the
+// wait passes through it: other arithmetic is not bound to volatile statements, and was scheduled ahead of them.
+template <typename... Results>
+__device__ inline void wait_for_pinned_mfmas(Results&... results) {
+  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  auto pass = [](f32x16& r) { asm volatile("" : "+v"(r)); };
+  (pass(results), ...);
+}
 
 // One LDS-direct load (64 lanes x 16 bytes of global memory to 1 KB of consecutive LDS) as asm: the compiler waits
 // for every such load it can see (vmcnt(0)) in front of the next LDS read that might alias it, i.e. a tile requested
