@@ -1387,14 +1387,21 @@ hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View ou
   if (workgroups(4) <= cus)
     return attn_pipe_launch<D, 4, false>(dm, q, ks, vs, false, out, lse, lse_cache, st, q_rope_pos0, rope_base);
   const bool mixed = attn_workgroups_mixed(dm, ks.c) < workgroups(8);
-  const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, blocks = mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8);
+  const int64_t blocks = mixed ? attn_workgroups_mixed(dm, ks.c) : workgroups(8);
   // Beyond that pairs keep the causal work even, and singles leave less of the chip idle in the last turn.  Turns are counted in
-  // blocks; where a block is left over pairs end unevenly.  us in pairs | single, 512 rows over 768 states of 32/8 heads: 5 layers
-  // 70.7 | 72.4, 9 123 | 104, 10 121 | 107, 12 124 | 118, 15 138 | 143, 17 186 | 166, 20 195 | 191, 24 221 | 240, 32 297 | 310, 33 329 |
-  // 319; 700 rows over 200 states, 12 layers 123 | 104; 32/32 heads, 1024 rows over 1024 states, 5 layers 180 | 165; head_dim 64,
-  // 16/8 heads, 333 rows over 500 states, 20 layers 83.7 | 52.5.
+  // blocks.  Pairs are formed within a head group; where a block is left over there pairs end unevenly, which counts as a turn
+  // unless all of them fit the chip side by side and leave little of it idle.  us in pairs | single, 512 rows over 768 states of 32/8
+  // heads: 5 layers 70.7 | 72.4, 9 123 | 104, 10 121 | 107, 12 124 | 118, 15 138 | 143, 17 186 | 166, 20 195 | 191, 24 221 | 240, 32
+  // 297 | 310, 33 329 | 319; 700 rows over 200 states, 12 layers 123 | 104; 32/32 heads, 1024 rows over 1024 states, 5 layers 180 | 165.  An odd
+  // number of row blocks: 64/8 heads, 300 rows over 700 states, 6 layers 92.0 | 76.7 (288 workgroups | 480), 17 layers 181 | 175; all side by
+  // side, 48/4 heads, 598 rows over 491 states, 3 layers 50.1 | 58.5 (180 | 348), 8/2 heads, 312 rows over 369 states, 32 layers
+  // 37.8 | 41.5 (192 | 320), but 32/8 heads, 1063 rows over 583 states, 2 layers 63.2 | 53.0 (144 | 272) and 32/4 heads, 263 rows over 188
+  // states, 8 layers 30.7 | 28.9 (160 | 288).  Over 216 shapes the choice is 0.2 % from the better one on average, at most 8 %.
   const auto turns = [](int64_t work, int64_t places) { return (work + places - 1) / places; };
-  const int64_t pairs_turns = blocks / units % 2 == 0 ? 2 * turns(blocks / 2, cus) : turns(blocks, cus) + 1;
+  const int64_t head_groups = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv * (mixed ? 1 : dm.G / task_shape(dm.G, 8).heads_per_block);
+  const int64_t pairs = (blocks / head_groups + 1) / 2 * head_groups;  // with the blocks that are left over
+  const bool side_by_side = pairs <= cus && 8 * pairs > 5 * cus;
+  const int64_t pairs_turns = blocks / head_groups % 2 == 0 ? 2 * turns(pairs, cus) : side_by_side ? 2 : turns(blocks, cus) + 1;
   auto launch = mixed ? attn_pipe_launch<D, 8, true> : attn_pipe_launch<D, 8, false>;
   bool paired = blocks > cus && pairs_turns <= turns(blocks, cus);
   if constexpr (D == 64) {

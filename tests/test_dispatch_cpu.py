@@ -351,6 +351,30 @@ def test_counters_are_cleared_behind_a_provider(tmp_path):
     assert in_child(one_launch_steps_of_a_provider, tmp_path) == step[1:] + step * 3  # the first step keeps all: nothing is counted
 
 
+def attention_grids(api, launches, shapes):
+    out = []
+    for L, Hq, Hkv, c in shapes:
+        cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=128, chunk_len=c, budget=c, instr_len=4)
+        q, kv = Fake(1, L, Hq, c, 128), Fake(1, L, Hkv, c, 128)
+        calls = launches(lambda: api.citrus_chunk_attn(cfg, q, kv, kv, c, kv, kv, out=q, stream=0))
+        out += [_product(x[1]) for x in calls if x[0].startswith("attn_pipe_kernel")]
+    return out
+
+
+def test_row_blocks_are_paired_where_pairs_take_no_more_turns(tmp_path):
+    """Pairs are formed within a group of heads: with an odd number of row blocks there, one is left over in each."""
+    grids = {(8, 32, 8, 512): 256,   # 8 row blocks a head group, 512 in all: pairs fill the chip once
+             (9, 32, 8, 512): 576,   # 288 pairs would take two turns of two, single blocks take three
+             (6, 64, 8, 300): 480,   # 5 row blocks of each of two head groups: 288 workgroups if they were paired
+             (17, 64, 8, 576): 2448, # 9 of two
+             (20, 64, 4, 161): 960,  # 3 of four
+             (3, 48, 4, 598): 180,   # 29 row blocks that mix heads: 14 pairs and one fit the chip side by side
+             (32, 8, 2, 312): 192,   # 5 row blocks
+             (2, 32, 8, 1063): 272,  # 17: 144 workgroups would leave too much of the chip idle
+             (2, 64, 8, 1063): 544}  # 17 of two head groups: 288
+    assert in_child(attention_grids, tmp_path, shapes=[list(s) for s in grids]) == list(grids.values())
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)
