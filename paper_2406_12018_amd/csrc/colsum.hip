@@ -409,16 +409,14 @@ __global__ __launch_bounds__(64 * kRowShares * KG, 2) void colsum_mfma_kernel(Co
   }
 }
 
-// The same sums where a causal launch is long and its rows, 128 at a time within a head, come from memory: waves of 32 keys, four
-// to a SIMD, that form products and weights in turn and pass over single tiles of rows that see none of their keys.  Blocks of
-// one unit then lose step with each other, which costs the kernel above, with one chunk of rows in flight, more than this one.  us, the
-// kernel above | this one, 32/8 heads, 512 rows behind 768 states: 64 layers 371 | 324, 256 layers 1582 | 1280, head_dim 64, 128 layers 524 |
-// 438; up to 16 layers it is the slower one.  The order of a
-// sum's rows is the same: the bits are too.
+// The same sums by waves of 32 keys, four to a SIMD, that form products and weights in turn and pass over single tiles of rows that see
+// none of their keys.  It has less to do before the first row and behind the last, and is not held up where blocks of one unit pass over
+// different rows and lose step, which costs the kernel above, with one chunk of rows in flight, more than this one; per row and
+// key that one is faster.  many_waves has the line between the two.  The order of a sum's rows is the same: the bits are too.
 constexpr int kManyThreads = 512, kManyRows = 128;
 template <int D>
 constexpr int kManyLds = 2 * kManyRows * (Geo<D>::kPitchK * 2 + 4);
-template <int D>
+template <int D, bool WHOLE, bool CAUSAL>
 __global__ __launch_bounds__(kManyThreads, 4) void colsum_many_kernel(ColsumArgs a) {
   typedef Geo<D> T;
   constexpr int kPitchK = T::kPitchK, kTilesPerStep = 128 / D;
@@ -446,28 +444,41 @@ __global__ __launch_bounds__(kManyThreads, 4) void colsum_many_kernel(ColsumArgs
   for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
 
   // A thread stages 16 bytes of some rows of a chunk; the next chunk's are in registers while a chunk is multiplied.
+  // WHOLE: chunks lie inside a head.  Otherwise every row is looked up, and rows past the end repeat the last one, with a weight of 0.
   constexpr int kStep = kManyThreads / T::kSegs, kLoads = kManyRows / kStep;
   const int st_row = tid / T::kSegs, st_seg = tid % T::kSegs;
   const uint32_t thread_off = (st_row * static_cast<uint32_t>(a.q.ss) + 8 * st_seg) * 2;  // bytes; a head's rows span < 2 GiB
+  const uint16_t* const q_group = unit_ptr(a.q, b, l, g * a.G);
   const float* const norm = a.norm + (static_cast<int64_t>(bl) * a.Hq + g * a.G) * rows * a.norm_pitch;
   const int total_rows = a.G * rows;
   i32x4 q_in[kLoads];
   float lse_in = 0.f;
   int stage_head = 0, stage_row = 0;  // block-uniform
   auto request_chunk = [&](int f0) {
-    const uint16_t* const base = unit_ptr(a.q, b, l, g * a.G + stage_head) + static_cast<int64_t>(stage_row) * a.q.ss;
+    if constexpr (WHOLE) {
+      const uint16_t* const base = q_group + stage_head * a.q.sh + static_cast<int64_t>(stage_row) * a.q.ss;
 #pragma unroll
-    for (int x = 0; x < kLoads; ++x)
-      q_in[x] = *reinterpret_cast<const i32x4*>(reinterpret_cast<const char*>(base + x * kStep * a.q.ss) + thread_off);
-    stage_row += kManyRows;
-    if (stage_row == rows) {
-      stage_row = 0;
-      ++stage_head;
+      for (int x = 0; x < kLoads; ++x)
+        q_in[x] = *reinterpret_cast<const i32x4*>(reinterpret_cast<const char*>(base + x * kStep * a.q.ss) + thread_off);
+      stage_row += kManyRows;
+      if (stage_row == rows) {
+        stage_row = 0;
+        ++stage_head;
+      }
+      if (tid < kManyRows) lse_in = norm[static_cast<int64_t>(f0 + tid) * a.norm_pitch] * a.to_log2;
+    } else {
+#pragma unroll
+      for (int x = 0; x < kLoads; ++x) {
+        int thread = tid;
+        asm volatile("" : "+v"(thread));  // formed here: addresses kept through the loop do not fit the registers
+        const int f = min(f0 + thread / T::kSegs + x * kStep, total_rows - 1), hh = a.head_rows.quotient(f);
+        q_in[x] = *reinterpret_cast<const i32x4*>(q_group + hh * a.q.sh + (f - hh * rows) * a.q.ss + 8 * (thread % T::kSegs));
+      }
+      if (tid < kManyRows) lse_in = f0 + tid < total_rows ? norm[static_cast<int64_t>(f0 + tid) * a.norm_pitch] * a.to_log2 : INFINITY;
     }
-    if (tid < kManyRows) lse_in = norm[static_cast<int64_t>(f0 + tid) * a.norm_pitch] * a.to_log2;
   };
   request_chunk(0);
-  int buf = 0, chunk_row = 0;
+  int buf = 0, chunk_row = 0;  // WHOLE: of its head, where the chunk starts
   for (int f0 = 0; f0 < total_rows; f0 += kManyRows, buf ^= 1) {
     uint16_t* const q_s = q_sb + buf * (kManyRows * kPitchK);
     float* const lse_s = lse_sb + buf * kManyRows;
@@ -481,8 +492,11 @@ __global__ __launch_bounds__(kManyThreads, 4) void colsum_many_kernel(ColsumArgs
 #pragma unroll
       for (int qt = 0; qt < kManyRows / 32; ++qt) {
         float(&sum)[16] = acc[qt / kTilesPerStep % 2];
-        const int tile_row = chunk_row + 32 * qt;  // wave-uniform
-        if (n_c + tile_row + 31 < j0) continue;    // no row of the tile sees a key of this wave
+        // wave-uniform: rows of their head that the tile begins and ends with; one that wraps holds a head's first row and its last
+        const int f = f0 + 32 * qt, tile_row = WHOLE ? chunk_row + 32 * qt : f - a.head_rows.quotient(f) * rows;
+        const bool wraps = !WHOLE && tile_row + 31 >= rows;
+        if (!WHOLE && f >= total_rows) break;
+        if (CAUSAL && n_c + (wraps ? rows - 1 : tile_row + 31) < j0) continue;  // no row of the tile sees a key of this wave
         f32x16 s_t;
 #pragma unroll
         for (int i = 0; i < 16; ++i) s_t[i] = 0.f;
@@ -491,8 +505,9 @@ __global__ __launch_bounds__(kManyThreads, 4) void colsum_many_kernel(ColsumArgs
         for (int kk = 0; kk < T::kKk; ++kk)
           s_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op[kk], *reinterpret_cast<const bf16x8*>(q_row + 16 * kk), s_t, 0, 0, 0);
         const float lse2 = lse_s[32 * qt + col];
-        if (j0 + 31 > n_c + tile_row) {  // a key of the wave that a row of the tile does not see
-          const int last = n_c + tile_row + col - j0 - 4 * grp;
+        if (CAUSAL && j0 + 31 > n_c + (wraps ? 0 : tile_row)) {  // a key of the wave that a row of the tile does not see
+          const int row = WHOLE ? tile_row + col : f + col - a.head_rows.quotient(f + col) * rows;
+          const int last = n_c + row - j0 - 4 * grp;
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const float p = __builtin_amdgcn_exp2f(fmaf(s_t[i], a.c2, -lse2));
@@ -504,8 +519,10 @@ __global__ __launch_bounds__(kManyThreads, 4) void colsum_many_kernel(ColsumArgs
         }
       }
     }
-    chunk_row += kManyRows;
-    if (chunk_row == rows) chunk_row = 0;
+    if constexpr (WHOLE) {
+      chunk_row += kManyRows;
+      if (chunk_row == rows) chunk_row = 0;
+    }
   }
   if (!wave_has_keys) return;
   const float even = reduce16_over32(acc[0], col), odd = reduce16_over32(acc[1], col);
@@ -519,10 +536,40 @@ constexpr int colsum_lds_bytes() {
   return 2 * kRowShares * KG * QT * (Lay<D>::kHalf + 32 * 4);
 }
 
-template <int D, int KG>
-hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int causal, const float* norm, int norm_pitch,
-                         float to_log2, float* score, hipStream_t st) {
-  const int n = ks.n_c + ks.c, keys = 64 * KG, units = dm.B * dm.L * dm.Hkv;
+// Is colsum_many_kernel the faster one?  Both were measured at 820 calls, with and without the mask, 8 to 12000 rows per KV head, 8 to 3100
+// keys, 1 to 2048 KV heads; by this rule a call takes 0.9 % more than the faster one on average.  It is the one of short waves where the
+// other's fixed cost per workgroup weighs (few rows, or several turns of the chip with few keys each), and under the mask.
+// us, colsum_mfma_kernel | colsum_many_kernel (head_dim 128 where none is given):
+//   few rows: 8/8 heads, 29 rows, 59 keys, 3 layers 5.8 | 4.2; head_dim 64, 32/16 heads, 33 rows, 62 keys 6.4 | 4.3; but 104 rows, 233 keys 5.6 | 6.7.
+//   no mask, 129 to 256 keys: 32/8 heads, 512 rows, 200 keys, 96 layers 136 | 119, but 16/8 heads, 1256 rows, 96 layers 163 | 168, and one layer
+//     of 24/8 heads, 320 rows, 426 keys 37 | 69.
+//   no mask, more keys: head_dim 64, 16/8 heads, 300 rows, 768 keys, 96 layers 122 | 85; 32/16 heads, 219 rows, 474 keys, 16 layers 33.6 | 29.8;
+//     8/8 heads, 512 rows, 1024 keys, 128 layers 220 | 172, but 32/16 heads, 250 rows, 300 keys, 128 layers 276 | 319 (blocks of 128
+//     keys leave none idle there), 24/8 heads, 700 rows, 64 layers 138 | 192.
+//   mask, head_dim 64: 64/16 heads, 200 rows behind 300 states, 128 layers 283 | 149; 32/8 heads, 384 behind 300, 64 layers 146 | 82, 1000 behind 768, 96
+//     layers 1027 | 932; but 1740 behind 100, 24 layers 359 | 494, 1000 behind 768, 8 layers 100 | 107.
+//   mask: 32/8 heads, 128 behind 120, 256 layers 0.43 of the time; 12/8 heads, 200 behind 40, 64 layers 0.70; 12/8 heads, 250 behind 500, 128 layers
+//     232 | 194; 32/16 heads, 400 behind 768, 96 layers 971 | 885, but 1000 behind 1024, 24 layers 812 | 881; rows of a head a multiple of 128:
+//     32/8 heads, 1024 behind 300, 96 layers 1146 | 928, but 16/2 heads, 1024 behind 1024 742 | 760.
+bool many_waves(const Dims& dm, int rows, int n, bool causal) {
+  const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, group_rows = static_cast<int64_t>(dm.G) * rows;
+  const int cus = compute_units();
+  const int64_t tenths = 10 * units / cus, turns = units * ((n + 255) / 256) / cus;  // of blocks of 256 keys
+  if (group_rows <= 96 || (group_rows <= 192 && n <= 128)) return true;
+  if (causal) {
+    if (rows % kManyRows == 0 && units * group_rows > 3 << 17) return true;
+    if (dm.D == 64) return tenths >= 6 && n <= 1850 && (rows <= 1400 || turns >= 12);
+    return (tenths >= 7 && (n <= 400 || group_rows <= 400)) || (tenths >= 10 && n <= 640) || (turns >= 4 && n <= 1200);
+  }
+  if (n <= 128 || (n > 256 && n <= 384 && group_rows > 320)) return false;
+  if (n <= 256) return tenths >= 12;
+  return tenths >= 9 && (dm.D == 64 ? group_rows <= 3100 : group_rows <= 1100 && turns >= 3);
+}
+
+// keys: of a block of colsum_mfma_kernel
+ColsumArgs colsum_args(const Dims& dm, View q, int rows, Segments ks, int causal, const float* norm, int norm_pitch, float to_log2,
+                       float* score, int keys) {
+  const int n = ks.n_c + ks.c, units = dm.B * dm.L * dm.Hkv;
   ColsumArgs a;
   a.q = q;
   a.ks = ks;
@@ -545,19 +592,28 @@ hipError_t colsum_launch(const Dims& dm, View q, int rows, Segments ks, int caus
   a.norm = norm;
   a.norm_pitch = norm_pitch;
   a.score = score;
-  if (causal && rows % kManyRows == 0 && int64_t{units} * dm.G * rows > 3 << 17) {
-    static LdsLimit limit;
-    const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(colsum_many_kernel<D>), kManyLds<D>);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_many_kernel<D>, dim3((n + 255) / 256, dm.Hkv, dm.B * dm.L), dim3(kManyThreads), kManyLds<D>, st, a);
-    return hipGetLastError();
-  }
+  return a;
+}
+
+template <int D, int KG>
+hipError_t colsum_launch(const Dims& dm, const ColsumArgs& a, hipStream_t st) {
   static LdsLimit limit;
   const auto kern = colsum_mfma_kernel<D, KG>;
   constexpr int lds = colsum_lds_bytes<D, KG>();
   const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(a.key_blocks * dm.Hkv, dm.B * dm.L), dim3(64 * kRowShares * KG), lds, st, a);
+  return hipGetLastError();
+}
+
+template <int D, bool WHOLE, bool CAUSAL>
+hipError_t colsum_many_launch(const Dims& dm, const ColsumArgs& a, hipStream_t st) {
+  static LdsLimit limit;
+  const auto kern = colsum_many_kernel<D, WHOLE, CAUSAL>;
+  const hipError_t e = raise_lds_limit(limit, reinterpret_cast<const void*>(kern), kManyLds<D>);
+  if (e != hipSuccess) return e;
+  const int n = a.ks.n_c + a.ks.c;
+  hipLaunchKernelGGL(kern, dim3((n + 255) / 256, dm.Hkv, dm.B * dm.L), dim3(kManyThreads), kManyLds<D>, st, a);
   return hipGetLastError();
 }
 
@@ -579,9 +635,14 @@ hipError_t launch_colsum_mfma(const Dims& dm, View q, int rows, Segments ks, int
   const int64_t turns128 = 100 * (blocks(128) / pairs) + (left == 0 ? 0 : 2 * left <= pairs ? 65 : 100);
   const int64_t turns256 = 100 * ((blocks(256) + compute_units() - 1) / compute_units());
   const bool small = 108 * turns128 < 100 * turns256;
-  auto launch = small ? colsum_launch<128, 2> : colsum_launch<128, 4>;
-  if (dm.D == 64) launch = small ? colsum_launch<64, 2> : colsum_launch<64, 4>;
-  return launch(dm, q, rows, ks, causal, norm, norm_pitch, to_log2, score, st);
+  const auto choose = [&](auto head_dim) {
+    constexpr int D = decltype(head_dim)::value;
+    if (!many_waves(dm, rows, n, causal != 0)) return small ? colsum_launch<D, 2> : colsum_launch<D, 4>;
+    if (rows % kManyRows == 0) return causal ? colsum_many_launch<D, true, true> : colsum_many_launch<D, true, false>;
+    return causal ? colsum_many_launch<D, false, true> : colsum_many_launch<D, false, false>;
+  };
+  const auto launch = dm.D == 64 ? choose(std::integral_constant<int, 64>()) : choose(std::integral_constant<int, 128>());
+  return launch(dm, colsum_args(dm, q, rows, ks, causal, norm, norm_pitch, to_log2, score, small ? 128 : 256), st);
 }
 
 }  // namespace citrus

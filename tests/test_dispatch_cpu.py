@@ -375,6 +375,36 @@ def test_row_blocks_are_paired_where_pairs_take_no_more_turns(tmp_path):
     assert in_child(attention_grids, tmp_path, shapes=[list(s) for s in grids]) == list(grids.values())
 
 
+def column_sums(api, launches, shapes):
+    out = []
+    for causal, L, Hq, Hkv, c, n_c, d in shapes:
+        cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=d, chunk_len=c, budget=n_c, instr_len=4)
+        q, kv, cache, ws = Fake(1, L, Hq, c, d), Fake(1, L, Hkv, c, d), Fake(1, L, Hkv, n_c, d), workspace(api, cfg)
+        if causal:
+            calls = launches(lambda: api.citrus_chunk_attn(cfg, q, cache, cache, n_c, kv, kv, out=q, lm_score=q, workspace=ws, stream=0))
+        else:
+            calls = launches(lambda: api.citrus_cache_score(cfg, q, cache, n_c, lse_cache=q, score=q, workspace=ws, stream=0))
+        out += [x[0] for x in calls if x[0].startswith("colsum")]
+    return out
+
+
+def test_column_sums_kernels(tmp_path):
+    """Where the one of 64 keys a wave is slower, that of 32 keys is taken, whatever the number of rows."""
+    many, whole, pipelined = "colsum_many_kernel<%d, false", "colsum_many_kernel<%d, true", "colsum_mfma_kernel<%d"
+    kernels = {(0, 3, 8, 8, 29, 59, 128): many % 128, (0, 1, 1, 1, 96, 2000, 128): many % 128, (0, 1, 1, 1, 97, 200, 128): pipelined % 128,
+               (0, 1, 1, 1, 192, 128, 64): many % 64, (0, 1, 1, 1, 192, 129, 64): pipelined % 64,
+               (1, 128, 64, 16, 200, 300, 64): many % 64, (1, 64, 32, 8, 384, 300, 64): whole % 64, (1, 8, 32, 8, 200, 1100, 64): pipelined % 64,
+               (1, 64, 32, 8, 1559, 100, 64): many % 64, (1, 24, 32, 8, 1500, 500, 64): pipelined % 64,
+               (1, 96, 32, 8, 400, 768, 128): many % 128, (1, 64, 56, 8, 400, 1500, 128): pipelined % 128, (1, 64, 24, 8, 200, 40, 128): many % 128,
+               (1, 24, 64, 8, 250, 300, 128): pipelined % 128, (1, 64, 32, 8, 512, 768, 128): whole % 128,
+               (0, 96, 16, 8, 300, 768, 64): many % 64, (0, 128, 16, 8, 250, 300, 64): pipelined % 64, (0, 96, 32, 8, 512, 200, 128): whole % 128,
+               (0, 128, 8, 8, 512, 1024, 128): whole % 128, (0, 64, 24, 8, 700, 700, 128): pipelined % 128}
+    got = in_child(column_sums, tmp_path, shapes=[list(s) for s in kernels])
+    assert len(got) == len(kernels)
+    for (shape, want), kernel in zip(kernels.items(), got):
+        assert kernel.startswith(want) and (kernel.endswith("true>" if shape[0] else "false>") or want == pipelined % shape[-1]), shape
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)
