@@ -1406,13 +1406,15 @@ hipError_t attn_launch(const Dims& dm, View q, Segments ks, Segments vs, View ou
   bool paired = blocks > cus && pairs_turns <= turns(blocks, cus);
   if constexpr (D == 64) {
     // Workgroups of four waves that leave the registers for three of them on a compute unit, one block (of half the size) each: taken
-    // where the pairs' last turn wastes more of the chip.  us, pairs | three to a compute unit, 512 rows over 768 states of 32/8
+    // in place of single blocks of eight waves (faster at 23 of 23 shapes: 16/8 heads, 641 rows over 231 states, 48 layers, pairs | single
+    // | three to a compute unit 199 | 208 | 166; 567 over 311, 11 layers 43.2 | 48.0 | 35.7), and where the pairs' last turn wastes more of
+    // the chip.  us, pairs | three to a compute unit, 512 rows over 768 states of 32/8
     // heads: 5 layers 52.5 | 49.4, 8 62.1 | 64, 9 109.9 | 71.9, 10 109 | 82, 12 109.7 | 94.3, 16 121 | 124, 32 235 | 235; 28/4
     // heads, 300 rows over 1000 states, 16 layers 135 | 97 (in 256 rows of a head at a time); 8/8 heads, 700 rows over 900 states,
     // 40 layers 213 | 154.
     const double of_pairs = static_cast<double>(blocks) / (pairs_turns * cus);
     const double of_three = static_cast<double>(workgroups(4)) / (turns(workgroups(4), 3 * cus) * 3 * cus);
-    if (blocks > cus && of_three > of_pairs + 0.05) {
+    if (blocks > cus && (!paired || of_three > of_pairs + 0.05)) {
       launch = attn_pipe_launch<64, 4, false, 3>;
       paired = false;
     }

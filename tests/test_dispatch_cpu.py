@@ -351,13 +351,13 @@ def test_counters_are_cleared_behind_a_provider(tmp_path):
     assert in_child(one_launch_steps_of_a_provider, tmp_path) == step[1:] + step * 3  # the first step keeps all: nothing is counted
 
 
-def attention_grids(api, launches, shapes):
+def attention_grids(api, launches, shapes, head_dim):
     out = []
     for L, Hq, Hkv, c in shapes:
-        cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=128, chunk_len=c, budget=c, instr_len=4)
-        q, kv = Fake(1, L, Hq, c, 128), Fake(1, L, Hkv, c, 128)
+        cfg = api.Config(batch=1, layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=head_dim, chunk_len=c, budget=c, instr_len=4)
+        q, kv = Fake(1, L, Hq, c, head_dim), Fake(1, L, Hkv, c, head_dim)
         calls = launches(lambda: api.citrus_chunk_attn(cfg, q, kv, kv, c, kv, kv, out=q, stream=0))
-        out += [_product(x[1]) for x in calls if x[0].startswith("attn_pipe_kernel")]
+        out += [[x[0], _product(x[1])] for x in calls if x[0].startswith("attn_pipe_kernel")]
     return out
 
 
@@ -372,7 +372,17 @@ def test_row_blocks_are_paired_where_pairs_take_no_more_turns(tmp_path):
              (32, 8, 2, 312): 192,   # 5 row blocks
              (2, 32, 8, 1063): 272,  # 17: 144 workgroups would leave too much of the chip idle
              (2, 64, 8, 1063): 544}  # 17 of two head groups: 288
-    assert in_child(attention_grids, tmp_path, shapes=[list(s) for s in grids]) == list(grids.values())
+    got = in_child(attention_grids, tmp_path, shapes=[list(s) for s in grids], head_dim=128)
+    assert [grid for _, grid in got] == list(grids.values())
+
+
+def test_single_row_blocks_of_head_dim_64_are_three_to_a_compute_unit(tmp_path):
+    """Beyond the compute units pairs of eight waves, or single blocks of four; never single blocks of eight."""
+    pairs, three = "attn_pipe_kernel<64, 8, false, 2>", "attn_pipe_kernel<64, 4, false, 3>"
+    launches = {(8, 32, 8, 512): [pairs, 256], (9, 32, 8, 512): [three, 1152],
+                (48, 16, 8, 641): [three, 4224],  # 2304 blocks of eight waves take nine turns, their pairs ten
+                (11, 16, 8, 567): [three, 792], (32, 8, 8, 256): [pairs, 256]}
+    assert in_child(attention_grids, tmp_path, shapes=[list(s) for s in launches], head_dim=64) == list(launches.values())
 
 
 def column_sums(api, launches, shapes):
