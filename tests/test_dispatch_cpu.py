@@ -415,6 +415,22 @@ def test_column_sums_kernels(tmp_path):
         assert kernel.startswith(want) and (kernel.endswith("true>" if shape[0] else "false>") or want == pipelined % shape[-1]), shape
 
 
+def f32_attention(api, launches, shapes):
+    out = []
+    for H, c, n_c, d in shapes:
+        cfg = api.Config(batch=1, layers=1, q_heads=H, kv_heads=H, head_dim=d, chunk_len=c, budget=n_c, instr_len=4, dtype=api.F32)
+        q, cache = Fake(1, 1, H, c, d), Fake(1, 1, H, n_c, d)
+        calls = launches(lambda: api.citrus_chunk_attn(cfg, q, cache, cache, n_c, q, q, out=q, stream=0))
+        out += [x[0] for x in calls if x[0] != "lds"]
+    return out
+
+
+def test_f32_waves_that_have_a_simd_each_keep_it(tmp_path):
+    """512 workgroups of two waves: as many waves as the chip has SIMDs."""
+    got = in_child(f32_attention, tmp_path, shapes=[[128, 55, 93, 128], [512, 10, 26, 128], [129, 55, 93, 128], [127, 55, 93, 128]])
+    assert got == ["attn_f32_apart_kernel<128, 2>"] * 2 + ["attn_f32_kernel<128, 2>", "attn_f32_kernel<128, 8>"]
+
+
 if __name__ == "__main__":
     fake = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)  # before anything that loads the real runtime
     sys.path.insert(0, ROOT)
