@@ -462,9 +462,12 @@ int32_t citrus_resident_provider(void* user, int32_t chunk_index, void* hip_stre
  *                 recorded event costs a few microseconds of stream time).  For
  *                 per-phase timing only.  Events between two steps keep their launches apart that are
  *                 merged otherwise (same results): 1 to 4 the chunk attention and the instruction
- *                 score of a small step in the single-cache modes, 3 and 6 a selection and its gather,
- *                 and 3, 4, 5 and 6 the evictions of DUAL's two caches, one launch behind the
- *                 instruction score.
+ *                 score of a small step in the single-cache modes, 5 and 6 these two and the step's
+ *                 eviction, 3 and 6 a selection and its gather, and 3, 4, 5 and 6 the evictions of
+ *                 DUAL's two caches, one launch behind the instruction score.  A step whose
+ *                 candidates all stay, and that carries no accumulated sums, forms no
+ *                 instruction scores unless 5 is asked for (bf16, single-cache modes, no side stream; in
+ *                 the f32 mode where the step is one launch): nothing reads them.
  * side            optional (NULL: every launch goes to hip_stream in the order a1 .. a4).  A second stream
  *                 of the same device and two events, all created by the caller.  In the single-cache
  *                 modes (INSTR, SHARED) a step then runs its instruction score first, and its selection

@@ -971,7 +971,7 @@ __global__ __launch_bounds__(WAVES * 64, PER_SIMD) void attn_pipe_kernel_rotq(At
 // instruction rows over 768 + 512 states: 22.4 + 9.2 us in two launches, 23.4 in one.
 // The eviction by those scores can be part of the launch too: the workgroup that is the last of its unit's strips to have
 // written its column selects and moves the unit's rows (into the other buffer, which nothing here reads).  No workgroup waits
-// for another one.  A document of such a layer, 7941 tokens, 525 -> 360 us; 8/4 heads, 43 rows and 86 instruction rows over 463 +
+// for another one.  A document of such a layer, 7941 tokens, 524 -> 385 us; 8/4 heads, 43 rows and 86 instruction rows over 463 +
 // 430 states, a step 24.3 -> 17.7.
 constexpr int kTailRows = 8;  // rows of a thread in flight: one workgroup moves all rows of a unit
 template <int TPW>
