@@ -536,34 +536,37 @@ constexpr int colsum_lds_bytes() {
   return 2 * kRowShares * KG * QT * (Lay<D>::kHalf + 32 * 4);
 }
 
-// Is colsum_many_kernel the faster one?  Both were measured at 820 calls, with and without the mask, 8 to 12000 rows per KV head, 8 to 3100
-// keys, 1 to 2048 KV heads; by this rule a call takes 0.9 % more than the faster one on average.  It is the one of short waves where the
-// other's fixed cost per workgroup weighs (few rows, or several turns of the chip with few keys each), and under the mask.
+// Is colsum_many_kernel the faster one?  Both were measured at 1220 calls, with and without the mask, 8 to 12000 rows per KV head, 8 to 4700
+// keys, 1 to 2048 KV heads; by this rule a call takes 1 % more than the faster one on average.  It is the one of short waves where the
+// other's fixed cost per workgroup weighs (few rows; several turns of the chip with few rows or keys each), and under the mask.
 // us, colsum_mfma_kernel | colsum_many_kernel (head_dim 128 where none is given):
 //   few rows: 8/8 heads, 29 rows, 59 keys, 3 layers 5.8 | 4.2; head_dim 64, 32/16 heads, 33 rows, 62 keys 6.4 | 4.3; but 104 rows, 233 keys 5.6 | 6.7.
 //   no mask, 129 to 256 keys: 32/8 heads, 512 rows, 200 keys, 96 layers 136 | 119, but 16/8 heads, 1256 rows, 96 layers 163 | 168, and one layer
 //     of 24/8 heads, 320 rows, 426 keys 37 | 69.
-//   no mask, more keys: head_dim 64, 16/8 heads, 300 rows, 768 keys, 96 layers 122 | 85; 32/16 heads, 219 rows, 474 keys, 16 layers 33.6 | 29.8;
+//   no mask, more keys: head_dim 64, 16/8 heads, 300 rows, 768 keys, 96 layers 122 | 85; 4/4 heads, 546 rows, 2000 keys, 48 layers 69 | 48;
 //     8/8 heads, 512 rows, 1024 keys, 128 layers 220 | 172, but 32/16 heads, 250 rows, 300 keys, 128 layers 276 | 319 (blocks of 128
 //     keys leave none idle there), 24/8 heads, 700 rows, 64 layers 138 | 192.
 //   mask, head_dim 64: 64/16 heads, 200 rows behind 300 states, 128 layers 283 | 149; 32/8 heads, 384 behind 300, 64 layers 146 | 82, 1000 behind 768, 96
-//     layers 1027 | 932; but 1740 behind 100, 24 layers 359 | 494, 1000 behind 768, 8 layers 100 | 107.
+//     layers 1027 | 932; 16/8 heads, 211 behind 2500, 24 layers 80 | 52; 4/2 heads, 275 behind 535, 64 layers 0.64 of the time; but 32/8 heads, 1740 behind 100, 24 layers 359 | 494, 1000 behind 768, 8
+//     layers 100 | 107.
 //   mask: 32/8 heads, 128 behind 120, 256 layers 0.43 of the time; 12/8 heads, 200 behind 40, 64 layers 0.70; 12/8 heads, 250 behind 500, 128 layers
 //     232 | 194; 32/16 heads, 400 behind 768, 96 layers 971 | 885, but 1000 behind 1024, 24 layers 812 | 881; rows of a head a multiple of 128:
 //     32/8 heads, 1024 behind 300, 96 layers 1146 | 928, but 16/2 heads, 1024 behind 1024 742 | 760.
 bool many_waves(const Dims& dm, int rows, int n, bool causal) {
   const int64_t units = static_cast<int64_t>(dm.B) * dm.L * dm.Hkv, group_rows = static_cast<int64_t>(dm.G) * rows;
   const int cus = compute_units();
-  const int64_t tenths = 10 * units / cus, turns = units * ((n + 255) / 256) / cus;  // of blocks of 256 keys
+  const int64_t tenths = 10 * units / cus, turn_tenths = 10 * units * ((n + 255) / 256) / cus;  // turns of blocks of 256 keys
+  const bool wide = dm.D == 128;
   if (group_rows <= 96 || (group_rows <= 192 && n <= 128)) return true;
+  const bool few_rows = turn_tenths >= 30 && group_rows <= (wide ? 1100 : 2700);
   if (causal) {
-    if (rows % kManyRows == 0 && units * group_rows > 3 << 17) return true;
-    if (dm.D == 64) return tenths >= 6 && n <= 1850 && (rows <= 1400 || turns >= 12);
-    return (tenths >= 7 && (n <= 400 || group_rows <= 400)) || (tenths >= 10 && n <= 640) || (turns >= 4 && n <= 1200);
+    if (few_rows || (rows % kManyRows == 0 && units * group_rows > 3 << 17)) return true;
+    if (wide) return (tenths >= 7 && (n <= 400 || group_rows <= 400)) || (tenths >= 10 && n <= 640) || (turn_tenths >= 40 && n <= 1200);
+    return (tenths >= 6 && n <= 1850 && rows <= 1400) || (turn_tenths >= 5 && n > 256 && group_rows <= 1600);
   }
   if (n <= 128 || (n > 256 && n <= 384 && group_rows > 320)) return false;
   if (n <= 256) return tenths >= 12;
-  return tenths >= 9 && (dm.D == 64 ? group_rows <= 3100 : group_rows <= 1100 && turns >= 3);
+  return few_rows || (!wide && ((tenths >= 9 && group_rows <= 3100) || (turn_tenths >= 8 && n > 384 && group_rows <= 800)));
 }
 
 // keys: of a block of colsum_mfma_kernel

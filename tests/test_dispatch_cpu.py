@@ -403,12 +403,14 @@ def test_column_sums_kernels(tmp_path):
     many, whole, pipelined = "colsum_many_kernel<%d, false", "colsum_many_kernel<%d, true", "colsum_mfma_kernel<%d"
     kernels = {(0, 3, 8, 8, 29, 59, 128): many % 128, (0, 1, 1, 1, 96, 2000, 128): many % 128, (0, 1, 1, 1, 97, 200, 128): pipelined % 128,
                (0, 1, 1, 1, 192, 128, 64): many % 64, (0, 1, 1, 1, 192, 129, 64): pipelined % 64,
-               (1, 128, 64, 16, 200, 300, 64): many % 64, (1, 64, 32, 8, 384, 300, 64): whole % 64, (1, 8, 32, 8, 200, 1100, 64): pipelined % 64,
-               (1, 64, 32, 8, 1559, 100, 64): many % 64, (1, 24, 32, 8, 1500, 500, 64): pipelined % 64,
+               (1, 128, 64, 16, 200, 300, 64): many % 64, (1, 64, 32, 8, 384, 300, 64): whole % 64, (1, 1, 32, 8, 200, 1100, 64): pipelined % 64,
+               (1, 96, 32, 8, 1400, 400, 64): many % 64, (1, 24, 32, 8, 1500, 500, 64): pipelined % 64, (1, 64, 4, 2, 275, 535, 64): many % 64,
                (1, 96, 32, 8, 400, 768, 128): many % 128, (1, 64, 56, 8, 400, 1500, 128): pipelined % 128, (1, 64, 24, 8, 200, 40, 128): many % 128,
                (1, 24, 64, 8, 250, 300, 128): pipelined % 128, (1, 64, 32, 8, 512, 768, 128): whole % 128,
                (0, 96, 16, 8, 300, 768, 64): many % 64, (0, 128, 16, 8, 250, 300, 64): pipelined % 64, (0, 96, 32, 8, 512, 200, 128): whole % 128,
-               (0, 128, 8, 8, 512, 1024, 128): whole % 128, (0, 64, 24, 8, 700, 700, 128): pipelined % 128}
+               (0, 128, 8, 8, 512, 1024, 128): whole % 128, (0, 64, 24, 8, 700, 700, 128): pipelined % 128,
+               (1, 24, 16, 8, 211, 2500, 64): many % 64, (0, 48, 4, 4, 546, 2000, 64): many % 64, (1, 1, 16, 8, 211, 2500, 64): pipelined % 64,
+               (1, 48, 4, 4, 148, 2500, 128): many % 128, (0, 48, 8, 4, 600, 2000, 128): pipelined % 128}
     got = in_child(column_sums, tmp_path, shapes=[list(s) for s in kernels])
     assert len(got) == len(kernels)
     for (shape, want), kernel in zip(kernels.items(), got):
